@@ -120,22 +120,31 @@ def _check(status: int, where: str):
         raise LxError(status, where)
 
 
+# Marshalling is on the critical path of the smallest calls (their kernels take a few microseconds
+# each), so it goes by plain integers: the argtypes above turn them into pointers, and the raw
+# stream handle is read without building a torch.cuda.Stream object (2.9 us -> 0.3 us per call).
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None or _get_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_get_device())
+
+
+_DTYPES = {torch.float32: LX_F32, torch.bfloat16: LX_BF16, torch.float16: LX_F16}
 
 
 def _dt(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return LX_F32
-    if t.dtype == torch.bfloat16:
-        return LX_BF16
-    if t.dtype == torch.float16:
-        return LX_F16
-    raise LxError(LX_ERR_UNSUPPORTED, f"dtype {t.dtype}")
+    dt = _DTYPES.get(t.dtype)
+    if dt is None:
+        raise LxError(LX_ERR_UNSUPPORTED, f"dtype {t.dtype}")
+    return dt
 
 
 class BlockList:
@@ -146,6 +155,7 @@ class BlockList:
         self.rows, self.cols, self.nnz_cap = rows, cols, nnz_cap
         self.row_ptr, self.col_idx = row_ptr, col_idx
         self.c = lx_blocklist(rows, cols, row_ptr.data_ptr(), col_idx.data_ptr(), nnz_cap)
+        self.ref = C.byref(self.c)   # made once: every call hands the same header over
 
 
 def lx_mask_compact(mask: torch.Tensor, transpose: bool = False, nnz_cap: int | None = None,
@@ -229,7 +239,7 @@ def lx_attn_combine_patterns(pool_r: BlockList, pool_c: BlockList | None, nblk: 
         out = (mk(), mk() if pool_c is not None else None)
     blr, blc = out
     _check(_lib.lx_attn_combine_patterns(
-        C.byref(pool_r.c), C.byref(pool_c.c) if pool_c is not None else None, P, nblk,
+        pool_r.ref, pool_c.ref if pool_c is not None else None, P, nblk,
         _ptr(head_pattern), Hm, _ptr(blr.row_ptr), _ptr(blr.col_idx),
         _ptr(blc.row_ptr) if blc is not None else None, _ptr(blc.col_idx) if blc is not None else None,
         max(cap, 1), _stream()), "lx_attn_combine_patterns")
@@ -267,7 +277,7 @@ def lx_ffn_gather_weight_blocks(W: torch.Tensor, bl: BlockList, blk_n: int, out=
     if compact is None:
         compact = BlockList(1, bl.nnz_cap, torch.empty(2, dtype=torch.int32, device=dev),
                             torch.empty(bl.nnz_cap, dtype=torch.int32, device=dev), bl.nnz_cap)
-    _check(_lib.lx_ffn_gather_weight_blocks(_dt(W), d, F, blk_n, _ptr(W), C.byref(bl.c), _ptr(out),
+    _check(_lib.lx_ffn_gather_weight_blocks(_dt(W), d, F, blk_n, _ptr(W), bl.ref, _ptr(out),
                                             _ptr(compact.row_ptr), _ptr(compact.col_idx), _stream()),
            "lx_ffn_gather_weight_blocks")
     return out, compact
@@ -282,7 +292,7 @@ def lx_sparse_ffn_bwd_workspace_bytes(dt, T, d, F, tile_t, blk_n, nnz_cap, have_
 
 
 def lx_sparse_ffn_split_workspace_bytes(dt, T, d, tile_t, bl: "BlockList") -> int:
-    return _lib.lx_sparse_ffn_split_workspace_bytes(dt, T, d, tile_t, C.byref(bl.c))
+    return _lib.lx_sparse_ffn_split_workspace_bytes(dt, T, d, tile_t, bl.ref)
 
 
 def lx_sparse_ffn_lora_fwd_workspace_bytes(T, d) -> int:
@@ -302,7 +312,7 @@ def lx_sparse_ffn_lora_fwd(X, W_up, A_pad, B_pad, W_down, bl: BlockList, Y, H_ac
         workspace = torch.empty(_lib.lx_sparse_ffn_lora_fwd_workspace_bytes(T, d), dtype=torch.uint8,
                                 device=X.device)
     _check(_lib.lx_sparse_ffn_lora_fwd(_dt(X), T, d, F, 64, 64, _ptr(X), _ptr(W_up), _ptr(A_pad),
-                                       _ptr(B_pad), _ptr(W_down), C.byref(bl.c), _ptr(Y), _ptr(H_act),
+                                       _ptr(B_pad), _ptr(W_down), bl.ref, _ptr(Y), _ptr(H_act),
                                        _ptr(U), _ptr(workspace), workspace.numel(), _stream()),
            "lx_sparse_ffn_lora_fwd")
 
@@ -316,7 +326,7 @@ def lx_sparse_ffn_lora_bwd(X, dY, H_act, U, W_up_t, W_down_t, A_pad, B_pad, bl: 
     assert dB.shape == (F, 64) and W_up_t.shape == (d, F) and W_down_t.shape == (F, d)
     _check(_lib.lx_sparse_ffn_lora_bwd(_dt(X), T, d, F, 64, 64, _ptr(X), _ptr(dY), _ptr(H_act), _ptr(U),
                                        _ptr(W_up_t), _ptr(W_down_t), _ptr(A_pad), _ptr(B_pad),
-                                       C.byref(bl.c), _ptr(dX), _ptr(dA), _ptr(dB), _ptr(workspace),
+                                       bl.ref, _ptr(dX), _ptr(dA), _ptr(dB), _ptr(workspace),
                                        workspace.numel(), _stream()), "lx_sparse_ffn_lora_bwd")
 
 
@@ -344,7 +354,7 @@ def lx_sparse_ffn_fwd(X, W_up, W_down, bl: BlockList, tile_t: int, blk_n: int, Y
     F = W_up.shape[0]
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(_lib.lx_sparse_ffn_fwd(_dt(X), T, d, F, tile_t, blk_n, _ptr(X), _ptr(W_up), _ptr(b_up),
-                                  _ptr(W_down), _ptr(b_down), C.byref(bl.c), _ptr(Y), _ptr(H_act),
+                                  _ptr(W_down), _ptr(b_down), bl.ref, _ptr(Y), _ptr(H_act),
                                   _ptr(workspace), ws_bytes, _stream()), "lx_sparse_ffn_fwd")
     return Y
 
@@ -356,7 +366,7 @@ def lx_sparse_ffn_bwd_dx(dY, H_act, W_up, W_down, bl: BlockList, tile_t: int, bl
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(_lib.lx_sparse_ffn_bwd_dx(_dt(dY), T, d, F, tile_t, blk_n, _ptr(dY), _ptr(H_act),
                                      _ptr(W_up), _ptr(W_down), _ptr(W_up_t), _ptr(W_down_t),
-                                     C.byref(bl.c), _ptr(dX), _ptr(workspace), ws_bytes, _stream()),
+                                     bl.ref, _ptr(dX), _ptr(workspace), ws_bytes, _stream()),
            "lx_sparse_ffn_bwd_dx")
     return dX
 
@@ -380,18 +390,24 @@ def lx_profile_end():
     return ms.value, n.value
 
 
-def _strides(t: torch.Tensor):
-    assert t.dim() == 4 and t.stride(3) == 1
-    return (_i64 * 3)(t.stride(0), t.stride(1), t.stride(2))
+_Strides3 = _i64 * 3
+
+
+def _strides(Q: torch.Tensor, *others: torch.Tensor):
+    """The first three element strides of Q, which the other tensors share with its shape."""
+    shape, st = Q.shape, Q.stride()
+    for t in others:
+        assert t.stride() == st and t.shape == shape
+    assert len(st) == 4 and st[3] == 1
+    return _Strides3(st[0], st[1], st[2])
 
 
 def lx_sparse_attn_fwd(Q, K, V, bl: BlockList, scale: float, causal: bool, O, LSE,
                        mask_batch: int = 1, head_active=None):
     B, Hh, S, D = Q.shape
-    for t in (K, V, O):
-        assert t.stride() == Q.stride() and t.shape == Q.shape
+    strides = _strides(Q, K, V, O)
     _check(_lib.lx_sparse_attn_fwd(_dt(Q), B, Hh, S, D, scale, int(causal), _ptr(Q), _ptr(K),
-                                   _ptr(V), _strides(Q), C.byref(bl.c), mask_batch,
+                                   _ptr(V), strides, bl.ref, mask_batch,
                                    _ptr(head_active), _ptr(O), _ptr(LSE), _stream()),
            "lx_sparse_attn_fwd")
     return O, LSE
@@ -401,12 +417,11 @@ def lx_sparse_attn_bwd_dx(Q, K, V, O, LSE, dO, bl_rows: BlockList, bl_cols: Bloc
                           scale: float, causal: bool, dQ, dK, dV, workspace, mask_batch: int = 1,
                           head_active=None):
     B, Hh, S, D = Q.shape
-    for t in (K, V, O, dO, dQ, dK, dV):
-        assert t.stride() == Q.stride() and t.shape == Q.shape
+    strides = _strides(Q, K, V, O, dO, dQ, dK, dV)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(_lib.lx_sparse_attn_bwd_dx(_dt(Q), B, Hh, S, D, scale, int(causal), _ptr(Q), _ptr(K),
-                                      _ptr(V), _ptr(O), _ptr(LSE), _ptr(dO), _strides(Q),
-                                      C.byref(bl_rows.c), C.byref(bl_cols.c), mask_batch,
+                                      _ptr(V), _ptr(O), _ptr(LSE), _ptr(dO), strides,
+                                      bl_rows.ref, bl_cols.ref, mask_batch,
                                       _ptr(head_active), _ptr(dQ), _ptr(dK), _ptr(dV),
                                       _ptr(workspace), ws_bytes, _stream()),
            "lx_sparse_attn_bwd_dx")
@@ -417,11 +432,10 @@ def lx_sparse_attn_bwd_dx_noalloc(Q, K, V, O, LSE, dO, bl_rows: BlockList, bl_co
                                   scale: float, causal: bool, dQ, dK, dV, mask_batch: int = 1,
                                   head_active=None):
     B, Hh, S, D = Q.shape
-    for t in (K, V, O, dO, dQ, dK, dV):
-        assert t.stride() == Q.stride() and t.shape == Q.shape
+    strides = _strides(Q, K, V, O, dO, dQ, dK, dV)
     _check(_lib.lx_sparse_attn_bwd_dx_noalloc(_dt(Q), B, Hh, S, D, scale, int(causal), _ptr(Q),
                                               _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(dO),
-                                              _strides(Q), C.byref(bl_rows.c), C.byref(bl_cols.c),
+                                              strides, bl_rows.ref, bl_cols.ref,
                                               mask_batch, _ptr(head_active), _ptr(dQ), _ptr(dK),
                                               _ptr(dV), _stream()),
            "lx_sparse_attn_bwd_dx_noalloc")
