@@ -1,8 +1,7 @@
-// fp32 sparse FFN kernels (Sec. VI-B neuron-centric tiled products), used for
-// the fp32 correctness configuration.  Plain LDS-tiled FMA kernels: on gfx950
-// the fp32 vector rate equals the fp32 matrix rate, so there is nothing to gain
-// from MFMA here and the straightforward tiling keeps fp32 rounding behaviour
-// easy to reason about (one fused multiply-add per term, ascending k).
+// fp32 sparse FFN kernels (Sec. VI-B neuron-centric tiled products), used for the fp32 correctness
+// configuration.  fp32 operands and accumulation throughout, on the 32x32x2 fp32 MFMA: its rate is
+// that of the vector unit, but an operand element is read once per 32 products instead of once per
+// one to two, and that is what the products are made of here.
 //
 // Two kernel shapes serve all four products:
 //   sdd: out block (i, j) = A_i [TT x K] . B_j [BN x K]^T for every listed
@@ -10,113 +9,207 @@
 //        stored activation sign.          (up-projection, dH)
 //   dsd: out tile  = sum over listed j of Act_ij [TT x BN] . B[:, j-block]^T
 //        (down-projection, dX), the contraction runs over active blocks only.
-#include "lx_dev.h"
-#include "lx_launch.h"
+//
+// The output tile of a workgroup is as small as a list block (32 or 64 tokens x 32 or 64 columns),
+// which fills the chip at the sizes this configuration runs at; its wavefronts share it by 32 x 32
+// quadrants and, beyond those, by ranges of the contraction index, whose partial sums are added
+// through LDS in a fixed order.  No two wavefronts of a range share an operand pair, so every
+// wavefront streams its own operands through its own two stages of LDS and the loop has no barrier.
+// The detour over LDS is for the loads: a lane's row is fixed by the MFMA's layout, and a load of 16
+// bytes from each of 32 rows occupies the CU's memory pipeline for 64 clocks where eight rows of 128
+// bytes take 16.
+// Measured at 512 tokens, 768 -> 3072 -> 768, 30 % of 32 x 32 blocks (460 blocks): 15-17 us per
+// product, of which 6 us are the MFMAs (0.73 GFLOP, at most two blocks per CU) and about 7 the launch
+// and the three dependent loads in front of the first operand; operands straight into registers 20-22,
+// 2 x 2 register tiles on the vector unit 48-52.
+#include "ffn_ring.h"
 
 namespace lx {
 
-constexpr int kF32Threads = 256;
-constexpr int kF32BK = 32;
+constexpr int kF32Batch = 32;      // contraction elements per step: a 128-byte row piece, sixteen MFMAs of depth two
+constexpr int kF32Stage = 64 * kF32Batch * 4;   // bytes of a stage: 32 token rows, 32 weight rows
+constexpr int kF32Stages = 2;
 
-// acc[a][b] += sum_k A[ty + 16a][k] * B[tx + 16b][k], k in [0, klen), klen % 32 == 0.
-template <int TM, int TN>
-__device__ __forceinline__ void gemm_nt_f32(const float* __restrict__ A, long long lda,
-                                            const float* __restrict__ B, long long ldb, int klen,
-                                            float (&acc)[TM / 16][TN / 16], float* As, float* Bs) {
-  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  constexpr int P = kF32BK + 1;
-  for (int k0 = 0; k0 < klen; k0 += kF32BK) {
-    for (int idx = tid; idx < (TM + TN) * 8; idx += kF32Threads) {
-      const int row = idx / 8, seg = idx % 8;
-      const float* src = row < TM ? A + (long long)row * lda : B + (long long)(row - TM) * ldb;
-      const float4 v = *reinterpret_cast<const float4*>(src + k0 + seg * 4);
-      float* dst = (row < TM ? As + row * P : Bs + (row - TM) * P) + seg * 4;
-      dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+// How the wavefronts of a workgroup with NQ quadrants share the work: KS ranges of the contraction
+// index per quadrant.
+template <int NQ>
+struct F32Split {
+  static constexpr int kRanges = NQ == 4 ? 2 : 4;
+  static constexpr int kWaves = NQ * kRanges;
+  static constexpr int kThreads = kWaves * kWave;
+};
+
+__device__ __forceinline__ f32x16 mfma32_f32(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// acc += W[32 rows] . A[32 rows]^T over n batches of 32 contraction elements; at(s, a, w) yields the
+// first element of batch s in row 0 of either operand, lda / ldw are the row strides.  `lds`: byte
+// address of this wavefront's stages.
+template <class At>
+__device__ __forceinline__ void mma_batches_f32(uint32_t lds, int n, long long lda, long long ldw, At at,
+                                                f32x16& acc) {
+  const int lane = threadIdx.x % kWave, r = lane % 32, h2 = lane / 32;
+  // instruction g of a stage brings rows 8g .. 8g+7 (g < 4: tokens), lane l slot l % 8 of row 8g + l/8
+  long long off[8];
+#pragma unroll
+  for (int g = 0; g < 8; ++g) {
+    const int row = 8 * g + lane / 8, seg = (lane % 8) ^ swz(row);
+    off[g] = (row % 32) * (g < 4 ? lda : ldw) + seg * 4;
+  }
+  auto issue = [&](int s) {
+    const float *a, *w;
+    at(s, a, w);
+    const uint32_t dst = lds + (s % kF32Stages) * kF32Stage;
+#pragma unroll
+    for (int g = 0; g < 8; ++g) dma16((g < 4 ? a : w) + off[g], dst + g * 1024);
+  };
+#pragma unroll
+  for (int p = 0; p < kF32Stages; ++p)
+    if (p < n) issue(p);
+  for (int s = 0; s < n; ++s) {
+    if (s + 1 < n) wait_vmcnt<8>(); else wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    const uint32_t st = lds + (s % kF32Stages) * kF32Stage;
+    f32x4 x[4], y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int slot = 2 * u + h2;
+      x[u] = __builtin_bit_cast(f32x4, lds_read16(st + r * 128 + ((slot ^ swz(r)) << 4)));
+      y[u] = __builtin_bit_cast(f32x4, lds_read16(st + (32 + r) * 128 + ((slot ^ swz(32 + r)) << 4)));
     }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < kF32BK; ++kk) {
-      float a[TM / 16], b[TN / 16];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read
+    if (s + kF32Stages < n) issue(s + kF32Stages);
 #pragma unroll
-      for (int i = 0; i < TM / 16; ++i) a[i] = As[(ty + 16 * i) * P + kk];
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int j = 0; j < TN / 16; ++j) b[j] = Bs[(tx + 16 * j) * P + kk];
-#pragma unroll
-      for (int i = 0; i < TM / 16; ++i)
-#pragma unroll
-        for (int j = 0; j < TN / 16; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+      for (int e = 0; e < 4; ++e) acc = mfma32_f32(y[u][e], x[u][e], acc);
   }
 }
 
+// Leaves the accumulators in LDS ([wave][16][lane] floats, over the stages) for folded_f32, which
+// adds group g of four accumulator elements over the KS ranges of a quadrant (wavefront = quadrant +
+// NQ * range), range 0 first.
+__device__ __forceinline__ void spill_f32(float* area, const f32x16& acc) {
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < 16; ++v) area[(wave * 16 + v) * kWave + lane] = acc[v];
+  __syncthreads();
+}
+template <int NQ, int KS>
+__device__ __forceinline__ f32x4 folded_f32(const float* area, int quadrant, int g) {
+  const int lane = threadIdx.x % kWave;
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < KS; ++k)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] += area[((quadrant + NQ * k) * 16 + 4 * g + e) * kWave + lane];
+  return s;
+}
+
 // MODE 0: out = max(acc + bias, 0).  MODE 1: out = gate > 0 ? acc : 0.
-template <int TT, int BN, int MODE>
-__global__ __launch_bounds__(kF32Threads) void ffn_sdd_f32(
+// Workgroup (token tile, list entry): the tile index is the fast one, so that the workgroups without
+// an entry come last in dispatch order.
+template <int TB, int MODE>
+__global__ __launch_bounds__(F32Split<TB * TB / 1024>::kThreads) void ffn_sdd_f32(
     const float* __restrict__ A, const float* __restrict__ W, const float* __restrict__ bias,
     const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int gt, int K, int nnz_cap,
     float* __restrict__ out_act, const float* __restrict__ gate_act) {
-  __shared__ float As[TT * (kF32BK + 1)];
-  __shared__ float Bs[BN * (kF32BK + 1)];
-  const int i = blockIdx.y;
+  constexpr int Q1 = TB / 32, NQ = Q1 * Q1, KS = F32Split<NQ>::kRanges;
+  __shared__ __attribute__((aligned(1024))) float stages[F32Split<NQ>::kWaves * kF32Stages * kF32Stage / 4];
+  const int i = blockIdx.x;
   // gt consecutive token tiles share row i / gt of the list; the activation blocks of a list
-  // row are stored as [entry][tile within the group]
+  // row are stored as [entry][tile within the row's group]
   const int rs = row_ptr[i / gt], n_i = row_ptr[i / gt + 1] - rs;
-  if ((int)blockIdx.x >= n_i) return;
-  const int lp = rs + blockIdx.x;
+  if ((int)blockIdx.y >= n_i) return;
+  const int lp = rs + blockIdx.y;
   if (lp >= nnz_cap) return;       // entries beyond the capacity of the list buffers are ignored
   const int j = col_idx[lp];
   const long long p = (long long)lp * gt + i % gt;
-  float acc[TT / 16][BN / 16] = {};
-  gemm_nt_f32<TT, BN>(A + (long long)i * TT * K, K, W + (long long)j * BN * K, K, K, acc, As, Bs);
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int quad = wave % NQ, range = wave / NQ;
+  const int t0 = 32 * (quad % Q1), n0 = 32 * (quad / Q1);      // this wavefront's quadrant
+  const int batches = K / kF32Batch;
+  const int b_lo = batches * range / KS, b_hi = batches * (range + 1) / KS;
+  const float* a0 = A + ((long long)i * TB + t0) * K + b_lo * kF32Batch;
+  const float* w0 = W + ((long long)j * TB + n0) * K + b_lo * kF32Batch;
+  f32x16 acc;
 #pragma unroll
-  for (int a = 0; a < TT / 16; ++a)
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  mma_batches_f32(lds_addr(stages) + wave * (kF32Stages * kF32Stage), b_hi - b_lo, K, K,
+                  [=](int s, const float*& a, const float*& w) {
+                    a = a0 + s * kF32Batch;
+                    w = w0 + s * kF32Batch;
+                  },
+                  acc);
+  spill_f32(stages, acc);
+  // accumulator group g: columns n0 + 8g + 4*(lane/32) .. +3 of token t0 + lane%32
 #pragma unroll
-    for (int b = 0; b < BN / 16; ++b) {
-      const int t = ty + 16 * a, n = tx + 16 * b;
-      const long long o = (long long)p * TT * BN + t * BN + n;
-      float v = acc[a][b];
-      if (MODE == 0) {
-        if (bias) v += bias[j * BN + n];
-        v = v > 0.f ? v : 0.f;
-      } else {
-        v = gate_act[o] > 0.f ? v : 0.f;
-      }
-      out_act[o] = v;
+  for (int g = range; g < 4; g += KS) {
+    f32x4 v = folded_f32<NQ, KS>(stages, quad, g);
+    const int t = t0 + lane % 32, n = n0 + 8 * g + 4 * (lane / 32);
+    const long long o = p * (TB * TB) + t * TB + n;
+    if (MODE == 0) {
+      if (bias) v += *reinterpret_cast<const f32x4*>(bias + j * TB + n);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+    } else {
+      const f32x4 gg = *reinterpret_cast<const f32x4*>(gate_act + o);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = gg[e] > 0.f ? v[e] : 0.f;
     }
+    *reinterpret_cast<f32x4*>(out_act + o) = v;
+  }
 }
 
-// out[i-tile, n0..n0+31] = sum_s act[p_s] [TT x BN] . W[n0.., j_s*BN ..]^T  (+ bias)
-template <int TT, int BN>
-__global__ __launch_bounds__(kF32Threads) void ffn_dsd_f32(
+// out[i-tile, n0..n0+31] = sum_s act[p_s] [TB x TB] . W[n0.., j_s*TB ..]^T  (+ bias).  The list
+// entries are dealt to the KS ranges in turn.
+template <int TB>
+__global__ __launch_bounds__(F32Split<TB / 32>::kThreads) void ffn_dsd_f32(
     const float* __restrict__ act, const float* __restrict__ W, long long ldw,
     const float* __restrict__ bias, const int* __restrict__ row_ptr,
     const int* __restrict__ col_idx, int gt, int ncols_out, int nnz_cap,
     float* __restrict__ out) {
-  constexpr int CT = 32;
-  __shared__ float As[TT * (kF32BK + 1)];
-  __shared__ float Bs[CT * (kF32BK + 1)];
-  const int i = blockIdx.y, n0 = blockIdx.x * CT;
+  constexpr int NQ = TB / 32, KS = F32Split<NQ>::kRanges;
+  __shared__ __attribute__((aligned(1024))) float stages[F32Split<NQ>::kWaves * kF32Stages * kF32Stage / 4];
+  const int i = blockIdx.y, n0 = blockIdx.x * 32;
   const int rs = row_ptr[i / gt], n_i = min(row_ptr[i / gt + 1], nnz_cap) - rs;
-  float acc[TT / 16][CT / 16] = {};
-  for (int s = 0; s < n_i; ++s) {
-    const int p = rs + s;
-    const int j = col_idx[p];
-    gemm_nt_f32<TT, CT>(act + ((long long)p * gt + i % gt) * TT * BN, BN, W + (long long)n0 * ldw + (long long)j * BN,
-                        ldw, BN, acc, As, Bs);
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int quad = wave % NQ, range = wave / NQ;
+  const int t0 = 32 * quad;
+  const float* a0 = act + t0 * TB;
+  const float* w0 = W + (long long)n0 * ldw;
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  // entries range, range + KS, ...; their columns are fetched 64 at a time, one per lane
+  for (int base = range; base < n_i; base += KS * kWave) {
+    const int mine = base + KS * lane;
+    const int col = mine < n_i ? col_idx[rs + mine] : 0;
+    const int cnt = min(kWave, (n_i - base + KS - 1) / KS);
+    constexpr int kPer = TB / kF32Batch;      // batches per entry
+    mma_batches_f32(lds_addr(stages) + wave * (kF32Stages * kF32Stage), cnt * kPer, TB, ldw,
+                    [&](int s, const float*& a, const float*& w) {
+                      const int e = s / kPer, h = (s % kPer) * kF32Batch;
+                      const long long p = (long long)(rs + base + KS * e) * gt + i % gt;
+                      const int j = __builtin_amdgcn_readlane(col, e);
+                      a = a0 + p * (TB * TB) + h;
+                      w = w0 + (long long)j * TB + h;
+                    },
+                    acc);
   }
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
+  spill_f32(stages, acc);
 #pragma unroll
-  for (int a = 0; a < TT / 16; ++a)
-#pragma unroll
-    for (int b = 0; b < CT / 16; ++b) {
-      const int t = i * TT + ty + 16 * a, n = n0 + tx + 16 * b;
-      out[(long long)t * ncols_out + n] = acc[a][b] + (bias ? bias[n] : 0.f);
-    }
+  for (int g = range; g < 4; g += KS) {
+    f32x4 v = folded_f32<NQ, KS>(stages, quad, g);
+    const int t = i * TB + t0 + lane % 32, n = n0 + 8 * g + 4 * (lane / 32);
+    if (bias) v += *reinterpret_cast<const f32x4*>(bias + n);
+    *reinterpret_cast<f32x4*>(out + (long long)t * ncols_out + n) = v;
+  }
 }
 
-template <int TT, int BN>
+template <int TB>
 static hipError_t launch_f32(int pass, int Tt, int gt, int Fb, int d, int F, const float* A, const float* W1,
                              const float* b1, const float* W2, const float* b2, const int* row_ptr,
                              const int* col_idx, int nnz_cap, float* act_out,
@@ -125,16 +218,16 @@ static hipError_t launch_f32(int pass, int Tt, int gt, int Fb, int d, int F, con
   {
     ProfScope ps(pass == 0 ? kKFfnUp : kKFfnDh, st);
     if (pass == 0)
-      hipLaunchKernelGGL((ffn_sdd_f32<TT, BN, 0>), dim3(Fb, Tt), dim3(kF32Threads), 0, st, A, W1,
+      hipLaunchKernelGGL((ffn_sdd_f32<TB, 0>), dim3(Tt, Fb), dim3(F32Split<TB * TB / 1024>::kThreads), 0, st, A, W1,
                          b1, row_ptr, col_idx, gt, d, nnz_cap, act_out, (const float*)nullptr);
     else
-      hipLaunchKernelGGL((ffn_sdd_f32<TT, BN, 1>), dim3(Fb, Tt), dim3(kF32Threads), 0, st, A, W1,
+      hipLaunchKernelGGL((ffn_sdd_f32<TB, 1>), dim3(Tt, Fb), dim3(F32Split<TB * TB / 1024>::kThreads), 0, st, A, W1,
                          (const float*)nullptr, row_ptr, col_idx, gt, d, nnz_cap, act_out, act_gate);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   ProfScope ps(pass == 0 ? kKFfnDown : kKFfnDx, st);
-  hipLaunchKernelGGL((ffn_dsd_f32<TT, BN>), dim3(d / 32, Tt), dim3(kF32Threads), 0, st,
+  hipLaunchKernelGGL(ffn_dsd_f32<TB>, dim3(d / 32, Tt), dim3(F32Split<TB / 32>::kThreads), 0, st,
                      (const float*)act_out, W2, (long long)F, b2, row_ptr, col_idx, gt, d, nnz_cap, out);
   return hipGetLastError();
 }
@@ -147,9 +240,9 @@ hipError_t launch_ffn_f32(int pass, int tile, int Tt, int gt, int Fb, int d, int
                           const int* row_ptr, const int* col_idx, int nnz_cap, float* act_out,
                           const float* act_gate, float* out, hipStream_t st) {
   if (tile == 32)
-    return launch_f32<32, 32>(pass, Tt, gt, Fb, d, F, A, W1, b1, W2, b2, row_ptr, col_idx, nnz_cap,
+    return launch_f32<32>(pass, Tt, gt, Fb, d, F, A, W1, b1, W2, b2, row_ptr, col_idx, nnz_cap,
                               act_out, act_gate, out, st);
-  return launch_f32<64, 64>(pass, Tt, gt, Fb, d, F, A, W1, b1, W2, b2, row_ptr, col_idx, nnz_cap,
+  return launch_f32<64>(pass, Tt, gt, Fb, d, F, A, W1, b1, W2, b2, row_ptr, col_idx, nnz_cap,
                             act_out, act_gate, out, st);
 }
 
