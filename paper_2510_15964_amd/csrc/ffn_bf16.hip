@@ -100,13 +100,12 @@ __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int r
   return false;
 }
 
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[kNI][2]) {
+template <int N>
+__device__ __forceinline__ void zero_acc(f32x16 (&acc)[N]) {
 #pragma unroll
-  for (int a = 0; a < kNI; ++a)
+  for (int b = 0; b < N; ++b)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
 }
 
 // MODE 0: out = bf16(max(acc + bias, 0));  MODE 1: out = gate > 0 ? bf16(acc) : 0;
@@ -115,102 +114,96 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[kNI][2]) {
 // tile) and W2 [F,64] (rows of the listed blocks): acc += A2_i W2_j^T, the low-rank branch
 // z = W x + B (A x) of Sec. II-C with A2 = X A^T computed beforehand and W2 = B, both padded to
 // rank 64.
-// NST: stages of the transfer ring.  Three stages leave room for one workgroup per CU, two for two:
-// the launcher takes two when the items are more than one but at most two per CU, so that all
-// of them are resident at once instead of running as a full round and a partly filled one.
-template <int DT, int MODE, bool LORA, int NST = kSddStages>
-__global__ __launch_bounds__(kThreads, NST == 2 ? 2 : 1) void ffn_sdd_bf16(
+// NE: list entries per workgroup (4, or 2 or 1 where that many would leave CUs without one), NST:
+// stages of the transfer ring; both chosen by launch_sdd_one.
+template <int DT, int MODE, bool LORA, int NE, int NST>
+__global__ __launch_bounds__(kThreads, OneStage<NE>::kElems * 2 * NST <= 81920 ? 2 : 1) void ffn_sdd_bf16(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
     const uint16_t* __restrict__ bias, const int* __restrict__ row_ptr,
     const int* __restrict__ col_idx, int rows, int gt, int K, int nnz_cap,
     uint16_t* __restrict__ out_act, const uint16_t* __restrict__ gate_act,
     const uint16_t* __restrict__ A2, const uint16_t* __restrict__ W2) {
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * kStageElems];
+  using St = OneStage<NE>;
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * St::kElems];
   int i, chunk;
-  if (!find_work(row_ptr, rows, gt, blockIdx.x, 4, nnz_cap, i, chunk)) return;
+  if (!find_work(row_ptr, rows, gt, blockIdx.x, NE, nnz_cap, i, chunk)) return;
   const int rs = row_ptr[i / gt], n_i = row_ptr[i / gt + 1] - rs;
-  const int first = chunk * 4;
+  const int first = chunk * NE;
   const int p0 = rs + first;
   if (p0 >= nnz_cap) return;       // entries beyond the capacity of the list buffers are ignored
-  const int nb = min(min(4, n_i - first), nnz_cap - p0);
+  const int nb = min(min(NE, n_i - first), nnz_cap - p0);
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
 
-  // per-instruction source pointers of this lane (K offset added per step)
-  const uint16_t* src[kIssues];
+  // per-instruction source pointers of this lane (K offset added per step): instruction 0 brings
+  // token rows, instruction 1 + e the rows of list entry e
+  const int row = 8 * wave + lane / 8;       // row within the 64 rows of an instruction group
+  const uint16_t* src[St::kIss];
 #pragma unroll
-  for (int u = 0; u < kIssues; ++u) {
-    const int g = wave + kFW * u, row = 8 * g + lane / 8;
-    const int seg = (lane % 8) ^ swz(row);
-    if (u < 8 / kFW) {
-      src[u] = A + ((long long)i * 64 + row) * K + seg * 8;
-    } else {
-      const int blk = g / 8 - 1, r = row - kRowsB - 64 * blk;
-      // blocks past the end of the list are filled from the first block (never used)
-      const int j = col_idx[p0 + (blk < nb ? blk : 0)];
-      src[u] = W + ((long long)j * 64 + r) * K + seg * 8;
-    }
+  for (int u = 0; u < St::kIss; ++u) {
+    const int seg = (lane % 8) ^ swz(64 * u + row);
+    // blocks past the end of the list are filled from the first block (never used)
+    const uint16_t* base = u == 0 ? A + ((long long)i * 64 + row) * K
+                                  : W + ((long long)col_idx[p0 + (u - 1 < nb ? u - 1 : 0)] * 64 + row) * K;
+    src[u] = base + seg * 8;
   }
   // the same for the low-rank step (rows of 64 elements), computed when that step is issued
   auto src2 = [&](int u) -> const uint16_t* {
-    const int g = wave + kFW * u, row = 8 * g + lane / 8;
-    const int seg = (lane % 8) ^ swz(row);
-    if (u < 8 / kFW) return A2 + ((long long)i * 64 + row) * 64 + seg * 8;
-    const int blk = g / 8 - 1, r = row - kRowsB - 64 * blk;
-    const int j = col_idx[p0 + (blk < nb ? blk : 0)];
-    return W2 + ((long long)j * 64 + r) * 64 + seg * 8;
+    const int seg = (lane % 8) ^ swz(64 * u + row);
+    if (u == 0) return A2 + ((long long)i * 64 + row) * 64 + seg * 8;
+    return W2 + ((long long)col_idx[p0 + (u - 1 < nb ? u - 1 : 0)] * 64 + row) * 64 + seg * 8;
   };
-  f32x16 acc[kNI][2];
+  f32x16 acc[St::kTI];
   zero_acc(acc);
-  const int blk_w = kNI * wave / 2;          // list entry (of the four) this wave works on
+  const int grp = wave % (2 * NE);            // group of 32 weight rows of this wave
+  const int ti0 = wave / (2 * NE);            // its first group of 32 tokens
+  const int blk_w = grp / 2;                  // list entry it belongs to
+  const bool wave_on = blk_w < nb && ti0 < 2;
   const int ksteps = K / kBK;
-  run_ring<DT, NST>(ksteps + (LORA ? 1 : 0), blk_w < nb, src, src2,
-                       [=](int s, long long& ob, long long& oa) {
-                         const bool alt = LORA && s == ksteps;
-                         ob = oa = alt ? 0 : (long long)s * kBK;
-                         return alt;
-                       },
-                       ring, acc);
-  if (blk_w >= nb) return;
+  run_ring<DT, NST, NE>(ksteps + (LORA ? 1 : 0), wave_on, src, src2,
+                        [=](int s, long long& ob, long long& oa) {
+                          const bool alt = LORA && s == ksteps;
+                          ob = oa = alt ? 0 : (long long)s * kBK;
+                          return alt;
+                        },
+                        ring, acc);
+  if (!wave_on) return;
 
   const int j = col_idx[p0 + blk_w];
   // compact activation block of (tile i, list entry): the entries of a list row are stored as
   // [entry][tile within the row's group of gt tiles]
   const long long p = (long long)rs * gt + (long long)(first + blk_w) * gt + i % gt;
   const int tl = lane % 32, nq = (lane / 32) * 4;
+  const int nh = grp % 2;                     // which 32 neurons of the block
 #pragma unroll
-  for (int ni = 0; ni < kNI; ++ni) {
-    const int nh = (kNI * wave + ni) % 2;    // which 32 neurons of the block
+  for (int ti = 0; ti < St::kTI; ++ti)
 #pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
+    for (int g = 0; g < 4; ++g) {
+      const int t = 32 * (ti0 + ti) + tl, n = 32 * nh + 8 * g + nq;
+      const long long o = p * 4096 + t * 64 + n;
+      float v[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int t = 32 * ti + tl, n = 32 * nh + 8 * g + nq;
-        const long long o = p * 4096 + t * 64 + n;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[ni][ti][4 * g + e];
-        if (MODE == 2) {
-        } else if (MODE == 0) {
-          if (bias) {
-            const uint2 bb = *reinterpret_cast<const uint2*>(bias + j * 64 + n);
-            v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
-            v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
-          }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-        } else {
-          const uint2 gg = *reinterpret_cast<const uint2*>(gate_act + o);
-          if (!(to_f32<DT>(gg.x & 0xFFFFu) > 0.f)) v[0] = 0.f;
-          if (!(to_f32<DT>(gg.x >> 16) > 0.f)) v[1] = 0.f;
-          if (!(to_f32<DT>(gg.y & 0xFFFFu) > 0.f)) v[2] = 0.f;
-          if (!(to_f32<DT>(gg.y >> 16) > 0.f)) v[3] = 0.f;
+      for (int e = 0; e < 4; ++e) v[e] = acc[ti][4 * g + e];
+      if (MODE == 2) {
+      } else if (MODE == 0) {
+        if (bias) {
+          const uint2 bb = *reinterpret_cast<const uint2*>(bias + j * 64 + n);
+          v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
+          v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
         }
-        uint2 ov;
-        ov.x = pack2<DT>(v[0], v[1]);
-        ov.y = pack2<DT>(v[2], v[3]);
-        *reinterpret_cast<uint2*>(out_act + o) = ov;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+      } else {
+        const uint2 gg = *reinterpret_cast<const uint2*>(gate_act + o);
+        if (!(to_f32<DT>(gg.x & 0xFFFFu) > 0.f)) v[0] = 0.f;
+        if (!(to_f32<DT>(gg.x >> 16) > 0.f)) v[1] = 0.f;
+        if (!(to_f32<DT>(gg.y & 0xFFFFu) > 0.f)) v[2] = 0.f;
+        if (!(to_f32<DT>(gg.y >> 16) > 0.f)) v[3] = 0.f;
       }
-  }
+      uint2 ov;
+      ov.x = pack2<DT>(v[0], v[1]);
+      ov.y = pack2<DT>(v[2], v[3]);
+      *reinterpret_cast<uint2*>(out_act + o) = ov;
+    }
 }
 
 // Which token tile the workgroups of grid row `slot` work on.  A workgroup of the dsd kernel
@@ -249,81 +242,77 @@ __device__ __forceinline__ int balanced_tile(const int* __restrict__ row_ptr, in
   return first + tile;
 }
 
-// out[i-tile rows, n0 .. n0+255] = sum_s act[p_s] [64 x 64] . W[n0.., j_s*64 ..]^T (+ bias)
+// out[i-tile rows, n0 .. n0 + 64*NE - 1] = sum_s act[p_s] [64 x 64] . W[n0.., j_s*64 ..]^T (+ bias)
 // LORA: one more step with the operands act2 [T,64] (the token tile's 64 x 64 block) and
 // W2 [ncols_out, 64]: out += act2_i W2[n0..]^T, the low-rank part (dZ B) A of the input gradient.
-template <int DT, bool LORA>
+// NE: groups of 64 output columns per workgroup, NST: ring stages (chosen by launch_dsd_one).
+template <int DT, bool LORA, int NE, int NST>
 __global__ __launch_bounds__(kThreads) void ffn_dsd_bf16(
     const uint16_t* __restrict__ act, const uint16_t* __restrict__ W, long long ldw,
     const uint16_t* __restrict__ bias, const int* __restrict__ row_ptr,
     const int* __restrict__ col_idx, int gt, int ncols_out, int nnz_cap,
     uint16_t* __restrict__ out, const uint16_t* __restrict__ act2,
     const uint16_t* __restrict__ W2, int tile0) {
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[kDsdStages * kStageElems];
+  using St = OneStage<NE>;
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * St::kElems];
   // the launch covers the token tiles tile0 .. tile0 + gridDim.y - 1
   const int i = balanced_tile(row_ptr, tile0, gridDim.y, gt, nnz_cap, blockIdx.y,
                               gridDim.x * gridDim.y <= 2 * kCUs, reinterpret_cast<int*>(ring));
-  const int n0 = blockIdx.x * kRowsA;
+  const int n0 = blockIdx.x * (64 * NE);
   const int rs = row_ptr[i / gt];
   const int n_i = min(row_ptr[i / gt + 1], nnz_cap) - rs;   // <= 0: nothing within the capacity
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const bool wave_on = n0 + 32 * kNI * wave < ncols_out;
+  const int grp = wave % (2 * NE);                          // group of 32 output columns of this wave
+  const int ti0 = wave / (2 * NE);                          // its first group of 32 tokens
+  const bool wave_on = n0 + 32 * grp < ncols_out && ti0 < 2;
 
-  const uint16_t* src[kIssues];
+  // instruction 0 brings the rows of a compact 64x64 activation block, 1 + e 64 rows of W
+  const int row = 8 * wave + lane / 8;
+  const uint16_t* src[St::kIss];
 #pragma unroll
-  for (int u = 0; u < kIssues; ++u) {
-    const int g = wave + kFW * u, row = 8 * g + lane / 8;
-    const int seg = (lane % 8) ^ swz(row);
-    if (u < 8 / kFW) {
-      src[u] = act + row * 64 + seg * 8;          // inside a compact 64x64 activation block
-    } else {
-      const int n = min(n0 + row - kRowsB, ncols_out - 1);   // rows past the edge: re-read the last
-      src[u] = W + (long long)n * ldw + seg * 8;
-    }
+  for (int u = 0; u < St::kIss; ++u) {
+    const int seg = (lane % 8) ^ swz(64 * u + row);
+    const int n = min(n0 + 64 * (u - 1) + row, ncols_out - 1);   // rows past the edge: re-read the last
+    src[u] = (u == 0 ? act + row * 64 : W + (long long)n * ldw) + seg * 8;
   }
   auto src2 = [&](int u) -> const uint16_t* {     // the low-rank step, computed when it is issued
-    const int g = wave + kFW * u, row = 8 * g + lane / 8;
-    const int seg = (lane % 8) ^ swz(row);
-    if (u < 8 / kFW) return act2 + ((long long)i * 64 + row) * 64 + seg * 8;
-    const int n = min(n0 + row - kRowsB, ncols_out - 1);
-    return W2 + (long long)n * 64 + seg * 8;
+    const int seg = (lane % 8) ^ swz(64 * u + row);
+    if (u == 0) return act2 + ((long long)i * 64 + row) * 64 + seg * 8;
+    return W2 + (long long)min(n0 + 64 * (u - 1) + row, ncols_out - 1) * 64 + seg * 8;
   };
-  f32x16 acc[kNI][2];
+  f32x16 acc[St::kTI];
   zero_acc(acc);
   const int lsteps = n_i > 0 ? n_i : 0;
-  run_ring<DT, kDsdStages>(lsteps + (LORA ? 1 : 0), wave_on, src, src2,
-               [&](int s, long long& ob, long long& oa) {
-                 const bool alt = LORA && s == lsteps;
-                 ob = alt ? 0 : ((long long)(rs + s) * gt + i % gt) * 4096;
-                 oa = alt ? 0 : (long long)col_idx[rs + s] * 64;
-                 return alt;
-               },
-                       ring, acc);
+  run_ring<DT, NST, NE>(lsteps + (LORA ? 1 : 0), wave_on, src, src2,
+                        [&](int s, long long& ob, long long& oa) {
+                          const bool alt = LORA && s == lsteps;
+                          ob = alt ? 0 : ((long long)(rs + s) * gt + i % gt) * 4096;
+                          oa = alt ? 0 : (long long)col_idx[rs + s] * 64;
+                          return alt;
+                        },
+                        ring, acc);
   if (!wave_on) return;
 
   const int tl = lane % 32, nq = (lane / 32) * 4;
 #pragma unroll
-  for (int ni = 0; ni < kNI; ++ni) {
+  for (int ti = 0; ti < St::kTI; ++ti)
 #pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
+    for (int g = 0; g < 4; ++g) {
+      const int t = i * 64 + 32 * (ti0 + ti) + tl;
+      const int n = n0 + 32 * grp + 8 * g + nq;
+      float v[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int t = i * 64 + 32 * ti + tl;
-        const int n = n0 + 32 * (kNI * wave + ni) + 8 * g + nq;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[ni][ti][4 * g + e];
-        if (bias) {
-          const uint2 bb = *reinterpret_cast<const uint2*>(bias + n);
-          v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
-          v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
-        }
-        uint2 ov;
-        ov.x = pack2<DT>(v[0], v[1]);
-        ov.y = pack2<DT>(v[2], v[3]);
-        *reinterpret_cast<uint2*>(out + (long long)t * ncols_out + n) = ov;
+      for (int e = 0; e < 4; ++e) v[e] = acc[ti][4 * g + e];
+      if (bias) {
+        const uint2 bb = *reinterpret_cast<const uint2*>(bias + n);
+        v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
+        v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
       }
-  }
+      uint2 ov;
+      ov.x = pack2<DT>(v[0], v[1]);
+      ov.y = pack2<DT>(v[2], v[3]);
+      *reinterpret_cast<uint2*>(out + (long long)t * ncols_out + n) = ov;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -613,9 +602,9 @@ __global__ __launch_bounds__(kThreads) void ffn_dsd_reduce(const float* __restri
 // pass 0 (forward):  A = X,  W1 = W_up [F,d],     W2 = W_down [d,F], act_out = H_act, out = Y
 // pass 1 (backward): A = dY, W1 = W_down_t [F,d], W2 = W_up_t [d,F], act_out = dZ_act,
 //                    act_gate = H_act, out = dX
-static dim3 sdd_grid(int Tt, int gt, int nnz_cap) {
-  // items <= nnz_cap / 4 + Tt; per XCD L = ceil(items / 8) of them in 8 * ceil(L / 8) slots
-  const long long items = ((long long)nnz_cap * gt + 3) / 4 + Tt;
+static dim3 sdd_grid(int Tt, int gt, int nnz_cap, int per) {
+  // items <= nnz_cap / per + Tt; per XCD L = ceil(items / 8) of them in 8 * ceil(L / 8) slots
+  const long long items = ((long long)nnz_cap * gt + per - 1) / per + (per > 1 ? Tt : 0);
   const int Lub = (int)((items + 7) / 8);
   return dim3(8 * 8 * ((Lub + 7) / 8));
 }
@@ -692,7 +681,7 @@ static void launch_sdd_multi(int pass, int Tt, int gt, int d, const uint16_t* A,
                              const uint16_t* b1, const int* row_ptr, const int* col_idx, int nnz_cap,
                              uint16_t* act_out, const uint16_t* act_gate, hipStream_t st) {
   const uint16_t* none = nullptr;
-  const dim3 g1 = sdd_grid(Tt / TT, gt / TT, nnz_cap);
+  const dim3 g1 = sdd_grid(Tt / TT, gt / TT, nnz_cap, 4);
   ProfScope ps(pass == 0 ? kKFfnUp : kKFfnDh, st);
   if (pass == 0)
     hipLaunchKernelGGL((ffn_sddn_bf16<DT, 0, false, TT>), g1, dim3(kThreads), 0, st, A, W1, b1, row_ptr,
@@ -701,31 +690,68 @@ static void launch_sdd_multi(int pass, int Tt, int gt, int d, const uint16_t* A,
     hipLaunchKernelGGL((ffn_sddn_bf16<DT, 1, false, TT>), g1, dim3(kThreads), 0, st, A, W1, none,
                        row_ptr, col_idx, Tt, gt, d, nnz_cap, act_out, act_gate, none, none);
 }
-// ... one token tile per workgroup
-template <int DT>
-static void launch_sdd_one(int pass, int Tt, int gt, int d, const uint16_t* A, const uint16_t* W1,
+// ... one token tile per workgroup.  NE list entries per workgroup: as many of 4, 2, 1 as still make
+// two workgroups for every three CUs.  A workgroup of fewer entries transfers more bytes per product
+// (16 KiB per 64 x 64 x 64 step with one entry, 12 with two, 10 with four), but a CU without a
+// workgroup transfers nothing: 192 tokens, 768 -> 3072, one list of 14 blocks (12 items of four
+// entries, 42 of one) took 15 us per product and takes 8.
+// The number of items is known on the device only; the estimate takes the list's capacity plus half a
+// ragged group per tile.  Measured at 4096 / 8192 tokens, 2048 -> 8192, a list per tile of 14 blocks
+// on average (250 / 500 items of four; us, by the items of the actual masks):
+//   4 entries, 3 stages, one workgroup per CU    31 up to one item per CU, else 50 / 72
+//   4 entries, 2 stages, two workgroups per CU   39-45 / 57 up to two items per CU, else 70
+//   2 entries, 3 stages, two workgroups per CU   34-36 / 66-70
+// so around one item of four per CU, where the estimate cannot tell the sides of the cliff apart, two
+// entries are taken.  Fewer items than CUs leave room for a ring that takes most of the LDS.
+static long long sdd_items(int Tt, int gt, int nnz_cap, int ne) {
+  return ((long long)nnz_cap * gt + ne - 1) / ne + (long long)Tt * (ne - 1) / (2 * ne);
+}
+template <int DT, int MODE, bool LORA>
+static void launch_sdd_one(int Tt, int gt, int d, const uint16_t* A, const uint16_t* W1,
                            const uint16_t* b1, const int* row_ptr, const int* col_idx, int nnz_cap,
-                           uint16_t* act_out, const uint16_t* act_gate, hipStream_t st) {
-  const dim3 g1 = sdd_grid(Tt, gt, nnz_cap);
-  const uint16_t* none = nullptr;
-  // more than one item per CU but at most two: two resident workgroups of two stages each
-  // (the item count is known on the device only; a list row of n entries makes ceil(n / 4) items,
-  // 3/8 of an item more than n / 4 on average, which is what the estimate adds per tile)
-  const long long items_est = ((long long)nnz_cap * gt + 3) / 4 + (3 * (long long)Tt + 7) / 8;
-  const bool two_resident = items_est > kCUs && items_est <= 2 * kCUs;
-  ProfScope ps(pass == 0 ? kKFfnUp : kKFfnDh, st);
-  if (pass == 0 && two_resident)
-    hipLaunchKernelGGL((ffn_sdd_bf16<DT, 0, false, 2>), g1, dim3(kThreads), 0, st, A, W1, b1, row_ptr,
-                       col_idx, Tt, gt, d, nnz_cap, act_out, none, none, none);
-  else if (pass == 0)
-    hipLaunchKernelGGL((ffn_sdd_bf16<DT, 0, false>), g1, dim3(kThreads), 0, st, A, W1, b1, row_ptr,
-                       col_idx, Tt, gt, d, nnz_cap, act_out, none, none, none);
-  else if (two_resident)
-    hipLaunchKernelGGL((ffn_sdd_bf16<DT, 1, false, 2>), g1, dim3(kThreads), 0, st, A, W1, none, row_ptr,
-                       col_idx, Tt, gt, d, nnz_cap, act_out, act_gate, none, none);
-  else
-    hipLaunchKernelGGL((ffn_sdd_bf16<DT, 1, false>), g1, dim3(kThreads), 0, st, A, W1, none, row_ptr,
-                       col_idx, Tt, gt, d, nnz_cap, act_out, act_gate, none, none);
+                           uint16_t* act_out, const uint16_t* act_gate, const uint16_t* A2,
+                           const uint16_t* W2, hipStream_t st) {
+#define LX_SDD(NE, NST)                                                                              \
+  hipLaunchKernelGGL((ffn_sdd_bf16<DT, MODE, LORA, NE, NST>), sdd_grid(Tt, gt, nnz_cap, NE), dim3(kThreads), \
+                     0, st, A, W1, b1, row_ptr, col_idx, Tt, gt, d, nnz_cap, act_out, act_gate, A2, W2)
+  const long long fill = kCUs * 2 / 3;
+  const long long n4 = sdd_items(Tt, gt, nnz_cap, 4), n2 = sdd_items(Tt, gt, nnz_cap, 2),
+                  n1 = sdd_items(Tt, gt, nnz_cap, 1);
+  if (n4 >= fill) {
+    if (n4 > kCUs * 31 / 32 && n4 <= kCUs * 5 / 4)
+      LX_SDD(2, 3);
+    else if (n4 > kCUs && n4 <= kCUs * 9 / 4)
+      LX_SDD(4, 2);
+    else
+      LX_SDD(4, kSddStages);
+  } else if (n2 >= fill) {
+    if (n2 > kCUs) LX_SDD(2, 3); else LX_SDD(2, 6);
+  } else {
+    if (n1 > kCUs) LX_SDD(1, 4); else LX_SDD(1, 8);
+  }
+#undef LX_SDD
+}
+// Second product, one token tile per workgroup: tiles tile0 .. tile0 + count - 1.  NE groups of 64
+// output columns per workgroup by the same rule as above; with one resident workgroup per CU the ring
+// takes most of the LDS.
+template <int DT, bool LORA>
+static void launch_dsd_one(int tile0, int count, int gt, int d, int F, const uint16_t* W2, const uint16_t* b2,
+                           const int* row_ptr, const int* col_idx, int nnz_cap, const uint16_t* act,
+                           uint16_t* out, const uint16_t* act2, const uint16_t* W2b, hipStream_t st) {
+#define LX_DSD(NE, NST)                                                                              \
+  hipLaunchKernelGGL((ffn_dsd_bf16<DT, LORA, NE, NST>), dim3((d + 64 * NE - 1) / (64 * NE), count),  \
+                     dim3(kThreads), 0, st, act, W2, (long long)F, b2, row_ptr, col_idx, gt, d, nnz_cap, out, \
+                     act2, W2b, tile0)
+  auto wgs = [&](int ne) { return (long long)((d + 64 * ne - 1) / (64 * ne)) * count; };
+  const long long fill = kCUs * 2 / 3;
+  if (wgs(4) >= fill) {
+    LX_DSD(4, kDsdStages);
+  } else if (wgs(2) >= fill) {
+    if (wgs(2) > kCUs) LX_DSD(2, 3); else LX_DSD(2, 6);
+  } else {
+    if (wgs(1) > kCUs) LX_DSD(1, 4); else LX_DSD(1, 8);
+  }
+#undef LX_DSD
 }
 
 // Second product of a pass for groups of TT token tiles.
@@ -772,9 +798,8 @@ static void launch_dsd_multi(int pass, int Tt, int gt, int d, int F, const uint1
                        act, W2, (long long)F, b2, row_ptr, col_idx, gt, d,
                        nnz_cap, out, none, none, groups * TT / 2, 0, chunks, 0, nopart);
   else if (left > 0)
-    hipLaunchKernelGGL((ffn_dsd_bf16<DT, false>), dim3(chunks, left), dim3(kThreads), 0, st,
-                       act, W2, (long long)F, b2, row_ptr, col_idx, gt, d,
-                       nnz_cap, out, none, none, groups * TT);
+    launch_dsd_one<DT, false>(groups * TT, left, gt, d, F, W2, b2, row_ptr, col_idx, nnz_cap, act, out,
+                              none, none, st);
 }
 
 template <int DT>
@@ -810,7 +835,15 @@ static hipError_t launch_ffn_bf16_t(int pass, int Tt, int gt, int Fb, int d, int
   else if (tts == 2)
     launch_sdd_multi<DT, 2>(pass, Tt, gt, d, A, W1, b1, row_ptr, col_idx, nnz_cap, act_out, act_gate, st);
   else
-    launch_sdd_one<DT>(pass, Tt, gt, d, A, W1, b1, row_ptr, col_idx, nnz_cap, act_out, act_gate, st);
+  {
+    ProfScope ps(pass == 0 ? kKFfnUp : kKFfnDh, st);
+    const uint16_t* none = nullptr;
+    if (pass == 0)
+      launch_sdd_one<DT, 0, false>(Tt, gt, d, A, W1, b1, row_ptr, col_idx, nnz_cap, act_out, none, none, none, st);
+    else
+      launch_sdd_one<DT, 1, false>(Tt, gt, d, A, W1, none, row_ptr, col_idx, nnz_cap, act_out, act_gate, none,
+                                   none, st);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (tt == 4) {
@@ -822,9 +855,7 @@ static hipError_t launch_ffn_bf16_t(int pass, int Tt, int gt, int Fb, int d, int
   } else {
     const uint16_t* none = nullptr;
     ProfScope ps(pass == 0 ? kKFfnDown : kKFfnDx, st);
-    hipLaunchKernelGGL((ffn_dsd_bf16<DT, false>), dim3((d + kRowsA - 1) / kRowsA, Tt), dim3(kThreads), 0, st,
-                       (const uint16_t*)act_out, W2, (long long)F, b2, row_ptr, col_idx, gt, d, nnz_cap,
-                       out, none, none, 0);
+    launch_dsd_one<DT, false>(0, Tt, gt, d, F, W2, b2, row_ptr, col_idx, nnz_cap, act_out, out, none, none, st);
   }
   return hipGetLastError();
 }
@@ -854,16 +885,12 @@ static hipError_t launch_ffn_lora_fwd_bf16_t(int Tt, int gt, int d, int F, const
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKFfnUp, st);
-    hipLaunchKernelGGL((ffn_sdd_bf16<DT, 0, true>), sdd_grid(Tt, gt, nnz_cap), dim3(kThreads), 0, st, X,
-                       W_up, none, row_ptr, col_idx, Tt, gt, d, nnz_cap, H_act, none,
-                       (const uint16_t*)U, B_pad);
+    launch_sdd_one<DT, 0, true>(Tt, gt, d, X, W_up, none, row_ptr, col_idx, nnz_cap, H_act, none, U, B_pad, st);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   ProfScope ps(kKFfnDown, st);
-  hipLaunchKernelGGL((ffn_dsd_bf16<DT, false>), dim3((d + kRowsA - 1) / kRowsA, Tt), dim3(kThreads), 0, st,
-                     (const uint16_t*)H_act, W_down, (long long)F, none, row_ptr, col_idx, gt, d,
-                     nnz_cap, Y, none, none, 0);
+  launch_dsd_one<DT, false>(0, Tt, gt, d, F, W_down, none, row_ptr, col_idx, nnz_cap, H_act, Y, none, none, st);
   return hipGetLastError();
 }
 
@@ -884,8 +911,8 @@ static hipError_t launch_ffn_lora_bwd_bf16_t(int Tt, int gt, int d, int F, const
   const uint16_t* none = nullptr;
   {
     ProfScope ps(kKFfnDh, st);
-    hipLaunchKernelGGL((ffn_sdd_bf16<DT, 1, false>), sdd_grid(Tt, gt, nnz_cap), dim3(kThreads), 0, st, dY,
-                       W_down_t, none, row_ptr, col_idx, Tt, gt, d, nnz_cap, dZ, H_act, none, none);
+    launch_sdd_one<DT, 1, false>(Tt, gt, d, dY, W_down_t, none, row_ptr, col_idx, nnz_cap, dZ, H_act, none, none,
+                                 st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -900,9 +927,7 @@ static hipError_t launch_ffn_lora_bwd_bf16_t(int Tt, int gt, int d, int F, const
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKFfnDx, st);
-    hipLaunchKernelGGL((ffn_dsd_bf16<DT, true>), dim3((d + kRowsA - 1) / kRowsA, Tt), dim3(kThreads), 0, st,
-                       (const uint16_t*)dZ, W_up_t, (long long)F, none, row_ptr, col_idx, gt, d,
-                       nnz_cap, dX, (const uint16_t*)G, (const uint16_t*)A_t, 0);
+    launch_dsd_one<DT, true>(0, Tt, gt, d, F, W_up_t, none, row_ptr, col_idx, nnz_cap, dZ, dX, G, A_t, st);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;

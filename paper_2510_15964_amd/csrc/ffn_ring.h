@@ -13,22 +13,29 @@
 namespace lx {
 
 constexpr int kFW = 8;             // wavefronts per workgroup
-constexpr int kNI = 8 / kFW;       // 32-row groups of the 256 weight rows per wavefront
 constexpr int kThreads = kFW * kWave;
 constexpr int kBK = 64;            // K-chunk per step: 64 bf16 = 128 bytes per row
 constexpr int kRowsB = 64;         // shared operand (token rows)
-constexpr int kRowsA = 256;        // per-wave operand (4 x 64 weight rows)
-constexpr int kStageRows = kRowsA + kRowsB;
-constexpr int kStageElems = kStageRows * kBK;                 // 20480 elements = 40 KiB
-constexpr int kIssues = kStageRows / 8 / (kThreads / kWave);  // DMA instructions per wave per stage
-// Ring depths.  Measured on the 11 %-dense FFN of the benchmark: a fourth stage (all 160 KiB of
-// LDS) does not help the sdd kernels, and the dsd kernel is faster with two resident
+constexpr int kRowsA = 256;        // per-wave operand (4 x 64 weight rows) of the widest stage
+// A stage of the one-tile kernels: 64 token rows and 64 * NE weight rows (NE = 1, 2 or 4 list blocks,
+// or groups of 64 output columns).  Wavefront w multiplies the 32 weight rows of group w % (2 * NE)
+// with kTI groups of 32 token rows, from group w / (2 * NE) on: all of them with NE = 4, one with NE = 2
+// and NE = 1, where four of the eight wavefronts only transfer.  (Sharing K between those instead
+// would change the order of the sums.)
+template <int NE>
+struct OneStage {
+  static constexpr int kElems = (kRowsB + 64 * NE) * kBK;      // 16 / 24 / 40 KiB
+  static constexpr int kIss = 1 + NE;                          // DMA instructions per wave and stage
+  static constexpr int kTI = NE == 4 ? 2 : 1;
+};
+// Ring depths for NE = 4.  Measured on the 11 %-dense FFN of the benchmark: a fourth stage (all 160
+// KiB of LDS) does not help the sdd kernels, and the dsd kernel is faster with two resident
 // workgroups of two stages each than with one workgroup of three or four.
 constexpr int kSddStages = 3, kDsdStages = 2;
 
 __device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
 
-// One stage = NISS DMA instructions per wave (kIssues for the 64 + 256 rows of the FFN kernels).
+// One stage = NISS DMA instructions per wave (1 + NE for the 64 + 64 * NE rows of the one-tile FFN kernels).
 // Instruction u of wave w fills stage rows 8g .. 8g+7 with g = w + kFW*u (g < 8: the 64 shared
 // rows, then the weight blocks); lane l brings the 16-byte slot l%8 of row 8g + l/8.  src[u]
 // already points at this lane's (row, swizzled segment); offB / offA are the element offsets of
@@ -55,27 +62,25 @@ struct NoAlt {
   __device__ __forceinline__ const uint16_t* operator()(int) const { return nullptr; }
 };
 
-// One 64-deep K-step from LDS: wave w multiplies its 32*kNI weight rows (row groups kNI*w ..)
-// with the 64 shared rows.  acc[ni][ti]: rows = weight rows 32*(kNI*w + ni).., columns = shared
-// rows 32ti..
-template <int DT>
-__device__ __forceinline__ void mma_step(const uint16_t* stage, int wave, f32x16 (&acc)[kNI][2]) {
+// One 64-deep K-step from LDS: acc[x] += group grp of 32 weight rows . groups ti0 + x of 32 token rows.
+// acc[x]: rows = weight rows, columns = token rows.
+template <int DT, int NE>
+__device__ __forceinline__ void mma_step(const uint16_t* stage, int grp, int ti0,
+                                         f32x16 (&acc)[OneStage<NE>::kTI]) {
+  constexpr int TI = OneStage<NE>::kTI;
   const int lane = threadIdx.x % kWave;
   const int r = lane % 32, h2 = lane / 32;
+  const int ra = kRowsB + 32 * grp + r;
   // all operand reads of the step are issued first, so that their LDS latency overlaps the
   // MFMAs instead of being paid once per k16 slice
-  uint4 a[4][kNI], b[4][2];
+  uint4 a[4], b[4][TI];
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     const int seg = 2 * kk + h2;
+    a[kk] = *reinterpret_cast<const uint4*>(stage + ra * kBK + ((seg ^ swz(ra)) << 3));
 #pragma unroll
-    for (int ni = 0; ni < kNI; ++ni) {
-      const int ra = kRowsB + 32 * (kNI * wave + ni) + r;
-      a[kk][ni] = *reinterpret_cast<const uint4*>(stage + ra * kBK + ((seg ^ swz(ra)) << 3));
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int rb = 32 * h + r;
+    for (int h = 0; h < TI; ++h) {
+      const int rb = 32 * (ti0 + h) + r;
       b[kk][h] = *reinterpret_cast<const uint4*>(stage + rb * kBK + ((seg ^ swz(rb)) << 3));
     }
   }
@@ -83,9 +88,7 @@ __device__ __forceinline__ void mma_step(const uint16_t* stage, int wave, f32x16
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-    for (int ni = 0; ni < kNI; ++ni)
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti) acc[ni][ti] = mfma32<DT>(a[kk][ni], b[kk][ti], acc[ni][ti]);
+    for (int ti = 0; ti < TI; ++ti) acc[ti] = mfma32<DT>(a[kk], b[kk][ti], acc[ti]);
 }
 
 // The same for a stage of 64*TT shared rows (TT = 2 or 4 token tiles) + 256 weight rows and a
@@ -182,15 +185,15 @@ __device__ __forceinline__ void run_ring_of(int nsteps, const uint16_t* const (&
   }
 }
 
-template <int DT, int NST, class AltPtr, class Offs>
+template <int DT, int NST, int NE, class AltPtr, class Offs>
 __device__ __forceinline__ void run_ring(int nsteps, bool wave_on,
-                                         const uint16_t* const (&src)[kIssues], AltPtr alt_ptr,
-                                         Offs offs, uint16_t* ring, f32x16 (&acc)[kNI][2]) {
+                                         const uint16_t* const (&src)[OneStage<NE>::kIss], AltPtr alt_ptr,
+                                         Offs offs, uint16_t* ring, f32x16 (&acc)[OneStage<NE>::kTI]) {
   const int wave = threadIdx.x / kWave;
-  run_ring_of<NST, kIssues, kStageElems>(nsteps, src, alt_ptr, offs, ring,
-                                         [&](const uint16_t* stage) {
-                                           if (wave_on) mma_step<DT>(stage, wave, acc);
-                                         });
+  run_ring_of<NST, OneStage<NE>::kIss, OneStage<NE>::kElems>(
+      nsteps, src, alt_ptr, offs, ring, [&](const uint16_t* stage) {
+        if (wave_on) mma_step<DT, NE>(stage, wave % (2 * NE), wave / (2 * NE), acc);
+      });
 }
 
 // Host side: calls fn<kF16> or fn<kBf16> according to the run-time element type `dt`.
