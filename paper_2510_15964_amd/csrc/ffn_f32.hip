@@ -21,7 +21,9 @@
 // Measured at 512 tokens, 768 -> 3072 -> 768, 30 % of 32 x 32 blocks (460 blocks): 15-17 us per
 // product, of which 6 us are the MFMAs (0.73 GFLOP, at most two blocks per CU) and about 7 the launch
 // and the three dependent loads in front of the first operand; operands straight into registers 20-22,
-// 2 x 2 register tiles on the vector unit 48-52.
+// 2 x 2 register tiles on the vector unit 48-52.  The up-projection, whose signs decide the ReLU gate,
+// adds its terms one by one in ascending order (21 us): a sum in another order would flip the gate of
+// activations within rounding of zero.
 #include "ffn_ring.h"
 
 namespace lx {
@@ -87,6 +89,96 @@ __device__ __forceinline__ void mma_batches_f32(uint32_t lds, int n, long long l
   }
 }
 
+// The same product with ONE fused multiply-add per term in ascending order of the contraction index,
+// on the 16x16x1 MFMA (four 16 x 16 blocks, the 2 x 2 of the 32 x 32 tile; as fast per product): what
+// the ReLU decides on does not depend on how the kernel is cut.  Lane l holds row l % 16 of block l / 16
+// of either operand; accumulator register 4b + i is C[4 * (l / 16) + i][l % 16] of block b.
+constexpr int kSeqStages = 4;
+template <class At>
+__device__ __forceinline__ void mma_batches_seq_f32(uint32_t lds, int n, long long lda, long long ldw, At at,
+                                                    f32x16& acc) {
+  const int lane = threadIdx.x % kWave, r = lane % 16, b = lane / 16;
+  long long off[8];
+#pragma unroll
+  for (int g = 0; g < 8; ++g) {
+    const int row = 8 * g + lane / 8, seg = (lane % 8) ^ swz(row);
+    off[g] = (row % 32) * (g < 4 ? lda : ldw) + seg * 4;
+  }
+  auto issue = [&](int s) {
+    const float *a, *w;
+    at(s, a, w);
+    const uint32_t dst = lds + (s % kSeqStages) * kF32Stage;
+#pragma unroll
+    for (int g = 0; g < 8; ++g) dma16((g < 4 ? a : w) + off[g], dst + g * 1024);
+  };
+  const int ra = 16 * (b / 2) + r, rw = 32 + 16 * (b % 2) + r;     // token row, weight row of the stage
+#pragma unroll
+  for (int p = 0; p < kSeqStages; ++p)
+    if (p < n) issue(p);
+  for (int s = 0; s < n; ++s) {
+    const int younger = n - 1 - s;
+    if (younger >= 3) wait_vmcnt<24>(); else wait_tail<8, 2>(younger);
+    asm volatile("" ::: "memory");
+    const uint32_t st = lds + (s % kSeqStages) * kF32Stage;
+    f32x4 x[8], y[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      x[u] = __builtin_bit_cast(f32x4, lds_read16(st + ra * 128 + ((u ^ swz(ra)) << 4)));
+      y[u] = __builtin_bit_cast(f32x4, lds_read16(st + rw * 128 + ((u ^ swz(rw)) << 4)));
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read
+    if (s + kSeqStages < n) issue(s + kSeqStages);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x1f32(y[u][e], x[u][e], acc, 0, 0, 0);
+  }
+}
+
+// out = max(A W^T + bias, 0), one fused multiply-add per term in ascending order.
+// Workgroup (token tile, list entry): the tile index is the fast one, so that the workgroups without
+// an entry come last in dispatch order.  A wavefront per 32 x 32 quadrant of the block.
+template <int TB>
+__global__ __launch_bounds__(TB * TB / 1024 * kWave) void ffn_up_f32(
+    const float* __restrict__ A, const float* __restrict__ W, const float* __restrict__ bias,
+    const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int gt, int K, int nnz_cap,
+    float* __restrict__ out_act) {
+  constexpr int Q1 = TB / 32, NQ = Q1 * Q1;
+  __shared__ __attribute__((aligned(1024))) float stages[NQ * kSeqStages * kF32Stage / 4];
+  const int i = blockIdx.x;
+  // gt consecutive token tiles share row i / gt of the list; the activation blocks of a list
+  // row are stored as [entry][tile within the row's group]
+  const int rs = row_ptr[i / gt], n_i = row_ptr[i / gt + 1] - rs;
+  if ((int)blockIdx.y >= n_i) return;
+  const int lp = rs + blockIdx.y;
+  if (lp >= nnz_cap) return;       // entries beyond the capacity of the list buffers are ignored
+  const int j = col_idx[lp];
+  const long long p = (long long)lp * gt + i % gt;
+  const int quad = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int t0 = 32 * (quad % Q1), n0 = 32 * (quad / Q1);      // this wavefront's quadrant
+  const float* a0 = A + ((long long)i * TB + t0) * K;
+  const float* w0 = W + ((long long)j * TB + n0) * K;
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  mma_batches_seq_f32(lds_addr(stages) + quad * (kSeqStages * kF32Stage), K / kF32Batch, K, K,
+                      [=](int s, const float*& a, const float*& w) {
+                        a = a0 + s * kF32Batch;
+                        w = w0 + s * kF32Batch;
+                      },
+                      acc);
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int t = t0 + 16 * (b / 2) + lane % 16, n = n0 + 16 * (b % 2) + 4 * (lane / 16);
+    const long long o = p * (TB * TB) + t * TB + n;
+    f32x4 v = {acc[4 * b], acc[4 * b + 1], acc[4 * b + 2], acc[4 * b + 3]};
+    if (bias) v += *reinterpret_cast<const f32x4*>(bias + j * TB + n);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+    *reinterpret_cast<f32x4*>(out_act + o) = v;
+  }
+}
+
 // Leaves the accumulators in LDS ([wave][16][lane] floats, over the stages) for folded_f32, which
 // adds group g of four accumulator elements over the KS ranges of a quadrant (wavefront = quadrant +
 // NQ * range), range 0 first.
@@ -108,12 +200,10 @@ __device__ __forceinline__ f32x4 folded_f32(const float* area, int quadrant, int
   return s;
 }
 
-// MODE 0: out = max(acc + bias, 0).  MODE 1: out = gate > 0 ? acc : 0.
-// Workgroup (token tile, list entry): the tile index is the fast one, so that the workgroups without
-// an entry come last in dispatch order.
-template <int TB, int MODE>
-__global__ __launch_bounds__(F32Split<TB * TB / 1024>::kThreads) void ffn_sdd_f32(
-    const float* __restrict__ A, const float* __restrict__ W, const float* __restrict__ bias,
+// out = gate > 0 ? A W^T : 0; same grid as above, the contraction in ranges.
+template <int TB>
+__global__ __launch_bounds__(F32Split<TB * TB / 1024>::kThreads) void ffn_gate_f32(
+    const float* __restrict__ A, const float* __restrict__ W,
     const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int gt, int K, int nnz_cap,
     float* __restrict__ out_act, const float* __restrict__ gate_act) {
   constexpr int Q1 = TB / 32, NQ = Q1 * Q1, KS = F32Split<NQ>::kRanges;
@@ -150,15 +240,9 @@ __global__ __launch_bounds__(F32Split<TB * TB / 1024>::kThreads) void ffn_sdd_f3
     f32x4 v = folded_f32<NQ, KS>(stages, quad, g);
     const int t = t0 + lane % 32, n = n0 + 8 * g + 4 * (lane / 32);
     const long long o = p * (TB * TB) + t * TB + n;
-    if (MODE == 0) {
-      if (bias) v += *reinterpret_cast<const f32x4*>(bias + j * TB + n);
+    const f32x4 gg = *reinterpret_cast<const f32x4*>(gate_act + o);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-    } else {
-      const f32x4 gg = *reinterpret_cast<const f32x4*>(gate_act + o);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = gg[e] > 0.f ? v[e] : 0.f;
-    }
+    for (int e = 0; e < 4; ++e) v[e] = gg[e] > 0.f ? v[e] : 0.f;
     *reinterpret_cast<f32x4*>(out_act + o) = v;
   }
 }
@@ -218,11 +302,11 @@ static hipError_t launch_f32(int pass, int Tt, int gt, int Fb, int d, int F, con
   {
     ProfScope ps(pass == 0 ? kKFfnUp : kKFfnDh, st);
     if (pass == 0)
-      hipLaunchKernelGGL((ffn_sdd_f32<TB, 0>), dim3(Tt, Fb), dim3(F32Split<TB * TB / 1024>::kThreads), 0, st, A, W1,
-                         b1, row_ptr, col_idx, gt, d, nnz_cap, act_out, (const float*)nullptr);
+      hipLaunchKernelGGL(ffn_up_f32<TB>, dim3(Tt, Fb), dim3(TB * TB / 1024 * kWave), 0, st, A, W1, b1, row_ptr,
+                         col_idx, gt, d, nnz_cap, act_out);
     else
-      hipLaunchKernelGGL((ffn_sdd_f32<TB, 1>), dim3(Tt, Fb), dim3(F32Split<TB * TB / 1024>::kThreads), 0, st, A, W1,
-                         (const float*)nullptr, row_ptr, col_idx, gt, d, nnz_cap, act_out, act_gate);
+      hipLaunchKernelGGL(ffn_gate_f32<TB>, dim3(Tt, Fb), dim3(F32Split<TB * TB / 1024>::kThreads), 0, st, A, W1,
+                         row_ptr, col_idx, gt, d, nnz_cap, act_out, act_gate);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
