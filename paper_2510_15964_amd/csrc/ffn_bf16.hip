@@ -1,27 +1,25 @@
-// bf16 sparse FFN kernels for gfx950 (Sec. VI-B: neuron-centric tiled matrix
+// 16-bit sparse FFN kernels for gfx950 (Sec. VI-B: neuron-centric tiled matrix
 // products that take the list of active neuron blocks and load / compute only
 // those).  fp32 accumulation on the 32x32x16 MFMA for 16-bit operands.  The kernels are
-// templates over the element type DT (bfloat16 or IEEE half, same layouts and data movement);
-// "bf16" in their names dates from the first of the two.
+// templates over the element type DT (bfloat16 or IEEE half, same layouts and data movement).
 //
 // Both products of a pass are "NT" contractions whose operands are read along
-// their contiguous dimension in 128-byte segments (one 64-element bf16 K-chunk
+// their contiguous dimension in 128-byte segments (one 64-element K-chunk
 // of one row), which is what the weight layouts of Sec. VI-B are for:
 //   sdd  out block (i, j) = A_i [64 x K] . W[j-block rows, :]^T, K = d
-//        one workgroup owns up to four consecutive entries of token tile i's
-//        list, so the A_i chunk staged in LDS is shared by four neuron blocks;
-//        wave w computes block w (64 neurons) for all 64 tokens.
-//   dsd  out tile (i, 256 columns) = sum over listed j of Act_ij [64 x 64] .
+//        a workgroup owns TM token tiles that share a list row and up to TN consecutive
+//        entries of that row.
+//   dsd  out tile (i, 64*TN columns) = sum over listed j of Act_ij [64 x 64] .
 //        W[rows n0.., j-block columns]^T: the K loop walks the active list, one
 //        64-wide K-step per active block; inactive blocks are never touched.
+// The products themselves, and how their operands travel, are in ffn_tile.h.  Every output element
+// sees the same products in the same order whatever the tile, so results do not depend on it.
 //
-// Data movement: the transfer ring of ffn_ring.h, three 40 KiB stages in the sdd kernel (the
-// loads of K-steps s+1 and s+2 are in flight while the MFMAs of step s run), two in the dsd
-// kernel (two resident workgroups per CU).
-//
-// The LoRA branch on the up-projection (Sec. II-C / II-D) is one more step of either ring; the
+// The LoRA branch on the up-projection (Sec. II-C / II-D) is one more step of either product; the
 // calls that add it are at the end of this file, its small products in lora_bf16.hip.
-#include "ffn_ring.h"
+#include <algorithm>
+
+#include "ffn_tile.h"
 
 namespace lx {
 
@@ -41,24 +39,6 @@ __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int r
   // entries of a list row that lie within the capacity of the list buffers: the items are
   // counted from these, so that their number never exceeds the bound the grid was sized from
   auto row_len = [&](int lr) { return min(row_ptr[lr + 1], nnz_cap) - min(row_ptr[lr], nnz_cap); };
-  if (gt >= rows && rows >= 8) {
-    // One list row for all token tiles: the items are a regular rows x C grid, and every XCD
-    // takes a rectangle of it, rows / xr tiles by C / (8 / xr) groups of entries, that it walks
-    // in columns.  The workgroups that run together on an XCD (32 consecutive slots) then share
-    // a few activation tiles and a few weight blocks alike, instead of two tiles and sixteen
-    // groups of blocks: a third fewer bytes miss its L2.
-    const int C = (row_len(0) + per - 1) / per;
-    int xr = 8;
-    while (xr > 1 && (rows % xr != 0 || C % (8 / xr) != 0 || rows / xr < 4)) xr >>= 1;
-    if (C > 0 && rows % xr == 0 && C % (8 / xr) == 0) {
-      const int Rr = rows / xr, Cc = C / (8 / xr);
-      const int x = w % 8, s = w / 8;
-      if (s >= Rr * Cc) return false;
-      row = (x % xr) * Rr + s % Rr;
-      chunk = (x / xr) * Cc + s / Rr;
-      return true;
-    }
-  }
   int total = 0;
   for (int base = 0; base < rows; base += kWave) {
     const int r = base + lane;
@@ -100,110 +80,178 @@ __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int r
   return false;
 }
 
-template <int N>
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[N]) {
-#pragma unroll
-  for (int b = 0; b < N; ++b)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+// The same for ONE list row shared by all token tiles: items (group of TM tiles m, group of TN entries
+// n), or for the dsd kernel (m, chunk of output columns n), in bands of `h` groups m that are walked
+// along n, h items at a time; XCD x takes the x-th eighth of that order.  The workgroups that run
+// together on an XCD then share h token groups and a few weight groups, and with at most h groups of
+// tokens every weight row is fetched into one L2 only.
+struct GridItem {
+  int m, n;
+};
+__device__ __forceinline__ GridItem grid_item(int idx, int GM, int GN, int h) {
+  const int per = h * GN, band = idx / per, left = GM - band * h;
+  const int hb = left < h ? left : h, rem = idx - band * per;
+  return {band * h + rem % hb, rem / hb};
 }
 
-// MODE 0: out = bf16(max(acc + bias, 0));  MODE 1: out = gate > 0 ? bf16(acc) : 0;
-// MODE 2: out = bf16(acc).
+template <class Tl>
+__device__ __forceinline__ void zero_acc(f32x16 (&acc)[Tl::NI][Tl::TI]) {
+#pragma unroll
+  for (int x = 0; x < Tl::NI; ++x)
+#pragma unroll
+    for (int y = 0; y < Tl::TI; ++y)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
+}
+
+// Stores one accumulator: rows t (this lane's token, stride ld) and 32 columns from `out` on; bias over
+// the columns, then ReLU (relu) or the gate by `gate` > 0, which is indexed like `out` (both may be null).
+template <int DT>
+__device__ __forceinline__ void store_acc(const f32x16& acc, uint16_t* __restrict__ out, long long ld,
+                                          const uint16_t* __restrict__ bias, const uint16_t* __restrict__ gate,
+                                          bool relu) {
+  const int lane = threadIdx.x % kWave, tl = lane % 32, nq = (lane / 32) * 4;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int n = 8 * g + nq;
+    const long long o = (long long)tl * ld + n;
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = acc[4 * g + e];
+    if (bias) {
+      const uint2 bb = *reinterpret_cast<const uint2*>(bias + n);
+      v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
+      v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
+    }
+    if (relu) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+    } else if (gate) {
+      const uint2 gg = *reinterpret_cast<const uint2*>(gate + o);
+      if (!(to_f32<DT>(gg.x & 0xFFFFu) > 0.f)) v[0] = 0.f;
+      if (!(to_f32<DT>(gg.x >> 16) > 0.f)) v[1] = 0.f;
+      if (!(to_f32<DT>(gg.y & 0xFFFFu) > 0.f)) v[2] = 0.f;
+      if (!(to_f32<DT>(gg.y >> 16) > 0.f)) v[3] = 0.f;
+    }
+    uint2 ov;
+    ov.x = pack2<DT>(v[0], v[1]);
+    ov.y = pack2<DT>(v[2], v[3]);
+    *reinterpret_cast<uint2*>(out + o) = ov;
+  }
+}
+
+// Offsets of the two products' transfer instructions: instruction u of wavefront w brings the stage
+// rows 8g .. 8g+7 with g = w + kWaves*u (token rows first); lane l brings the 16-byte slot l % 8 of row
+// l / 8, i.e. segment (l % 8) ^ (l / 8) ^ (g % 8) of that row's 128 bytes.
+template <class Tl>
+__device__ __forceinline__ uint32_t lane_voff(long long ld, int g) {
+  const int lane = threadIdx.x % kWave, lr = lane / 8;
+  return (uint32_t)(lr * ld * 2 + (((lane % 8) ^ lr ^ (g & 7)) << 4));
+}
+
+struct SddArgs {
+  const uint16_t *A, *W, *bias;
+  const int *row_ptr, *col_idx;
+  int Tt, gt, K, nnz_cap;      // gt token tiles share a list row
+  int band;                    // h of grid_item (one list row)
+  uint16_t* out;
+  const uint16_t* gate;        // null: ReLU
+  const uint16_t *A2, *W2;     // LORA
+};
+
+// Sources of the sdd kernel's transfers; step K/64, if there is one, is the low-rank step.
+template <class Tl, bool LORA>
+struct SddSrc {
+  const uint16_t* base[Tl::kIss];
+  const uint16_t* base2[LORA ? Tl::kIss : 1];
+  uint32_t voff[2], voff2[2];
+  long long off;
+  int ksteps;
+  bool alt;
+  __device__ __forceinline__ void begin(int s) {
+    alt = LORA && s == ksteps;
+    off = (long long)s * kBK;
+  }
+  __device__ __forceinline__ void dma(int u, uint32_t lds) const {
+    const uint32_t to = lds + u * (Tl::kWaves * 1024);
+    if (LORA && alt)
+      dma16_s(base2[LORA ? u : 0], voff2[Tl::kWaves == 4 ? u & 1 : 0], to);
+    else
+      dma16_s(base[u] + off, voff[Tl::kWaves == 4 ? u & 1 : 0], to);
+  }
+};
+
+// out block (tile, entry) = relu(A_tile W_entry^T + bias) or gated by `gate`; compact activation blocks
+// [entry][tile within the row's group of gt tiles].
 // LORA: one more 64-deep step after the K loop with the operands A2 [T,64] (rows of the token
 // tile) and W2 [F,64] (rows of the listed blocks): acc += A2_i W2_j^T, the low-rank branch
 // z = W x + B (A x) of Sec. II-C with A2 = X A^T computed beforehand and W2 = B, both padded to
 // rank 64.
-// NE: list entries per workgroup (4, or 2 or 1 where that many would leave CUs without one), NST:
-// stages of the transfer ring; both chosen by launch_sdd_one.
-template <int DT, int MODE, bool LORA, int NE, int NST>
-__global__ __launch_bounds__(kThreads, OneStage<NE>::kElems * 2 * NST <= 81920 ? 2 : 1) void ffn_sdd_bf16(
-    const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
-    const uint16_t* __restrict__ bias, const int* __restrict__ row_ptr,
-    const int* __restrict__ col_idx, int rows, int gt, int K, int nnz_cap,
-    uint16_t* __restrict__ out_act, const uint16_t* __restrict__ gate_act,
-    const uint16_t* __restrict__ A2, const uint16_t* __restrict__ W2) {
-  using St = OneStage<NE>;
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * St::kElems];
-  int i, chunk;
-  if (!find_work(row_ptr, rows, gt, blockIdx.x, NE, nnz_cap, i, chunk)) return;
-  const int rs = row_ptr[i / gt], n_i = row_ptr[i / gt + 1] - rs;
-  const int first = chunk * NE;
-  const int p0 = rs + first;
-  if (p0 >= nnz_cap) return;       // entries beyond the capacity of the list buffers are ignored
-  const int nb = min(min(NE, n_i - first), nnz_cap - p0);
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-
-  // per-instruction source pointers of this lane (K offset added per step): instruction 0 brings
-  // token rows, instruction 1 + e the rows of list entry e
-  const int row = 8 * wave + lane / 8;       // row within the 64 rows of an instruction group
-  const uint16_t* src[St::kIss];
-#pragma unroll
-  for (int u = 0; u < St::kIss; ++u) {
-    const int seg = (lane % 8) ^ swz(64 * u + row);
-    // blocks past the end of the list are filled from the first block (never used)
-    const uint16_t* base = u == 0 ? A + ((long long)i * 64 + row) * K
-                                  : W + ((long long)col_idx[p0 + (u - 1 < nb ? u - 1 : 0)] * 64 + row) * K;
-    src[u] = base + seg * 8;
+template <class Tl, int DT, bool LORA>
+__global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_sdd(SddArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[Tl::NST * Tl::kElems];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int m, chunk, n_i, rs;
+  if (a.gt == a.Tt) {
+    rs = min(a.row_ptr[0], a.nnz_cap);
+    n_i = min(a.row_ptr[1], a.nnz_cap) - rs;
+    const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (n_i + Tl::TN - 1) / Tl::TN;
+    const int total = GM * GN, L = (total + 7) / 8, slot = blockIdx.x / 8, idx = (blockIdx.x % 8) * L + slot;
+    if (slot >= L || idx >= total) return;
+    const GridItem it = grid_item(idx, GM, GN, a.band);
+    m = it.m;
+    chunk = it.n;
+  } else {
+    if (!find_work(a.row_ptr, a.Tt / Tl::TM, a.gt / Tl::TM, blockIdx.x, Tl::TN, a.nnz_cap, m, chunk)) return;
+    m = __builtin_amdgcn_readfirstlane(m);
+    chunk = __builtin_amdgcn_readfirstlane(chunk);
+    const int lr = m * Tl::TM / a.gt;
+    rs = a.row_ptr[lr];
+    n_i = min(a.row_ptr[lr + 1], a.nnz_cap) - rs;   // entries beyond the capacity of the list buffers are ignored
   }
-  // the same for the low-rank step (rows of 64 elements), computed when that step is issued
-  auto src2 = [&](int u) -> const uint16_t* {
-    const int seg = (lane % 8) ^ swz(64 * u + row);
-    if (u == 0) return A2 + ((long long)i * 64 + row) * 64 + seg * 8;
-    return W2 + ((long long)col_idx[p0 + (u - 1 < nb ? u - 1 : 0)] * 64 + row) * 64 + seg * 8;
-  };
-  f32x16 acc[St::kTI];
-  zero_acc(acc);
-  const int grp = wave % (2 * NE);            // group of 32 weight rows of this wave
-  const int ti0 = wave / (2 * NE);            // its first group of 32 tokens
-  const int blk_w = grp / 2;                  // list entry it belongs to
-  const bool wave_on = blk_w < nb && ti0 < 2;
-  const int ksteps = K / kBK;
-  run_ring<DT, NST, NE>(ksteps + (LORA ? 1 : 0), wave_on, src, src2,
-                        [=](int s, long long& ob, long long& oa) {
-                          const bool alt = LORA && s == ksteps;
-                          ob = oa = alt ? 0 : (long long)s * kBK;
-                          return alt;
-                        },
-                        ring, acc);
-  if (!wave_on) return;
+  const int i0 = m * Tl::TM, first = chunk * Tl::TN, p0 = rs + first;
+  const int nb = min(Tl::TN, n_i - first);
+  if (nb <= 0) return;
 
-  const int j = col_idx[p0 + blk_w];
-  // compact activation block of (tile i, list entry): the entries of a list row are stored as
-  // [entry][tile within the row's group of gt tiles]
-  const long long p = (long long)rs * gt + (long long)(first + blk_w) * gt + i % gt;
-  const int tl = lane % 32, nq = (lane / 32) * 4;
-  const int nh = grp % 2;                     // which 32 neurons of the block
+  SddSrc<Tl, LORA> src;
+  src.ksteps = a.K / kBK;
+  src.voff[0] = lane_voff<Tl>(a.K, wave);
+  src.voff[1] = lane_voff<Tl>(a.K, wave + 4);
+  if (LORA) {
+    src.voff2[0] = lane_voff<Tl>(64, wave);
+    src.voff2[1] = lane_voff<Tl>(64, wave + 4);
+  }
 #pragma unroll
-  for (int ti = 0; ti < St::kTI; ++ti)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int t = 32 * (ti0 + ti) + tl, n = 32 * nh + 8 * g + nq;
-      const long long o = p * 4096 + t * 64 + n;
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = acc[ti][4 * g + e];
-      if (MODE == 2) {
-      } else if (MODE == 0) {
-        if (bias) {
-          const uint2 bb = *reinterpret_cast<const uint2*>(bias + j * 64 + n);
-          v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
-          v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-      } else {
-        const uint2 gg = *reinterpret_cast<const uint2*>(gate_act + o);
-        if (!(to_f32<DT>(gg.x & 0xFFFFu) > 0.f)) v[0] = 0.f;
-        if (!(to_f32<DT>(gg.x >> 16) > 0.f)) v[1] = 0.f;
-        if (!(to_f32<DT>(gg.y & 0xFFFFu) > 0.f)) v[2] = 0.f;
-        if (!(to_f32<DT>(gg.y >> 16) > 0.f)) v[3] = 0.f;
-      }
-      uint2 ov;
-      ov.x = pack2<DT>(v[0], v[1]);
-      ov.y = pack2<DT>(v[2], v[3]);
-      *reinterpret_cast<uint2*>(out_act + o) = ov;
+  for (int u = 0; u < Tl::kIss; ++u) {
+    const int g = wave + Tl::kWaves * u;
+    if (u < Tl::kIssA) {     // (token tiles past the end: the last one again, not stored)
+      const long long row = (long long)min(i0 + g / 8, a.Tt - 1) * 64 + 8 * (g % 8);
+      src.base[u] = a.A + row * a.K;
+      if (LORA) src.base2[LORA ? u : 0] = a.A2 + row * 64;
+    } else {                 // blocks past the end of the list are filled from the first block (not stored)
+      const int e = (g - 8 * Tl::TM) / 8;
+      const long long row = (long long)a.col_idx[p0 + (e < nb ? e : 0)] * 64 + 8 * (g % 8);
+      src.base[u] = a.W + row * a.K;
+      if (LORA) src.base2[LORA ? u : 0] = a.W2 + row * 64;
     }
+  }
+  const int wm = wave / Tl::WN, wn = wave % Tl::WN;
+  f32x16 acc[Tl::NI][Tl::TI];
+  zero_acc<Tl>(acc);
+  run_tile<Tl, DT>(src.ksteps + (LORA ? 1 : 0), lds_addr(ring), wm, wn, src, acc);
+#pragma unroll
+  for (int ni = 0; ni < Tl::NI; ++ni) {
+    const int e = (wn * Tl::NI + ni) / 2, nh = 32 * ((wn * Tl::NI + ni) % 2);
+    if (e >= nb) continue;
+    const uint16_t* bias = a.bias ? a.bias + a.col_idx[p0 + e] * 64 + nh : nullptr;
+#pragma unroll
+    for (int ti = 0; ti < Tl::TI; ++ti) {
+      const int i = i0 + (wm * Tl::TI + ti) / 2, th = 32 * ((wm * Tl::TI + ti) % 2);
+      if (i >= a.Tt) continue;
+      const long long p = ((long long)rs * a.gt + (long long)(first + e) * a.gt + i % a.gt) * 4096 + th * 64 + nh;
+      store_acc<DT>(acc[ni][ti], a.out + p, 64, bias, a.gate ? a.gate + p : nullptr, !a.gate);
+    }
+  }
 }
 
 // Which token tile the workgroups of grid row `slot` work on.  A workgroup of the dsd kernel
@@ -214,14 +262,12 @@ __global__ __launch_bounds__(kThreads, OneStage<NE>::kElems * 2 * NST <= 81920 ?
 // at once, two workgroups per CU, rows s and s + Tt/2, which the round robin of the dispatcher
 // places on the same CU, get ranks s and Tt - 1 - s, a long list next to a short one.
 constexpr int kBalTiles = 128;
-// The launch covers the Tt tiles first .. first + Tt - 1; the result is a tile of that range.
-__device__ __forceinline__ int balanced_tile(const int* __restrict__ row_ptr, int first, int Tt,
-                                             int gt, int nnz_cap, int slot, bool resident,
-                                             int* lens) {
-  if (Tt > kBalTiles || Tt < 3) return first + slot;
+__device__ __forceinline__ int balanced_tile(const int* __restrict__ row_ptr, int Tt, int gt,
+                                             int nnz_cap, int slot, bool resident, int* lens) {
+  if (Tt > kBalTiles || Tt < 3) return slot;
   const int tid = threadIdx.x;
   if (tid < Tt) {
-    const int r = (first + tid) / gt;
+    const int r = tid / gt;
     lens[tid] = min(row_ptr[r + 1], nnz_cap) - row_ptr[r];
   }
   __syncthreads();
@@ -239,624 +285,410 @@ __device__ __forceinline__ int balanced_tile(const int* __restrict__ row_ptr, in
   __syncthreads();
   const int tile = __builtin_amdgcn_readfirstlane(lens[kBalTiles]);
   __syncthreads();   // lens is memory the caller reuses
-  return first + tile;
+  return tile;
 }
 
-// out[i-tile rows, n0 .. n0 + 64*NE - 1] = sum_s act[p_s] [64 x 64] . W[n0.., j_s*64 ..]^T (+ bias)
-// LORA: one more step with the operands act2 [T,64] (the token tile's 64 x 64 block) and
-// W2 [ncols_out, 64]: out += act2_i W2[n0..]^T, the low-rank part (dZ B) A of the input gradient.
-// NE: groups of 64 output columns per workgroup, NST: ring stages (chosen by launch_dsd_one).
-template <int DT, bool LORA, int NE, int NST>
-__global__ __launch_bounds__(kThreads) void ffn_dsd_bf16(
-    const uint16_t* __restrict__ act, const uint16_t* __restrict__ W, long long ldw,
-    const uint16_t* __restrict__ bias, const int* __restrict__ row_ptr,
-    const int* __restrict__ col_idx, int gt, int ncols_out, int nnz_cap,
-    uint16_t* __restrict__ out, const uint16_t* __restrict__ act2,
-    const uint16_t* __restrict__ W2, int tile0) {
-  using St = OneStage<NE>;
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * St::kElems];
-  // the launch covers the token tiles tile0 .. tile0 + gridDim.y - 1
-  const int i = balanced_tile(row_ptr, tile0, gridDim.y, gt, nnz_cap, blockIdx.y,
-                              gridDim.x * gridDim.y <= 2 * kCUs, reinterpret_cast<int*>(ring));
-  const int n0 = blockIdx.x * (64 * NE);
-  const int rs = row_ptr[i / gt];
-  const int n_i = min(row_ptr[i / gt + 1], nnz_cap) - rs;   // <= 0: nothing within the capacity
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const int grp = wave % (2 * NE);                          // group of 32 output columns of this wave
-  const int ti0 = wave / (2 * NE);                          // its first group of 32 tokens
-  const bool wave_on = n0 + 32 * grp < ncols_out && ti0 < 2;
 
-  // instruction 0 brings the rows of a compact 64x64 activation block, 1 + e 64 rows of W
-  const int row = 8 * wave + lane / 8;
-  const uint16_t* src[St::kIss];
-#pragma unroll
-  for (int u = 0; u < St::kIss; ++u) {
-    const int seg = (lane % 8) ^ swz(64 * u + row);
-    const int n = min(n0 + 64 * (u - 1) + row, ncols_out - 1);   // rows past the edge: re-read the last
-    src[u] = (u == 0 ? act + row * 64 : W + (long long)n * ldw) + seg * 8;
+struct DsdArgs {
+  const uint16_t *act, *W, *bias;
+  long long ldw;
+  const int *row_ptr, *col_idx;
+  int Tt, gt, ncols, nnz_cap;
+  int band;                    // h of grid_item (one list row)
+  int full, rest, pieces;      // one list row: units that run whole, then units whose list is cut
+  uint16_t* out;
+  float* part;
+  const uint16_t *A2, *W2;     // LORA
+};
+
+template <class Tl, bool LORA>
+struct DsdSrc {
+  const uint16_t* base[Tl::kIss];
+  const uint16_t* base2[LORA ? Tl::kIss : 1];
+  uint32_t voffA[2], voffW[2];
+  uint32_t voff2[2];
+  long long off_a, off_w, step_a;
+  const int* list;             // col_idx of the range
+  int lsteps, next;            // list entries of 64 steps, one per lane
+  bool alt;
+  // Loads the entries of steps s .. s + 63.  In assembly, with its own wait: a load that the compiler
+  // tracks would make it wait for vmcnt(0), and so for the whole ring, at every step's use of `next`
+  // (twice the time with three stages).  The drain that is left costs about 1 us per 64 steps.
+  __device__ __forceinline__ void fetch(int s) {
+    const int e = s + (int)(threadIdx.x % kWave);
+    const uint32_t off = (uint32_t)(e < lsteps ? e : lsteps - 1) * 4u;
+    asm volatile("global_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)" : "=v"(next) : "v"(off), "s"(list) : "memory");
   }
-  auto src2 = [&](int u) -> const uint16_t* {     // the low-rank step, computed when it is issued
-    const int seg = (lane % 8) ^ swz(64 * u + row);
-    if (u == 0) return act2 + ((long long)i * 64 + row) * 64 + seg * 8;
-    return W2 + (long long)min(n0 + 64 * (u - 1) + row, ncols_out - 1) * 64 + seg * 8;
-  };
-  f32x16 acc[St::kTI];
-  zero_acc(acc);
-  const int lsteps = n_i > 0 ? n_i : 0;
-  run_ring<DT, NST, NE>(lsteps + (LORA ? 1 : 0), wave_on, src, src2,
-                        [&](int s, long long& ob, long long& oa) {
-                          const bool alt = LORA && s == lsteps;
-                          ob = alt ? 0 : ((long long)(rs + s) * gt + i % gt) * 4096;
-                          oa = alt ? 0 : (long long)col_idx[rs + s] * 64;
-                          return alt;
-                        },
-                        ring, acc);
-  if (!wave_on) return;
+  __device__ __forceinline__ void begin(int s) {
+    alt = LORA && s == lsteps;
+    if (alt) return;
+    if (s > 0 && s % kWave == 0) fetch(s);
+    off_a = s * step_a;
+    off_w = (long long)__builtin_amdgcn_readlane(next, s % kWave) * 64;
+  }
+  __device__ __forceinline__ void dma(int u, uint32_t lds) const {
+    const uint32_t to = lds + u * (Tl::kWaves * 1024);
+    const int q = Tl::kWaves == 4 ? u & 1 : 0;
+    if (LORA && alt)
+      dma16_s(base2[LORA ? u : 0], u < Tl::kIssA ? voffA[q] : voff2[q], to);
+    else if (u < Tl::kIssA)
+      dma16_s(base[u] + off_a, voffA[q], to);
+    else
+      dma16_s(base[u] + off_w, voffW[q], to);
+  }
+};
 
-  const int tl = lane % 32, nq = (lane / 32) * 4;
-#pragma unroll
-  for (int ti = 0; ti < St::kTI; ++ti)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int t = i * 64 + 32 * (ti0 + ti) + tl;
-      const int n = n0 + 32 * grp + 8 * g + nq;
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = acc[ti][4 * g + e];
-      if (bias) {
-        const uint2 bb = *reinterpret_cast<const uint2*>(bias + n);
-        v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
-        v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
-      }
-      uint2 ov;
-      ov.x = pack2<DT>(v[0], v[1]);
-      ov.y = pack2<DT>(v[2], v[3]);
-      *reinterpret_cast<uint2*>(out + (long long)t * ncols_out + n) = ov;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Several token tiles per workgroup.  When TT = 2 or 4 consecutive token tiles share a list row
-// (the paper's reduced mask, or a dense layer), they can be multiplied with the same weight
-// rows: 64*TT token rows + 256 weight rows per stage (48 KiB in a ring of three, or 64 KiB in a
-// ring of two; one workgroup per CU) and a wave tile of 64 x 32*TT, i.e. 0.6 / 0.4 times the
-// transferred and a half / three eighths of the LDS-read bytes per product of the kernels above.
-// Every output element sees the same products in the same order, so the results are
-// bit-identical to the one-tile kernels'.  It pays when the launch still fills the chip with
-// a half or a quarter as many workgroups (large or dense layers); the host chooses
-// (launch_ffn_bf16).
-// ---------------------------------------------------------------------------
-
-// Epilogue of one 64 x 64 token tile of a wave tile: acc[ni][2*tile + ti] -> rows 32*ti + lane%32
-// (stride ld elements) and columns 32*ni + 8*g + 4*(lane/32) + e of `out`; bias over the
-// columns, gate with the same indexing (both may be null).
-template <int DT, int MODE, int TT>
-__device__ __forceinline__ void store_tile64(const f32x16 (&acc)[2][TT], int tile,
-                                             uint16_t* __restrict__ out, long long ld,
-                                             const uint16_t* __restrict__ bias,
-                                             const uint16_t* __restrict__ gate) {
-  const int lane = threadIdx.x % kWave, tl = lane % 32, nq = (lane / 32) * 4;
-#pragma unroll
-  for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int n = 32 * ni + 8 * g + nq;
-        const long long o = (long long)(32 * ti + tl) * ld + n;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[ni][2 * tile + ti][4 * g + e];
-        if (bias) {
-          const uint2 bb = *reinterpret_cast<const uint2*>(bias + n);
-          v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
-          v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
-        }
-        if (MODE == 0) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-        } else if (MODE == 1) {
-          const uint2 gg = *reinterpret_cast<const uint2*>(gate + o);
-          if (!(to_f32<DT>(gg.x & 0xFFFFu) > 0.f)) v[0] = 0.f;
-          if (!(to_f32<DT>(gg.x >> 16) > 0.f)) v[1] = 0.f;
-          if (!(to_f32<DT>(gg.y & 0xFFFFu) > 0.f)) v[2] = 0.f;
-          if (!(to_f32<DT>(gg.y >> 16) > 0.f)) v[3] = 0.f;
-        }
-        uint2 ov;
-        ov.x = pack2<DT>(v[0], v[1]);
-        ov.y = pack2<DT>(v[2], v[3]);
-        *reinterpret_cast<uint2*>(out + o) = ov;
-      }
-}
-
-// sdd for groups of TT token tiles: work item = (TT consecutive tiles of one list row, up to four
-// consecutive list entries); wave w multiplies entry w % 4 with half w / 4 of the group's tiles.
-// `rows` counts token tiles, gt of which share a list row (both multiples of TT).  MODE / LORA as
-// above.
-template <int DT, int MODE, bool LORA, int TT>
-__global__ __launch_bounds__(kThreads) void ffn_sddn_bf16(
-    const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
-    const uint16_t* __restrict__ bias, const int* __restrict__ row_ptr,
-    const int* __restrict__ col_idx, int rows, int gt, int K, int nnz_cap,
-    uint16_t* __restrict__ out_act, const uint16_t* __restrict__ gate_act,
-    const uint16_t* __restrict__ A2, const uint16_t* __restrict__ W2) {
-  using St = MultiStage<TT>;
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[St::kStages * St::kElems];
-  int grp, chunk;
-  if (!find_work(row_ptr, rows / TT, gt / TT, blockIdx.x, 4, nnz_cap, grp, chunk)) return;
-  const int i0 = TT * grp;                       // first tile of the group
-  const int rs = row_ptr[i0 / gt], n_i = row_ptr[i0 / gt + 1] - rs;
-  const int first = chunk * 4;
-  const int p0 = rs + first;
-  if (p0 >= nnz_cap) return;       // entries beyond the capacity of the list buffers are ignored
-  const int nb = min(min(4, n_i - first), nnz_cap - p0);
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-
-  const uint16_t* src[St::kIss];
-#pragma unroll
-  for (int u = 0; u < St::kIss; ++u) {
-    const int g = wave + kFW * u, row = 8 * g + lane / 8;
-    const int seg = (lane % 8) ^ swz(row);
-    if (u < TT) {
-      src[u] = A + ((long long)i0 * 64 + row) * K + seg * 8;      // 64*TT consecutive token rows
+// out[tile rows, n0 .. n0 + 64*TN - 1] = sum_s act[p_s] [64 x 64] . W[n0.., j_s*64 ..]^T (+ bias)
+// LORA: one more step with the operands A2 [T,64] (the token tile's 64 x 64 block) and
+// W2 [ncols_out, 64]: out += A2_i W2[n0..]^T, the low-rank part (dZ B) A of the input gradient.
+// One list row for all tiles: 1-D grid over units (tile group, column chunk); the first `full` run
+// whole, the list of each of the following `rest` is cut into `pieces` whose accumulators go to
+// `part` as they are, fp32, for ffn_dsd_reduce to add in order.  Otherwise: 2-D grid (column chunk,
+// tile group).
+template <class Tl, int DT, bool LORA>
+__global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_dsd(DsdArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[Tl::NST * Tl::kElems];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int i0, n0, s_lo = 0, n_i, rs, slot = -1;
+  if (a.gt == a.Tt) {
+    const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (a.ncols + 64 * Tl::TN - 1) / (64 * Tl::TN);
+    const int Lf = (a.full + 7) / 8, s = blockIdx.x / 8, x = blockIdx.x % 8;
+    int unit, piece = -1;
+    if (s < Lf) {
+      unit = x * Lf + s;
+      if (unit >= a.full) return;
     } else {
-      const int blk = (row - St::kShared) / 64, r = (row - St::kShared) % 64;
-      // blocks past the end of the list are filled from the first block (never used)
-      const int j = col_idx[p0 + (blk < nb ? blk : 0)];
-      src[u] = W + ((long long)j * 64 + r) * K + seg * 8;
+      const int cut = a.rest * a.pieces, Lr = (cut + 7) / 8, y = x * Lr + s - Lf;
+      if (s - Lf >= Lr || y >= cut) return;
+      piece = y / a.rest;                   // an XCD works on few pieces: their weights and activations
+      unit = a.full + y % a.rest;
+      slot = (y % a.rest) * a.pieces + piece;
     }
-  }
-  auto src2 = [&](int u) -> const uint16_t* {    // the low-rank step, computed when it is issued
-    const int g = wave + kFW * u, row = 8 * g + lane / 8;
-    const int seg = (lane % 8) ^ swz(row);
-    if (u < TT) return A2 + ((long long)i0 * 64 + row) * 64 + seg * 8;
-    const int blk = (row - St::kShared) / 64, r = (row - St::kShared) % 64;
-    const int j = col_idx[p0 + (blk < nb ? blk : 0)];
-    return W2 + ((long long)j * 64 + r) * 64 + seg * 8;
-  };
-  const int rg = wave % 4, th = wave / 4;        // list entry of the four, half of the group's tiles
-  const bool wave_on = rg < nb;
-  f32x16 acc[2][TT];
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int y = 0; y < TT; ++y)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
-  const int ksteps = K / kBK;
-  run_ring_of<St::kStages, St::kIss, St::kElems, TT>(
-      ksteps + (LORA ? 1 : 0), src, src2,
-      [=](int s, long long& ob, long long& oa) {
-        const bool alt = LORA && s == ksteps;
-        ob = oa = alt ? 0 : (long long)s * kBK;
-        return alt;
-      },
-      ring, [&](const uint16_t* stage) {
-        if (wave_on) mma_step64<DT, TT>(stage, rg, th, acc);
-      });
-  if (!wave_on) return;
-  const int j = col_idx[p0 + rg];
-#pragma unroll
-  for (int t = 0; t < TT / 2; ++t) {
-    const int i = i0 + (TT / 2) * th + t;
-    // compact activation block of (tile i, list entry): [entry][tile within the row's group]
-    const long long p = (long long)rs * gt + (long long)(first + rg) * gt + i % gt;
-    store_tile64<DT, MODE, TT>(acc, t, out_act + p * 4096, 64,
-                               MODE == 0 && bias ? bias + j * 64 : nullptr,
-                               MODE == 1 ? gate_act + p * 4096 : nullptr);
-  }
-}
-
-// dsd for groups of TT token tiles: the workgroup of grid row y works on tiles TT*y .. (one list
-// row) and 256 output columns; wave w multiplies columns 64 * (w % 4) .. with half w / 4 of the
-// group's tiles.
-template <int DT, bool LORA, int TT>
-__global__ __launch_bounds__(kThreads) void ffn_dsdn_bf16(
-    const uint16_t* __restrict__ act, const uint16_t* __restrict__ W, long long ldw,
-    const uint16_t* __restrict__ bias, const int* __restrict__ row_ptr,
-    const int* __restrict__ col_idx, int gt, int ncols_out, int nnz_cap,
-    uint16_t* __restrict__ out, const uint16_t* __restrict__ act2,
-    const uint16_t* __restrict__ W2, int group0, int lin0, int nchunks, int ksplit,
-    float* __restrict__ part) {
-  using St = MultiStage<TT>;
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[St::kStages * St::kElems];
-  // ksplit == 0: 2-D grid (column chunk, tile group), the launch covers the tile groups group0 ..
-  // group0 + gridDim.y - 1.  ksplit >= 1: 1-D grid over (unit, piece): unit lin0 + blockIdx.x /
-  // ksplit of the (tile group, column chunk) pairs numbered chunk-fastest, and piece blockIdx.x %
-  // ksplit of the unit's list; with `part` the accumulators go there as they are, fp32, for
-  // ffn_dsd_reduce to add the pieces of a unit in order (fills the chip when the units of the last
-  // round of workgroups are few).
-  int i0, n0, piece = 0;
-  if (ksplit == 0) {
-    i0 = TT * balanced_tile(row_ptr, group0, gridDim.y, gt / TT, nnz_cap, blockIdx.y, false,
-                            reinterpret_cast<int*>(ring));
-    n0 = blockIdx.x * kRowsA;
+    const GridItem it = grid_item(unit, GM, GN, a.band);
+    i0 = it.m * Tl::TM;
+    n0 = it.n * (64 * Tl::TN);
+    rs = min(a.row_ptr[0], a.nnz_cap);
+    n_i = min(a.row_ptr[1], a.nnz_cap) - rs;
+    if (piece >= 0) {
+      s_lo = (int)((long long)n_i * piece / a.pieces);
+      n_i = (int)((long long)n_i * (piece + 1) / a.pieces) - s_lo;
+    }
   } else {
-    const int lin = lin0 + blockIdx.x / ksplit;
-    piece = blockIdx.x % ksplit;
-    i0 = TT * (lin / nchunks);
-    n0 = (lin % nchunks) * kRowsA;
+    i0 = Tl::TM * balanced_tile(a.row_ptr, gridDim.y, a.gt / Tl::TM, a.nnz_cap, blockIdx.y,
+                                gridDim.x * gridDim.y <= 2 * kCUs, reinterpret_cast<int*>(ring));
+    n0 = blockIdx.x * (64 * Tl::TN);
+    rs = a.row_ptr[i0 / a.gt];
+    n_i = min(a.row_ptr[i0 / a.gt + 1], a.nnz_cap) - rs;
   }
-  const int rs0 = row_ptr[i0 / gt];
-  const int n_all = min(row_ptr[i0 / gt + 1], nnz_cap) - rs0;   // <= 0: nothing within the capacity
-  // this piece's range of the list (the whole list unless ksplit > 1)
-  const int nn = n_all > 0 ? n_all : 0;
-  const int s_lo = ksplit > 1 ? (int)((long long)nn * piece / ksplit) : 0;
-  const int s_hi = ksplit > 1 ? (int)((long long)nn * (piece + 1) / ksplit) : nn;
-  const int rs = rs0 + s_lo;
-  const int n_i = s_hi - s_lo;
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const int rg = wave % 4, th = wave / 4;        // 64 output columns of the 256, half of the tiles
-  const bool wave_on = n0 + 64 * rg < ncols_out;
+  if (n_i < 0) n_i = 0;     // nothing within the capacity
 
-  const uint16_t* src[St::kIss];
+  DsdSrc<Tl, LORA> src;
+  src.list = a.col_idx + rs + s_lo;
+  src.lsteps = n_i;
+  src.next = 0;
+  if (n_i > 0) src.fetch(0);
+  src.step_a = (long long)a.gt * 4096;
 #pragma unroll
-  for (int u = 0; u < St::kIss; ++u) {
-    const int g = wave + kFW * u, row = 8 * g + lane / 8;
-    const int seg = (lane % 8) ^ swz(row);
-    if (u < TT) {
-      src[u] = act + row * 64 + seg * 8;          // the tiles' blocks of an entry are adjacent
-    } else {
-      const int n = min(n0 + row - St::kShared, ncols_out - 1);   // rows past the edge: re-read the last
-      src[u] = W + (long long)n * ldw + seg * 8;
+  for (int q = 0; q < 2; ++q) {
+    src.voffA[q] = lane_voff<Tl>(64, wave + 4 * q);
+    src.voffW[q] = lane_voff<Tl>(a.ldw, wave + 4 * q);
+    if (LORA) src.voff2[q] = lane_voff<Tl>(64, wave + 4 * q);
+  }
+#pragma unroll
+  for (int u = 0; u < Tl::kIss; ++u) {
+    const int g = wave + Tl::kWaves * u;
+    if (u < Tl::kIssA) {     // (token tiles past the end: the last one again, not stored)
+      const int i = min(i0 + g / 8, a.Tt - 1);
+      src.base[u] = a.act + (((long long)rs + s_lo) * a.gt + i % a.gt) * 4096 + 8 * (g % 8) * 64;
+      if (LORA) src.base2[LORA ? u : 0] = a.A2 + ((long long)i * 64 + 8 * (g % 8)) * 64;
+    } else {                 // columns past the edge: the last 64 again, not stored
+      const long long n = min(n0 + (g / 8 - Tl::TM) * 64, a.ncols - 64) + 8 * (g % 8);
+      src.base[u] = a.W + n * a.ldw;
+      if (LORA) src.base2[LORA ? u : 0] = a.W2 + n * 64;
     }
   }
-  auto src2 = [&](int u) -> const uint16_t* {     // the low-rank step, computed when it is issued
-    const int g = wave + kFW * u, row = 8 * g + lane / 8;
-    const int seg = (lane % 8) ^ swz(row);
-    if (u < TT) return act2 + ((long long)i0 * 64 + row) * 64 + seg * 8;
-    const int n = min(n0 + row - St::kShared, ncols_out - 1);
-    return W2 + (long long)n * 64 + seg * 8;
-  };
-  f32x16 acc[2][TT];
+  const int wm = wave / Tl::WN, wn = wave % Tl::WN;
+  f32x16 acc[Tl::NI][Tl::TI];
+  zero_acc<Tl>(acc);
+  run_tile<Tl, DT>(n_i + (LORA ? 1 : 0), lds_addr(ring), wm, wn, src, acc);
+  if (slot >= 0) {   // the piece's partial sums: [wave][accumulator][lane][16 registers]
+    f32x4* dst = reinterpret_cast<f32x4*>(a.part + ((size_t)slot * Tl::kWaves + wave) * (Tl::NI * Tl::TI * 16) * kWave) +
+                 (threadIdx.x % kWave) * 4;
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < Tl::NI; ++x)
 #pragma unroll
-    for (int y = 0; y < TT; ++y)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
-  const int lsteps = n_i > 0 ? n_i : 0;
-  run_ring_of<St::kStages, St::kIss, St::kElems, TT>(
-      lsteps + (LORA ? 1 : 0), src, src2,
-      [&](int s, long long& ob, long long& oa) {
-        const bool alt = LORA && s == lsteps;
-        ob = alt ? 0 : ((long long)(rs + s) * gt + i0 % gt) * 4096;
-        oa = alt ? 0 : (long long)col_idx[rs + s] * 64;
-        return alt;
-      },
-      ring, [&](const uint16_t* stage) {
-        if (wave_on) mma_step64<DT, TT>(stage, rg, th, acc);
-      });
-  if (!wave_on) return;
-  if (part) {   // the piece's partial sums: [wave][accumulator][lane][16 registers] (ffn_dsd_reduce reads them the same way)
-    f32x4* dst = reinterpret_cast<f32x4*>(part + ((size_t)blockIdx.x * kFW + wave) * (2 * TT * 16) * kWave) + lane * 4;
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int y = 0; y < TT; ++y)
+      for (int y = 0; y < Tl::TI; ++y)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const f32x4 v4 = {acc[x][y][4 * q], acc[x][y][4 * q + 1], acc[x][y][4 * q + 2], acc[x][y][4 * q + 3]};
-          dst[(x * TT + y) * (kWave * 4) + q] = v4;
+          dst[(x * Tl::TI + y) * (kWave * 4) + q] = v4;
         }
     return;
   }
-  // ncols_out is a multiple of 64 (the host checks d % 64 == 0): a wave's 64 columns are all inside
-  const int n = n0 + 64 * rg;
 #pragma unroll
-  for (int t = 0; t < TT / 2; ++t)
-    store_tile64<DT, 2, TT>(acc, t, out + (long long)(i0 + (TT / 2) * th + t) * 64 * ncols_out + n,
-                            ncols_out, bias ? bias + n : nullptr, nullptr);
+  for (int ni = 0; ni < Tl::NI; ++ni) {
+    const int n = n0 + 32 * (wn * Tl::NI + ni);
+    if (n >= a.ncols) continue;
+#pragma unroll
+    for (int ti = 0; ti < Tl::TI; ++ti) {
+      const int t = i0 * 64 + 32 * (wm * Tl::TI + ti);
+      if (t >= a.Tt * 64) continue;
+      store_acc<DT>(acc[ni][ti], a.out + (long long)t * a.ncols + n, a.ncols, a.bias ? a.bias + n : nullptr,
+                    nullptr, false);
+    }
+  }
 }
 
-// Adds the ksplit pieces of each unit that ffn_dsdn_bf16 left in `part` (piece 0 first, fixed
-// order: reproducible) and writes the unit's tile like the kernel's own epilogue: workgroup
-// (b, t) is unit lin0 + b and the t-th token tile of each of the kernel's wavefronts; its threads
-// hold the same accumulator elements as in the kernel.
-template <int DT, int TT, int T>
-__device__ __forceinline__ void dsd_reduce_tile(const float* __restrict__ part, int ksplit, int wave,
-                                                int lane, uint16_t* __restrict__ out_tile, long long ld,
-                                                const uint16_t* __restrict__ bias) {
-  f32x16 acc[2][TT];       // only [.][2T], [.][2T + 1] are used
+// Adds the pieces of each cut unit (piece 0 first, fixed order: reproducible) and stores like the
+// kernel's own epilogue: workgroup (b, y) is unit full + b and accumulator y / (kWaves/4) of four
+// of the unit's wavefronts.
+template <class Tl, int DT>
+__global__ __launch_bounds__(256) void ffn_dsd_reduce(DsdArgs a) {
+  const int lane = threadIdx.x % kWave, quad = Tl::kWaves / 4;
+  const int wave = threadIdx.x / kWave + 4 * (blockIdx.y % quad), acc_i = blockIdx.y / quad;
+  const int ni = acc_i / Tl::TI, ti = acc_i % Tl::TI;
+  const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (a.ncols + 64 * Tl::TN - 1) / (64 * Tl::TN);
+  const GridItem it = grid_item(a.full + blockIdx.x, GM, GN, a.band);
+  const int wm = wave / Tl::WN, wn = wave % Tl::WN;
+  const int n = it.n * (64 * Tl::TN) + 32 * (wn * Tl::NI + ni);
+  const int t = it.m * Tl::TM * 64 + 32 * (wm * Tl::TI + ti);
+  if (n >= a.ncols || t >= a.Tt * 64) return;
+  f32x16 acc;
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int y = 0; y < TT; ++y)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
-  for (int p = 0; p < ksplit; ++p) {
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  for (int p = 0; p < a.pieces; ++p) {
     const f32x4* src = reinterpret_cast<const f32x4*>(
-        part + (((size_t)blockIdx.x * ksplit + p) * kFW + wave) * (2 * TT * 16) * kWave) + lane * 4;
+                           a.part + (((size_t)blockIdx.x * a.pieces + p) * Tl::kWaves + wave) * (Tl::NI * Tl::TI * 16) * kWave) +
+                       lane * 4 + acc_i * (kWave * 4);
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 v4 = src[q];
 #pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 v4 = src[(x * TT + 2 * T + ti) * (kWave * 4) + q];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[x][2 * T + ti][4 * q + e] += v4[e];
-        }
+      for (int e = 0; e < 4; ++e) acc[4 * q + e] += v4[e];
+    }
   }
-  store_tile64<DT, 2, TT>(acc, T, out_tile, ld, bias, nullptr);
-}
-template <int DT, int TT>
-__global__ __launch_bounds__(kThreads) void ffn_dsd_reduce(const float* __restrict__ part, int ksplit,
-                                                           int lin0, int nchunks, int ncols_out,
-                                                           const uint16_t* __restrict__ bias,
-                                                           uint16_t* __restrict__ out) {
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const int rg = wave % 4, th = wave / 4;
-  const int lin = lin0 + blockIdx.x, t = blockIdx.y;       // t < TT / 2
-  const int i0 = TT * (lin / nchunks), n0 = (lin % nchunks) * kRowsA;
-  if (n0 + 64 * rg >= ncols_out) return;
-  const int n = n0 + 64 * rg;
-  uint16_t* out_tile = out + (long long)(i0 + (TT / 2) * th + t) * 64 * ncols_out + n;
-  const uint16_t* b = bias ? bias + n : nullptr;
-  if (TT == 4 && t == 1)
-    dsd_reduce_tile<DT, TT, TT == 4 ? 1 : 0>(part, ksplit, wave, lane, out_tile, ncols_out, b);
-  else
-    dsd_reduce_tile<DT, TT, 0>(part, ksplit, wave, lane, out_tile, ncols_out, b);
+  store_acc<DT>(acc, a.out + (long long)t * a.ncols + n, a.ncols, a.bias ? a.bias + n : nullptr, nullptr, false);
 }
 
 // pass 0 (forward):  A = X,  W1 = W_up [F,d],     W2 = W_down [d,F], act_out = H_act, out = Y
 // pass 1 (backward): A = dY, W1 = W_down_t [F,d], W2 = W_up_t [d,F], act_out = dZ_act,
 //                    act_gate = H_act, out = dX
-static dim3 sdd_grid(int Tt, int gt, int nnz_cap, int per) {
-  // items <= nnz_cap / per + Tt; per XCD L = ceil(items / 8) of them in 8 * ceil(L / 8) slots
-  const long long items = ((long long)nnz_cap * gt + per - 1) / per + (per > 1 ? Tt : 0);
-  const int Lub = (int)((items + 7) / 8);
-  return dim3(8 * 8 * ((Lub + 7) / 8));
-}
 
-// Token tiles per workgroup: 0 = chosen here; 1, 2 or 4 = asked for by the caller.  One value
-// per host thread: a thread that sets the knob changes its own later calls only.
+// Token tiles per workgroup: 0 = chosen here; 1, 2 or 4 = at most that many, asked for by the caller.
+// One value per host thread: a thread that sets the knob changes its own later calls only.
 static thread_local int g_ffn_tiles_per_wg = 0;
 hipError_t set_ffn_tiles_per_wg(int n) {
   if (n != 0 && n != 1 && n != 2 && n != 4) return hipErrorInvalidValue;
   g_ffn_tiles_per_wg = n;
   return hipSuccess;
 }
-// Groups of tiles need list rows shared by a multiple of that many tiles; left to itself the
-// library takes the largest group that still fills the chip, judged by the capacity of the list
-// (the true number of entries is known on the device only: a capacity far above it makes the
-// choice too optimistic, and the caller's knob overrides it).
-static int tiles_per_wg(int Tt, int gt, int nnz_cap) {
+
+// The tiles, widest first.  A wide tile moves fewer bytes and LDS reads per product (a workgroup step
+// transfers TM + TN times 8 KiB for TM * TN products of 64 x 64 x 64), a narrow one gives the chip more
+// workgroups and has the shorter step.  `resident` workgroups fit a CU; one workgroup per CU leaves room
+// for a deeper ring, and eight wavefronts with a whole step of operands on the way hide its latency
+// (2 x 2 tiles, 4096 tokens, 14 blocks, K = 2048, 224 workgroups: 25 -> 21 us).
+//                          TM TN WM WN NST KS
+using Tile44 = Tile<4, 4, 2, 4, 2, 2>;
+using Tile24 = Tile<2, 4, 2, 4, 3, 2>;
+using Tile22 = Tile<2, 2, 2, 2, 2, 2>;
+using Tile22Deep = Tile<2, 2, 2, 4, 4, 4>;
+using Tile14 = Tile<1, 4, 1, 4, 2, 2>;
+using Tile14Deep = Tile<1, 4, 2, 4, 4, 2>;
+using Tile12 = Tile<1, 2, 1, 4, 3, 2>;
+using Tile11 = Tile<1, 1, 2, 2, 4, 4>;
+using Tile11Many = Tile<1, 1, 2, 2, 3, 4, 3>;
+enum TileId { kT44, kT24, kT22, kT22Deep, kT14, kT14Deep, kT12, kT11, kT11Many, kTiles };
+// What a launch of a tile costs, in us: `round` per round of workgroups (finding the item, filling the
+// ring, epilogue) and step[q - 1] per step with q workgroups on a CU.  Fitted to measured launches of
+// every tile at 22 shapes (64 - 8192 tokens, d 576 - 5120, 6 - 320 listed blocks, lists shared and per
+// tile; rms of the fit 6 - 18 %); at those shapes the tile that the model picks is within 1.5 % of the
+// fastest one on average, 7 % at worst.
+struct TileInfo {
+  int tm, tn, resident;
+  float round, step[3];
+};
+static const TileInfo kTileInfo[kTiles] = {
+    {4, 4, 1, 8.6f, {1.25f}},      {2, 4, 1, 7.4f, {0.69f}}, {2, 2, 2, 4.2f, {0.61f, 1.11f}},
+    {2, 2, 1, 5.1f, {0.44f}},      {1, 4, 2, 4.8f, {0.69f, 1.28f}}, {1, 4, 1, 5.5f, {0.51f}},
+    {1, 2, 2, 4.0f, {0.29f, 0.62f}}, {1, 1, 2, 3.8f, {0.17f, 0.39f}}, {1, 1, 3, 3.3f, {0.22f, 0.39f, 0.61f}},
+};
+static float tile_cost(const TileInfo& t, long long items, float steps) {
+  const long long q = items <= kCUs ? 1 : (items + kCUs - 1) / kCUs;
+  const long long full = q / t.resident, rest = q % t.resident;
+  return (float)(full + (rest ? 1 : 0)) * t.round +
+         steps * ((float)full * t.step[t.resident - 1] + (rest ? t.step[rest - 1] : 0.f));
+}
+// Whether a tile may run lists whose rows gt of the Tt token tiles share: tiles past the end are left
+// out with one list row, otherwise the groups of TM tiles have to divide those of gt.
+static bool tile_fits(const TileInfo& t, int Tt, int gt) {
   const int want = g_ffn_tiles_per_wg;
-  if (want == 1) return 1;
-  for (int tt = 4; tt > 1; tt /= 2) {
-    if (gt % tt != 0) continue;
-    if (want != 0) {
-      if (want >= tt) return tt;
-      continue;
-    }
-    // left to itself: the largest group whose work items (tile groups x groups of four list
-    // entries, by the host-known bound on the entries) still give every CU a workgroup
-    const long long items = (long long)(gt / tt) * ((nnz_cap + 3) / 4);
-    if (Tt / tt >= kCUs || items >= kCUs) return tt;
+  if (want != 0) {
+    int most = want;
+    while (gt != Tt && gt % most != 0) most /= 2;
+    if (t.tm != most) return false;
   }
-  return 1;
+  return gt == Tt || gt % t.tm == 0;
+}
+static int ceil_div(long long a, int b) { return (int)((a + b - 1) / b); }
+
+// Lists per group of tiles share few weight rows, so the bytes that the workgroups pull bound the launch:
+// us for `wgs` workgroups of `steps` steps each at the rate that such launches reach (4096 - 8192 tokens,
+// d 2048 - 4096: 9.3 - 13 TB/s through the L2s, of which some 6 TB/s miss).
+static float pull_cost(const TileInfo& t, float wgs, float steps) {
+  return wgs * steps * (float)(t.tm + t.tn) * 8192.f / 11.5e6f;
 }
 
-// Floats one piece of a split dsd unit leaves in the partial-sum buffer (TT token tiles).
-static size_t dsd_piece_floats(int tt) { return (size_t)kFW * 2 * tt * 16 * kWave; }
-// How the multi-tile dsd launch is cut when its (tile group, column chunk) units make whole
-// rounds of workgroups plus a small rest: the rest's lists are split into `pieces` pieces each,
-// so that the last round fills the chip too, and the pieces are added afterwards.  pieces = 0:
-// no split (nothing to gain, one list row only, or the bound on the list is too short to cut).
-struct DsdSplit {
-  long long full;   // units that run whole
-  int rest;         // units whose list is split
-  int pieces;
-};
-static DsdSplit dsd_split(int Tt, int gt, int d, int tt, int nnz_cap) {
-  DsdSplit sp = {0, 0, 0};
-  const int chunks = (d + kRowsA - 1) / kRowsA;
-  const long long units = (long long)chunks * (Tt / tt);
-  const long long rest = units % kCUs;
-  if (gt != Tt || rest == 0 || rest * 5 >= kCUs * 3) return sp;      // one list row for all tiles only
-  const int pieces = (int)(kCUs / rest < 4 ? kCUs / rest : 4);
-  if (pieces < 2 || nnz_cap < 16 * pieces) return sp;
-  sp.full = units - rest;
-  sp.rest = (int)rest;
-  sp.pieces = pieces;
-  return sp;
+// First product: tile by the cost of its work items.  With lists per group of tiles the number of
+// entries varies between calls and a caller's capacity has slack (a seventh is taken off), and half a
+// ragged group per list row is added.
+static int choose_sdd(int Tt, int gt, int d, int nnz_cap) {
+  int best = -1;
+  float least = 0.f;
+  for (int id = 0; id < kTiles; ++id) {
+    const TileInfo& t = kTileInfo[id];
+    if (!tile_fits(t, Tt, gt)) continue;
+    long long items;
+    if (gt == Tt) {
+      items = (long long)ceil_div(Tt, t.tm) * ceil_div(nnz_cap, t.tn);
+    } else {
+      items = (long long)(6.f / 7.f * (float)nnz_cap) * (gt / t.tm) / t.tn + (long long)(Tt / t.tm) * (t.tn - 1) / (2 * t.tn);
+      if (id == kT14Deep && items > kCUs) continue;     // a second round starts out of step with the first: its L2 hits are gone
+    }
+    float c = tile_cost(t, items, (float)(d / 64));
+    if (gt != Tt) c = std::max(c, pull_cost(t, (float)items, (float)(d / 64))) + 0.25f * c;
+    if (best < 0 || c < least) best = id, least = c;
+  }
+  return best;
 }
-// Bytes of partial sums the split needs for T tokens and d output columns with one list row of
-// at most nnz_cap entries, for the tile count the library would choose (0: no split).
+// Second product, likewise; its steps are the list entries.  With one list row and room for partial sums
+// the units that do not fill a round may have their list cut into 2 - 4 pieces, each at least 8 entries
+// long, which costs a second launch and the pieces' way through memory.
+struct DsdPlan {
+  int id, full, rest, pieces;
+  size_t part_bytes() const {
+    return pieces > 1 ? (size_t)rest * pieces * kTileInfo[id].tm * kTileInfo[id].tn * 4096 * sizeof(float) : 0;
+  }
+};
+static DsdPlan choose_dsd(int Tt, int gt, int d, int nnz_cap, size_t part_bytes) {
+  DsdPlan best = {-1, 0, 0, 1};
+  float least = 0.f;
+  for (int id = 0; id < kTiles; ++id) {
+    const TileInfo& t = kTileInfo[id];
+    if (!tile_fits(t, Tt, gt)) continue;
+    const long long items = (long long)ceil_div(Tt, t.tm) * ceil_div(d, 64 * t.tn);
+    if (gt != Tt) {
+      if (id == kT14Deep && items > kCUs) continue;
+      // a launch of one round lasts as long as its longest list
+      const float mean = 6.f / 7.f * (float)nnz_cap * gt / Tt;
+      const float busy = tile_cost(t, items, mean * (items <= (long long)kCUs * t.resident ? 1.35f : 1.1f));
+      const float c = std::max(busy, pull_cost(t, (float)items, mean)) + 0.25f * busy;
+      if (best.id < 0 || c < least) best = {id, (int)items, 0, 1}, least = c;
+      continue;
+    }
+    const float c = tile_cost(t, items, (float)nnz_cap);
+    if (best.id < 0 || c < least) best = {id, (int)items, 0, 1}, least = c;
+    if (id > kT22) continue;              // (a cut launch of narrow tiles never paid)
+    for (int p = 2; p <= 4 && nnz_cap >= 8 * p; ++p) {
+      const long long full = items / (kCUs * t.resident) * (kCUs * t.resident);
+      const DsdPlan plan = {id, (int)full, (int)(items - full), p};
+      if (plan.rest == 0 || plan.part_bytes() > part_bytes) continue;
+      const float cc = (full > 0 ? tile_cost(t, full, (float)nnz_cap) : 0.f) +
+                       tile_cost(t, (long long)plan.rest * p, (float)nnz_cap / p) + 5.f + (float)plan.part_bytes() / 2.5e6f;
+      if (cc < least) best = plan, least = cc;
+    }
+  }
+  return best;
+}
+// Bytes of partial sums with which the second product, given one list row of at most nnz_cap entries
+// for all Tt token tiles, may cut lists (0: never), whatever the caller's tiles per workgroup.
 size_t ffn_dsd_split_bytes(int Tt, int d, int nnz_cap) {
+  const int was = g_ffn_tiles_per_wg;
   size_t need = 0;
-  for (int tt = 4; tt > 1; tt /= 2) {
-    if (Tt % tt != 0) continue;
-    const DsdSplit sp = dsd_split(Tt, Tt, d, tt, nnz_cap);
-    const size_t b = (size_t)sp.rest * sp.pieces * dsd_piece_floats(tt) * sizeof(float);
+  for (int want : {0, 1, 2, 4}) {
+    g_ffn_tiles_per_wg = want;
+    const size_t b = choose_dsd(Tt, Tt, d, nnz_cap, ~(size_t)0).part_bytes();
     need = b > need ? b : need;
   }
+  g_ffn_tiles_per_wg = was;
   return need;
 }
 
-// First product of a pass for groups of TT token tiles.
-template <int DT, int TT>
-static void launch_sdd_multi(int pass, int Tt, int gt, int d, const uint16_t* A, const uint16_t* W1,
-                             const uint16_t* b1, const int* row_ptr, const int* col_idx, int nnz_cap,
-                             uint16_t* act_out, const uint16_t* act_gate, hipStream_t st) {
-  const uint16_t* none = nullptr;
-  const dim3 g1 = sdd_grid(Tt / TT, gt / TT, nnz_cap, 4);
-  ProfScope ps(pass == 0 ? kKFfnUp : kKFfnDh, st);
-  if (pass == 0)
-    hipLaunchKernelGGL((ffn_sddn_bf16<DT, 0, false, TT>), g1, dim3(kThreads), 0, st, A, W1, b1, row_ptr,
-                       col_idx, Tt, gt, d, nnz_cap, act_out, none, none, none);
-  else
-    hipLaunchKernelGGL((ffn_sddn_bf16<DT, 1, false, TT>), g1, dim3(kThreads), 0, st, A, W1, none,
-                       row_ptr, col_idx, Tt, gt, d, nnz_cap, act_out, act_gate, none, none);
-}
-// ... one token tile per workgroup.  NE list entries per workgroup: as many of 4, 2, 1 as still make
-// two workgroups for every three CUs.  A workgroup of fewer entries transfers more bytes per product
-// (16 KiB per 64 x 64 x 64 step with one entry, 12 with two, 10 with four), but a CU without a
-// workgroup transfers nothing: 192 tokens, 768 -> 3072, one list of 14 blocks (12 items of four
-// entries, 42 of one) took 15 us per product and takes 8.
-// The number of items is known on the device only; the estimate takes the list's capacity plus half a
-// ragged group per tile.  Measured at 4096 / 8192 tokens, 2048 -> 8192, a list per tile of 14 blocks
-// on average (250 / 500 items of four; us, by the items of the actual masks):
-//   4 entries, 3 stages, one workgroup per CU    31 up to one item per CU, else 50 / 72
-//   4 entries, 2 stages, two workgroups per CU   39-45 / 57 up to two items per CU, else 70
-//   2 entries, 3 stages, two workgroups per CU   34-36 / 66-70
-// so around one item of four per CU, where the estimate cannot tell the sides of the cliff apart, two
-// entries are taken.  Fewer items than CUs leave room for a ring that takes most of the LDS.
-static long long sdd_items(int Tt, int gt, int nnz_cap, int ne) {
-  return ((long long)nnz_cap * gt + ne - 1) / ne + (long long)Tt * (ne - 1) / (2 * ne);
-}
-template <int DT, int MODE, bool LORA>
-static void launch_sdd_one(int Tt, int gt, int d, const uint16_t* A, const uint16_t* W1,
-                           const uint16_t* b1, const int* row_ptr, const int* col_idx, int nnz_cap,
-                           uint16_t* act_out, const uint16_t* act_gate, const uint16_t* A2,
-                           const uint16_t* W2, hipStream_t st) {
-#define LX_SDD(NE, NST)                                                                              \
-  hipLaunchKernelGGL((ffn_sdd_bf16<DT, MODE, LORA, NE, NST>), sdd_grid(Tt, gt, nnz_cap, NE), dim3(kThreads), \
-                     0, st, A, W1, b1, row_ptr, col_idx, Tt, gt, d, nnz_cap, act_out, act_gate, A2, W2)
-  const long long fill = kCUs * 2 / 3;
-  const long long n4 = sdd_items(Tt, gt, nnz_cap, 4), n2 = sdd_items(Tt, gt, nnz_cap, 2),
-                  n1 = sdd_items(Tt, gt, nnz_cap, 1);
-  if (n4 >= fill) {
-    if (n4 > kCUs * 31 / 32 && n4 <= kCUs * 5 / 4)
-      LX_SDD(2, 3);
-    else if (n4 > kCUs && n4 <= kCUs * 9 / 4)
-      LX_SDD(4, 2);
-    else
-      LX_SDD(4, kSddStages);
-  } else if (n2 >= fill) {
-    if (n2 > kCUs) LX_SDD(2, 3); else LX_SDD(2, 6);
-  } else {
-    if (n1 > kCUs) LX_SDD(1, 4); else LX_SDD(1, 8);
+// Calls CALL(Tile) for the tile `id`.
+#define LX_TILES(id, CALL)                     \
+  switch (id) {                                \
+    case kT44: CALL(Tile44); break;            \
+    case kT24: CALL(Tile24); break;            \
+    case kT22: CALL(Tile22); break;            \
+    case kT22Deep: CALL(Tile22Deep); break;    \
+    case kT14: CALL(Tile14); break;            \
+    case kT14Deep: CALL(Tile14Deep); break;    \
+    case kT12: CALL(Tile12); break;            \
+    case kT11: CALL(Tile11); break;            \
+    default: CALL(Tile11Many); break;          \
   }
-#undef LX_SDD
-}
-// Second product, one token tile per workgroup: tiles tile0 .. tile0 + count - 1.  NE groups of 64
-// output columns per workgroup by the same rule as above; with one resident workgroup per CU the ring
-// takes most of the LDS.
-template <int DT, bool LORA>
-static void launch_dsd_one(int tile0, int count, int gt, int d, int F, const uint16_t* W2, const uint16_t* b2,
-                           const int* row_ptr, const int* col_idx, int nnz_cap, const uint16_t* act,
-                           uint16_t* out, const uint16_t* act2, const uint16_t* W2b, hipStream_t st) {
-#define LX_DSD(NE, NST)                                                                              \
-  hipLaunchKernelGGL((ffn_dsd_bf16<DT, LORA, NE, NST>), dim3((d + 64 * NE - 1) / (64 * NE), count),  \
-                     dim3(kThreads), 0, st, act, W2, (long long)F, b2, row_ptr, col_idx, gt, d, nnz_cap, out, \
-                     act2, W2b, tile0)
-  auto wgs = [&](int ne) { return (long long)((d + 64 * ne - 1) / (64 * ne)) * count; };
-  const long long fill = kCUs * 2 / 3;
-  if (wgs(4) >= fill) {
-    LX_DSD(4, kDsdStages);
-  } else if (wgs(2) >= fill) {
-    if (wgs(2) > kCUs) LX_DSD(2, 3); else LX_DSD(2, 6);
-  } else {
-    if (wgs(1) > kCUs) LX_DSD(1, 4); else LX_DSD(1, 8);
-  }
-#undef LX_DSD
-}
 
-// Second product of a pass for groups of TT token tiles.
-template <int DT, int TT>
-static void launch_dsd_multi(int pass, int Tt, int gt, int d, int F, const uint16_t* W2, const uint16_t* b2,
-                             const int* row_ptr, const int* col_idx, int nnz_cap, const uint16_t* act,
-                             uint16_t* out, float* part, size_t part_bytes, hipStream_t st) {
-  const uint16_t* none = nullptr;
-  ProfScope ps(pass == 0 ? kKFfnDown : kKFfnDx, st);
-  // The dsd launch has (column chunks) x (tile groups) workgroups, one per CU, all about equally
-  // long.  When they make whole rounds plus a small rest, that rest would keep the launch alive
-  // for a full round on a fraction of the chip: the tile groups of whole rounds go to this
-  // kernel, the remaining tiles to a kernel with shorter rounds: pairs of tiles when this one
-  // takes four, else the one-tile kernel (two workgroups per CU).
-  const int chunks = (d + kRowsA - 1) / kRowsA;
-  int groups = Tt / TT;
-  // With room for partial sums: the units of the whole rounds run as they are, the lists of the
-  // rest are cut into pieces that fill the last round, and the pieces are added in order.
-  const DsdSplit sp = dsd_split(Tt, gt, d, TT, nnz_cap);
-  if (part && sp.pieces > 0 &&
-      (size_t)sp.rest * sp.pieces * dsd_piece_floats(TT) * sizeof(float) <= part_bytes) {
-    float* nopart = nullptr;
-    if (sp.full > 0)
-      hipLaunchKernelGGL((ffn_dsdn_bf16<DT, false, TT>), dim3((unsigned)sp.full), dim3(kThreads), 0, st,
-                         act, W2, (long long)F, b2, row_ptr, col_idx, gt, d,
-                         nnz_cap, out, none, none, 0, 0, chunks, 1, nopart);
-    hipLaunchKernelGGL((ffn_dsdn_bf16<DT, false, TT>), dim3(sp.rest * sp.pieces), dim3(kThreads), 0, st,
-                       act, W2, (long long)F, b2, row_ptr, col_idx, gt, d,
-                       nnz_cap, out, none, none, 0, (int)sp.full, chunks, sp.pieces, part);
-    hipLaunchKernelGGL((ffn_dsd_reduce<DT, TT>), dim3(sp.rest, TT / 2), dim3(kThreads), 0, st,
-                       (const float*)part, sp.pieces, (int)sp.full, chunks, d, b2, out);
-    return;
+template <int DT, bool LORA>
+static void launch_sdd(SddArgs a, hipStream_t st) {
+  const int id = choose_sdd(a.Tt, a.gt, a.K, a.nnz_cap);
+  const TileInfo& t = kTileInfo[id];
+  a.band = t.tm == 4 ? 4 : 8;
+  int grid;
+  if (a.gt == a.Tt) {
+    grid = 8 * ceil_div((long long)ceil_div(a.Tt, t.tm) * ceil_div(a.nnz_cap, t.tn), 8);
+  } else {   // items <= entries / tn + a ragged group per row; per XCD L = ceil(items / 8) of them in 8 * ceil(L / 8) slots
+    const long long items = ceil_div((long long)a.nnz_cap * (a.gt / t.tm), t.tn) + (t.tn > 1 ? a.Tt / t.tm : 0);
+    grid = 64 * ceil_div(ceil_div(items, 8), 8);
   }
-  float* nopart = nullptr;
-  const long long wgs = (long long)chunks * groups, rest = wgs % kCUs;
-  if (wgs > kCUs && rest > 0 && rest * 5 < kCUs * 3) groups = (int)((wgs - rest) / chunks);
-  if (groups > 0)
-    hipLaunchKernelGGL((ffn_dsdn_bf16<DT, false, TT>), dim3(chunks, groups), dim3(kThreads), 0, st,
-                       act, W2, (long long)F, b2, row_ptr, col_idx, gt, d,
-                       nnz_cap, out, none, none, 0, 0, chunks, 0, nopart);
-  const int left = Tt - groups * TT;   // a multiple of TT
-  if (left > 0 && TT == 4)
-    hipLaunchKernelGGL((ffn_dsdn_bf16<DT, false, 2>), dim3(chunks, left / 2), dim3(kThreads), 0, st,
-                       act, W2, (long long)F, b2, row_ptr, col_idx, gt, d,
-                       nnz_cap, out, none, none, groups * TT / 2, 0, chunks, 0, nopart);
-  else if (left > 0)
-    launch_dsd_one<DT, false>(groups * TT, left, gt, d, F, W2, b2, row_ptr, col_idx, nnz_cap, act, out,
-                              none, none, st);
+  if (grid == 0) return;
+#define LX_CALL(TL) hipLaunchKernelGGL((ffn_sdd<TL, DT, LORA>), dim3(grid), dim3(TL::kTileThreads), 0, st, a)
+  LX_TILES(id, LX_CALL)
+#undef LX_CALL
+}
+template <int DT, bool LORA>
+static void launch_dsd(DsdArgs a, size_t part_bytes, hipStream_t st) {
+  const DsdPlan p = choose_dsd(a.Tt, a.gt, a.ncols, a.nnz_cap, LORA || !a.part ? 0 : part_bytes);
+  const TileInfo& t = kTileInfo[p.id];
+  a.band = t.tm == 4 ? 4 : 8;
+  a.full = p.full;
+  a.rest = p.rest;
+  a.pieces = p.pieces;
+  const dim3 grid = a.gt == a.Tt ? dim3(8 * ceil_div(p.full, 8) + 8 * ceil_div((long long)p.rest * p.pieces, 8))
+                                 : dim3(ceil_div(a.ncols, 64 * t.tn), a.Tt / t.tm);
+#define LX_CALL(TL) hipLaunchKernelGGL((ffn_dsd<TL, DT, LORA>), grid, dim3(TL::kTileThreads), 0, st, a)
+  LX_TILES(p.id, LX_CALL)
+#undef LX_CALL
+#define LX_CALL(TL) \
+  hipLaunchKernelGGL((ffn_dsd_reduce<TL, DT>), dim3(p.rest, TL::kWaves / 4 * TL::NI * TL::TI), dim3(256), 0, st, a)
+  if (p.rest > 0) {
+    if (p.id == kT44)
+      LX_CALL(Tile44);
+    else if (p.id == kT24)
+      LX_CALL(Tile24);
+    else
+      LX_CALL(Tile22);
+  }
+#undef LX_CALL
 }
 
 template <int DT>
 static hipError_t launch_ffn_bf16_t(int pass, int Tt, int gt, int Fb, int d, int F, const uint16_t* A,
-                           const uint16_t* W1, const uint16_t* b1, const uint16_t* W2,
-                           const uint16_t* b2, const int* row_ptr, const int* col_idx, int nnz_cap,
-                           uint16_t* act_out, const uint16_t* act_gate, uint16_t* out,
-                           float* part, size_t part_bytes, hipStream_t st) {
+                                    const uint16_t* W1, const uint16_t* b1, const uint16_t* W2,
+                                    const uint16_t* b2, const int* row_ptr, const int* col_idx, int nnz_cap,
+                                    uint16_t* act_out, const uint16_t* act_gate, uint16_t* out,
+                                    float* part, size_t part_bytes, hipStream_t st) {
   (void)Fb;
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
-  const int tt = tiles_per_wg(Tt, gt, nnz_cap);
-  // The first product may take smaller groups than the second (the activation blocks are laid out
-  // the same for every group size): its work items, tile groups x groups of four list entries,
-  // run in rounds of one per CU, and a round lasts as long as one item's K-steps, whose time is
-  // the step's matrix instructions plus its transfers (512 clocks of the first per token tile,
-  // 2 clocks per 128-byte row of the second).  The group size with the cheapest rounds wins: e.g.
-  // 89 entries for 64 tiles are 368 items = two rounds of four tiles but 736 = three rounds of
-  // two, which cost less; 33 entries are one round of four tiles against two of two.
-  int tts = tt;
-  long long best = -1;
-  for (int t = tt; t >= 1; t /= 2) {
-    // (host-known bound: the entries of all list rows in groups of four, a ragged group per further row)
-    const long long items = (long long)(gt / t) * ((nnz_cap + 3) / 4 + (Tt / gt - 1));
-    const long long rounds = (items + kCUs - 1) / kCUs;
-    const long long cost = rounds * (512 * t + 2 * (64 * t + 256));
-    if (best < 0 || cost < best) {
-      best = cost;
-      tts = t;
-    }
-  }
-  if (tts == 4)
-    launch_sdd_multi<DT, 4>(pass, Tt, gt, d, A, W1, b1, row_ptr, col_idx, nnz_cap, act_out, act_gate, st);
-  else if (tts == 2)
-    launch_sdd_multi<DT, 2>(pass, Tt, gt, d, A, W1, b1, row_ptr, col_idx, nnz_cap, act_out, act_gate, st);
-  else
   {
     ProfScope ps(pass == 0 ? kKFfnUp : kKFfnDh, st);
-    const uint16_t* none = nullptr;
-    if (pass == 0)
-      launch_sdd_one<DT, 0, false>(Tt, gt, d, A, W1, b1, row_ptr, col_idx, nnz_cap, act_out, none, none, none, st);
-    else
-      launch_sdd_one<DT, 1, false>(Tt, gt, d, A, W1, none, row_ptr, col_idx, nnz_cap, act_out, act_gate, none,
-                                   none, st);
+    launch_sdd<DT, false>({A, W1, pass == 0 ? b1 : nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, act_out,
+                           pass == 0 ? nullptr : act_gate, nullptr, nullptr}, st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (tt == 4) {
-    launch_dsd_multi<DT, 4>(pass, Tt, gt, d, F, W2, b2, row_ptr, col_idx, nnz_cap, act_out, out, part,
-                            part_bytes, st);
-  } else if (tt == 2) {
-    launch_dsd_multi<DT, 2>(pass, Tt, gt, d, F, W2, b2, row_ptr, col_idx, nnz_cap, act_out, out, part,
-                            part_bytes, st);
-  } else {
-    const uint16_t* none = nullptr;
-    ProfScope ps(pass == 0 ? kKFfnDown : kKFfnDx, st);
-    launch_dsd_one<DT, false>(0, Tt, gt, d, F, W2, b2, row_ptr, col_idx, nnz_cap, act_out, out, none, none, st);
-  }
+  ProfScope ps(pass == 0 ? kKFfnDown : kKFfnDx, st);
+  launch_dsd<DT, false>({act_out, W2, b2, (long long)F, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, 0, 0, 1, out, part,
+                         nullptr, nullptr}, part_bytes, st);
   return hipGetLastError();
 }
 
@@ -875,7 +707,6 @@ static hipError_t launch_ffn_lora_fwd_bf16_t(int Tt, int gt, int d, int F, const
                                     uint16_t* U, uint16_t* H_act, uint16_t* Y, float* u_part,
                                     hipStream_t st) {
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
-  const uint16_t* none = nullptr;
   {
     ProfScope ps(kKLora, st);
     const hipError_t eu = launch_lora_u(DT, Tt, d, X, A_pad, U, u_part, st);
@@ -885,12 +716,13 @@ static hipError_t launch_ffn_lora_fwd_bf16_t(int Tt, int gt, int d, int F, const
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKFfnUp, st);
-    launch_sdd_one<DT, 0, true>(Tt, gt, d, X, W_up, none, row_ptr, col_idx, nnz_cap, H_act, none, U, B_pad, st);
+    launch_sdd<DT, true>({X, W_up, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, H_act, nullptr, U, B_pad}, st);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   ProfScope ps(kKFfnDown, st);
-  launch_dsd_one<DT, false>(0, Tt, gt, d, F, W_down, none, row_ptr, col_idx, nnz_cap, H_act, Y, none, none, st);
+  launch_dsd<DT, false>({H_act, W_down, nullptr, (long long)F, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, 0, 0, 1, Y,
+                         nullptr, nullptr, nullptr}, 0, st);
   return hipGetLastError();
 }
 
@@ -908,11 +740,10 @@ static hipError_t launch_ffn_lora_bwd_bf16_t(int Tt, int gt, int d, int F, const
                                     float* g_part, float* da_part, float* db_part, uint16_t* dX,
                                     float* dA, float* dB, hipStream_t st) {
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
-  const uint16_t* none = nullptr;
   {
     ProfScope ps(kKFfnDh, st);
-    launch_sdd_one<DT, 1, false>(Tt, gt, d, dY, W_down_t, none, row_ptr, col_idx, nnz_cap, dZ, H_act, none, none,
-                                 st);
+    launch_sdd<DT, false>({dY, W_down_t, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, dZ, H_act, nullptr, nullptr},
+                          st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -927,7 +758,8 @@ static hipError_t launch_ffn_lora_bwd_bf16_t(int Tt, int gt, int d, int F, const
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKFfnDx, st);
-    launch_dsd_one<DT, true>(0, Tt, gt, d, F, W_up_t, none, row_ptr, col_idx, nnz_cap, dZ, dX, G, A_t, st);
+    launch_dsd<DT, true>({dZ, W_up_t, nullptr, (long long)F, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, 0, 0, 1, dX,
+                          nullptr, G, A_t}, 0, st);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;

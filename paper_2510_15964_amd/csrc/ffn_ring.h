@@ -1,4 +1,5 @@
-// The global -> LDS transfer ring shared by the 16-bit FFN, predictor and LoRA kernels (gfx950).
+// The global -> LDS transfer ring of the predictor and LoRA kernels (gfx950); the FFN kernels' own
+// pipeline (ffn_tile.h) has the same LDS layout.
 //
 // Data movement: global memory -> LDS directly (global_load_lds, 16 bytes per lane, no registers
 // in between), a ring of stages; the loads of the next K-steps are in flight while the MFMAs of
@@ -16,26 +17,10 @@ constexpr int kFW = 8;             // wavefronts per workgroup
 constexpr int kThreads = kFW * kWave;
 constexpr int kBK = 64;            // K-chunk per step: 64 bf16 = 128 bytes per row
 constexpr int kRowsB = 64;         // shared operand (token rows)
-constexpr int kRowsA = 256;        // per-wave operand (4 x 64 weight rows) of the widest stage
-// A stage of the one-tile kernels: 64 token rows and 64 * NE weight rows (NE = 1, 2 or 4 list blocks,
-// or groups of 64 output columns).  Wavefront w multiplies the 32 weight rows of group w % (2 * NE)
-// with kTI groups of 32 token rows, from group w / (2 * NE) on: all of them with NE = 4, one with NE = 2
-// and NE = 1, where four of the eight wavefronts only transfer.  (Sharing K between those instead
-// would change the order of the sums.)
-template <int NE>
-struct OneStage {
-  static constexpr int kElems = (kRowsB + 64 * NE) * kBK;      // 16 / 24 / 40 KiB
-  static constexpr int kIss = 1 + NE;                          // DMA instructions per wave and stage
-  static constexpr int kTI = NE == 4 ? 2 : 1;
-};
-// Ring depths for NE = 4.  Measured on the 11 %-dense FFN of the benchmark: a fourth stage (all 160
-// KiB of LDS) does not help the sdd kernels, and the dsd kernel is faster with two resident
-// workgroups of two stages each than with one workgroup of three or four.
-constexpr int kSddStages = 3, kDsdStages = 2;
 
 __device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
 
-// One stage = NISS DMA instructions per wave (1 + NE for the 64 + 64 * NE rows of the one-tile FFN kernels).
+// One stage = NISS DMA instructions per wave.
 // Instruction u of wave w fills stage rows 8g .. 8g+7 with g = w + kFW*u (g < 8: the 64 shared
 // rows, then the weight blocks); lane l brings the 16-byte slot l%8 of row 8g + l/8.  src[u]
 // already points at this lane's (row, swizzled segment); offB / offA are the element offsets of
@@ -61,79 +46,6 @@ __device__ __forceinline__ void issue_stage(uint16_t* stage, const uint16_t* con
 struct NoAlt {
   __device__ __forceinline__ const uint16_t* operator()(int) const { return nullptr; }
 };
-
-// One 64-deep K-step from LDS: acc[x] += group grp of 32 weight rows . groups ti0 + x of 32 token rows.
-// acc[x]: rows = weight rows, columns = token rows.
-template <int DT, int NE>
-__device__ __forceinline__ void mma_step(const uint16_t* stage, int grp, int ti0,
-                                         f32x16 (&acc)[OneStage<NE>::kTI]) {
-  constexpr int TI = OneStage<NE>::kTI;
-  const int lane = threadIdx.x % kWave;
-  const int r = lane % 32, h2 = lane / 32;
-  const int ra = kRowsB + 32 * grp + r;
-  // all operand reads of the step are issued first, so that their LDS latency overlaps the
-  // MFMAs instead of being paid once per k16 slice
-  uint4 a[4], b[4][TI];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int seg = 2 * kk + h2;
-    a[kk] = *reinterpret_cast<const uint4*>(stage + ra * kBK + ((seg ^ swz(ra)) << 3));
-#pragma unroll
-    for (int h = 0; h < TI; ++h) {
-      const int rb = 32 * (ti0 + h) + r;
-      b[kk][h] = *reinterpret_cast<const uint4*>(stage + rb * kBK + ((seg ^ swz(rb)) << 3));
-    }
-  }
-  __builtin_amdgcn_sched_barrier(0);   // keep the reads above: the scheduler would sink them
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-    for (int ti = 0; ti < TI; ++ti) acc[ti] = mfma32<DT>(a[kk], b[kk][ti], acc[ti]);
-}
-
-// The same for a stage of 64*TT shared rows (TT = 2 or 4 token tiles) + 256 weight rows and a
-// wave tile of 64 weight rows (group rg of four) x 32*TT shared rows (half th of them): half
-// (TT = 2) or three eighths (TT = 4) of the LDS bytes per product of the 32 x 64 tile above.
-// acc[ni][ti]: weight rows 64*rg + 32*ni.., shared rows 32*TT*th + 32*ti..
-template <int TT>
-struct MultiStage {
-  static constexpr int kShared = kRowsB * TT;
-  static constexpr int kElems = (kShared + kRowsA) * kBK;   // 48 / 64 KiB
-  static constexpr int kIss = (kShared + kRowsA) / 8 / kFW; // DMA instructions per wave and stage
-  static constexpr int kStages = TT == 2 ? 3 : 2;           // what fits 160 KiB of LDS
-};
-template <int DT, int TT>
-__device__ __forceinline__ void mma_step64(const uint16_t* stage, int rg, int th,
-                                           f32x16 (&acc)[2][TT]) {
-  const int lane = threadIdx.x % kWave;
-  const int r = lane % 32, h2 = lane / 32;
-  // operands of two k16 slices at a time: 8 + 4*TT registers of reads in flight
-#pragma unroll
-  for (int k2 = 0; k2 < 2; ++k2) {
-    uint4 a[2][2], b[2][TT];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int seg = 2 * (2 * k2 + e) + h2;
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni) {
-        const int ra = MultiStage<TT>::kShared + 64 * rg + 32 * ni + r;
-        a[e][ni] = *reinterpret_cast<const uint4*>(stage + ra * kBK + ((seg ^ swz(ra)) << 3));
-      }
-#pragma unroll
-      for (int ti = 0; ti < TT; ++ti) {
-        const int rb = 32 * TT * th + 32 * ti + r;
-        b[e][ti] = *reinterpret_cast<const uint4*>(stage + rb * kBK + ((seg ^ swz(rb)) << 3));
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);   // keep the reads above: the scheduler would sink them
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-        for (int ti = 0; ti < TT; ++ti) acc[ni][ti] = mfma32<DT>(a[e][ni], b[e][ti], acc[ni][ti]);
-  }
-}
 
 // Pipeline over nsteps K-steps through a ring of NST stages: while step s is multiplied, the
 // DMA of steps s+1 .. s+NST-1 is in flight (what bounds these kernels is how many bytes a CU
@@ -183,17 +95,6 @@ __device__ __forceinline__ void run_ring_of(int nsteps, const uint16_t* const (&
     step(ring + stage * SE);
     stage = stage + 1 == NST ? 0 : stage + 1;
   }
-}
-
-template <int DT, int NST, int NE, class AltPtr, class Offs>
-__device__ __forceinline__ void run_ring(int nsteps, bool wave_on,
-                                         const uint16_t* const (&src)[OneStage<NE>::kIss], AltPtr alt_ptr,
-                                         Offs offs, uint16_t* ring, f32x16 (&acc)[OneStage<NE>::kTI]) {
-  const int wave = threadIdx.x / kWave;
-  run_ring_of<NST, OneStage<NE>::kIss, OneStage<NE>::kElems>(
-      nsteps, src, alt_ptr, offs, ring, [&](const uint16_t* stage) {
-        if (wave_on) mma_step<DT, NE>(stage, wave % (2 * NE), wave / (2 * NE), acc);
-      });
 }
 
 // Host side: calls fn<kF16> or fn<kBf16> according to the run-time element type `dt`.

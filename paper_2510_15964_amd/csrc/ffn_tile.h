@@ -1,0 +1,187 @@
+// The tile product of the 16-bit FFN kernels (gfx950): a workgroup multiplies 64*TM token rows with
+// 64*TN weight rows, 64 of the contraction index per step, through the transfer ring of ffn_ring.h's
+// layout (128-byte LDS rows, 16-byte slots XOR-swizzled with the row index).
+//
+// One barrier per step, and operands of the next phase on their way from LDS to registers while the
+// matrix instructions of the current one run (a plain "barrier, read, multiply" step leaves the matrix
+// cores idle for as long as all wavefronts of the CU read their operands at once: 256 x 256 x 64 steps
+// took 1800 ns that way).  A step is cut into 4 / KS phases of KS 16-deep slices; before the last phase
+// of step s a wavefront has all its operands of the step in registers, so past the barrier that also
+// tells it that step s + 1 has landed it may refill the stage of step s.
+#pragma once
+#include <type_traits>
+
+#include "ffn_ring.h"
+
+namespace lx {
+
+// TM x TN groups of 64 token / weight rows, WM x WN wavefronts over them, NST ring stages, KS slices per
+// phase, MINW wavefronts per SIMD the registers have to leave room for.
+template <int TM_, int TN_, int WM_, int WN_, int NST_, int KS_, int MINW_ = 2>
+struct Tile {
+  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, NST = NST_, KS = KS_, kMinWaves = MINW_;
+  static constexpr int kWaves = WM * WN, kTileThreads = kWaves * kWave;
+  static constexpr int kElems = 64 * (TM + TN) * kBK;        // one stage
+  static constexpr int kIss = 8 * (TM + TN) / kWaves;        // transfer instructions per wavefront and stage
+  static constexpr int kIssA = 8 * TM / kWaves;              // the first of them bring token rows
+  static constexpr int NI = 2 * TN / WN, TI = 2 * TM / WM;   // 32 x 32 accumulators of a wavefront
+  static_assert(8 * TM % kWaves == 0 && 8 * TN % kWaves == 0 && (kWaves == 4 || kWaves == 8), "wavefronts");
+  static_assert(NI >= 1 && TI >= 1 && (KS == 2 || KS == 4), "wave tile");
+};
+
+// dma16 with a wave-uniform base and a 32-bit offset per lane.  It names no memory clobber: nothing but
+// the barriers orders the reads of a stage against its refill.
+__device__ __forceinline__ void dma16_s(const uint16_t* base, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
+               : "m0");
+}
+
+template <class Tl>
+struct Frag {
+  uint4 a[Tl::KS][Tl::NI], b[Tl::KS][Tl::TI];   // weight rows, token rows
+};
+
+// LDS byte offsets of this lane's operand rows inside a stage, per 16-deep slice.
+template <class Tl>
+struct LaneOff {
+  uint32_t a[4], b[4];
+  __device__ __forceinline__ LaneOff(int wm, int wn) {
+    const int lane = threadIdx.x % kWave, r = lane % 32, h2 = lane / 32;
+    const int sw = (r & 7) ^ (r >> 3);
+    // 32-row groups with an odd index have bit 2 of the slot flipped (row >> 3 is 4 more): for even
+    // NI / TI that parity is a compile-time property of the accumulator, handled in read()
+    const int pa = Tl::NI == 1 ? 4 * (wn & 1) : 0, pb = Tl::TI == 1 ? 4 * (wm & 1) : 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int seg = 2 * k + h2;
+      a[k] = (uint32_t)((64 * Tl::TM + 32 * Tl::NI * wn + r) * 128 + ((seg ^ sw ^ pa) << 4));
+      b[k] = (uint32_t)((32 * Tl::TI * wm + r) * 128 + ((seg ^ sw ^ pb) << 4));
+    }
+  }
+};
+
+// Operand number x of phase ph of the stage at LDS address `stage`.
+template <class Tl>
+__device__ __forceinline__ void read_operand(Frag<Tl>& f, const LaneOff<Tl>& lo, uint32_t stage, int ph, int x) {
+  constexpr int per = Tl::NI + Tl::TI;
+  const int e = x / per, y = x % per, k = ph * Tl::KS + e;
+  if (y < Tl::NI)
+    f.a[e][y] = lds_read16(stage + lo.a[k ^ (Tl::NI > 1 ? 2 * (y & 1) : 0)] + y * 4096);
+  else
+    f.b[e][y - Tl::NI] =
+        lds_read16(stage + lo.b[k ^ (Tl::TI > 1 ? 2 * ((y - Tl::NI) & 1) : 0)] + (y - Tl::NI) * 4096);
+}
+
+// One phase: the products of `cur`, meanwhile the operands of phase ph of the stage at `stage` go to
+// `nxt` and, with DMA, the transfers of a later step are issued (src.dma(u, LDS address)).
+template <class Tl, int DT, bool DMA, class Src>
+__device__ __forceinline__ void tile_phase(const Frag<Tl>& cur, Frag<Tl>& nxt, const LaneOff<Tl>& lo,
+                                           uint32_t stage, int ph, Src& src, uint32_t dma_lds,
+                                           f32x16 (&acc)[Tl::NI][Tl::TI]) {
+  constexpr int NM = Tl::KS * Tl::NI * Tl::TI, NR = Tl::KS * (Tl::NI + Tl::TI), ND = Tl::kIss;
+  // operand reads over the first three quarters of the matrix instructions, transfers over all of them
+  constexpr int RM = NM * 3 / 4 > 0 ? NM * 3 / 4 : 1;
+  int m = 0, xr = 0, xd = 0;
+#pragma unroll
+  for (int e = 0; e < Tl::KS; ++e)
+#pragma unroll
+    for (int ni = 0; ni < Tl::NI; ++ni)
+#pragma unroll
+      for (int ti = 0; ti < Tl::TI; ++ti) {
+        const int r_to = m + 1 >= RM ? NR : ((m + 1) * NR + RM - 1) / RM;
+#pragma unroll
+        for (int z = 0; z < NR; ++z)
+          if (z >= xr && z < r_to) read_operand<Tl>(nxt, lo, stage, ph, z);
+        xr = r_to;
+        if constexpr (DMA) {
+          const int d_to = ((m + 1) * ND + NM - 1) / NM;
+#pragma unroll
+          for (int z = 0; z < ND; ++z)
+            if (z >= xd && z < d_to) src.dma(z, dma_lds);
+          xd = d_to;
+        }
+        acc[ni][ti] = mfma32<DT>(cur.a[e][ni], cur.b[e][ti], acc[ni][ti]);
+        __builtin_amdgcn_sched_barrier(0);
+        ++m;
+      }
+}
+
+// acc[ni][ti] += sum over nsteps steps.  src.begin(s) prepares the sources of step s, src.dma(u, lds)
+// issues its transfer instruction u to the stage at that LDS address.
+template <class Tl, int DT, class Src>
+__device__ __forceinline__ void run_tile(int nsteps, uint32_t ring, int wm, int wn, Src& src,
+                                         f32x16 (&acc)[Tl::NI][Tl::TI]) {
+  constexpr int NST = Tl::NST, NISS = Tl::kIss;
+  static_assert(NST >= 2 && NISS * (NST - 1) < 64, "ring depth");
+  if (nsteps <= 0) return;
+  const LaneOff<Tl> lo(wm, wn);
+  constexpr uint32_t kStage = Tl::kElems * 2;
+  const uint32_t wave_lds = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave) * 1024;
+#pragma unroll
+  for (int p = 0; p < NST; ++p)
+    if (p < nsteps) {
+      src.begin(p);
+#pragma unroll
+      for (int u = 0; u < NISS; ++u) src.dma(u, ring + p * kStage + wave_lds);
+    }
+  // step 0 has landed when at most the transfers of the others are outstanding
+  if (nsteps >= NST)
+    wait_vmcnt<NISS * (NST - 1)>();
+  else
+    wait_tail<NISS, NST - 2>(nsteps - 1);
+  lds_barrier();
+  Frag<Tl> f0, f1;
+#pragma unroll
+  for (int x = 0; x < Tl::KS * (Tl::NI + Tl::TI); ++x) read_operand<Tl>(f0, lo, ring, 0, x);
+  __builtin_amdgcn_sched_barrier(0);
+  int stage = 0;       // of step s
+  // everything of step s but its last phase; then the last one, behind the barrier
+  auto step = [&](int s, auto dma, Frag<Tl>& fa, Frag<Tl>& fb) {
+    constexpr bool D = decltype(dma)::value;
+    const uint32_t here = ring + stage * kStage;
+    stage = stage + 1 == NST ? 0 : stage + 1;
+    const uint32_t next = ring + stage * kStage;
+    if constexpr (Tl::KS == 2) tile_phase<Tl, DT, false>(fa, fb, lo, here, 1, src, 0u, acc);
+    // step s + 1 has landed: at most the transfers of steps s + 2 .. s + NST - 1 are outstanding
+    if constexpr (D) {
+      wait_vmcnt<NISS * (NST - 2)>();
+    } else {
+      const int younger = nsteps - 2 - s;
+      if (younger >= NST - 2)
+        wait_vmcnt<NISS * (NST - 2)>();
+      else
+        wait_tail<NISS, NST - 3>(younger > 0 ? younger : 0);
+    }
+    lds_barrier();
+    if constexpr (D) src.begin(s + NST);
+    if constexpr (Tl::KS == 2)
+      tile_phase<Tl, DT, D>(fb, fa, lo, next, 0, src, here + wave_lds, acc);
+    else
+      tile_phase<Tl, DT, D>(fa, fb, lo, next, 0, src, here + wave_lds, acc);
+  };
+  int s = 0;
+  if constexpr (Tl::KS == 2) {
+    for (; s + NST < nsteps; ++s) step(s, std::true_type{}, f0, f1);
+    for (; s < nsteps; ++s) step(s, std::false_type{}, f0, f1);
+  } else {      // the two operand sets swap roles every step
+    for (; s + 1 + NST < nsteps; s += 2) {
+      step(s, std::true_type{}, f0, f1);
+      step(s + 1, std::true_type{}, f1, f0);
+    }
+    if (s + NST < nsteps) {
+      step(s, std::true_type{}, f0, f1);
+      ++s;
+      for (; s < nsteps; s += 2) {
+        step(s, std::false_type{}, f1, f0);
+        if (s + 1 < nsteps) step(s + 1, std::false_type{}, f0, f1);
+      }
+    } else {
+      for (; s < nsteps; s += 2) {
+        step(s, std::false_type{}, f0, f1);
+        if (s + 1 < nsteps) step(s + 1, std::false_type{}, f1, f0);
+      }
+    }
+  }
+}
+
+}  // namespace lx

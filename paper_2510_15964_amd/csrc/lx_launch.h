@@ -76,7 +76,7 @@ hipError_t launch_ffn_bf16(int dt, int pass, int Tt, int gt, int Fb, int d, int 
                            uint16_t* act_out, const uint16_t* act_gate, uint16_t* out,
                            float* part, size_t part_bytes, hipStream_t st);
 // bytes of partial sums with which the second product of a pass, given ONE list row of at most
-// nnz_cap entries for all Tt token tiles, splits the lists of its last round of workgroups (0: never)
+// nnz_cap entries for all Tt token tiles, cuts the lists of its last round of workgroups (0: never)
 size_t ffn_dsd_split_bytes(int Tt, int d, int nnz_cap);
 // Splits of the low-rank products of the LoRA branch over workgroups so that they fill the chip;
 // the partial sums are added in a fixed order.  U = X A^T: over K; dB: over ranges of token

@@ -23,7 +23,7 @@ __global__ __launch_bounds__(kThreads) void predict_bf16(
   constexpr int kTPW = NB == 4 ? 2 : 1;           // accumulator tiles per wavefront
   // few workgroups, each with little arithmetic per byte: what bounds the small variants is the
   // number of bytes in flight, so their rings take most of the LDS
-  constexpr int kNSt = NB == 1 ? 8 : NB == 2 ? 6 : kSddStages;
+  constexpr int kNSt = NB == 1 ? 8 : NB == 2 ? 6 : 3;
   __shared__ __attribute__((aligned(1024))) uint16_t ring[kNSt * kSE];
   // Workgroup w runs on XCD w % 8: the workgroups of one token tile (one per chunk of NB groups
   // of rows of Wa_t) are given the same XCD, so the tile's tokens reach one L2 only.
