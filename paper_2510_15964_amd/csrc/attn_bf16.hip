@@ -67,39 +67,43 @@ __device__ __forceinline__ int tswz(int row) {
   return D == 64 ? ((row ^ (row >> 3)) & 7) : (row & 15);
 }
 
-// Per-lane element offsets (relative to the tile's first row) of the DMA instructions this
-// wave issues for one [64 x D] tile.  One instruction moves 1 KiB = 64*16/(2D) rows.
+// The DMA instructions this wave issues for one [64 x D] tile: a wave-uniform base per instruction and
+// one 32-bit offset per lane.  One instruction moves 1 KiB = 64*16/(2D) rows.
 template <int D>
 struct TileDma {
   static constexpr int kSlots = D / 8;            // 16-byte slots per row
   static constexpr int kRowsPer = 64 / kSlots;    // rows per DMA instruction
   static constexpr int kPerWave = 64 / kRowsPer / kAW;
-  long long off[kPerWave];
+  long long row0[kPerWave];                       // element offset of the instruction's first row
+  uint32_t off[kPerWave];                         // bytes from there: row lane / kSlots, swizzled slot
+  uint32_t wave_lds;
   __device__ __forceinline__ void init(long long ld) {
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    wave_lds = wave * 1024;
 #pragma unroll
     for (int u = 0; u < kPerWave; ++u) {
-      const int g = wave + kAW * u;
-      const int row = kRowsPer * g + lane / kSlots;
+      const int first = kRowsPer * (wave + kAW * u), row = first + lane / kSlots;
       const int slot = (lane % kSlots) ^ tswz<D>(row);
-      off[u] = (long long)row * ld + slot * 8;
+      row0[u] = first * ld;
+      off[u] = (uint32_t)((lane / kSlots) * ld * 2) + slot * 16;
     }
   }
-  // tile_addr: LDS byte address of the destination tile
+  // tile_addr: LDS byte address of the destination tile; g0: wave-uniform
   __device__ __forceinline__ void issue(uint32_t tile_addr, const uint16_t* g0) const {
-    const int wave = threadIdx.x / kWave;
 #pragma unroll
-    for (int u = 0; u < kPerWave; ++u) dma16(g0 + off[u], tile_addr + (wave + kAW * u) * 1024);
+    for (int u = 0; u < kPerWave; ++u)
+      dma16_s(g0 + row0[u], off[u], tile_addr + wave_lds + u * (kAW * 1024));
   }
 };
 
 // LDS byte offsets inside a [64 x D] tile.  Element (row, col) sits at
 // row*2D + (((col/8) ^ tswz(row)) << 4) + (col%8)*2.  tswz is linear over XOR and the row, slot
 // and in-slot parts occupy disjoint bits, so the offset of (r0 + dr, c0 + dc) is the offset of
-// (r0, c0) XOR a compile-time constant whenever r0/dr and c0/dc have disjoint bits.  The kernels
-// keep ONE per-lane offset per access pattern in a register and derive every address of the
-// pattern with an XOR by a constant (tile base addresses are multiples of the tile size, so they
-// combine with OR): this is what keeps the address arithmetic out of the register budget.
+// (r0, c0) XOR a compile-time constant whenever r0/dr and c0/dc have disjoint bits.  Of that constant
+// the row part only adds (bits that r0 leaves clear), so it goes into the LDS instruction's immediate
+// offset; what is left are 4 or 8 different XORs of the slot bits per access pattern, each kept as one
+// per-lane offset to which the stage's address is added once per tile (an XOR per LDS read was a
+// sixth of the forward kernel's vector instructions).
 template <int D>
 __device__ __forceinline__ constexpr uint32_t tile_off(int row, int col) {
   return (uint32_t)(row * 2 * D + ((((col >> 3) ^ tswz<D>(row)) << 4)) + (col & 7) * 2);
@@ -221,17 +225,29 @@ __device__ __forceinline__ f32x4 mfma16(uint4 a, uint4 b, f32x4 c) {
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Per-lane offsets of the two access patterns into a streamed [64 x D] tile.
+// Per-lane offsets of the two access patterns into a streamed [64 x D] tile, for every XOR of the slot
+// bits that the patterns' rows and columns make.
 template <int D>
 struct LaneOff16 {
-  uint32_t rows;   // element (lane%16, 8*(lane/16)); row tile t, k slice kk: XOR tile_off(16t, 32kk)
-  uint32_t tr;     // element (4*(lane/16) + (lane%16)/4, 4*(lane%4)); XOR tile_off(32kk + 16i, 16ct)
+  static constexpr int kTr = D == 64 ? 4 : 8;
+  uint32_t rows[4];   // element (lane%16, 8*(lane/16)); row tile t, k slice kk: entry xr(t, kk), + 16t rows
+  uint32_t tr[kTr];   // element (4*(lane/16) + (lane%16)/4, 4*(lane%4)); entry xt(kk, i, ct), + 32kk + 16i rows
+  static __device__ __forceinline__ constexpr int xr(int t, int kk) { return D == 64 ? (2 * kk) ^ t : kk; }
+  static __device__ __forceinline__ constexpr int xt(int kk, int i, int ct) { return D == 64 ? ct ^ (2 * kk) ^ i : ct; }
   __device__ __forceinline__ void init() {
     const int lane = threadIdx.x % kWave, g = lane / 16, j = lane % 16;
-    rows = tile_off<D>(j, 8 * g);
-    tr = tile_off<D>(4 * g + j / 4, 4 * (j % 4));
+#pragma unroll
+    for (int x = 0; x < 4; ++x) rows[x] = tile_off<D>(j, 8 * g) ^ (x << (D == 64 ? 5 : 6));
+#pragma unroll
+    for (int x = 0; x < kTr; ++x) tr[x] = tile_off<D>(4 * g + j / 4, 4 * (j % 4)) ^ (x << 5);
   }
 };
+// v + s, opaque to the compiler: constants added to the result stay in the LDS instructions' immediates
+__device__ __forceinline__ uint32_t add_lds(uint32_t v, uint32_t s) {
+  uint32_t r;
+  asm("v_add_u32 %0, %1, %2" : "=v"(r) : "s"(s), "v"(v));
+  return r;
+}
 
 // acc[t] = R[rows 16t + lane%16][:] . F^T for the four row tiles t of a row-major tile R in LDS
 // (byte address `tile`); F: per-lane fragments of the own rows (column index = lane%16).
@@ -240,12 +256,14 @@ template <int D, int DT>
 __device__ __forceinline__ void mma_rows16(uint32_t tile, const LaneOff16<D>& lo,
                                            const uint4 (&frag)[D / 32], f32x4 (&acc)[4]) {
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  const uint32_t a0 = tile | lo.rows;
+  uint32_t a0[4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) a0[x] = add_lds(lo.rows[x], tile);
   uint4 a[D / 32][4];
 #pragma unroll
   for (int kk = 0; kk < D / 32; ++kk)
 #pragma unroll
-    for (int t = 0; t < 4; ++t) a[kk][t] = lds_read16(a0 ^ tile_off<D>(16 * t, 32 * kk));
+    for (int t = 0; t < 4; ++t) a[kk][t] = lds_read16(a0[lo.xr(t, kk)] + 16 * t * 2 * D);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int kk = 0; kk < D / 32; ++kk)
@@ -263,13 +281,15 @@ struct TrOps16 {
 };
 template <int D>
 __device__ __forceinline__ void load_tr16(uint32_t tile, const LaneOff16<D>& lo, TrOps16<D>& t) {
-  const uint32_t a0 = tile | lo.tr;
+  uint32_t a0[LaneOff16<D>::kTr];
+#pragma unroll
+  for (int x = 0; x < LaneOff16<D>::kTr; ++x) a0[x] = add_lds(lo.tr[x], tile);
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
     for (int ct = 0; ct < D / 16; ++ct) {
-      const uint2 l = lds_read8_tr(a0 ^ tile_off<D>(32 * kk, 16 * ct));
-      const uint2 h = lds_read8_tr(a0 ^ tile_off<D>(32 * kk + 16, 16 * ct));
+      const uint2 l = lds_read8_tr(a0[lo.xt(kk, 0, ct)] + (32 * kk) * 2 * D);
+      const uint2 h = lds_read8_tr(a0[lo.xt(kk, 1, ct)] + (32 * kk + 16) * 2 * D);
       t.a[kk][ct] = make_uint4(l.x, l.y, h.x, h.y);
     }
 }
@@ -329,14 +349,37 @@ __device__ __forceinline__ void zero4(f32x4 (&a)[N]) {
 #pragma unroll
   for (int i = 0; i < N; ++i) a[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
-// sum / maximum over the four lanes that share lane%16
+// sum / maximum over the four lanes that share lane%16.  The rows of 16 lanes are exchanged in the vector
+// unit: a swap of two copies of x leaves x of the even row (lower half) in both rows (halves) of one and
+// x of the odd row (upper half) in the other.  In assembly: clang's builtin returns the first result
+// twice; the s_nop is the distance a swap needs from the instruction that wrote its operands.
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
 __device__ __forceinline__ float sum_g(float x) {
-  x += __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
+  float y = x;
+  swap16(x, y);
+  x += y;
+  y = x;
+  swap32(x, y);
+  return x + y;
 }
 __device__ __forceinline__ float max_g(float x) {
-  x = fmaxf(x, __shfl_xor(x, 16));
-  return fmaxf(x, __shfl_xor(x, 32));
+  float y = x;
+  swap16(x, y);
+  x = fmaxf(x, y);
+  y = x;
+  swap32(x, y);
+  return fmaxf(x, y);
+}
+// (fmaxf makes the compiler quiet each argument first)
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -440,8 +483,7 @@ __device__ __forceinline__ void walk_table(int* tab, const RowSet& rows, const i
   }
   const int total = offs[kRMax];
   auto entry = [&](int i) { return __builtin_amdgcn_readfirstlane(tab[i]); };
-  auto issue = [&](int stage, int i) {
-    const int e = entry(i);
+  auto issue_entry = [&](int stage, int e) {
     if (e & kEOwn)
       issue_own(stage, e);
     else if (XAUX >= 0 && (e & kEAux))
@@ -456,20 +498,34 @@ __device__ __forceinline__ void walk_table(int* tab, const RowSet& rows, const i
     fill_table(tab, rows, col_idx, offs, first, cnt, kPre);
 #pragma unroll
     for (int i = 0; i < NS - 1; ++i)
-      if (i < cnt) issue(i, i);
+      if (i < cnt) issue_entry(i, entry(i));
     unsigned hist = 0;                   // byte i: store instructions issued while entry t-1-i was consumed
     int stage = 0, istage = NS - 1;      // stage of entry t, stage entry t + NS - 1 goes to
+    int q[NS];                           // entries t .. t + NS - 1, read from the table a step before they are needed
+#pragma unroll
+    for (int u = 0; u < NS; ++u) q[u] = entry(min(u, cnt - 1));
     for (int t = 0; t < cnt; ++t) {
-      const int e = entry(t);
-      int n = 0;
+      const int e = q[0];
+      const int ahead = tab[min(t + NS, cnt - 1)];
+      if constexpr (NS == 2) {           // what was issued since: the stores of the previous entry
+        const unsigned st = hist & 0xFF;
+        if (st == 0)
+          wait_vmcnt<0>();
+        else if (YAUX > 0 && YAUX != YST && st == YAUX)
+          wait_vmcnt<YAUX>();
+        else
+          wait_vmcnt<YST>();
+      } else {
+        int n = 0;
 #pragma unroll
-      for (int u = 0; u < NS - 1; ++u) n += (hist >> (8 * u)) & 0xFF;
+        for (int u = 0; u < NS - 1; ++u) n += (hist >> (8 * u)) & 0xFF;
 #pragma unroll
-      for (int u = 1; u <= NS - 2; ++u)
-        if (t + u < cnt) n += issued_by(entry(t + u));
-      wait_vmcnt_dyn(n);
+        for (int u = 1; u <= NS - 2; ++u)
+          if (t + u < cnt) n += issued_by(q[u]);
+        wait_vmcnt_dyn(n);
+      }
       lds_barrier();
-      if (t + NS - 1 < cnt) issue(istage, t + NS - 1);
+      if (t + NS - 1 < cnt) issue_entry(istage, q[NS - 1]);
       int stores = 0;
       if (e & kEOwn) {
         row_begin(stage, e);
@@ -486,8 +542,39 @@ __device__ __forceinline__ void walk_table(int* tab, const RowSet& rows, const i
       hist = (hist << 8) | (unsigned)stores;
       stage = stage + 1 == NS ? 0 : stage + 1;
       istage = istage + 1 == NS ? 0 : istage + 1;
+#pragma unroll
+      for (int u = 0; u < NS - 1; ++u) q[u] = q[u + 1];
+      q[NS - 1] = __builtin_amdgcn_readfirstlane(ahead);
     }
   }
+}
+
+// Which workgroup of which (batch entry, head group) pair this is.  Workgroup w runs on XCD w % 8.  Whole
+// rounds of eight pairs are dealt to the XCDs in turn, all `gz` workgroups of a pair to one XCD: they
+// stream the same tiles, so these are fetched into one L2 only, whatever the batch and head counts
+// (dealt by the plain linear index, only multiples of eight pairs had that: 5 x 31 heads of 1536 tokens,
+// 68 % of the blocks, forward 91 us, see the launcher).  The workgroups of the last P % 8 pairs are spread over all XCDs in
+// runs.  The batch entry is the fast index of a pair: the masks of the batch entries are the same or
+// alike, those of the heads are not, so every XCD gets about the same mix of heads.
+struct PairWork {
+  int b, group, z;
+};
+__device__ __forceinline__ bool pair_work(const AttnArgs& a, PairWork& p) {
+  const int P = a.B * (a.Hh / a.vheads), gz = a.gz;
+  const int x = blockIdx.x % 8, s = blockIdx.x / 8, whole = P / 8 * gz;
+  int pair;
+  if (s < whole) {
+    pair = s / gz * 8 + x;
+    p.z = s % gz;
+  } else {
+    const int rest = P % 8 * gz, L = (rest + 7) / 8, r = x * L + (s - whole);
+    if (s - whole >= L || r >= rest) return false;
+    pair = P / 8 * 8 + r / gz;
+    p.z = r % gz;
+  }
+  p.b = pair % a.B;
+  p.group = pair / a.B;
+  return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -500,7 +587,9 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   __shared__ int btab[kTabCap];
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;   // bytes
   const int nqb = a.S / 64;
-  const int b = blockIdx.x, h0 = blockIdx.y * a.vheads;   // batch entry fastest: see the launchers
+  PairWork pw;
+  if (!pair_work(a, pw)) return;
+  const int b = pw.b, h0 = pw.group * a.vheads;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, ql = 16 * wave + lane % 16;    // this lane's query inside the block
   auto base_of = [&](int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
@@ -510,7 +599,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
 
   RowSet rows;
   rows.init(rowtab, a.row_ptr, a.nnz_cap, ((a.mask_batch == 1 ? 0 : b) * a.Hh + h0) * nqb, nqb,
-            a.vheads, h0, a.head_active, blockIdx.z, gridDim.z, a.rows_per_wg, true);
+            a.vheads, h0, a.head_active, pw.z, a.gz, a.rows_per_wg, true);
   // rows without a listed block (or of an inactive head): O = 0, LSE = -inf, nothing to read
   for (int j = 0; j < kRMax; ++j)
     if (rows.blk(j) >= 0 && rows.n(j) == 0) {
@@ -530,7 +619,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   long long qoff = 0, soff = 0;
   uint4 qf[D / 32];
   f32x4 o_acc[D / 16];
-  float m = -INFINITY, lsum = 0.f;   // running maximum of the query; this lane's share of its sum
+  float m = -INFINITY, m_use = 0.f, lsum = 0.f;   // reference point of the query (0 for -inf); this lane's share of its sum
 
   auto issue_own = [&](int stage, int e) {
     const long long t0 = base_of(rows.head(entry_slot(e))) + (long long)entry_blk(e) * 64 * a.ss;
@@ -552,6 +641,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
     for (int kk = 0; kk < D / 32; ++kk) qf[kk] = lds_read16(q0 ^ tile_off<D>(0, 32 * kk));
     zero4(o_acc);
     m = -INFINITY;
+    m_use = 0.f;
     lsum = 0.f;
   };
   auto comp = [&](int stage, int e) {
@@ -563,19 +653,31 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
     load_tr16<D>(stg + kTile, lo, vt);
     __builtin_amdgcn_sched_barrier(0);
     if (a.causal && col >= qb) mask_diag16(s, ql, col > qb);
-    float mloc = fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3]));
+    float mloc = max3(s[0][0], s[0][1], s[0][2]);
+    mloc = max3(mloc, s[0][3], s[1][0]);
 #pragma unroll
-    for (int t = 1; t < 4; ++t) mloc = fmaxf(mloc, fmaxf(fmaxf(s[t][0], s[t][1]), fmaxf(s[t][2], s[t][3])));
-    mloc = max_g(mloc);
+    for (int t = 1; t < 4; ++t) {
+      mloc = max3(mloc, s[t][1], s[t][2]);
+      mloc = max3(mloc, s[t][3], s[t < 3 ? t + 1 : t][0]);
+    }
     // The reference point m of the running sums only has to bound the scores from above up to a
     // factor that fp32 holds comfortably: it follows the running maximum only when that has moved
-    // by more than kSlack (then exp2(score - m) <= 2^kSlack), so most blocks need no rescaling.
-    const float cand = mloc * sc;
-    const float m_new = cand > m + kSlack ? cand : m;
-    // a query none of whose keys so far is allowed keeps m = -inf; subtracting 0 instead keeps
-    // the exponentials below at exp2(-inf) = 0 rather than exp2(-inf + inf)
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;
-    const float alpha = __builtin_amdgcn_exp2f(m - m_use);
+    // by more than kSlack (then exp2(score - m) <= 2^kSlack).  Most blocks move it for no query of
+    // the wavefront, which every lane sees from its own scores: no exchange, no rescaling.
+    if (__any(mloc * sc > m + kSlack)) {
+      const float cand = max_g(mloc) * sc;
+      const float m_new = cand > m + kSlack ? cand : m;
+      // a query none of whose keys so far is allowed keeps m = -inf; subtracting 0 instead keeps
+      // the exponentials below at exp2(-inf) = 0 rather than exp2(-inf + inf)
+      m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(m - m_use);
+      lsum *= alpha;
+      if (__any(alpha != 1.f && m != -INFINITY)) {
+#pragma unroll
+        for (int ct = 0; ct < D / 16; ++ct) o_acc[ct] *= alpha;
+      }
+      m = m_new;
+    }
     float psum = 0.f;
 #pragma unroll
     for (int t = 0; t < 4; ++t)
@@ -585,13 +687,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
         s[t][v] = p;
         psum += p;
       }
-    lsum = lsum * alpha + psum;     // the four lanes of a query add their shares at the row's end
-    const bool rescale = __any(alpha != 1.f && m != -INFINITY);
-    m = m_new;
-    if (rescale) {
-#pragma unroll
-      for (int ct = 0; ct < D / 16; ++ct) o_acc[ct] *= alpha;
-    }
+    lsum += psum;                   // the four lanes of a query add their shares at the row's end
     mma_tr16<D, DT>(vt, s, o_acc);              // O^T += V^T P^T
   };
   auto row_end = [&](int) {
@@ -617,7 +713,9 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
   __shared__ int btab[kTabCap];
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;
   const int nqb = a.S / 64;
-  const int b = blockIdx.x, h0 = blockIdx.y * a.vheads;   // batch entry fastest: see the launchers
+  PairWork pw;
+  if (!pair_work(a, pw)) return;
+  const int b = pw.b, h0 = pw.group * a.vheads;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, ql = 16 * wave + lane % 16;
   auto base_of = [&](int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
@@ -627,7 +725,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
 
   RowSet rows;
   rows.init(rowtab, a.row_ptr, a.nnz_cap, ((a.mask_batch == 1 ? 0 : b) * a.Hh + h0) * nqb, nqb,
-            a.vheads, h0, a.head_active, blockIdx.z, gridDim.z, a.rows_per_wg, true);
+            a.vheads, h0, a.head_active, pw.z, a.gz, a.rows_per_wg, true);
   // rows without a listed block (or of an inactive head): dQ = 0, Delta = 0, nothing to read
   for (int j = 0; j < kRMax; ++j)
     if (rows.blk(j) >= 0 && rows.n(j) == 0) {
@@ -743,7 +841,9 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
   __shared__ int btab[kTabCap];
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;
   const int nkb = a.S / 64;
-  const int b = blockIdx.x, h0 = blockIdx.y * a.vheads;   // batch entry fastest: see the launchers
+  PairWork pw;
+  if (!pair_work(a, pw)) return;
+  const int b = pw.b, h0 = pw.group * a.vheads;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, kl = 16 * wave + lane % 16;    // this lane's key inside the block
   auto base_of = [&](int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
@@ -753,7 +853,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
 
   RowSet rows;
   rows.init(rowtab, a.crow_ptr, a.cnnz_cap, ((a.mask_batch == 1 ? 0 : b) * a.Hh + h0) * nkb, nkb,
-            a.vheads, h0, a.head_active, blockIdx.z, gridDim.z, a.rows_per_wg, false);
+            a.vheads, h0, a.head_active, pw.z, a.gz, a.rows_per_wg, false);
   // key blocks used by no query block: zero gradients, nothing to read
   for (int j = 0; j < kRMax; ++j)
     if (rows.blk(j) >= 0 && rows.n(j) == 0) {
@@ -866,44 +966,41 @@ static int rows_per_wg(int nblk, int heads, int B, int slots) {
   return r > nblk ? nblk : r;
 }
 
-// Grid: (batch entry, head group, workgroup of the group).  Workgroups go to the eight XCDs round
-// robin by their linear index, so with the batch entry fastest an XCD gets the same mix of heads
-// as every other one (the masks of the batch entries are the same or alike, those of the heads
-// are not), and all workgroups of a (batch, head) pair share one L2.
+// Completes the arguments for workgroups of which `slots` fit the chip; returns the grid (see pair_work).
+static int attn_grid(AttnArgs& a, int B, int slots) {
+  const int nblk = a.S / 64;
+  a.B = B;
+  a.vheads = heads_per_group(nblk, a.Hh);
+  a.rows_per_wg = rows_per_wg(nblk, a.Hh, B, slots);
+  a.gz = (nblk + a.rows_per_wg - 1) / a.rows_per_wg * a.vheads;
+  const int P = B * (a.Hh / a.vheads);
+  return 8 * (P / 8 * a.gz + (P % 8 * a.gz + 7) / 8);
+}
+
 template <int D, int DT>
 static hipError_t launch_fwd(AttnArgs a, int B, hipStream_t st) {
   ProfScope ps(kKAttnFwd, st);
-  const int nblk = a.S / 64;
-  a.vheads = heads_per_group(nblk, a.Hh);
   constexpr int kNs = D == 64 ? kFwdNs64 : 2, kOcc = D == 64 ? kFwdOcc64 : 2;
-  a.rows_per_wg = rows_per_wg(nblk, a.Hh, B, kCUs * kOcc);
-  const int G = (nblk + a.rows_per_wg - 1) / a.rows_per_wg;
-  hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc>), dim3(B, a.Hh / a.vheads, G * a.vheads), dim3(kAT), 0,
-                     st, a);
+  const int grid = attn_grid(a, B, kCUs * kOcc);
+  hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc>), dim3(grid), dim3(kAT), 0, st, a);
   return hipGetLastError();
 }
 
 template <int D, int DT>
 static hipError_t launch_bwd(AttnArgs a, int B, hipStream_t st) {
-  const int nblk = a.S / 64;
-  a.vheads = heads_per_group(nblk, a.Hh);
   {
     ProfScope ps(kKAttnDq, st);
     constexpr int kNs = D == 64 ? kDqNs64 : 2, kOcc = D == 64 ? kDqOcc64 : 2;
-    a.rows_per_wg = rows_per_wg(nblk, a.Hh, B, kCUs * kOcc);
-    const int G = (nblk + a.rows_per_wg - 1) / a.rows_per_wg;
-    hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc>), dim3(B, a.Hh / a.vheads, G * a.vheads),
-                       dim3(kAT), 0, st, a);
+    const int grid = attn_grid(a, B, kCUs * kOcc);
+    hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc>), dim3(grid), dim3(kAT), 0, st, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKAttnDkv, st);
     constexpr int kNs = D == 64 ? kDkvNs64 : 2, kOcc = D == 64 ? kDkvOcc64 : 2;
-    a.rows_per_wg = rows_per_wg(nblk, a.Hh, B, kCUs * kOcc);
-    const int G = (nblk + a.rows_per_wg - 1) / a.rows_per_wg;
-    hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc>), dim3(B, a.Hh / a.vheads, G * a.vheads),
-                       dim3(kAT), 0, st, a);
+    const int grid = attn_grid(a, B, kCUs * kOcc);
+    hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc>), dim3(grid), dim3(kAT), 0, st, a);
   }
   return hipGetLastError();
 }

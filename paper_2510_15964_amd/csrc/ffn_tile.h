@@ -29,13 +29,6 @@ struct Tile {
   static_assert(NI >= 1 && TI >= 1 && (KS == 2 || KS == 4), "wave tile");
 };
 
-// dma16 with a wave-uniform base and a 32-bit offset per lane.  It names no memory clobber: nothing but
-// the barriers orders the reads of a stage against its refill.
-__device__ __forceinline__ void dma16_s(const uint16_t* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
-               : "m0");
-}
-
 template <class Tl>
 struct Frag {
   uint4 a[Tl::KS][Tl::NI], b[Tl::KS][Tl::TI];   // weight rows, token rows

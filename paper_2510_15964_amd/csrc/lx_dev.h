@@ -60,7 +60,14 @@ __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_wave_base) 
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(l), "v"(gptr)
                : "memory", "m0");
 }
-// Same with 4 bytes per lane (lane l lands at lds_wave_base + 4*l).
+// dma16 with a wave-uniform base and a 32-bit offset per lane.  It names no memory clobber: nothing but
+// the barriers orders the reads of a stage against its refill.
+__device__ __forceinline__ void dma16_s(const void* base, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
+               : "m0");
+}
+
+// dma16 with 4 bytes per lane (lane l lands at lds_wave_base + 4*l).
 __device__ __forceinline__ void dma4(const void* gptr, uint32_t lds_wave_base) {
   const uint32_t l = __builtin_amdgcn_readfirstlane(lds_wave_base);
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(l), "v"(gptr)
