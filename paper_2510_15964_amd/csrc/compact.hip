@@ -2,7 +2,7 @@
 // neuron-block index list of Sec. VI-B).
 //
 // The masks of one layer are tiny (tens of thousands of bytes), so the whole
-// job is latency-bound: a 1024-thread workgroup does count -> scan -> scatter
+// job is latency-bound: a 512-thread workgroup does count -> scan -> scatter
 // for a list (or for a part of its rows) in a single launch with no host
 // round trip.  One wavefront owns a mask row at
 // a time: a 64-wide ballot gives the row's bit pattern, popcount its total and
@@ -12,9 +12,10 @@
 
 namespace lx {
 
-constexpr int kCompactThreads = 1024;
+constexpr int kCompactThreads = 512;
 constexpr int kCompactWaves = kCompactThreads / kWave;
-constexpr int kChunkRows = 4096;    // rows scanned per pass (4 per thread)
+constexpr int kChunkRows = 4096;    // rows scanned per pass (8 per thread)
+constexpr int kRowsPer = kChunkRows / kCompactThreads;
 constexpr int kStageBytes = 32768;  // mask bytes staged in LDS per pass
 
 // The mask chunk is first copied into LDS with all loads in flight at once (strided or not),
@@ -26,18 +27,39 @@ struct CompactJobs {
   CompactJob j[kMaxJobs];
 };
 
+// How the bytes of a job lie: the rows of all masks one after the other, or every mask contiguous in
+// the other orientation (the column list of contiguous masks), or anything else.
+enum MaskLayout { kRowMajor, kColMajor, kStrided };
+__host__ __device__ inline MaskLayout mask_layout(const CompactJob& j) {
+  const bool whole = j.batch == 1 || j.bstride == (long long)j.rows * j.cols;
+  if (whole && j.cstride == 1 && j.rstride == j.cols) return kRowMajor;
+  if (whole && j.rstride == 1 && j.cstride == j.rows) return kColMajor;
+  return kStrided;
+}
 // Workgroups (blockIdx.x = job, blockIdx.y = part of the job's rows): a launch builds one list,
 // the row list and the column list of the same masks, or the lists of several independent masks
-// side by side.  A mask of more than kSplitBytes is divided by rows among up to kMaxSplit
-// workgroups; a workgroup that does not start at row 0 first counts the active entries of all
-// rows before its own (a plain count over bytes it would otherwise wait for another workgroup to
-// scan), so the parts need no communication.
-constexpr int kSplitBytes = 4096, kMaxSplit = 16;
-__host__ __device__ inline int compact_parts(long long total_rows, int cols) {
-  long long p = (total_rows * cols + kSplitBytes - 1) / kSplitBytes;
-  if (p > kMaxSplit) p = kMaxSplit;
-  if (p > total_rows) p = total_rows;
-  return p < 1 ? 1 : (int)p;
+// side by side.  A large mask is divided by rows; a workgroup that does not start at row 0 first
+// counts the active entries of all rows before its own (a plain count over bytes it would otherwise
+// wait for another workgroup to scan), so the parts need no communication.  Where several masks that
+// fit the stage lie one after the other, the parts are whole masks: what precedes a part is then one
+// range of bytes, and the part another, in either orientation (16 bytes per load for both).  A part
+// is about 1 KB: 32 heads of 32 x 32 in 32 parts per list take 13 us in eight parts of bytes loaded
+// one by one for the column list, 7 so.  Strided bytes are slow to count, so those parts are larger.
+struct CompactParts {
+  int parts, rows;      // rows per part
+};
+__host__ __device__ inline CompactParts compact_parts(const CompactJob& j) {
+  const long long total = (long long)j.batch * j.rows;
+  const MaskLayout lay = mask_layout(j);
+  const bool masks = lay != kStrided && j.batch > 1 && j.rows <= kChunkRows && (long long)j.rows * j.cols <= kStageBytes;
+  const int unit = masks ? j.rows : 1;
+  const bool fast = masks || lay == kRowMajor;
+  const long long units = total / unit;
+  long long p = (total * j.cols + (fast ? 1023 : 4095)) / (fast ? 1024 : 4096);
+  p = p > (fast ? 64 : 16) ? (fast ? 64 : 16) : p;
+  p = p > units ? units : p < 1 ? 1 : p;
+  const long long per = (units + p - 1) / p;
+  return {(int)((units + per - 1) / per), (int)per * unit};
 }
 
 // Walks the flattened (batch, row, column) index space of a job in steps of kCompactThreads
@@ -97,19 +119,23 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
   __shared__ __attribute__((aligned(16))) uint8_t stage[kStageBytes + 16];
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const int total_rows = batch * rows;
-  const int parts = compact_parts(total_rows, cols), part = blockIdx.y;
+  const CompactParts cparts = compact_parts(job);
+  const int parts = cparts.parts, part = blockIdx.y;
   if (part >= parts) return;
-  const int per_part = (total_rows + parts - 1) / parts;
-  const int row_lo = min(part * per_part, total_rows), row_hi = min(row_lo + per_part, total_rows);
+  const int row_lo = min(part * cparts.rows, total_rows), row_hi = min(row_lo + cparts.rows, total_rows);
+  const MaskLayout layout = mask_layout(job);
+  const bool rowmajor = layout == kRowMajor;
+  // whole masks in the other orientation: staged as they lie
+  const bool colmajor = layout == kColMajor && rows <= kChunkRows && (long long)rows * cols <= kStageBytes &&
+                        cparts.rows % rows == 0;
   const bool staged = cols <= kStageBytes;
-  const int chunk_rows = staged ? max(1, min(kChunkRows, kStageBytes / cols)) : 1;
+  const int chunk_rows = colmajor ? min(kChunkRows / rows, kStageBytes / (rows * cols)) * rows
+                         : staged ? max(1, min(kChunkRows, kStageBytes / cols)) : 1;
   int cp = kWave;                       // columns handled per wave pass (power of two)
   while (cp > 1 && (cp >> 1) >= cols) cp >>= 1;
   const int rpw = kWave / cp;           // rows per wave pass
   const int sub = lane / cp, cl = lane % cp;
   const unsigned long long field = cp == 64 ? ~0ull : ((1ull << cp) - 1ull);
-  // all rows of all masks are one contiguous range of bytes, row after row
-  const bool rowmajor = cstride == 1 && rstride == cols && (batch == 1 || bstride == (long long)rows * cols);
   int carry = 0;
   if (row_lo > 0) {      // active entries of the rows before this part
     const long long before = (long long)row_lo * cols;
@@ -119,16 +145,15 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
     // mask is contiguous in the other orientation; the rest (the rows of the mask the part
     // starts in, masks with other strides) byte by byte below.
     long long done = 0;
-    const bool dense = bstride == (long long)rows * cols && rstride == 1 && cstride == rows;
     const long long nbytes = rowmajor ? before
-                             : (dense && row_lo >= rows ? (long long)(row_lo / rows) * rows * cols : 0);
+                             : layout == kColMajor ? (long long)(row_lo / rows) * rows * cols : 0;
     if (nbytes > 0) {
       long long head = (16 - (long long)(reinterpret_cast<uintptr_t>(mask) & 15)) & 15;
       head = head < nbytes ? head : nbytes;
       if (tid < head) cnt += mask[tid] != 0;
       const long long nvec = (nbytes - head) / 16;
       const uint4* __restrict__ vp = reinterpret_cast<const uint4*>(mask + head);
-      constexpr int kVec = 4;
+      constexpr int kVec = 8;
       for (long long i0 = tid; i0 < nvec; i0 += (long long)kCompactThreads * kVec) {
         uint4 q[kVec];
 #pragma unroll
@@ -170,7 +195,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
   for (int chunk = row_lo; chunk < row_hi; chunk += chunk_rows) {
     const int n = min(chunk_rows, row_hi - chunk);
     int soff = 0;          // where the chunk's first byte sits in `stage`
-    if (staged && rowmajor) {
+    if (colmajor || (staged && rowmajor)) {
       // a contiguous range: 16 bytes per load, placed so that source and stage are aligned alike
       const uint8_t* __restrict__ src = mask + (long long)chunk * cols;
       const int len = n * cols;
@@ -204,6 +229,10 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
     }
     auto is_on = [&](int r, int c) -> bool {
       if (c >= cols) return false;
+      if (colmajor) {
+        const int q = r / rows;
+        return stage[soff + q * rows * cols + c * rows + (r - q * rows)] != 0;
+      }
       if (staged) return stage[soff + r * cols + c] != 0;
       const int gr = chunk + r;
       return mask[(long long)(gr / rows) * bstride + (long long)(gr % rows) * rstride +
@@ -222,11 +251,11 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
       if (cl == 0 && r < n) offs[r] = cnt;
     }
     __syncthreads();
-    // 2. exclusive scan of the counts (4 consecutive rows per thread)
-    int v[4], s = 0;
+    // 2. exclusive scan of the counts (8 consecutive rows per thread)
+    int v[kRowsPer], s = 0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = tid * 4 + e;
+    for (int e = 0; e < kRowsPer; ++e) {
+      const int idx = tid * kRowsPer + e;
       v[e] = idx < n ? offs[idx] : 0;
       s += v[e];
     }
@@ -247,8 +276,8 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
     }
     int run = carry + wbase + incl - s;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = tid * 4 + e;
+    for (int e = 0; e < kRowsPer; ++e) {
+      const int idx = tid * kRowsPer + e;
       if (idx < n) {
         offs[idx] = run;
         row_ptr[chunk + idx] = run;
@@ -280,7 +309,7 @@ hipError_t launch_compact_jobs(const CompactJob* jobs, int n, hipStream_t stream
   int parts = 1;
   for (int i = 0; i < n; ++i) {
     js.j[i] = jobs[i];
-    const int p = compact_parts((long long)jobs[i].batch * jobs[i].rows, jobs[i].cols);
+    const int p = compact_parts(jobs[i]).parts;
     parts = p > parts ? p : parts;
   }
   ProfScope ps(kKCompact, stream);
