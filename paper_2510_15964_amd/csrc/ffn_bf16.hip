@@ -698,18 +698,18 @@ static hipError_t launch_ffn_bf16_t(int pass, int Tt, int gt, int Fb, int d, int
 // ---------------------------------------------------------------------------
 
 // forward: U = X A_pad^T [T,64];  H_act = ReLU(X W_up^T + U B_pad^T) on the listed blocks;
-// Y = H W_down^T.  u_part: lora_u_split(Tt, d) * T * 64 floats of scratch (unused for a split of 1).
+// Y = H W_down^T.
 template <int DT>
 static hipError_t launch_ffn_lora_fwd_bf16_t(int Tt, int gt, int d, int F, const uint16_t* X,
                                     const uint16_t* W_up, const uint16_t* A_pad,
                                     const uint16_t* B_pad, const uint16_t* W_down,
                                     const int* row_ptr, const int* col_idx, int nnz_cap,
-                                    uint16_t* U, uint16_t* H_act, uint16_t* Y, float* u_part,
+                                    uint16_t* U, uint16_t* H_act, uint16_t* Y,
                                     hipStream_t st) {
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
   {
     ProfScope ps(kKLora, st);
-    const hipError_t eu = launch_lora_u(DT, Tt, d, X, A_pad, U, u_part, st);
+    const hipError_t eu = launch_lora_u(DT, Tt, d, X, A_pad, U, st);
     if (eu != hipSuccess) return eu;
   }
   hipError_t e = hipGetLastError();
@@ -728,16 +728,16 @@ static hipError_t launch_ffn_lora_fwd_bf16_t(int Tt, int gt, int d, int F, const
 
 // backward: dZ = (dY W_down) (.) [H > 0] on the listed blocks;  G = dZ B_pad [T,64];
 // dX = dZ W_up + G A_pad;  dB = dZ^T U;  dA = G^T X.
-// Scratch: B_t [64,F], A_t [d,64], G [T,64], g_part [lora_g_split][T][64], da_part [lora_da_split][64][d] and
-// db_part [lora_db_split][F][64] (each unused for a split of 1).
+// Scratch: A_t [d,64], G [T,64], da_part [lora_da_split][64][d] and db_part [lora_db_split][F][64] (the latter
+// unused for a split of 1).
 template <int DT>
 static hipError_t launch_ffn_lora_bwd_bf16_t(int Tt, int gt, int d, int F, const uint16_t* X,
                                     const uint16_t* dY, const uint16_t* H_act, const uint16_t* U,
                                     const uint16_t* W_down_t, const uint16_t* W_up_t,
                                     const uint16_t* A_pad, const uint16_t* B_pad,
                                     const int* row_ptr, const int* col_idx, int nnz_cap,
-                                    uint16_t* dZ, uint16_t* B_t, uint16_t* A_t, uint16_t* G,
-                                    float* g_part, float* da_part, float* db_part, uint16_t* dX,
+                                    uint16_t* dZ, uint16_t* A_t, uint16_t* G,
+                                    float* da_part, float* db_part, uint16_t* dX,
                                     float* dA, float* dB, hipStream_t st) {
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
   {
@@ -749,9 +749,7 @@ static hipError_t launch_ffn_lora_bwd_bf16_t(int Tt, int gt, int d, int F, const
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKLora, st);
-    const hipError_t et = launch_lora_transposes(d, F, A_pad, A_t, B_pad, B_t, st);
-    if (et != hipSuccess) return et;
-    const hipError_t eg = launch_lora_g(DT, Tt, gt, F, dZ, B_t, row_ptr, col_idx, nnz_cap, G, g_part, st);
+    const hipError_t eg = launch_lora_g(DT, Tt, gt, d, dZ, B_pad, row_ptr, col_idx, nnz_cap, G, A_pad, A_t, st);
     if (eg != hipSuccess) return eg;
   }
   e = hipGetLastError();
@@ -781,21 +779,21 @@ hipError_t launch_ffn_lora_fwd_bf16(int dt, int Tt, int gt, int d, int F, const 
                                     const uint16_t* W_up, const uint16_t* A_pad,
                                     const uint16_t* B_pad, const uint16_t* W_down,
                                     const int* row_ptr, const int* col_idx, int nnz_cap,
-                                    uint16_t* U, uint16_t* H_act, uint16_t* Y, float* u_part,
+                                    uint16_t* U, uint16_t* H_act, uint16_t* Y,
                                     hipStream_t st) {
   return LX_BY_DT(launch_ffn_lora_fwd_bf16_t, Tt, gt, d, F, X, W_up, A_pad, B_pad, W_down, row_ptr,
-                  col_idx, nnz_cap, U, H_act, Y, u_part, st);
+                  col_idx, nnz_cap, U, H_act, Y, st);
 }
 hipError_t launch_ffn_lora_bwd_bf16(int dt, int Tt, int gt, int d, int F, const uint16_t* X,
                                     const uint16_t* dY, const uint16_t* H_act, const uint16_t* U,
                                     const uint16_t* W_down_t, const uint16_t* W_up_t,
                                     const uint16_t* A_pad, const uint16_t* B_pad,
                                     const int* row_ptr, const int* col_idx, int nnz_cap,
-                                    uint16_t* dZ, uint16_t* B_t, uint16_t* A_t, uint16_t* G,
-                                    float* g_part, float* da_part, float* db_part, uint16_t* dX,
+                                    uint16_t* dZ, uint16_t* A_t, uint16_t* G,
+                                    float* da_part, float* db_part, uint16_t* dX,
                                     float* dA, float* dB, hipStream_t st) {
   return LX_BY_DT(launch_ffn_lora_bwd_bf16_t, Tt, gt, d, F, X, dY, H_act, U, W_down_t, W_up_t,
-                  A_pad, B_pad, row_ptr, col_idx, nnz_cap, dZ, B_t, A_t, G, g_part, da_part, db_part, dX,
+                  A_pad, B_pad, row_ptr, col_idx, nnz_cap, dZ, A_t, G, da_part, db_part, dX,
                   dA, dB, st);
 }
 

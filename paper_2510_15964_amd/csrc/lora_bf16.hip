@@ -1,6 +1,6 @@
 // The small products of the LoRA branch on the up-projection (Sec. II-C: z = W x + B A x;
-// Sec. II-D: its gradients) for gfx950: U = X A^T, dB = dZ^T U over the listed blocks,
-// dA = G^T X, and the transposes of the two matrices.  A_pad [64, d] and B_pad [F, 64] hold
+// Sec. II-D: its gradients) for gfx950: U = X A^T, G = dZ B and dB = dZ^T U over the listed blocks,
+// dA = G^T X, and the transpose of A.  A_pad [64, d] and B_pad [F, 64] hold
 // A [r, d] and B [F, r] zero-padded to rank 64.  The branch's steps inside the up-projection and
 // the input-gradient product live in the FFN kernels themselves.
 #include "ffn_ring.h"
@@ -46,97 +46,153 @@ __device__ __forceinline__ bool fold_khalves(float* area, f32x16& acc) {
   return true;
 }
 
-// out[t][q] = sum over steps of sum_k P_s[t][k] Q_s[q][k] for token tile blockIdx.x ([64 x 64], both
-// operands read along their rows) over the range of steps of blockIdx.y.
+// dst[c][r] = src[r][c] of a 64 x 64 tile, by 128 or more threads; t: 64 x 72 elements of LDS.
+__device__ __forceinline__ void transpose64(const uint16_t* __restrict__ src, long long lds, uint16_t* __restrict__ dst,
+                                            long long ldd, uint16_t* t) {
+  for (int piece = threadIdx.x; piece < 512; piece += blockDim.x) {
+    const int r = piece / 8, c8 = (piece % 8) * 8;
+    const uint4 v = *reinterpret_cast<const uint4*>(src + r * lds + c8);
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      t[(c8 + 2 * e) * 72 + r] = (uint16_t)(w[e] & 0xFFFFu);
+      t[(c8 + 2 * e + 1) * 72 + r] = (uint16_t)(w[e] >> 16);
+    }
+  }
+  __syncthreads();
+  for (int piece = threadIdx.x; piece < 512; piece += blockDim.x) {
+    const int r = piece / 8, c8 = (piece % 8) * 8;
+    *reinterpret_cast<uint4*>(dst + r * ldd + c8) = *reinterpret_cast<const uint4*>(t + r * 72 + c8);
+  }
+}
+
+// out[t][q] = sum over steps of sum_k P_s[t][k] Q_s[q][k] for the 32 x 32 quadrant blockIdx.x % 4 of token
+// tile blockIdx.x / 4, the steps cut into ranges (lora_u_split / lora_g_split of them).
 // MODE 0, U = X A_pad^T (Sec. II-C: the inner factor A x of the branch): P = X, Q = A_pad, row
 //   stride ld of both; the steps are the ld / 64 chunks of K.
 // MODE 1, G = dZ B_pad (Sec. II-D: the gradient that reaches A x): P = the compact blocks dZ_ij of
-//   the tile's list, Q = B_t [64, ld]; the steps are the list entries, step s takes the columns
-//   64 j_s .. of B_t.
-// gridDim.y == 1: out [T,64] is stored in the element type; otherwise fp32 partial sums
-// part[y][T][64], which lora_u_reduce_kernel adds.
+//   the tile's list, Q_s[q][k] = B_pad[64 j_s + k][q]; the steps are the list entries.  The last ld / 64
+//   workgroups of the launch transpose A_pad [64,ld] into A_t [ld,64] meanwhile, which the
+//   input-gradient product reads.
+// What bounds these products is latency: there are few of them.  A quadrant per workgroup gives every CU
+// one at 64 tiles; a wavefront owns one half (32 of the 64 k) of the steps of one range and streams its
+// own operands through its own stages, 4 KB each, without a barrier; halves and ranges are added at the end
+// through LDS, in that order (the same sums as 64 x 64 tiles with partial sums in memory, in one
+// launch instead of two: U at 4096 tokens, d = 2048 6.5 + 4.3 us before).
+constexpr int kNtStage = 4096;                 // bytes: 32 rows of 64 bytes of P, 32 of Q
+constexpr int kNtStages(int waves) { return waves <= 4 ? 8 : 32 / waves; }
+constexpr int kNtLds = 32 * kNtStage;          // stages of all wavefronts
 template <int DT, int MODE>
-__global__ __launch_bounds__(kThreads) void lora_nt_kernel(
+__global__ __launch_bounds__(1024) void lora_nt_kernel(
     const uint16_t* __restrict__ P, const uint16_t* __restrict__ Q, int ld,
-    const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int gt, int nnz_cap,
-    uint16_t* __restrict__ U, float* __restrict__ part, long long part_stride) {
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[kPairStages * kPairElems];
-  const int i = blockIdx.x;
+    const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int Tt, int gt, int nnz_cap,
+    uint16_t* __restrict__ out, const uint16_t* __restrict__ A_pad, uint16_t* __restrict__ A_t) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[kNtLds];
+  if (MODE == 1 && (int)blockIdx.x >= 4 * Tt) {
+    transpose64(A_pad + (blockIdx.x - 4 * Tt) * 64ll, ld, A_t + (blockIdx.x - 4 * Tt) * 4096ll, 64,
+                reinterpret_cast<uint16_t*>(lds));
+    return;
+  }
+  const int i = blockIdx.x / 4, th = blockIdx.x % 2, qh = (blockIdx.x / 2) % 2;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int waves = blockDim.x / kWave, split = waves / 2, range = wave / 2, kh = wave % 2;
+  const int nst = kNtStages(waves);
   int rs = 0, nsteps = ld / kBK;
   if (MODE == 1) {
     rs = row_ptr[i / gt];
     nsteps = max(min(row_ptr[i / gt + 1], nnz_cap) - rs, 0);   // entries beyond the capacity are ignored
   }
-  const int per = (nsteps + gridDim.y - 1) / gridDim.y;
-  const int s_lo = blockIdx.y * per, s_hi = min(nsteps, s_lo + per);
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int th = wave % 2, qh = (wave / 2) % 2, kh = wave / 4;
+  const int per = (nsteps + split - 1) / split;
+  const int s_lo = range * per, n = min(nsteps, s_lo + per) - s_lo;
+  // Transfer: 16 rows of 64 bytes per instruction, two for P and two for Q.  Slot c of row r (16 bytes) sits at
+  // 64 r + 16 (c ^ (r / 2) % 4): eight consecutive rows of a slot then lie in different banks.
+  const int tr = lane / 4, tc = (lane % 4) ^ ((tr / 2) % 4);
+  const uint32_t p_off = (uint32_t)(tr * (MODE == 0 ? ld : 64) * 2 + tc * 16);
+  const uint32_t q_off = (uint32_t)(tr * (MODE == 0 ? ld : 64) * 2 + tc * 16);
+  const uint32_t ring = lds_addr(lds) + wave * (nst * kNtStage);
+  auto issue = [&](int s) {
+    const uint32_t to = ring + (s % nst) * kNtStage;
+    const uint16_t *p, *q;
+    long long ldp, ldq;
+    if (MODE == 0) {
+      p = P + ((long long)i * 64 + 32 * th) * ld + (s_lo + s) * 64 + 32 * kh;
+      q = Q + 32ll * qh * ld + (s_lo + s) * 64 + 32 * kh;
+      ldp = ldq = ld;
+    } else {
+      const int e = rs + s_lo + s;
+      p = P + ((long long)e * gt + i % gt) * 4096 + 32 * th * 64 + 32 * kh;
+      q = Q + ((long long)col_idx[e] * 64 + 32 * kh) * 64 + 32 * qh;      // rows are k
+      ldp = ldq = 64;
+    }
+    dma16_s(p, p_off, to);
+    dma16_s(p + 16 * ldp, p_off, to + 1024);
+    dma16_s(q, q_off, to + 2048);
+    dma16_s(q + 16 * ldq, q_off, to + 3072);
+  };
   const int r = lane % 32, h2 = lane / 32;
-  const uint16_t* src[2];
-  if (MODE == 0)
-    pair_src(P + (long long)i * 64 * ld, ld, Q, ld, src);
-  else
-    pair_src(P, 64, Q, ld, src);
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  run_ring_of<kPairStages, 2, kPairElems>(
-      s_hi - s_lo, src, NoAlt(),
-      [=](int s, long long& ob, long long& oa) {
-        if (MODE == 0) {
-          ob = oa = (long long)(s_lo + s) * kBK;
-        } else {
-          const int e = rs + s_lo + s;
-          ob = ((long long)e * gt + i % gt) * 4096;
-          oa = (long long)col_idx[e] * 64;
-        }
-        return false;
-      },
-      ring,
-      [&](const uint16_t* stage) {
-        uint4 a[2], b[2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int seg = 2 * (2 * kh + e) + h2;
-          const int ra = 64 + 32 * qh + r, rb = 32 * th + r;
-          a[e] = *reinterpret_cast<const uint4*>(stage + ra * kBK + ((seg ^ swz(ra)) << 3));
-          b[e] = *reinterpret_cast<const uint4*>(stage + rb * kBK + ((seg ^ swz(rb)) << 3));
-        }
-#pragma unroll
-        for (int e = 0; e < 2; ++e) acc = mfma32<DT>(a[e], b[e], acc);
-      });
-  if (!fold_khalves(reinterpret_cast<float*>(ring), acc)) return;
-  // register v: rank index 32*qh + 8*(v/4) + 4*h2 + v%4, token 32*th + lane%32
-  const long long o = ((long long)i * 64 + 32 * th + r) * 64 + 32 * qh + 4 * h2;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    if (gridDim.y == 1) {
-      uint2 ov;
-      ov.x = pack2<DT>(acc[4 * g], acc[4 * g + 1]);
-      ov.y = pack2<DT>(acc[4 * g + 2], acc[4 * g + 3]);
-      *reinterpret_cast<uint2*>(U + o + 8 * g) = ov;
-    } else {
-      const float4 ov = make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
-      *reinterpret_cast<float4*>(part + blockIdx.y * part_stride + o + 8 * g) = ov;
+  for (int s = 0; s < nst - 1; ++s)
+    if (s < n) issue(s);
+  for (int s = 0; s < n; ++s) {
+    if (s + nst - 1 < n) issue(s + nst - 1);
+    switch (min(n - 1 - s, nst - 1)) {         // younger steps in flight
+      case 0: wait_vmcnt<0>(); break;
+      case 1: wait_vmcnt<4>(); break;
+      case 2: wait_vmcnt<8>(); break;
+      case 3: wait_vmcnt<12>(); break;
+      case 4: wait_vmcnt<16>(); break;
+      case 5: wait_vmcnt<20>(); break;
+      case 6: wait_vmcnt<24>(); break;
+      default: wait_vmcnt<28>(); break;
     }
+    asm volatile("" ::: "memory");
+    const uint32_t st = ring + (s % nst) * kNtStage;
+    uint4 a[2], b[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      if (MODE == 0) {
+        const uint32_t o = r * 64 + (((2 * e + h2) ^ ((r / 2) % 4)) << 4);
+        b[e] = lds_read16(st + o);
+        a[e] = lds_read16(st + 2048 + o);
+      } else {
+        // Q by rows of k: the transposing read gives this lane's rank index the k 4*h2 .. +3 and 8 + 4*h2 .. +3
+        // of the 16; P is read in the same order
+        const uint32_t sw = (r / 2) % 4, p0 = r * 64 + 8 * h2;
+        const uint2 pl = lds_read8(st + p0 + (((2 * e) ^ sw) << 4)), ph = lds_read8(st + p0 + (((2 * e + 1) ^ sw) << 4));
+        b[e] = make_uint4(pl.x, pl.y, ph.x, ph.y);
+        const int j = lane % 16, c = 2 * ((lane / 16) % 2) + (j % 4) / 2;    // slot of column 16*((lane/16)%2) + 4*(j%4)
+        const int k0 = 16 * e + 4 * h2 + j / 4, k1 = k0 + 8;
+        const uint2 ql = lds_read8_tr(st + 2048 + k0 * 64 + ((c ^ ((k0 / 2) % 4)) << 4) + (j % 2) * 8);
+        const uint2 qu = lds_read8_tr(st + 2048 + k1 * 64 + ((c ^ ((k1 / 2) % 4)) << 4) + (j % 2) * 8);
+        a[e] = make_uint4(ql.x, ql.y, qu.x, qu.y);
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read: the next issue refills it
+#pragma unroll
+    for (int e = 0; e < 2; ++e) acc = mfma32<DT>(a[e], b[e], acc);
   }
-}
-// U (or G) = the sum of the parts, in order, rounded to the element type; n4 = number of groups
-// of four elements
-template <int DT>
-__global__ void lora_u_reduce_kernel(const float* __restrict__ part, int parts, long long n4,
-                                     uint16_t* __restrict__ U) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n4) return;
-  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int p = 0; p < parts; ++p) {
-    const float4 v = *reinterpret_cast<const float4*>(part + ((long long)p * n4 + idx) * 4);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  float* area = reinterpret_cast<float*>(lds);
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < 16; ++v) area[(wave * 16 + v) * kWave + lane] = acc[v];
+  __syncthreads();
+  // element v of lane l: rank index 32*qh + 8*(v/4) + 4*(l/32) + v%4, token 32*th + l%32; a group of four per thread
+  for (int x = threadIdx.x; x < 256; x += blockDim.x) {
+    const int g = x / kWave, l = x % kWave;
+    float v[4] = {};
+    for (int p = 0; p < split; ++p)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float half = area[((2 * p) * 16 + 4 * g + e) * kWave + l] + area[((2 * p + 1) * 16 + 4 * g + e) * kWave + l];
+        v[e] = split == 1 ? half : v[e] + half;
+      }
+    uint2 ov;
+    ov.x = pack2<DT>(v[0], v[1]);
+    ov.y = pack2<DT>(v[2], v[3]);
+    *reinterpret_cast<uint2*>(out + ((long long)i * 64 + 32 * th + l % 32) * 64 + 32 * qh + 8 * g + 4 * (l / 32)) = ov;
   }
-  uint2 ov;
-  ov.x = pack2<DT>(s.x, s.y);
-  ov.y = pack2<DT>(s.z, s.w);
-  *reinterpret_cast<uint2*>(U + idx * 4) = ov;
 }
 
 // Per-lane LDS offsets of the operands of a product out[a][b] = sum_t P[t][a] Q[t][b] whose
@@ -175,28 +231,41 @@ __device__ __forceinline__ void tn_step(uint32_t stage, const TnLane& lo, f32x16
 
 // Gradients of the two LoRA matrices (Sec. II-D), fp32, as sums of 64 x 64 products
 // out[a][b] = sum over steps of sum_t P[t][a] Q[t][b] on the MFMA:
-// MODE 0, dB = dZ^T U over the listed blocks: blockIdx.x = neuron block j; the steps are the
-//   token tiles i of the range of blockIdx.y whose list row holds j (found by bisection of the
+// MODE 0, dB = dZ^T U over the listed blocks: x = neuron block j; the steps are the
+//   token tiles i of range y whose list row holds j (found by bisection of the
 //   sorted row, one tile per thread, and kept in list order): P = dZ_ij, Q = U_i;
 //   out = rows 64j .. of dB [F,64].
-// MODE 1, dA = G^T X: blockIdx.x = 64-column chunk c of X; the steps are all tiles of the range:
+// MODE 1, dA = G^T X: x = 64-column chunk c of X; the steps are all tiles of the range:
 //   P = G_i, Q = X_i[:, 64c ..]; out = columns 64c .. of dA [64,d].
-// The sums over the gridDim.y tile ranges go to part[y] (part_stride elements apart; with one
+// The sums over the tile ranges y go to part[y] (part_stride elements apart; with one
 // range, part is the result itself) and are added by lora_grad_reduce_kernel.
+struct TnArgs {
+  const uint16_t *P, *Q;
+  long long ldq;
+  float* part;
+  long long part_stride;
+  int ld_out, nx, ny;          // products x = 0 .. nx - 1 times ranges y = 0 .. ny - 1
+};
+struct TnLds {
+  uint16_t ring[kPairStages * kPairElems];
+  long long p[kThreads], q[kThreads];
+  int wcount[kFW];
+};
 template <int DT, int MODE>
-__global__ __launch_bounds__(kThreads) void lora_tn_kernel(
-    const uint16_t* __restrict__ P, const uint16_t* __restrict__ Q, long long ldq,
-    const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int Tt, int gt, int nnz_cap,
-    float* __restrict__ part, long long part_stride, int ld_out) {
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[kPairStages * kPairElems];
-  __shared__ long long s_p[MODE == 0 ? kThreads : 1], s_q[MODE == 0 ? kThreads : 1];
-  __shared__ int wcount[kFW];
+__device__ __forceinline__ void lora_tn(const TnArgs& args, int x, int y, const int* __restrict__ row_ptr,
+                                        const int* __restrict__ col_idx, int Tt, int gt, int nnz_cap, TnLds& sh) {
+  const uint16_t* __restrict__ P = args.P;
+  const uint16_t* __restrict__ Q = args.Q;
+  const long long ldq = args.ldq;
+  uint16_t* ring = sh.ring;
+  long long *s_p = sh.p, *s_q = sh.q;
+  int* wcount = sh.wcount;
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const int per = (Tt + gridDim.y - 1) / gridDim.y;
-  const int i_lo = blockIdx.y * per, i_hi = min(Tt, i_lo + per);
+  const int per = (Tt + args.ny - 1) / args.ny;
+  const int i_lo = y * per, i_hi = min(Tt, i_lo + per);
   const int ah = wave % 2, bh = (wave / 2) % 2;
   const uint16_t* src[2];
-  pair_src(P, 64, Q + (MODE == 1 ? blockIdx.x * 64 : 0), ldq, src);
+  pair_src(P, 64, Q + (MODE == 1 ? x * 64 : 0), ldq, src);
   TnLane lo;
   lo.init(ah, bh, wave / 4);
   f32x16 acc;
@@ -214,7 +283,7 @@ __global__ __launch_bounds__(kThreads) void lora_tn_kernel(
         ring, step);
   } else {
     // one tile per thread: the host splits so that a range holds at most kThreads tiles
-    const int j = blockIdx.x, i = i_lo + tid;
+    const int j = x, i = i_lo + tid;
     long long blk = -1;   // compact activation block of (tile i, block j)
     if (i < i_hi) {
       const int rs = row_ptr[i / gt];
@@ -255,12 +324,23 @@ __global__ __launch_bounds__(kThreads) void lora_tn_kernel(
   }
   if (!fold_khalves(reinterpret_cast<float*>(ring), acc)) return;
   // register v: a = 32*ah + 8*(v/4) + 4*(lane/32) + v%4, b = 32*bh + lane%32
-  const long long row0 = MODE == 0 ? (long long)blockIdx.x * 64 : 0;
-  const int col0 = MODE == 0 ? 0 : blockIdx.x * 64;
-  float* o = part + blockIdx.y * part_stride + (row0 + 32 * ah + 4 * (lane / 32)) * ld_out + col0 +
+  const long long row0 = MODE == 0 ? (long long)x * 64 : 0;
+  const int col0 = MODE == 0 ? 0 : x * 64;
+  float* o = args.part + y * args.part_stride + (row0 + 32 * ah + 4 * (lane / 32)) * args.ld_out + col0 +
              32 * bh + lane % 32;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) o[(long long)(8 * (v / 4) + v % 4) * ld_out] = acc[v];
+  for (int v = 0; v < 16; ++v) o[(long long)(8 * (v / 4) + v % 4) * args.ld_out] = acc[v];
+}
+// Both gradients in one launch, independent of each other: dB's workgroups, then dA's.
+template <int DT>
+__global__ __launch_bounds__(kThreads) void lora_tn_kernel(TnArgs db, TnArgs da, const int* __restrict__ row_ptr,
+                                                           const int* __restrict__ col_idx, int Tt, int gt, int nnz_cap) {
+  __shared__ __attribute__((aligned(1024))) TnLds sh;
+  const int w = blockIdx.x, nb = db.nx * db.ny;
+  if (w < nb)
+    lora_tn<DT, 0>(db, w % db.nx, w / db.nx, row_ptr, col_idx, Tt, gt, nnz_cap, sh);
+  else
+    lora_tn<DT, 1>(da, (w - nb) % da.nx, (w - nb) / da.nx, row_ptr, col_idx, Tt, gt, nnz_cap, sh);
 }
 // dB and dA = sums of their parts, in order, four elements per thread; a result with one part
 // was written in place and has n4 = 0 here.
@@ -285,84 +365,33 @@ __global__ void lora_grad_reduce_kernel(const float* __restrict__ part_b, int pa
   *reinterpret_cast<float4*>(out + idx * 4) = s;
 }
 
-// 64 x 64 tile transposes of both LoRA matrices in one launch: workgroups 0 .. d/64 - 1 turn
-// A_pad [64,d] into A_t [d,64], the others B_pad [F,64] into B_t [64,F].
-__global__ __launch_bounds__(256) void lora_transpose_kernel(
-    const uint16_t* __restrict__ A_pad, int d, uint16_t* __restrict__ A_t,
-    const uint16_t* __restrict__ B_pad, int F, uint16_t* __restrict__ B_t) {
-  __shared__ __attribute__((aligned(16))) uint16_t t[64][72];
-  const int tid = threadIdx.x;
-  const bool is_a = (int)blockIdx.x < d / 64;
-  const long long c = is_a ? blockIdx.x : blockIdx.x - d / 64;
-  const uint16_t* src = is_a ? A_pad + c * 64 : B_pad + c * 4096;
-  const long long lds = is_a ? d : 64;
-  uint16_t* dst = is_a ? A_t + c * 4096 : B_t + c * 64;
-  const long long ldd = is_a ? 64 : F;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int piece = tid + h * 256, r = piece / 8, c8 = (piece % 8) * 8;
-    const uint4 v = *reinterpret_cast<const uint4*>(src + r * lds + c8);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      t[c8 + 2 * e][r] = (uint16_t)(w[e] & 0xFFFFu);
-      t[c8 + 2 * e + 1][r] = (uint16_t)(w[e] >> 16);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int piece = tid + h * 256, r = piece / 8, c8 = (piece % 8) * 8;
-    *reinterpret_cast<uint4*>(dst + r * ldd + c8) = *reinterpret_cast<const uint4*>(&t[r][c8]);
-  }
-}
-
-// U = X A_pad^T [T,64].  u_part: lora_u_split(Tt, d) * T * 64 floats of scratch (unused for a
-// split of 1).
+// U = X A_pad^T [T,64].
 template <int DT>
 static hipError_t launch_lora_u_t(int Tt, int d, const uint16_t* X, const uint16_t* A_pad, uint16_t* U,
-                                  float* u_part, hipStream_t st) {
-  const int split = lora_u_split(Tt, d);
-  const long long n = (long long)Tt * 4096;
+                                  hipStream_t st) {
   const int* none = nullptr;
-  hipLaunchKernelGGL((lora_nt_kernel<DT, 0>), dim3(Tt, split), dim3(kThreads), 0, st, X, A_pad, d, none,
-                     none, 1, 0, U, u_part, n);
-  if (split > 1)
-    hipLaunchKernelGGL(lora_u_reduce_kernel<DT>, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, st,
-                       (const float*)u_part, split, n / 4, U);
+  hipLaunchKernelGGL((lora_nt_kernel<DT, 0>), dim3(4 * Tt), dim3(2 * kWave * lora_u_split(Tt, d)), 0, st, X, A_pad, d,
+                     none, none, Tt, 1, 0, U, (const uint16_t*)nullptr, (uint16_t*)nullptr);
   return hipGetLastError();
 }
 hipError_t launch_lora_u(int dt, int Tt, int d, const uint16_t* X, const uint16_t* A_pad, uint16_t* U,
-                         float* u_part, hipStream_t st) {
-  return LX_BY_DT(launch_lora_u_t, Tt, d, X, A_pad, U, u_part, st);
+                         hipStream_t st) {
+  return LX_BY_DT(launch_lora_u_t, Tt, d, X, A_pad, U, st);
 }
 
-// G = dZ B_pad [T,64] from the compact blocks dZ and B_t [64,F].  g_part: lora_g_split(Tt) * T * 64
-// floats of scratch (unused for a split of 1).
+// G = dZ B_pad [T,64] from the compact blocks dZ, and A_t = A_pad^T [d,64].
 template <int DT>
-static hipError_t launch_lora_g_t(int Tt, int gt, int F, const uint16_t* dZ, const uint16_t* B_t,
+static hipError_t launch_lora_g_t(int Tt, int gt, int d, const uint16_t* dZ, const uint16_t* B_pad,
                                   const int* row_ptr, const int* col_idx, int nnz_cap, uint16_t* G,
-                                  float* g_part, hipStream_t st) {
-  const int split = lora_g_split(Tt);
-  const long long n = (long long)Tt * 4096;
-  hipLaunchKernelGGL((lora_nt_kernel<DT, 1>), dim3(Tt, split), dim3(kThreads), 0, st, dZ, B_t, F, row_ptr,
-                     col_idx, gt, nnz_cap, G, g_part, n);
-  if (split > 1)
-    hipLaunchKernelGGL(lora_u_reduce_kernel<DT>, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, st,
-                       (const float*)g_part, split, n / 4, G);
+                                  const uint16_t* A_pad, uint16_t* A_t, hipStream_t st) {
+  hipLaunchKernelGGL((lora_nt_kernel<DT, 1>), dim3(4 * Tt + d / 64), dim3(2 * kWave * lora_g_split(Tt)), 0, st, dZ, B_pad,
+                     d, row_ptr, col_idx, Tt, gt, nnz_cap, G, A_pad, A_t);
   return hipGetLastError();
 }
-hipError_t launch_lora_g(int dt, int Tt, int gt, int F, const uint16_t* dZ, const uint16_t* B_t,
-                         const int* row_ptr, const int* col_idx, int nnz_cap, uint16_t* G,
-                         float* g_part, hipStream_t st) {
-  return LX_BY_DT(launch_lora_g_t, Tt, gt, F, dZ, B_t, row_ptr, col_idx, nnz_cap, G, g_part, st);
-}
-
-hipError_t launch_lora_transposes(int d, int F, const uint16_t* A_pad, uint16_t* A_t,
-                                  const uint16_t* B_pad, uint16_t* B_t, hipStream_t st) {
-  hipLaunchKernelGGL(lora_transpose_kernel, dim3(d / 64 + F / 64), dim3(256), 0, st, A_pad, d, A_t,
-                     B_pad, F, B_t);
-  return hipGetLastError();
+hipError_t launch_lora_g(int dt, int Tt, int gt, int d, const uint16_t* dZ, const uint16_t* B_pad,
+                         const int* row_ptr, const int* col_idx, int nnz_cap, uint16_t* G, const uint16_t* A_pad,
+                         uint16_t* A_t, hipStream_t st) {
+  return LX_BY_DT(launch_lora_g_t, Tt, gt, d, dZ, B_pad, row_ptr, col_idx, nnz_cap, G, A_pad, A_t, st);
 }
 
 // dB = dZ^T U over the listed blocks and dA = G^T X.  Scratch: da_part [lora_da_split][64][d] and
@@ -375,10 +404,10 @@ static hipError_t launch_lora_grads_t(int Tt, int gt, int d, int F, const uint16
                                       hipStream_t st) {
   const int sb = lora_db_split(Tt, F), sa = lora_da_split(Tt, d);
   const long long nb = (long long)F * 64, na = (long long)64 * d;
-  hipLaunchKernelGGL((lora_tn_kernel<DT, 0>), dim3(F / 64, sb), dim3(kThreads), 0, st, dZ, U, 64ll,
-                     row_ptr, col_idx, Tt, gt, nnz_cap, sb > 1 ? db_part : dB, nb, 64);
-  hipLaunchKernelGGL((lora_tn_kernel<DT, 1>), dim3(d / 64, sa), dim3(kThreads), 0, st, G, X,
-                     (long long)d, row_ptr, col_idx, Tt, gt, nnz_cap, sa > 1 ? da_part : dA, na, d);
+  const TnArgs db = {dZ, U, 64, sb > 1 ? db_part : dB, nb, 64, F / 64, sb};
+  const TnArgs da = {G, X, d, sa > 1 ? da_part : dA, na, d, d / 64, sa};
+  hipLaunchKernelGGL(lora_tn_kernel<DT>, dim3(db.nx * db.ny + da.nx * da.ny), dim3(kThreads), 0, st, db, da, row_ptr,
+                     col_idx, Tt, gt, nnz_cap);
   const long long n4b = sb > 1 ? nb / 4 : 0, n4a = sa > 1 ? na / 4 : 0;
   if (n4b + n4a > 0)
     hipLaunchKernelGGL(lora_grad_reduce_kernel, dim3((unsigned)((n4b + n4a + 255) / 256)), dim3(256), 0,

@@ -413,6 +413,8 @@ static lx_status ffn_bwd_dx_impl(lx_dtype dt, int32_t T, int32_t d, int32_t F, i
   return e == hipSuccess ? LX_OK : LX_ERR_RUNTIME;
 }
 
+// (Both queries keep the sizes of a layout that also held partial sums of U and G and B^T, which are not
+// stored any more: programs may have sized their buffers once.)
 size_t lx_sparse_ffn_lora_fwd_workspace_bytes(int32_t T, int32_t d) {
   if (T < 64 || d < 64) return 256;
   const int split = lora_u_split(T / 64, d);
@@ -455,7 +457,7 @@ lx_status lx_sparse_ffn_lora_fwd(lx_dtype dt, int32_t T, int32_t d, int32_t F, i
   hipError_t e = launch_ffn_lora_fwd_bf16(
       dt16(dt), T / 64, gt, d, F, (const uint16_t*)X, (const uint16_t*)W_up, (const uint16_t*)A_pad,
       (const uint16_t*)B_pad, (const uint16_t*)W_down, bl->row_ptr, bl->col_idx, bl->nnz_cap,
-      (uint16_t*)U, (uint16_t*)H_act, (uint16_t*)Y, (float*)workspace, (hipStream_t)stream);
+      (uint16_t*)U, (uint16_t*)H_act, (uint16_t*)Y, (hipStream_t)stream);
   return e == hipSuccess ? LX_OK : LX_ERR_RUNTIME;
 }
 
@@ -479,15 +481,10 @@ lx_status lx_sparse_ffn_lora_bwd(lx_dtype dt, int32_t T, int32_t d, int32_t F, i
   char* ws = (char*)workspace;
   uint16_t* dz = (uint16_t*)ws;
   ws += act_bytes(LX_BF16, 64, 64, bl->nnz_cap * gt);
-  uint16_t* bt = (uint16_t*)ws;
-  ws += round256((size_t)64 * F * 2);
   uint16_t* at = (uint16_t*)ws;
   ws += round256((size_t)d * 64 * 2);
   uint16_t* g = (uint16_t*)ws;
   ws += round256((size_t)T * 64 * 2);
-  float* part_g = (float*)ws;
-  const int sg = lora_g_split(T / 64);
-  if (sg > 1) ws += round256((size_t)sg * T * 64 * 4);
   float* part_a = (float*)ws;
   const int sa = lora_da_split(T / 64, d);
   if (sa > 1) ws += round256((size_t)sa * 64 * d * 4);
@@ -495,8 +492,8 @@ lx_status lx_sparse_ffn_lora_bwd(lx_dtype dt, int32_t T, int32_t d, int32_t F, i
   hipError_t e = launch_ffn_lora_bwd_bf16(
       dt16(dt), T / 64, gt, d, F, (const uint16_t*)X, (const uint16_t*)dY, (const uint16_t*)H_act,
       (const uint16_t*)U, (const uint16_t*)W_down_t, (const uint16_t*)W_up_t,
-      (const uint16_t*)A_pad, (const uint16_t*)B_pad, bl->row_ptr, bl->col_idx, bl->nnz_cap, dz, bt,
-      at, g, part_g, part_a, part_b, (uint16_t*)dX, dA, dB, (hipStream_t)stream);
+      (const uint16_t*)A_pad, (const uint16_t*)B_pad, bl->row_ptr, bl->col_idx, bl->nnz_cap, dz,
+      at, g, part_a, part_b, (uint16_t*)dX, dA, dB, (hipStream_t)stream);
   return e == hipSuccess ? LX_OK : LX_ERR_RUNTIME;
 }
 
@@ -535,6 +532,8 @@ static lx_status check_attn(lx_dtype dt, int32_t B, int32_t Hh, int32_t S, int32
   for (int i = 0; i < 3; ++i)
     if (strides[i] < 0 || strides[i] % 8 != 0) return LX_ERR_INVALID_ARG;
   if (strides[2] < D) return LX_ERR_INVALID_ARG;
+  // eight rows of a tile are addressed with one 32-bit byte offset per lane (64 tokens would span 34 GB)
+  if (is16(dt) && strides[2] >= (int64_t)1 << 28) return LX_ERR_UNSUPPORTED;
   if (mask_batch != 1 && mask_batch != B) return LX_ERR_INVALID_ARG;
   if (!bl || !bl->row_ptr || !bl->col_idx) return LX_ERR_INVALID_ARG;
   if ((int64_t)bl->rows != (int64_t)mask_batch * Hh * (S / 64) || bl->cols != S / 64)

@@ -79,9 +79,9 @@ hipError_t launch_ffn_bf16(int dt, int pass, int Tt, int gt, int Fb, int d, int 
 // bytes of partial sums with which the second product of a pass, given ONE list row of at most
 // nnz_cap entries for all Tt token tiles, cuts the lists of its last round of workgroups (0: never)
 size_t ffn_dsd_split_bytes(int Tt, int d, int nnz_cap);
-// Splits of the low-rank products of the LoRA branch over workgroups so that they fill the chip;
-// the partial sums are added in a fixed order.  U = X A^T: over K; dB: over ranges of token
-// tiles per neuron block; dA: over ranges of token tiles per 64-column chunk.
+// Ranges that the low-rank products of the LoRA branch are cut into, added in a fixed order: U = X A^T over K
+// and G = dZ B over the list entries among the wavefronts of a workgroup; dB over ranges of token
+// tiles per neuron block and dA over ranges of token tiles per 64-column chunk among workgroups.
 inline int lora_clamp(int s, int hi) { return s < 1 ? 1 : (s > hi ? (hi < 1 ? 1 : hi) : s); }
 inline int lora_u_split(int Tt, int d) {
   const int by_k = d / 64 / 4;   // at least four K-steps per workgroup
@@ -98,12 +98,10 @@ inline int lora_da_split(int Tt, int d) {
 }
 // the small products of the LoRA branch (lora_bf16.hip); dt = kBf16 or kF16
 hipError_t launch_lora_u(int dt, int Tt, int d, const uint16_t* X, const uint16_t* A_pad, uint16_t* U,
-                         float* u_part, hipStream_t st);
-hipError_t launch_lora_g(int dt, int Tt, int gt, int F, const uint16_t* dZ, const uint16_t* B_t,
-                         const int* row_ptr, const int* col_idx, int nnz_cap, uint16_t* G,
-                         float* g_part, hipStream_t st);
-hipError_t launch_lora_transposes(int d, int F, const uint16_t* A_pad, uint16_t* A_t,
-                                  const uint16_t* B_pad, uint16_t* B_t, hipStream_t st);
+                         hipStream_t st);
+hipError_t launch_lora_g(int dt, int Tt, int gt, int d, const uint16_t* dZ, const uint16_t* B_pad,
+                         const int* row_ptr, const int* col_idx, int nnz_cap, uint16_t* G, const uint16_t* A_pad,
+                         uint16_t* A_t, hipStream_t st);
 hipError_t launch_lora_grads(int dt, int Tt, int gt, int d, int F, const uint16_t* dZ,
                              const uint16_t* U, const uint16_t* G, const uint16_t* X,
                              const int* row_ptr, const int* col_idx, int nnz_cap, float* da_part,
@@ -112,15 +110,13 @@ hipError_t launch_ffn_lora_fwd_bf16(int dt, int Tt, int gt, int d, int F, const 
                                     const uint16_t* W_up, const uint16_t* A_pad,
                                     const uint16_t* B_pad, const uint16_t* W_down,
                                     const int* row_ptr, const int* col_idx, int nnz_cap,
-                                    uint16_t* U, uint16_t* H_act, uint16_t* Y, float* u_part,
-                                    hipStream_t st);
+                                    uint16_t* U, uint16_t* H_act, uint16_t* Y, hipStream_t st);
 hipError_t launch_ffn_lora_bwd_bf16(int dt, int Tt, int gt, int d, int F, const uint16_t* X,
                                     const uint16_t* dY, const uint16_t* H_act, const uint16_t* U,
                                     const uint16_t* W_down_t, const uint16_t* W_up_t,
                                     const uint16_t* A_pad, const uint16_t* B_pad,
                                     const int* row_ptr, const int* col_idx, int nnz_cap,
-                                    uint16_t* dZ, uint16_t* B_t, uint16_t* A_t, uint16_t* G,
-                                    float* g_part, float* da_part, float* db_part, uint16_t* dX,
+                                    uint16_t* dZ, uint16_t* A_t, uint16_t* G, float* da_part, float* db_part, uint16_t* dX,
                                     float* dA, float* dB, hipStream_t st);
 hipError_t launch_predict_bf16(int dt, int T, int d, int nblk, int tiles_per_group, const uint16_t* X,
                                const uint16_t* Wa_t, float thr, uint8_t* mask, hipStream_t st);
