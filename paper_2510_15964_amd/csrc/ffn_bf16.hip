@@ -104,39 +104,74 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[Tl::NI][Tl::TI]) {
       for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
 }
 
-// Stores one accumulator: rows t (this lane's token, stride ld) and 32 columns from `out` on; bias over
-// the columns, then ReLU (relu) or the gate by `gate` > 0, which is indexed like `out` (both may be null).
+// Epilogue.  The accumulators hold four consecutive columns of a lane's token; stored as they are, the 8-byte
+// pieces of 32 rows per instruction took up to two fifths of a launch (4096 tokens, d = 2048, one list of 14
+// blocks, second product: 24 us, 14 without the stores).  They go through LDS instead, as [64 x 64] blocks
+// (tile t, group of 64 columns e at index t * TN + e) whose 128-byte rows have their 16-byte slots XOR-swizzled
+// with the row, and leave in 16-byte pieces, eight lanes to a full row of a block.
+__device__ __forceinline__ uint32_t out_slot(int block, int row, int slot) {
+  return (uint32_t)(block * 8192 + row * 128 + ((slot ^ (row & 7)) << 4));
+}
+// One 32 x 32 accumulator (token rows th, columns nh .. of the block) -> LDS, rounded; bias: the 32 columns' (or
+// null), then ReLU.
 template <int DT>
-__device__ __forceinline__ void store_acc(const f32x16& acc, uint16_t* __restrict__ out, long long ld,
-                                          const uint16_t* __restrict__ bias, const uint16_t* __restrict__ gate,
-                                          bool relu) {
-  const int lane = threadIdx.x % kWave, tl = lane % 32, nq = (lane / 32) * 4;
+__device__ __forceinline__ void acc_to_lds(const f32x16& acc, uint32_t lds, int block, int th, int nh,
+                                           const uint16_t* __restrict__ bias, bool relu) {
+  const int lane = threadIdx.x % kWave, tl = th + lane % 32, h2 = lane / 32;
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    const int n = 8 * g + nq;
-    const long long o = (long long)tl * ld + n;
     float v[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = acc[4 * g + e];
     if (bias) {
-      const uint2 bb = *reinterpret_cast<const uint2*>(bias + n);
+      const uint2 bb = *reinterpret_cast<const uint2*>(bias + 8 * g + 4 * h2);
       v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
       v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
     }
     if (relu) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-    } else if (gate) {
-      const uint2 gg = *reinterpret_cast<const uint2*>(gate + o);
-      if (!(to_f32<DT>(gg.x & 0xFFFFu) > 0.f)) v[0] = 0.f;
-      if (!(to_f32<DT>(gg.x >> 16) > 0.f)) v[1] = 0.f;
-      if (!(to_f32<DT>(gg.y & 0xFFFFu) > 0.f)) v[2] = 0.f;
-      if (!(to_f32<DT>(gg.y >> 16) > 0.f)) v[3] = 0.f;
     }
-    uint2 ov;
-    ov.x = pack2<DT>(v[0], v[1]);
-    ov.y = pack2<DT>(v[2], v[3]);
-    *reinterpret_cast<uint2*>(out + o) = ov;
+    lds_write8(lds + out_slot(block, tl, nh / 8 + g) + 8 * h2, make_uint2(pack2<DT>(v[0], v[1]), pack2<DT>(v[2], v[3])));
+  }
+}
+// The elements of v whose gate is positive, 0 for the others (two packed 16-bit elements each).
+template <int DT>
+__device__ __forceinline__ uint32_t gate2(uint32_t v, uint32_t g) {
+  return (to_f32<DT>(g & 0xFFFFu) > 0.f ? v & 0xFFFFu : 0u) | (to_f32<DT>(g >> 16) > 0.f ? v & 0xFFFF0000u : 0u);
+}
+// The blocks in LDS -> memory: block_at(t, e) is the first element of block (t, e), its rows ld elements apart,
+// or negative: not stored.  gate: indexed like out (or null).  THROUGH: the lines are written through the L2 at
+// once instead of when the kernel ends, which is when all workgroups of a round store: second product, 4096 tokens,
+// d = 2048, one list of 14 blocks 21.0 -> 19.2 us, 8192 tokens with a list per tile 51 -> 48; no use for the first
+// product, whose outputs the second reads again.
+template <class Tl, int DT, bool THROUGH, class BlockAt>
+__device__ __forceinline__ void lds_to_out(uint32_t lds, uint16_t* __restrict__ out, long long ld,
+                                           const uint16_t* __restrict__ gate, BlockAt block_at) {
+  constexpr int kPieces = Tl::TM * Tl::TN * 512, kT = Tl::kTileThreads, kPer = kPieces / kT;
+  constexpr int kGroup = kPer < 8 ? kPer : 8;      // gate loads in flight
+#pragma unroll
+  for (int u0 = 0; u0 < kPer; u0 += kGroup) {
+    uint4 g[kGroup];
+    long long o[kGroup];
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u) {
+      const int x = (u0 + u) * kT + (int)threadIdx.x, block = x / 512, row = x % 512 / 8, slot = x % 8;
+      const long long first = block_at(block / Tl::TN, block % Tl::TN);
+      o[u] = first < 0 ? -1 : first + row * ld + slot * 8;
+      if (gate && o[u] >= 0) g[u] = *reinterpret_cast<const uint4*>(gate + o[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u) {
+      const int x = (u0 + u) * kT + (int)threadIdx.x;
+      uint4 v = lds_read16(lds + out_slot(x / 512, x % 512 / 8, x % 8));
+      if (o[u] < 0) continue;
+      if (gate) v = make_uint4(gate2<DT>(v.x, g[u].x), gate2<DT>(v.y, g[u].y), gate2<DT>(v.z, g[u].z), gate2<DT>(v.w, g[u].w));
+      if (THROUGH)
+        asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(out + o[u]), "v"(__builtin_bit_cast(u32x4, v)) : "memory");
+      else
+        *reinterpret_cast<uint4*>(out + o[u]) = v;
+    }
   }
 }
 
@@ -239,19 +274,21 @@ __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_sdd(SddAr
   f32x16 acc[Tl::NI][Tl::TI];
   zero_acc<Tl>(acc);
   run_tile<Tl, DT>(src.ksteps + (LORA ? 1 : 0), lds_addr(ring), wm, wn, src, acc);
+  lds_barrier();       // nobody reads the ring any more
 #pragma unroll
   for (int ni = 0; ni < Tl::NI; ++ni) {
     const int e = (wn * Tl::NI + ni) / 2, nh = 32 * ((wn * Tl::NI + ni) % 2);
-    if (e >= nb) continue;
-    const uint16_t* bias = a.bias ? a.bias + a.col_idx[p0 + e] * 64 + nh : nullptr;
+    const uint16_t* bias = a.bias && e < nb ? a.bias + a.col_idx[p0 + e] * 64 + nh : nullptr;
 #pragma unroll
-    for (int ti = 0; ti < Tl::TI; ++ti) {
-      const int i = i0 + (wm * Tl::TI + ti) / 2, th = 32 * ((wm * Tl::TI + ti) % 2);
-      if (i >= a.Tt) continue;
-      const long long p = ((long long)rs * a.gt + (long long)(first + e) * a.gt + i % a.gt) * 4096 + th * 64 + nh;
-      store_acc<DT>(acc[ni][ti], a.out + p, 64, bias, a.gate ? a.gate + p : nullptr, !a.gate);
-    }
+    for (int ti = 0; ti < Tl::TI; ++ti)
+      acc_to_lds<DT>(acc[ni][ti], lds_addr(ring), (wm * Tl::TI + ti) / 2 * Tl::TN + e, 32 * ((wm * Tl::TI + ti) % 2), nh,
+                     bias, !a.gate);
   }
+  lds_barrier();
+  lds_to_out<Tl, DT, false>(lds_addr(ring), a.out, 64, a.gate, [&](int t, int e) {
+    const int i = i0 + t;
+    return i < a.Tt && e < nb ? (((long long)rs + first + e) * a.gt + i % a.gt) * 4096 : -1ll;
+  });
 }
 
 // Which token tile the workgroups of grid row `slot` work on.  A workgroup of the dsd kernel
@@ -411,9 +448,9 @@ __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_dsd(DsdAr
   f32x16 acc[Tl::NI][Tl::TI];
   zero_acc<Tl>(acc);
   run_tile<Tl, DT>(n_i + (LORA ? 1 : 0), lds_addr(ring), wm, wn, src, acc);
-  if (slot >= 0) {   // the piece's partial sums: [wave][accumulator][lane][16 registers]
+  if (slot >= 0) {   // the piece's partial sums: [wave][accumulator][quarter][lane][4 registers]
     f32x4* dst = reinterpret_cast<f32x4*>(a.part + ((size_t)slot * Tl::kWaves + wave) * (Tl::NI * Tl::TI * 16) * kWave) +
-                 (threadIdx.x % kWave) * 4;
+                 threadIdx.x % kWave;
 #pragma unroll
     for (int x = 0; x < Tl::NI; ++x)
 #pragma unroll
@@ -421,53 +458,57 @@ __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_dsd(DsdAr
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const f32x4 v4 = {acc[x][y][4 * q], acc[x][y][4 * q + 1], acc[x][y][4 * q + 2], acc[x][y][4 * q + 3]};
-          dst[(x * Tl::TI + y) * (kWave * 4) + q] = v4;
+          dst[((x * Tl::TI + y) * 4 + q) * kWave] = v4;
         }
     return;
   }
+  lds_barrier();       // nobody reads the ring any more
 #pragma unroll
   for (int ni = 0; ni < Tl::NI; ++ni) {
-    const int n = n0 + 32 * (wn * Tl::NI + ni);
-    if (n >= a.ncols) continue;
+    const int c = wn * Tl::NI + ni, n = n0 + 32 * c;
 #pragma unroll
-    for (int ti = 0; ti < Tl::TI; ++ti) {
-      const int t = i0 * 64 + 32 * (wm * Tl::TI + ti);
-      if (t >= a.Tt * 64) continue;
-      store_acc<DT>(acc[ni][ti], a.out + (long long)t * a.ncols + n, a.ncols, a.bias ? a.bias + n : nullptr,
-                    nullptr, false);
-    }
+    for (int ti = 0; ti < Tl::TI; ++ti)
+      acc_to_lds<DT>(acc[ni][ti], lds_addr(ring), (wm * Tl::TI + ti) / 2 * Tl::TN + c / 2, 32 * ((wm * Tl::TI + ti) % 2),
+                     32 * (c % 2), a.bias && n < a.ncols ? a.bias + n : nullptr, false);
   }
+  lds_barrier();
+  lds_to_out<Tl, DT, true>(lds_addr(ring), a.out, a.ncols, nullptr, [&](int t, int e) {
+    return i0 + t < a.Tt && n0 + 64 * e < a.ncols ? (long long)(i0 + t) * 64 * a.ncols + n0 + 64 * e : -1ll;
+  });
 }
 
-// Adds the pieces of each cut unit (piece 0 first, fixed order: reproducible) and stores like the
-// kernel's own epilogue: workgroup (b, y) is unit full + b and accumulator y / (kWaves/4) of four
-// of the unit's wavefronts.
+// Adds the pieces of each cut unit (piece 0 first, fixed order: reproducible) and stores like the kernel's own
+// epilogue: workgroup (b, y) is unit full + b and the y-th 64 x 64 block of its tile; wavefront w adds the
+// accumulator that holds quadrant (w % 2, w / 2) of the block.
 template <class Tl, int DT>
 __global__ __launch_bounds__(256) void ffn_dsd_reduce(DsdArgs a) {
-  const int lane = threadIdx.x % kWave, quad = Tl::kWaves / 4;
-  const int wave = threadIdx.x / kWave + 4 * (blockIdx.y % quad), acc_i = blockIdx.y / quad;
-  const int ni = acc_i / Tl::TI, ti = acc_i % Tl::TI;
+  __shared__ __attribute__((aligned(1024))) uint16_t block[64 * 64];
+  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  const int t = blockIdx.y / Tl::TN, e = blockIdx.y % Tl::TN, nh = w % 2, th = w / 2;
+  const int tg = 2 * t + th, ng = 2 * e + nh;        // 32-row groups of the tile
+  const int wave = tg / Tl::TI * Tl::WN + ng / Tl::NI, acc_i = ng % Tl::NI * Tl::TI + tg % Tl::TI;
   const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (a.ncols + 64 * Tl::TN - 1) / (64 * Tl::TN);
   const GridItem it = grid_item(a.full + blockIdx.x, GM, GN, a.band);
-  const int wm = wave / Tl::WN, wn = wave % Tl::WN;
-  const int n = it.n * (64 * Tl::TN) + 32 * (wn * Tl::NI + ni);
-  const int t = it.m * Tl::TM * 64 + 32 * (wm * Tl::TI + ti);
-  if (n >= a.ncols || t >= a.Tt * 64) return;
+  const int i = it.m * Tl::TM + t, n = (it.n * Tl::TN + e) * 64;
+  if (i >= a.Tt || n >= a.ncols) return;
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
   for (int p = 0; p < a.pieces; ++p) {
     const f32x4* src = reinterpret_cast<const f32x4*>(
                            a.part + (((size_t)blockIdx.x * a.pieces + p) * Tl::kWaves + wave) * (Tl::NI * Tl::TI * 16) * kWave) +
-                       lane * 4 + acc_i * (kWave * 4);
+                       acc_i * (kWave * 4) + lane;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const f32x4 v4 = src[q];
+      const f32x4 v4 = src[q * kWave];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[4 * q + e] += v4[e];
+      for (int r = 0; r < 4; ++r) acc[4 * q + r] += v4[r];
     }
   }
-  store_acc<DT>(acc, a.out + (long long)t * a.ncols + n, a.ncols, a.bias ? a.bias + n : nullptr, nullptr, false);
+  acc_to_lds<DT>(acc, lds_addr(block), 0, 32 * th, 32 * nh, a.bias ? a.bias + n + 32 * nh : nullptr, false);
+  lds_barrier();
+  lds_to_out<Tile<1, 1, 2, 2, 2, 2>, DT, true>(lds_addr(block), a.out, a.ncols, nullptr,
+                                         [&](int, int) { return (long long)i * 64 * a.ncols + n; });
 }
 
 // pass 0 (forward):  A = X,  W1 = W_up [F,d],     W2 = W_down [d,F], act_out = H_act, out = Y
@@ -659,7 +700,7 @@ static void launch_dsd(DsdArgs a, size_t part_bytes, hipStream_t st) {
   LX_TILES(p.id, LX_CALL)
 #undef LX_CALL
 #define LX_CALL(TL) \
-  hipLaunchKernelGGL((ffn_dsd_reduce<TL, DT>), dim3(p.rest, TL::kWaves / 4 * TL::NI * TL::TI), dim3(256), 0, st, a)
+  hipLaunchKernelGGL((ffn_dsd_reduce<TL, DT>), dim3(p.rest, TL::TM * TL::TN), dim3(256), 0, st, a)
   if (p.rest > 0) {
     if (p.id == kT44)
       LX_CALL(Tile44);

@@ -100,6 +100,9 @@ typedef short short4v __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 lds_read16(uint32_t addr) {
   return __builtin_bit_cast(uint4, *reinterpret_cast<const LX_AS3 u32x4*>((uintptr_t)addr));
 }
+__device__ __forceinline__ void lds_write8(uint32_t addr, uint2 v) {
+  *reinterpret_cast<LX_AS3 short4v*>((uintptr_t)addr) = __builtin_bit_cast(short4v, v);
+}
 __device__ __forceinline__ uint2 lds_read8(uint32_t addr) {
   return __builtin_bit_cast(uint2, *reinterpret_cast<const LX_AS3 short4v*>((uintptr_t)addr));
 }
