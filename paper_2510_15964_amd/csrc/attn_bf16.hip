@@ -353,7 +353,8 @@ __device__ __forceinline__ void zero4(f32x4 (&a)[N]) {
 // unit: a swap of two copies of x leaves x of the even row (lower half) in both rows (halves) of one and
 // x of the odd row (upper half) in the other.  In assembly: clang's builtin returns the first result
 // twice; the s_nop is the distance a swap needs from the instruction that wrote its operands.
-__device__ __forceinline__ void swap16(float& a, float& b) {
+template <class T>
+__device__ __forceinline__ void swap16(T& a, T& b) {
   asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
 __device__ __forceinline__ void swap32(float& a, float& b) {
@@ -433,24 +434,34 @@ __device__ __forceinline__ void wait_vmcnt_dyn(int n) {
 
 // Stores issued as assembly: the walk below counts every vector-memory instruction a wavefront
 // issues (vmcnt retires loads and stores in order), so their number must not be the compiler's choice.
-__device__ __forceinline__ void store8(uint16_t* p, uint2 v) {
-  const unsigned long long d = (unsigned long long)v.x | ((unsigned long long)v.y << 32);
-  asm volatile("global_store_dwordx2 %0, %1, off" ::"v"(p), "v"(d) : "memory");
+// (a store of more than 8 bytes still reads its registers for two wait states, which the compiler keeps for
+// its own stores only)
+__device__ __forceinline__ void store16(uint16_t* p, uint4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" ::"v"(p), "v"(__builtin_bit_cast(u32x4, v)) : "memory");
 }
 __device__ __forceinline__ void store4(float* p, float v) {
   asm volatile("global_store_dword %0, %1, off" ::"v"(p), "v"(v) : "memory");
 }
-// accumulator layout -> global, D/16 store instructions
+// accumulator layout -> global, D/32 store instructions: the lanes of a row hold four consecutive columns
+// each; a swap of the odd rows of 16 lanes between two column tiles leaves eight in a lane, so an
+// instruction writes 64 bytes of each of its 16 rows.  With 32-byte pieces (8 bytes per lane) the stores
+// held up the walk's next transfers: forward / dQ / dK and dV over 48 sizes took 4.5 / 3.6 / 7.5 % longer.
 template <int D, int DT>
 __device__ __forceinline__ void store_acc16_asm(const f32x4 (&acc)[D / 16], float mul,
                                                 uint16_t* __restrict__ dst_row) {
   const int g = (threadIdx.x % kWave) / 16;
+  uint16_t* dst = dst_row + 16 * (g % 2) + 8 * (g / 2);
 #pragma unroll
-  for (int ct = 0; ct < D / 16; ++ct) {
-    uint2 o;
-    o.x = pack2<DT>(acc[ct][0] * mul, acc[ct][1] * mul);
-    o.y = pack2<DT>(acc[ct][2] * mul, acc[ct][3] * mul);
-    store8(dst_row + 16 * ct + 4 * g, o);
+  for (int ct = 0; ct < D / 16; ct += 2) {
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      w[2 * e] = pack2<DT>(acc[ct + e][0] * mul, acc[ct + e][1] * mul);
+      w[2 * e + 1] = pack2<DT>(acc[ct + e][2] * mul, acc[ct + e][3] * mul);
+    }
+    swap16(w[0], w[2]);
+    swap16(w[1], w[3]);
+    store16(dst + 16 * ct, make_uint4(w[0], w[1], w[2], w[3]));
   }
 }
 
@@ -698,7 +709,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
     // (the four lanes of a query store the same value)
     store4(a.LSE + soff, any ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY);
   };
-  walk_table<NS, TileDma<D>::kPerWave, -1, 2 * TileDma<D>::kPerWave, 0, D / 16 + 1>(
+  walk_table<NS, TileDma<D>::kPerWave, -1, 2 * TileDma<D>::kPerWave, 0, D / 32 + 1>(
       btab, rows, a.col_idx, issue_own, NoAux(), issue_blk, row_begin, NoAux(), comp, row_end);
 }
 
@@ -825,7 +836,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
     mma_tr16<D, DT>(kt, s, dq_acc);             // dQ^T += K^T dS^T
   };
   auto row_end = [&](int) { store_acc16_asm<D, DT>(dq_acc, a.scale, a.dQ + qoff); };
-  walk_table<NS, 2 * TileDma<D>::kPerWave, TileDma<D>::kPerWave + 1, 2 * TileDma<D>::kPerWave, 2, D / 16>(
+  walk_table<NS, 2 * TileDma<D>::kPerWave, TileDma<D>::kPerWave + 1, 2 * TileDma<D>::kPerWave, 2, D / 32>(
       btab, rows, a.col_idx, issue_own, issue_aux, issue_blk, row_begin, aux, comp, row_end);
 }
 
@@ -938,7 +949,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
     store_acc16_asm<D, DT>(dv_acc, 1.f, a.dV + koff);
     store_acc16_asm<D, DT>(dk_acc, a.scale, a.dK + koff);
   };
-  walk_table<NS, 2 * TileDma<D>::kPerWave, -1, 2 * TileDma<D>::kPerWave + 1, 0, 2 * (D / 16)>(
+  walk_table<NS, 2 * TileDma<D>::kPerWave, -1, 2 * TileDma<D>::kPerWave + 1, 0, 2 * (D / 32)>(
       btab, rows, a.ccol_idx, issue_own, NoAux(), issue_blk, row_begin, NoAux(), comp, row_end);
 }
 

@@ -167,8 +167,8 @@ __device__ __forceinline__ void lds_to_out(uint32_t lds, uint16_t* __restrict__ 
       uint4 v = lds_read16(lds + out_slot(x / 512, x % 512 / 8, x % 8));
       if (o[u] < 0) continue;
       if (gate) v = make_uint4(gate2<DT>(v.x, g[u].x), gate2<DT>(v.y, g[u].y), gate2<DT>(v.z, g[u].z), gate2<DT>(v.w, g[u].w));
-      if (THROUGH)
-        asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(out + o[u]), "v"(__builtin_bit_cast(u32x4, v)) : "memory");
+      if (THROUGH)  // (s_nop: the store still reads its registers for two wait states, unknown to the compiler)
+        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(out + o[u]), "v"(__builtin_bit_cast(u32x4, v)) : "memory");
       else
         *reinterpret_cast<uint4*>(out + o[u]) = v;
     }
