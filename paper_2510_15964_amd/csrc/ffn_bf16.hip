@@ -194,7 +194,9 @@ struct SddArgs {
   const uint16_t *A2, *W2;     // LORA
 };
 
-// Sources of the sdd kernel's transfers; step K/64, if there is one, is the low-rank step.
+// Sources of the sdd kernel's transfers; step K/64, if there is one, is the low-rank step.  It is the last
+// one, so its sources replace the others; a choice at each transfer instruction instead was a branch between
+// the matrix instructions and cost a 64 x 64 tile 90 ns per step (704 tokens, 4928 -> 19712: 26.6 -> 19.9 us).
 template <class Tl, bool LORA>
 struct SddSrc {
   const uint16_t* base[Tl::kIss];
@@ -202,17 +204,18 @@ struct SddSrc {
   uint32_t voff[2], voff2[2];
   long long off;
   int ksteps;
-  bool alt;
   __device__ __forceinline__ void begin(int s) {
-    alt = LORA && s == ksteps;
     off = (long long)s * kBK;
+    if (LORA && s == ksteps) {
+      off = 0;
+      voff[0] = voff2[0];
+      voff[1] = voff2[1];
+#pragma unroll
+      for (int u = 0; u < Tl::kIss; ++u) base[u] = base2[LORA ? u : 0];
+    }
   }
   __device__ __forceinline__ void dma(int u, uint32_t lds) const {
-    const uint32_t to = lds + u * (Tl::kWaves * 1024);
-    if (LORA && alt)
-      dma16_s(base2[LORA ? u : 0], voff2[Tl::kWaves == 4 ? u & 1 : 0], to);
-    else
-      dma16_s(base[u] + off, voff[Tl::kWaves == 4 ? u & 1 : 0], to);
+    dma16_s(base[u] + off, voff[Tl::kWaves == 4 ? u & 1 : 0], lds + u * (Tl::kWaves * 1024));
   }
 };
 
@@ -347,7 +350,6 @@ struct DsdSrc {
   long long off_a, off_w, step_a;
   const int* list;             // col_idx of the range
   int lsteps, next;            // list entries of 64 steps, one per lane
-  bool alt;
   // Loads the entries of steps s .. s + 63.  In assembly, with its own wait: a load that the compiler
   // tracks would make it wait for vmcnt(0), and so for the whole ring, at every step's use of `next`
   // (twice the time with three stages).  The drain that is left costs about 1 us per 64 steps.
@@ -357,8 +359,14 @@ struct DsdSrc {
     asm volatile("global_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)" : "=v"(next) : "v"(off), "s"(list) : "memory");
   }
   __device__ __forceinline__ void begin(int s) {
-    alt = LORA && s == lsteps;
-    if (alt) return;
+    if (LORA && s == lsteps) {  // (the last step, as in SddSrc)
+      off_a = off_w = 0;
+      voffW[0] = voff2[0];
+      voffW[1] = voff2[1];
+#pragma unroll
+      for (int u = 0; u < Tl::kIss; ++u) base[u] = base2[LORA ? u : 0];
+      return;
+    }
     if (s > 0 && s % kWave == 0) fetch(s);
     off_a = s * step_a;
     off_w = (long long)__builtin_amdgcn_readlane(next, s % kWave) * 64;
@@ -366,9 +374,7 @@ struct DsdSrc {
   __device__ __forceinline__ void dma(int u, uint32_t lds) const {
     const uint32_t to = lds + u * (Tl::kWaves * 1024);
     const int q = Tl::kWaves == 4 ? u & 1 : 0;
-    if (LORA && alt)
-      dma16_s(base2[LORA ? u : 0], u < Tl::kIssA ? voffA[q] : voff2[q], to);
-    else if (u < Tl::kIssA)
+    if (u < Tl::kIssA)
       dma16_s(base[u] + off_a, voffA[q], to);
     else
       dma16_s(base[u] + off_w, voffW[q], to);
