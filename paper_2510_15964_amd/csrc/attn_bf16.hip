@@ -25,9 +25,9 @@
 // global memory directly.  The rows of a group of up to four consecutive heads
 // are ranked by the length of their lists and dealt to the group's workgroups
 // in a snake over the ranks, which evens out the number of blocks per
-// workgroup for any mask and between heads with long and short lists (all
-// workgroups of a launch are resident at once, so the launch lasts as long as
-// its longest workgroup).
+// workgroup for any mask and between heads with long and short lists (where all
+// workgroups of a launch are resident at once, it lasts as long as its longest
+// workgroup).
 //
 // Data movement: tiles go from global memory straight into LDS
 // (global_load_lds, 16 bytes per lane) through a ring of two or three stages.
@@ -953,9 +953,18 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
       btab, rows, a.ccol_idx, issue_own, NoAux(), issue_blk, row_begin, NoAux(), comp, row_end);
 }
 
-// Rows per workgroup: the smallest count with which all workgroups of the launch are resident at
-// once on the chip's `slots` workgroup slots (a causal mask keeps the groups balanced for every
-// count, because slots are filled in pairs k, 2G-1-k), unless the caller fixed the number.
+// Rows per workgroup, unless the caller fixed the number: the smallest count with which all workgroups of the
+// launch are resident at once on the chip's `slots` workgroup slots (a causal mask keeps the groups balanced for
+// every count, because slots are filled in pairs k, 2G-1-k), or a smaller one with more workgroups than slots.
+// Those pay a start per round, but the dispatcher hands them out as slots become free, which evens out pairs with
+// long and short lists, and fewer pairs share an L2 at a time.  The estimate, in units of one row: a round costs
+// r rows plus its start, which weighs more where lists are short; a last round that is not full is faster,
+// workgroups being alone on their CUs, and the more so when earlier rounds have spread the starts; a single round
+// lasts 1.5 % longer per row, having nothing to even it out.  Fitted to 74 launches of both head sizes, byte
+// masks and patterns; against one round always, forward / dQ / dK and dV take 0.907 / 0.912 / 0.932 of the time
+// with head size 128 and 0.964 / 0.966 / 0.962 with 64, at worst 1.07 (4 x 32 heads of 2048 tokens, 25 % of the
+// blocks, D = 128, 8 rows -> 4: 85 -> 72 us, 107 -> 95, 114 -> 113; 2 x 40 heads of 4096, patterns, D = 64,
+// 6 -> 2: 147 -> 62, 183 -> 81, 8 -> 2: 311 -> 160).
 static thread_local int g_rows_per_wg = 0;   // one value per host thread
 hipError_t set_attn_rows_per_wg(int r) {
   if (r < 0 || r > kRMax) return hipErrorInvalidValue;
@@ -971,8 +980,19 @@ static int heads_per_group(int nblk, int heads) {
   return 1;
 }
 static int rows_per_wg(int nblk, int heads, int B, int slots) {
+  auto groups = [&](int r) { return (long long)((nblk + r - 1) / r) * heads * B; };
   int r = 1;
-  while (r < kRMax && (long long)((nblk + r - 1) / r) * heads * B > slots) ++r;
+  while (r < kRMax && groups(r) > slots) ++r;
+  const double start = 0.38 * (1 + 16.0 / nblk);
+  auto cost = [&](int q) {
+    const long long n = groups(q), full = n / slots, left = n % slots;
+    if (n <= slots) return (q + start) * (1 + 0.015 * q);
+    const double f = (double)left / slots;
+    const double last = left == 0 ? 0.0 : full > 1 && f <= 0.5 ? 0.5 + 0.35 * f : fmin(1.0, 0.5 + 1.1 * f);
+    return q * (full + last) + start * (full + (left > 0));
+  };
+  for (int q = r - 1; q >= 1; --q)
+    if (cost(q) < cost(r)) r = q;
   if (g_rows_per_wg > 0) r = g_rows_per_wg;
   return r > nblk ? nblk : r;
 }
