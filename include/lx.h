@@ -356,7 +356,8 @@ size_t lx_sparse_attn_bwd_workspace_bytes(lx_dtype dt, int32_t B, int32_t Hh, in
  * Rows with no allowed key and inactive heads give O = 0, LSE = -inf.
  *   Q,K,V,O  [B,Hh,S,D], element (b,h,s,c) at b*strides_bhs[0] + h*strides_bhs[1]
  *            + s*strides_bhs[2] + c (HOST array of 3 element strides, each a
- *            multiple of 8), all four tensors share the strides.
+ *            multiple of 8, the last one at least D and of any length beyond
+ *            that), all four tensors share the strides.
  *   bl       rows = mask_batch*Hh*(S/64) ordered (batch, head, query block);
  *            mask_batch is 1 (mask shared over the batch, Sec. V-A) or B.
  *   head_active  uint8[Hh] or NULL (all heads active)

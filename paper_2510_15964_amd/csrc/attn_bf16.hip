@@ -46,6 +46,8 @@
 //    the same row-major tile with the transposing LDS read (ds_read_b64_tr_b16:
 //    within 16 lanes, lane j receives column c0+j of the four rows addressed by
 //    lanes 0-3, 4-7, 8-11, 12-15).
+#include <type_traits>
+
 #include "lx_dev.h"
 #include "lx_launch.h"
 
@@ -54,7 +56,7 @@ namespace lx {
 constexpr int kAT = 256;                 // threads per workgroup
 constexpr int kAW = kAT / kWave;         // wavefronts per workgroup
 // ring stages / resident workgroups per CU (= wavefronts per SIMD) the kernels are compiled
-// for, head size 64: forward 2 / 4, dQ 2 / 4 (128 registers, four of them spilled), dK/dV 3 / 3
+// for, head size 64: forward 2 / 4, dQ 2 / 4, dK/dV 3 / 3
 // (measured against 3 / 3, 3 / 3 and 2 / 3, and 2 / 2 or 4 / 2); head size 128: 2 / 2
 // everywhere (a stage is 32 KiB)
 constexpr int kFwdNs64 = 2, kFwdOcc64 = 4, kDqNs64 = 2, kDqOcc64 = 4, kDkvNs64 = 3, kDkvOcc64 = 3;
@@ -68,14 +70,17 @@ __device__ __forceinline__ int tswz(int row) {
 }
 
 // The DMA instructions this wave issues for one [64 x D] tile: a wave-uniform base per instruction and
-// one 32-bit offset per lane.  One instruction moves 1 KiB = 64*16/(2D) rows.
-template <int D>
+// one 32-bit offset per lane.  One instruction moves 1 KiB = 64*16/(2D) rows, up to eight, so the offsets
+// reach over token strides below kWideStride.  WIDE, for longer ones: a 64-bit address per lane.
+constexpr long long kWideStride = 1ll << 28;      // elements; 7 rows of 2 * 2^28 bytes and a row's 112 fit 32 bits
+template <int D, bool WIDE>
 struct TileDma {
   static constexpr int kSlots = D / 8;            // 16-byte slots per row
   static constexpr int kRowsPer = 64 / kSlots;    // rows per DMA instruction
   static constexpr int kPerWave = 64 / kRowsPer / kAW;
+  using Off = std::conditional_t<WIDE, long long, uint32_t>;
   long long row0[kPerWave];                       // element offset of the instruction's first row
-  uint32_t off[kPerWave];                         // bytes from there: row lane / kSlots, swizzled slot
+  Off off[kPerWave];                              // bytes from there: row lane / kSlots, swizzled slot
   uint32_t wave_lds;
   __device__ __forceinline__ void init(long long ld) {
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -85,14 +90,19 @@ struct TileDma {
       const int first = kRowsPer * (wave + kAW * u), row = first + lane / kSlots;
       const int slot = (lane % kSlots) ^ tswz<D>(row);
       row0[u] = first * ld;
-      off[u] = (uint32_t)((lane / kSlots) * ld * 2) + slot * 16;
+      off[u] = (Off)((lane / kSlots) * ld * 2) + slot * 16;
     }
   }
   // tile_addr: LDS byte address of the destination tile; g0: wave-uniform
   __device__ __forceinline__ void issue(uint32_t tile_addr, const uint16_t* g0) const {
 #pragma unroll
-    for (int u = 0; u < kPerWave; ++u)
-      dma16_s(g0 + row0[u], off[u], tile_addr + wave_lds + u * (kAW * 1024));
+    for (int u = 0; u < kPerWave; ++u) {
+      const uint32_t to = tile_addr + wave_lds + u * (kAW * 1024);
+      if constexpr (WIDE)
+        dma16(reinterpret_cast<const char*>(g0 + row0[u]) + off[u], to);
+      else
+        dma16_s(g0 + row0[u], off[u], to);
+    }
   }
 };
 
@@ -591,7 +601,7 @@ __device__ __forceinline__ bool pair_work(const AttnArgs& a, PairWork& p) {
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-template <int D, int DT, int NS, int OCC>
+template <int D, int DT, int NS, int OCC, bool WIDE>
 __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   __shared__ __attribute__((aligned(2 * 64 * D))) uint16_t st[NS][2 * 64 * D];   // stage: K tile, V tile
   __shared__ int rowtab[4 * kRMax];
@@ -621,7 +631,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
       if (g == 0) a.LSE[stat_of(hh) + rows.blk(j) * 64 + ql] = -INFINITY;
     }
 
-  TileDma<D> dma;
+  TileDma<D, WIDE> dma;
   dma.init(a.ss);
   LaneOff16<D> lo;
   lo.init();
@@ -709,14 +719,14 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
     // (the four lanes of a query store the same value)
     store4(a.LSE + soff, any ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY);
   };
-  walk_table<NS, TileDma<D>::kPerWave, -1, 2 * TileDma<D>::kPerWave, 0, D / 32 + 1>(
+  walk_table<NS, TileDma<D, WIDE>::kPerWave, -1, 2 * TileDma<D, WIDE>::kPerWave, 0, D / 32 + 1>(
       btab, rows, a.col_idx, issue_own, NoAux(), issue_blk, row_begin, NoAux(), comp, row_end);
 }
 
 // ---------------------------------------------------------------------------
 // backward, query side
 // ---------------------------------------------------------------------------
-template <int D, int DT, int NS, int OCC>
+template <int D, int DT, int NS, int OCC, bool WIDE>
 __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
   __shared__ __attribute__((aligned(2 * 64 * D))) uint16_t st[NS][2 * 64 * D];   // stage: K, V (or Q, dO; or O) tile
   __shared__ __attribute__((aligned(256))) float slse[NS][4][16];   // stage, wavefront: LSE of its 16 own rows
@@ -750,7 +760,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
       }
     }
 
-  TileDma<D> dma;
+  TileDma<D, WIDE> dma;
   dma.init(a.ss);
   LaneOff16<D> lo;
   lo.init();
@@ -836,7 +846,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
     mma_tr16<D, DT>(kt, s, dq_acc);             // dQ^T += K^T dS^T
   };
   auto row_end = [&](int) { store_acc16_asm<D, DT>(dq_acc, a.scale, a.dQ + qoff); };
-  walk_table<NS, 2 * TileDma<D>::kPerWave, TileDma<D>::kPerWave + 1, 2 * TileDma<D>::kPerWave, 2, D / 32>(
+  walk_table<NS, 2 * TileDma<D, WIDE>::kPerWave, TileDma<D, WIDE>::kPerWave + 1, 2 * TileDma<D, WIDE>::kPerWave, 2, D / 32>(
       btab, rows, a.col_idx, issue_own, issue_aux, issue_blk, row_begin, aux, comp, row_end);
 }
 
@@ -844,7 +854,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
 // backward, key side: a wavefront owns 16 keys; the streamed tiles are Q and dO of the listed
 // query blocks, with the queries' -LSE*log2(e) and Delta beside them
 // ---------------------------------------------------------------------------
-template <int D, int DT, int NS, int OCC>
+template <int D, int DT, int NS, int OCC, bool WIDE>
 __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) {
   __shared__ __attribute__((aligned(2 * 64 * D))) uint16_t st[NS][2 * 64 * D];   // stage: Q, dO (or K, V) tile
   __shared__ __attribute__((aligned(512))) float sstat[NS][4][32];   // stage, query tile: -LSE*log2e [16], Delta [16]
@@ -875,7 +885,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
       store_acc16<D, DT>(z, 0.f, a.dK + koff);
     }
 
-  TileDma<D> dma;
+  TileDma<D, WIDE> dma;
   dma.init(a.ss);
   LaneOff16<D> lo;
   lo.init();
@@ -949,7 +959,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
     store_acc16_asm<D, DT>(dv_acc, 1.f, a.dV + koff);
     store_acc16_asm<D, DT>(dk_acc, a.scale, a.dK + koff);
   };
-  walk_table<NS, 2 * TileDma<D>::kPerWave, -1, 2 * TileDma<D>::kPerWave + 1, 0, 2 * (D / 32)>(
+  walk_table<NS, 2 * TileDma<D, WIDE>::kPerWave, -1, 2 * TileDma<D, WIDE>::kPerWave + 1, 0, 2 * (D / 32)>(
       btab, rows, a.ccol_idx, issue_own, NoAux(), issue_blk, row_begin, NoAux(), comp, row_end);
 }
 
@@ -1008,32 +1018,40 @@ static int attn_grid(AttnArgs& a, int B, int slots) {
   return 8 * (P / 8 * a.gz + (P % 8 * a.gz + 7) / 8);
 }
 
-template <int D, int DT>
-static hipError_t launch_fwd(AttnArgs a, int B, hipStream_t st) {
+template <int D, int DT, bool WIDE>
+static hipError_t launch_fwd_t(AttnArgs a, int B, hipStream_t st) {
   ProfScope ps(kKAttnFwd, st);
-  constexpr int kNs = D == 64 ? kFwdNs64 : 2, kOcc = D == 64 ? kFwdOcc64 : 2;
+  constexpr int kNs = D == 64 && !WIDE ? kFwdNs64 : 2, kOcc = D == 64 && !WIDE ? kFwdOcc64 : 2;
   const int grid = attn_grid(a, B, kCUs * kOcc);
-  hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc>), dim3(grid), dim3(kAT), 0, st, a);
+  hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
   return hipGetLastError();
 }
-
 template <int D, int DT>
-static hipError_t launch_bwd(AttnArgs a, int B, hipStream_t st) {
+static hipError_t launch_fwd(const AttnArgs& a, int B, hipStream_t st) {
+  return a.ss < kWideStride ? launch_fwd_t<D, DT, false>(a, B, st) : launch_fwd_t<D, DT, true>(a, B, st);
+}
+
+template <int D, int DT, bool WIDE>
+static hipError_t launch_bwd_t(AttnArgs a, int B, hipStream_t st) {
   {
     ProfScope ps(kKAttnDq, st);
-    constexpr int kNs = D == 64 ? kDqNs64 : 2, kOcc = D == 64 ? kDqOcc64 : 2;
+    constexpr int kNs = D == 64 && !WIDE ? kDqNs64 : 2, kOcc = D == 64 && !WIDE ? kDqOcc64 : 2;
     const int grid = attn_grid(a, B, kCUs * kOcc);
-    hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc>), dim3(grid), dim3(kAT), 0, st, a);
+    hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKAttnDkv, st);
-    constexpr int kNs = D == 64 ? kDkvNs64 : 2, kOcc = D == 64 ? kDkvOcc64 : 2;
+    constexpr int kNs = D == 64 && !WIDE ? kDkvNs64 : 2, kOcc = D == 64 && !WIDE ? kDkvOcc64 : 2;
     const int grid = attn_grid(a, B, kCUs * kOcc);
-    hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc>), dim3(grid), dim3(kAT), 0, st, a);
+    hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
   }
   return hipGetLastError();
+}
+template <int D, int DT>
+static hipError_t launch_bwd(const AttnArgs& a, int B, hipStream_t st) {
+  return a.ss < kWideStride ? launch_bwd_t<D, DT, false>(a, B, st) : launch_bwd_t<D, DT, true>(a, B, st);
 }
 
 // dt: element type (kBf16 or kF16)

@@ -532,8 +532,6 @@ static lx_status check_attn(lx_dtype dt, int32_t B, int32_t Hh, int32_t S, int32
   for (int i = 0; i < 3; ++i)
     if (strides[i] < 0 || strides[i] % 8 != 0) return LX_ERR_INVALID_ARG;
   if (strides[2] < D) return LX_ERR_INVALID_ARG;
-  // eight rows of a tile are addressed with one 32-bit byte offset per lane (64 tokens would span 34 GB)
-  if (is16(dt) && strides[2] >= (int64_t)1 << 28) return LX_ERR_UNSUPPORTED;
   if (mask_batch != 1 && mask_batch != B) return LX_ERR_INVALID_ARG;
   if (!bl || !bl->row_ptr || !bl->col_idx) return LX_ERR_INVALID_ARG;
   if ((int64_t)bl->rows != (int64_t)mask_batch * Hh * (S / 64) || bl->cols != S / 64)

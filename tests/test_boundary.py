@@ -290,3 +290,19 @@ def test_tuning_knobs_reject_values_outside_their_range(lxmod):
         assert L._lib.lx_ffn_set_token_tiles_per_workgroup(v) == L.LX_OK
     assert L._lib.lx_attn_set_rows_per_workgroup(9) == L.LX_ERR_INVALID_ARG
     assert L._lib.lx_attn_set_rows_per_workgroup(0) == L.LX_OK
+
+
+def test_attn_token_stride_of_any_length_is_accepted(lxmod):
+    """No upper bound on the token stride, for any element type: the check that then fails is the
+    one for the deliberately missing Q."""
+    L = lxmod
+    bl = _bl(L, 2, 2)
+    need = L.lx_sparse_attn_bwd_workspace_bytes(L.LX_BF16, 1, 1, 128, 64)
+    for dt in (L.LX_BF16, L.LX_F16, L.LX_F32):
+        for ss in ((1 << 28) - 8, 1 << 28, 1 << 40):
+            st = (C.c_int64 * 3)(64, 64, ss)
+            assert L._lib.lx_sparse_attn_fwd(dt, 1, 1, 128, 64, 0.125, 1, None, FAKE, FAKE, st, C.byref(bl), 1,
+                                             None, FAKE, FAKE, None) == L.LX_ERR_INVALID_ARG
+            assert L._lib.lx_sparse_attn_bwd_dx(dt, 1, 1, 128, 64, 0.125, 1, None, FAKE, FAKE, FAKE, FAKE, FAKE,
+                                                st, C.byref(bl), C.byref(bl), 1, None, FAKE, FAKE, FAKE, FAKE,
+                                                need, None) == L.LX_ERR_INVALID_ARG

@@ -322,3 +322,38 @@ def test_fp32_attention_strided_and_above_diagonal(lx, oracle):
     for k in a:
         assert np.array_equal(a[k], b[k], equal_nan=True), k
     check(a, ref, "f32 bshd, blocks above the diagonal", dtype="f32")
+
+
+@pytest.mark.parametrize("D,dtype", [(64, "bf16"), (128, "f16")])
+def test_token_strides_beyond_32_bit_offsets(lx, D, dtype):
+    """A token stride of 2^28 elements (all tensors interleaved in one buffer of 127 strides, of which only the
+    128 token rows are touched): the bits of the same call on contiguous tensors."""
+    import torch
+    Hh, S, ss = 2, 128, 1 << 28
+    c = inputs.attn_blocks(1, Hh, S, D, 0.7, 77, dtype=dtype, force_diagonal=True)
+    torch.cuda.empty_cache()
+    buf = torch.empty((S - 1) * ss + 8 * Hh * D, dtype=dev(c["Q"], dtype).dtype, device="cuda")
+    at = lambda i: buf.as_strided((1, Hh, S, D), (Hh * D, D, ss, 1), i * Hh * D)
+    mask = torch.from_numpy(c["mask"]).cuda()
+    rows, cols = lx.lx_mask_compact_pair(mask)
+    ws = torch.empty(lx.lx_sparse_attn_bwd_workspace_bytes(lx_dtype(lx, dtype), 1, Hh, S, D), dtype=torch.uint8,
+                     device="cuda")
+
+    def call(new):
+        Q, K, V, dO, O, dQ, dK, dV = (new(i) for i in range(8))
+        for t, k in ((Q, "Q"), (K, "K"), (V, "V"), (dO, "dO")):
+            t.copy_(dev(c[k], dtype))
+        for t in (O, dQ, dK, dV):
+            t.fill_(float("nan"))
+        LSE = torch.full((1, Hh, S), float("nan"), device="cuda")
+        lx.lx_sparse_attn_fwd(Q, K, V, rows, c["scale"], c["causal"], O, LSE)
+        lx.lx_sparse_attn_bwd_dx(Q, K, V, O, LSE, dO, rows, cols, c["scale"], c["causal"], dQ, dK, dV, ws)
+        torch.cuda.synchronize()
+        return [t.contiguous() for t in (O, LSE, dQ, dK, dV)]
+
+    wide = call(at)
+    plain = call(lambda i: torch.empty((1, Hh, S, D), dtype=buf.dtype, device="cuda"))
+    for a, b in zip(wide, plain):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
+    del buf, wide
+    torch.cuda.empty_cache()
