@@ -66,34 +66,44 @@ __device__ __forceinline__ void transpose64(const uint16_t* __restrict__ src, lo
   }
 }
 
-// out[t][q] = sum over steps of sum_k P_s[t][k] Q_s[q][k] for the 32 x 32 quadrant blockIdx.x % 4 of token
-// tile blockIdx.x / 4, the steps cut into ranges (lora_u_split / lora_g_split of them).
+// out[t][q] = sum over steps of sum_k P_s[t][k] Q_s[q][k], a 64 x 64 tile per token tile i.
 // MODE 0, U = X A_pad^T (Sec. II-C: the inner factor A x of the branch): P = X, Q = A_pad, row
 //   stride ld of both; the steps are the ld / 64 chunks of K.
 // MODE 1, G = dZ B_pad (Sec. II-D: the gradient that reaches A x): P = the compact blocks dZ_ij of
 //   the tile's list, Q_s[q][k] = B_pad[64 j_s + k][q]; the steps are the list entries.  The last ld / 64
 //   workgroups of the launch transpose A_pad [64,ld] into A_t [ld,64] meanwhile, which the
 //   input-gradient product reads.
-// What bounds these products is latency: there are few of them.  A quadrant per workgroup gives every CU
-// one at 64 tiles; a wavefront owns one half (32 of the 64 k) of the steps of one range and streams its
-// own operands through its own stages, 4 KB each, without a barrier; halves and ranges are added at the end
-// through LDS, in that order (the same sums as 64 x 64 tiles with partial sums in memory, in one
-// launch instead of two: U at 4096 tokens, d = 2048 6.5 + 4.3 us before).
+// Two kernels: up to kNtQuadTiles token tiles a workgroup per 32 x 32 quadrant with the steps cut into ranges,
+// beyond that a workgroup per tile.  At d = 2048, U (bf16; one range per quadrant from 256 tiles on, two from
+// 128): 64 tiles 10.5 us by quadrants and 13.6 by tiles, 72 tiles 15.4 and 13.7, 128 tiles 14.7 and 14.3, 256
+// tiles 34.7 and 16.3, 512 tiles 64.6 and 33.3 (134 MB of X: 4 TB/s, the copy rate).  Tiles lose where they leave
+// half of the CUs idle over a long K: 128 tiles, d = 5120 35.6 us, 25.1 with K cut in two and a launch that adds.
+constexpr int kNtQuadTiles = 64;
+
+// Few tiles: what bounds the product is latency.  A quadrant per workgroup gives every CU one at 64 tiles; a
+// wavefront owns one half (32 of the 64 k) of the steps of one range (lora_u_split / lora_g_split of them) and
+// streams its own operands through its own stages, 4 KB each, without a barrier; halves and ranges are added at
+// the end through LDS, in that order.  The quadrants of a tile sit eight workgroups apart, on one XCD, so that a
+// tile's rows are fetched into one L2 only (neighbours, on four XCDs: 64 tiles, d = 2048 U 13.7 us, now 10.5).
 constexpr int kNtStage = 4096;                 // bytes: 32 rows of 64 bytes of P, 32 of Q
 constexpr int kNtStages(int waves) { return waves <= 4 ? 8 : 32 / waves; }
-constexpr int kNtLds = 32 * kNtStage;          // stages of all wavefronts
+constexpr int kNtLds = 32 * kNtStage;          // stages of all wavefronts (one workgroup per CU, see above)
+// Workgroups of the quadrants of Tt tiles, in whole groups of eight tiles.
+__host__ __device__ constexpr int nt_quads(int Tt) { return 32 * ((Tt + 7) / 8); }
 template <int DT, int MODE>
 __global__ __launch_bounds__(1024) void lora_nt_kernel(
     const uint16_t* __restrict__ P, const uint16_t* __restrict__ Q, int ld,
     const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int Tt, int gt, int nnz_cap,
     uint16_t* __restrict__ out, const uint16_t* __restrict__ A_pad, uint16_t* __restrict__ A_t) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kNtLds];
-  if (MODE == 1 && (int)blockIdx.x >= 4 * Tt) {
-    transpose64(A_pad + (blockIdx.x - 4 * Tt) * 64ll, ld, A_t + (blockIdx.x - 4 * Tt) * 4096ll, 64,
-                reinterpret_cast<uint16_t*>(lds));
+  const int w = blockIdx.x, quads = nt_quads(Tt);
+  if (MODE == 1 && w >= quads) {
+    transpose64(A_pad + (w - quads) * 64ll, ld, A_t + (w - quads) * 4096ll, 64, reinterpret_cast<uint16_t*>(lds));
     return;
   }
-  const int i = blockIdx.x / 4, th = blockIdx.x % 2, qh = (blockIdx.x / 2) % 2;
+  const int i = w / 32 * 8 + w % 8, quad = w / 8 % 4;
+  if (i >= Tt) return;
+  const int th = quad % 2, qh = quad / 2;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int waves = blockDim.x / kWave, split = waves / 2, range = wave / 2, kh = wave % 2;
   const int nst = kNtStages(waves);
@@ -193,6 +203,91 @@ __global__ __launch_bounds__(1024) void lora_nt_kernel(
     ov.y = pack2<DT>(v[2], v[3]);
     *reinterpret_cast<uint2*>(out + ((long long)i * 64 + 32 * th + l % 32) * 64 + 32 * qh + 8 * g + 4 * (l / 32)) = ov;
   }
+}
+
+// More tiles: a workgroup per tile, which reads the tile's rows once in whole 128-byte lines and shares them between
+// its wavefronts (a quadrant and a half of k each) through the ring; two workgroups per CU.
+template <int DT, int MODE>
+__global__ __launch_bounds__(kThreads) void lora_nt_tile_kernel(
+    const uint16_t* __restrict__ P, const uint16_t* __restrict__ Q, int ld,
+    const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int Tt, int gt, int nnz_cap,
+    uint16_t* __restrict__ out, const uint16_t* __restrict__ A_pad, uint16_t* __restrict__ A_t) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[kPairStages * kPairElems];
+  const int i = blockIdx.x;
+  if (MODE == 1 && i >= Tt) {
+    transpose64(A_pad + (i - Tt) * 64ll, ld, A_t + (i - Tt) * 4096ll, 64, ring);
+    return;
+  }
+  int rs = 0, nsteps = ld / kBK;
+  if (MODE == 1) {
+    rs = row_ptr[i / gt];
+    nsteps = max(min(row_ptr[i / gt + 1], nnz_cap) - rs, 0);   // entries beyond the capacity are ignored
+  }
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int th = wave % 2, qh = (wave / 2) % 2, kh = wave / 4;
+  const int r = lane % 32, h2 = lane / 32;
+  const uint16_t* src[2];
+  if (MODE == 0)
+    pair_src(P + (long long)i * 64 * ld, ld, Q, ld, src);
+  else
+    pair_src(P, 64, Q, 64, src);
+  // byte offsets inside a stage, per 16-deep slice of this wavefront's half of k
+  uint32_t po[2][2], qo[2][2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int k = 32 * kh + 16 * e;
+    if (MODE == 0) {
+      po[e][0] = tile64_off(32 * th + r, k + 8 * h2);
+      qo[e][0] = 64 * 128 + tile64_off(32 * qh + r, k + 8 * h2);
+    } else {
+      const int j = lane % 16, col = 32 * qh + 16 * ((lane / 16) % 2) + 4 * (j % 4);
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        po[e][x] = tile64_off(32 * th + r, k + 8 * x + 4 * h2);
+        qo[e][x] = 64 * 128 + tile64_off(k + 8 * x + 4 * h2 + j / 4, col);
+      }
+    }
+  }
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  run_ring_of<kPairStages, 2, kPairElems>(
+      nsteps, src, NoAlt(),
+      [=](int s, long long& ob, long long& oa) {
+        if (MODE == 0) {
+          ob = oa = (long long)s * kBK;
+        } else {
+          ob = ((long long)(rs + s) * gt + i % gt) * 4096;
+          oa = (long long)col_idx[rs + s] * 4096;
+        }
+        return false;
+      },
+      ring,
+      [&](const uint16_t* stage) {
+        const uint32_t st = lds_addr(stage);
+        uint4 a[2], b[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          if (MODE == 0) {
+            a[e] = lds_read16(st + qo[e][0]);
+            b[e] = lds_read16(st + po[e][0]);
+          } else {
+            const uint2 pl = lds_read8(st + po[e][0]), ph = lds_read8(st + po[e][1]);
+            const uint2 ql = lds_read8_tr(st + qo[e][0]), qu = lds_read8_tr(st + qo[e][1]);
+            b[e] = make_uint4(pl.x, pl.y, ph.x, ph.y);
+            a[e] = make_uint4(ql.x, ql.y, qu.x, qu.y);
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) acc = mfma32<DT>(a[e], b[e], acc);
+      });
+  if (!fold_khalves(reinterpret_cast<float*>(ring), acc)) return;
+  // register v: rank index 32*qh + 8*(v/4) + 4*h2 + v%4, token 32*th + lane%32
+  uint16_t* o = out + ((long long)i * 64 + 32 * th + r) * 64 + 32 * qh + 4 * h2;
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    *reinterpret_cast<uint2*>(o + 8 * g) =
+        make_uint2(pack2<DT>(acc[4 * g], acc[4 * g + 1]), pack2<DT>(acc[4 * g + 2], acc[4 * g + 3]));
 }
 
 // Per-lane LDS offsets of the operands of a product out[a][b] = sum_t P[t][a] Q[t][b] whose
@@ -370,8 +465,13 @@ template <int DT>
 static hipError_t launch_lora_u_t(int Tt, int d, const uint16_t* X, const uint16_t* A_pad, uint16_t* U,
                                   hipStream_t st) {
   const int* none = nullptr;
-  hipLaunchKernelGGL((lora_nt_kernel<DT, 0>), dim3(4 * Tt), dim3(2 * kWave * lora_u_split(Tt, d)), 0, st, X, A_pad, d,
-                     none, none, Tt, 1, 0, U, (const uint16_t*)nullptr, (uint16_t*)nullptr);
+  const uint16_t* none16 = nullptr;
+  if (Tt <= kNtQuadTiles)
+    hipLaunchKernelGGL((lora_nt_kernel<DT, 0>), dim3(nt_quads(Tt)), dim3(2 * kWave * lora_u_split(Tt, d)), 0, st, X, A_pad,
+                       d, none, none, Tt, 1, 0, U, none16, (uint16_t*)nullptr);
+  else
+    hipLaunchKernelGGL((lora_nt_tile_kernel<DT, 0>), dim3(Tt), dim3(kThreads), 0, st, X, A_pad, d, none, none, Tt, 1, 0, U,
+                       none16, (uint16_t*)nullptr);
   return hipGetLastError();
 }
 hipError_t launch_lora_u(int dt, int Tt, int d, const uint16_t* X, const uint16_t* A_pad, uint16_t* U,
@@ -384,8 +484,12 @@ template <int DT>
 static hipError_t launch_lora_g_t(int Tt, int gt, int d, const uint16_t* dZ, const uint16_t* B_pad,
                                   const int* row_ptr, const int* col_idx, int nnz_cap, uint16_t* G,
                                   const uint16_t* A_pad, uint16_t* A_t, hipStream_t st) {
-  hipLaunchKernelGGL((lora_nt_kernel<DT, 1>), dim3(4 * Tt + d / 64), dim3(2 * kWave * lora_g_split(Tt)), 0, st, dZ, B_pad,
-                     d, row_ptr, col_idx, Tt, gt, nnz_cap, G, A_pad, A_t);
+  if (Tt <= kNtQuadTiles)
+    hipLaunchKernelGGL((lora_nt_kernel<DT, 1>), dim3(nt_quads(Tt) + d / 64), dim3(2 * kWave * lora_g_split(Tt)), 0, st, dZ,
+                       B_pad, d, row_ptr, col_idx, Tt, gt, nnz_cap, G, A_pad, A_t);
+  else
+    hipLaunchKernelGGL((lora_nt_tile_kernel<DT, 1>), dim3(Tt + d / 64), dim3(kThreads), 0, st, dZ, B_pad, d, row_ptr,
+                       col_idx, Tt, gt, nnz_cap, G, A_pad, A_t);
   return hipGetLastError();
 }
 hipError_t launch_lora_g(int dt, int Tt, int gt, int d, const uint16_t* dZ, const uint16_t* B_pad,

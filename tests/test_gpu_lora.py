@@ -263,3 +263,17 @@ def test_lora_bench_shape_full_size_sampled(lx, oracle):
     assert not dX2.reshape(T // 64, 64, d)[untouched].any()
     listed = mask[list(tiles)].any(0)
     assert not dB2.reshape(F // 64, 64, 64)[~listed].any()
+
+
+@pytest.mark.parametrize("Tt,d,F,rows,dtype", [
+    (9, 128, 192, 9, "bf16"),       # one tile into the second group of eight
+    (64, 64, 192, 64, "f16"),       # the last count that runs by quadrants; one K step
+    (65, 192, 128, 65, "bf16"),     # the first that runs by tiles
+    (66, 128, 192, 2, "f16"),       # list rows shared by 33 tiles
+    (130, 64, 128, 1, "bf16"),
+])
+def test_lora_token_tile_counts(lx, oracle, Tt, d, F, rows, dtype):
+    """U and G on both sides of the count from which a workgroup takes a whole token tile."""
+    c = make_case(64 * Tt, d, F, 16, 0.5, 40 + Tt, rows=None if rows == Tt else rows, dtype=dtype)
+    got, ref = run_both(lx, oracle, c)
+    check(got, ref, f"{Tt} tiles d={d} F={F} rows={rows} {dtype}", dtype=dtype)
