@@ -17,11 +17,23 @@
 //
 // The LoRA branch on the up-projection (Sec. II-C / II-D) is one more step of either product; the
 // calls that add it are at the end of this file, its small products in lora_bf16.hip.
-#include <algorithm>
-
+#include "ffn_plan.h"
 #include "ffn_tile.h"
 
 namespace lx {
+
+// The tiles of ffn_plan.h.  TM TN WM WN NST KS
+using Tile44 = Tile<4, 4, 2, 4, 2, 2>;
+using Tile24 = Tile<2, 4, 2, 4, 3, 2>;
+using Tile22 = Tile<2, 2, 2, 2, 2, 2>;
+using Tile22Deep = Tile<2, 2, 2, 4, 4, 4>;
+using Tile14 = Tile<1, 4, 1, 4, 2, 2>;
+using Tile14Deep = Tile<1, 4, 2, 4, 4, 2>;
+using Tile12 = Tile<1, 2, 1, 4, 3, 2>;
+using Tile11 = Tile<1, 1, 2, 2, 4, 4>;
+using Tile11Many = Tile<1, 1, 2, 2, 3, 4, 3>;
+template <class Tl>
+constexpr int kRingElems = Tl::NST * Tl::kElems;
 
 // Work items of the sdd kernel are (token tile, group of `per` consecutive list entries),
 // numbered in list order; `rows` counts token tiles, and gt consecutive tiles share one row of
@@ -188,7 +200,9 @@ struct SddArgs {
   const uint16_t *A, *W, *bias;
   const int *row_ptr, *col_idx;
   int Tt, gt, K, nnz_cap;      // gt token tiles share a list row
-  int band;                    // h of grid_item (one list row)
+  int rows, blocks;            // list rows, and blocks that the list could hold
+  int own, grid;               // of SddPlan
+  unsigned allowed;
   uint16_t* out;
   const uint16_t* gate;        // null: ReLU
   const uint16_t *A2, *W2;     // LORA
@@ -226,9 +240,9 @@ struct SddSrc {
 // z = W x + B (A x) of Sec. II-C with A2 = X A^T computed beforehand and W2 = B, both padded to
 // rank 64.
 template <class Tl, int DT, bool LORA>
-__global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_sdd(SddArgs a) {
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[Tl::NST * Tl::kElems];
+__device__ __forceinline__ void sdd_tile(const SddArgs& a, uint16_t* ring) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (wave >= Tl::kWaves) return;      // (barriers wait for the wavefronts that are left)
   int m, chunk, n_i, rs;
   if (a.gt == a.Tt) {
     rs = min(a.row_ptr[0], a.nnz_cap);
@@ -236,7 +250,7 @@ __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_sdd(SddAr
     const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (n_i + Tl::TN - 1) / Tl::TN;
     const int total = GM * GN, L = (total + 7) / 8, slot = blockIdx.x / 8, idx = (blockIdx.x % 8) * L + slot;
     if (slot >= L || idx >= total) return;
-    const GridItem it = grid_item(idx, GM, GN, a.band);
+    const GridItem it = grid_item(idx, GM, GN, Tl::TM == 4 ? 4 : 8);
     m = it.m;
     chunk = it.n;
   } else {
@@ -292,6 +306,45 @@ __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_sdd(SddAr
     const int i = i0 + t;
     return i < a.Tt && e < nb ? (((long long)rs + first + e) * a.gt + i % a.gt) * 4096 : -1ll;
   });
+}
+
+template <class Tl, int DT, bool LORA>
+__global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_sdd(SddArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[kRingElems<Tl>];
+  sdd_tile<Tl, DT, LORA>(a, ring);
+}
+// The tile that suits the list as it is, of the set with RESIDENT workgroups per CU: see SddSet.  First product with
+// the list's length / four times that / every block as capacity: 4096 tokens, d = 2048, 14 blocks 24.2 / 24.1 / 24.2 us
+// (by the capacity's tile 23.3 / 46.3 / 45.9), 2048 tokens, d = 2560, 20 blocks 25.8 / 25.4 / 25.4 (25.7 / 54.8 /
+// 35.6), 1024 tokens, d = 4096, 26 blocks 26.6 / 28.2 / 28.0 (26.3 / 46.3 / 76.8); four token tiles per list row, 1024
+// tokens, d = 4096, every block as capacity 31 us (79).
+template <int DT, int RESIDENT>
+__global__ __launch_bounds__(RESIDENT == 1 ? 512 : 256, 2) void ffn_sdd_any(SddArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[RESIDENT == 1 ? kRingElems<Tile14Deep> : kRingElems<Tile14>];
+  const int n = min(a.row_ptr[a.rows], a.nnz_cap) - min(a.row_ptr[0], a.nnz_cap);
+  int id = a.own;
+  if (!sdd_keeps_own(a.nnz_cap, n)) {
+    const int limit = sdd_limit<RESIDENT>(a.own, a.grid, a.Tt, a.gt, n);
+    if ((int)blockIdx.x >= limit) return;
+    id = sdd_pick<RESIDENT>(a.own, a.allowed, limit, a.Tt, a.gt, a.K, n);
+  }
+  if constexpr (RESIDENT == 1) {
+    switch (id) {
+      case kT44: sdd_tile<Tile44, DT, false>(a, ring); break;
+      case kT24: sdd_tile<Tile24, DT, false>(a, ring); break;
+      case kT22Deep: sdd_tile<Tile22Deep, DT, false>(a, ring); break;
+      case kT14Deep: sdd_tile<Tile14Deep, DT, false>(a, ring); break;
+      case kT12: sdd_tile<Tile12, DT, false>(a, ring); break;
+      case kT11: sdd_tile<Tile11, DT, false>(a, ring); break;
+    }
+  } else {
+    switch (id) {
+      case kT22: sdd_tile<Tile22, DT, false>(a, ring); break;
+      case kT14: sdd_tile<Tile14, DT, false>(a, ring); break;
+      case kT12: sdd_tile<Tile12, DT, false>(a, ring); break;
+      case kT11: sdd_tile<Tile11, DT, false>(a, ring); break;
+    }
+  }
 }
 
 // Which token tile the workgroups of grid row `slot` work on.  A workgroup of the dsd kernel
@@ -530,134 +583,14 @@ hipError_t set_ffn_tiles_per_wg(int n) {
   return hipSuccess;
 }
 
-// The tiles, widest first.  A wide tile moves fewer bytes and LDS reads per product (a workgroup step
-// transfers TM + TN times 8 KiB for TM * TN products of 64 x 64 x 64), a narrow one gives the chip more
-// workgroups and has the shorter step.  `resident` workgroups fit a CU; one workgroup per CU leaves room
-// for a deeper ring, and eight wavefronts with a whole step of operands on the way hide its latency
-// (2 x 2 tiles, 4096 tokens, 14 blocks, K = 2048, 224 workgroups: 25 -> 21 us).
-//                          TM TN WM WN NST KS
-using Tile44 = Tile<4, 4, 2, 4, 2, 2>;
-using Tile24 = Tile<2, 4, 2, 4, 3, 2>;
-using Tile22 = Tile<2, 2, 2, 2, 2, 2>;
-using Tile22Deep = Tile<2, 2, 2, 4, 4, 4>;
-using Tile14 = Tile<1, 4, 1, 4, 2, 2>;
-using Tile14Deep = Tile<1, 4, 2, 4, 4, 2>;
-using Tile12 = Tile<1, 2, 1, 4, 3, 2>;
-using Tile11 = Tile<1, 1, 2, 2, 4, 4>;
-using Tile11Many = Tile<1, 1, 2, 2, 3, 4, 3>;
-enum TileId { kT44, kT24, kT22, kT22Deep, kT14, kT14Deep, kT12, kT11, kT11Many, kTiles };
-// What a launch of a tile costs, in us: `round` per round of workgroups (finding the item, filling the
-// ring, epilogue) and step[q - 1] per step with q workgroups on a CU.  Fitted to measured launches of
-// every tile at 22 shapes (64 - 8192 tokens, d 576 - 5120, 6 - 320 listed blocks, lists shared and per
-// tile; rms of the fit 6 - 18 %); at those shapes the tile that the model picks is within 1.5 % of the
-// fastest one on average, 7 % at worst.
-struct TileInfo {
-  int tm, tn, resident;
-  float round, step[3];
-};
-static const TileInfo kTileInfo[kTiles] = {
-    {4, 4, 1, 8.6f, {1.25f}},      {2, 4, 1, 7.4f, {0.69f}}, {2, 2, 2, 4.2f, {0.61f, 1.11f}},
-    {2, 2, 1, 5.1f, {0.44f}},      {1, 4, 2, 4.8f, {0.69f, 1.28f}}, {1, 4, 1, 5.5f, {0.51f}},
-    {1, 2, 2, 4.0f, {0.29f, 0.62f}}, {1, 1, 2, 3.8f, {0.17f, 0.39f}}, {1, 1, 3, 3.3f, {0.22f, 0.39f, 0.61f}},
-};
-static float tile_cost(const TileInfo& t, long long items, float steps) {
-  const long long q = items <= kCUs ? 1 : (items + kCUs - 1) / kCUs;
-  const long long full = q / t.resident, rest = q % t.resident;
-  return (float)(full + (rest ? 1 : 0)) * t.round +
-         steps * ((float)full * t.step[t.resident - 1] + (rest ? t.step[rest - 1] : 0.f));
-}
-// Whether a tile may run lists whose rows gt of the Tt token tiles share: tiles past the end are left
-// out with one list row, otherwise the groups of TM tiles have to divide those of gt.
-static bool tile_fits(const TileInfo& t, int Tt, int gt) {
-  const int want = g_ffn_tiles_per_wg;
-  if (want != 0) {
-    int most = want;
-    while (gt != Tt && gt % most != 0) most /= 2;
-    if (t.tm != most) return false;
-  }
-  return gt == Tt || gt % t.tm == 0;
-}
-static int ceil_div(long long a, int b) { return (int)((a + b - 1) / b); }
-
-// Lists per group of tiles share few weight rows, so the bytes that the workgroups pull bound the launch:
-// us for `wgs` workgroups of `steps` steps each at the rate that such launches reach (4096 - 8192 tokens,
-// d 2048 - 4096: 9.3 - 13 TB/s through the L2s, of which some 6 TB/s miss).
-static float pull_cost(const TileInfo& t, float wgs, float steps) {
-  return wgs * steps * (float)(t.tm + t.tn) * 8192.f / 11.5e6f;
-}
-
-// First product: tile by the cost of its work items.  With lists per group of tiles the number of
-// entries varies between calls and a caller's capacity has slack (a seventh is taken off), and half a
-// ragged group per list row is added.
-static int choose_sdd(int Tt, int gt, int d, int nnz_cap) {
-  int best = -1;
-  float least = 0.f;
-  for (int id = 0; id < kTiles; ++id) {
-    const TileInfo& t = kTileInfo[id];
-    if (!tile_fits(t, Tt, gt)) continue;
-    long long items;
-    if (gt == Tt) {
-      items = (long long)ceil_div(Tt, t.tm) * ceil_div(nnz_cap, t.tn);
-    } else {
-      items = (long long)(6.f / 7.f * (float)nnz_cap) * (gt / t.tm) / t.tn + (long long)(Tt / t.tm) * (t.tn - 1) / (2 * t.tn);
-      if (id == kT14Deep && items > kCUs) continue;     // a second round starts out of step with the first: its L2 hits are gone
-    }
-    float c = tile_cost(t, items, (float)(d / 64));
-    if (gt != Tt) c = std::max(c, pull_cost(t, (float)items, (float)(d / 64))) + 0.25f * c;
-    if (best < 0 || c < least) best = id, least = c;
-  }
-  return best;
-}
-// Second product, likewise; its steps are the list entries.  With one list row and room for partial sums
-// the units that do not fill a round may have their list cut into 2 - 4 pieces, each at least 8 entries
-// long, which costs a second launch and the pieces' way through memory.
-struct DsdPlan {
-  int id, full, rest, pieces;
-  size_t part_bytes() const {
-    return pieces > 1 ? (size_t)rest * pieces * kTileInfo[id].tm * kTileInfo[id].tn * 4096 * sizeof(float) : 0;
-  }
-};
-static DsdPlan choose_dsd(int Tt, int gt, int d, int nnz_cap, size_t part_bytes) {
-  DsdPlan best = {-1, 0, 0, 1};
-  float least = 0.f;
-  for (int id = 0; id < kTiles; ++id) {
-    const TileInfo& t = kTileInfo[id];
-    if (!tile_fits(t, Tt, gt)) continue;
-    const long long items = (long long)ceil_div(Tt, t.tm) * ceil_div(d, 64 * t.tn);
-    if (gt != Tt) {
-      if (id == kT14Deep && items > kCUs) continue;
-      // a launch of one round lasts as long as its longest list
-      const float mean = 6.f / 7.f * (float)nnz_cap * gt / Tt;
-      const float busy = tile_cost(t, items, mean * (items <= (long long)kCUs * t.resident ? 1.35f : 1.1f));
-      const float c = std::max(busy, pull_cost(t, (float)items, mean)) + 0.25f * busy;
-      if (best.id < 0 || c < least) best = {id, (int)items, 0, 1}, least = c;
-      continue;
-    }
-    const float c = tile_cost(t, items, (float)nnz_cap);
-    if (best.id < 0 || c < least) best = {id, (int)items, 0, 1}, least = c;
-    if (id > kT22) continue;              // (a cut launch of narrow tiles never paid)
-    for (int p = 2; p <= 4 && nnz_cap >= 8 * p; ++p) {
-      const long long full = items / (kCUs * t.resident) * (kCUs * t.resident);
-      const DsdPlan plan = {id, (int)full, (int)(items - full), p};
-      if (plan.rest == 0 || plan.part_bytes() > part_bytes) continue;
-      const float cc = (full > 0 ? tile_cost(t, full, (float)nnz_cap) : 0.f) +
-                       tile_cost(t, (long long)plan.rest * p, (float)nnz_cap / p) + 5.f + (float)plan.part_bytes() / 2.5e6f;
-      if (cc < least) best = plan, least = cc;
-    }
-  }
-  return best;
-}
 // Bytes of partial sums with which the second product, given one list row of at most nnz_cap entries
 // for all Tt token tiles, may cut lists (0: never), whatever the caller's tiles per workgroup.
 size_t ffn_dsd_split_bytes(int Tt, int d, int nnz_cap) {
-  const int was = g_ffn_tiles_per_wg;
   size_t need = 0;
   for (int want : {0, 1, 2, 4}) {
-    g_ffn_tiles_per_wg = want;
-    const size_t b = choose_dsd(Tt, Tt, d, nnz_cap, ~(size_t)0).part_bytes();
+    const size_t b = choose_dsd(Tt, Tt, d, nnz_cap, ~(size_t)0, want).part_bytes();
     need = b > need ? b : need;
   }
-  g_ffn_tiles_per_wg = was;
   return need;
 }
 
@@ -677,24 +610,25 @@ size_t ffn_dsd_split_bytes(int Tt, int d, int nnz_cap) {
 
 template <int DT, bool LORA>
 static void launch_sdd(SddArgs a, hipStream_t st) {
-  const int id = choose_sdd(a.Tt, a.gt, a.K, a.nnz_cap);
-  const TileInfo& t = kTileInfo[id];
-  a.band = t.tm == 4 ? 4 : 8;
-  int grid;
-  if (a.gt == a.Tt) {
-    grid = 8 * ceil_div((long long)ceil_div(a.Tt, t.tm) * ceil_div(a.nnz_cap, t.tn), 8);
-  } else {   // items <= entries / tn + a ragged group per row; per XCD L = ceil(items / 8) of them in 8 * ceil(L / 8) slots
-    const long long items = ceil_div((long long)a.nnz_cap * (a.gt / t.tm), t.tn) + (t.tn > 1 ? a.Tt / t.tm : 0);
-    grid = 64 * ceil_div(ceil_div(items, 8), 8);
+  const SddPlan p = plan_sdd(a.Tt, a.gt, a.K, a.nnz_cap, a.blocks, g_ffn_tiles_per_wg);
+  if (p.grid == 0) return;
+  if (!LORA && p.allowed) {
+    a.own = p.id;
+    a.grid = p.grid;
+    a.allowed = p.allowed;
+    if (kTileInfo[p.id].resident == 1)
+      hipLaunchKernelGGL((ffn_sdd_any<DT, 1>), dim3(p.grid), dim3(512), 0, st, a);
+    else
+      hipLaunchKernelGGL((ffn_sdd_any<DT, 2>), dim3(p.grid), dim3(256), 0, st, a);
+    return;
   }
-  if (grid == 0) return;
-#define LX_CALL(TL) hipLaunchKernelGGL((ffn_sdd<TL, DT, LORA>), dim3(grid), dim3(TL::kTileThreads), 0, st, a)
-  LX_TILES(id, LX_CALL)
+#define LX_CALL(TL) hipLaunchKernelGGL((ffn_sdd<TL, DT, LORA>), dim3(p.grid), dim3(TL::kTileThreads), 0, st, a)
+  LX_TILES(p.id, LX_CALL)
 #undef LX_CALL
 }
 template <int DT, bool LORA>
 static void launch_dsd(DsdArgs a, size_t part_bytes, hipStream_t st) {
-  const DsdPlan p = choose_dsd(a.Tt, a.gt, a.ncols, a.nnz_cap, LORA || !a.part ? 0 : part_bytes);
+  const DsdPlan p = choose_dsd(a.Tt, a.gt, a.ncols, a.nnz_cap, LORA || !a.part ? 0 : part_bytes, g_ffn_tiles_per_wg);
   const TileInfo& t = kTileInfo[p.id];
   a.band = t.tm == 4 ? 4 : 8;
   a.full = p.full;
@@ -728,7 +662,7 @@ static hipError_t launch_ffn_bf16_t(int pass, int Tt, int gt, int Fb, int d, int
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
   {
     ProfScope ps(pass == 0 ? kKFfnUp : kKFfnDh, st);
-    launch_sdd<DT, false>({A, W1, pass == 0 ? b1 : nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, act_out,
+    launch_sdd<DT, false>({A, W1, pass == 0 ? b1 : nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, act_out,
                            pass == 0 ? nullptr : act_gate, nullptr, nullptr}, st);
   }
   hipError_t e = hipGetLastError();
@@ -763,7 +697,7 @@ static hipError_t launch_ffn_lora_fwd_bf16_t(int Tt, int gt, int d, int F, const
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKFfnUp, st);
-    launch_sdd<DT, true>({X, W_up, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, H_act, nullptr, U, B_pad}, st);
+    launch_sdd<DT, true>({X, W_up, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, H_act, nullptr, U, B_pad}, st);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -789,7 +723,7 @@ static hipError_t launch_ffn_lora_bwd_bf16_t(int Tt, int gt, int d, int F, const
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
   {
     ProfScope ps(kKFfnDh, st);
-    launch_sdd<DT, false>({dY, W_down_t, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, dZ, H_act, nullptr, nullptr},
+    launch_sdd<DT, false>({dY, W_down_t, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, dZ, H_act, nullptr, nullptr},
                           st);
   }
   hipError_t e = hipGetLastError();

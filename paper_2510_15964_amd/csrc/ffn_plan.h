@@ -1,0 +1,201 @@
+// Which tile the 16-bit FFN products run with: a cost model over sizes.  Plain C++ for host and device: the host
+// decides by the list's capacity, the first product's kernels decide again by its true length (see SddSet).
+#pragma once
+#include <stddef.h>
+
+#include "lx_chip.h"
+
+#if defined(__HIPCC__)
+#define LX_HD __host__ __device__ inline
+#else
+#define LX_HD inline
+#endif
+
+namespace lx {
+
+// The tiles, widest first.  A wide tile moves fewer bytes and LDS reads per product (a workgroup step
+// transfers TM + TN times 8 KiB for TM * TN products of 64 x 64 x 64), a narrow one gives the chip more
+// workgroups and has the shorter step.  `resident` workgroups fit a CU; one workgroup per CU leaves room
+// for a deeper ring, and eight wavefronts with a whole step of operands on the way hide its latency
+// (2 x 2 tiles, 4096 tokens, 14 blocks, K = 2048, 224 workgroups: 25 -> 21 us).
+enum TileId { kT44, kT24, kT22, kT22Deep, kT14, kT14Deep, kT12, kT11, kT11Many, kTiles };
+// What a launch of a tile costs, in us: `round` per round of workgroups (finding the item, filling the
+// ring, epilogue) and step[q - 1] per step with q workgroups on a CU.  Fitted to measured launches of
+// every tile at 22 shapes (64 - 8192 tokens, d 576 - 5120, 6 - 320 listed blocks, lists shared and per
+// tile; rms of the fit 6 - 18 %); at those shapes the tile that the model picks is within 1.5 % of the
+// fastest one on average, 7 % at worst.
+struct TileInfo {
+  int tm, tn, resident;
+  float round, step[3];
+};
+constexpr TileInfo kTileInfo[kTiles] = {
+    {4, 4, 1, 8.6f, {1.25f}},      {2, 4, 1, 7.4f, {0.69f}}, {2, 2, 2, 4.2f, {0.61f, 1.11f}},
+    {2, 2, 1, 5.1f, {0.44f}},      {1, 4, 2, 4.8f, {0.69f, 1.28f}}, {1, 4, 1, 5.5f, {0.51f}},
+    {1, 2, 2, 4.0f, {0.29f, 0.62f}}, {1, 1, 2, 3.8f, {0.17f, 0.39f}}, {1, 1, 3, 3.3f, {0.22f, 0.39f, 0.61f}},
+};
+LX_HD int ceil_div(int a, int b) { return (int)(((unsigned)a + (unsigned)b - 1) / (unsigned)b); }   // a >= 0
+// `resident`: at most the tile's own
+LX_HD float tile_cost(const TileInfo& t, int resident, int items, float steps) {
+  const unsigned q = items <= kCUs ? 1 : ceil_div(items, kCUs), full = q / (unsigned)resident, rest = q % (unsigned)resident;
+  const float all = t.step[resident - 1], last = rest == 0 ? 0.f : rest == 1 ? t.step[0] : t.step[1];
+  return (float)(full + (rest ? 1 : 0)) * t.round + steps * ((float)full * all + last);
+}
+// Lists per group of tiles share few weight rows, so the bytes that the workgroups pull bound the launch:
+// us for `wgs` workgroups of `steps` steps each at the rate that such launches reach (4096 - 8192 tokens,
+// d 2048 - 4096: 9.3 - 13 TB/s through the L2s, of which some 6 TB/s miss).
+LX_HD float pull_cost(const TileInfo& t, float wgs, float steps) {
+  return wgs * steps * (float)((t.tm + t.tn) * 8192) / 11.5e6f;
+}
+
+// Whether a tile may run lists whose rows gt of the Tt token tiles share: tiles past the end are left
+// out with one list row, otherwise the groups of TM tiles have to divide those of gt.  `want`: tiles per
+// workgroup that the caller asked for (0: any).
+inline bool tile_fits(const TileInfo& t, int Tt, int gt, int want) {
+  if (want != 0) {
+    int most = want;
+    while (gt != Tt && gt % most != 0) most /= 2;
+    if (t.tm != most) return false;
+  }
+  return gt == Tt || gt % t.tm == 0;
+}
+
+// ---- first product -------------------------------------------------------------------------
+// Workgroups that hold all items of a list of n entries; the kernels find theirs in the first ones.  (Their numbers
+// stay below 2^30: the launchers' callers see to that.)
+LX_HD int sdd_grid(const TileInfo& t, int Tt, int gt, int n) {
+  if (gt == Tt) return 8 * ceil_div(ceil_div(Tt, t.tm) * ceil_div(n, t.tn), 8);
+  // items <= entries / tn + a ragged group per row; per XCD L = ceil(items / 8) of them in 8 * ceil(L / 8) slots
+  const int items = ceil_div(n * (int)((unsigned)gt / t.tm), t.tn) + (t.tn > 1 ? (unsigned)Tt / t.tm : 0u);
+  return 64 * ceil_div(ceil_div(items, 8), 8);
+}
+// us for a list of n entries; with lists per group of tiles half a ragged group per list row is added.
+LX_HD int sdd_items_about(const TileInfo& t, int Tt, int gt, int n) {
+  return (unsigned)n * ((unsigned)gt / t.tm) / t.tn + (unsigned)Tt / t.tm * (t.tn - 1) / (2 * t.tn);
+}
+LX_HD float sdd_cost(const TileInfo& t, int resident, int Tt, int gt, int d, int n) {
+  const float steps = (float)((unsigned)d / 64);
+  if (gt == Tt) return tile_cost(t, resident, ceil_div(Tt, t.tm) * ceil_div(n, t.tn), steps);
+  const int items = sdd_items_about(t, Tt, gt, n);
+  const float busy = tile_cost(t, resident, items, steps), pull = pull_cost(t, (float)items, steps);
+  return (pull > busy ? pull : busy) + 0.25f * busy;
+}
+// With lists per group of tiles the deep 1 x 4 tile takes one round at most: a second one starts out of step with the
+// first, and its L2 hits are gone.
+LX_HD bool sdd_out_of_step(int id, int Tt, int gt, int n) {
+  return id == kT14Deep && gt != Tt && sdd_items_about(kTileInfo[kT14Deep], Tt, gt, n) > kCUs;
+}
+// The tile for a list of at most nnz_cap entries.  With lists per group of tiles the number of entries varies
+// between calls and a caller's capacity has slack: a seventh is taken off.
+inline int choose_sdd(int Tt, int gt, int d, int nnz_cap, int want) {
+  const int n = gt == Tt ? nnz_cap : (int)(6.f / 7.f * (float)nnz_cap);
+  int best = -1;
+  float least = 0.f;
+  for (int id = 0; id < kTiles; ++id) {
+    const TileInfo& t = kTileInfo[id];
+    if (!tile_fits(t, Tt, gt, want) || sdd_out_of_step(id, Tt, gt, n)) continue;
+    const float c = sdd_cost(t, t.resident, Tt, gt, d, n);
+    if (best < 0 || c < least) best = id, least = c;
+  }
+  return best;
+}
+
+// A capacity may say little about a list, and only the device knows the length.  The tiles therefore come in sets,
+// each compiled into one kernel, and the kernel takes the best of its set for the list that it finds: tiles of eight
+// wavefronts, one workgroup per CU, and of four, two per CU (the narrow ones are in both; in the first, half of the
+// wavefronts end at once).  The capacity decides the set and the grid: a tile is taken only if its items fit the
+// workgroups that the capacity's own tile needs for this list, or that the CUs hold at once.
+struct SddSet {
+  int n, ids[6];
+};
+constexpr SddSet kSddWide = {6, {kT44, kT24, kT22Deep, kT14Deep, kT12, kT11}};
+constexpr SddSet kSddNarrow = {4, {kT22, kT14, kT12, kT11}};
+constexpr SddSet sdd_set(int resident) { return resident == 1 ? kSddWide : kSddNarrow; }
+// The workgroups, out of the `grid` launched, that may have an item of a list of n entries.
+template <int RESIDENT>
+LX_HD int sdd_limit(int own, int grid, int Tt, int gt, int n) {
+  const int need = sdd_grid(kTileInfo[own], Tt, gt, n), once = grid < RESIDENT * kCUs ? grid : RESIDENT * kCUs;
+  return need > once ? need : once;
+}
+// The tile of a set for a list of n entries: `own`, the capacity's (its items always fit), or a better one of those
+// in the bit mask `allowed` whose items fit `limit` workgroups.
+template <int RESIDENT>
+LX_HD int sdd_pick(int own, unsigned allowed, int limit, int Tt, int gt, int d, int n) {
+  constexpr SddSet set = sdd_set(RESIDENT);
+  int best = own;
+  float least = 0.f;
+  bool first = true;
+#pragma unroll
+  for (int k = 0; k < set.n; ++k) {
+    const int id = set.ids[k];
+    const TileInfo t = kTileInfo[id];
+    if (id != own && (!(allowed >> id & 1u) || sdd_grid(t, Tt, gt, n) > limit || sdd_out_of_step(id, Tt, gt, n))) continue;
+    const float c = sdd_cost(t, RESIDENT, Tt, gt, d, n);
+    if (first || c < least) best = id, least = c, first = false;
+  }
+  return best;
+}
+// A list that fills three quarters of its capacity keeps the capacity's tile: the choice takes up to a microsecond.
+LX_HD bool sdd_keeps_own(int nnz_cap, int n) { return n >= nnz_cap - nnz_cap / 4; }
+struct SddPlan {
+  int id, grid;          // the capacity's tile, whose `resident` names the set; workgroups
+  unsigned allowed;      // tiles for sdd_pick, 0: `id` as it is
+};
+// `blocks`: every block that the list could hold.  The kernel chooses for one list row, whose length it reads anyway;
+// with lists per group of tiles, where that is a load before the first, only if the capacity is every block, that is,
+// if the caller knows nothing better, and with a list per tile only up to 64 tiles: from there on the 1 x 4 tile
+// serves most lists, and the search costs every surplus workgroup more than it gains (64 tiles, d = 2048, 11 % of the
+// blocks, every block as capacity: 42 us by the capacity's tile, 45 with the choice; 32 tiles 33.5 and 25.8).
+inline SddPlan plan_sdd(int Tt, int gt, int d, int nnz_cap, int blocks, int want) {
+  SddPlan p = {choose_sdd(Tt, gt, d, nnz_cap, want), 0, 0u};
+  const int resident = kTileInfo[p.id].resident;
+  p.grid = sdd_grid(kTileInfo[p.id], Tt, gt, nnz_cap);
+  if (p.grid == 0 || p.id >= kT11) return p;      // (nothing is narrower than kT11)
+  if (gt != Tt && (nnz_cap < blocks || (resident == 2 && Tt >= 64))) return p;
+  if (p.grid < resident * kCUs) p.grid = resident * kCUs;
+  for (int id = 0; id < kTiles; ++id)
+    if (tile_fits(kTileInfo[id], Tt, gt, want)) p.allowed |= 1u << id;
+  return p;
+}
+
+// ---- second product ------------------------------------------------------------------------
+// Its steps are the list entries.  With one list row and room for partial sums
+// the units that do not fill a round may have their list cut into 2 - 4 pieces, each at least 8 entries
+// long, which costs a second launch and the pieces' way through memory.
+struct DsdPlan {
+  int id, full, rest, pieces;
+  size_t part_bytes() const {
+    return pieces > 1 ? (size_t)rest * pieces * kTileInfo[id].tm * kTileInfo[id].tn * 4096 * sizeof(float) : 0;
+  }
+};
+inline DsdPlan choose_dsd(int Tt, int gt, int d, int nnz_cap, size_t part_bytes, int want) {
+  DsdPlan best = {-1, 0, 0, 1};
+  float least = 0.f;
+  for (int id = 0; id < kTiles; ++id) {
+    const TileInfo& t = kTileInfo[id];
+    if (!tile_fits(t, Tt, gt, want)) continue;
+    const int items = ceil_div(Tt, t.tm) * ceil_div(d, 64 * t.tn);
+    if (gt != Tt) {
+      if (id == kT14Deep && items > kCUs) continue;
+      // a launch of one round lasts as long as its longest list
+      const float mean = 6.f / 7.f * (float)nnz_cap * gt / Tt;
+      const float busy = tile_cost(t, t.resident, items, mean * (items <= kCUs * t.resident ? 1.35f : 1.1f));
+      const float pull = pull_cost(t, (float)items, mean), c = (pull > busy ? pull : busy) + 0.25f * busy;
+      if (best.id < 0 || c < least) best = {id, items, 0, 1}, least = c;
+      continue;
+    }
+    const float c = tile_cost(t, t.resident, items, (float)nnz_cap);
+    if (best.id < 0 || c < least) best = {id, items, 0, 1}, least = c;
+    if (id > kT22) continue;              // (a cut launch of narrow tiles never paid)
+    for (int p = 2; p <= 4 && nnz_cap >= 8 * p; ++p) {
+      const int full = items / (kCUs * t.resident) * (kCUs * t.resident);
+      const DsdPlan plan = {id, full, items - full, p};
+      if (plan.rest == 0 || plan.part_bytes() > part_bytes) continue;
+      const float cc = (full > 0 ? tile_cost(t, t.resident, full, (float)nnz_cap) : 0.f) +
+                       tile_cost(t, t.resident, plan.rest * p, (float)nnz_cap / p) + 5.f + (float)plan.part_bytes() / 2.5e6f;
+      if (cc < least) best = plan, least = cc;
+    }
+  }
+  return best;
+}
+
+}  // namespace lx

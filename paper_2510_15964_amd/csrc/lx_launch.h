@@ -3,9 +3,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lx_chip.h"
+
 namespace lx {
 
-constexpr int kCUs = 256;   // compute units of the chip
 // element types of the 16-bit kernels (the `dt` argument of their launchers)
 constexpr int kBf16 = 0, kF16 = 1;
 

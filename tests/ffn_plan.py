@@ -1,0 +1,25 @@
+"""The library's tile rules (csrc/ffn_plan.h) for the tests: which tile a call of given sizes runs with."""
+import ctypes as C
+import os
+import subprocess
+import tempfile
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+TILES = ("4x4", "2x4", "2x2", "2x2 deep", "1x4", "1x4 deep", "1x2", "1x1", "1x1 many")   # order of TileId
+
+
+def load():
+    d = tempfile.mkdtemp()
+    lib = os.path.join(d, "ffn_plan.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Wno-unknown-pragmas", "-shared", "-fPIC",
+                    os.path.join(HERE, "ffn_plan_shim.cpp"), "-o", lib], check=True)
+    L = C.CDLL(lib)
+    L.sdd_us.restype = C.c_float
+    L.dsd_tile.argtypes = [C.c_int] * 4 + [C.c_longlong, C.c_int, C.POINTER(C.c_int)]
+    return L
+
+
+def dsd(L, Tt, gt, d, cap, part_bytes=0, want=0):
+    """(tile, pieces) of the second product."""
+    p = C.c_int(0)
+    return TILES[L.dsd_tile(Tt, gt, d, cap, part_bytes, want, C.byref(p))], p.value

@@ -1,0 +1,31 @@
+// The tile rules of csrc/ffn_plan.h as C functions (compiled by ffn_plan.py with the host compiler).
+#include "../paper_2510_15964_amd/csrc/ffn_plan.h"
+
+using namespace lx;
+
+extern "C" {
+
+// The first product's tile for a list of n entries handed over with the capacity nnz_cap.
+int sdd_tile(int Tt, int gt, int d, int nnz_cap, int blocks, int want, int n) {
+  const SddPlan p = plan_sdd(Tt, gt, d, nnz_cap, blocks, want);
+  if (!p.allowed || sdd_keeps_own(nnz_cap, n)) return p.id;
+  if (kTileInfo[p.id].resident == 1)
+    return sdd_pick<1>(p.id, p.allowed, sdd_limit<1>(p.id, p.grid, Tt, gt, n), Tt, gt, d, n);
+  return sdd_pick<2>(p.id, p.allowed, sdd_limit<2>(p.id, p.grid, Tt, gt, n), Tt, gt, d, n);
+}
+// Workgroups launched, and those that the tile of sdd_tile needs.
+int sdd_launched(int Tt, int gt, int d, int nnz_cap, int blocks, int want) {
+  return plan_sdd(Tt, gt, d, nnz_cap, blocks, want).grid;
+}
+int sdd_needed(int id, int Tt, int gt, int n) { return sdd_grid(kTileInfo[id], Tt, gt, n); }
+// The tile that the rule took before the list's length played a part, and the model's time for a tile.
+int sdd_tile_of_capacity(int Tt, int gt, int d, int nnz_cap, int want) { return choose_sdd(Tt, gt, d, nnz_cap, want); }
+float sdd_us(int id, int Tt, int gt, int d, int n) { return sdd_cost(kTileInfo[id], kTileInfo[id].resident, Tt, gt, d, n); }
+// The second product's tile; *pieces: 1, or what the lists of its last units are cut into.
+int dsd_tile(int Tt, int gt, int d, int nnz_cap, long long part_bytes, int want, int* pieces) {
+  const DsdPlan p = choose_dsd(Tt, gt, d, nnz_cap, (size_t)part_bytes, want);
+  *pieces = p.pieces;
+  return p.id;
+}
+
+}  // extern "C"

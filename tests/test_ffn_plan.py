@@ -1,0 +1,55 @@
+"""The tile rules of the 16-bit FFN products, on the host: the choice by the list's length against the choice by its
+capacity."""
+import random
+
+import pytest
+
+import ffn_plan
+from ffn_plan import TILES
+from test_gpu_ffn_tiles import CAPACITIES
+
+
+@pytest.fixture(scope="module")
+def L():
+    return ffn_plan.load()
+
+
+# token tiles, d, neuron blocks, listed blocks (one list for all tiles): a tenth of the neurons of OPT layers
+SHARED = [(64, 2048, 128, 14), (128, 2048, 128, 14), (32, 2560, 160, 20), (16, 4096, 256, 26), (128, 4096, 256, 28),
+          (61, 5120, 320, 32)]
+
+
+@pytest.mark.parametrize("Tt,d,Fb,n", SHARED)
+def test_first_product_survives_a_loose_capacity(L, Tt, d, Fb, n):
+    """Twice, four times and every block as capacity: by the model at most 15 % slower than with the exact one.  (By
+    the capacity's tile it was up to 2.5 times.)"""
+    us = lambda tile: L.sdd_us(tile, Tt, Tt, d, n)
+    exact = us(L.sdd_tile(Tt, Tt, d, n, Fb, 0, n))
+    worst = 0.0
+    for cap in (2 * n, 4 * n, Fb):
+        assert us(L.sdd_tile(Tt, Tt, d, cap, Fb, 0, n)) <= 1.15 * exact, cap
+        worst = max(worst, us(L.sdd_tile_of_capacity(Tt, Tt, d, cap, 0)) / exact)
+    print(Tt, d, n, "capacity's tile", worst)
+
+
+def test_items_always_fit_the_launch(L):
+    """Whatever the sizes, capacity, length and knob: the tile that a kernel picks needs no more workgroups than were
+    launched, and an exact capacity's own tile is kept."""
+    rng = random.Random(5)
+    for _ in range(20000):
+        rows = rng.choice([1, rng.randint(1, 40)])
+        gt = rng.choice([1, rng.randint(1, 40)])
+        Tt, d, Fb, want = rows * gt, 64 * rng.randint(1, 80), rng.randint(1, 320), rng.choice([0, 0, 1, 2, 4])
+        blocks = rows * Fb
+        cap = rng.choice([blocks, rng.randint(1, blocks)])
+        n = rng.randint(0, cap)
+        tile = L.sdd_tile(Tt, gt, d, cap, blocks, want, n)
+        assert L.sdd_needed(tile, Tt, gt, n) <= L.sdd_launched(Tt, gt, d, cap, blocks, want), (Tt, gt, d, Fb, cap, n)
+        assert L.sdd_tile(Tt, gt, d, cap, blocks, want, cap) == L.sdd_tile_of_capacity(Tt, gt, d, cap, want)
+
+
+def test_labels_of_the_gpu_cases(L):
+    for _, Tt, d, Fb, nnz, rows, by_cap, by_list in CAPACITIES:
+        gt, blocks = Tt // rows, rows * Fb
+        got = (TILES[L.sdd_tile_of_capacity(Tt, gt, d, blocks, 0)], TILES[L.sdd_tile(Tt, gt, d, blocks, blocks, 0, rows * nnz)])
+        assert got == (by_cap, by_list), (Tt, d, Fb, nnz, rows, got)

@@ -103,3 +103,58 @@ def test_cut_lists(lx, Tt, d, nnz):
         assert torch.isfinite(Y).all()
         assert (Y - out[0]).norm() <= 1e-3 * out[0].norm()
         assert (Y - out[0]).abs().max() <= 2 ** -7 * out[0].abs().max()
+
+
+# dtype, token tiles, d, neuron blocks, listed blocks per list row, list rows; the first product's tile by the
+# capacity of every block and by the list (checked in test_ffn_plan.py)
+CAPACITIES = [
+    ("bf16", 24, 64, 96, 1, 1, "4x4", "1x1"),
+    ("f16", 61, 64, 48, 5, 1, "4x4", "1x2"),
+    ("bf16", 24, 64, 96, 24, 1, "4x4", "2x2 deep"),
+    ("bf16", 25, 64, 96, 48, 1, "4x4", "2x4"),
+    ("bf16", 48, 1024, 96, 48, 1, "2x4", "4x4"),
+    ("bf16", 24, 64, 96, 0, 1, "4x4", "1x1"),          # nothing listed
+    ("bf16", 18, 512, 48, 24, 1, "2x2 deep", "1x2"),
+    ("f16", 13, 64, 96, 45, 1, "2x2", "1x2"),
+    ("bf16", 18, 64, 96, 48, 2, "1x4", "1x2"),
+    ("bf16", 18, 1024, 48, 24, 2, "1x4 deep", "1x2"),
+    ("f16", 60, 64, 48, 12, 3, "4x4", "2x2 deep"),
+    ("bf16", 8, 1024, 96, 1, 8, "1x4 deep", "1x1"),
+    ("bf16", 60, 64, 24, 5, 60, "1x4", "1x1"),
+    ("bf16", 60, 512, 48, 24, 60, "1x2", "1x4"),
+    ("f16", 42, 1024, 17, 17, 2, "1x4 deep", "1x4 deep"),   # every block listed
+    ("bf16", 50, 1024, 12, 12, 2, "1x1 many", "1x1 many"),
+]
+
+
+@pytest.mark.parametrize("dtype,Tt,d,Fb,nnz,rows,by_cap,by_list", CAPACITIES)
+def test_capacity_does_not_change_results(lx, dtype, Tt, d, Fb, nnz, rows, by_cap, by_list):
+    """A list handed over with room for every block runs by another tile than with its exact capacity: same bits."""
+    import torch
+    T, F, gt = Tt * 64, Fb * 64, Tt // rows
+    rng = np.random.default_rng(1000 + Tt)
+    mask = np.zeros((rows, Fb), np.uint8)
+    for r in mask:
+        r[rng.choice(Fb, nnz, replace=False)] = 1
+    dt = dev(np.zeros(1, np.float32), dtype).dtype
+    g = torch.Generator(device="cuda").manual_seed(Tt)
+    mk = lambda *s: (torch.randn(s, device="cuda", generator=g) * 0.1).to(dt)
+    X, dY, Wu, Wd = mk(T, d), mk(T, d), mk(F, d), mk(d, F)
+    Wut, Wdt = lx.lx_ffn_pack_weights(Wu, Wd)
+    out = []
+    for cap in (max(rows * nnz, 1), rows * Fb):
+        print(dtype, Tt, d, Fb, nnz, rows, "capacity", cap, flush=True)
+        bl = lx.lx_mask_compact(torch.from_numpy(mask).cuda(), nnz_cap=cap)
+        H = torch.full(((cap * gt + 1) * 4096,), float("nan"), dtype=dt, device="cuda")
+        Y, dX = (torch.full((T + 64, d), float("nan"), dtype=dt, device="cuda") for _ in range(2))
+        ws = torch.empty(lx.lx_sparse_ffn_bwd_workspace_bytes(lx_dtype(lx, dtype), T, d, F, 64, 64, cap * gt, 1),
+                         dtype=torch.uint8, device="cuda")
+        lx.lx_sparse_ffn_fwd(X, Wu, Wd, bl, 64, 64, Y[:T], H)
+        lx.lx_sparse_ffn_bwd_dx(dY, H, Wu, Wd, bl, 64, 64, dX[:T], ws, W_up_t=Wut, W_down_t=Wdt)
+        torch.cuda.synchronize()
+        n = rows * nnz * gt * 4096
+        assert torch.isnan(H[n:]).all() and torch.isnan(Y[T:]).all() and torch.isnan(dX[T:]).all()
+        assert not any(torch.isnan(t).any() for t in (H[:n], Y[:T], dX[:T]))
+        out.append((H[:n], Y[:T], dX[:T]))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
