@@ -1,12 +1,13 @@
 """The tile rules of the 16-bit FFN products, on the host: the choice by the list's length against the choice by its
-capacity."""
+capacity, and that the GPU tests reach every tile."""
 import random
 
 import pytest
 
 import ffn_plan
 from ffn_plan import TILES
-from test_gpu_ffn_tiles import CAPACITIES
+from test_gpu_ffn_tiles import CAPACITIES, CUT_BY_TILE, EDGES
+from test_gpu_lora import LORA_TILES
 
 
 @pytest.fixture(scope="module")
@@ -53,3 +54,27 @@ def test_labels_of_the_gpu_cases(L):
         gt, blocks = Tt // rows, rows * Fb
         got = (TILES[L.sdd_tile_of_capacity(Tt, gt, d, blocks, 0)], TILES[L.sdd_tile(Tt, gt, d, blocks, blocks, 0, rows * nnz)])
         assert got == (by_cap, by_list), (Tt, d, Fb, nnz, rows, got)
+    for Tt, d, nnz, tile, pieces in CUT_BY_TILE:
+        assert ffn_plan.dsd(L, Tt, Tt, d, nnz, 1 << 40) == (tile, pieces), (Tt, d, nnz)
+    for Tt, d, Fb, rows, up, dx in LORA_TILES:
+        gt, cap = Tt // rows, rows * Fb
+        got = (TILES[L.sdd_tile_of_capacity(Tt, gt, d, cap, 0)], ffn_plan.dsd(L, Tt, gt, d, cap)[0])
+        assert got == (up, dx), (Tt, d, Fb, rows, got)
+
+
+def test_gpu_cases_reach_every_tile(L):
+    """Plain FFN: the cases of test_tile_edges (the library's choice and every knob value) and of the capacity test;
+    with the low-rank step: test_lora_every_tile; the reductions: test_cut_lists_by_tile."""
+    up, down = set(), set()
+    for _, Tt, d, Fb, nnz, _ in EDGES:
+        for want in (0, 1, 2, 4):
+            up.add(TILES[L.sdd_tile(Tt, Tt, d, nnz, Fb, want, nnz)])
+            down.add(ffn_plan.dsd(L, Tt, Tt, d, nnz, 0, want)[0])
+    for _, Tt, d, Fb, nnz, rows, _, by_list in CAPACITIES:
+        for cap in (max(rows * nnz, 1), rows * Fb):
+            up.add(TILES[L.sdd_tile(Tt, Tt // rows, d, cap, rows * Fb, 0, rows * nnz)])
+            down.add(ffn_plan.dsd(L, Tt, Tt // rows, d, cap)[0])
+    assert up == set(TILES), set(TILES) - up
+    assert down == set(TILES), set(TILES) - down
+    assert {c[4] for c in LORA_TILES} == set(TILES) and {c[5] for c in LORA_TILES} == set(TILES)
+    assert {c[3] for c in CUT_BY_TILE} == {"4x4", "2x4", "2x2"}

@@ -18,7 +18,7 @@ def lx():
     return lx
 
 
-@pytest.mark.parametrize("dtype,Tt,d,Fb,nnz,bias", [
+EDGES = [
     ("bf16", 1, 64, 3, 1, False),        # one tile, one column chunk, one block
     ("bf16", 3, 320, 8, 5, True),        # short groups of two and four, columns short of 128 and 256
     ("f16", 7, 192, 70, 63, False),      # one entry short of a fetch
@@ -26,7 +26,14 @@ def lx():
     ("bf16", 9, 128, 70, 65, True),      # one entry into the second fetch
     ("f16", 2, 576, 140, 129, False),
     ("bf16", 61, 128, 16, 9, False),     # many workgroups, ragged groups of entries
-])
+    ("bf16", 103, 512, 12, 9, True),     # 2 x 4 tiles in the first product, short last groups on both sides
+    ("bf16", 103, 576, 12, 8, False),    # 2 x 4 tiles in the second, columns short of a workgroup's
+    ("f16", 86, 1536, 3, 1, False),      # 2 x 2 tiles, eight wavefronts
+    ("bf16", 21, 512, 40, 37, False),
+]
+
+
+@pytest.mark.parametrize("dtype,Tt,d,Fb,nnz,bias", EDGES)
 def test_tile_edges(lx, oracle, dtype, Tt, d, Fb, nnz, bias):
     """Every number of token tiles per workgroup gives the same bits; sampled tiles match the oracle."""
     import torch
@@ -158,3 +165,31 @@ def test_capacity_does_not_change_results(lx, dtype, Tt, d, Fb, nnz, rows, by_ca
         out.append((H[:n], Y[:T], dX[:T]))
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+# token tiles, d, listed blocks; the second product's tile and the pieces its last lists are cut into
+CUT_BY_TILE = [(65, 256, 129, "2x2", 3), (130, 192, 129, "2x4", 3), (130, 2048, 33, "4x4", 4)]
+
+
+@pytest.mark.parametrize("Tt,d,nnz,tile,pieces", CUT_BY_TILE)
+def test_cut_lists_by_tile(lx, Tt, d, nnz, tile, pieces):
+    """The reduction of every tile that cuts lists: equal to the uncut call to the rounding of fp32 sums."""
+    import torch
+    T, F = Tt * 64, nnz * 64
+    g = torch.Generator(device="cuda").manual_seed(nnz)
+    mk = lambda *s: (torch.randn(s, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    X, Wu, Wd = mk(T, d), mk(F, d), mk(d, F)
+    bl = lx.lx_mask_compact(torch.ones((1, nnz), dtype=torch.uint8, device="cuda"))
+    H = torch.zeros((nnz * Tt * 4096,), dtype=X.dtype, device="cuda")
+    nbytes = lx.lx_sparse_ffn_split_workspace_bytes(lx.LX_BF16, T, d, 64, bl)
+    assert nbytes > 0
+    out = []
+    for n in (0, nbytes):
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda") if n else None
+        Y = torch.full_like(X, float("nan"))
+        lx.lx_sparse_ffn_fwd(X, Wu, Wd, bl, 64, 64, Y, H, workspace=ws)
+        torch.cuda.synchronize()
+        out.append(Y.float())
+    assert torch.isfinite(out[1]).all()
+    assert (out[1] - out[0]).norm() <= 1e-3 * out[0].norm()              # few elements round the other way
+    assert (out[1] - out[0]).abs().max() <= 2 ** -7 * out[0].abs().max()  # and by one unit of bf16 at most

@@ -277,3 +277,63 @@ def test_lora_token_tile_counts(lx, oracle, Tt, d, F, rows, dtype):
     c = make_case(64 * Tt, d, F, 16, 0.5, 40 + Tt, rows=None if rows == Tt else rows, dtype=dtype)
     got, ref = run_both(lx, oracle, c)
     check(got, ref, f"{Tt} tiles d={d} F={F} rows={rows} {dtype}", dtype=dtype)
+
+
+# token tiles, d, listed blocks, list rows; the tiles of the two products that carry the low-rank step (checked in
+# test_ffn_plan.py)
+LORA_TILES = [
+    (129, 64, 6, 1, "1x2", "1x1 many"),
+    (51, 64, 40, 1, "1x4", "1x1"),
+    (103, 64, 9, 1, "2x2", "1x1 many"),
+    (57, 768, 9, 1, "2x2 deep", "1x1 many"),
+    (103, 512, 9, 1, "2x4", "2x2 deep"),
+    (115, 64, 17, 1, "4x4", "1x1"),
+    (42, 1024, 17, 2, "1x4 deep", "1x1 many"),
+    (103, 576, 1, 1, "1x1 many", "2x2"),
+    (85, 1536, 1, 1, "1x1", "1x4"),
+    (103, 576, 8, 1, "2x2 deep", "2x4"),
+    (129, 1024, 1, 1, "1x1", "4x4"),
+    (98, 512, 12, 2, "1x1 many", "1x4 deep"),
+    (97, 512, 1, 1, "1x1 many", "1x2"),
+    (6, 192, 3, 6, "1x1 many", "1x1 many"),
+]
+
+
+@pytest.mark.parametrize("Tt,d,Fb,rows,up,dx", LORA_TILES)
+def test_lora_every_tile(lx, Tt, d, Fb, rows, up, dx):
+    """The low-rank step in every tile, odd token tile counts and short last groups of entries among them, against the
+    definitions in float64 (all blocks listed; both sides take the same stored activations and U)."""
+    import torch
+    T, F, r, dt = 64 * Tt, 64 * Fb, 16, "bf16"
+    rng = np.random.default_rng(Tt + d)
+    q = lambda *s, std: round_to(rng.standard_normal(s) * std, dt).astype(np.float64)
+    X, dY, Wu, Wd = q(T, d, std=1), q(T, d, std=1), q(F, d, std=0.05), q(d, F, std=0.05)
+    A, B = np.zeros((64, d)), np.zeros((F, 64))
+    A[:r], B[:, :r] = q(r, d, std=1 / np.sqrt(d)), q(F, r, std=0.05)
+    d32 = lambda a: dev(a.astype(np.float32), dt)
+    Xd, Wud, Wdd, Ad, Bd = (d32(a) for a in (X, Wu, Wd, A, B))
+    bl = lx.lx_mask_compact(torch.ones((rows, Fb), dtype=torch.uint8, device="cuda"))
+    gt, nb = Tt // rows, Tt * Fb
+    blocks = lambda a: np.ascontiguousarray(a.reshape(rows, gt, 64, Fb, 64).transpose(0, 3, 1, 2, 4)).reshape(nb, 64, 64)
+    H_act = torch.full(((nb + 1) * 4096,), float("nan"), dtype=Xd.dtype, device="cuda")
+    Y, dX = (torch.full_like(Xd, float("nan")) for _ in range(2))
+    U = torch.full((T, 64), float("nan"), dtype=Xd.dtype, device="cuda")
+    lx.lx_sparse_ffn_lora_fwd(Xd, Wud, Ad, Bd, Wdd, bl, Y, H_act, U)
+    torch.cuda.synchronize()
+    assert torch.isnan(H_act[nb * 4096:]).all()
+    Uo = X @ A.T
+    Ho = np.maximum(X @ Wu.T + Uo @ B.T, 0)
+    got = dict(U=host(U), H=host(H_act[:nb * 4096]).reshape(nb, 64, 64), Y=host(Y))
+    ref = dict(U=Uo, H=blocks(Ho), Y=Ho @ Wd.T)
+    Hq, Uq = round_to(Ho.astype(np.float32), dt), round_to(Uo.astype(np.float32), dt)
+    H_act[:nb * 4096] = dev(blocks(Hq).reshape(-1), dt)
+    Wut, Wdt = lx.lx_ffn_pack_weights(Wud, Wdd)
+    ws = torch.empty(lx.lx_sparse_ffn_lora_bwd_workspace_bytes(T, d, F, nb), dtype=torch.uint8, device="cuda")
+    dA = torch.full((64, d), float("nan"), dtype=torch.float32, device="cuda")
+    dB = torch.full((F, 64), float("nan"), dtype=torch.float32, device="cuda")
+    lx.lx_sparse_ffn_lora_bwd(Xd, d32(dY), H_act, dev(Uq, dt), Wut, Wdt, Ad, Bd, bl, dX, dA, dB, ws)
+    torch.cuda.synchronize()
+    dZ = (dY @ Wd) * (Hq > 0)
+    got.update(dX=host(dX), dA=host(dA), dB=host(dB))
+    ref.update(dX=dZ @ Wu + (dZ @ B) @ A, dA=(dZ @ B).T @ X, dB=dZ.T @ Uq.astype(np.float64))
+    check(got, ref, f"{up} / {dx}")
