@@ -577,16 +577,26 @@ __device__ __forceinline__ void walk_table(int* tab, const RowSet& rows, const i
 // 68 % of the blocks, forward 91 us, see the launcher).  The workgroups of the last P % 8 pairs are spread over all XCDs in
 // runs.  The batch entry is the fast index of a pair: the masks of the batch entries are the same or
 // alike, those of the heads are not, so every XCD gets about the same mix of heads.
+// The longest workgroups of a pair have the smallest numbers z.  Where all workgroups of a launch are resident at
+// once and own few rows (a.spread: otherwise the deal of the rows makes them equal), it matters which of them share
+// a CU: an XCD's go to its 32 CUs in turn, so they are ordered by z, the first 32 the other way round: a CU's first
+// workgroup is short where its second one is long, and the longest are alone where there are not two per CU.
+// Against z after z of one pair and then the next (forward / dQ / dK and dV, us): 4 x 12 heads of 512 tokens, D = 128,
+// all blocks 18.2 / 23.1 / 28.0 -> 15.7 / 20.2 / 23.5; 16 heads of 4096, D = 64, 25 % of the blocks 29.5 / 37.3 / 47.5
+// -> 24.8 / 30.6 / 43.7; 32 heads of 2048, D = 128, dK and dV at 25 % 43.3 -> 36.1, with all blocks 90.4 -> 94.6 (the
+// largest loss of 204 launches; with four or more rows per workgroup the order costs up to 8 % there, and gains little).
 struct PairWork {
   int b, group, z;
 };
 __device__ __forceinline__ bool pair_work(const AttnArgs& a, PairWork& p) {
   const int P = a.B * (a.Hh / a.vheads), gz = a.gz;
-  const int x = blockIdx.x % 8, s = blockIdx.x / 8, whole = P / 8 * gz;
-  int pair;
+  const int x = blockIdx.x % 8, whole = P / 8 * gz;
+  int s = blockIdx.x / 8, pair;
+  if (a.spread && s < kCUs / 8 && whole >= kCUs / 8) s = kCUs / 8 - 1 - s;
   if (s < whole) {
-    pair = s / gz * 8 + x;
-    p.z = s % gz;
+    const int W = P / 8;
+    pair = (a.spread ? s % W : s / gz) * 8 + x;
+    p.z = a.spread ? s / W : s % gz;
   } else {
     const int rest = P % 8 * gz, L = (rest + 7) / 8, r = x * L + (s - whole);
     if (s - whole >= L || r >= rest) return false;
@@ -1015,6 +1025,7 @@ static int attn_grid(AttnArgs& a, int B, int slots) {
   a.rows_per_wg = rows_per_wg(nblk, a.Hh, B, slots);
   a.gz = (nblk + a.rows_per_wg - 1) / a.rows_per_wg * a.vheads;
   const int P = B * (a.Hh / a.vheads);
+  a.spread = a.rows_per_wg <= 3 && (long long)P * a.gz <= slots;
   return 8 * (P / 8 * a.gz + (P % 8 * a.gz + 7) / 8);
 }
 

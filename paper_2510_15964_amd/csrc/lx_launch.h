@@ -41,6 +41,7 @@ struct AttnArgs {
   int rows_per_wg;   // rows of the mask per workgroup, set by the launcher
   int vheads;        // consecutive heads whose rows one group of workgroups shares, set by the launcher
   int B, gz;         // batch entries, workgroups of a group, set by the launcher
+  int spread;        // 1: the workgroups of an XCD by their length (pair_work), set by the launcher
 };
 
 hipError_t launch_compact(const uint8_t*, int, int, int, long long, long long, long long, int*, int*,

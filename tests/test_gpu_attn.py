@@ -357,3 +357,26 @@ def test_token_strides_beyond_32_bit_offsets(lx, D, dtype):
         assert torch.isfinite(a).all() and torch.equal(a, b)
     del buf, wide
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("B,Hh,S,D,kw", [
+    (4, 8, 512, 64, dict(density=0.4)),                   # one pair per XCD, 32 workgroups each
+    (4, 12, 512, 128, dict(density=1.0)),                 # and a rest of four pairs
+    (3, 10, 320, 64, dict(density=0.5, causal=False)),    # 15 pairs: a rest of seven, runs that cross pairs
+    (2, 5, 4096, 64, dict(density=0.05)),                 # a head per pair
+])
+def test_order_of_the_workgroups(lx, B, Hh, S, D, kw):
+    """Few rows per workgroup (an XCD's workgroups ordered by their length) against eight (pair after pair): same bits."""
+    c = inputs.attn_blocks(B, Hh, S, D, seed=B * S + Hh, dtype="bf16", **kw)
+    out = []
+    for rows in (8, 1, 2, 3):
+        print(B, Hh, S, D, "rows per workgroup", rows, flush=True)
+        lx.lx_attn_set_rows_per_workgroup(rows)
+        try:
+            out.append(run_gpu(lx, c))
+        finally:
+            lx.lx_attn_set_rows_per_workgroup(0)
+        for k in ("O", "dQ", "dK", "dV"):
+            assert np.isfinite(out[-1][k]).all()
+            assert np.array_equal(out[-1][k], out[0][k]), (rows, k)
+        assert np.array_equal(out[-1]["LSE"], out[0]["LSE"])
