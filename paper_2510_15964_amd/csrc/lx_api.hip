@@ -413,22 +413,20 @@ static lx_status ffn_bwd_dx_impl(lx_dtype dt, int32_t T, int32_t d, int32_t F, i
   return e == hipSuccess ? LX_OK : LX_ERR_RUNTIME;
 }
 
-// (Both queries keep the sizes of a layout that also held partial sums of U and G and B^T, which are not
-// stored any more: programs may have sized their buffers once.)
+// Nothing is stored in the forward workspace any more.  Its size stays that of fp32 partial sums of U, which callers
+// may have counted on: a call with less, or without a workspace, is still refused.
 size_t lx_sparse_ffn_lora_fwd_workspace_bytes(int32_t T, int32_t d) {
   if (T < 64 || d < 64) return 256;
   const int split = lora_u_split(T / 64, d);
   return 256 + (split > 1 ? round256((size_t)split * T * 64 * 4) : 0);
 }
 
+// dZ, A^T, G and the partial sums of dA and dB, in this order.
 size_t lx_sparse_ffn_lora_bwd_workspace_bytes(int32_t T, int32_t d, int32_t F, int32_t nnz_cap) {
   if (T < 64 || d < 64 || F < 64) return 0;
-  const int sa = lora_da_split(T / 64, d), sb = lora_db_split(T / 64, F), sg = lora_g_split(T / 64);
-  return act_bytes(LX_BF16, 64, 64, nnz_cap) + round256((size_t)64 * F * 2) +
-         round256((size_t)d * 64 * 2) + round256((size_t)T * 64 * 2) +
-         (sg > 1 ? round256((size_t)sg * T * 64 * 4) : 0) +
-         (sa > 1 ? round256((size_t)sa * 64 * d * 4) : 0) +
-         (sb > 1 ? round256((size_t)sb * F * 64 * 4) : 0);
+  const int sa = lora_da_split(T / 64, d), sb = lora_db_split(T / 64, F);
+  return act_bytes(LX_BF16, 64, 64, nnz_cap) + round256((size_t)d * 64 * 2) + round256((size_t)T * 64 * 2) +
+         (sa > 1 ? round256((size_t)sa * 64 * d * 4) : 0) + (sb > 1 ? round256((size_t)sb * F * 64 * 4) : 0);
 }
 
 static lx_status check_lora(lx_dtype dt, int32_t T, int32_t d, int32_t F, int32_t tile_t,

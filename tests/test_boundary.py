@@ -306,3 +306,13 @@ def test_attn_token_stride_of_any_length_is_accepted(lxmod):
             assert L._lib.lx_sparse_attn_bwd_dx(dt, 1, 1, 128, 64, 0.125, 1, None, FAKE, FAKE, FAKE, FAKE, FAKE,
                                                 st, C.byref(bl), C.byref(bl), 1, None, FAKE, FAKE, FAKE, FAKE,
                                                 need, None) == L.LX_ERR_INVALID_ARG
+
+
+def test_lora_backward_workspace_is_what_the_call_uses(lxmod):
+    """dZ blocks, A^T, G, and fp32 partial sums of dA over ranges of token tiles per 64 columns and of dB per neuron
+    block, as many ranges as fill 256 / 512 workgroups (at most 32 / 16, none for one range)."""
+    L = lxmod
+    for T, d, F, nnz, sa, sb in ((4096, 2048, 8192, 934, 8, 4), (64, 64, 64, 1, 1, 1), (16384, 16384, 65536, 7, 1, 1),
+                                 (512, 128, 1024, 128, 8, 8)):
+        want = nnz * 8192 + d * 128 + T * 128 + (sa > 1) * sa * 256 * d + (sb > 1) * sb * F * 256
+        assert L.lx_sparse_ffn_lora_bwd_workspace_bytes(T, d, F, nnz) == want, (T, d, F)
