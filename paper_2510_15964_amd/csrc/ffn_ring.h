@@ -26,26 +26,13 @@ __device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
 // already points at this lane's (row, swizzled segment); offB / offA are the element offsets of
 // the current K-step for the shared rows (the first NSH instructions of a wave) and the weight
 // rows.
-// With `alt` (wave-uniform) the source of instruction u is alt_ptr(u) instead: a step whose
-// operands live in other buffers with another row stride (the LoRA branch).  alt_ptr is
-// evaluated only then, so such a step costs no registers in the steady state.
-template <int NISS, int NSH, class AltPtr>
-__device__ __forceinline__ void issue_stage(uint16_t* stage, const uint16_t* const (&src)[NISS],
-                                            AltPtr alt_ptr, bool alt, long long offB,
+template <int NISS, int NSH>
+__device__ __forceinline__ void issue_stage(uint16_t* stage, const uint16_t* const (&src)[NISS], long long offB,
                                             long long offA) {
   const uint32_t base = lds_addr(stage) + (threadIdx.x / kWave) * 1024;
-  if (alt) {
 #pragma unroll
-    for (int u = 0; u < NISS; ++u) dma16(alt_ptr(u), base + u * (kFW * 1024));
-  } else {
-#pragma unroll
-    for (int u = 0; u < NISS; ++u)
-      dma16(src[u] + (u < NSH ? offB : offA), base + u * (kFW * 1024));
-  }
+  for (int u = 0; u < NISS; ++u) dma16(src[u] + (u < NSH ? offB : offA), base + u * (kFW * 1024));
 }
-struct NoAlt {
-  __device__ __forceinline__ const uint16_t* operator()(int) const { return nullptr; }
-};
 
 // Pipeline over nsteps K-steps through a ring of NST stages: while step s is multiplied, the
 // DMA of steps s+1 .. s+NST-1 is in flight (what bounds these kernels is how many bytes a CU
@@ -69,16 +56,14 @@ __device__ __forceinline__ void wait_tail(int y) {
 }
 
 // step(stage pointer) is the multiplication of one landed stage; a stage holds SE elements.
-// offs(s, offB, offA) yields the element offsets of step s and returns whether the step takes
-// its operands from alt_ptr(u).
-template <int NST, int NISS, int SE, int NSH = 1, class AltPtr, class Offs, class Step>
-__device__ __forceinline__ void run_ring_of(int nsteps, const uint16_t* const (&src)[NISS],
-                                            AltPtr alt_ptr, Offs offs, uint16_t* ring, Step step) {
+template <int NST, int NISS, int SE, int NSH = 1, class Offs, class Step>
+__device__ __forceinline__ void run_ring_of(int nsteps, const uint16_t* const (&src)[NISS], Offs offs, uint16_t* ring,
+                                            Step step) {
   static_assert(NST >= 2 && NISS * (NST - 2) < 64, "ring depth");
-  long long ob, oa;
   auto issue = [&](int s, int stage) {
-    const bool alt = offs(s, ob, oa);
-    issue_stage<NISS, NSH>(ring + stage * SE, src, alt_ptr, alt, ob, oa);
+    long long ob, oa;
+    offs(s, ob, oa);
+    issue_stage<NISS, NSH>(ring + stage * SE, src, ob, oa);
   };
 #pragma unroll
   for (int p = 0; p < NST - 1; ++p)

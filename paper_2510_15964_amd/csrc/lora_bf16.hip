@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kThreads) void lora_nt_tile_kernel(
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
   run_ring_of<kPairStages, 2, kPairElems>(
-      nsteps, src, NoAlt(),
+      nsteps, src,
       [=](int s, long long& ob, long long& oa) {
         if (MODE == 0) {
           ob = oa = (long long)s * kBK;
@@ -260,7 +260,6 @@ __global__ __launch_bounds__(kThreads) void lora_nt_tile_kernel(
           ob = ((long long)(rs + s) * gt + i % gt) * 4096;
           oa = (long long)col_idx[rs + s] * 4096;
         }
-        return false;
       },
       ring,
       [&](const uint16_t* stage) {
@@ -369,11 +368,10 @@ __device__ __forceinline__ void lora_tn(const TnArgs& args, int x, int y, const 
   auto step = [&](const uint16_t* stage) { tn_step<DT>(lds_addr(stage), lo, acc); };
   if (MODE == 1) {
     run_ring_of<kPairStages, 2, kPairElems>(
-        i_hi - i_lo, src, NoAlt(),
+        i_hi - i_lo, src,
         [=](int s, long long& ob, long long& oa) {
           ob = (long long)(i_lo + s) * 4096;
           oa = (long long)(i_lo + s) * 64 * ldq;
-          return false;
         },
         ring, step);
   } else {
@@ -409,11 +407,10 @@ __device__ __forceinline__ void lora_tn(const TnArgs& args, int x, int y, const 
     }
     __syncthreads();
     run_ring_of<kPairStages, 2, kPairElems>(
-        __builtin_amdgcn_readfirstlane(total), src, NoAlt(),
+        __builtin_amdgcn_readfirstlane(total), src,
         [&](int s, long long& ob, long long& oa) {
           ob = s_p[s];
           oa = s_q[s];
-          return false;
         },
         ring, step);
   }

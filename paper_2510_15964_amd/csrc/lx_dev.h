@@ -89,7 +89,6 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-#define LX_AS1 __attribute__((address_space(1)))
 #define LX_AS3 __attribute__((address_space(3)))
 
 // LDS reads by byte address.  lds_read8_tr is the transposing read (ds_read_b64_tr_b16): within

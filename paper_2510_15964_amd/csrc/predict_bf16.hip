@@ -52,10 +52,9 @@ __global__ __launch_bounds__(kThreads) void predict_bf16(
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
   run_ring_of<kNSt, kNIss, kSE>(
-      K / kBK, src, NoAlt(),
+      K / kBK, src,
       [](int s, long long& ob, long long& oa) {
         ob = oa = (long long)s * kBK;
-        return false;
       },
       ring,
       [&](const uint16_t* stage) {
@@ -126,10 +125,9 @@ __global__ __launch_bounds__(kThreads) void predict_half_bf16(
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
   run_ring_of<kNSt, kNIss, kSE>(
-      K / (2 * kBK), src, NoAlt(),
+      K / (2 * kBK), src,
       [](int s, long long& ob, long long& oa) {
         ob = oa = (long long)s * (2 * kBK);
-        return false;
       },
       ring,
       [&](const uint16_t* stage) {
