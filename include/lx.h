@@ -67,7 +67,11 @@ typedef enum { LX_F32 = 0, LX_BF16 = 1, LX_F16 = 2 } lx_dtype;
  *               column list used by the backward pass)
  * nnz_cap is a host-known upper bound on the number of active blocks (rows*cols
  * if nothing better is known); it sizes H_act and bounds launch grids, because
- * the true count lives only on the device.  If row_ptr counts more entries
+ * the true count lives only on the device.  It also informs the choice of tiles;
+ * a bound several times the true count costs the FFN calls little with one list
+ * row or with rows*cols, up to some 40 % of the first product with a bound in
+ * between and a row per tile or per group of tiles; calls with a LoRA branch
+ * choose by the bound alone.  If row_ptr counts more entries
  * than nnz_cap (a bound that was too small), every call ignores the entries
  * after the first nnz_cap in list order: the results are those of the
  * truncated list and nothing outside the stated buffers is read or written.
@@ -137,7 +141,7 @@ lx_status lx_mask_compact_pair(const uint8_t* mask, int32_t batch, int32_t rows,
 
 /*
  * Several independent compactions in ONE launch (all masks of a layer step: the
- * FFN token-tile masks and both attention lists), one workgroup per job.  Each
+ * FFN token-tile masks and both attention lists).  Each
  * job has the meaning of one lx_mask_compact call.  `jobs` is a HOST array of
  * 1..8 entries holding DEVICE pointers; it is copied into the launch.
  */
@@ -228,16 +232,17 @@ size_t lx_sparse_ffn_bwd_workspace_bytes(lx_dtype dt, int32_t T, int32_t d, int3
 
 /*
  * Optional extra workspace of the two FFN calls (16-bit types).  With ONE list row for all token
- * tiles the second product of a pass (Y, dX) runs as (group of token tiles) x (256 output
+ * tiles the second product of a pass (Y, dX) runs as (group of token tiles) x (64 to 256 output
  * columns) units, all equally long; when they make whole rounds of workgroups plus a small rest,
  * that rest would keep a fraction of the chip busy for a full round.  Given this many bytes
  * BEYOND what lx_sparse_ffn_fwd_workspace_bytes / lx_sparse_ffn_bwd_workspace_bytes return (the
- * same pointer, a larger workspace_bytes), the calls cut the lists of the rest's units into
- * pieces that fill the last round and add the pieces' fp32 partial sums in a fixed order
+ * same pointer, a larger workspace_bytes), the calls may cut the lists of the rest's units into
+ * 2 to 4 pieces that fill the last round and add the pieces' fp32 partial sums in a fixed order
  * (reproducible; the outputs of those units then differ in the last bit from the unsplit sum).
  * Returns 0 where no split would be made (several list rows, units that fill their rounds, lists
- * whose bound bl->nnz_cap is too short to cut); a workspace without the extra bytes is always
- * valid and gives the unsplit sums.
+ * whose bound bl->nnz_cap is too short to cut, and wherever it would not pay); a workspace without
+ * the extra bytes is always valid and gives the unsplit sums.  The calls with a LoRA branch never
+ * cut lists.
  */
 size_t lx_sparse_ffn_split_workspace_bytes(lx_dtype dt, int32_t T, int32_t d, int32_t tile_t,
                                            const lx_blocklist* bl);
@@ -291,8 +296,8 @@ lx_status lx_sparse_ffn_bwd_dx(lx_dtype dt, int32_t T, int32_t d, int32_t F, int
  *   U = X A_pad^T [T,64];  H_ij = ReLU(X_i W_up_j^T + U_i B_pad_j^T);  Y_i = sum_j H_ij W_down_j^T
  *   U      out [T,64], needed by the backward call
  *   H_act  out, compact activations as in lx_sparse_ffn_fwd (required)
- *   workspace  >= lx_sparse_ffn_lora_fwd_workspace_bytes(T, d): fp32 partial sums of U when the
- *              product is split over K to fill the chip (few token tiles)
+ *   workspace  >= lx_sparse_ffn_lora_fwd_workspace_bytes(T, d) (required; the present kernels
+ *              store nothing there)
  * Backward:
  *   dZ_ij = (dY_i W_down[:, j]) (.) [H_ij > 0];   G = sum_j dZ_ij B_pad_j  [T,64]
  *   dX_i = sum_j dZ_ij W_up_j + G_i A_pad
@@ -453,22 +458,21 @@ lx_status lx_probe_stream_copy(const void* src, void* dst, size_t bytes, void* s
 lx_status lx_attn_set_rows_per_workgroup(int32_t rows);
 
 /*
- * Tuning knob of the 16-bit FFN calls: how many token tiles one workgroup
- * multiplies with the weight rows it has staged.  Two or four tiles (possible
- * when list rows are shared by a multiple of that many consecutive tiles) cut
- * the weight bytes moved per product to 0.6 / 0.4 but also the number of
- * workgroups to a half / a quarter, so they pay for dense or large layers and
- * lose where one tile per workgroup just fills the chip.  tiles = 0 (the
- * default) lets the library choose: the largest group with which the work
- * items -- tile groups x groups of four list entries, counted from the list's
- * capacity nnz_cap -- still number at least one per CU; 1, 2 or 4 asks for at most that many for all later calls
- * of the calling host thread (per-thread setting; the library falls back to 2
- * or 1 where the list rows are not shared accordingly, and always uses 1 in the
- * LoRA calls).  The value governs the second product of a pass; the first
- * product takes that group size or a smaller one, whichever makes its rounds
- * of workgroups (one work item per CU) cheapest by the list's capacity.
- * Results are bit-identical for every value.  Returns LX_ERR_INVALID_ARG for
- * other values.
+ * Tuning knob of the 16-bit FFN calls, those with a LoRA branch among them: how
+ * many token tiles one workgroup multiplies with the weight rows it has staged.
+ * A workgroup takes 1, 2 or 4 token tiles by 1, 2 or 4 groups of 64 weight rows
+ * (list entries in the first product of a pass, output columns in the second);
+ * wide tiles move fewer bytes per product, narrow ones give the chip more
+ * workgroups.  tiles = 0 (the default) lets the library choose both numbers for
+ * each product by a model of their time (token tiles can share a workgroup when
+ * list rows are shared by a multiple of that many consecutive tiles); 1, 2 or 4
+ * asks for that many token tiles for all later calls of the calling host thread
+ * (per-thread setting; 2 or 1 where the list rows are not shared accordingly).
+ * The value does not change the result: every output element sums the same
+ * products in the same order.  The exception are calls with room for partial
+ * sums (lx_sparse_ffn_split_workspace_bytes): which units have their lists cut
+ * depends on the tile, and the outputs of those differ in the rounding of
+ * fp32 sums.  Returns LX_ERR_INVALID_ARG for other values.
  */
 lx_status lx_ffn_set_token_tiles_per_workgroup(int32_t tiles);
 

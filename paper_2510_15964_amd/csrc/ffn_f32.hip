@@ -18,12 +18,14 @@
 // The detour over LDS is for the loads: a lane's row is fixed by the MFMA's layout, and a load of 16
 // bytes from each of 32 rows occupies the CU's memory pipeline for 64 clocks where eight rows of 128
 // bytes take 16.
-// Measured at 512 tokens, 768 -> 3072 -> 768, 30 % of 32 x 32 blocks (460 blocks): 15-17 us per
+// Measured at 512 tokens, 768 -> 3072 -> 768, 30 % of 32 x 32 blocks (460 blocks): 16-20 us per
 // product, of which 6 us are the MFMAs (0.73 GFLOP, at most two blocks per CU) and about 7 the launch
 // and the three dependent loads in front of the first operand; operands straight into registers 20-22,
-// 2 x 2 register tiles on the vector unit 48-52.  The up-projection, whose signs decide the ReLU gate,
-// adds its terms one by one in ascending order (21 us): a sum in another order would flip the gate of
-// activations within rounding of zero.
+// 2 x 2 register tiles on the vector unit 58-62.  The up-projection, whose signs decide the ReLU gate,
+// adds its terms one by one in ascending order (23 us): a sum in another order would flip the gate of
+// activations within rounding of zero.  With 64 x 64 blocks one workgroup fits a CU (128 KB of LDS: eight
+// wavefronts of two stages, four of four in the up-projection): the same layer 20-24 us per product, 4096 tokens, 2048 -> 8192 (30 %, 2469 blocks) 450-550 us; on the
+// vector unit 88-92 and 1008-1077.
 #include "ffn_ring.h"
 
 namespace lx {

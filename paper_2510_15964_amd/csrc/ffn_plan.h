@@ -20,10 +20,11 @@ namespace lx {
 // (2 x 2 tiles, 4096 tokens, 14 blocks, K = 2048, 224 workgroups: 25 -> 21 us).
 enum TileId { kT44, kT24, kT22, kT22Deep, kT14, kT14Deep, kT12, kT11, kT11Many, kTiles };
 // What a launch of a tile costs, in us: `round` per round of workgroups (finding the item, filling the
-// ring, epilogue) and step[q - 1] per step with q workgroups on a CU.  Fitted to measured launches of
-// every tile at 22 shapes (64 - 8192 tokens, d 576 - 5120, 6 - 320 listed blocks, lists shared and per
-// tile; rms of the fit 6 - 18 %); at those shapes the tile that the model picks is within 1.5 % of the
-// fastest one on average, 7 % at worst.
+// ring, epilogue) and step[q - 1] per step with q workgroups on a CU.  Fitted to measured launches (64 - 8192 tokens,
+// d 576 - 5120, 6 - 320 listed blocks, lists shared and per tile).  Checked at 26 shapes, every tile of both products
+// (profiles/ffn_tile_sweep.txt): model to measured 0.99 in the geometric mean, rms 17 %, and the tile that is taken is
+// 1 % slower than the fastest one on average, 10 % at worst (4096 tokens, d = 2048, a list row per four tiles: 33 us by
+// 2 x 4 tiles, 30 by 2 x 2).
 struct TileInfo {
   int tm, tn, resident;
   float round, step[3];

@@ -82,7 +82,7 @@ hipError_t launch_ffn_bf16(int dt, int pass, int Tt, int gt, int Fb, int d, int 
 // nnz_cap entries for all Tt token tiles, cuts the lists of its last round of workgroups (0: never)
 size_t ffn_dsd_split_bytes(int Tt, int d, int nnz_cap);
 // Ranges that the low-rank products of the LoRA branch are cut into, added in a fixed order: U = X A^T over K
-// and G = dZ B over the list entries among the wavefronts of a workgroup; dB over ranges of token
+// and G = dZ B over the list entries among the wavefronts of a workgroup (few token tiles only); dB over ranges of token
 // tiles per neuron block and dA over ranges of token tiles per 64-column chunk among workgroups.
 inline int lora_clamp(int s, int hi) { return s < 1 ? 1 : (s > hi ? (hi < 1 ? 1 : hi) : s); }
 inline int lora_u_split(int Tt, int d) {
@@ -138,6 +138,6 @@ hipError_t launch_probe_copy(const void* src, void* dst, long long units16, hipS
 hipError_t launch_attn_fwd_f32(int D, int B, const AttnArgs& a, hipStream_t st);
 hipError_t launch_attn_bwd_f32(int D, int B, const AttnArgs& a, hipStream_t st);
 hipError_t set_attn_rows_per_wg(int r);   // 0 = automatic
-hipError_t set_ffn_tiles_per_wg(int n);   // 0 = automatic, 1, 2
+hipError_t set_ffn_tiles_per_wg(int n);   // 0 = automatic, 1, 2, 4
 
 }  // namespace lx
