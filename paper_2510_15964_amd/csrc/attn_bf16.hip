@@ -1026,7 +1026,8 @@ static int attn_grid(AttnArgs& a, int B, int slots) {
   a.rows_per_wg = rows_per_wg(nblk, a.Hh, B, slots);
   a.gz = (nblk + a.rows_per_wg - 1) / a.rows_per_wg * a.vheads;
   const int P = B * (a.Hh / a.vheads);
-  a.spread = a.rows_per_wg <= 3 && (long long)P * a.gz <= slots;
+  const long long n = (long long)P * a.gz;
+  a.spread = a.rows_per_wg <= 3 && n > kCUs && n <= slots;
   return 8 * (P / 8 * a.gz + (P % 8 * a.gz + 7) / 8);
 }
 
