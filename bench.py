@@ -9,12 +9,12 @@ outside it.
 
 Workloads (recipes in paper_2510_15964_amd/inputs.py):
   opt1.3b_layer   default.  An OPT-1.3B-shaped layer over 8 x 1024 tokens:
-                  attention = configs[2] (30 % of causal blocks), FFN =
-                  configs[1]'s shape and recipe (planted ReLU support, ~10 %
-                  blocks, a list per 64-token tile) applied to the 8192 tokens
+                  attention over 30 % of the causal blocks, FFN with
+                  planted ReLU support (~10 % of the
+                  blocks, a list per 64-token tile) over the 8192 tokens
                   in one call: 8 kernel launches per step.
   opt1.3b_layer_twocalls  the same layer with the FFN as two X[4096,2048] calls
-                  (configs[1]'s own token count) that share the weights: 12 launches.
+                  that share the weights: 12 launches.
   The variants below keep the two-call FFN, the shape their parity tests cover:
   opt1.3b_layer_shared    the FFN masks predicted on the
                   device every step (MLP predictor, one list for all tokens of
@@ -30,12 +30,12 @@ Workloads (recipes in paper_2510_15964_amd/inputs.py):
                   every call moves the listed neuron blocks to the device first (Sec. VII-B);
                   opt1.3b_layer_hostw_overlap = the same with the transfers on a second stream
                   under the attention kernels.
-  config4         OPT-6.7B-shaped layer (configs[3]).
-  config5:<rho>   OPT-13B-shaped layer at block density rho (configs[4]);
+  config4         OPT-6.7B-shaped layer.
+  config5:<rho>   OPT-13B-shaped layer at block density rho;
                   config5:<rho>:shared = the same with one FFN list for all token tiles
-                  and four token tiles per FFN workgroup (the dense path at rho = 1).
+                  (the dense path at rho = 1).
 
-Prints ONE JSON line.  `--sweep FILE` additionally runs the configs[4] density
+Prints ONE JSON line.  `--sweep FILE` additionally runs the OPT-13B density
 sweep and writes one JSON line per density to FILE.
 """
 from __future__ import annotations
@@ -69,13 +69,13 @@ def log(*a):
 def make_workload(name: str):
     from paper_2510_15964_amd import inputs
     if name == "opt1.3b_layer":
-        # attention = configs[2]; FFN = configs[1]'s shape and planted-support recipe over the
+        # attention over 30 % of the causal blocks; FFN shape and planted-support recipe over the
         # layer's 8 x 1024 = 8192 tokens in ONE call (128 token tiles, a list per tile)
         f = inputs.ffn_planted_support(8192, 2048, 8192, 64, 64, 0.5, 4.0, seed=2000)
         a = inputs.config3_attn()
         ffn_calls = 1
     elif name == "opt1.3b_layer_twocalls":
-        # the same layer with the FFN as two calls of configs[1]'s own 4096 tokens that share the
+        # the same layer with the FFN as two calls of 4096 tokens that share the
         # frozen weights: four more launches per step, and half as many token tiles share an XCD's L2
         f = inputs.ffn_planted_support(8192, 2048, 8192, 64, 64, 0.5, 4.0, seed=2000)
         a = inputs.config3_attn()
@@ -661,10 +661,9 @@ def run(workload: str, steps: int, warmup: int, with_cpu: bool, cache: str = "wa
 
 
 def density_efficiency(results):
-    """E(rho) = rho * t(dense) / t(rho) from whole-step times of configs[4] workloads (Sec. VII-C:
+    """E(rho) = rho * t(dense) / t(rho) from whole-step times of the OPT-13B workloads (Sec. VII-C:
     operator time against density): `results` maps workload name -> ms per step.  Two references:
-    the dense PATH (rho = 1 with one list for all token tiles and four token tiles per workgroup,
-    what a dense layer would run) and the sparse kernels themselves at rho = 1."""
+    the dense PATH (rho = 1 with one list for all token tiles, what a dense layer would run) and the sparse kernels themselves at rho = 1."""
     dense_path = results.get("config5:1.0:shared")
     dense_lists = results.get("config5:1.0")
     out = {}
@@ -694,9 +693,9 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-extras", action="store_true",
                     help="skip the legs next to the headline: measured peaks, the cache-cold "
-                         "variant and the density-efficiency runs of configs[4]")
+                         "variant and the density-efficiency runs of the OPT-13B layer")
     ap.add_argument("--sweep", metavar="FILE", default=None,
-                    help="also run the configs[4] density sweep, one JSON line per density into FILE")
+                    help="also run the OPT-13B density sweep, one JSON line per density into FILE")
     args = ap.parse_args()
     if args.gpus != 1:
         raise SystemExit("bench.py: this build is single-GPU; run with --gpus 1 "
@@ -725,14 +724,14 @@ def main():
             res["cache_cold"]["roofline_frac"] = cold["roofline"]["frac"]
             log(f"cache-cold: {cold['ms_per_step']:.3f} ms/step")
         if args.workload == DEFAULT_WORKLOAD:
-            # the same layer with the FFN as two calls of configs[1]'s own 4096 tokens
+            # the same layer with the FFN as two calls of 4096 tokens
             two = run("opt1.3b_layer_twocalls", max(args.steps // 2, 5), 2, False, "warm", peaks)
             res["ffn_as_two_calls"] = {k: two[k] for k in ("value", "ms_per_step", "ms_per_step_median",
                                                           "launches_per_step")}
             res["ffn_as_two_calls"]["roofline"] = {k: two["roofline"][k] for k in ("kernel", "bound", "frac",
                                                                                   "avg_launch_us")}
             log(f"FFN as two calls of 4096 tokens: {two['ms_per_step']:.3f} ms/step")
-        # density efficiency at the benchmark spec's 10 % and 30 % (configs[4] shapes), short runs
+        # density efficiency at 10 % and 30 % (OPT-13B shapes), short runs
         ms = {}
         for wl in ("config5:1.0:shared", "config5:0.1", "config5:0.3", "config5:0.1:shared",
                    "config5:0.3:shared"):

@@ -291,8 +291,8 @@ def attn_patterns(B, Hh, S, D, seed, dtype="bf16", causal=True, probs=None, head
 
 
 def config3_patterns(seed=3100):
-    """configs[2]'s shape with per-head patterns drawn so that the mean density inside the
-    causal region is about 30 %, as in configs[2]."""
+    """The OPT-1.3B attention shape with per-head patterns drawn so that the mean density inside the
+    causal region is about 30 %, as with the dense masks."""
     return attn_patterns(8, 32, 1024, 64, seed, probs=(0.5, 0.08, 0.27, 0.03, 0.05, 0.05, 0.02, 0.0))
 
 

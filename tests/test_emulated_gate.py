@@ -1,6 +1,6 @@
 """CPU: what an ideal 16-bit pipeline loses against the fp64 oracle (tests/emulate16.py), on inputs
 of the GPU parity tests.  These figures are the reason the element-wise error with an rms floor is
-not gated at the benchmark spec's 2e-2 for 16-bit runs, and they are what the GPU tests gate it at
+not gated at 2e-2 for 16-bit runs, and they are what the GPU tests gate it at
 instead (at most util.EMUL_FACTOR times the emulated figure of the same input, per tensor)."""
 import numpy as np
 import pytest
@@ -53,7 +53,7 @@ def test_attention_large_score_range_frobenius(oracle):
 
 
 def test_ffn_ideal_pipeline_on_planted_support(oracle):
-    """Planted-support FFN input (the recipe of configs[1] at a small size): the gate channels make
+    """Planted-support FFN input (at a small size): the gate channels make
     rows of dX differ in scale, so the ideal pipeline's rms-floored error is a multiple of a bf16
     roundoff (2^-9) although its max-norm and Frobenius errors are a fraction of their gates."""
     c = inputs.ffn_planted_support(256, 256, 1024, 64, 64, 0.5, 4.0, seed=51)

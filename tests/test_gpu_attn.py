@@ -175,7 +175,7 @@ def test_unused_key_blocks_are_never_read(lx, oracle):
 
 
 def test_config3_full_size_sampled_heads(lx, oracle):
-    """configs[2] at full size in the benchmark's launch configuration; the
+    """The OPT-1.3B attention at full size in the benchmark's launch configuration; the
     oracle checks sampled (batch, head) pairs, which are independent."""
     c = inputs.config3_attn()
     got = run_gpu(lx, c)
@@ -192,7 +192,7 @@ def test_config3_full_size_sampled_heads(lx, oracle):
 
 
 def test_config4_shape_sampled_heads(lx, oracle):
-    """configs[3] attention half (head size 128, 2048 tokens), reduced batch."""
+    """OPT-6.7B attention half (head size 128, 2048 tokens), reduced batch."""
     c = inputs.attn_blocks(1, 4, 2048, 128, 0.25, seed=4000, dtype="bf16")
     got = run_gpu(lx, c)
     for h in (0, 3):
@@ -271,7 +271,7 @@ def test_blocks_above_the_diagonal_of_a_causal_mask(lx, oracle, D):
     (dict(B=2, Hh=4, S=128, D=128, density=0.5, head_keep=0.5), 84),
     (dict(B=3, Hh=2, S=192, D=64, density=0.4, mask_batch=3), 85),
     (dict(B=1, Hh=2, S=128, D=64, density=0.0), 86),
-    (dict(B=1, Hh=2, S=1024, D=64, density=0.3), 87),          # configs[2]'s sequence length
+    (dict(B=1, Hh=2, S=1024, D=64, density=0.3), 87),          # the benchmark's sequence length
 ])
 def test_fp32_attention(lx, oracle, kw, seed):
     """LX_F32 attention (the correctness configuration): forward and backward within the fp32 gates

@@ -1,5 +1,5 @@
-"""GPU parity at the launch shapes of the benchmark's large configurations (configs[3]: OPT-6.7B,
-configs[4]: OPT-13B density sweep) and of the benchmark's one-call layer: the full-size launch
+"""GPU parity at the launch shapes of the large configurations (OPT-6.7B,
+OPT-13B density sweep) and of the benchmark's one-call layer: the full-size launch
 runs on the GPU, the oracle computes sampled token rows (FFN) or sampled heads (attention).
 
 FFN sampling.  Token rows are independent in both passes (the ReLU gate is element-wise), and the
@@ -138,20 +138,20 @@ ROWS8 = (0, 9, 18, 27, 36, 45, 54, 63)     # both 32-row halves, every residue o
 
 
 def test_config4_ffn_full_size_sampled_rows(lx, oracle):
-    """configs[3] FFN: 128 token tiles in one call, d = 4096, F = 16384 (256 blocks per row)."""
+    """OPT-6.7B FFN: 128 token tiles in one call, d = 4096, F = 16384 (256 blocks per row)."""
     c = inputs.config4_ffn()
     check_ffn_sampled(lx, oracle, c, sample_tiles(c["mask"], (63, 64, 100)), ROWS8, label="config4")
 
 
 def test_onecall_layer_ffn_full_size_sampled_rows(lx, oracle):
-    """The benchmark's one-call layer: configs[1]'s recipe over 8192 tokens (128 token tiles)."""
+    """The benchmark's one-call layer: the planted-support recipe over 8192 tokens (128 token tiles)."""
     c = inputs.ffn_planted_support(8192, 2048, 8192, 64, 64, 0.5, 4.0, seed=2000)
     check_ffn_sampled(lx, oracle, c, sample_tiles(c["mask"], (63, 64, 97)), ROWS8, label="onecall")
 
 
 @pytest.mark.parametrize("rho,rows", [(0.05, ROWS8), (0.3, (0, 27, 36, 63)), (1.0, (5, 58))])
 def test_config5_ffn_full_size_sampled_rows(lx, oracle, rho, rows):
-    """configs[4] FFN at three densities: d = 5120, F = 20480 (320 blocks per row), a list per tile."""
+    """OPT-13B FFN at three densities: d = 5120, F = 20480 (320 blocks per row), a list per tile."""
     c = inputs.config5_ffn(rho)
     tiles = sample_tiles(c["mask"], (31,))[:3 if rho >= 1.0 else 5]
     check_ffn_sampled(lx, oracle, c, tiles, rows, label=f"config5 rho={rho}")
@@ -160,9 +160,9 @@ def test_config5_ffn_full_size_sampled_rows(lx, oracle, rho, rows):
 @pytest.mark.parametrize("rho,rows,tiles_per_wg", [(0.1, ROWS8, 0), (0.3, (0, 27, 36, 63), 0), (0.3, (0, 27, 36, 63), 4),
                                                    (1.0, (5, 58), 4)])
 def test_config5_ffn_shared_list_several_tiles_per_workgroup(lx, oracle, rho, rows, tiles_per_wg):
-    """configs[4] FFN with ONE list row for all token tiles: the benchmark's config5:RHO:shared
+    """OPT-13B FFN with ONE list row for all token tiles: the benchmark's config5:RHO:shared
     workloads (the dense path at rho = 1), with the library's own choice of token tiles per
-    workgroup (0: two at 10 %, four at 30 %) and with four asked for."""
+    workgroup (0: two) and with four asked for."""
     c = inputs.config5_ffn(rho)
     c["mask"] = np.repeat(c["mask"][:1], c["mask"].shape[0], axis=0)
     check_ffn_sampled(lx, oracle, c, (0, 30, 63), rows, shared=True, tiles_per_wg=tiles_per_wg,
@@ -170,7 +170,7 @@ def test_config5_ffn_shared_list_several_tiles_per_workgroup(lx, oracle, rho, ro
 
 
 def test_config5_dense_path_with_split_lists(lx, oracle):
-    """The benchmark's dense path (configs[4] at density 1, one list row, four token tiles per
+    """The benchmark's dense path (OPT-13B FFN at density 1, one list row, four token tiles per
     workgroup) with the extra workspace: the 320 (tile group, column chunk) units of the second
     product are 256 whole ones and 64 whose lists are cut into four pieces (fp32 partial sums
     added in order).  Tiles 0 and 30 lie in the whole units, tile 63 in the split ones."""
@@ -212,7 +212,7 @@ def test_more_than_64_token_tiles_small_d(lx, oracle, Tt, d, F, density, seed):
 
 
 def test_config5_attention_full_size_sampled_heads(lx, oracle):
-    """configs[4] attention half at full size (2 x 40 heads x 2048 tokens, head size 128) at 30 %
+    """OPT-13B attention half at full size (2 x 40 heads x 2048 tokens, head size 128) at 30 %
     density; the oracle checks sampled (batch, head) pairs."""
     from test_gpu_attn import check, run_gpu, run_oracle
     c = inputs.config5_attn(0.3)

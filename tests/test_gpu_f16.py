@@ -48,7 +48,7 @@ def test_ffn_f16_bias(lx, oracle):
 
 
 def test_ffn_f16_bench_widths(lx, oracle):
-    """OPT-1.3B widths, planted-support recipe of configs[1] with half-precision rounding, 256
+    """OPT-1.3B widths, planted-support recipe with half-precision rounding, 256
     tokens (the oracle's fp64 loops set the size)."""
     c = inputs.ffn_planted_support(256, 2048, 8192, 64, 64, 0.5, 4.0, seed=2001, dtype="f16")
     F.compare(lx, oracle, c)
@@ -80,7 +80,7 @@ def test_attn_f16_matches_oracle(lx, oracle, kw, seed):
 
 
 def test_attn_f16_config3_shape_sampled_heads(lx, oracle):
-    """configs[2]'s shape and mask recipe with half-precision tensors, full size on the GPU;
+    """The OPT-1.3B attention shape and mask recipe with half-precision tensors, full size on the GPU;
     the oracle checks sampled (batch, head) pairs."""
     c = inputs.attn_blocks(8, 32, 1024, 64, 0.30, seed=3001, dtype="f16", head_keep=7 / 8)
     got = A.run_gpu(lx, c)
@@ -91,7 +91,7 @@ def test_attn_f16_config3_shape_sampled_heads(lx, oracle):
                    **{k: np.ascontiguousarray(c[k][b:b + 1, h:h + 1]) for k in ("Q", "K", "V", "dO")})
         ref = A.run_oracle(oracle, sub)
         g = {k: v[b:b + 1, h:h + 1] for k, v in got.items()}
-        A.check(g, ref, f"f16 configs[2] shape b={b} h={h}", dtype="f16")
+        A.check(g, ref, f"f16 OPT-1.3B shape b={b} h={h}", dtype="f16")
     off = np.nonzero(c["head_active"] == 0)[0]
     for k in ("O", "dQ", "dK", "dV"):
         assert not got[k][:, off].any()

@@ -103,7 +103,7 @@ def compare(lx, oracle, c, mask=None, packed=True, bias=False):
 
 
 def test_config1_fp32_full(lx, oracle):
-    """configs[0]: OPT-125m-shaped FFN, fp32, 32x32 blocks, 30 % density."""
+    """OPT-125m-shaped FFN, fp32, 32x32 blocks, 30 % density."""
     compare(lx, oracle, inputs.config1_ffn())
 
 
@@ -186,7 +186,7 @@ def test_planted_support_mask_equals_dense_on_device(lx, oracle):
 
 
 def test_config2_bf16_full_size_sampled_tiles(lx, oracle):
-    """configs[1] at full size in the benchmark's launch configuration; the
+    """The OPT-1.3B FFN at full size in the benchmark's launch configuration; the
     oracle checks sampled token tiles (tiles are independent)."""
     c = inputs.config2_ffn()
     got = run_gpu(lx, c)
