@@ -368,8 +368,8 @@ size_t lx_sparse_attn_bwd_workspace_bytes(lx_dtype dt, int32_t B, int32_t Hh, in
  *   head_active  uint8[Hh] or NULL (all heads active)
  *   LSE      out float32 [B,Hh,S] contiguous
  * Supported: LX_BF16 / LX_F16 / LX_F32, D in {64, 128}, S % 64 == 0.  LX_F32 (float tensors,
- * fp32 arithmetic throughout) is the correctness configuration, like the fp32 FFN: plain
- * multiply-adds, not tuned.
+ * fp32 arithmetic throughout) is the correctness configuration: plain multiply-adds,
+ * not tuned.
  */
 lx_status lx_sparse_attn_fwd(lx_dtype dt, int32_t B, int32_t Hh, int32_t S, int32_t D,
                              float scale, int32_t causal, const void* Q, const void* K,
