@@ -70,10 +70,9 @@ typedef enum { LX_F32 = 0, LX_BF16 = 1, LX_F16 = 2 } lx_dtype;
  * the true count lives only on the device.  It also informs the choice of tiles;
  * a bound several times the true count costs the FFN calls little with one list
  * row or with rows*cols, up to some 40 % of the first product with a bound in
- * between and a row per tile or per group of tiles; calls with a LoRA branch
- * choose by the bound alone.  If row_ptr counts more entries
- * than nnz_cap (a bound that was too small), every call ignores the entries
- * after the first nnz_cap in list order: the results are those of the
+ * between and a row per tile or per group of tiles.  If row_ptr counts more
+ * entries than nnz_cap (a bound that was too small), every call ignores the
+ * entries after the first nnz_cap in list order: the results are those of the
  * truncated list and nothing outside the stated buffers is read or written.
  * (The attention backward call takes two lists of the same mask; each is
  * truncated by itself, so dQ and dK/dV then belong to different truncations:

@@ -317,8 +317,10 @@ __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_sdd(SddAr
 // the list's length / four times that / every block as capacity: 4096 tokens, d = 2048, 14 blocks 24.2 / 24.1 / 24.2 us
 // (by the capacity's tile 23.3 / 46.3 / 45.9), 2048 tokens, d = 2560, 20 blocks 25.8 / 25.4 / 25.4 (25.7 / 54.8 /
 // 35.6), 1024 tokens, d = 4096, 26 blocks 26.6 / 28.2 / 28.0 (26.3 / 46.3 / 76.8); four token tiles per list row, 1024
-// tokens, d = 4096, every block as capacity 31 us (79).
-template <int DT, int RESIDENT>
+// tokens, d = 4096, every block as capacity 31 us (79).  With the low-rank step, rank 64: 4096 tokens, d = 2048, 14
+// blocks, capacities 14 / 56 / 128 25 / 25 / 25 us (23 / 48 / 48), 1024 tokens, d = 4096, 26 blocks, capacities 26 / 104 /
+// 256 28 / 30 / 30 (27 / 47 / 80), four token tiles per row as above 33 (82).
+template <int DT, bool LORA, int RESIDENT>
 __global__ __launch_bounds__(RESIDENT == 1 ? 512 : 256, 2) void ffn_sdd_any(SddArgs a) {
   __shared__ __attribute__((aligned(1024))) uint16_t ring[RESIDENT == 1 ? kRingElems<Tile14Deep> : kRingElems<Tile14>];
   const int n = min(a.row_ptr[a.rows], a.nnz_cap) - min(a.row_ptr[0], a.nnz_cap);
@@ -330,19 +332,19 @@ __global__ __launch_bounds__(RESIDENT == 1 ? 512 : 256, 2) void ffn_sdd_any(SddA
   }
   if constexpr (RESIDENT == 1) {
     switch (id) {
-      case kT44: sdd_tile<Tile44, DT, false>(a, ring); break;
-      case kT24: sdd_tile<Tile24, DT, false>(a, ring); break;
-      case kT22Deep: sdd_tile<Tile22Deep, DT, false>(a, ring); break;
-      case kT14Deep: sdd_tile<Tile14Deep, DT, false>(a, ring); break;
-      case kT12: sdd_tile<Tile12, DT, false>(a, ring); break;
-      case kT11: sdd_tile<Tile11, DT, false>(a, ring); break;
+      case kT44: sdd_tile<Tile44, DT, LORA>(a, ring); break;
+      case kT24: sdd_tile<Tile24, DT, LORA>(a, ring); break;
+      case kT22Deep: sdd_tile<Tile22Deep, DT, LORA>(a, ring); break;
+      case kT14Deep: sdd_tile<Tile14Deep, DT, LORA>(a, ring); break;
+      case kT12: sdd_tile<Tile12, DT, LORA>(a, ring); break;
+      case kT11: sdd_tile<Tile11, DT, LORA>(a, ring); break;
     }
   } else {
     switch (id) {
-      case kT22: sdd_tile<Tile22, DT, false>(a, ring); break;
-      case kT14: sdd_tile<Tile14, DT, false>(a, ring); break;
-      case kT12: sdd_tile<Tile12, DT, false>(a, ring); break;
-      case kT11: sdd_tile<Tile11, DT, false>(a, ring); break;
+      case kT22: sdd_tile<Tile22, DT, LORA>(a, ring); break;
+      case kT14: sdd_tile<Tile14, DT, LORA>(a, ring); break;
+      case kT12: sdd_tile<Tile12, DT, LORA>(a, ring); break;
+      case kT11: sdd_tile<Tile11, DT, LORA>(a, ring); break;
     }
   }
 }
@@ -612,14 +614,14 @@ template <int DT, bool LORA>
 static void launch_sdd(SddArgs a, hipStream_t st) {
   const SddPlan p = plan_sdd(a.Tt, a.gt, a.K, a.nnz_cap, a.blocks, g_ffn_tiles_per_wg);
   if (p.grid == 0) return;
-  if (!LORA && p.allowed) {
+  if (p.allowed) {
     a.own = p.id;
     a.grid = p.grid;
     a.allowed = p.allowed;
     if (kTileInfo[p.id].resident == 1)
-      hipLaunchKernelGGL((ffn_sdd_any<DT, 1>), dim3(p.grid), dim3(512), 0, st, a);
+      hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 1>), dim3(p.grid), dim3(512), 0, st, a);
     else
-      hipLaunchKernelGGL((ffn_sdd_any<DT, 2>), dim3(p.grid), dim3(256), 0, st, a);
+      hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 2>), dim3(p.grid), dim3(256), 0, st, a);
     return;
   }
 #define LX_CALL(TL) hipLaunchKernelGGL((ffn_sdd<TL, DT, LORA>), dim3(p.grid), dim3(TL::kTileThreads), 0, st, a)

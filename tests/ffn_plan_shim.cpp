@@ -13,6 +13,10 @@ int sdd_tile(int Tt, int gt, int d, int nnz_cap, int blocks, int want, int n) {
     return sdd_pick<1>(p.id, p.allowed, sdd_limit<1>(p.id, p.grid, Tt, gt, n), Tt, gt, d, n);
   return sdd_pick<2>(p.id, p.allowed, sdd_limit<2>(p.id, p.grid, Tt, gt, n), Tt, gt, d, n);
 }
+// 1: the kernel of that tile alone is launched, 0: one that chooses among its set.
+int sdd_alone(int Tt, int gt, int d, int nnz_cap, int blocks, int want) {
+  return plan_sdd(Tt, gt, d, nnz_cap, blocks, want).allowed == 0;
+}
 // Workgroups launched, and those that the tile of sdd_tile needs.
 int sdd_launched(int Tt, int gt, int d, int nnz_cap, int blocks, int want) {
   return plan_sdd(Tt, gt, d, nnz_cap, blocks, want).grid;

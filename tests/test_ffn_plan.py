@@ -63,18 +63,29 @@ def test_labels_of_the_gpu_cases(L):
 
 
 def test_gpu_cases_reach_every_tile(L):
-    """Plain FFN: the cases of test_tile_edges (the library's choice and every knob value) and of the capacity test;
-    with the low-rank step: test_lora_every_tile; the reductions: test_cut_lists_by_tile."""
-    up, down = set(), set()
+    """First product, with and without the low-rank step: the cases of the two capacity tests, by a kernel of every tile
+    alone and by the kernels that choose among a set.  Second product: test_tile_edges (the library's choice and every
+    knob value) and the capacity test; with the low-rank step test_lora_every_tile, which holds both products against
+    the definitions; the reductions: test_cut_lists_by_tile."""
+    alone, chosen, down = set(), set(), set()
+    for _, Tt, d, Fb, nnz, rows, _, _ in CAPACITIES:
+        for cap in (max(rows * nnz, 1), rows * Fb):
+            args = (Tt, Tt // rows, d, cap, rows * Fb, 0)
+            tile = TILES[L.sdd_tile(*args, rows * nnz)]
+            if L.sdd_alone(*args):
+                alone.add(tile)
+            else:
+                own = L.sdd_tile_of_capacity(Tt, Tt // rows, d, cap, 0)
+                chosen.add(("narrow" if TILES[own] in ("2x2", "1x4", "1x2", "1x1") else "wide", tile))
+            down.add(ffn_plan.dsd(L, Tt, Tt // rows, d, cap)[0])
     for _, Tt, d, Fb, nnz, _ in EDGES:
         for want in (0, 1, 2, 4):
-            up.add(TILES[L.sdd_tile(Tt, Tt, d, nnz, Fb, want, nnz)])
             down.add(ffn_plan.dsd(L, Tt, Tt, d, nnz, 0, want)[0])
-    for _, Tt, d, Fb, nnz, rows, _, by_list in CAPACITIES:
-        for cap in (max(rows * nnz, 1), rows * Fb):
-            up.add(TILES[L.sdd_tile(Tt, Tt // rows, d, cap, rows * Fb, 0, rows * nnz)])
-            down.add(ffn_plan.dsd(L, Tt, Tt // rows, d, cap)[0])
-    assert up == set(TILES), set(TILES) - up
-    assert down == set(TILES), set(TILES) - down
-    assert {c[4] for c in LORA_TILES} == set(TILES) and {c[5] for c in LORA_TILES} == set(TILES)
+    every = set(TILES)
+    assert alone == every, every - alone
+    sets = ({("wide", t) for t in ("4x4", "2x4", "2x2 deep", "1x4 deep", "1x2", "1x1")} |
+            {("narrow", t) for t in ("2x2", "1x4", "1x2", "1x1")})
+    assert chosen == sets, sets - chosen
+    assert down == every, every - down
+    assert {c[4] for c in LORA_TILES} == every and {c[5] for c in LORA_TILES} == every
     assert {c[3] for c in CUT_BY_TILE} == {"4x4", "2x4", "2x2"}

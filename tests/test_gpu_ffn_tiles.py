@@ -131,12 +131,21 @@ CAPACITIES = [
     ("bf16", 60, 512, 48, 24, 60, "1x2", "1x4"),
     ("f16", 42, 1024, 17, 17, 2, "1x4 deep", "1x4 deep"),   # every block listed
     ("bf16", 50, 1024, 12, 12, 2, "1x1 many", "1x1 many"),
+    # with the exact capacity a kernel of one tile runs, with every block as capacity one that chooses: the same tile
+    ("bf16", 40, 64, 24, 23, 2, "1x2", "1x2"),
+    ("f16", 40, 512, 24, 23, 2, "2x2 deep", "2x2 deep"),
+    ("bf16", 36, 64, 48, 33, 3, "2x2", "2x2"),
+    ("bf16", 108, 512, 12, 11, 3, "2x4", "2x4"),
+    ("f16", 72, 64, 48, 33, 3, "4x4", "4x4"),
+    ("bf16", 72, 64, 24, 17, 24, "1x4", "1x4"),
+    ("bf16", 66, 1024, 12, 11, 66, "1x4 deep", "1x4 deep"),
 ]
 
 
 @pytest.mark.parametrize("dtype,Tt,d,Fb,nnz,rows,by_cap,by_list", CAPACITIES)
 def test_capacity_does_not_change_results(lx, dtype, Tt, d, Fb, nnz, rows, by_cap, by_list):
-    """A list handed over with room for every block runs by another tile than with its exact capacity: same bits."""
+    """A list handed over with room for every block may run by another tile, or another kernel of the same tile, than
+    with its exact capacity: same bits."""
     import torch
     T, F, gt = Tt * 64, Fb * 64, Tt // rows
     rng = np.random.default_rng(1000 + Tt)

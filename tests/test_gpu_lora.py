@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2510_15964_amd import inputs
+from test_gpu_ffn_tiles import CAPACITIES
 from util import FRO, TOL, compact_blocks, dev, host, rel_err_fro, rel_err_max, round_to
 
 pytestmark = pytest.mark.gpu
@@ -337,3 +338,36 @@ def test_lora_every_tile(lx, Tt, d, Fb, rows, up, dx):
     got.update(dX=host(dX), dA=host(dA), dB=host(dB))
     ref.update(dX=dZ @ Wu + (dZ @ B) @ A, dA=(dZ @ B).T @ X, dB=dZ.T @ Uq.astype(np.float64))
     check(got, ref, f"{up} / {dx}")
+
+
+@pytest.mark.parametrize("dtype,Tt,d,Fb,nnz,rows,by_cap,by_list", CAPACITIES)
+def test_lora_capacity_does_not_change_results(lx, dtype, Tt, d, Fb, nnz, rows, by_cap, by_list):
+    """The cases of the plain FFN's capacity test with a LoRA branch: same bits in every output."""
+    import torch
+    T, F, gt = Tt * 64, Fb * 64, Tt // rows
+    rng = np.random.default_rng(2000 + Tt)
+    mask = np.zeros((rows, Fb), np.uint8)
+    for r in mask:
+        r[rng.choice(Fb, nnz, replace=False)] = 1
+    dt = dev(np.zeros(1, np.float32), dtype).dtype
+    g = torch.Generator(device="cuda").manual_seed(Tt)
+    mk = lambda *s: (torch.randn(s, device="cuda", generator=g) * 0.1).to(dt)
+    X, dY, Wu, Wd, A, B = mk(T, d), mk(T, d), mk(F, d), mk(d, F), mk(64, d), mk(F, 64)
+    Wut, Wdt = lx.lx_ffn_pack_weights(Wu, Wd)
+    out = []
+    for cap in (max(rows * nnz, 1), rows * Fb):
+        print(dtype, Tt, d, Fb, nnz, rows, "capacity", cap, flush=True)
+        bl = lx.lx_mask_compact(torch.from_numpy(mask).cuda(), nnz_cap=cap)
+        H = torch.full(((cap * gt + 1) * 4096,), float("nan"), dtype=dt, device="cuda")
+        Y, dX, U = (torch.full((T, n), float("nan"), dtype=dt, device="cuda") for n in (d, d, 64))
+        dA, dB = (torch.full(s, float("nan"), device="cuda") for s in ((64, d), (F, 64)))
+        ws = torch.empty(lx.lx_sparse_ffn_lora_bwd_workspace_bytes(T, d, F, cap * gt), dtype=torch.uint8, device="cuda")
+        lx.lx_sparse_ffn_lora_fwd(X, Wu, A, B, Wd, bl, Y, H, U)
+        lx.lx_sparse_ffn_lora_bwd(X, dY, H, U, Wut, Wdt, A, B, bl, dX, dA, dB, ws)
+        torch.cuda.synchronize()
+        n = rows * nnz * gt * 4096
+        assert torch.isnan(H[n:]).all()
+        out.append((H[:n], Y, U, dX, dA, dB))
+        assert not any(torch.isnan(t).any() for t in out[-1])
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
