@@ -28,6 +28,7 @@ using Tile24 = Tile<2, 4, 2, 4, 3, 2>;
 using Tile22 = Tile<2, 2, 2, 2, 2, 2>;
 using Tile22Deep = Tile<2, 2, 2, 4, 4, 4>;
 using Tile14 = Tile<1, 4, 1, 4, 2, 2>;
+using Tile14Lean = Tile<1, 4, 1, 4, 1, 1, 4>;      // four workgroups on a CU: see sdd_lean, dsd_lean
 using Tile14Deep = Tile<1, 4, 2, 4, 4, 2>;
 using Tile12 = Tile<1, 2, 1, 4, 3, 2>;
 using Tile11 = Tile<1, 1, 2, 2, 4, 4>;
@@ -35,59 +36,81 @@ using Tile11Many = Tile<1, 1, 2, 2, 3, 4, 3>;
 template <class Tl>
 constexpr int kRingElems = Tl::NST * Tl::kElems;
 
-// Work items of the sdd kernel are (token tile, group of `per` consecutive list entries),
-// numbered in list order; `rows` counts token tiles, and gt consecutive tiles share one row of
-// the list (gt = 1: a list row per tile).  The launch grid is the host-known upper bound on their number and
-// every wavefront finds its item from row_ptr with 64-wide scans, so the active workgroups are
-// the FIRST ones of the grid and spread evenly over shader engines and CUs (a 2-D grid with
-// early exits piles them onto a few CUs).  Workgroup w runs on XCD w % 8; it takes item
-// of the range (w % 8) * L .. + L - 1 with L = ceil(total / 8), so each XCD owns a contiguous
-// range of items, i.e. of token tiles: a tile's activations are fetched into one L2 only, and
-// the weight blocks an XCD needs are those of one eighth of the tiles.  Returns false past the
-// end.
+// Work items of the sdd kernel are (token tile, group of `per` consecutive list entries); `rows` counts token
+// tiles, and gt consecutive tiles share one row of the list (gt = 1: a list row per tile).  The launch grid is
+// the host-known upper bound on their number and every wavefront finds its item from row_ptr with 64-wide
+// scans, so the active workgroups are the FIRST ones of the grid and spread evenly over shader engines and
+// CUs (a 2-D grid with early exits piles them onto a few CUs).
+// The items are numbered by the first halves of all lists, tile after tile, and then the second halves.
+// Workgroup w runs on XCD w % 8; it takes item of the range (w % 8) * L .. + L - 1 with L = ceil(total / 8), so
+// each XCD owns a quarter of the token tiles and, the lists being sorted, about half of the neuron axis.  Its L2
+// then fetches the rows of a quarter of the tokens and the listed ones of half of the weights, fewer bytes than
+// an eighth of the tokens and all listed weights (by the masks of 128 tiles, d = 4096, 8 % of the blocks: 470 MB over
+// the XCDs against 593 if all its workgroups kept step, d = 2048, 11 %: 156 and 184).  Returns false past the end.
 __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int rows, int gt, int w,
                                           int per, int nnz_cap, int& row, int& chunk) {
   const int lane = threadIdx.x % kWave;
-  // entries of a list row that lie within the capacity of the list buffers: the items are
-  // counted from these, so that their number never exceeds the bound the grid was sized from
-  auto row_len = [&](int lr) { return min(row_ptr[lr + 1], nnz_cap) - min(row_ptr[lr], nnz_cap); };
-  int total = 0;
+  // groups of entries of a token tile.  Entries of its list row count that lie within the capacity of the list buffers,
+  // so that the number of items never exceeds the bound the grid was sized from
+  auto groups = [&](int r) {
+    if (r >= rows) return 0;
+    const int lr = r / gt;
+    return (min(row_ptr[lr + 1], nnz_cap) - min(row_ptr[lr], nnz_cap) + per - 1) / per;
+  };
+  // inclusive sums over the lanes
+  auto scan = [&](int v) {
+#pragma unroll
+    for (int dlt = 1; dlt < kWave; dlt <<= 1) {
+      const int up = __shfl_up(v, dlt);
+      if (lane >= dlt) v += up;
+    }
+    return v;
+  };
+  // Item w of the launch's: which one of all; -1 past the end.  Inside an XCD's range consecutive workgroups are
+  // an eighth of the range apart, so the workgroups that run at the same time come from different token tiles and,
+  // the lists being sorted, from the same region of the neuron axis: the weight blocks that several tiles of
+  // the XCD use are then fetched into its L2 once.
+  auto item_of = [&](int total) {
+    const int L = (total + 7) / 8, q = (L + 7) / 8, slot = w / 8, pos = (slot % 8) * q + slot / 8;
+    const int work = (w % 8) * L + pos;
+    return slot >= 8 * q || pos >= L || work >= total ? -1 : work;
+  };
+  // The row among this wavefront's 64 whose items, `mine` up to the inclusive sum `incl`, hold item `work`.
+  auto place = [&](int work, int incl, int mine, int h, bool second) {
+    const int first = __ffsll((long long)__ballot(incl > work)) - 1;
+    chunk = work - __shfl(incl - mine, first) + (second ? __shfl(h, first) : 0);
+    return first;
+  };
+  if (rows <= kWave && (long long)nnz_cap * gt < 1 << 16) {     // one scan of both halves, 16 bits each
+    const int c = groups(lane), h = (c + 1) / 2, both = scan(h | (c - h) << 16), all = __shfl(both, kWave - 1);
+    const int firsts = all & 0xFFFF;
+    const int work = item_of(firsts + (int)((unsigned)all >> 16));
+    if (work < 0) return false;
+    const bool second = work >= firsts;
+    row = place(second ? work - firsts : work, second ? (int)((unsigned)both >> 16) : both & 0xFFFF, second ? c - h : h, h, second);
+    return true;
+  }
+  int total = 0, firsts = 0;           // of all lists; of their first halves
   for (int base = 0; base < rows; base += kWave) {
-    const int r = base + lane;
-    int c = 0;
-    if (r < rows) c = (row_len(r / gt) + per - 1) / per;
+    int c = groups(base + lane);
+    firsts += __popcll(__ballot(c & 1));
 #pragma unroll
     for (int dlt = 32; dlt > 0; dlt >>= 1) c += __shfl_xor(c, dlt);
     total += c;
   }
-  const int L = (total + 7) / 8;
-  // Inside an XCD's range consecutive workgroups are an eighth of the range apart, so the
-  // workgroups that run at the same time come from different token tiles and, the lists being
-  // sorted, from the same region of the neuron axis: the weight blocks that several tiles of
-  // the XCD use are then fetched into its L2 once (with all blocks listed: once per eight tiles).
-  const int q = (L + 7) / 8, slot = w / 8;
-  const int pos = (slot % 8) * q + slot / 8, work = (w % 8) * L + pos;
-  if (slot >= 8 * q || pos >= L || work >= total) return false;
-  int running = 0;
+  firsts = (total + firsts) / 2;       // (a first half is the longer one)
+  int work = item_of(total);
+  if (work < 0) return false;
+  const bool second = work >= firsts;
+  if (second) work -= firsts;
   for (int base = 0; base < rows; base += kWave) {
-    const int r = base + lane;
-    int c = 0;
-    if (r < rows) c = (row_len(r / gt) + per - 1) / per;
-    int incl = c;
-#pragma unroll
-    for (int dlt = 1; dlt < kWave; dlt <<= 1) {
-      const int up = __shfl_up(incl, dlt);
-      if (lane >= dlt) incl += up;
-    }
+    const int c = groups(base + lane), h = (c + 1) / 2, mine = second ? c - h : h, incl = scan(mine);
     const int seg = __shfl(incl, kWave - 1);
-    if (work < running + seg) {
-      const unsigned long long hit = __ballot(running + incl > work);
-      const int first = __ffsll((long long)hit) - 1;
-      row = base + first;
-      chunk = work - running - __shfl(incl - c, first);
+    if (work < seg) {
+      row = base + place(work, incl, mine, h, second);
       return true;
     }
-    running += seg;
+    work -= seg;
   }
   return false;
 }
@@ -349,25 +372,17 @@ __global__ __launch_bounds__(RESIDENT == 1 ? 512 : 256, 2) void ffn_sdd_any(SddA
   }
 }
 
-// Which token tile the workgroups of grid row `slot` work on.  A workgroup of the dsd kernel
-// lasts as long as its tile's list is long, and a launch of few tiles lasts as long as its
-// slowest CU.  Up to kBalTiles tiles are therefore ranked by list length (ties by index; every
-// workgroup computes the same ranking, so the assignment is a permutation): grid rows are
-// dispatched in order, so the longest lists start first; and when the whole launch is resident
-// at once, two workgroups per CU, rows s and s + Tt/2, which the round robin of the dispatcher
-// places on the same CU, get ranks s and Tt - 1 - s, a long list next to a short one.
-constexpr int kBalTiles = 128;
-__device__ __forceinline__ int balanced_tile(const int* __restrict__ row_ptr, int Tt, int gt,
-                                             int nnz_cap, int slot, bool resident, int* lens) {
-  if (Tt > kBalTiles || Tt < 3) return slot;
+// The token tile whose list has rank `want` by length (longest first, ties by index), out of up to kBalTiles; every
+// workgroup computes the same ranking, so the assignment is a permutation.  Beyond: tile `want`.
+__device__ __forceinline__ int tile_of_rank(const int* __restrict__ row_ptr, int Tt, int gt,
+                                            int nnz_cap, int want, int* lens) {
+  if (Tt > kBalTiles || Tt < 3) return want;
   const int tid = threadIdx.x;
   if (tid < Tt) {
     const int r = tid / gt;
     lens[tid] = min(row_ptr[r + 1], nnz_cap) - row_ptr[r];
   }
   __syncthreads();
-  const int half = (Tt + 1) / 2;
-  const int want = resident && slot >= half ? Tt - 1 - (slot - half) : slot;
   if (tid < Tt) {
     const int n = lens[tid];
     int rank = 0;
@@ -391,6 +406,7 @@ struct DsdArgs {
   int Tt, gt, ncols, nnz_cap;
   int band;                    // h of grid_item (one list row)
   int full, rest, pieces;      // one list row: units that run whole, then units whose list is cut
+  int GM, GN, order;           // otherwise: token groups, column chunks, DsdOrder
   uint16_t* out;
   float* part;
   const uint16_t *A2, *W2;     // LORA
@@ -401,7 +417,6 @@ struct DsdSrc {
   const uint16_t* base[Tl::kIss];
   const uint16_t* base2[LORA ? Tl::kIss : 1];
   uint32_t voffA[2], voffW[2];
-  uint32_t voff2[2];
   long long off_a, off_w, step_a;
   const int* list;             // col_idx of the range
   int lsteps, next;            // list entries of 64 steps, one per lane
@@ -416,8 +431,8 @@ struct DsdSrc {
   __device__ __forceinline__ void begin(int s) {
     if (LORA && s == lsteps) {  // (the last step, as in SddSrc)
       off_a = off_w = 0;
-      voffW[0] = voff2[0];
-      voffW[1] = voff2[1];
+      voffW[0] = voffA[0];     // rows of 64 elements too
+      voffW[1] = voffA[1];
 #pragma unroll
       for (int u = 0; u < Tl::kIss; ++u) base[u] = base2[LORA ? u : 0];
       return;
@@ -441,8 +456,8 @@ struct DsdSrc {
 // W2 [ncols_out, 64]: out += A2_i W2[n0..]^T, the low-rank part (dZ B) A of the input gradient.
 // One list row for all tiles: 1-D grid over units (tile group, column chunk); the first `full` run
 // whole, the list of each of the following `rest` is cut into `pieces` whose accumulators go to
-// `part` as they are, fp32, for ffn_dsd_reduce to add in order.  Otherwise: 2-D grid (column chunk,
-// tile group).
+// `part` as they are, fp32, for ffn_dsd_reduce to add in order.  Otherwise: 1-D grid of (column chunk, tile group),
+// see dsd_unit.
 template <class Tl, int DT, bool LORA>
 __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_dsd(DsdArgs a) {
   __shared__ __attribute__((aligned(1024))) uint16_t ring[Tl::NST * Tl::kElems];
@@ -472,9 +487,14 @@ __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_dsd(DsdAr
       n_i = (int)((long long)n_i * (piece + 1) / a.pieces) - s_lo;
     }
   } else {
-    i0 = Tl::TM * balanced_tile(a.row_ptr, gridDim.y, a.gt / Tl::TM, a.nnz_cap, blockIdx.y,
-                                gridDim.x * gridDim.y <= 2 * kCUs, reinterpret_cast<int*>(ring));
-    n0 = blockIdx.x * (64 * Tl::TN);
+    int chunk, rank;
+    if (!dsd_unit(a.order, a.GM, a.GN, blockIdx.x, chunk, rank)) return;
+    chunk = __builtin_amdgcn_readfirstlane(chunk);
+    rank = __builtin_amdgcn_readfirstlane(rank);
+    if (a.order != kUnranked)
+      rank = tile_of_rank(a.row_ptr, a.GM, a.gt / Tl::TM, a.nnz_cap, rank, reinterpret_cast<int*>(ring));
+    i0 = Tl::TM * rank;
+    n0 = chunk * (64 * Tl::TN);
     rs = a.row_ptr[i0 / a.gt];
     n_i = min(a.row_ptr[i0 / a.gt + 1], a.nnz_cap) - rs;
   }
@@ -490,7 +510,6 @@ __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_dsd(DsdAr
   for (int q = 0; q < 2; ++q) {
     src.voffA[q] = lane_voff<Tl>(64, wave + 4 * q);
     src.voffW[q] = lane_voff<Tl>(a.ldw, wave + 4 * q);
-    if (LORA) src.voff2[q] = lane_voff<Tl>(64, wave + 4 * q);
   }
 #pragma unroll
   for (int u = 0; u < Tl::kIss; ++u) {
@@ -625,6 +644,10 @@ static void launch_sdd(SddArgs a, hipStream_t st) {
     return;
   }
 #define LX_CALL(TL) hipLaunchKernelGGL((ffn_sdd<TL, DT, LORA>), dim3(p.grid), dim3(TL::kTileThreads), 0, st, a)
+  if (sdd_lean(p.id, a.Tt, a.gt, a.nnz_cap)) {
+    LX_CALL(Tile14Lean);
+    return;
+  }
   LX_TILES(p.id, LX_CALL)
 #undef LX_CALL
 }
@@ -636,10 +659,16 @@ static void launch_dsd(DsdArgs a, size_t part_bytes, hipStream_t st) {
   a.full = p.full;
   a.rest = p.rest;
   a.pieces = p.pieces;
-  const dim3 grid = a.gt == a.Tt ? dim3(8 * ceil_div(p.full, 8) + 8 * ceil_div((long long)p.rest * p.pieces, 8))
-                                 : dim3(ceil_div(a.ncols, 64 * t.tn), a.Tt / t.tm);
+  a.GM = a.Tt / t.tm;
+  a.GN = ceil_div(a.ncols, 64 * t.tn);
+  const bool lean = dsd_lean(p.id, a.Tt, a.gt, a.GM, a.GN);
+  a.order = dsd_order(a.GM, a.GN, lean);
+  const dim3 grid(a.gt == a.Tt ? 8 * ceil_div(p.full, 8) + 8 * ceil_div((long long)p.rest * p.pieces, 8) : 8 * ceil_div(a.GM * a.GN, 8));
 #define LX_CALL(TL) hipLaunchKernelGGL((ffn_dsd<TL, DT, LORA>), grid, dim3(TL::kTileThreads), 0, st, a)
-  LX_TILES(p.id, LX_CALL)
+  if (lean)
+    LX_CALL(Tile14Lean);
+  else
+    LX_TILES(p.id, LX_CALL)
 #undef LX_CALL
 #define LX_CALL(TL) \
   hipLaunchKernelGGL((ffn_dsd_reduce<TL, DT>), dim3(p.rest, TL::TM * TL::TN), dim3(256), 0, st, a)
@@ -670,7 +699,7 @@ static hipError_t launch_ffn_bf16_t(int pass, int Tt, int gt, int Fb, int d, int
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   ProfScope ps(pass == 0 ? kKFfnDown : kKFfnDx, st);
-  launch_dsd<DT, false>({act_out, W2, b2, (long long)F, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, 0, 0, 1, out, part,
+  launch_dsd<DT, false>({act_out, W2, b2, (long long)F, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, 0, 0, 1, 0, 0, 0, out, part,
                          nullptr, nullptr}, part_bytes, st);
   return hipGetLastError();
 }
@@ -704,7 +733,7 @@ static hipError_t launch_ffn_lora_fwd_bf16_t(int Tt, int gt, int d, int F, const
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   ProfScope ps(kKFfnDown, st);
-  launch_dsd<DT, false>({H_act, W_down, nullptr, (long long)F, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, 0, 0, 1, Y,
+  launch_dsd<DT, false>({H_act, W_down, nullptr, (long long)F, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, 0, 0, 1, 0, 0, 0, Y,
                          nullptr, nullptr, nullptr}, 0, st);
   return hipGetLastError();
 }
@@ -739,7 +768,7 @@ static hipError_t launch_ffn_lora_bwd_bf16_t(int Tt, int gt, int d, int F, const
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKFfnDx, st);
-    launch_dsd<DT, true>({dZ, W_up_t, nullptr, (long long)F, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, 0, 0, 1, dX,
+    launch_dsd<DT, true>({dZ, W_up_t, nullptr, (long long)F, row_ptr, col_idx, Tt, gt, d, nnz_cap, 0, 0, 0, 1, 0, 0, 0, dX,
                           nullptr, G, A_t}, 0, st);
   }
   e = hipGetLastError();

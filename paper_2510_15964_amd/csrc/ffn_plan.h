@@ -199,4 +199,87 @@ inline DsdPlan choose_dsd(int Tt, int gt, int d, int nnz_cap, size_t part_bytes,
   return best;
 }
 
+// Lists per group of token tiles: the units are (column chunk, of GN; token group, of GM).  Three ways to deal them:
+// - kByChunk: XCD w % 8 takes the w % 8th eighth of the units, chunk after chunk, and so fetches the weight rows of an
+//   eighth of the columns only.  Where an eighth ends inside a chunk, its parts get long and short lists in
+//   proportion: the groups by length (rank 0: the longest list) are dealt evenly over them.  Inside a part the longest go
+//   first, except that every other 32 workgroups, one for each CU of the XCD, go the other way round: workgroups on a CU
+//   then have long and short lists.
+// - kByRank: the chunks of the longest list, then those of the next.  An XCD has an eighth of the columns here too if the
+//   number of chunks divides eight or is divided by it, and the workgroups that run together have lists of similar
+//   length: they walk along the columns at the same pace, and what one fetches the others find in the L2 (4096 tokens,
+//   d = 4096, 10 % of the blocks: 84.5 us, 89.4 by kByChunk).  With other numbers every XCD fetches all columns: 8192 tokens,
+//   d = 4160, 8 % 207 us, 137 by kByChunk; 7424 tokens, d = 2624, 25 % 238 and 142; 2048 tokens, d = 3200, 50 % 214 and 133.
+// - kUnranked: kByChunk by the number of the token group instead of its rank, up to one workgroup per CU: nothing to even
+//   out, and the ranking costs a load and three barriers.
+enum DsdOrder { kByChunk, kByRank, kUnranked };
+constexpr int kBalTiles = 128;     // most token groups that are ranked; beyond, their numbers take the place of the ranks
+inline DsdOrder dsd_order(int GM, int GN, bool lean) {
+  if (GM * GN <= kCUs) return kUnranked;
+  return !lean && (GN % 8 == 0 || 8 % GN == 0) ? kByRank : kByChunk;
+}
+// a / b for a >= 0, b > 0: a reciprocal and a correction (the compiler's division is some forty instructions, and
+// they stand at the head of a workgroup's chain of loads)
+LX_HD int quick_div(int a, int b) {
+  if (a >= 1 << 22) return a / b;
+#if defined(__HIP_DEVICE_COMPILE__)
+  int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+#else
+  int q = (int)((float)a * (1.f / (float)b));
+#endif
+  const int r = a - q * b;
+  q += r >= b ? 1 : 0;
+  q -= r < 0 ? 1 : 0;
+  return q;
+}
+// The unit of workgroup w; false past the end.
+LX_HD bool dsd_unit(int order, int GM, int GN, int w, int& chunk, int& rank) {
+  const int total = GM * GN;
+  if (order == kByRank) {
+    if (w >= total) return false;
+    rank = quick_div(w, GN);
+    chunk = w - rank * GN;
+    // where all are resident, two per CU, the round robin of the dispatcher puts rows s and s + GM/2 on one CU: a long list
+    // next to a short one
+    const int half = (GM + 1) / 2;
+    if (total <= 2 * kCUs && rank >= half) rank = GM - 1 - (rank - half);
+    return true;
+  }
+  const int L = ceil_div(total, 8), x = w % 8, slot = w / 8;
+  int unit = x * L + slot;
+  if (order == kByChunk && slot / 32 % 2) {
+    const int layer = slot / 32 * 32, width = L - layer < 32 ? L - layer : 32;
+    unit = x * L + layer + width - 1 - (slot - layer);
+  }
+  if (slot >= L || unit >= total) return false;
+  chunk = quick_div(unit, GM);
+  rank = unit - chunk * GM;
+  if (order == kUnranked || GM > kBalTiles) return true;
+  // part s of the chunk begins at position 0, f, f + L, ...; the j-th of its n units out of the R that it and the
+  // later ones share is rank ceil((j + 1) R / n) - 1 of those, the e-th of the later ones' b is rank e R / b
+  const int over = chunk * GM - quick_div(chunk * GM, L) * L, f = L - over;
+  const int s = rank < f ? 0 : quick_div(rank - f, L) + 1;
+  const int begin = s == 0 ? 0 : f + (s - 1) * L, end = f + s * L < GM ? f + s * L : GM, n = end - begin;
+  int e = quick_div((rank - begin + 1) * (GM - begin) + n - 1, n) - 1;
+  for (int t = s - 1; t >= 0; --t) e = quick_div(e * (t == 0 ? GM : GM - f - (t - 1) * L), GM - f - t * L);
+  rank = e;
+  return true;
+}
+// Lists per group of token tiles, 1 x 4 tiles: whether four workgroups per CU with one stage each (Tile14Lean) run the
+// launch instead of two with two stages.  A workgroup is slower with the one, so it has to pay otherwise:
+// - first product: up to one and a half rounds of two, where the second round is short (four: 0.8 - 1.0 of the time at
+//   525 - 720 items: 8192 tokens, d = 768, 40 % of the blocks 41 -> 33 us, 4096 tokens, d = 1024, 55 % 45 -> 37, 8192
+//   tokens, d = 4096, 8 % 172 -> 162; at 850 and more 1.0 - 1.15);
+// - second product: where an XCD's eighth is whole column chunks of more than 64 token groups, which two per CU would
+//   walk through in more than one round, fetching the chunk's weight rows in each (8192 tokens, d = 2048, 10 / 30 % 50 / 101
+//   -> 43 / 94 us; d = 4096, 8 % 125 -> 112; with parts of chunks or 64 groups 0.98 - 1.11 of the time).
+LX_HD bool sdd_lean(int id, int Tt, int gt, int nnz_cap) {
+  if (id != kT14 || gt == Tt) return false;
+  const int items = sdd_items_about(kTileInfo[kT14], Tt, gt, (int)(6.f / 7.f * (float)nnz_cap));
+  return items > 2 * kCUs && items <= 3 * kCUs;
+}
+LX_HD bool dsd_lean(int id, int Tt, int gt, int GM, int GN) {
+  return id == kT14 && gt != Tt && GN % 8 == 0 && GM > 64 && GM * GN > 2 * kCUs;
+}
+
 }  // namespace lx

@@ -26,7 +26,7 @@ struct Tile {
   static constexpr int kIssA = 8 * TM / kWaves;              // the first of them bring token rows
   static constexpr int NI = 2 * TN / WN, TI = 2 * TM / WM;   // 32 x 32 accumulators of a wavefront
   static_assert(8 * TM % kWaves == 0 && 8 * TN % kWaves == 0 && (kWaves == 4 || kWaves == 8), "wavefronts");
-  static_assert(NI >= 1 && TI >= 1 && (KS == 2 || KS == 4), "wave tile");
+  static_assert(NI >= 1 && TI >= 1 && (KS == 2 || KS == 4 || (KS == 1 && NST == 1)), "wave tile");
 };
 
 template <class Tl>
@@ -99,10 +99,53 @@ __device__ __forceinline__ void tile_phase(const Frag<Tl>& cur, Frag<Tl>& nxt, c
       }
 }
 
+// run_tile with a ring of one stage: a workgroup waits for the transfers of its next step, and the three others that
+// such a stage leaves room for on the CU compute meanwhile.
+template <class Tl, int DT, class Src>
+__device__ __forceinline__ void run_tile_one_stage(int nsteps, uint32_t ring, int wm, int wn, Src& src,
+                                                   f32x16 (&acc)[Tl::NI][Tl::TI]) {
+  if (nsteps <= 0) return;
+  const LaneOff<Tl> lo(wm, wn);
+  const uint32_t to = ring + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave) * 1024;
+  Frag<Tl> f[2];
+  auto read = [&](int ph) {
+#pragma unroll
+    for (int x = 0; x < Tl::NI + Tl::TI; ++x) read_operand<Tl>(f[ph % 2], lo, ring, ph, x);
+  };
+  src.begin(0);
+#pragma unroll
+  for (int u = 0; u < Tl::kIss; ++u) src.dma(u, to);
+  for (int s = 0; s < nsteps; ++s) {
+    wait_vmcnt<0>();
+    lds_barrier();
+    read(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ph = 0; ph < 4; ++ph) {
+      if (ph < 3) {
+        read(ph + 1);
+      } else {
+        lds_barrier();     // every wavefront has the step's operands in registers
+        if (s + 1 < nsteps) {
+          src.begin(s + 1);
+#pragma unroll
+          for (int u = 0; u < Tl::kIss; ++u) src.dma(u, to);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ni = 0; ni < Tl::NI; ++ni)
+#pragma unroll
+        for (int ti = 0; ti < Tl::TI; ++ti) acc[ni][ti] = mfma32<DT>(f[ph % 2].a[0][ni], f[ph % 2].b[0][ti], acc[ni][ti]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
 // acc[ni][ti] += sum over nsteps steps.  src.begin(s) prepares the sources of step s, src.dma(u, lds)
 // issues its transfer instruction u to the stage at that LDS address.
 template <class Tl, int DT, class Src>
-__device__ __forceinline__ void run_tile(int nsteps, uint32_t ring, int wm, int wn, Src& src,
+__device__ __forceinline__ void run_tile_ring(int nsteps, uint32_t ring, int wm, int wn, Src& src,
                                          f32x16 (&acc)[Tl::NI][Tl::TI]) {
   constexpr int NST = Tl::NST, NISS = Tl::kIss;
   static_assert(NST >= 2 && NISS * (NST - 1) < 64, "ring depth");
@@ -175,6 +218,15 @@ __device__ __forceinline__ void run_tile(int nsteps, uint32_t ring, int wm, int 
       }
     }
   }
+}
+
+template <class Tl, int DT, class Src>
+__device__ __forceinline__ void run_tile(int nsteps, uint32_t ring, int wm, int wn, Src& src,
+                                         f32x16 (&acc)[Tl::NI][Tl::TI]) {
+  if constexpr (Tl::NST == 1)
+    run_tile_one_stage<Tl, DT>(nsteps, ring, wm, wn, src, acc);
+  else
+    run_tile_ring<Tl, DT>(nsteps, ring, wm, wn, src, acc);
 }
 
 }  // namespace lx
