@@ -64,9 +64,14 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kSlack = 8.f;            // log2 units; see the forward kernel
 
+// What the 16-byte slots of a row are XORed with.  A 16-byte read takes four clocks if no two lanes of 0 .. 3, 12 .. 15 and
+// 20 .. 27, or of the others of a half wavefront, meet in a bank (64 of them), and a transposing read two if none of the 32
+// lanes of a half do; both hold for the two access patterns below.  (Measured in a loop of such reads, eight wavefronts:
+// with row ^ row / 8 at D = 64 and row at D = 128, conflict-free for eight lanes in a row, the 16-byte reads took 8 clocks
+// at D = 64 and the transposing ones 4.2 at D = 128.)  Rows 16 apart have the same.
 template <int D>
-__device__ __forceinline__ int tswz(int row) {
-  return D == 64 ? ((row ^ (row >> 3)) & 7) : (row & 15);
+__device__ __forceinline__ constexpr int tswz(int row) {
+  return D == 64 ? row & 7 : (row & 3) << 1 | ((row >> 2 ^ row >> 3) & 1) << 3 | (row >> 2 & 1);
 }
 
 // The DMA instructions this wave issues for one [64 x D] tile: a wave-uniform base per instruction and
@@ -111,7 +116,7 @@ struct TileDma {
 // and in-slot parts occupy disjoint bits, so the offset of (r0 + dr, c0 + dc) is the offset of
 // (r0, c0) XOR a compile-time constant whenever r0/dr and c0/dc have disjoint bits.  Of that constant
 // the row part only adds (bits that r0 leaves clear), so it goes into the LDS instruction's immediate
-// offset; what is left are 4 or 8 different XORs of the slot bits per access pattern, each kept as one
+// offset; what is left are D / 32 or D / 16 different XORs of the slot bits per access pattern, each kept as one
 // per-lane offset to which the stage's address is added once per tile (an XOR per LDS read was a
 // sixth of the forward kernel's vector instructions).
 template <int D>
@@ -239,17 +244,14 @@ __device__ __forceinline__ f32x4 mfma16(uint4 a, uint4 b, f32x4 c) {
 // bits that the patterns' rows and columns make.
 template <int D>
 struct LaneOff16 {
-  static constexpr int kTr = D == 64 ? 4 : 8;
-  uint32_t rows[4];   // element (lane%16, 8*(lane/16)); row tile t, k slice kk: entry xr(t, kk), + 16t rows
-  uint32_t tr[kTr];   // element (4*(lane/16) + (lane%16)/4, 4*(lane%4)); entry xt(kk, i, ct), + 32kk + 16i rows
-  static __device__ __forceinline__ constexpr int xr(int t, int kk) { return D == 64 ? (2 * kk) ^ t : kk; }
-  static __device__ __forceinline__ constexpr int xt(int kk, int i, int ct) { return D == 64 ? ct ^ (2 * kk) ^ i : ct; }
+  uint32_t rows[D / 32];   // element (lane%16, 8*(lane/16)) of k slice kk; row tile t: + 16t rows
+  uint32_t tr[D / 16];     // element (4*(lane/16) + (lane%16)/4, 4*(lane%4)) of column tile ct; + 32kk + 16i rows
   __device__ __forceinline__ void init() {
     const int lane = threadIdx.x % kWave, g = lane / 16, j = lane % 16;
 #pragma unroll
-    for (int x = 0; x < 4; ++x) rows[x] = tile_off<D>(j, 8 * g) ^ (x << (D == 64 ? 5 : 6));
+    for (int kk = 0; kk < D / 32; ++kk) rows[kk] = tile_off<D>(j, 8 * g) ^ (kk << 6);
 #pragma unroll
-    for (int x = 0; x < kTr; ++x) tr[x] = tile_off<D>(4 * g + j / 4, 4 * (j % 4)) ^ (x << 5);
+    for (int ct = 0; ct < D / 16; ++ct) tr[ct] = tile_off<D>(4 * g + j / 4, 4 * (j % 4)) ^ (ct << 5);
   }
 };
 // v + s, opaque to the compiler: constants added to the result stay in the LDS instructions' immediates
@@ -266,14 +268,14 @@ template <int D, int DT>
 __device__ __forceinline__ void mma_rows16(uint32_t tile, const LaneOff16<D>& lo,
                                            const uint4 (&frag)[D / 32], f32x4 (&acc)[4]) {
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  uint32_t a0[4];
+  uint32_t a0[D / 32];
 #pragma unroll
-  for (int x = 0; x < 4; ++x) a0[x] = add_lds(lo.rows[x], tile);
+  for (int kk = 0; kk < D / 32; ++kk) a0[kk] = add_lds(lo.rows[kk], tile);
   uint4 a[D / 32][4];
 #pragma unroll
   for (int kk = 0; kk < D / 32; ++kk)
 #pragma unroll
-    for (int t = 0; t < 4; ++t) a[kk][t] = lds_read16(a0[lo.xr(t, kk)] + 16 * t * 2 * D);
+    for (int t = 0; t < 4; ++t) a[kk][t] = lds_read16(a0[kk] + 16 * t * 2 * D);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int kk = 0; kk < D / 32; ++kk)
@@ -291,15 +293,15 @@ struct TrOps16 {
 };
 template <int D>
 __device__ __forceinline__ void load_tr16(uint32_t tile, const LaneOff16<D>& lo, TrOps16<D>& t) {
-  uint32_t a0[LaneOff16<D>::kTr];
+  uint32_t a0[D / 16];
 #pragma unroll
-  for (int x = 0; x < LaneOff16<D>::kTr; ++x) a0[x] = add_lds(lo.tr[x], tile);
+  for (int ct = 0; ct < D / 16; ++ct) a0[ct] = add_lds(lo.tr[ct], tile);
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
     for (int ct = 0; ct < D / 16; ++ct) {
-      const uint2 l = lds_read8_tr(a0[lo.xt(kk, 0, ct)] + (32 * kk) * 2 * D);
-      const uint2 h = lds_read8_tr(a0[lo.xt(kk, 1, ct)] + (32 * kk + 16) * 2 * D);
+      const uint2 l = lds_read8_tr(a0[ct] + (32 * kk) * 2 * D);
+      const uint2 h = lds_read8_tr(a0[ct] + (32 * kk + 16) * 2 * D);
       t.a[kk][ct] = make_uint4(l.x, l.y, h.x, h.y);
     }
 }
