@@ -98,7 +98,7 @@ typedef enum {
   LX_K_FFN_DX = 4,       /* dX_i = sum_j dZ_ij W_up_j */
   LX_K_ATTN_FWD = 5,     /* fused SDD + softmax + DSD */
   LX_K_ATTN_BWD_DQ = 6,  /* Delta and dQ, query side */
-  LX_K_ATTN_BWD_DKV = 7, /* dK and dV, key side */
+  LX_K_ATTN_BWD_DKV = 7, /* dK and dV, key side (small calls: both sides in one launch) */
   LX_K_TRANSPOSE = 8,    /* weight repack */
   LX_K_PREDICT = 9,      /* MLP predictor: scores + threshold + OR over the tokens */
   LX_K_COMBINE = 10,     /* per-head pattern layouts -> multi-head block list */

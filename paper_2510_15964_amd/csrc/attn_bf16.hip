@@ -590,10 +590,10 @@ __device__ __forceinline__ void walk_table(int* tab, const RowSet& rows, const i
 struct PairWork {
   int b, group, z;
 };
-__device__ __forceinline__ bool pair_work(const AttnArgs& a, PairWork& p) {
+__device__ __forceinline__ bool pair_work(const AttnArgs& a, int w, PairWork& p) {
   const int P = a.B * (a.Hh / a.vheads), gz = a.gz;
-  const int x = blockIdx.x % 8, whole = P / 8 * gz;
-  int s = blockIdx.x / 8, pair;
+  const int x = w % 8, whole = P / 8 * gz;
+  int s = w / 8, pair;
   if (a.spread && s < kCUs / 8 && whole >= kCUs / 8) s = kCUs / 8 - 1 - s;
   if (s < whole) {
     const int W = P / 8;
@@ -621,7 +621,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;   // bytes
   const int nqb = a.S / 64;
   PairWork pw;
-  if (!pair_work(a, pw)) return;
+  if (!pair_work(a, blockIdx.x, pw)) return;
   const int b = pw.b, h0 = pw.group * a.vheads;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, ql = 16 * wave + lane % 16;    // this lane's query inside the block
@@ -738,16 +738,30 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
 // ---------------------------------------------------------------------------
 // backward, query side
 // ---------------------------------------------------------------------------
-template <int D, int DT, int NS, int OCC, bool WIDE>
-__global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
-  __shared__ __attribute__((aligned(2 * 64 * D))) uint16_t st[NS][2 * 64 * D];   // stage: K, V (or Q, dO; or O) tile
-  __shared__ __attribute__((aligned(256))) float slse[NS][4][16];   // stage, wavefront: LSE of its 16 own rows
-  __shared__ int rowtab[4 * kRMax];
-  __shared__ int btab[kTabCap];
+// sum + the products of eight elements of two operands
+template <int DT>
+__device__ __forceinline__ float dot8(uint4 a, uint4 b, float sum) {
+  const uint32_t x[4] = {a.x, a.y, a.z, a.w}, y[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    sum += to_f32<DT>(x[q] & 0xFFFFu) * to_f32<DT>(y[q] & 0xFFFFu) + to_f32<DT>(x[q] >> 16) * to_f32<DT>(y[q] >> 16);
+  return sum;
+}
+template <int D, int NS>
+struct DqLds {                       // (aligned to a tile where it is declared)
+  uint16_t st[NS][2 * 64 * D];       // stage: K, V (or Q, dO; or O) tile
+  float slse[NS][4][16];             // stage, wavefront: LSE of its 16 own rows
+  int rowtab[4 * kRMax];
+  int btab[kTabCap];
+};
+template <int D, int DT, int NS, bool WIDE>
+__device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, NS>& sh) {
+  auto& st = sh.st;
+  auto& slse = sh.slse;
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;
   const int nqb = a.S / 64;
   PairWork pw;
-  if (!pair_work(a, pw)) return;
+  if (!pair_work(a, w, pw)) return;
   const int b = pw.b, h0 = pw.group * a.vheads;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, ql = 16 * wave + lane % 16;
@@ -757,7 +771,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
   const uint32_t own_off = tile_off<D>(ql, 8 * g);
 
   RowSet rows;
-  rows.init(rowtab, a.row_ptr, a.nnz_cap, ((a.mask_batch == 1 ? 0 : b) * a.Hh + h0) * nqb, nqb,
+  rows.init(sh.rowtab, a.row_ptr, a.nnz_cap, ((a.mask_batch == 1 ? 0 : b) * a.Hh + h0) * nqb, nqb,
             a.vheads, h0, a.head_active, pw.z, a.gz, a.rows_per_wg, true);
   // rows without a listed block (or of an inactive head): dQ = 0, Delta = 0, nothing to read
   for (int j = 0; j < kRMax; ++j)
@@ -822,12 +836,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
     float sum = 0.f;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) {
-      const uint4 of = lds_read16(o0 ^ tile_off<D>(0, 32 * kk));
-      const uint32_t x[4] = {dof[kk].x, dof[kk].y, dof[kk].z, dof[kk].w};
-      const uint32_t y[4] = {of.x, of.y, of.z, of.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        sum += to_f32<DT>(x[q] & 0xFFFFu) * to_f32<DT>(y[q] & 0xFFFFu) + to_f32<DT>(x[q] >> 16) * to_f32<DT>(y[q] >> 16);
+      sum = dot8<DT>(dof[kk], lds_read16(o0 ^ tile_off<D>(0, 32 * kk)), sum);
     }
     delta = sum_g(sum);
     // a row whose listed blocks hold no allowed key has LSE = -inf: +inf here makes every
@@ -859,23 +868,34 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
   };
   auto row_end = [&](int) { store_acc16_asm<D, DT>(dq_acc, a.scale, a.dQ + qoff); };
   walk_table<NS, 2 * TileDma<D, WIDE>::kPerWave, TileDma<D, WIDE>::kPerWave + 1, 2 * TileDma<D, WIDE>::kPerWave, 2, D / 32>(
-      btab, rows, a.col_idx, issue_own, issue_aux, issue_blk, row_begin, aux, comp, row_end);
+      sh.btab, rows, a.col_idx, issue_own, issue_aux, issue_blk, row_begin, aux, comp, row_end);
+}
+template <int D, int DT, int NS, int OCC, bool WIDE>
+__global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
+  __shared__ __attribute__((aligned(2 * 64 * D))) DqLds<D, NS> sh;
+  attn_bwd_dq<D, DT, NS, WIDE>(a, blockIdx.x, sh);
 }
 
 // ---------------------------------------------------------------------------
 // backward, key side: a wavefront owns 16 keys; the streamed tiles are Q and dO of the listed
-// query blocks, with the queries' -LSE*log2(e) and Delta beside them
+// query blocks, with the queries' -LSE*log2(e) and Delta beside them.  ALONE: O is streamed too and they are made here,
+// as the query side makes them, so that the two sides need not follow each other
 // ---------------------------------------------------------------------------
-template <int D, int DT, int NS, int OCC, bool WIDE>
-__global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) {
-  __shared__ __attribute__((aligned(2 * 64 * D))) uint16_t st[NS][2 * 64 * D];   // stage: Q, dO (or K, V) tile
-  __shared__ __attribute__((aligned(512))) float sstat[NS][4][32];   // stage, query tile: -LSE*log2e [16], Delta [16]
-  __shared__ int rowtab[4 * kRMax];
-  __shared__ int btab[kTabCap];
-  constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;
+template <int D, int NS, bool ALONE>
+struct DkvLds {                      // (aligned to a tile where it is declared)
+  uint16_t st[NS][(ALONE ? 3 : 2) * 64 * D];      // stage: Q, dO (or K, V), O tile
+  float sstat[NS][4][32];            // stage, query tile: -LSE*log2e [16], Delta [16]
+  int rowtab[4 * kRMax];
+  int btab[kTabCap];
+};
+template <int D, int DT, int NS, bool WIDE, bool ALONE>
+__device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D, NS, ALONE>& sh) {
+  auto& st = sh.st;
+  auto& sstat = sh.sstat;
+  constexpr uint32_t kTile = 2 * 64 * D, kStage = (ALONE ? 3 : 2) * kTile;
   const int nkb = a.S / 64;
   PairWork pw;
-  if (!pair_work(a, pw)) return;
+  if (!pair_work(a, w, pw)) return;
   const int b = pw.b, h0 = pw.group * a.vheads;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, kl = 16 * wave + lane % 16;    // this lane's key inside the block
@@ -885,7 +905,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
   const uint32_t own_off = tile_off<D>(kl, 8 * g);
 
   RowSet rows;
-  rows.init(rowtab, a.crow_ptr, a.cnnz_cap, ((a.mask_batch == 1 ? 0 : b) * a.Hh + h0) * nkb, nkb,
+  rows.init(sh.rowtab, a.crow_ptr, a.cnnz_cap, ((a.mask_batch == 1 ? 0 : b) * a.Hh + h0) * nkb, nkb,
             a.vheads, h0, a.head_active, pw.z, a.gz, a.rows_per_wg, false);
   // key blocks used by no query block: zero gradients, nothing to read
   for (int j = 0; j < kRMax; ++j)
@@ -902,8 +922,8 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
   LaneOff16<D> lo;
   lo.init();
   const float sc = a.scale * kLog2e;
-  // lanes 0-15 of wave w bring -LSE*log2(e), lanes 16-31 Delta of queries 16w .. 16w+15 of a block
-  const float* stat_src = (lane < 16 ? a.NegLse2 : a.Delta) + 16 * wave + lane % 16;
+  // lanes 0-15 of wave w bring -LSE*log2(e), lanes 16-31 Delta of queries 16w .. 16w+15 of a block; ALONE: lanes 0-15 LSE
+  const float* stat_src = (ALONE ? a.LSEin : lane < 16 ? a.NegLse2 : a.Delta) + 16 * wave + lane % 16;
   int kb = 0;
   long long koff = 0;
   uint4 kf[D / 32], vf[D / 32];
@@ -921,7 +941,8 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
     const uint32_t dst = st_addr + stage * kStage;
     dma.issue(dst, a.Q + t0);
     dma.issue(dst + kTile, a.dO + t0);
-    if (lane < 32) dma4(stat_src + stat_of(hh) + qbk * 64, sstat_addr + stage * 512 + wave * 128);
+    if (ALONE) dma.issue(dst + 2 * kTile, a.O + t0);
+    if (lane < (ALONE ? 16 : 32)) dma4(stat_src + stat_of(hh) + qbk * 64, sstat_addr + stage * 512 + wave * 128);
   };
   auto row_begin = [&](int stage, int e) {
     kb = entry_blk(e);
@@ -938,6 +959,21 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
   auto comp = [&](int stage, int e) {
     const int col = entry_blk(e);
     const uint32_t stg = st_addr + stage * kStage;
+    if (ALONE) {      // the same sums in the same order as the query side's
+      const uint32_t o0 = stg + kTile + own_off;
+      float sum = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < D / 32; ++kk) {
+        const uint4 df = lds_read16(o0 ^ tile_off<D>(0, 32 * kk)), of = lds_read16((o0 + kTile) ^ tile_off<D>(0, 32 * kk));
+        sum = dot8<DT>(df, of, sum);
+      }
+      const float delta = sum_g(sum), lse = sstat[stage][wave][lane % 16];
+      if (g == 0) {
+        sstat[stage][wave][lane] = lse == -INFINITY ? -INFINITY : -(lse * kLog2e);
+        sstat[stage][wave][16 + lane] = delta;
+      }
+      lds_barrier();
+    }
     f32x4 s[4], dp[4];
     mma_rows16<D, DT>(stg, lo, kf, s);                   // S[q][key]
     mma_rows16<D, DT>(stg + kTile, lo, vf, dp);          // dP[q][key]
@@ -971,9 +1007,26 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
     store_acc16_asm<D, DT>(dv_acc, 1.f, a.dV + koff);
     store_acc16_asm<D, DT>(dk_acc, a.scale, a.dK + koff);
   };
-  walk_table<NS, 2 * TileDma<D, WIDE>::kPerWave, -1, 2 * TileDma<D, WIDE>::kPerWave + 1, 0, 2 * (D / 32)>(
-      btab, rows, a.ccol_idx, issue_own, NoAux(), issue_blk, row_begin, NoAux(), comp, row_end);
+  walk_table<NS, 2 * TileDma<D, WIDE>::kPerWave, -1, (ALONE ? 3 : 2) * TileDma<D, WIDE>::kPerWave + 1, 0, 2 * (D / 32)>(
+      sh.btab, rows, a.ccol_idx, issue_own, NoAux(), issue_blk, row_begin, NoAux(), comp, row_end);
 }
+template <int D, int DT, int NS, int OCC, bool WIDE>
+__global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) {
+  __shared__ __attribute__((aligned(2 * 64 * D))) DkvLds<D, NS, false> sh;
+  attn_bwd_dkv<D, DT, NS, WIDE, false>(a, blockIdx.x, sh);
+}
+
+// Both sides in one launch (bwd_in_one): the first `half` workgroups take the key side, which is the longer one.
+template <int D, int DT, int NS, int OCC, bool WIDE>
+__global__ __launch_bounds__(kAT, OCC) void attn_bwd_both_bf16(const AttnArgs a, int half) {
+  __shared__ __attribute__((aligned(2 * 64 * D))) DkvLds<D, NS, true> sh;
+  static_assert(sizeof(DqLds<D, NS>) <= sizeof(sh), "shared memory");
+  if ((int)blockIdx.x < half)
+    attn_bwd_dkv<D, DT, NS, WIDE, true>(a, blockIdx.x, sh);
+  else
+    attn_bwd_dq<D, DT, NS, WIDE>(a, blockIdx.x - half, reinterpret_cast<DqLds<D, NS>&>(sh));
+}
+
 
 // Rows per workgroup, unless the caller fixed the number: the smallest count with which all workgroups of the
 // launch are resident at once on the chip's `slots` workgroup slots (a causal mask keeps the groups balanced for
@@ -1046,8 +1099,33 @@ static hipError_t launch_fwd(const AttnArgs& a, int B, hipStream_t st) {
   return a.ss < kWideStride ? launch_fwd_t<D, DT, false>(a, B, st) : launch_fwd_t<D, DT, true>(a, B, st);
 }
 
+// Whether the two sides of a backward pass run in one launch.  The key side then makes Delta itself, for every block that
+// it streams, from O tiles of which the other two launches need none; and a CU has room for three workgroups (head size
+// 64) or one (128: three tiles a stage are 96 KB).  What it saves is the chain of loads that starts a launch, and a
+// launch that lasts as long as its longest row; so it pays while the rows of both sides are resident at about the same
+// time, two each: up to 768 rows of both heads and batch (1.3 - 1.6 times faster: 12 heads of 320 tokens 18 -> 12 us, 3 x
+// 32 of 512 21 -> 14, 10 of 3136 121 -> 75), with short rows up to 1728 (1.02 - 1.2; 16 heads of 4096, all blocks 0.97, 24
+// of 4096 0.88); head size 128 up to 256 (1.2 - 1.6; 384 rows 1.07, 512 0.96).  Results are the same to the last bit.
+// An output on the place of an input (dK on K, say), which the order of the launches allows, keeps them apart.
+constexpr int kBothOcc(int D) { return D == 64 ? 3 : 1; }
+static bool bwd_in_one(const AttnArgs& a, int D, int B) {
+  const int nblk = a.S / 64;
+  const long long rows = (long long)B * a.Hh * nblk;
+  if (D == 128 ? rows > 256 : rows > 768 && (rows > 1728 || rows * nblk > 20000)) return false;
+  for (const uint16_t* out : {a.dQ, a.dK, a.dV})
+    for (const uint16_t* in : {a.Q, a.K, a.V, a.O, a.dO})
+      if (out == in) return false;
+  return true;
+}
 template <int D, int DT, bool WIDE>
 static hipError_t launch_bwd_t(AttnArgs a, int B, hipStream_t st) {
+  if (bwd_in_one(a, D, B)) {
+    ProfScope ps(kKAttnDkv, st);
+    constexpr int kOcc = kBothOcc(D);
+    const int half = attn_grid(a, B, kCUs * kOcc / 2);
+    hipLaunchKernelGGL((attn_bwd_both_bf16<D, DT, 2, kOcc, WIDE>), dim3(2 * half), dim3(kAT), 0, st, a, half);
+    return hipGetLastError();
+  }
   {
     ProfScope ps(kKAttnDq, st);
     constexpr int kNs = D == 64 && !WIDE ? kDqNs64 : 2, kOcc = D == 64 && !WIDE ? kDqOcc64 : 2;

@@ -662,7 +662,7 @@ static void launch_dsd(DsdArgs a, size_t part_bytes, hipStream_t st) {
   a.GM = a.Tt / t.tm;
   a.GN = ceil_div(a.ncols, 64 * t.tn);
   const bool lean = dsd_lean(p.id, a.Tt, a.gt, a.GM, a.GN);
-  a.order = dsd_order(a.GM, a.GN, lean);
+  a.order = dsd_order(a.GM, a.GN, lean, a.ldw * a.ncols * 2);
   const dim3 grid(a.gt == a.Tt ? 8 * ceil_div(p.full, 8) + 8 * ceil_div((long long)p.rest * p.pieces, 8) : 8 * ceil_div(a.GM * a.GN, 8));
 #define LX_CALL(TL) hipLaunchKernelGGL((ffn_dsd<TL, DT, LORA>), grid, dim3(TL::kTileThreads), 0, st, a)
   if (lean)

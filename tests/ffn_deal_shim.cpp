@@ -10,9 +10,9 @@ int unit_of(int order, int GM, int GN, int w) {
   int chunk, rank;
   return dsd_unit(order, GM, GN, w, chunk, rank) ? chunk * GM + rank : -1;
 }
-int order_of(int Tt, int gt, int d, int nnz_cap) {
+int order_of(int Tt, int gt, int d, int Fb, int nnz_cap) {
   const int id = choose_dsd(Tt, gt, d, nnz_cap, 0, 0).id, GM = Tt / kTileInfo[id].tm, GN = ceil_div(d, 64 * kTileInfo[id].tn);
-  return dsd_order(GM, GN, dsd_lean(id, Tt, gt, GM, GN));
+  return dsd_order(GM, GN, dsd_lean(id, Tt, gt, GM, GN), 128ll * Fb * d);
 }
 // bit 0: the first product by tiles of one stage, bit 1: the second.
 int lean_of(int Tt, int gt, int d, int nnz_cap) {

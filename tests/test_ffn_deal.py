@@ -50,5 +50,5 @@ def test_quotients(L):
 
 def test_labels_of_the_gpu_cases(L):
     for _, Tt, gt, d, Fb, cap, lean, order, _ in CASES:
-        assert (L.lean_of(Tt, gt, d, cap), L.order_of(Tt, gt, d, cap)) == (lean, order), (Tt, gt, d, Fb)
+        assert (L.lean_of(Tt, gt, d, cap), L.order_of(Tt, gt, d, Fb, cap)) == (lean, order), (Tt, gt, d, Fb)
     assert {c[6] for c in CASES} == {0, 1, 2, 3} and {c[7] for c in CASES} == {BY_CHUNK, BY_RANK, UNRANKED}

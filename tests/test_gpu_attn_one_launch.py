@@ -1,0 +1,80 @@
+"""Attention backward of small calls: the query side and the key side in one launch.  An output on the place of an input
+keeps the two launches apart, so the two ways are compared bit for bit; the oracle holds the small ones (test_gpu_attn.py)."""
+import numpy as np
+import pytest
+
+from util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lx():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2510_15964_amd import lx
+    return lx
+
+
+@pytest.mark.parametrize("dtype,B,Hh,S,D,density,causal,mask_batch,layout", [
+    ("bf16", 1, 1, 64, 64, 1.0, True, 1, "bhsd"),        # one block
+    ("f16", 1, 1, 64, 128, 1.0, False, 1, "bhsd"),
+    ("bf16", 1, 12, 320, 64, 0.4, True, 1, "bhsd"),
+    ("bf16", 3, 5, 256, 128, 0.3, True, 3, "bshd"),
+    ("f16", 2, 7, 448, 64, 0.5, False, 2, "bshd"),
+    ("bf16", 3, 32, 512, 64, 0.2, True, 1, "bshd"),      # 768 rows: two per workgroup
+    ("bf16", 1, 8, 4096, 64, 0.3, True, 1, "bhsd"),      # 64 rows per head
+    ("bf16", 1, 3, 4160, 64, 0.2, True, 1, "bhsd"),      # more: dealt by their number
+    ("f16", 8, 36, 384, 64, 0.6, True, 1, "bhsd"),       # 1728 short rows
+    ("bf16", 4, 8, 512, 128, 1.0, True, 1, "bhsd"),      # 256 rows at head size 128
+    ("bf16", 1, 16, 1024, 128, 0.3, False, 1, "bshd"),
+])
+def test_one_launch_equals_two(lx, dtype, B, Hh, S, D, density, causal, mask_batch, layout):
+    import torch
+    nb = S // 64
+    rng = np.random.default_rng(S + D)
+    m = rng.random((mask_batch, Hh, nb, nb)) < density
+    if causal:
+        m &= np.tril(np.ones((nb, nb), bool))
+    m[:, 0, 0, :] = False                 # a query block without keys, a key block without queries
+    m[:, -1, :, nb // 2] = False
+    m[:, -1, nb - 1, 0] = True
+    mask = torch.from_numpy(m.astype(np.uint8)).cuda()
+    active = torch.ones(Hh, dtype=torch.uint8, device="cuda")
+    if Hh > 2:
+        active[1] = 0
+    g = torch.Generator(device="cuda").manual_seed(S)
+    tdt = dev(np.zeros(1, np.float32), dtype).dtype
+
+    def new(fill):
+        return fill((B, Hh, S, D)) if layout == "bhsd" else fill((B, S, Hh, D)).transpose(1, 2)
+
+    def like(x):
+        return torch.full_like(x, float("nan"))      # (keeps the strides)
+
+    Q, K, V, dO = (new(lambda sh: torch.randn(sh, device="cuda", generator=g).to(tdt)) for _ in range(4))
+    rows, cols = lx.lx_mask_compact_pair(mask)
+    O, LSE = like(Q), torch.empty((B, Hh, S), device="cuda")
+    scale = D ** -0.5
+    lx.lx_sparse_attn_fwd(Q, K, V, rows, scale, causal, O, LSE, mask_batch=mask_batch, head_active=active)
+    ws = torch.empty(lx.lx_sparse_attn_bwd_workspace_bytes(lx.LX_F16 if dtype == "f16" else lx.LX_BF16, B, Hh, S, D), dtype=torch.uint8,
+                     device="cuda")
+
+    def bwd(O, dQ, r):
+        dK, dV = like(K), like(V)
+        lx.lx_attn_set_rows_per_workgroup(r)
+        try:
+            lx.lx_sparse_attn_bwd_dx(Q, K, V, O, LSE, dO, rows, cols, scale, causal, dQ, dK, dV, ws, mask_batch=mask_batch,
+                                     head_active=active)
+        finally:
+            lx.lx_attn_set_rows_per_workgroup(0)
+        return dQ, dK, dV
+
+    for r in (0, 1, 3):
+        one = bwd(O, like(Q), r)
+        shared = torch.empty_like(O)
+        shared.copy_(O)
+        assert shared.stride() == O.stride()
+        two = bwd(shared, shared, r)
+        for a, b in zip(one, two):
+            assert torch.isfinite(a.float()).all() and torch.equal(a, b), r

@@ -23,11 +23,11 @@ def lx():
 CASES = [
     ("bf16", 66, 1, 1024, 48, 2851, 1, 1, 0.8),
     ("f16", 80, 1, 320, 48, 3443, 1, 2, 0.8),
-    ("bf16", 129, 1, 320, 24, 2788, 1, 0, 0.8),       # more groups than are ranked
+    ("bf16", 129, 1, 1600, 24, 2788, 1, 0, 0.8),       # more groups than are ranked
     ("bf16", 80, 1, 2048, 12, 275, 2, 0, 0.2),
     ("f16", 96, 1, 2048, 32, 2767, 3, 0, 0.8),
-    ("bf16", 49, 1, 1152, 20, 260, 0, 0, 0.2),        # chunks cut by an XCD's eighth
-    ("bf16", 100, 2, 1600, 16, 230, 0, 0, 0.25),
+    ("bf16", 49, 1, 1152, 40, 500, 0, 0, 0.2),        # chunks cut by an XCD's eighth
+    ("bf16", 100, 2, 1600, 24, 330, 0, 0, 0.25),
     ("bf16", 128, 1, 512, 40, 1000, 0, 1, 0.15),
     ("f16", 3, 1, 832, 40, 70, 0, 2, 0.5),
     ("bf16", 64, 1, 64, 1100, 70400, 0, 2, 0.01),     # 64 rows, a capacity beyond 16 bits
