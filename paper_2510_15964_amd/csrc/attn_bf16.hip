@@ -74,39 +74,49 @@ __device__ __forceinline__ constexpr int tswz(int row) {
   return D == 64 ? row & 7 : (row & 3) << 1 | ((row >> 2 ^ row >> 3) & 1) << 3 | (row >> 2 & 1);
 }
 
-// The DMA instructions this wave issues for one [64 x D] tile: a wave-uniform base per instruction and
-// one 32-bit offset per lane.  One instruction moves 1 KiB = 64*16/(2D) rows, up to eight, so the offsets
-// reach over token strides below kWideStride.  WIDE, for longer ones: a 64-bit address per lane.
-constexpr long long kWideStride = 1ll << 28;      // elements; 7 rows of 2 * 2^28 bytes and a row's 112 fit 32 bits
+// The DMA instructions this wave issues for one [64 x D] tile: one moves 1 KiB = 64*16/(2D) rows, up to eight.  All of them
+// have the tile's address as their wave-uniform base and a 32-bit offset per lane, which reaches over token strides below
+// kWideStride, and one assembly block steps their LDS address: a wavefront does nothing else while it issues them, once
+// per block.  (A base and an LDS address per instruction and 64-bit products for the tile's address were 85 scalar
+// instructions for the two tiles of a block instead of 31.  Forward / dQ / dK and dV, us: 32 heads of 4096 tokens, D = 128, half of
+// the blocks 102.9 / 132.9 / 164.2 -> 100.2 / 131.1 / 161.7; 16 of 4096, D = 64, all blocks 54.7 / 67.6 / 95.5 -> 53.6
+// / 66.0 / 93.5; over ten sizes 1.8 / 1.2 / 1.4 % less.)  WIDE, for longer strides: a 64-bit address per lane.
+constexpr long long kWideStride = 1ll << 25;      // elements; 63 rows of 2 * 2^25 bytes and a row's 240 fit 32 bits
 template <int D, bool WIDE>
 struct TileDma {
   static constexpr int kSlots = D / 8;            // 16-byte slots per row
   static constexpr int kRowsPer = 64 / kSlots;    // rows per DMA instruction
   static constexpr int kPerWave = 64 / kRowsPer / kAW;
   using Off = std::conditional_t<WIDE, long long, uint32_t>;
-  long long row0[kPerWave];                       // element offset of the instruction's first row
-  Off off[kPerWave];                              // bytes from there: row lane / kSlots, swizzled slot
+  Off off[kPerWave];                              // bytes from the tile's address: row, swizzled slot
   uint32_t wave_lds;
   __device__ __forceinline__ void init(long long ld) {
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     wave_lds = wave * 1024;
 #pragma unroll
     for (int u = 0; u < kPerWave; ++u) {
-      const int first = kRowsPer * (wave + kAW * u), row = first + lane / kSlots;
-      const int slot = (lane % kSlots) ^ tswz<D>(row);
-      row0[u] = first * ld;
-      off[u] = (Off)((lane / kSlots) * ld * 2) + slot * 16;
+      const int row = kRowsPer * (wave + kAW * u) + lane / kSlots, slot = (lane % kSlots) ^ tswz<D>(row);
+      off[u] = (Off)(row * ld * 2) + slot * 16;
     }
   }
-  // tile_addr: LDS byte address of the destination tile; g0: wave-uniform
-  __device__ __forceinline__ void issue(uint32_t tile_addr, const uint16_t* g0) const {
+  // tile_addr: LDS byte address of the destination tile; g0: wave-uniform.  (No memory clobber: see dma16_s.)
+  __device__ __forceinline__ void issue(uint32_t tile_addr, const char* g0) const {
+    const uint32_t to = tile_addr + wave_lds;
+    if constexpr (WIDE) {
 #pragma unroll
-    for (int u = 0; u < kPerWave; ++u) {
-      const uint32_t to = tile_addr + wave_lds + u * (kAW * 1024);
-      if constexpr (WIDE)
-        dma16(reinterpret_cast<const char*>(g0 + row0[u]) + off[u], to);
+      for (int u = 0; u < kPerWave; ++u) dma16(g0 + off[u], to + u * (kAW * 1024));
+    } else {
+#define LX_FIRST "s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %1"
+#define LX_NEXT(V) "\n\ts_add_u32 m0, m0, 4096\n\ts_nop 0\n\tglobal_load_lds_dwordx4 " V ", %1"
+      static_assert(kAW * 1024 == 4096 && (kPerWave == 2 || kPerWave == 4), "the assembly's steps");
+      if constexpr (kPerWave == 2)
+        asm volatile(LX_FIRST LX_NEXT("%3") ::"s"(to), "s"(g0), "v"(off[0]), "v"(off[1]) : "m0", "scc");
       else
-        dma16_s(g0 + row0[u], off[u], to);
+        asm volatile(LX_FIRST LX_NEXT("%3") LX_NEXT("%4") LX_NEXT("%5") ::"s"(to), "s"(g0), "v"(off[0]), "v"(off[1]),
+                     "v"(off[2]), "v"(off[3])
+                     : "m0", "scc");
+#undef LX_FIRST
+#undef LX_NEXT
     }
   }
 };
@@ -223,6 +233,23 @@ struct RowSet {
   __device__ __forceinline__ int rs(int k) const { return __builtin_amdgcn_readlane(reg, kRMax + k); }
   __device__ __forceinline__ int n(int k) const { return __builtin_amdgcn_readlane(reg, 2 * kRMax + k); }
   __device__ __forceinline__ int head(int k) const { return __builtin_amdgcn_readlane(reg, 3 * kRMax + k); }
+};
+
+// One 64-bit byte offset per row slot (its head's in a tensor), in the lanes of a register pair; with an entry's block added.
+struct SlotOffset {
+  uint32_t lo, hi;
+  template <class OfHead>
+  __device__ __forceinline__ void init(const RowSet& rows, OfHead of_head) {
+    const long long v = of_head(rows.tab[3 * kRMax + threadIdx.x % kRMax]);
+    lo = (uint32_t)v;
+    hi = (uint32_t)((unsigned long long)v >> 32);
+  }
+  // + blk blocks of `step` bytes; Step: uint32_t where a step fits it (two instructions for the product instead of four)
+  template <class Step>
+  __device__ __forceinline__ long long at(int slot, uint32_t blk, Step step) const {
+    const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)lo, slot), h = (uint32_t)__builtin_amdgcn_readlane((int)hi, slot);
+    return (long long)(((unsigned long long)h << 32 | l) + (unsigned long long)blk * step);
+  }
 };
 
 // ---------------------------------------------------------------------------
@@ -403,6 +430,7 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 // index, 24..26 row slot.
 // ---------------------------------------------------------------------------
 constexpr int kTabCap = 512;                       // entries per fill of the table
+constexpr int kTabInts = kTabCap + 4;              // its size: a walk reads up to a ring past the last entry
 constexpr int kEOwn = 1 << 30, kELast = 1 << 29, kEAux = 1 << 28;
 
 __device__ __forceinline__ int entry_blk(int e) { return e & 0xFFFFFF; }
@@ -523,13 +551,13 @@ __device__ __forceinline__ void walk_table(int* tab, const RowSet& rows, const i
     for (int i = 0; i < NS - 1; ++i)
       if (i < cnt) issue_entry(i, entry(i));
     unsigned hist = 0;                   // byte i: store instructions issued while entry t-1-i was consumed
-    int stage = 0, istage = NS - 1;      // stage of entry t, stage entry t + NS - 1 goes to
+    int stage = 0, istage = NS - 1;      // stage of entry t; that of t - 1, which entry t + NS - 1 goes to
     int q[NS];                           // entries t .. t + NS - 1, read from the table a step before they are needed
 #pragma unroll
-    for (int u = 0; u < NS; ++u) q[u] = entry(min(u, cnt - 1));
+    for (int u = 0; u < NS; ++u) q[u] = entry(u);
     for (int t = 0; t < cnt; ++t) {
       const int e = q[0];
-      const int ahead = tab[min(t + NS, cnt - 1)];
+      const int ahead = tab[t + NS];     // (past the end: not used)
       if constexpr (NS == 2) {           // what was issued since: the stores of the previous entry
         const unsigned st = hist & 0xFF;
         if (st == 0)
@@ -563,8 +591,8 @@ __device__ __forceinline__ void walk_table(int* tab, const RowSet& rows, const i
         }
       }
       hist = (hist << 8) | (unsigned)stores;
-      stage = stage + 1 == NS ? 0 : stage + 1;
-      istage = istage + 1 == NS ? 0 : istage + 1;
+      istage = stage;
+      stage = NS == 2 ? stage ^ 1 : stage + 1 == NS ? 0 : stage + 1;
 #pragma unroll
       for (int u = 0; u < NS - 1; ++u) q[u] = q[u + 1];
       q[NS - 1] = __builtin_amdgcn_readfirstlane(ahead);
@@ -617,7 +645,7 @@ template <int D, int DT, int NS, int OCC, bool WIDE>
 __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   __shared__ __attribute__((aligned(2 * 64 * D))) uint16_t st[NS][2 * 64 * D];   // stage: K tile, V tile
   __shared__ int rowtab[4 * kRMax];
-  __shared__ int btab[kTabCap];
+  __shared__ int btab[kTabInts];
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;   // bytes
   const int nqb = a.S / 64;
   PairWork pw;
@@ -645,6 +673,13 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
 
   TileDma<D, WIDE> dma;
   dma.init(a.ss);
+  using Step = std::conditional_t<WIDE, unsigned long long, uint32_t>;
+  SlotOffset heads;
+  heads.init(rows, [&](int hh) { return 2 * base_of(hh); });
+  // tensor p's tile of an entry
+  auto tile_of = [&](const uint16_t* p, int e) {
+    return reinterpret_cast<const char*>(p) + heads.at(entry_slot(e), entry_blk(e), (Step)(128 * a.ss));
+  };
   LaneOff16<D> lo;
   lo.init();
   const float sc = a.scale * kLog2e;
@@ -655,14 +690,12 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   float m = -INFINITY, m_use = 0.f, lsum = 0.f;   // reference point of the query (0 for -inf); this lane's share of its sum
 
   auto issue_own = [&](int stage, int e) {
-    const long long t0 = base_of(rows.head(entry_slot(e))) + (long long)entry_blk(e) * 64 * a.ss;
-    dma.issue(st_addr + stage * kStage, a.Q + t0);
+    dma.issue(st_addr + stage * kStage, tile_of(a.Q, e));
   };
   auto issue_blk = [&](int stage, int e) {
-    const long long t0 = base_of(rows.head(entry_slot(e))) + (long long)entry_blk(e) * 64 * a.ss;
     const uint32_t dst = st_addr + stage * kStage;
-    dma.issue(dst, a.K + t0);
-    dma.issue(dst + kTile, a.V + t0);
+    dma.issue(dst, tile_of(a.K, e));
+    dma.issue(dst + kTile, tile_of(a.V, e));
   };
   auto row_begin = [&](int stage, int e) {
     qb = entry_blk(e);
@@ -752,7 +785,7 @@ struct DqLds {                       // (aligned to a tile where it is declared)
   uint16_t st[NS][2 * 64 * D];       // stage: K, V (or Q, dO; or O) tile
   float slse[NS][4][16];             // stage, wavefront: LSE of its 16 own rows
   int rowtab[4 * kRMax];
-  int btab[kTabCap];
+  int btab[kTabInts];
 };
 template <int D, int DT, int NS, bool WIDE>
 __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, NS>& sh) {
@@ -788,6 +821,13 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
 
   TileDma<D, WIDE> dma;
   dma.init(a.ss);
+  using Step = std::conditional_t<WIDE, unsigned long long, uint32_t>;
+  SlotOffset heads;
+  heads.init(rows, [&](int hh) { return 2 * base_of(hh); });
+  // tensor p's tile of an entry
+  auto tile_of = [&](const uint16_t* p, int e) {
+    return reinterpret_cast<const char*>(p) + heads.at(entry_slot(e), entry_blk(e), (Step)(128 * a.ss));
+  };
   LaneOff16<D> lo;
   lo.init();
   const float sc = a.scale * kLog2e;
@@ -799,23 +839,21 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   f32x4 dq_acc[D / 16];
 
   auto issue_own = [&](int stage, int e) {
-    const long long t0 = base_of(rows.head(entry_slot(e))) + (long long)entry_blk(e) * 64 * a.ss;
     const uint32_t dst = st_addr + stage * kStage;
-    dma.issue(dst, a.Q + t0);
-    dma.issue(dst + kTile, a.dO + t0);
+    dma.issue(dst, tile_of(a.Q, e));
+    dma.issue(dst + kTile, tile_of(a.dO, e));
   };
   // the row's O tile, needed once for Delta = rowsum(dO . O), and the LSE of its 64 queries
   // (lanes 0-15 of wavefront w bring those of its own rows 16w .. 16w+15)
   auto issue_aux = [&](int stage, int e) {
     const int hh = rows.head(entry_slot(e)), blk = entry_blk(e);
-    dma.issue(st_addr + stage * kStage, a.O + base_of(hh) + (long long)blk * 64 * a.ss);
+    dma.issue(st_addr + stage * kStage, tile_of(a.O, e));
     if (lane < 16) dma4(a.LSEin + stat_of(hh) + blk * 64 + ql, slse_addr + stage * 256 + wave * 64);
   };
   auto issue_blk = [&](int stage, int e) {
-    const long long t0 = base_of(rows.head(entry_slot(e))) + (long long)entry_blk(e) * 64 * a.ss;
     const uint32_t dst = st_addr + stage * kStage;
-    dma.issue(dst, a.K + t0);
-    dma.issue(dst + kTile, a.V + t0);
+    dma.issue(dst, tile_of(a.K, e));
+    dma.issue(dst + kTile, tile_of(a.V, e));
   };
   auto row_begin = [&](int stage, int e) {
     qb = entry_blk(e);
@@ -886,7 +924,7 @@ struct DkvLds {                      // (aligned to a tile where it is declared)
   uint16_t st[NS][(ALONE ? 3 : 2) * 64 * D];      // stage: Q, dO (or K, V), O tile
   float sstat[NS][4][32];            // stage, query tile: -LSE*log2e [16], Delta [16]
   int rowtab[4 * kRMax];
-  int btab[kTabCap];
+  int btab[kTabInts];
 };
 template <int D, int DT, int NS, bool WIDE, bool ALONE>
 __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D, NS, ALONE>& sh) {
@@ -919,30 +957,36 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
 
   TileDma<D, WIDE> dma;
   dma.init(a.ss);
+  using Step = std::conditional_t<WIDE, unsigned long long, uint32_t>;
+  SlotOffset heads;
+  heads.init(rows, [&](int hh) { return 2 * base_of(hh); });
+  // tensor p's tile of an entry
+  auto tile_of = [&](const uint16_t* p, int e) {
+    return reinterpret_cast<const char*>(p) + heads.at(entry_slot(e), entry_blk(e), (Step)(128 * a.ss));
+  };
   LaneOff16<D> lo;
   lo.init();
   const float sc = a.scale * kLog2e;
   // lanes 0-15 of wave w bring -LSE*log2(e), lanes 16-31 Delta of queries 16w .. 16w+15 of a block; ALONE: lanes 0-15 LSE
-  const float* stat_src = (ALONE ? a.LSEin : lane < 16 ? a.NegLse2 : a.Delta) + 16 * wave + lane % 16;
+  const char* stat_src = reinterpret_cast<const char*>((ALONE ? a.LSEin : lane < 16 ? a.NegLse2 : a.Delta) + 16 * wave + lane % 16);
+  SlotOffset stats;
+  stats.init(rows, [&](int hh) { return 4 * stat_of(hh); });
   int kb = 0;
   long long koff = 0;
   uint4 kf[D / 32], vf[D / 32];
   f32x4 dk_acc[D / 16], dv_acc[D / 16];
 
   auto issue_own = [&](int stage, int e) {
-    const long long t0 = base_of(rows.head(entry_slot(e))) + (long long)entry_blk(e) * 64 * a.ss;
     const uint32_t dst = st_addr + stage * kStage;
-    dma.issue(dst, a.K + t0);
-    dma.issue(dst + kTile, a.V + t0);
+    dma.issue(dst, tile_of(a.K, e));
+    dma.issue(dst + kTile, tile_of(a.V, e));
   };
   auto issue_blk = [&](int stage, int e) {
-    const int hh = rows.head(entry_slot(e)), qbk = entry_blk(e);
-    const long long t0 = base_of(hh) + (long long)qbk * 64 * a.ss;
     const uint32_t dst = st_addr + stage * kStage;
-    dma.issue(dst, a.Q + t0);
-    dma.issue(dst + kTile, a.dO + t0);
-    if (ALONE) dma.issue(dst + 2 * kTile, a.O + t0);
-    if (lane < (ALONE ? 16 : 32)) dma4(stat_src + stat_of(hh) + qbk * 64, sstat_addr + stage * 512 + wave * 128);
+    dma.issue(dst, tile_of(a.Q, e));
+    dma.issue(dst + kTile, tile_of(a.dO, e));
+    if (ALONE) dma.issue(dst + 2 * kTile, tile_of(a.O, e));
+    if (lane < (ALONE ? 16 : 32)) dma4(stat_src + stats.at(entry_slot(e), entry_blk(e), 256u), sstat_addr + stage * 512 + wave * 128);
   };
   auto row_begin = [&](int stage, int e) {
     kb = entry_blk(e);
