@@ -22,15 +22,10 @@ constexpr int kStageBytes = 32768;  // mask bytes staged in LDS per pass
 // because a wavefront that walks rows straight from global memory pays one full memory
 // latency per row; the ballots then run out of LDS.
 
-constexpr int kMaxJobs = 8;
-struct CompactJobs {
-  CompactJob j[kMaxJobs];
-};
-
 // How the bytes of a job lie: the rows of all masks one after the other, or every mask contiguous in
 // the other orientation (the column list of contiguous masks), or anything else.
 enum MaskLayout { kRowMajor, kColMajor, kStrided };
-__host__ __device__ inline MaskLayout mask_layout(const CompactJob& j) {
+inline MaskLayout mask_layout(const CompactJob& j) {
   const bool whole = j.batch == 1 || j.bstride == (long long)j.rows * j.cols;
   if (whole && j.cstride == 1 && j.rstride == j.cols) return kRowMajor;
   if (whole && j.rstride == 1 && j.cstride == j.rows) return kColMajor;
@@ -47,8 +42,10 @@ __host__ __device__ inline MaskLayout mask_layout(const CompactJob& j) {
 // one by one for the column list, 7 so.  Strided bytes are slow to count, so those parts are larger.
 struct CompactParts {
   int parts, rows;      // rows per part
+  int chunk;            // rows per pass
+  int layout, colmajor; // MaskLayout; whether whole masks in the other orientation are staged as they lie
 };
-__host__ __device__ inline CompactParts compact_parts(const CompactJob& j) {
+inline CompactParts compact_parts(const CompactJob& j) {
   const long long total = (long long)j.batch * j.rows;
   const MaskLayout lay = mask_layout(j);
   const bool masks = lay != kStrided && j.batch > 1 && j.rows <= kChunkRows && (long long)j.rows * j.cols <= kStageBytes;
@@ -59,8 +56,26 @@ __host__ __device__ inline CompactParts compact_parts(const CompactJob& j) {
   p = p > (fast ? 64 : 16) ? (fast ? 64 : 16) : p;
   p = p > units ? units : p < 1 ? 1 : p;
   const long long per = (units + p - 1) / p;
-  return {(int)((units + per - 1) / per), (int)per * unit};
+  CompactParts c = {(int)((units + per - 1) / per), (int)per * unit, 1, lay, 0};
+  c.colmajor = lay == kColMajor && j.rows <= kChunkRows && (long long)j.rows * j.cols <= kStageBytes && c.rows % j.rows == 0;
+  if (c.colmajor) {
+    const int masks_fit = kStageBytes / (j.rows * j.cols), by_rows = kChunkRows / j.rows;
+    c.chunk = (masks_fit < by_rows ? masks_fit : by_rows) * j.rows;
+  } else if (j.cols <= kStageBytes) {
+    const int fit = kStageBytes / j.cols;
+    c.chunk = fit < 1 ? 1 : fit < kChunkRows ? fit : kChunkRows;
+  }
+  return c;
 }
+constexpr int kMaxJobs = 8;
+// The parts are the host's to compute: some dozen divisions, half of them of 64 bits, took a workgroup as long as a load.
+// Without them, with the first chunk's bytes loaded while those before it are counted and without the division per byte of the other
+// orientation, us: one list of 64 x 128 bytes 8.1 -> 7.2, the three of a layer (128 x 128; 32 heads of 16 x 16, both
+// orientations) 9.1 -> 7.3, both of 32 heads of 32 x 32 8.5 -> 7.8, one row of 48 bytes 4.1 -> 3.7.
+struct CompactJobs {
+  CompactJob j[kMaxJobs];
+  CompactParts p[kMaxJobs];
+};
 
 // Walks the flattened (batch, row, column) index space of a job in steps of kCompactThreads
 // elements without dividing per element (a 32-bit division costs some forty vector instructions,
@@ -119,23 +134,27 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
   __shared__ __attribute__((aligned(16))) uint8_t stage[kStageBytes + 16];
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const int total_rows = batch * rows;
-  const CompactParts cparts = compact_parts(job);
+  const CompactParts cparts = jobs.p[blockIdx.x];
   const int parts = cparts.parts, part = blockIdx.y;
   if (part >= parts) return;
   const int row_lo = min(part * cparts.rows, total_rows), row_hi = min(row_lo + cparts.rows, total_rows);
-  const MaskLayout layout = mask_layout(job);
-  const bool rowmajor = layout == kRowMajor;
-  // whole masks in the other orientation: staged as they lie
-  const bool colmajor = layout == kColMajor && rows <= kChunkRows && (long long)rows * cols <= kStageBytes &&
-                        cparts.rows % rows == 0;
-  const bool staged = cols <= kStageBytes;
-  const int chunk_rows = colmajor ? min(kChunkRows / rows, kStageBytes / (rows * cols)) * rows
-                         : staged ? max(1, min(kChunkRows, kStageBytes / cols)) : 1;
+  const bool rowmajor = cparts.layout == kRowMajor, colmajor = cparts.colmajor != 0, staged = cols <= kStageBytes;
+  const int chunk_rows = cparts.chunk;
+  const float per_row = 1.f / (float)rows;
   int cp = kWave;                       // columns handled per wave pass (power of two)
   while (cp > 1 && (cp >> 1) >= cols) cp >>= 1;
   const int rpw = kWave / cp;           // rows per wave pass
   const int sub = lane / cp, cl = lane % cp;
   const unsigned long long field = cp == 64 ? ~0ull : ((1ull << cp) - 1ull);
+  // this thread's 16 bytes of the first aligned ones in a contiguous range
+  auto first_vec = [&](const uint8_t* src, int len) {
+    const int head = min((16 - (int)(reinterpret_cast<uintptr_t>(src) & 15)) & 15, len);
+    return tid < (len - head) / 16 ? reinterpret_cast<const uint4*>(src + head)[tid] : make_uint4(0, 0, 0, 0);
+  };
+  // the first chunk's bytes are loaded while those before them are counted
+  const bool range = colmajor || (staged && rowmajor);
+  uint4 ahead = make_uint4(0, 0, 0, 0);
+  if (range) ahead = first_vec(mask + (long long)row_lo * cols, min(chunk_rows, row_hi - row_lo) * cols);
   int carry = 0;
   if (row_lo > 0) {      // active entries of the rows before this part
     const long long before = (long long)row_lo * cols;
@@ -146,7 +165,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
     // starts in, masks with other strides) byte by byte below.
     long long done = 0;
     const long long nbytes = rowmajor ? before
-                             : layout == kColMajor ? (long long)(row_lo / rows) * rows * cols : 0;
+                             : cparts.layout == kColMajor ? (long long)(row_lo / rows) * rows * cols : 0;
     if (nbytes > 0) {
       long long head = (16 - (long long)(reinterpret_cast<uintptr_t>(mask) & 15)) & 15;
       head = head < nbytes ? head : nbytes;
@@ -172,7 +191,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
     }
     constexpr int kBatch = 8;
     MaskCursor cur;
-    cur.init(done + tid, rows, cols);
+    if (done < before) cur.init(done + tid, rows, cols);
     for (long long i0 = done + tid; i0 < before; i0 += (long long)kCompactThreads * kBatch) {
       uint8_t v[kBatch];
 #pragma unroll
@@ -195,17 +214,18 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
   for (int chunk = row_lo; chunk < row_hi; chunk += chunk_rows) {
     const int n = min(chunk_rows, row_hi - chunk);
     int soff = 0;          // where the chunk's first byte sits in `stage`
-    if (colmajor || (staged && rowmajor)) {
+    if (range) {
       // a contiguous range: 16 bytes per load, placed so that source and stage are aligned alike
       const uint8_t* __restrict__ src = mask + (long long)chunk * cols;
       const int len = n * cols;
       soff = (int)(reinterpret_cast<uintptr_t>(src) & 15);
-      const int head = min((16 - soff) & 15, len);
+      const int head = min((16 - soff) & 15, len), nvec = (len - head) / 16;
+      if (chunk > row_lo) ahead = first_vec(src, len);
       if (tid < head) stage[soff + tid] = src[tid];
-      const int nvec = (len - head) / 16;
       const uint4* __restrict__ vp = reinterpret_cast<const uint4*>(src + head);
       uint4* sp = reinterpret_cast<uint4*>(stage + soff + head);
-      for (int i = tid; i < nvec; i += kCompactThreads) sp[i] = vp[i];
+      if (tid < nvec) sp[tid] = ahead;
+      for (int i = tid + kCompactThreads; i < nvec; i += kCompactThreads) sp[i] = vp[i];
       const int tail = head + nvec * 16;                   // fewer than 16 bytes remain
       if (tail + tid < len) stage[soff + tail + tid] = src[tail + tid];
       __syncthreads();
@@ -230,7 +250,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
     auto is_on = [&](int r, int c) -> bool {
       if (c >= cols) return false;
       if (colmajor) {
-        const int q = r / rows;
+        const int q = (int)(((float)r + 0.5f) * per_row);      // r / rows: r < 4096, so the product errs by less than 0.5 / rows
         return stage[soff + q * rows * cols + c * rows + (r - q * rows)] != 0;
       }
       if (staged) return stage[soff + r * cols + c] != 0;
@@ -309,8 +329,8 @@ hipError_t launch_compact_jobs(const CompactJob* jobs, int n, hipStream_t stream
   int parts = 1;
   for (int i = 0; i < n; ++i) {
     js.j[i] = jobs[i];
-    const int p = compact_parts(jobs[i]).parts;
-    parts = p > parts ? p : parts;
+    js.p[i] = compact_parts(jobs[i]);
+    parts = js.p[i].parts > parts ? js.p[i].parts : parts;
   }
   ProfScope ps(kKCompact, stream);
   hipLaunchKernelGGL(compact_kernel, dim3(n, parts), dim3(kCompactThreads), 0, stream, js);
