@@ -323,6 +323,40 @@ __device__ __forceinline__ void tn_step(uint32_t stage, const TnLane& lo, f32x16
   for (int i = 0; i < 2; ++i) acc = mfma32<DT>(a[i], b[i], acc);
 }
 
+// The token tiles i_lo .. i_hi - 1, at most kThreads of them, whose list holds neuron block j: calls put(place in their
+// order, tile, compact activation block) in one thread each, returns their number to all.  wcount: kFW ints of LDS.
+template <class Put>
+__device__ __forceinline__ int listed_tiles(const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int gt, int nnz_cap,
+                                            int j, int i_lo, int i_hi, int* wcount, Put put) {
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, i = i_lo + (int)threadIdx.x;
+  long long blk = -1;
+  if (i < i_hi) {
+    const int rs = row_ptr[i / gt];
+    int lo_ = 0, hi_ = min(row_ptr[i / gt + 1], nnz_cap) - rs;   // entries beyond the capacity are ignored
+    while (lo_ < hi_) {
+      const int mid = (lo_ + hi_) / 2, c = col_idx[rs + mid];
+      if (c == j) {
+        blk = ((long long)rs + mid) * gt + i % gt;
+        break;
+      }
+      if (c < j) lo_ = mid + 1; else hi_ = mid;
+    }
+  }
+  const unsigned long long hit = __ballot(blk >= 0);
+  if (lane == 0) wcount[wave] = __popcll(hit);
+  __syncthreads();
+  int before = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kFW; ++w) {
+    const int c = wcount[w];
+    if (w < wave) before += c;
+    total += c;
+  }
+  if (blk >= 0) put(before + __popcll(hit & ((1ull << lane) - 1ull)), i, blk);
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(total);
+}
+
 // Gradients of the two LoRA matrices (Sec. II-D), fp32, as sums of 64 x 64 products
 // out[a][b] = sum over steps of sum_t P[t][a] Q[t][b] on the MFMA:
 // MODE 0, dB = dZ^T U over the listed blocks: x = neuron block j; the steps are the
@@ -353,8 +387,7 @@ __device__ __forceinline__ void lora_tn(const TnArgs& args, int x, int y, const 
   const long long ldq = args.ldq;
   uint16_t* ring = sh.ring;
   long long *s_p = sh.p, *s_q = sh.q;
-  int* wcount = sh.wcount;
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int per = (Tt + args.ny - 1) / args.ny;
   const int i_lo = y * per, i_hi = min(Tt, i_lo + per);
   const int ah = wave % 2, bh = (wave / 2) % 2;
@@ -375,39 +408,13 @@ __device__ __forceinline__ void lora_tn(const TnArgs& args, int x, int y, const 
         },
         ring, step);
   } else {
-    // one tile per thread: the host splits so that a range holds at most kThreads tiles
-    const int j = x, i = i_lo + tid;
-    long long blk = -1;   // compact activation block of (tile i, block j)
-    if (i < i_hi) {
-      const int rs = row_ptr[i / gt];
-      int lo_ = 0, hi_ = min(row_ptr[i / gt + 1], nnz_cap) - rs;   // entries beyond the capacity are ignored
-      while (lo_ < hi_) {
-        const int mid = (lo_ + hi_) / 2, c = col_idx[rs + mid];
-        if (c == j) {
-          blk = ((long long)rs + mid) * gt + i % gt;
-          break;
-        }
-        if (c < j) lo_ = mid + 1; else hi_ = mid;
-      }
-    }
-    const unsigned long long hit = __ballot(blk >= 0);
-    if (lane == 0) wcount[wave] = __popcll(hit);
-    __syncthreads();
-    int before = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < kFW; ++w) {
-      const int c = wcount[w];
-      if (w < wave) before += c;
-      total += c;
-    }
-    if (blk >= 0) {
-      const int idx = before + __popcll(hit & ((1ull << lane) - 1ull));
-      s_p[idx] = blk * 4096;
-      s_q[idx] = (long long)i * 64 * ldq;
-    }
-    __syncthreads();
+    // (the host splits so that a range holds at most kThreads tiles)
+    const int total = listed_tiles(row_ptr, col_idx, gt, nnz_cap, x, i_lo, i_hi, sh.wcount, [&](int k, int i, long long blk) {
+      s_p[k] = blk * 4096;
+      s_q[k] = (long long)i * 64 * ldq;
+    });
     run_ring_of<kPairStages, 2, kPairElems>(
-        __builtin_amdgcn_readfirstlane(total), src,
+        total, src,
         [&](int s, long long& ob, long long& oa) {
           ob = s_p[s];
           oa = s_q[s];
@@ -442,6 +449,127 @@ __global__ __launch_bounds__(kThreads) void lora_tn_kernel(TnArgs db, TnArgs da,
   else
     lora_tn<DT, 1>(da, w_a % da.nx, w_a / da.nx, row_ptr, col_idx, Tt, gt, nnz_cap, sh);
 }
+// Few token tiles: a workgroup per 32 x 32 quadrant of a product, whose eight wavefronts take a range of its token tiles
+// each, in steps of 32 token rows through stages of their own (4 KB, no barrier), and add up through LDS in a fixed
+// order: there are no parts in memory and no launch that adds them.  The quadrants of a product sit eight
+// workgroups apart, on one XCD.  What bounds it is latency while all workgroups are resident at once, two per CU, and
+// their number times the tiles beyond that.  G, both gradients and the sums, us, by parts and by quadrants (F = 4 d): 3
+// tiles, d = 768 17.1 / 13.3; 8, 1024 23.8 / 15.3; 16, 2048 25.3 / 19.7; 32, 2048 26.0 / 21.1; 64, 768 27.2 / 22.0; 64, 2048
+// 28.8 / 26.5; 16, 5120 28.8 / 27.4; past the line 64, 2560 32.0 / 29.5; 32, 5120 34.4 / 36.2; 64, 5120 41.5 / 53.5; 128, 768
+// 30.7 / 32.0; 128, 2048 40.6 / 44.0; 256, 512 35.2 / 52.9.  Errors of dA and dB against 64 bits over eleven sizes are 0.91 - 1 and
+// 0.87 - 1 times those by parts.
+inline bool grads_by_quads(int Tt, int d, int F) { return Tt <= 64 && (long long)Tt * (d / 64 + F / 64) <= 12000; }
+constexpr int kTnQuadStages = 2, kTnQuadStage = 4096;
+struct TnQuadLds {
+  uint8_t ring[kFW * kTnQuadStages * kTnQuadStage];     // (the sums at the end: 32 KB)
+  int tile[kThreads], wcount[kFW];
+  long long blk[kThreads];
+};
+constexpr int tn_quads(int nx) { return 32 * ((nx + 7) / 8); }
+template <int DT, int MODE>
+__device__ __forceinline__ void lora_tn_quad(const TnArgs& args, int w, const int* __restrict__ row_ptr,
+                                             const int* __restrict__ col_idx, int Tt, int gt, int nnz_cap, TnQuadLds& sh) {
+  const int x = w / 32 * 8 + w % 8, quad = w / 8 % 4;
+  if (x >= args.nx) return;
+  const int ah = quad % 2, bh = quad / 2;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int tiles = Tt;
+  if (MODE == 0)
+    tiles = listed_tiles(row_ptr, col_idx, gt, nnz_cap, x, 0, Tt, sh.wcount, [&](int k, int i, long long blk) {
+      sh.tile[k] = i;
+      sh.blk[k] = blk;
+    });
+  const int per = (tiles + kFW - 1) / kFW, t_lo = min(wave * per, tiles), n = 2 * (min(tiles, t_lo + per) - t_lo);
+  // 16 rows of 64 bytes per transfer, two for P and two for Q; slot c (16 bytes) of row r sits at 64 r + 16 (c ^ (r / 2) % 4)
+  const int tr = lane / 4, tc = (lane % 4) ^ ((tr / 2) % 4);
+  const uint32_t p_off = (uint32_t)(tr * 128 + tc * 16), q_off = (uint32_t)(tr * args.ldq * 2 + tc * 16);
+  const uint32_t ring = lds_addr(sh.ring) + wave * (kTnQuadStages * kTnQuadStage);
+  auto issue = [&](int s) {
+    const uint32_t to = ring + (s % kTnQuadStages) * kTnQuadStage;
+    const int k = t_lo + s / 2, half = 32 * (s % 2);
+    long long blk = k, i = k;
+    if (MODE == 0) {
+      i = __builtin_amdgcn_readfirstlane(sh.tile[k]);
+      blk = (long long)__builtin_amdgcn_readfirstlane((int)(sh.blk[k] >> 32)) << 32 |
+            (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.blk[k]);
+    }
+    const uint16_t* p = args.P + blk * 4096 + half * 64 + 32 * ah;
+    const uint16_t* q = args.Q + (i * 64 + half) * args.ldq + (MODE == 1 ? x * 64 : 0) + 32 * bh;
+    dma16_s(p, p_off, to);
+    dma16_s(p + 16 * 64, p_off, to + 1024);
+    dma16_s(q, q_off, to + 2048);
+    dma16_s(q + 16 * args.ldq, q_off, to + 3072);
+  };
+  // operands: column 16*((lane/16)%2) + lane%16 of the rows 16e + 4*(lane/32) .. + 3 and those eight further on
+  const int h2 = lane / 32, j = lane % 16, c = 2 * ((lane / 16) % 2) + (j % 4) / 2;
+  uint32_t off[2][2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int k = 16 * e + 8 * u + 4 * h2 + j / 4;
+      off[e][u] = ring + k * 64 + ((c ^ ((k / 2) % 4)) << 4) + (j % 2) * 8;
+    }
+  // the halves of a tile are summed apart, as by parts: shorter sums, smaller errors, and products that need not wait
+  f32x16 acc, odd;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = odd[v] = 0.f;
+  for (int s = 0; s < kTnQuadStages; ++s)
+    if (s < n) issue(s);
+  auto step = [&](int s, f32x16& sum) {
+    wait_tail<4, kTnQuadStages - 1>(min(n - 1 - s, kTnQuadStages - 1));    // younger steps in flight
+    asm volatile("" ::: "memory");
+    const uint32_t st = (s % kTnQuadStages) * kTnQuadStage;
+    uint4 a[2], b[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const uint2 al = lds_read8_tr(off[e][0] + st), au = lds_read8_tr(off[e][1] + st);
+      const uint2 bl = lds_read8_tr(off[e][0] + st + 2048), bu = lds_read8_tr(off[e][1] + st + 2048);
+      a[e] = make_uint4(al.x, al.y, au.x, au.y);
+      b[e] = make_uint4(bl.x, bl.y, bu.x, bu.y);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read
+    if (s + kTnQuadStages < n) issue(s + kTnQuadStages);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) sum = mfma32<DT>(a[e], b[e], sum);
+  };
+  for (int s = 0; s < n; s += 2) {
+    step(s, acc);
+    step(s + 1, odd);
+  }
+  float* area = reinterpret_cast<float*>(sh.ring);
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < 16; ++v) area[(wave * 16 + v) * kWave + lane] = acc[v] + odd[v];
+  __syncthreads();
+  // element v of lane l: row 32*ah + 8*(v/4) + 4*(l/32) + v%4, column 32*bh + l%32
+  float* o = args.part + ((MODE == 0 ? x * 64ll : 0) + 32 * ah) * args.ld_out + (MODE == 1 ? x * 64 : 0) + 32 * bh;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int v = wave + kFW * u;
+    float sum[kFW];
+#pragma unroll
+    for (int q = 0; q < kFW; ++q) sum[q] = area[(q * 16 + v) * kWave + lane];
+#pragma unroll
+    for (int n2 = 1; n2 < kFW; n2 *= 2)     // by pairs: smaller errors than one after the other
+#pragma unroll
+      for (int q = 0; q < kFW; q += 2 * n2) sum[q] += sum[q + n2];
+    o[(8 * (v / 4) + 4 * (lane / 32) + v % 4) * (long long)args.ld_out + lane % 32] = sum[0];
+  }
+}
+template <int DT>
+__global__ __launch_bounds__(kThreads, 4) void lora_tn_quad_kernel(TnArgs db, TnArgs da, const int* __restrict__ row_ptr,
+                                                                   const int* __restrict__ col_idx, int Tt, int gt, int nnz_cap) {
+  __shared__ __attribute__((aligned(1024))) TnQuadLds sh;
+  const int nb = tn_quads(db.nx), na = tn_quads(da.nx);
+  const bool db_first = gt == Tt;
+  const int w = blockIdx.x, w_b = db_first ? w : w - na, w_a = db_first ? w - nb : w;
+  if (db_first ? w < nb : w >= na)
+    lora_tn_quad<DT, 0>(db, w_b, row_ptr, col_idx, Tt, gt, nnz_cap, sh);
+  else
+    lora_tn_quad<DT, 1>(da, w_a, row_ptr, col_idx, Tt, gt, nnz_cap, sh);
+}
+
 // dB and dA = sums of their parts, in order, four elements per thread; a result with one part
 // was written in place and has n4 = 0 here.
 __global__ void lora_grad_reduce_kernel(const float* __restrict__ part_b, int parts_b, long long n4_b,
@@ -504,13 +632,19 @@ hipError_t launch_lora_g(int dt, int Tt, int gt, int d, const uint16_t* dZ, cons
 }
 
 // dB = dZ^T U over the listed blocks and dA = G^T X.  Scratch: da_part [lora_da_split][64][d] and
-// db_part [lora_db_split][F][64] (each unused for a split of 1).
+// db_part [lora_db_split][F][64] (each unused for a split of 1, both by quadrants).
 template <int DT>
 static hipError_t launch_lora_grads_t(int Tt, int gt, int d, int F, const uint16_t* dZ,
                                       const uint16_t* U, const uint16_t* G, const uint16_t* X,
                                       const int* row_ptr, const int* col_idx, int nnz_cap,
                                       float* da_part, float* db_part, float* dA, float* dB,
                                       hipStream_t st) {
+  if (grads_by_quads(Tt, d, F)) {
+    const TnArgs db = {dZ, U, 64, dB, 0, 64, F / 64, 1}, da = {G, X, d, dA, 0, d, d / 64, 1};
+    hipLaunchKernelGGL(lora_tn_quad_kernel<DT>, dim3(tn_quads(db.nx) + tn_quads(da.nx)), dim3(kThreads), 0, st, db, da,
+                       row_ptr, col_idx, Tt, gt, nnz_cap);
+    return hipGetLastError();
+  }
   const int sb = lora_db_split(Tt, F), sa = lora_da_split(Tt, d);
   const long long nb = (long long)F * 64, na = (long long)64 * d;
   const TnArgs db = {dZ, U, 64, sb > 1 ? db_part : dB, nb, 64, F / 64, sb};
