@@ -115,20 +115,6 @@ __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int r
   return false;
 }
 
-// The same for ONE list row shared by all token tiles: items (group of TM tiles m, group of TN entries
-// n), or for the dsd kernel (m, chunk of output columns n), in bands of `h` groups m that are walked
-// along n, h items at a time; XCD x takes the x-th eighth of that order.  The workgroups that run
-// together on an XCD then share h token groups and a few weight groups, and with at most h groups of
-// tokens every weight row is fetched into one L2 only.
-struct GridItem {
-  int m, n;
-};
-__device__ __forceinline__ GridItem grid_item(int idx, int GM, int GN, int h) {
-  const int per = h * GN, band = idx / per, left = GM - band * h;
-  const int hb = left < h ? left : h, rem = idx - band * per;
-  return {band * h + rem % hb, rem / hb};
-}
-
 template <class Tl>
 __device__ __forceinline__ void zero_acc(f32x16 (&acc)[Tl::NI][Tl::TI]) {
 #pragma unroll
@@ -226,6 +212,7 @@ struct SddArgs {
   int rows, blocks;            // list rows, and blocks that the list could hold
   int own, grid;               // of SddPlan
   unsigned allowed;
+  bool mix;                    // sdd_may_mix
   uint16_t* out;
   const uint16_t* gate;        // null: ReLU
   const uint16_t *A2, *W2;     // LORA
@@ -262,20 +249,24 @@ struct SddSrc {
 // tile) and W2 [F,64] (rows of the listed blocks): acc += A2_i W2_j^T, the low-rank branch
 // z = W x + B (A x) of Sec. II-C with A2 = X A^T computed beforehand and W2 = B, both padded to
 // rank 64.
+// placed: the item's number along the tokens and along the list where the caller has chosen it (one list row), -1: this
+// workgroup's of a launch of such tiles.
 template <class Tl, int DT, bool LORA>
-__device__ __forceinline__ void sdd_tile(const SddArgs& a, uint16_t* ring) {
+__device__ __forceinline__ void sdd_tile(const SddArgs& a, uint16_t* ring, GridItem placed = {-1, -1}) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (wave >= Tl::kWaves) return;      // (barriers wait for the wavefronts that are left)
   int m, chunk, n_i, rs;
   if (a.gt == a.Tt) {
     rs = min(a.row_ptr[0], a.nnz_cap);
     n_i = min(a.row_ptr[1], a.nnz_cap) - rs;
-    const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (n_i + Tl::TN - 1) / Tl::TN;
-    const int total = GM * GN, L = (total + 7) / 8, slot = blockIdx.x / 8, idx = (blockIdx.x % 8) * L + slot;
-    if (slot >= L || idx >= total) return;
-    const GridItem it = grid_item(idx, GM, GN, Tl::TM == 4 ? 4 : 8);
-    m = it.m;
-    chunk = it.n;
+    if (placed.m < 0) {
+      const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (n_i + Tl::TN - 1) / Tl::TN;
+      const int total = GM * GN, L = (total + 7) / 8, slot = blockIdx.x / 8, idx = (blockIdx.x % 8) * L + slot;
+      if (slot >= L || idx >= total) return;
+      placed = grid_item(idx, GM, GN, Tl::TM == 4 ? 4 : 8);
+    }
+    m = placed.m;
+    chunk = placed.n;
   } else {
     if (!find_work(a.row_ptr, a.Tt / Tl::TM, a.gt / Tl::TM, blockIdx.x, Tl::TN, a.nnz_cap, m, chunk)) return;
     m = __builtin_amdgcn_readfirstlane(m);
@@ -348,16 +339,22 @@ __global__ __launch_bounds__(RESIDENT == 1 ? 512 : 256, 2) void ffn_sdd_any(SddA
   __shared__ __attribute__((aligned(1024))) uint16_t ring[RESIDENT == 1 ? kRingElems<Tile14Deep> : kRingElems<Tile14>];
   const int n = min(a.row_ptr[a.rows], a.nnz_cap) - min(a.row_ptr[0], a.nnz_cap);
   int id = a.own;
-  if (!sdd_keeps_own(a.nnz_cap, n)) {
+  GridItem it = {-1, -1};
+  if (sdd_keeps_own(a.nnz_cap, n)) {
+    if (RESIDENT == 1 && a.mix) {
+      const SddMix mix = sdd_mix(a.Tt, n);
+      if (sdd_mixes(mix) && !sdd_mix_item(mix, a.Tt, n, blockIdx.x, id, it)) return;
+    }
+  } else {
     const int limit = sdd_limit<RESIDENT>(a.own, a.grid, a.Tt, a.gt, n);
     if ((int)blockIdx.x >= limit) return;
     id = sdd_pick<RESIDENT>(a.own, a.allowed, limit, a.Tt, a.gt, a.K, n);
   }
   if constexpr (RESIDENT == 1) {
     switch (id) {
-      case kT44: sdd_tile<Tile44, DT, LORA>(a, ring); break;
-      case kT24: sdd_tile<Tile24, DT, LORA>(a, ring); break;
-      case kT22Deep: sdd_tile<Tile22Deep, DT, LORA>(a, ring); break;
+      case kT44: sdd_tile<Tile44, DT, LORA>(a, ring, it); break;
+      case kT24: sdd_tile<Tile24, DT, LORA>(a, ring, it); break;
+      case kT22Deep: sdd_tile<Tile22Deep, DT, LORA>(a, ring, it); break;
       case kT14Deep: sdd_tile<Tile14Deep, DT, LORA>(a, ring); break;
       case kT12: sdd_tile<Tile12, DT, LORA>(a, ring); break;
       case kT11: sdd_tile<Tile11, DT, LORA>(a, ring); break;
@@ -637,8 +634,10 @@ static void launch_sdd(SddArgs a, hipStream_t st) {
     a.own = p.id;
     a.grid = p.grid;
     a.allowed = p.allowed;
+    a.mix = sdd_may_mix(p, a.Tt, a.gt, a.K, a.nnz_cap, g_ffn_tiles_per_wg);
+    if (a.mix) a.grid = max(p.grid, sdd_mix_grid(a.Tt, a.nnz_cap));
     if (kTileInfo[p.id].resident == 1)
-      hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 1>), dim3(p.grid), dim3(512), 0, st, a);
+      hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 1>), dim3(a.grid), dim3(512), 0, st, a);
     else
       hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 2>), dim3(p.grid), dim3(256), 0, st, a);
     return;
@@ -693,7 +692,7 @@ static hipError_t launch_ffn_bf16_t(int pass, int Tt, int gt, int Fb, int d, int
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
   {
     ProfScope ps(pass == 0 ? kKFfnUp : kKFfnDh, st);
-    launch_sdd<DT, false>({A, W1, pass == 0 ? b1 : nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, act_out,
+    launch_sdd<DT, false>({A, W1, pass == 0 ? b1 : nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, false, act_out,
                            pass == 0 ? nullptr : act_gate, nullptr, nullptr}, st);
   }
   hipError_t e = hipGetLastError();
@@ -728,7 +727,7 @@ static hipError_t launch_ffn_lora_fwd_bf16_t(int Tt, int gt, int d, int F, const
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKFfnUp, st);
-    launch_sdd<DT, true>({X, W_up, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, H_act, nullptr, U, B_pad}, st);
+    launch_sdd<DT, true>({X, W_up, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, false, H_act, nullptr, U, B_pad}, st);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -754,7 +753,7 @@ static hipError_t launch_ffn_lora_bwd_bf16_t(int Tt, int gt, int d, int F, const
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
   {
     ProfScope ps(kKFfnDh, st);
-    launch_sdd<DT, false>({dY, W_down_t, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, dZ, H_act, nullptr, nullptr},
+    launch_sdd<DT, false>({dY, W_down_t, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, false, dZ, H_act, nullptr, nullptr},
                           st);
   }
   hipError_t e = hipGetLastError();

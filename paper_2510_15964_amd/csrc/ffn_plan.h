@@ -158,6 +158,70 @@ inline SddPlan plan_sdd(int Tt, int gt, int d, int nnz_cap, int blocks, int want
   return p;
 }
 
+// ONE list row shared by all token tiles: items (group of TM tiles m, group of TN entries
+// n), or for the dsd kernel (m, chunk of output columns n), in bands of `h` groups m that are walked
+// along n, h items at a time; XCD x takes the x-th eighth of that order.  The workgroups that run
+// together on an XCD then share h token groups and a few weight groups, and with at most h groups of
+// tokens every weight row is fetched into one L2 only.
+struct GridItem {
+  int m, n;
+};
+LX_HD GridItem grid_item(int idx, int GM, int GN, int h) {
+  const int per = h * GN, band = idx / per, left = GM - band * h;
+  const int hb = left < h ? left : h, rem = idx - band * per;
+  return {band * h + rem % hb, rem / hb};
+}
+
+// One list row: the items of 4 x 4 tiles that do not fill a round run by narrower tiles, halved or quartered, whose round
+// is shorter.  Per XCD: L items, of which `whole` run as they are and each of the rest in `parts` of tile `tail` (-1:
+// nothing is left, or more than half a round).  First product, plain and mixed, us: 8192 tokens, d = 4160, 36 blocks 167 ->
+// 139; 4096, 4096, 72 164 -> 136; 2560, 3200, 110 132 -> 111; 8192, 1024, 40 57.5 -> 51.5; 3904, 5120, 96 224 -> 212; 6144, 4096,
+// 190 510 -> 493; 31 sizes 0.999 - 1.21 times as fast, 1.12 in the geometric mean.  (2 x 4 tiles with a rest by 2 x 2 are
+// slower than the 4 x 4 tiles that the plan takes there: ten sizes, 0.94 - 0.997.)
+struct SddMix {
+  int L, whole, tail, parts;
+};
+LX_HD SddMix sdd_mix(int Tt, int n) {
+  constexpr int per = kCUs / 8;
+  SddMix m = {ceil_div(ceil_div(Tt, 4) * ceil_div(n, 4), 8), 0, -1, 1};
+  m.whole = m.L / per * per;
+  const int rest = m.L - m.whole;
+  if (rest > 0 && 4 * rest <= per)
+    m.tail = kT22Deep, m.parts = 4;
+  else if (rest > 0 && 2 * rest <= per)
+    m.tail = kT24, m.parts = 2;
+  return m;
+}
+// Whether lists of that length run so (with nothing left as well: whole rounds of the widest tile).
+LX_HD bool sdd_mixes(const SddMix& m) { return m.whole > 0 && (m.tail >= 0 || m.whole == m.L); }
+// Workgroup w: tile and item (along the tokens, along the list, in units of the tile); false past the end.
+LX_HD bool sdd_mix_item(const SddMix& x, int Tt, int n, int w, int& id, GridItem& it) {
+  const int GM = ceil_div(Tt, 4), GN = ceil_div(n, 4), slot = w / 8, over = slot - x.whole, rest = over > 0 ? over : 0;
+  const int q = x.parts == 4 ? rest / 4 : x.parts == 2 ? rest / 2 : rest, part = rest - q * x.parts;
+  const int at = over < 0 ? slot : x.whole + q, idx = w % 8 * x.L + at;
+  if (at >= x.L || idx >= GM * GN) return false;
+  it = grid_item(idx, GM, GN, 4);
+  id = kT44;
+  if (over < 0) return true;
+  id = x.tail;
+  it.m = 2 * it.m + part % 2;
+  if (id == kT22Deep) it.n = 2 * it.n + part / 2;
+  const int tn = id == kT22Deep ? 2 : 4;
+  return 2 * it.m < Tt && tn * it.n < n;
+}
+// Whether a launch is laid out for that: for a list as long as its capacity it would be faster by the model.
+inline bool sdd_may_mix(const SddPlan& p, int Tt, int gt, int d, int nnz_cap, int want) {
+  if (want != 0 || gt != Tt || !p.allowed || kTileInfo[p.id].resident != 1) return false;
+  const SddMix m = sdd_mix(Tt, nnz_cap);
+  if (!sdd_mixes(m) || m.tail < 0) return false;
+  const float steps = (float)(d / 64);
+  const TileInfo &b = kTileInfo[kT44], &t = kTileInfo[m.tail];
+  return (float)(m.whole / (kCUs / 8)) * (b.round + steps * b.step[0]) + t.round + steps * t.step[0] <
+         0.98f * sdd_cost(kTileInfo[p.id], 1, Tt, gt, d, nnz_cap);
+}
+// Workgroups that hold any mix for lists up to n entries (the rest of an XCD takes a round at most).
+inline int sdd_mix_grid(int Tt, int n) { return 8 * (sdd_mix(Tt, n).whole + kCUs / 8); }
+
 // ---- second product ------------------------------------------------------------------------
 // Its steps are the list entries.  With one list row and room for partial sums
 // the units that do not fill a round may have their list cut into 2 - 4 pieces, each at least 8 entries
