@@ -455,28 +455,31 @@ struct DsdSrc {
 // whole, the list of each of the following `rest` is cut into `pieces` whose accumulators go to
 // `part` as they are, fp32, for ffn_dsd_reduce to add in order.  Otherwise: 1-D grid of (column chunk, tile group),
 // see dsd_unit.
+// placed: as in sdd_tile.
 template <class Tl, int DT, bool LORA>
-__global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_dsd(DsdArgs a) {
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[Tl::NST * Tl::kElems];
+__device__ __forceinline__ void dsd_tile(const DsdArgs& a, uint16_t* ring, GridItem placed = {-1, -1}) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   int i0, n0, s_lo = 0, n_i, rs, slot = -1;
   if (a.gt == a.Tt) {
     const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (a.ncols + 64 * Tl::TN - 1) / (64 * Tl::TN);
-    const int Lf = (a.full + 7) / 8, s = blockIdx.x / 8, x = blockIdx.x % 8;
-    int unit, piece = -1;
-    if (s < Lf) {
-      unit = x * Lf + s;
-      if (unit >= a.full) return;
-    } else {
-      const int cut = a.rest * a.pieces, Lr = (cut + 7) / 8, y = x * Lr + s - Lf;
-      if (s - Lf >= Lr || y >= cut) return;
-      piece = y / a.rest;                   // an XCD works on few pieces: their weights and activations
-      unit = a.full + y % a.rest;
-      slot = (y % a.rest) * a.pieces + piece;
+    int piece = -1;
+    if (placed.m < 0) {
+      const int Lf = (a.full + 7) / 8, s = blockIdx.x / 8, x = blockIdx.x % 8;
+      int unit;
+      if (s < Lf) {
+        unit = x * Lf + s;
+        if (unit >= a.full) return;
+      } else {
+        const int cut = a.rest * a.pieces, Lr = (cut + 7) / 8, y = x * Lr + s - Lf;
+        if (s - Lf >= Lr || y >= cut) return;
+        piece = y / a.rest;                 // an XCD works on few pieces: their weights and activations
+        unit = a.full + y % a.rest;
+        slot = (y % a.rest) * a.pieces + piece;
+      }
+      placed = grid_item(unit, GM, GN, a.band);
     }
-    const GridItem it = grid_item(unit, GM, GN, a.band);
-    i0 = it.m * Tl::TM;
-    n0 = it.n * (64 * Tl::TN);
+    i0 = placed.m * Tl::TM;
+    n0 = placed.n * (64 * Tl::TN);
     rs = min(a.row_ptr[0], a.nnz_cap);
     n_i = min(a.row_ptr[1], a.nnz_cap) - rs;
     if (piece >= 0) {
@@ -552,6 +555,27 @@ __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_dsd(DsdAr
   lds_to_out<Tl, DT, true>(lds_addr(ring), a.out, a.ncols, nullptr, [&](int t, int e) {
     return i0 + t < a.Tt && n0 + 64 * e < a.ncols ? (long long)(i0 + t) * 64 * a.ncols + n0 + 64 * e : -1ll;
   });
+}
+template <class Tl, int DT, bool LORA>
+__global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_dsd(DsdArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[Tl::NST * Tl::kElems];
+  dsd_tile<Tl, DT, LORA>(a, ring);
+}
+// 4 x 4 tiles and the rest of a round by narrower ones (SddMix).
+template <int DT, bool LORA>
+__global__ __launch_bounds__(512, 2) void ffn_dsd_mix(DsdArgs a) {
+  constexpr int kRing = Tile24::NST * Tile24::kElems;          // the longest of the three
+  static_assert(Tile44::NST * Tile44::kElems <= kRing && Tile22Deep::NST * Tile22Deep::kElems <= kRing, "shared memory");
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[kRing];
+  int id;
+  GridItem it;
+  if (!sdd_mix_item(sdd_mix(a.Tt, a.ncols / 64), a.Tt, a.ncols / 64, blockIdx.x, id, it)) return;
+  if (id == kT44)
+    dsd_tile<Tile44, DT, LORA>(a, ring, it);
+  else if (id == kT24)
+    dsd_tile<Tile24, DT, LORA>(a, ring, it);
+  else
+    dsd_tile<Tile22Deep, DT, LORA>(a, ring, it);
 }
 
 // Adds the pieces of each cut unit (piece 0 first, fixed order: reproducible) and stores like the kernel's own
@@ -653,6 +677,10 @@ static void launch_sdd(SddArgs a, hipStream_t st) {
 template <int DT, bool LORA>
 static void launch_dsd(DsdArgs a, size_t part_bytes, hipStream_t st) {
   const DsdPlan p = choose_dsd(a.Tt, a.gt, a.ncols, a.nnz_cap, LORA || !a.part ? 0 : part_bytes, g_ffn_tiles_per_wg);
+  if (dsd_may_mix(p, a.Tt, a.gt, a.ncols, a.nnz_cap, g_ffn_tiles_per_wg)) {
+    hipLaunchKernelGGL((ffn_dsd_mix<DT, LORA>), dim3(sdd_mix_grid(a.Tt, a.ncols / 64)), dim3(512), 0, st, a);
+    return;
+  }
   const TileInfo& t = kTileInfo[p.id];
   a.band = t.tm == 4 ? 4 : 8;
   a.full = p.full;

@@ -263,6 +263,23 @@ inline DsdPlan choose_dsd(int Tt, int gt, int d, int nnz_cap, size_t part_bytes,
   return best;
 }
 
+// One list row: whether the launch runs by 4 x 4 tiles with a rest by narrower ones (SddMix, the 64-column chunks of the output
+// in the place of the list's entries).  Second product, us, by the plan's own tile, that with cut lists, mixed: 4544 tokens, d = 4096,
+// 48 blocks 122 / 109 / 102; 3968, 5120, 48 124 / 120 / 105; 5312, 3200, 30 82 / 75 / 68; 3904, 5120, 96 231 / 216 / 207; 8192, 5120, 96 429 / 411 / 402;
+// 8192, 4608, 8 58 / - / 52; 66 sizes 1.00 - 1.21 times as fast as the first and 0.999 - 1.19 times as the second, which is left
+// where more than half a round is.
+inline bool dsd_may_mix(const DsdPlan& p, int Tt, int gt, int d, int nnz_cap, int want) {
+  if (want != 0 || gt != Tt) return false;
+  const SddMix m = sdd_mix(Tt, d / 64);
+  if (!sdd_mixes(m) || m.tail < 0) return false;
+  const TileInfo &own = kTileInfo[p.id], &b = kTileInfo[kT44], &t = kTileInfo[m.tail];
+  const float n = (float)nnz_cap;
+  const float plan = p.pieces == 1 ? tile_cost(own, own.resident, p.full, n)
+                                   : (p.full > 0 ? tile_cost(own, own.resident, p.full, n) : 0.f) +
+                                         tile_cost(own, own.resident, p.rest * p.pieces, n / p.pieces) + 5.f + (float)p.part_bytes() / 2.5e6f;
+  return (float)(m.whole / (kCUs / 8)) * (b.round + n * b.step[0]) + t.round + n * t.step[0] < 0.98f * plan;
+}
+
 // Lists per group of token tiles: the units are (column chunk, of GN; token group, of GM).  Three ways to deal them:
 // - kByChunk: XCD w % 8 takes the w % 8th eighth of the units, chunk after chunk, and so fetches the weight rows of an
 //   eighth of the columns only.  Where an eighth ends inside a chunk, its parts get long and short lists in

@@ -26,6 +26,11 @@ int mix_item(int Tt, int n, int w, int* out) {
   out[3] = t.tn;
   return 1;
 }
+// Second product: -2: by the plan's own tile, otherwise the tile of the rest.
+int down_tail(int Tt, int d, int cap, int want) {
+  if (!dsd_may_mix(choose_dsd(Tt, Tt, d, cap, ~(size_t)0, want), Tt, Tt, d, cap, want)) return -2;
+  return sdd_mix(Tt, d / 64).tail;
+}
 int keeps_own(int cap, int n) { return sdd_keeps_own(cap, n); }
 
 }  // extern "C"

@@ -1,4 +1,4 @@
-"""First product with one list row, wide tiles and a rest by narrower ones: who computes what, on the host."""
+"""Launches with one list row, wide tiles and a rest by narrower ones: who computes what, on the host."""
 import ctypes as C
 import os
 import subprocess
@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from ffn_plan import TILES
-from test_gpu_ffn_mix import CASES
+from test_gpu_ffn_mix import CASES, DOWN
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -51,3 +51,8 @@ def test_the_cases_run_as_they_claim(L, dtype, Tt, d, Fb, cap, n, tail):
     assert L.may_mix(Tt, d, cap, Fb, 0) and not L.may_mix(Tt, d, cap, Fb, 1)
     got = L.mix_tail(Tt, n) if L.keeps_own(cap, n) else -2
     assert tail == (None if got == -2 else "4x4" if got == -1 else TILES[got])
+
+
+@pytest.mark.parametrize("dtype,Tt,d,n,tail", DOWN)
+def test_the_second_products_run_as_they_claim(L, dtype, Tt, d, n, tail):
+    assert TILES[L.down_tail(Tt, d, n, 0)] == tail and L.down_tail(Tt, d, n, 1) == -2

@@ -1,4 +1,4 @@
-"""First product with one list row, wide tiles and a rest by narrower ones: every tile gives the same bits, so the results
+"""Launches with one list row, wide tiles and a rest by narrower ones: every tile gives the same bits, so the results
 are those of a workgroup per token tile."""
 import numpy as np
 import pytest
@@ -29,11 +29,28 @@ CASES = [
     ("f16", 128, 512, 90, 65, 58, None),              # more than half a round is left
     ("bf16", 130, 768, 64, 40, 12, None),             # far shorter than its capacity
 ]
+# the second product: element type, token tiles, d, listed blocks, tile of the rest
+DOWN = [
+    ("bf16", 130, 2048, 9, "2x2 deep"),               # two token tiles in the last group
+    ("f16", 165, 2048, 9, "2x4"),
+    ("bf16", 117, 2112, 20, "2x2 deep"),              # 33 column chunks: one in the last group, one token tile too
+    ("f16", 163, 2112, 70, "2x4"),                    # three tiles; more entries than are fetched at once
+]
+
+
+@pytest.mark.parametrize("lora", [False, True])
+@pytest.mark.parametrize("dtype,Tt,d,n,tail", DOWN)
+def test_bits_of_the_second_products_mix(lx, dtype, Tt, d, n, tail, lora):
+    compare(lx, dtype, Tt, d, n + 3, n, n, lora)
 
 
 @pytest.mark.parametrize("lora", [False, True])
 @pytest.mark.parametrize("dtype,Tt,d,Fb,cap,n,tail", CASES)
 def test_bits_of_the_mix(lx, dtype, Tt, d, Fb, cap, n, tail, lora):
+    compare(lx, dtype, Tt, d, Fb, cap, n, lora)
+
+
+def compare(lx, dtype, Tt, d, Fb, cap, n, lora):
     import torch
     T, F = 64 * Tt, 64 * Fb
     rng = np.random.default_rng(Tt + d)
