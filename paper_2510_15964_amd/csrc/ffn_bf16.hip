@@ -612,6 +612,191 @@ __global__ __launch_bounds__(256) void ffn_dsd_reduce(DsdArgs a) {
                                          [&](int, int) { return (long long)i * 64 * a.ncols + n; });
 }
 
+// ---------------------------------------------------------------------------
+// Few tiles: a workgroup per quarter (32 x 32) of a 64 x 64 tile.  The quarters of a tile sit eight workgroups
+// apart, on one XCD and on different CUs.  Results are those of the other tiles, to the last bit.
+// ---------------------------------------------------------------------------
+struct QuarterOf {
+  int tile, th, nh;        // number of the tile's workgroup; token half, column half
+  __device__ __forceinline__ QuarterOf() {
+    const int w = blockIdx.x, q = w / 8 % 4;
+    tile = w / 32 * 8 + w % 8;
+    th = q % 2;
+    nh = q / 2;
+  }
+};
+// This lane's two 16-byte pieces of the quarter: element offsets of piece u from the quarter's first element.
+__device__ __forceinline__ long long quarter_piece(int u, long long ld) {
+  const int x = u * kWave + (int)threadIdx.x;
+  return x / 4 * ld + x % 4 * 8;
+}
+// By the first wavefront, which is the only one left.
+template <int DT, bool THROUGH>
+__device__ __forceinline__ void store_quarter(const f32x16& acc, uint32_t lds, const uint16_t* __restrict__ bias, bool relu,
+                                              bool gated, const uint4 (&gate)[2], uint16_t* __restrict__ out, long long ld) {
+  lds_barrier();
+  acc_to_lds<DT>(acc, lds, 0, 0, 0, bias, relu);
+  lds_barrier();
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int x = u * kWave + (int)threadIdx.x;
+    uint4 v = lds_read16(lds + out_slot(0, x / 4, x % 4));
+    if (gated) v = make_uint4(gate2<DT>(v.x, gate[u].x), gate2<DT>(v.y, gate[u].y), gate2<DT>(v.z, gate[u].z), gate2<DT>(v.w, gate[u].w));
+    uint16_t* p = out + quarter_piece(u, ld);
+    if (THROUGH)
+      asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(__builtin_bit_cast(u32x4, v)) : "memory");
+    else
+      *reinterpret_cast<uint4*>(p) = v;
+  }
+}
+// The transfers of one operand's 32 rows: this lane's offsets from their first element, rows ld elements apart (32 of
+// them within 4 GiB: quarters_pay); `second`: the weight rows, which come after the token rows in a stage.
+struct QuarterRows {
+  uint32_t voff[4];
+  __device__ __forceinline__ void init(long long ld, bool second) {
+    const int lane = threadIdx.x % kWave, lr = lane / 8;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) voff[u] = (uint32_t)((8 * u + lr) * ld * 2 + (((lane % 8) ^ lr ^ (second ? 4 + u : u)) << 4));
+  }
+  __device__ __forceinline__ void issue(const uint16_t* first, uint32_t lds) const {
+    dma16_s_at<0>(first, voff[0], lds);
+    dma16_s_at<1024>(first, voff[1], lds);
+    dma16_s_at<2048>(first, voff[2], lds);
+    dma16_s_at<3072>(first, voff[3], lds);
+  }
+};
+// A wave-uniform pointer, for an operand that has to be scalar.  (readfirstlane returns a signed int.)
+__device__ __forceinline__ const uint16_t* scalar(const uint16_t* p) {
+  const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return reinterpret_cast<const uint16_t*>((unsigned long long)hi << 32 | lo);
+}
+template <bool LORA>
+struct QuarterSddSrc {
+  const uint16_t *rows, *rows2;          // the operand's first element; of the low-rank step
+  QuarterRows t, t2;
+  uint32_t at;                           // of the operand in a step
+  int ksteps;
+  __device__ __forceinline__ void issue(int s, uint32_t lds) const {
+    if (LORA && s == ksteps)
+      t2.issue(scalar(rows2), lds + at);
+    else
+      t.issue(LORA ? scalar(rows + (long long)s * kBK) : rows + (long long)s * kBK, lds + at);
+  }
+};
+
+template <int DT, bool LORA, int NST>
+__global__ __launch_bounds__(Quarter::kTileThreads, 2) void ffn_sdd_quarter(SddArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * 2 * Quarter::kElems];
+  const QuarterOf q;
+  int m, e, rs;
+  if (a.gt == a.Tt) {
+    rs = min(a.row_ptr[0], a.nnz_cap);
+    const int n_i = min(a.row_ptr[1], a.nnz_cap) - rs;
+    const int total = a.Tt * n_i, L = (total + 7) / 8, slot = q.tile / 8, idx = (q.tile % 8) * L + slot;
+    if (slot >= L || idx >= total) return;
+    const GridItem it = grid_item(idx, a.Tt, n_i, 8);
+    m = it.m;
+    e = it.n;
+  } else {
+    if (!find_work(a.row_ptr, a.Tt, a.gt, q.tile, 1, a.nnz_cap, m, e)) return;
+    m = __builtin_amdgcn_readfirstlane(m);
+    e = __builtin_amdgcn_readfirstlane(e);
+    rs = a.row_ptr[m / a.gt];
+  }
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), col = a.col_idx[rs + e];
+  const long long row_a = m * 64ll + 32 * q.th, row_w = col * 64ll + 32 * q.nh;
+  uint16_t* out = a.out + (((long long)rs + e) * a.gt + m % a.gt) * 4096 + 32 * q.th * 64 + 32 * q.nh;
+  uint4 gate[2] = {};
+  QuarterSddSrc<LORA> src;
+  src.ksteps = a.K / kBK;
+  if (wave == 0) {
+    if (a.gate) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) gate[u] = *reinterpret_cast<const uint4*>(a.gate + (out - a.out) + quarter_piece(u, 64));
+    }
+  } else {
+    const bool weights = wave == 2;
+    src.rows = weights ? a.W + row_w * a.K : a.A + row_a * a.K;
+    src.at = weights ? 32 * kBK * 2 : 0;
+    src.t.init(a.K, weights);
+    if (LORA) {
+      src.rows2 = weights ? a.W2 + row_w * 64 : a.A2 + row_a * 64;
+      src.t2.init(64, weights);
+    }
+  }
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  run_quarter<DT, NST>(src.ksteps + (LORA ? 1 : 0), lds_addr(ring), src, acc);
+  if (wave > 0) return;
+  store_quarter<DT, false>(acc, lds_addr(ring), a.bias ? a.bias + row_w : nullptr, !a.gate, a.gate != nullptr, gate, out, 64);
+}
+
+template <bool LORA>
+struct QuarterDsdSrc {
+  const uint16_t *rows, *rows2;
+  QuarterRows t, t2;
+  uint32_t at;
+  long long step;                        // of the token rows from list entry to list entry
+  const int* list;                       // null: the token rows
+  int lsteps, next;                      // as in DsdSrc
+  __device__ __forceinline__ void fetch(int s) {
+    const int e = s + (int)(threadIdx.x % kWave);
+    const uint32_t off = (uint32_t)(e < lsteps ? e : lsteps - 1) * 4u;
+    asm volatile("global_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)" : "=v"(next) : "v"(off), "s"(list) : "memory");
+  }
+  __device__ __forceinline__ void issue(int s, uint32_t lds) {
+    if (LORA && s == lsteps) {
+      t2.issue(rows2, lds + at);
+    } else if (!list) {
+      t.issue(rows + s * step, lds + at);
+    } else {
+      if (s > 0 && s % kWave == 0) fetch(s);
+      t.issue(rows + (long long)__builtin_amdgcn_readlane(next, s % kWave) * 64, lds + at);
+    }
+  }
+};
+
+template <int DT, bool LORA, int NST>
+__global__ __launch_bounds__(Quarter::kTileThreads, 2) void ffn_dsd_quarter(DsdArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * 2 * Quarter::kElems];
+  const QuarterOf q;
+  int chunk, i;
+  if (!dsd_unit(kUnranked, a.GM, a.GN, q.tile, chunk, i)) return;
+  chunk = __builtin_amdgcn_readfirstlane(chunk);
+  i = __builtin_amdgcn_readfirstlane(i);
+  const int rs = min(a.row_ptr[i / a.gt], a.nnz_cap), n_i = min(a.row_ptr[i / a.gt + 1], a.nnz_cap) - rs, n0 = chunk * 64 + 32 * q.nh;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  QuarterDsdSrc<LORA> src;
+  src.lsteps = n_i;
+  src.next = 0;
+  src.list = nullptr;
+  src.step = 0;
+  if (wave == 1) {
+    src.rows = a.act + ((long long)rs * a.gt + i % a.gt) * 4096 + 32 * q.th * 64;
+    src.step = (long long)a.gt * 4096;
+    src.at = 0;
+    src.t.init(64, false);
+    if (LORA) src.rows2 = a.A2 + (i * 64ll + 32 * q.th) * 64, src.t2 = src.t;
+  } else if (wave == 2) {
+    src.list = a.col_idx + rs;
+    if (n_i > 0) src.fetch(0);
+    src.rows = a.W + n0 * a.ldw;
+    src.at = 32 * kBK * 2;
+    src.t.init(a.ldw, true);
+    if (LORA) src.rows2 = a.W2 + n0 * 64ll, src.t2.init(64, true);
+  }
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  run_quarter<DT, NST>(n_i + (LORA ? 1 : 0), lds_addr(ring), src, acc);
+  if (wave > 0) return;
+  const uint4 none[2] = {};
+  store_quarter<DT, true>(acc, lds_addr(ring), a.bias ? a.bias + n0 : nullptr, false, false, none,
+                          a.out + (i * 64ll + 32 * q.th) * a.ncols + n0, a.ncols);
+}
+
 // pass 0 (forward):  A = X,  W1 = W_up [F,d],     W2 = W_down [d,F], act_out = H_act, out = Y
 // pass 1 (backward): A = dY, W1 = W_down_t [F,d], W2 = W_up_t [d,F], act_out = dZ_act,
 //                    act_gate = H_act, out = dX
@@ -654,6 +839,14 @@ template <int DT, bool LORA>
 static void launch_sdd(SddArgs a, hipStream_t st) {
   const SddPlan p = plan_sdd(a.Tt, a.gt, a.K, a.nnz_cap, a.blocks, g_ffn_tiles_per_wg);
   if (p.grid == 0) return;
+  if (const int items = (long long)a.nnz_cap * a.gt < 1 << 20 ? a.nnz_cap * a.gt : 1 << 20; quarters_pay(items, a.K, g_ffn_tiles_per_wg)) {
+    const dim3 grid(4 * sdd_grid(kTileInfo[kT11], a.Tt, a.gt, a.nnz_cap));
+    if (items <= kQuarterTilesAlone)
+      hipLaunchKernelGGL((ffn_sdd_quarter<DT, LORA, 8>), grid, dim3(Quarter::kTileThreads), 0, st, a);
+    else
+      hipLaunchKernelGGL((ffn_sdd_quarter<DT, LORA, 4>), grid, dim3(Quarter::kTileThreads), 0, st, a);
+    return;
+  }
   if (p.allowed) {
     a.own = p.id;
     a.grid = p.grid;
@@ -676,6 +869,16 @@ static void launch_sdd(SddArgs a, hipStream_t st) {
 }
 template <int DT, bool LORA>
 static void launch_dsd(DsdArgs a, size_t part_bytes, hipStream_t st) {
+  if (const int items = a.Tt < 4096 ? a.Tt * (a.ncols / 64) : 1 << 20; quarters_pay(items, a.ldw, g_ffn_tiles_per_wg)) {
+    a.GM = a.Tt;
+    a.GN = a.ncols / 64;
+    const dim3 grid(32 * ceil_div(a.GM * a.GN, 8));
+    if (items <= kQuarterTilesAlone)
+      hipLaunchKernelGGL((ffn_dsd_quarter<DT, LORA, 8>), grid, dim3(Quarter::kTileThreads), 0, st, a);
+    else
+      hipLaunchKernelGGL((ffn_dsd_quarter<DT, LORA, 4>), grid, dim3(Quarter::kTileThreads), 0, st, a);
+    return;
+  }
   const DsdPlan p = choose_dsd(a.Tt, a.gt, a.ncols, a.nnz_cap, LORA || !a.part ? 0 : part_bytes, g_ffn_tiles_per_wg);
   if (dsd_may_mix(p, a.Tt, a.gt, a.ncols, a.nnz_cap, g_ffn_tiles_per_wg)) {
     hipLaunchKernelGGL((ffn_dsd_mix<DT, LORA>), dim3(sdd_mix_grid(a.Tt, a.ncols / 64)), dim3(512), 0, st, a);

@@ -280,6 +280,13 @@ inline bool dsd_may_mix(const DsdPlan& p, int Tt, int gt, int d, int nnz_cap, in
   return (float)(m.whole / (kCUs / 8)) * (b.round + n * b.step[0]) + t.round + n * t.step[0] < 0.98f * plan;
 }
 
+// Whether a launch of `items` 64 x 64 tiles, its weight rows ld elements apart, runs by quarters of them (Quarter): while all
+// quarters are resident at once, with rings of eight pairs of steps one per CU, of four two.  Beyond, a quarter's 8 KB per
+// 32 x 32 products is more than the L2s deliver (192 tokens, d = 5056, 68 blocks, 204 tiles 24 us, 33 by quarters; the
+// second product, 237 tiles, 21 and 32).
+constexpr int kQuarterTiles = kCUs / 2, kQuarterTilesAlone = kCUs / 4;
+inline bool quarters_pay(int items, long long ld, int want) { return want == 0 && items <= kQuarterTiles && ld < 1 << 25; }
+
 // Lists per group of token tiles: the units are (column chunk, of GN; token group, of GM).  Three ways to deal them:
 // - kByChunk: XCD w % 8 takes the w % 8th eighth of the units, chunk after chunk, and so fetches the weight rows of an
 //   eighth of the columns only.  Where an eighth ends inside a chunk, its parts get long and short lists in

@@ -229,4 +229,93 @@ __device__ __forceinline__ void run_tile(int nsteps, uint32_t ring, int wm, int 
     run_tile_ring<Tl, DT>(nsteps, ring, wm, wn, src, acc);
 }
 
+// The quarter tile: 32 token rows times 32 weight rows by ONE wavefront that multiplies and two that transfer, the one the
+// token rows, the other the weight rows.  For launches of few tiles: a 64 x 64 tile of four wavefronts takes 390 clocks per
+// step, of which the CU's memory path is busy for 256 with its 16 KB; four quarters on four CUs have 128 each, as
+// many as the chain of a step's matrix instructions takes, if nothing else has to be issued between them (one wavefront
+// that does it all is 3 - 8 % faster than the 64 x 64 tile).  By that tile and by quarters, us, first / second product: 192
+// tokens, d = 768, 15 blocks 6.6 / 6.1 -> 5.4 / 5.2; 64, 1792, 44 9.5 / 11.2 -> 7.5 / 9.2; 64, 2560, 16 12.1 / 5.8 -> 9.3 / 5.1; 64,
+// 4288, 14 15.3 / 5.6 -> 12.3 / 4.9; 64 tokens, d = 2496,
+// 92 blocks 11.5 / 19.8 -> 11.1 / 15.4; 192 tokens, d = 832, a list per tile, 128 tiles 7.8 / 5.2 -> 6.0 / 4.4.
+struct Quarter {
+  static constexpr int kWaves = 3, kTileThreads = kWaves * kWave;
+  static constexpr int kElems = 64 * kBK;               // of a step: 32 token rows, 32 weight rows, laid out like the others
+  static constexpr int kIss = 4;                        // transfer instructions of a wavefront per step
+};
+// acc += sum over nsteps steps, in the order of run_tile, in the first wavefront.  NST stages of two steps each.
+// src.issue(step, LDS address) starts the calling wavefront's transfers of a step (steps past the end: the last one again).
+template <int DT, int NST, class Src>
+__device__ __forceinline__ void run_quarter(int nsteps, uint32_t ring, Src& src, f32x16& acc) {
+  constexpr uint32_t kStep = Quarter::kElems * 2, kStage = 2 * kStep;
+  const int pairs = (nsteps + 1) / 2, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (wave > 0) {
+    auto issue = [&](int d) {
+      const uint32_t to = ring + (uint32_t)(d % NST) * kStage;
+      src.issue(2 * d, to);
+      src.issue(2 * d + 1 < nsteps ? 2 * d + 1 : 2 * d, to + kStep);
+    };
+    for (int d = 0; d < NST - 1 && d < pairs; ++d) issue(d);
+    for (int d = 0; d < pairs; ++d) {
+      // pair d has landed; behind the barrier pair d - 1 is in the registers of the first wavefront
+      const int younger = pairs - 1 - d;
+      wait_tail<2 * Quarter::kIss, NST - 2>(younger < NST - 2 ? younger : NST - 2);
+      lds_barrier();
+      if (d + NST - 1 < pairs) issue(d + NST - 1);
+    }
+    return;
+  }
+  const int lane = threadIdx.x % kWave, r = lane % 32, h2 = lane / 32, sw = (r & 7) ^ (r >> 3);
+  uint32_t a_off[4], b_off[4];       // weight rows, token rows
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    b_off[k] = ring + (uint32_t)(r * 128 + (((2 * k + h2) ^ sw) << 4));
+    a_off[k] = ring + (uint32_t)((32 + r) * 128 + (((2 * k + h2) ^ sw ^ 4) << 4));
+  }
+  struct Operands {
+    uint4 a[8], b[8];
+  } f[2];
+  auto read = [&](Operands& o, int d) {
+    const uint32_t st = (uint32_t)(d % NST) * kStage;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      o.a[k] = lds_read16(a_off[k % 4] + st + k / 4 * kStep);
+      o.b[k] = lds_read16(b_off[k % 4] + st + k / 4 * kStep);
+    }
+  };
+  auto multiply = [&](const Operands& o) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc = mfma32<DT>(o.a[k], o.b[k], acc);
+  };
+  if (pairs > 0) {
+    lds_barrier();
+    read(f[0], 0);
+  }
+  int d = 1;
+  for (; d + 1 < pairs; d += 2) {
+    lds_barrier();                   // (waits for the reads of pair d - 1)
+    read(f[1], d);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(f[0]);
+    lds_barrier();
+    read(f[0], d + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(f[1]);
+  }
+  if (d < pairs) {
+    lds_barrier();
+    read(f[1], d);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(f[0]);
+    f[0] = f[1];
+  }
+  const int last = pairs > 0 ? nsteps - 2 * (pairs - 1) : 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (last > 0) acc = mfma32<DT>(f[0].a[k], f[0].b[k], acc);
+  if (last > 1) {
+#pragma unroll
+    for (int k = 4; k < 8; ++k) acc = mfma32<DT>(f[0].a[k], f[0].b[k], acc);
+  }
+}
+
 }  // namespace lx

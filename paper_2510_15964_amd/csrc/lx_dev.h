@@ -67,6 +67,13 @@ __device__ __forceinline__ void dma16_s(const void* base, uint32_t voff, uint32_
                : "m0");
 }
 
+// ... to lds + IMM
+template <int IMM>
+__device__ __forceinline__ void dma16_s_at(const void* base, uint32_t voff, uint32_t lds) {
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base), "n"(IMM)
+               : "m0", "scc");
+}
+
 // dma16 with 4 bytes per lane (lane l lands at lds_wave_base + 4*l).
 __device__ __forceinline__ void dma4(const void* gptr, uint32_t lds_wave_base) {
   const uint32_t l = __builtin_amdgcn_readfirstlane(lds_wave_base);
