@@ -663,22 +663,6 @@ __device__ __forceinline__ void store_quarter(const f32x16& acc, uint32_t lds, c
       *reinterpret_cast<uint4*>(p) = v;
   }
 }
-// The transfers of one operand's 32 rows: this lane's offsets from their first element, rows ld elements apart (32 of
-// them within 4 GiB: quarters_pay); `second`: the weight rows, which come after the token rows in a stage.
-struct QuarterRows {
-  uint32_t voff[4];
-  __device__ __forceinline__ void init(long long ld, bool second) {
-    const int lane = threadIdx.x % kWave, lr = lane / 8;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) voff[u] = (uint32_t)((8 * u + lr) * ld * 2 + (((lane % 8) ^ lr ^ (second ? 4 + u : u)) << 4));
-  }
-  __device__ __forceinline__ void issue(const uint16_t* first, uint32_t lds) const {
-    dma16_s_at<0>(first, voff[0], lds);
-    dma16_s_at<1024>(first, voff[1], lds);
-    dma16_s_at<2048>(first, voff[2], lds);
-    dma16_s_at<3072>(first, voff[3], lds);
-  }
-};
 // A wave-uniform pointer, for an operand that has to be scalar.  (readfirstlane returns a signed int.)
 __device__ __forceinline__ const uint16_t* scalar(const uint16_t* p) {
   const unsigned long long v = reinterpret_cast<unsigned long long>(p);

@@ -242,6 +242,22 @@ struct Quarter {
   static constexpr int kElems = 64 * kBK;               // of a step: 32 token rows, 32 weight rows, laid out like the others
   static constexpr int kIss = 4;                        // transfer instructions of a wavefront per step
 };
+// The transfers of one operand's 32 rows: this lane's offsets from their first element, rows ld elements apart (32 of
+// them within 4 GiB: quarters_pay); `second`: the weight rows, which come after the token rows in a stage.
+struct QuarterRows {
+  uint32_t voff[4];
+  __device__ __forceinline__ void init(long long ld, bool second) {
+    const int lane = threadIdx.x % kWave, lr = lane / 8;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) voff[u] = (uint32_t)((8 * u + lr) * ld * 2 + (((lane % 8) ^ lr ^ (second ? 4 + u : u)) << 4));
+  }
+  __device__ __forceinline__ void issue(const uint16_t* first, uint32_t lds) const {
+    dma16_s_at<0>(first, voff[0], lds);
+    dma16_s_at<1024>(first, voff[1], lds);
+    dma16_s_at<2048>(first, voff[2], lds);
+    dma16_s_at<3072>(first, voff[3], lds);
+  }
+};
 // acc += sum over nsteps steps, in the order of run_tile, in the first wavefront.  NST stages of two steps each.
 // src.issue(step, LDS address) starts the calling wavefront's transfers of a step (steps past the end: the last one again).
 template <int DT, int NST, class Src>

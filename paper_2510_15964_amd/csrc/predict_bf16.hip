@@ -1,7 +1,8 @@
 // Inference side of the MLP predictor (Sec. V-A) for gfx950: block scores on the MFMA, threshold
 // and reduction over a group of tokens fused into the epilogue.  Templates over the 16-bit
-// element type like the FFN kernels, whose transfer ring they share.
-#include "ffn_ring.h"
+// element type like the FFN kernels, whose transfer ring and quarter tile they share.
+#include "ffn_plan.h"
+#include "ffn_tile.h"
 
 namespace lx {
 
@@ -166,6 +167,43 @@ __global__ __launch_bounds__(kThreads) void predict_half_bf16(
   }
 }
 
+// Few token tiles and K no multiple of 128: a workgroup per 32 rows of Wa_t x 32 tokens (Quarter), with the sums of
+// predict_bf16, bit for bit.  192 tokens, d = 5056, 320 blocks: 25 us by predict_bf16<1>,
+// 12 by quarters.
+struct PredictSrc {
+  const uint16_t* rows;
+  QuarterRows t;
+  uint32_t at;
+  __device__ __forceinline__ void issue(int s, uint32_t lds) const { t.issue(rows + (long long)s * kBK, lds + at); }
+};
+template <int DT, int NST>
+__global__ __launch_bounds__(Quarter::kTileThreads, 2) void predict_quarter_bf16(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wa_t, int tiles, int K, int nblk,
+    int tiles_per_group, float thr, uint8_t* __restrict__ mask) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * 2 * Quarter::kElems];
+  const int w = blockIdx.x, unit = w / 32 * 8 + w % 8, q = w / 8 % 4;     // quarters of a tile on one XCD
+  const int i = unit % tiles, r0 = unit / tiles * 64 + 32 * (q / 2);
+  if (r0 >= nblk) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+  PredictSrc src;
+  src.rows = wave == 2 ? Wa_t + (long long)r0 * K : X + ((long long)i * 64 + 32 * (q % 2)) * K;
+  src.at = wave == 2 ? 32 * kBK * 2 : 0;
+  src.t.init(K, wave == 2);
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  run_quarter<DT, NST>(K / kBK, lds_addr(ring), src, acc);
+  if (wave > 0) return;
+  uint8_t* out = mask + (long long)(i / tiles_per_group) * nblk + r0;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const unsigned long long hit = __ballot(acc[v] > thr);
+    const int n = 8 * (v / 4) + v % 4;
+    if (lane == 0 && (uint32_t)hit != 0u) out[n] = 1;
+    if (lane == 32 && (hit >> 32) != 0ull) out[n + 4] = 1;
+  }
+}
+
 __global__ void zero_bytes_kernel(uint8_t* __restrict__ p, int n) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx < n) p[idx] = 0;
@@ -191,6 +229,10 @@ static hipError_t launch_predict_bf16_t(int T, int d, int nblk, int tiles_per_gr
   else if ((long long)ng * Tt < kCUs && d % 128 == 0)
     hipLaunchKernelGGL(predict_half_bf16<DT>, dim3(2 * ng * T8), dim3(kThreads), 0, st, X, Wa_t, Tt, d,
                        nblk, tiles_per_group, thr, mask);
+  else if (quarters_pay(ng * Tt, d, 0))
+    hipLaunchKernelGGL((ng * Tt <= kQuarterTilesAlone ? predict_quarter_bf16<DT, 8> : predict_quarter_bf16<DT, 4>),
+                       dim3(32 * ((ng * Tt + 7) / 8)), dim3(Quarter::kTileThreads), 0, st, X, Wa_t, Tt, d, nblk, tiles_per_group,
+                       thr, mask);
   else
     hipLaunchKernelGGL((predict_bf16<DT, 1>), dim3(ng * T8), dim3(kThreads), 0, st, X, Wa_t, Tt, d, nblk,
                        tiles_per_group, thr, mask);
