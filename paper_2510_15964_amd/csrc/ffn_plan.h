@@ -65,7 +65,7 @@ inline bool tile_fits(const TileInfo& t, int Tt, int gt, int want) {
 // stay below 2^30: the launchers' callers see to that.)
 LX_HD int sdd_grid(const TileInfo& t, int Tt, int gt, int n) {
   if (gt == Tt) return 8 * ceil_div(ceil_div(Tt, t.tm) * ceil_div(n, t.tn), 8);
-  // items <= entries / tn + a ragged group per row; per XCD L = ceil(items / 8) of them in 8 * ceil(L / 8) slots
+  // items <= entries / tn + a ragged group per row; per XCD L = ceil(items / 8) of them in 4 * ceil(L / 4) slots at most
   const int items = ceil_div(n * (int)((unsigned)gt / t.tm), t.tn) + (t.tn > 1 ? (unsigned)Tt / t.tm : 0u);
   return 64 * ceil_div(ceil_div(items, 8), 8);
 }
