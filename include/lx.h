@@ -385,6 +385,9 @@ lx_status lx_sparse_attn_fwd(lx_dtype dt, int32_t B, int32_t Hh, int32_t S, int3
  *            rows = mask_batch*Hh*(S/64) ordered (batch, head, key block),
  *            entries = query blocks.
  *   workspace  >= lx_sparse_attn_bwd_workspace_bytes (holds Delta and a rescaled LSE).
+ * Overlap: dQ may be written in the place of O, dK of K and dV of V; dK and dV may also lie anywhere over O, LSE and the
+ * arrays of bl_rows, and over a dQ that is not wanted.  No other overlap is allowed.  The query side (dQ) then runs
+ * before the key side; small 16-bit calls whose outputs overlap nothing run both in one launch, with the same results.
  */
 lx_status lx_sparse_attn_bwd_dx(lx_dtype dt, int32_t B, int32_t Hh, int32_t S, int32_t D,
                                 float scale, int32_t causal, const void* Q, const void* K,

@@ -48,6 +48,7 @@
 //    lanes 0-3, 4-7, 8-11, 12-15).
 #include <type_traits>
 
+#include "attn_plan.h"
 #include "lx_dev.h"
 #include "lx_launch.h"
 
@@ -1143,23 +1144,18 @@ static hipError_t launch_fwd(const AttnArgs& a, int B, hipStream_t st) {
   return a.ss < kWideStride ? launch_fwd_t<D, DT, false>(a, B, st) : launch_fwd_t<D, DT, true>(a, B, st);
 }
 
-// Whether the two sides of a backward pass run in one launch.  The key side then makes Delta itself, for every block that
-// it streams, from O tiles of which the other two launches need none; and a CU has room for three workgroups (head size
-// 64) or one (128: three tiles a stage are 96 KB).  What it saves is the chain of loads that starts a launch, and a
-// launch that lasts as long as its longest row; so it pays while the rows of both sides are resident at about the same
-// time, two each: up to 768 rows of both heads and batch (1.3 - 1.6 times faster: 12 heads of 320 tokens 18 -> 12 us, 3 x
-// 32 of 512 21 -> 14, 10 of 3136 121 -> 75), with short rows up to 1728 (1.02 - 1.2; 16 heads of 4096, all blocks 0.97, 24
-// of 4096 0.88); head size 128 up to 256 (1.2 - 1.6; 384 rows 1.07, 512 0.96).  Results are the same to the last bit.
-// An output on the place of an input (dK on K, say), which the order of the launches allows, keeps them apart.
+// Whether the two sides of a backward pass run in one launch: results are the same to the last bit.
 constexpr int kBothOcc(int D) { return D == 64 ? 3 : 1; }
 static bool bwd_in_one(const AttnArgs& a, int D, int B) {
   const int nblk = a.S / 64;
-  const long long rows = (long long)B * a.Hh * nblk;
-  if (D == 128 ? rows > 256 : rows > 768 && (rows > 1728 || rows * nblk > 20000)) return false;
-  for (const uint16_t* out : {a.dQ, a.dK, a.dV})
-    for (const uint16_t* in : {a.Q, a.K, a.V, a.O, a.dO})
-      if (out == in) return false;
-  return true;
+  if (!bwd_one_launch_pays(D, (long long)B * a.Hh * nblk, nblk)) return false;
+  const long long rows = (long long)a.mask_batch * a.Hh * nblk, stats = (long long)B * a.Hh * a.S * 4;
+  return bwd_sides_apart({{{B, a.Hh, a.S}, {2 * a.sb, 2 * a.sh, 2 * a.ss}, 2 * D},
+                          {a.Q, a.K, a.V, a.O, a.dO},
+                          {a.dQ, a.dK, a.dV},
+                          {a.LSEin, stats},
+                          {{a.row_ptr, 4 * (rows + 1)}, {a.col_idx, 4ll * a.nnz_cap}},
+                          {{a.Delta, stats}, {a.NegLse2, stats}}});
 }
 template <int D, int DT, bool WIDE>
 static hipError_t launch_bwd_t(AttnArgs a, int B, hipStream_t st) {

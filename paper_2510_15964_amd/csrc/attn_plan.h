@@ -1,0 +1,96 @@
+// Which attention backward calls run their two sides in one launch.  Plain C++, without the device's headers.
+#pragma once
+
+namespace lx {
+
+// Where the elements of a call's tensors [B, Hh, S, D] lie, in bytes: rows of `row`, n[i] of them stride[i] apart.
+struct TensorShape {
+  long long n[3], stride[3], row;
+  long long extent() const {
+    long long e = row;
+    for (int i = 0; i < 3; ++i) e += (n[i] - 1) * stride[i];
+    return e;
+  }
+};
+struct Range {
+  const void* p;
+  long long bytes;
+};
+inline long long byte_distance(const void* a, const void* b) { return (const char*)b - (const char*)a; }
+inline bool ranges_meet(const Range& a, const Range& b) {
+  const long long d = byte_distance(a.p, b.p);
+  return d < a.bytes && -d < b.bytes;
+}
+// Whether two tensors of that shape, the second `delta` bytes behind the first, have a byte in common: some difference of
+// two of their rows' places is less than a row from delta.  The places are sums over the dimensions, so this goes down
+// from the longest stride, with the differences that the shorter ones can still make up for: two at most where the
+// dimensions are nested, which tensors interleaved in one buffer are too.  Where they are not, and there are many, the
+// tensors count as meeting.
+inline bool tensors_meet(const TensorShape& t, long long delta) {
+  struct {
+    long long n, stride;
+  } dim[3];
+  int dims = 0;
+  for (int i = 0; i < 3; ++i) {
+    if (t.n[i] <= 1 || t.stride[i] == 0) continue;
+    int at = dims++;
+    for (; at > 0 && dim[at - 1].stride < t.stride[i]; --at) dim[at] = dim[at - 1];
+    dim[at] = {t.n[i], t.stride[i]};
+  }
+  struct Walk {
+    decltype(dim)& d;
+    int dims;
+    long long row;
+    bool operator()(long long delta, int level) const {
+      if (level == dims) return delta < row && -delta < row;
+      const long long s = d[level].stride, most = d[level].n - 1;
+      long long reach = row - 1;       // of the dimensions below
+      for (int i = level + 1; i < dims; ++i) reach += (d[i].n - 1) * d[i].stride;
+      auto floor_div = [&](long long a) { return a >= 0 ? a / s : -((-a + s - 1) / s); };
+      long long lo = -floor_div(reach - delta), hi = floor_div(delta + reach);
+      lo = lo < -most ? -most : lo;
+      hi = hi > most ? most : hi;
+      if (hi - lo >= 8) return true;
+      for (long long k = lo; k <= hi; ++k)
+        if ((*this)(delta - k * s, level + 1)) return true;
+      return false;
+    }
+  };
+  return Walk{dim, dims, t.row}(delta, 0);
+}
+
+// The buffers of a backward call: tensors of one shape, and what lies in one piece.
+struct BwdBuffers {
+  TensorShape shape;
+  const void *in[5], *out[3];          // Q, K, V, O, dO; dQ, dK, dV
+  Range lse, list[2];                  // list: what the query side walks
+  Range scratch[2];                    // Delta, the rescaled LSE
+};
+// Whether the two sides may run side by side.  One after the other, an output may lie over whatever the query side alone
+// reads (O, LSE, its list) or over the rows that a workgroup alone reads (dK on K, dV on V, dQ on O), an output that is not
+// wanted on another one's place, and the rescaled LSE on LSE.
+inline bool bwd_sides_apart(const BwdBuffers& b) {
+  const long long extent = b.shape.extent();
+  for (int o = 0; o < 3; ++o) {
+    for (const void* in : b.in)
+      if (tensors_meet(b.shape, byte_distance(in, b.out[o]))) return false;
+    for (int p = 0; p < o; ++p)
+      if (tensors_meet(b.shape, byte_distance(b.out[p], b.out[o]))) return false;
+    const Range out = {b.out[o], extent};
+    if (ranges_meet(out, b.lse) || ranges_meet(out, b.list[0]) || ranges_meet(out, b.list[1])) return false;
+  }
+  return !ranges_meet(b.scratch[0], b.lse) && !ranges_meet(b.scratch[1], b.lse);
+}
+
+// Whether one launch pays.  The key side then makes Delta itself, for every block that it streams, from O tiles of which the
+// other two launches need none; and a CU has room for three workgroups (head size 64) or one (128: three tiles a stage
+// are 96 KB).  What it saves is the chain of loads that starts a launch, and a launch that lasts as long as its longest
+// row; so it pays while the rows of both sides are resident at about the same time, two each: up to 768 rows of all
+// heads and batch entries (1.3 - 1.6 times faster: 12 heads of 320 tokens 18 -> 12 us, 3 x 32 of 512 21 -> 14, 10 of 3136
+// 121 -> 75), with short rows up to 1728 (1.02 - 1.2; 16 heads of 4096, all blocks 0.97, 24 of 4096 0.88); head size 128
+// up to 256 (1.2 - 1.6; 384 rows 1.07, 512 0.96).
+inline bool bwd_one_launch_pays(int D, long long rows, int nblk) {
+  return D == 128 ? rows <= 256 : rows <= 768 || (rows <= 1728 && rows * nblk <= 20000);
+}
+
+}  // namespace lx

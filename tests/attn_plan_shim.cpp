@@ -1,0 +1,24 @@
+// Which attention backward calls run in one launch (csrc/attn_plan.h), as C functions.
+#include "../paper_2510_15964_amd/csrc/attn_plan.h"
+
+using namespace lx;
+
+extern "C" {
+
+int meet(const long long* n, const long long* stride, long long row, long long delta) {
+  return tensors_meet({{n[0], n[1], n[2]}, {stride[0], stride[1], stride[2]}, row}, delta);
+}
+int pays(int D, long long rows, int nblk) { return bwd_one_launch_pays(D, rows, nblk); }
+// at: byte addresses of Q, K, V, O, dO; dQ, dK, dV; LSE, row_ptr, col_idx, Delta, the rescaled LSE
+int sides_apart(const long long* n, const long long* stride, long long row, const long long* at, long long stats, long long ptrs,
+                long long entries) {
+  auto p = [&](int i) { return (const void*)at[i]; };
+  return bwd_sides_apart({{{n[0], n[1], n[2]}, {stride[0], stride[1], stride[2]}, row},
+                          {p(0), p(1), p(2), p(3), p(4)},
+                          {p(5), p(6), p(7)},
+                          {p(8), stats},
+                          {{p(9), ptrs}, {p(10), entries}},
+                          {{p(11), stats}, {p(12), stats}}});
+}
+
+}  // extern "C"
