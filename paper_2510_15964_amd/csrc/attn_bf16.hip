@@ -816,7 +816,7 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
       store_acc16<D, DT>(z, 0.f, a.dQ + base_of(hh) + (long long)(rows.blk(j) * 64 + ql) * a.ss);
       if (g == 0) {
         a.Delta[stat_of(hh) + rows.blk(j) * 64 + ql] = 0.f;
-        a.NegLse2[stat_of(hh) + rows.blk(j) * 64 + ql] = INFINITY;
+        a.NegLse2[stat_of(hh) + rows.blk(j) * 64 + ql] = -INFINITY;      // no probability, if a column list names the row
       }
     }
 

@@ -138,3 +138,38 @@ def test_outputs_over_inputs(lx, place):
         if k == "dQ" and place[0] == "dQ" and place[1] in one:
             continue                                             # (overwritten by the output that is wanted)
         assert torch.isfinite(one[k].float()).all() and torch.equal(one[k], two[k]), k
+
+
+@pytest.mark.parametrize("dtype,D,B,Hh,launches", [("bf16", 64, 2, 6, 0), ("f16", 128, 1, 6, 0), ("bf16", 64, 8, 24, 1), ("f16", 128, 4, 10, 1)])
+def test_rows_emptied_by_their_list_s_capacity(lx, dtype, D, B, Hh, launches):
+    """Query rows that the capacity of the row list leaves without a block, but that the column list still names, have
+    LSE = -inf, and no part in dK and dV: as if the mask did not list them."""
+    import torch
+    S = 640
+    nb = S // 64
+    g = torch.Generator(device="cuda").manual_seed(D + B)
+    mask = (torch.rand(1, Hh, nb, nb, device="cuda", generator=g) < 0.6).to(torch.uint8)
+    short = mask.clone()
+    short[0, Hh - 2, 7:] = 0                                 # the last rows in list order
+    short[0, Hh - 1] = 0
+    tdt = dev(np.zeros(1, np.float32), dtype).dtype
+    Q, K, V, dO = (torch.randn(B, Hh, S, D, device="cuda", generator=g).to(tdt) for _ in range(4))
+    ws = torch.empty(lx.lx_sparse_attn_bwd_workspace_bytes(lx.LX_BF16, B, Hh, S, D), dtype=torch.uint8, device="cuda")
+
+    def run(rows, cols):
+        O, dQ, dK, dV = (torch.full_like(Q, float("nan")) for _ in range(4))
+        LSE = torch.full((B, Hh, S), float("nan"), device="cuda")
+        lx.lx_sparse_attn_fwd(Q, K, V, rows, D ** -0.5, False, O, LSE)
+        lx.lx_profile_begin(lx.LX_K_ATTN_BWD_DQ, 1)
+        try:
+            lx.lx_sparse_attn_bwd_dx(Q, K, V, O, LSE, dO, rows, cols, D ** -0.5, False, dQ, dK, dV, ws)
+        finally:
+            assert lx.lx_profile_end()[1] == launches
+        return O, LSE, dQ, dK, dV
+
+    cols = lx.lx_mask_compact(mask, transpose=True)
+    cut = run(lx.lx_mask_compact(mask, nnz_cap=int(short.sum())), cols)
+    ref = run(*lx.lx_mask_compact_pair(short))
+    assert torch.isneginf(cut[1][:, Hh - 1]).all()
+    for a, b in zip(cut, ref):
+        assert torch.equal(a, b)
