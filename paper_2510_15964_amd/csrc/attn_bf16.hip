@@ -1062,14 +1062,14 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) 
 }
 
 // Both sides in one launch (bwd_in_one): the first `half` workgroups take the key side, which is the longer one.
-template <int D, int DT, int NS, int OCC, bool WIDE>
+template <int D, int DT, int NS, int OCC>
 __global__ __launch_bounds__(kAT, OCC) void attn_bwd_both_bf16(const AttnArgs a, int half) {
   __shared__ __attribute__((aligned(2 * 64 * D))) DkvLds<D, NS, true> sh;
   static_assert(sizeof(DqLds<D, NS>) <= sizeof(sh), "shared memory");
   if ((int)blockIdx.x < half)
-    attn_bwd_dkv<D, DT, NS, WIDE, true>(a, blockIdx.x, sh);
+    attn_bwd_dkv<D, DT, NS, false, true>(a, blockIdx.x, sh);
   else
-    attn_bwd_dq<D, DT, NS, WIDE>(a, blockIdx.x - half, reinterpret_cast<DqLds<D, NS>&>(sh));
+    attn_bwd_dq<D, DT, NS, false>(a, blockIdx.x - half, reinterpret_cast<DqLds<D, NS>&>(sh));
 }
 
 
@@ -1134,7 +1134,7 @@ static int attn_grid(AttnArgs& a, int B, int slots) {
 template <int D, int DT, bool WIDE>
 static hipError_t launch_fwd_t(AttnArgs a, int B, hipStream_t st) {
   ProfScope ps(kKAttnFwd, st);
-  constexpr int kNs = D == 64 && !WIDE ? kFwdNs64 : 2, kOcc = D == 64 && !WIDE ? kFwdOcc64 : 2;
+  constexpr int kNs = D == 64 ? kFwdNs64 : 2, kOcc = D == 64 ? kFwdOcc64 : 2;
   const int grid = attn_grid(a, B, kCUs * kOcc);
   hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
   return hipGetLastError();
@@ -1159,16 +1159,17 @@ static bool bwd_in_one(const AttnArgs& a, int D, int B) {
 }
 template <int D, int DT, bool WIDE>
 static hipError_t launch_bwd_t(AttnArgs a, int B, hipStream_t st) {
-  if (bwd_in_one(a, D, B)) {
-    ProfScope ps(kKAttnDkv, st);
-    constexpr int kOcc = kBothOcc(D);
-    const int half = attn_grid(a, B, kCUs * kOcc / 2);
-    hipLaunchKernelGGL((attn_bwd_both_bf16<D, DT, 2, kOcc, WIDE>), dim3(2 * half), dim3(kAT), 0, st, a, half);
-    return hipGetLastError();
-  }
+  if constexpr (!WIDE)      // (long strides: see bwd_one_launch_pays)
+    if (bwd_in_one(a, D, B)) {
+      ProfScope ps(kKAttnDkv, st);
+      constexpr int kOcc = kBothOcc(D);
+      const int half = attn_grid(a, B, kCUs * kOcc / 2);
+      hipLaunchKernelGGL((attn_bwd_both_bf16<D, DT, 2, kOcc>), dim3(2 * half), dim3(kAT), 0, st, a, half);
+      return hipGetLastError();
+    }
   {
     ProfScope ps(kKAttnDq, st);
-    constexpr int kNs = D == 64 && !WIDE ? kDqNs64 : 2, kOcc = D == 64 && !WIDE ? kDqOcc64 : 2;
+    constexpr int kNs = D == 64 ? kDqNs64 : 2, kOcc = D == 64 ? kDqOcc64 : 2;
     const int grid = attn_grid(a, B, kCUs * kOcc);
     hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
   }
@@ -1176,7 +1177,7 @@ static hipError_t launch_bwd_t(AttnArgs a, int B, hipStream_t st) {
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKAttnDkv, st);
-    constexpr int kNs = D == 64 && !WIDE ? kDkvNs64 : 2, kOcc = D == 64 && !WIDE ? kDkvOcc64 : 2;
+    constexpr int kNs = D == 64 ? kDkvNs64 : 2, kOcc = D == 64 ? kDkvOcc64 : 2;
     const int grid = attn_grid(a, B, kCUs * kOcc);
     hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
   }

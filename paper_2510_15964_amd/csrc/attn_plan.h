@@ -88,7 +88,9 @@ inline bool bwd_sides_apart(const BwdBuffers& b) {
 // row; so it pays while the rows of both sides are resident at about the same time, two each: up to 768 rows of all
 // heads and batch entries (1.3 - 1.6 times faster: 12 heads of 320 tokens 18 -> 12 us, 3 x 32 of 512 21 -> 14, 10 of 3136
 // 121 -> 75), with short rows up to 1728 (1.02 - 1.2; 16 heads of 4096, all blocks 0.97, 24 of 4096 0.88); head size 128
-// up to 256 (1.2 - 1.6; 384 rows 1.07, 512 0.96).
+// up to 256 (1.2 - 1.6; 384 rows 1.07, 512 0.96).  Not at the token strides of the kernels with 64-bit addresses (kWideStride),
+// where every row lies in pages of its own and reading O again costs more than a launch: head size 64, 2^26 elements, 128
+// heads of 512 tokens 114 us in one, 102 in two; 256 of 256 76 and 72; 32 of 1024 96 and 86 (2^25: 62 and 59, 42 and 43, 55 and 53).
 inline bool bwd_one_launch_pays(int D, long long rows, int nblk) {
   return D == 128 ? rows <= 256 : rows <= 768 || (rows <= 1728 && rows * nblk <= 20000);
 }

@@ -173,3 +173,29 @@ def test_rows_emptied_by_their_list_s_capacity(lx, dtype, D, B, Hh, launches):
     assert torch.isneginf(cut[1][:, Hh - 1]).all()
     for a, b in zip(cut, ref):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("ss,launches", [((1 << 25) - 8, 0), (1 << 25, 1)])
+def test_long_token_strides_run_in_two(lx, D, ss, launches):
+    """From the strides on that have 64-bit addresses; bits as of contiguous tensors: test_gpu_attn_strides.py."""
+    import torch
+    Hh, S = 2, 64
+    torch.cuda.empty_cache()
+    buf = torch.empty((S - 1) * ss + 8 * Hh * D, dtype=torch.bfloat16, device="cuda")
+    Q, K, V, dO, O, dQ, dK, dV = (buf.as_strided((1, Hh, S, D), (Hh * D, D, ss, 1), i * Hh * D) for i in range(8))
+    for t in (Q, K, V, dO):
+        t.normal_()
+    rows, cols = lx.lx_mask_compact_pair(torch.ones(1, Hh, 1, 1, dtype=torch.uint8, device="cuda"))
+    LSE = torch.empty((1, Hh, S), device="cuda")
+    ws = torch.empty(lx.lx_sparse_attn_bwd_workspace_bytes(lx.LX_BF16, 1, Hh, S, D), dtype=torch.uint8, device="cuda")
+    lx.lx_sparse_attn_fwd(Q, K, V, rows, D ** -0.5, True, O, LSE)
+    lx.lx_profile_begin(lx.LX_K_ATTN_BWD_DQ, 1)
+    try:
+        lx.lx_sparse_attn_bwd_dx(Q, K, V, O, LSE, dO, rows, cols, D ** -0.5, True, dQ, dK, dV, ws)
+        torch.cuda.synchronize()
+    finally:
+        assert lx.lx_profile_end()[1] == launches
+    assert all(torch.isfinite(t.float()).all() for t in (dQ, dK, dV))
+    del buf, Q, K, V, dO, O, dQ, dK, dV
+    torch.cuda.empty_cache()
