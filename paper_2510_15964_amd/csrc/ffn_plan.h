@@ -287,7 +287,7 @@ inline bool dsd_may_mix(const DsdPlan& p, int Tt, int gt, int d, int nnz_cap, in
 constexpr int kQuarterTiles = kCUs / 2, kQuarterTilesAlone = kCUs / 4;
 inline bool quarters_pay(int items, long long ld, int want) { return want == 0 && items <= kQuarterTiles && ld < 1 << 25; }
 
-// Lists per group of token tiles: the units are (column chunk, of GN; token group, of GM).  Three ways to deal them:
+// Lists per group of token tiles: the units are (column chunk, of GN; token group, of GM).  The ways to deal them:
 // - kByChunk: XCD w % 8 takes the w % 8th eighth of the units, chunk after chunk, and so fetches the weight rows of an
 //   eighth of the columns only.  Where an eighth ends inside a chunk, its parts get long and short lists in
 //   proportion: the groups by length (rank 0: the longest list) are dealt evenly over them.  Inside a part the longest go
@@ -298,14 +298,24 @@ inline bool quarters_pay(int items, long long ld, int want) { return want == 0 &
 //   length: they walk along the columns at the same pace, and what one fetches the others find in the L2 (4096 tokens,
 //   d = 4096, 10 % of the blocks: 84.5 us, 89.4 by kByChunk).  With other numbers every XCD fetches all columns: 8192 tokens,
 //   d = 4160, 8 % 207 us, 137 by kByChunk; 7424 tokens, d = 2624, 25 % 238 and 142; 2048 tokens, d = 3200, 50 % 214 and 133.
+//   By 64 columns (tiles of one weight group) the workgroups of a tile that run together are many, and by rank is the better
+//   one also with a multiple of four chunks: d = 768, 96 tiles, 20 % 23.6 us, 26.5 by kByChunk; d = 1280, 64 tiles, 10 % 21.3
+//   and 23.4.
 // - kUnranked: kByChunk by the number of the token group instead of its rank, up to one workgroup per CU: nothing to even
 //   out, and the ranking costs a load and three barriers.
-enum DsdOrder { kByChunk, kByRank, kUnranked };
+// - kByFill: the kernel takes kByRank if every block is listed, when all lists are one and the tiles keep in step without
+//   more ado, kByChunk otherwise.  For capacities of every block and twelve chunks or more, an even number: 64 tiles, d = 4608,
+//   100 / 98 / 90 % of the blocks 913 / 858 / 936 us by rank and 980 / 833 / 718 by chunk; d = 5120, 100 / 98 % 1018 / 943 and
+//   1073 / 918; d = 3072 381 / 368 and 411 / 365; ten chunks 280 / 272 and 277 / 259; 13 chunks 505 / 463 and 446 / 393.
+enum DsdOrder { kByChunk, kByRank, kUnranked, kByFill };
 constexpr int kBalTiles = 128;     // most token groups that are ranked; beyond, their numbers take the place of the ranks
 // `weights`: bytes of the matrix.  One that fits an L2 (4 MB) may be in all of them: 5184 tokens, d = 704 11.7 us by rank, 12.0.
-inline DsdOrder dsd_order(int GM, int GN, bool lean, long long weights) {
+// every_block: the capacity of the lists is that.
+inline DsdOrder dsd_order(int GM, int GN, int tn, bool lean, long long weights, bool every_block) {
   if (GM * GN <= kCUs) return kUnranked;
-  return !lean && (GN % 8 == 0 || 8 % GN == 0 || weights <= 4 << 20) ? kByRank : kByChunk;
+  if (lean) return kByChunk;
+  if (GN % 8 == 0 || 8 % GN == 0 || weights <= 4 << 20 || (tn == 1 && GN % 4 == 0)) return kByRank;
+  return every_block && GN >= 12 && GN % 2 == 0 ? kByFill : kByChunk;
 }
 // a / b for a >= 0, b > 0: a reciprocal and a correction (the compiler's division is some forty instructions, and
 // they stand at the head of a workgroup's chain of loads)
@@ -361,14 +371,20 @@ LX_HD bool dsd_unit(int order, int GM, int GN, int w, int& chunk, int& rank) {
 //   tokens, d = 4096, 8 % 172 -> 162; at 850 and more 1.0 - 1.15);
 // - second product: where an XCD's eighth is whole column chunks of more than 64 token groups, which two per CU would
 //   walk through in more than one round, fetching the chunk's weight rows in each (8192 tokens, d = 2048, 10 / 30 % 50 / 101
-//   -> 43 / 94 us; d = 4096, 8 % 125 -> 112; with parts of chunks or 64 groups 0.98 - 1.11 of the time).
-LX_HD bool sdd_lean(int id, int Tt, int gt, int nnz_cap) {
+//   -> 43 / 94 us; with parts of chunks or 64 groups 0.98 - 1.11 of the time).  A chunk's rows have to fit an L2 for that, and
+//   the units must not fill whole rounds of two per CU (128 groups, d = 2048, 40 / 70 / 100 % 121 / 197 / 271 us by two, 121 / 202 / 280
+//   by four), or the lists have to be short, a quarter of the groups' number, so that few of the rows are in use at a time:
+//   d = 4096 by two / by four, 128 groups of 13 / 26 / 52 entries 118 / 174 / 277 and 105 / 168 / 304 us, 81 groups of 12 / 25 / 50
+//   76 / 115 / 170 and 72 / 120 / 212.
+inline bool sdd_lean(int id, int Tt, int gt, int nnz_cap) {
   if (id != kT14 || gt == Tt) return false;
   const int items = sdd_items_about(kTileInfo[kT14], Tt, gt, (int)(6.f / 7.f * (float)nnz_cap));
   return items > 2 * kCUs && items <= 3 * kCUs;
 }
-LX_HD bool dsd_lean(int id, int Tt, int gt, int GM, int GN) {
-  return id == kT14 && gt != Tt && GN % 8 == 0 && GM > 64 && GM * GN > 2 * kCUs;
+inline bool dsd_lean(int id, int Tt, int gt, int GM, int GN, int nnz_cap, long long ldw) {
+  if (id != kT14 || gt == Tt || GN % 8 != 0 || GM <= 64 || GM * GN <= 2 * kCUs) return false;
+  const float mean = 6.f / 7.f * (float)nnz_cap * gt / Tt;
+  return 4.f * mean <= (float)GM || (256 * 2 * ldw <= 4 << 20 && GM * GN % (2 * kCUs) != 0);
 }
 
 }  // namespace lx

@@ -12,13 +12,13 @@ int unit_of(int order, int GM, int GN, int w) {
 }
 int order_of(int Tt, int gt, int d, int Fb, int nnz_cap) {
   const int id = choose_dsd(Tt, gt, d, nnz_cap, 0, 0).id, GM = Tt / kTileInfo[id].tm, GN = ceil_div(d, 64 * kTileInfo[id].tn);
-  return dsd_order(GM, GN, dsd_lean(id, Tt, gt, GM, GN), 128ll * Fb * d);
+  return dsd_order(GM, GN, kTileInfo[id].tn, dsd_lean(id, Tt, gt, GM, GN, nnz_cap, 64ll * Fb), 128ll * Fb * d, nnz_cap >= Tt / gt * Fb);
 }
 // bit 0: the first product by tiles of one stage, bit 1: the second.
-int lean_of(int Tt, int gt, int d, int nnz_cap) {
+int lean_of(int Tt, int gt, int d, int Fb, int nnz_cap) {
   const int up = choose_sdd(Tt, gt, d, nnz_cap, 0), down = choose_dsd(Tt, gt, d, nnz_cap, 0, 0).id;
   const TileInfo& t = kTileInfo[down];
-  return (sdd_lean(up, Tt, gt, nnz_cap) ? 1 : 0) | (dsd_lean(down, Tt, gt, Tt / t.tm, ceil_div(d, 64 * t.tn)) ? 2 : 0);
+  return (sdd_lean(up, Tt, gt, nnz_cap) ? 1 : 0) | (dsd_lean(down, Tt, gt, Tt / t.tm, ceil_div(d, 64 * t.tn), nnz_cap, 64ll * Fb) ? 2 : 0);
 }
 int quick(int a, int b) { return quick_div(a, b); }
 
