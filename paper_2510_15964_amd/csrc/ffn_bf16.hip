@@ -41,14 +41,15 @@ constexpr int kRingElems = Tl::NST * Tl::kElems;
 // the host-known upper bound on their number and every wavefront finds its item from row_ptr with 64-wide
 // scans, so the active workgroups are the FIRST ones of the grid and spread evenly over shader engines and
 // CUs (a 2-D grid with early exits piles them onto a few CUs).
-// The items are numbered by the first halves of all lists, tile after tile, and then the second halves.
+// The items are numbered by the first halves of all lists, tile after tile, and then the second halves; without `halves` (see
+// sdd_halves) by the whole lists, which are then the first halves.
 // Workgroup w runs on XCD w % 8; it takes item of the range (w % 8) * L .. + L - 1 with L = ceil(total / 8), so
 // each XCD owns a quarter of the token tiles and, the lists being sorted, about half of the neuron axis.  Its L2
 // then fetches the rows of a quarter of the tokens and the listed ones of half of the weights, fewer bytes than
 // an eighth of the tokens and all listed weights (by the masks of 128 tiles, d = 4096, 8 % of the blocks: 470 MB over
 // the XCDs against 593 if all its workgroups kept step, d = 2048, 11 %: 156 and 184).  Returns false past the end.
 __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int rows, int gt, int w,
-                                          int per, int nnz_cap, int& row, int& chunk) {
+                                          int per, int nnz_cap, bool halves, int& row, int& chunk) {
   const int lane = threadIdx.x % kWave;
   // groups of entries of a token tile.  Entries of its list row count that lie within the capacity of the list buffers,
   // so that the number of items never exceeds the bound the grid was sized from
@@ -57,6 +58,8 @@ __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int r
     const int lr = r / gt;
     return (min(row_ptr[lr + 1], nnz_cap) - min(row_ptr[lr], nnz_cap) + per - 1) / per;
   };
+  // those of its first half
+  auto first_half = [&](int c) { return halves ? (c + 1) / 2 : c; };
   // inclusive sums over the lanes
   auto scan = [&](int v) {
 #pragma unroll
@@ -88,7 +91,7 @@ __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int r
   // product 11.9 us by the loops below, 10.9 so).
   if (rows <= 2 * kWave && (long long)nnz_cap * gt < 1 << 16) {
     const bool two = rows > kWave;
-    const int c0 = groups(two ? 2 * lane : lane), c1 = two ? groups(2 * lane + 1) : 0, h0 = (c0 + 1) / 2, h1 = (c1 + 1) / 2;
+    const int c0 = groups(two ? 2 * lane : lane), c1 = two ? groups(2 * lane + 1) : 0, h0 = first_half(c0), h1 = first_half(c1);
     const int c = c0 + c1, h = h0 + h1, both = scan(h | (c - h) << 16), all = __shfl(both, kWave - 1), firsts = all & 0xFFFF;
     int work = item_of(firsts + (int)((unsigned)all >> 16));
     if (work < 0) return false;
@@ -115,13 +118,13 @@ __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int r
     for (int dlt = 32; dlt > 0; dlt >>= 1) c += __shfl_xor(c, dlt);
     total += c;
   }
-  firsts = (total + firsts) / 2;       // (a first half is the longer one)
+  firsts = halves ? (total + firsts) / 2 : total;       // (a first half is the longer one)
   int work = item_of(total);
   if (work < 0) return false;
   const bool second = work >= firsts;
   if (second) work -= firsts;
   for (int base = 0; base < rows; base += kWave) {
-    const int c = groups(base + lane), h = (c + 1) / 2, mine = second ? c - h : h, incl = scan(mine);
+    const int c = groups(base + lane), h = first_half(c), mine = second ? c - h : h, incl = scan(mine);
     const int seg = __shfl(incl, kWave - 1);
     if (work < seg) {
       row = base + place(work, incl, mine, h, second);
@@ -229,7 +232,7 @@ struct SddArgs {
   int rows, blocks;            // list rows, and blocks that the list could hold
   int own, grid;               // of SddPlan
   unsigned allowed;
-  bool mix;                    // sdd_may_mix
+  bool mix, halves;            // sdd_may_mix, sdd_halves
   uint16_t* out;
   const uint16_t* gate;        // null: ReLU
   const uint16_t *A2, *W2;     // LORA
@@ -285,7 +288,7 @@ __device__ __forceinline__ void sdd_tile(const SddArgs& a, uint16_t* ring, GridI
     m = placed.m;
     chunk = placed.n;
   } else {
-    if (!find_work(a.row_ptr, a.Tt / Tl::TM, a.gt / Tl::TM, blockIdx.x, Tl::TN, a.nnz_cap, m, chunk)) return;
+    if (!find_work(a.row_ptr, a.Tt / Tl::TM, a.gt / Tl::TM, blockIdx.x, Tl::TN, a.nnz_cap, a.halves, m, chunk)) return;
     m = __builtin_amdgcn_readfirstlane(m);
     chunk = __builtin_amdgcn_readfirstlane(chunk);
     const int lr = m * Tl::TM / a.gt;
@@ -701,7 +704,7 @@ __global__ __launch_bounds__(Quarter::kTileThreads, 2) void ffn_sdd_quarter(SddA
     m = it.m;
     e = it.n;
   } else {
-    if (!find_work(a.row_ptr, a.Tt, a.gt, q.tile, 1, a.nnz_cap, m, e)) return;
+    if (!find_work(a.row_ptr, a.Tt, a.gt, q.tile, 1, a.nnz_cap, a.halves, m, e)) return;
     m = __builtin_amdgcn_readfirstlane(m);
     e = __builtin_amdgcn_readfirstlane(e);
     rs = a.row_ptr[m / a.gt];
@@ -839,6 +842,7 @@ size_t ffn_dsd_split_bytes(int Tt, int d, int nnz_cap) {
 
 template <int DT, bool LORA>
 static void launch_sdd(SddArgs a, hipStream_t st) {
+  a.halves = sdd_halves(a.Tt, a.gt, a.nnz_cap);
   const SddPlan p = plan_sdd(a.Tt, a.gt, a.K, a.nnz_cap, a.blocks, g_ffn_tiles_per_wg);
   if (p.grid == 0) return;
   if (const int items = (long long)a.nnz_cap * a.gt < 1 << 20 ? a.nnz_cap * a.gt : 1 << 20; quarters_pay(items, a.K, g_ffn_tiles_per_wg)) {
@@ -925,7 +929,7 @@ static hipError_t launch_ffn_bf16_t(int pass, int Tt, int gt, int Fb, int d, int
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
   {
     ProfScope ps(pass == 0 ? kKFfnUp : kKFfnDh, st);
-    launch_sdd<DT, false>({A, W1, pass == 0 ? b1 : nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, false, act_out,
+    launch_sdd<DT, false>({A, W1, pass == 0 ? b1 : nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, false, false, act_out,
                            pass == 0 ? nullptr : act_gate, nullptr, nullptr}, st);
   }
   hipError_t e = hipGetLastError();
@@ -960,7 +964,7 @@ static hipError_t launch_ffn_lora_fwd_bf16_t(int Tt, int gt, int d, int F, const
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKFfnUp, st);
-    launch_sdd<DT, true>({X, W_up, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, false, H_act, nullptr, U, B_pad}, st);
+    launch_sdd<DT, true>({X, W_up, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, false, false, H_act, nullptr, U, B_pad}, st);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -986,7 +990,7 @@ static hipError_t launch_ffn_lora_bwd_bf16_t(int Tt, int gt, int d, int F, const
   if (((long long)nnz_cap * gt + 3) / 4 + Tt > (1ll << 30)) return hipErrorInvalidValue;
   {
     ProfScope ps(kKFfnDh, st);
-    launch_sdd<DT, false>({dY, W_down_t, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, false, dZ, H_act, nullptr, nullptr},
+    launch_sdd<DT, false>({dY, W_down_t, nullptr, row_ptr, col_idx, Tt, gt, d, nnz_cap, Tt / gt, Tt / gt * (F / 64), 0, 0, 0u, false, false, dZ, H_act, nullptr, nullptr},
                           st);
   }
   hipError_t e = hipGetLastError();

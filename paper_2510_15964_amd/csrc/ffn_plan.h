@@ -364,6 +364,15 @@ LX_HD bool dsd_unit(int order, int GM, int GN, int w, int& chunk, int& rank) {
   rank = e;
   return true;
 }
+// First product, lists per group of token tiles: whether an XCD takes half of every list of a quarter of the tiles (see
+// find_work) or the whole lists of an eighth of them.  The half saves weight rows that several tiles of the XCD list, and
+// costs it the token rows of twice the tiles; with few entries in a list few are in common.  By halves / whole lists, us: 64
+// tiles, d = 2048, lists of 6 entries in the mean 24.5 / 22.4; 96, 2048, 7 34.0 / 31.4; 64, 3200, 10 46.7 / 43.6; 96, 2048, 13
+// 51.7 / 55.8; 128, 2048, 13 51.0 / 52.2; 128, 4096, 26 220 / 235.  980 launches of 2 - 10 % of the blocks take 0.982 of the
+// time by halves always, at most 1.09; lines at 8, 10 and 13 entries 0.985, 0.983 and 0.981, the last at most 1.09 in twice
+// as many launches.
+inline bool sdd_halves(int Tt, int gt, int nnz_cap) { return 6.f / 7.f * (float)nnz_cap * gt >= 11.f * (float)Tt; }
+
 // Lists per group of token tiles, 1 x 4 tiles: whether four workgroups per CU with one stage each (Tile14Lean) run the
 // launch instead of two with two stages.  A workgroup is slower with the one, so it has to pay otherwise:
 // - first product: up to one and a half rounds of two, where the second round is short (four: 0.8 - 1.0 of the time at

@@ -20,6 +20,8 @@ int lean_of(int Tt, int gt, int d, int Fb, int nnz_cap) {
   const TileInfo& t = kTileInfo[down];
   return (sdd_lean(up, Tt, gt, nnz_cap) ? 1 : 0) | (dsd_lean(down, Tt, gt, Tt / t.tm, ceil_div(d, 64 * t.tn), nnz_cap, 64ll * Fb) ? 2 : 0);
 }
+// 1: an XCD takes half of every list in the first product, 0: whole lists.
+int halves_of(int Tt, int gt, int nnz_cap) { return sdd_halves(Tt, gt, nnz_cap); }
 int quick(int a, int b) { return quick_div(a, b); }
 
 }  // extern "C"

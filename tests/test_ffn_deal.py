@@ -5,7 +5,7 @@ import subprocess
 
 import pytest
 
-from test_gpu_ffn_deal import CASES, FULL
+from test_gpu_ffn_deal import CASES, FULL, THIN
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 BY_CHUNK, BY_RANK, UNRANKED, BY_FILL = range(4)
@@ -49,7 +49,7 @@ def test_quotients(L):
 
 
 def test_labels_of_the_gpu_cases(L):
-    for _, Tt, gt, d, Fb, cap, lean, order, _ in CASES:
+    for _, Tt, gt, d, Fb, cap, lean, order, _ in CASES + THIN:
         assert (L.lean_of(Tt, gt, d, Fb, cap), L.order_of(Tt, gt, d, Fb, cap)) == (lean, order), (Tt, gt, d, Fb)
     assert {c[6] for c in CASES} == {0, 1, 2, 3} and {c[7] for c in CASES} == {BY_CHUNK, BY_RANK, UNRANKED}
 
@@ -73,3 +73,13 @@ def test_deals_where_the_other_one_was_slower(L, Tt, d, share, lean, order):
 def test_full_lists_are_dealt_by_what_they_hold(L):
     for _, Tt, d, Fb in FULL:
         assert L.order_of(Tt, 1, d, Fb, Tt * Fb) == BY_FILL and L.order_of(Tt, 1, d, Fb, Tt * Fb - 1) == BY_CHUNK
+
+
+def test_first_products_of_thin_lists_take_whole_ones(L):
+    """Lists of 6 - 10 entries in the mean, where halves were up to 1.13 times as slow; not the longer ones."""
+    for Tt, mean in ((64, 6), (96, 7), (64, 10), (128, 10)):
+        assert not L.halves_of(Tt, 1, int(1.1 * mean * Tt) + 64), (Tt, mean)
+    for Tt, mean in ((64, 13), (96, 13), (128, 14), (64, 50)):
+        assert L.halves_of(Tt, 1, int(1.1 * mean * Tt) + 64), (Tt, mean)
+    assert {L.halves_of(c[1], c[2], c[5]) for c in CASES} == {0, 1}
+    assert not any(L.halves_of(c[1], c[2], c[5]) for c in THIN)

@@ -123,3 +123,18 @@ def test_full_lists(lx, dtype, Tt, d, Fb, missing):
     assert torch.isfinite(Y).all()
     for i in sorted({0, 1, Tt // 2, Tt - 1, int(m.sum(1).argmin())}):
         assert torch.equal(Y[64 * i:64 * i + 64], run(X[64 * i:64 * i + 64], m[i:i + 1])), i
+
+
+# like CASES: lists of few entries, whose tiles' whole lists go to one XCD in the first product
+THIN = [
+    ("bf16", 129, 1, 1600, 24, 700, 0, 0, 0.15),      # rows beyond one scan
+    ("f16", 150, 3, 832, 40, 330, 0, 0, 0.12),
+    ("bf16", 64, 1, 512, 128, 800, 0, 2, 0.06),
+    ("bf16", 100, 1, 704, 30, 400, 0, 1, 0.1),        # two rows per lane
+]
+
+
+@pytest.mark.parametrize("lora", [False, True])
+@pytest.mark.parametrize("dtype,Tt,gt,d,Fb,cap,lean,order,density", THIN)
+def test_deals_of_thin_lists(lx, dtype, Tt, gt, d, Fb, cap, lean, order, density, lora):
+    test_deals(lx, dtype, Tt, gt, d, Fb, cap, lean, order, density, lora)
