@@ -507,12 +507,11 @@ __device__ __forceinline__ void dsd_tile(const DsdArgs& a, uint16_t* ring, GridI
       n_i = (int)((long long)n_i * (piece + 1) / a.pieces) - s_lo;
     }
   } else {
-    int chunk, rank, order = a.order;
-    if (order == kByFill) order = a.row_ptr[a.Tt / a.gt] >= a.nnz_cap ? kByRank : kByChunk;
-    if (!dsd_unit(order, a.GM, a.GN, blockIdx.x, chunk, rank)) return;
+    int chunk, rank;
+    if (!dsd_unit(a.order, a.GM, a.GN, blockIdx.x, chunk, rank)) return;
     chunk = __builtin_amdgcn_readfirstlane(chunk);
     rank = __builtin_amdgcn_readfirstlane(rank);
-    if (order != kUnranked)
+    if (a.order != kUnranked)
       rank = tile_of_rank(a.row_ptr, a.GM, a.gt / Tl::TM, a.nnz_cap, rank, reinterpret_cast<int*>(ring));
     i0 = Tl::TM * rank;
     n0 = chunk * (64 * Tl::TN);
@@ -898,7 +897,7 @@ static void launch_dsd(DsdArgs a, size_t part_bytes, hipStream_t st) {
   a.GM = a.Tt / t.tm;
   a.GN = ceil_div(a.ncols, 64 * t.tn);
   const bool lean = dsd_lean(p.id, a.Tt, a.gt, a.GM, a.GN, a.nnz_cap, a.ldw);
-  a.order = dsd_order(a.GM, a.GN, t.tn, lean, a.ldw * a.ncols * 2, a.nnz_cap >= a.Tt / a.gt * (a.ldw / 64));
+  a.order = dsd_order(a.GM, a.GN, t.tn, lean, a.ldw * a.ncols * 2);
   const dim3 grid(a.gt == a.Tt ? 8 * ceil_div(p.full, 8) + 8 * ceil_div((long long)p.rest * p.pieces, 8) : 8 * ceil_div(a.GM * a.GN, 8));
 #define LX_CALL(TL) hipLaunchKernelGGL((ffn_dsd<TL, DT, LORA>), grid, dim3(TL::kTileThreads), 0, st, a)
   if (lean)

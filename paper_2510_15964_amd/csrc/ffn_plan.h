@@ -303,19 +303,17 @@ inline bool quarters_pay(int items, long long ld, int want) { return want == 0 &
 //   and 23.4.
 // - kUnranked: kByChunk by the number of the token group instead of its rank, up to one workgroup per CU: nothing to even
 //   out, and the ranking costs a load and three barriers.
-// - kByFill: the kernel takes kByRank if every block is listed, when all lists are one and the tiles keep in step without
-//   more ado, kByChunk otherwise.  For capacities of every block and twelve chunks or more, an even number: 64 tiles, d = 4608,
-//   100 / 98 / 90 % of the blocks 913 / 858 / 936 us by rank and 980 / 833 / 718 by chunk; d = 5120, 100 / 98 % 1018 / 943 and
-//   1073 / 918; d = 3072 381 / 368 and 411 / 365; ten chunks 280 / 272 and 277 / 259; 13 chunks 505 / 463 and 446 / 393.
-enum DsdOrder { kByChunk, kByRank, kUnranked, kByFill };
+// With every block listed all lists are one, the tiles keep in step without more ado, and by rank is faster with an even
+// number of twelve chunks or more too: 64 tiles, d = 4608, 100 / 98 / 90 % of the blocks 913 / 858 / 936 us by rank and 980 / 833 / 718
+// by chunk; d = 5120, 100 / 98 % 1018 / 943 and 1073 / 918; d = 3072 381 / 368 and 411 / 365.  Only the device knows, and a kernel
+// that chose was slower elsewhere (48 tiles, d = 2048, 70 %, with the low-rank step 93 -> 105 us); one list row for all tiles
+// is the way to run full lists (680 us for the 1073).
+enum DsdOrder { kByChunk, kByRank, kUnranked };
 constexpr int kBalTiles = 128;     // most token groups that are ranked; beyond, their numbers take the place of the ranks
 // `weights`: bytes of the matrix.  One that fits an L2 (4 MB) may be in all of them: 5184 tokens, d = 704 11.7 us by rank, 12.0.
-// every_block: the capacity of the lists is that.
-inline DsdOrder dsd_order(int GM, int GN, int tn, bool lean, long long weights, bool every_block) {
+inline DsdOrder dsd_order(int GM, int GN, int tn, bool lean, long long weights) {
   if (GM * GN <= kCUs) return kUnranked;
-  if (lean) return kByChunk;
-  if (GN % 8 == 0 || 8 % GN == 0 || weights <= 4 << 20 || (tn == 1 && GN % 4 == 0)) return kByRank;
-  return every_block && GN >= 12 && GN % 2 == 0 ? kByFill : kByChunk;
+  return !lean && (GN % 8 == 0 || 8 % GN == 0 || weights <= 4 << 20 || (tn == 1 && GN % 4 == 0)) ? kByRank : kByChunk;
 }
 // a / b for a >= 0, b > 0: a reciprocal and a correction (the compiler's division is some forty instructions, and
 // they stand at the head of a workgroup's chain of loads)

@@ -12,7 +12,7 @@ int unit_of(int order, int GM, int GN, int w) {
 }
 int order_of(int Tt, int gt, int d, int Fb, int nnz_cap) {
   const int id = choose_dsd(Tt, gt, d, nnz_cap, 0, 0).id, GM = Tt / kTileInfo[id].tm, GN = ceil_div(d, 64 * kTileInfo[id].tn);
-  return dsd_order(GM, GN, kTileInfo[id].tn, dsd_lean(id, Tt, gt, GM, GN, nnz_cap, 64ll * Fb), 128ll * Fb * d, nnz_cap >= Tt / gt * Fb);
+  return dsd_order(GM, GN, kTileInfo[id].tn, dsd_lean(id, Tt, gt, GM, GN, nnz_cap, 64ll * Fb), 128ll * Fb * d);
 }
 // bit 0: the first product by tiles of one stage, bit 1: the second.
 int lean_of(int Tt, int gt, int d, int Fb, int nnz_cap) {

@@ -5,10 +5,10 @@ import subprocess
 
 import pytest
 
-from test_gpu_ffn_deal import CASES, FULL, THIN
+from test_gpu_ffn_deal import CASES, THIN
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-BY_CHUNK, BY_RANK, UNRANKED, BY_FILL = range(4)
+BY_CHUNK, BY_RANK, UNRANKED = range(3)
 
 
 @pytest.fixture(scope="module")
@@ -59,7 +59,6 @@ RULES = [
     (128, 4096, 0.08, 2, BY_CHUNK), (128, 4096, 0.2, 0, BY_RANK), (96, 4096, 0.2, 0, BY_RANK), (81, 4096, 0.4, 0, BY_RANK),
     (81, 4096, 0.05, 2, BY_CHUNK), (128, 2048, 0.11, 2, BY_CHUNK), (96, 2048, 1.0, 2, BY_CHUNK), (128, 2048, 0.9, 0, BY_RANK),
     (96, 768, 0.2, 0, BY_RANK), (64, 1280, 0.1, 0, BY_RANK), (128, 3200, 0.2, 0, BY_CHUNK), (64, 5120, 0.2, 0, BY_CHUNK),
-    (64, 5120, 1.0, 0, BY_FILL), (64, 4608, 1.0, 0, BY_FILL), (64, 2560, 1.0, 0, BY_CHUNK), (64, 3200, 1.0, 0, BY_CHUNK),
 ]
 
 
@@ -68,11 +67,6 @@ def test_deals_where_the_other_one_was_slower(L, Tt, d, share, lean, order):
     Fb = 4 * d // 64
     cap = min(Tt * Fb, int(1.1 * share * Tt * Fb) + 64)
     assert (L.lean_of(Tt, 1, d, Fb, cap) & 2, L.order_of(Tt, 1, d, Fb, cap)) == (lean, order)
-
-
-def test_full_lists_are_dealt_by_what_they_hold(L):
-    for _, Tt, d, Fb in FULL:
-        assert L.order_of(Tt, 1, d, Fb, Tt * Fb) == BY_FILL and L.order_of(Tt, 1, d, Fb, Tt * Fb - 1) == BY_CHUNK
 
 
 def test_first_products_of_thin_lists_take_whole_ones(L):

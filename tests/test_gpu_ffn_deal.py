@@ -93,38 +93,6 @@ def test_deals(lx, dtype, Tt, gt, d, Fb, cap, lean, order, density, lora):
             assert torch.equal(h.view(-1, 4096)[:lens[r]], H.view(-1, 4096)[torch.from_numpy(blocks).cuda()]), i
 
 
-# element type, token tiles, d, neuron blocks: capacities of every block with which the second product's deal depends on
-# whether all are listed
-FULL = [("bf16", 64, 1536, 24), ("f16", 66, 3072, 12), ("bf16", 32, 4608, 8)]
-
-
-@pytest.mark.parametrize("missing", [0, 1, 40])
-@pytest.mark.parametrize("dtype,Tt,d,Fb", FULL)
-def test_full_lists(lx, dtype, Tt, d, Fb, missing):
-    import torch
-    T, F = 64 * Tt, 64 * Fb
-    rng = np.random.default_rng(d + missing)
-    m = np.ones(Tt * Fb, np.uint8)
-    m[rng.permutation(Tt * Fb)[:missing]] = 0
-    m = m.reshape(Tt, Fb)
-    g = torch.Generator(device="cuda").manual_seed(d)
-    tdt = dev(np.zeros(1, np.float32), dtype).dtype
-    X = torch.randn(T, d, device="cuda", generator=g).to(tdt)
-    Wu, Wd = ((torch.randn(s, device="cuda", generator=g) * 0.05).to(tdt) for s in ((F, d), (d, F)))
-
-    def run(X, mask):
-        bl = lx.lx_mask_compact(torch.from_numpy(np.ascontiguousarray(mask)).cuda())
-        H = torch.empty(bl.nnz_cap * 4096, dtype=tdt, device="cuda")
-        Y = torch.full_like(X, float("nan"))
-        lx.lx_sparse_ffn_fwd(X, Wu, Wd, bl, 64, 64, Y, H)
-        return Y
-
-    Y = run(X, m)
-    assert torch.isfinite(Y).all()
-    for i in sorted({0, 1, Tt // 2, Tt - 1, int(m.sum(1).argmin())}):
-        assert torch.equal(Y[64 * i:64 * i + 64], run(X[64 * i:64 * i + 64], m[i:i + 1])), i
-
-
 # like CASES: lists of few entries, whose tiles' whole lists go to one XCD in the first product
 THIN = [
     ("bf16", 129, 1, 1600, 24, 700, 0, 0, 0.15),      # rows beyond one scan
