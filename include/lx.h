@@ -306,8 +306,8 @@ lx_status lx_sparse_ffn_bwd_dx(lx_dtype dt, int32_t T, int32_t d, int32_t F, int
  *   workspace  >= lx_sparse_ffn_lora_bwd_workspace_bytes(T, d, F, nnz_cap) with
  *              nnz_cap counted in activation blocks as for lx_sparse_ffn_bwd_workspace_bytes
  * U, dA and dB are summed over a number of ranges (of K, of token tiles) that depends
- * on the shape only, each range in ascending order and the ranges in a fixed order:
- * results are bit-reproducible.
+ * on the shape only (for dB also on how many tiles list a block), each range in ascending
+ * order and the ranges in a fixed order: results are bit-reproducible.
  */
 size_t lx_sparse_ffn_lora_fwd_workspace_bytes(int32_t T, int32_t d);
 size_t lx_sparse_ffn_lora_bwd_workspace_bytes(int32_t T, int32_t d, int32_t F, int32_t nnz_cap);

@@ -394,4 +394,16 @@ inline bool dsd_lean(int id, int Tt, int gt, int GM, int GN, int nnz_cap, long l
   return 4.f * mean <= (float)GM || (256 * 2 * ldw <= 4 << 20 && GM * GN % (2 * kCUs) != 0);
 }
 
+// Gradients of the LoRA matrices: whether a workgroup per quadrant of a product adds all its token tiles (lora_tn_quad), or
+// ranges of tiles are added apart, as parts in memory, and a second launch adds those.  By the shape only: the sums' order is
+// not to change with a list's capacity.  Quadrants read both operands twice, so there must not be much to add, and a
+// workgroup's start weighs as much as some ten tiles.  G, both gradients and the sums, us, by parts and by quadrants (F = 4 d, 5 / 20 / 70 % of
+// the blocks): 8 tiles, d = 1024 23.8 / 23.4 / 26.5 and 13.7 / 16.0 / 20.1; 32, 768 25.9 / 26.8 / 31.3 and 15.2 / 17.7 / 22.2; 64, 2048 25.6 / 31.1 / 44.6
+// and 23.0 / 28.7 / 48.9; 16, 5120 27.9 / 38.0 / 67.2 and 27.7 / 39.1 / 67.8; 24, 5120 30.3 / 39.7 / 76.4 and 32.2 / 43.2 / 83.7; 48, 3200 27.5 / 34.8 /
+// 55.6 and 24.4 / 33.4 / 62.5; past 64 tiles 128, 768 30.7 and 32.0.  A single tile has one part, so there is no second launch to be
+// saved: d = 3200 13.8 and 15.8, d = 5120 15.7 and 19.8.
+inline bool lora_grads_by_quads(int Tt, int d, int F) {
+  return Tt >= 2 && Tt <= 64 && (Tt + 10ll) * (d / 64 + F / 64) <= 12500;
+}
+
 }  // namespace lx

@@ -3,6 +3,7 @@
 // dA = G^T X, and the transpose of A.  A_pad [64, d] and B_pad [F, 64] hold
 // A [r, d] and B [F, r] zero-padded to rank 64.  The branch's steps inside the up-projection and
 // the input-gradient product live in the FFN kernels themselves.
+#include "ffn_plan.h"
 #include "ffn_ring.h"
 
 namespace lx {
@@ -453,12 +454,8 @@ __global__ __launch_bounds__(kThreads) void lora_tn_kernel(TnArgs db, TnArgs da,
 // each, in steps of 32 token rows through stages of their own (4 KB, no barrier), and add up through LDS in a fixed
 // order: there are no parts in memory and no launch that adds them.  The quadrants of a product sit eight
 // workgroups apart, on one XCD.  What bounds it is latency while all workgroups are resident at once, two per CU, and
-// their number times the tiles beyond that.  G, both gradients and the sums, us, by parts and by quadrants (F = 4 d): 3
-// tiles, d = 768 17.1 / 13.3; 8, 1024 23.8 / 15.3; 16, 2048 25.3 / 19.7; 32, 2048 26.0 / 21.1; 64, 768 27.2 / 22.0; 64, 2048
-// 28.8 / 26.5; 16, 5120 28.8 / 27.4; past the line 64, 2560 32.0 / 29.5; 32, 5120 34.4 / 36.2; 64, 5120 41.5 / 53.5; 128, 768
-// 30.7 / 32.0; 128, 2048 40.6 / 44.0; 256, 512 35.2 / 52.9.  Errors of dA and dB against 64 bits over eleven sizes are 0.91 - 1 and
-// 0.87 - 1 times those by parts.
-inline bool grads_by_quads(int Tt, int d, int F) { return Tt <= 64 && (long long)Tt * (d / 64 + F / 64) <= 12000; }
+// the products that they add beyond that (see lora_grads_by_quads).  Errors of dA and dB against 64 bits over eleven sizes are
+// 0.91 - 1 and 0.87 - 1 times those by parts.
 constexpr int kTnQuadStages = 2, kTnQuadStage = 4096;
 struct TnQuadLds {
   uint8_t ring[kFW * kTnQuadStages * kTnQuadStage];     // (the sums at the end: 32 KB)
@@ -639,7 +636,7 @@ static hipError_t launch_lora_grads_t(int Tt, int gt, int d, int F, const uint16
                                       const int* row_ptr, const int* col_idx, int nnz_cap,
                                       float* da_part, float* db_part, float* dA, float* dB,
                                       hipStream_t st) {
-  if (grads_by_quads(Tt, d, F)) {
+  if (lora_grads_by_quads(Tt, d, F)) {
     const TnArgs db = {dZ, U, 64, dB, 0, 64, F / 64, 1}, da = {G, X, d, dA, 0, d, d / 64, 1};
     hipLaunchKernelGGL(lora_tn_quad_kernel<DT>, dim3(tn_quads(db.nx) + tn_quads(da.nx)), dim3(kThreads), 0, st, db, da,
                        row_ptr, col_idx, Tt, gt, nnz_cap);

@@ -31,5 +31,7 @@ int dsd_tile(int Tt, int gt, int d, int nnz_cap, long long part_bytes, int want,
   *pieces = p.pieces;
   return p.id;
 }
+// 1: the gradients of the LoRA matrices by quadrants, 0: by parts.
+int grads_by_quads(int Tt, int d, int F) { return lora_grads_by_quads(Tt, d, F); }
 
 }  // extern "C"

@@ -8,6 +8,7 @@ import ffn_plan
 from ffn_plan import TILES
 from test_gpu_ffn_tiles import CAPACITIES, CUT_BY_TILE, EDGES
 from test_gpu_lora import LORA_TILES
+from test_gpu_lora_grads import CASES as GRADS
 
 
 @pytest.fixture(scope="module")
@@ -89,3 +90,12 @@ def test_gpu_cases_reach_every_tile(L):
     assert down == every, every - down
     assert {c[4] for c in LORA_TILES} == every and {c[5] for c in LORA_TILES} == every
     assert {c[3] for c in CUT_BY_TILE} == {"4x4", "2x4", "2x2"}
+
+
+def test_lora_gradients_by_quadrants(L):
+    """The GPU cases but the first run so; not a single tile, nor where quadrants were the slower ones at any density."""
+    assert [L.grads_by_quads(Tt, d, F) for Tt, d, F, *_ in GRADS] == [0] + [1] * (len(GRADS) - 1)
+    for Tt, d in ((2, 5120), (8, 1024), (32, 768), (64, 2048), (16, 5120), (32, 3200)):
+        assert L.grads_by_quads(Tt, d, 4 * d), (Tt, d)
+    for Tt, d in ((1, 768), (1, 5120), (24, 5120), (48, 3200), (65, 768)):
+        assert not L.grads_by_quads(Tt, d, 4 * d), (Tt, d)
