@@ -368,6 +368,18 @@ def kernel_model(lx, ffn_jobs, attn):
     }
 
 
+def one_launch_backward(lx, model, launched, unit):
+    """Small attention backward calls run both sides in one launch, which is recorded as the key side's:
+    its model then covers both, with Q, K, V and dO read once.  launched: kernel id -> launches recorded."""
+    if launched[lx.LX_K_ATTN_BWD_DQ] > 0:
+        return model
+    _, fl, by = model[lx.LX_K_ATTN_BWD_DQ]
+    n, fl_k, by_k = model[lx.LX_K_ATTN_BWD_DKV]
+    out = {k: v for k, v in model.items() if k != lx.LX_K_ATTN_BWD_DQ}
+    out[lx.LX_K_ATTN_BWD_DKV] = (n, fl + fl_k, by + by_k - 4 * unit)
+    return out
+
+
 def cpu_baseline(f, a, ffn_tiles=3, attn_heads=24):
     """The oracle as it stands, single thread, on a bounded sample of the same
     workload: the first `ffn_tiles` token tiles (forward + input gradient) and
@@ -519,7 +531,7 @@ def run(workload: str, steps: int, warmup: int, with_cpu: bool, cache: str = "wa
 
     # per-kernel breakdown (untimed pre-pass, 3 steps per kernel)
     model = kernel_model(lx, ffn_jobs, attn)
-    per_kernel = {}
+    per_kernel, launched = {}, {}
     for kid, (launches, _, _) in model.items():
         lx.lx_profile_begin(kid, 3 * launches)
         for _ in range(3):
@@ -527,6 +539,8 @@ def run(workload: str, steps: int, warmup: int, with_cpu: bool, cache: str = "wa
         torch.cuda.synchronize()
         ms, n = lx.lx_profile_end()
         per_kernel[kid] = (ms / 3.0, ms / max(n, 1))      # ms per step, ms per launch
+        launched[kid] = n
+    model = one_launch_backward(lx, model, launched, attn.unit_bytes())
     dom = max((k for k in per_kernel if k not in (lx.LX_K_COMPACT, lx.LX_K_COMBINE, lx.LX_K_LORA)),
               key=lambda k: per_kernel[k][0])
 
@@ -644,7 +658,7 @@ def run(workload: str, steps: int, warmup: int, with_cpu: bool, cache: str = "wa
         "attn": {"ms_per_step_kernels": att_ms, "active_tflops": att_fl / (att_ms * 1e-3) / 1e12,
                  "mfma_util": att_fl / (att_ms * 1e-3) / PEAK_MFMA_BF16},
         "kernels_us_per_launch": {lx.KERNEL_NAMES[k]: round(v[1] * 1e3, 2)
-                                  for k, v in per_kernel.items()},
+                                  for k, v in per_kernel.items() if k in model},
         "roofline": roof,
     }
     if peaks:

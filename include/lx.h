@@ -97,7 +97,7 @@ typedef enum {
   LX_K_FFN_DH = 3,       /* dZ_ij = (dY_i W_down_j) (.) [H_ij > 0] */
   LX_K_FFN_DX = 4,       /* dX_i = sum_j dZ_ij W_up_j */
   LX_K_ATTN_FWD = 5,     /* fused SDD + softmax + DSD */
-  LX_K_ATTN_BWD_DQ = 6,  /* Delta and dQ, query side */
+  LX_K_ATTN_BWD_DQ = 6,  /* Delta and dQ, query side (small calls: no launch of its own) */
   LX_K_ATTN_BWD_DKV = 7, /* dK and dV, key side (small calls: both sides in one launch) */
   LX_K_TRANSPOSE = 8,    /* weight repack */
   LX_K_PREDICT = 9,      /* MLP predictor: scores + threshold + OR over the tokens */
@@ -424,7 +424,8 @@ lx_status lx_sparse_attn_bwd_dx_noalloc(lx_dtype dt, int32_t B, int32_t Hh, int3
  * launch of `kernel` is bracketed by a pair of HIP events recorded on the
  * launch stream (at most max_launches launches; later ones are not timed).
  * lx_profile_end waits for those events, returns the summed kernel time in
- * milliseconds and the number of timed launches through HOST pointers, and
+ * milliseconds and the number of timed launches through HOST pointers (0 where no
+ * call launched that kernel, as LX_K_ATTN_BWD_DQ in small calls), and
  * switches the bracketing off.  begin creates events (it allocates; call it
  * outside timed regions); not thread-safe.
  */
