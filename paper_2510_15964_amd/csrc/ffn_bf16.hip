@@ -841,66 +841,53 @@ size_t ffn_dsd_split_bytes(int Tt, int d, int nnz_cap) {
 
 template <int DT, bool LORA>
 static void launch_sdd(SddArgs a, hipStream_t st) {
-  a.halves = sdd_halves(a.Tt, a.gt, a.nnz_cap);
-  const SddPlan p = plan_sdd(a.Tt, a.gt, a.K, a.nnz_cap, a.blocks, g_ffn_tiles_per_wg);
-  if (p.grid == 0) return;
-  if (const int items = (long long)a.nnz_cap * a.gt < 1 << 20 ? a.nnz_cap * a.gt : 1 << 20; quarters_pay(items, a.K, g_ffn_tiles_per_wg)) {
-    const dim3 grid(4 * sdd_grid(kTileInfo[kT11], a.Tt, a.gt, a.nnz_cap));
-    if (items <= kQuarterTilesAlone)
-      hipLaunchKernelGGL((ffn_sdd_quarter<DT, LORA, 8>), grid, dim3(Quarter::kTileThreads), 0, st, a);
-    else
-      hipLaunchKernelGGL((ffn_sdd_quarter<DT, LORA, 4>), grid, dim3(Quarter::kTileThreads), 0, st, a);
-    return;
-  }
-  if (p.allowed) {
-    a.own = p.id;
-    a.grid = p.grid;
-    a.allowed = p.allowed;
-    a.mix = sdd_may_mix(p, a.Tt, a.gt, a.K, a.nnz_cap, g_ffn_tiles_per_wg);
-    if (a.mix) a.grid = max(p.grid, sdd_mix_grid(a.Tt, a.nnz_cap));
-    if (kTileInfo[p.id].resident == 1)
-      hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 1>), dim3(a.grid), dim3(512), 0, st, a);
-    else
-      hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 2>), dim3(p.grid), dim3(256), 0, st, a);
-    return;
-  }
-#define LX_CALL(TL) hipLaunchKernelGGL((ffn_sdd<TL, DT, LORA>), dim3(p.grid), dim3(TL::kTileThreads), 0, st, a)
-  if (sdd_lean(p.id, a.Tt, a.gt, a.nnz_cap)) {
+  const SddRoute r = sdd_route(a.Tt, a.gt, a.K, a.nnz_cap, a.blocks, g_ffn_tiles_per_wg);
+  const dim3 grid(r.grid);
+  a.halves = r.halves;
+  a.own = r.plan.id;
+  a.grid = r.grid;
+  a.allowed = r.plan.allowed;
+  a.mix = r.mix;
+#define LX_CALL(TL) hipLaunchKernelGGL((ffn_sdd<TL, DT, LORA>), grid, dim3(TL::kTileThreads), 0, st, a)
+  if (r.by == kByQuarters && r.items <= kQuarterTilesAlone)
+    hipLaunchKernelGGL((ffn_sdd_quarter<DT, LORA, 8>), grid, dim3(Quarter::kTileThreads), 0, st, a);
+  else if (r.by == kByQuarters)
+    hipLaunchKernelGGL((ffn_sdd_quarter<DT, LORA, 4>), grid, dim3(Quarter::kTileThreads), 0, st, a);
+  else if (r.by == kBySet && kTileInfo[r.plan.id].resident == 1)
+    hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 1>), grid, dim3(512), 0, st, a);
+  else if (r.by == kBySet)
+    hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 2>), grid, dim3(256), 0, st, a);
+  else if (r.by == kByLean)
     LX_CALL(Tile14Lean);
-    return;
-  }
-  LX_TILES(p.id, LX_CALL)
+  else if (r.by == kByTile)
+    LX_TILES(r.plan.id, LX_CALL)
 #undef LX_CALL
 }
 template <int DT, bool LORA>
 static void launch_dsd(DsdArgs a, size_t part_bytes, hipStream_t st) {
-  if (const int items = a.Tt < 4096 ? a.Tt * (a.ncols / 64) : 1 << 20; quarters_pay(items, a.ldw, g_ffn_tiles_per_wg)) {
-    a.GM = a.Tt;
-    a.GN = a.ncols / 64;
-    const dim3 grid(32 * ceil_div(a.GM * a.GN, 8));
-    if (items <= kQuarterTilesAlone)
+  const DsdRoute r = dsd_route(a.Tt, a.gt, a.ncols, a.ldw, a.nnz_cap, LORA || !a.part ? 0 : part_bytes, g_ffn_tiles_per_wg);
+  const DsdPlan& p = r.plan;
+  const dim3 grid(r.grid);
+  a.GM = r.GM;
+  a.GN = r.GN;
+  a.order = r.order;
+  if (r.by == kByQuarters) {
+    if (r.items <= kQuarterTilesAlone)
       hipLaunchKernelGGL((ffn_dsd_quarter<DT, LORA, 8>), grid, dim3(Quarter::kTileThreads), 0, st, a);
     else
       hipLaunchKernelGGL((ffn_dsd_quarter<DT, LORA, 4>), grid, dim3(Quarter::kTileThreads), 0, st, a);
     return;
   }
-  const DsdPlan p = choose_dsd(a.Tt, a.gt, a.ncols, a.nnz_cap, LORA || !a.part ? 0 : part_bytes, g_ffn_tiles_per_wg);
-  if (dsd_may_mix(p, a.Tt, a.gt, a.ncols, a.nnz_cap, g_ffn_tiles_per_wg)) {
-    hipLaunchKernelGGL((ffn_dsd_mix<DT, LORA>), dim3(sdd_mix_grid(a.Tt, a.ncols / 64)), dim3(512), 0, st, a);
+  if (r.by == kByMix) {
+    hipLaunchKernelGGL((ffn_dsd_mix<DT, LORA>), grid, dim3(512), 0, st, a);
     return;
   }
-  const TileInfo& t = kTileInfo[p.id];
-  a.band = t.tm == 4 ? 4 : 8;
+  a.band = kTileInfo[p.id].tm == 4 ? 4 : 8;
   a.full = p.full;
   a.rest = p.rest;
   a.pieces = p.pieces;
-  a.GM = a.Tt / t.tm;
-  a.GN = ceil_div(a.ncols, 64 * t.tn);
-  const bool lean = dsd_lean(p.id, a.Tt, a.gt, a.GM, a.GN, a.nnz_cap, a.ldw);
-  a.order = dsd_order(a.GM, a.GN, t.tn, lean, a.ldw * a.ncols * 2);
-  const dim3 grid(a.gt == a.Tt ? 8 * ceil_div(p.full, 8) + 8 * ceil_div((long long)p.rest * p.pieces, 8) : 8 * ceil_div(a.GM * a.GN, 8));
 #define LX_CALL(TL) hipLaunchKernelGGL((ffn_dsd<TL, DT, LORA>), grid, dim3(TL::kTileThreads), 0, st, a)
-  if (lean)
+  if (r.by == kByLean)
     LX_CALL(Tile14Lean);
   else
     LX_TILES(p.id, LX_CALL)

@@ -394,6 +394,63 @@ inline bool dsd_lean(int id, int Tt, int gt, int GM, int GN, int nnz_cap, long l
   return 4.f * mean <= (float)GM || (256 * 2 * ldw <= 4 << 20 && GM * GN % (2 * kCUs) != 0);
 }
 
+// ---- which kernel a launch runs by -----------------------------------------------------------
+// kBySet: a kernel that holds several tiles and takes the one that suits the list (SddSet, with `mix` its SddMix), kByMix: 4 x 4
+// tiles and narrower ones for a rest, kByLean: the 1 x 4 tile of one stage, kByTile: the plan's own tile.
+enum Route { kNothing, kByQuarters, kBySet, kByMix, kByLean, kByTile };
+struct SddRoute {
+  Route by;
+  SddPlan plan;
+  bool mix, halves;
+  int grid, items;         // workgroups; 64 x 64 tiles of the capacity (quarters)
+};
+inline SddRoute sdd_route(int Tt, int gt, int d, int nnz_cap, int blocks, int want) {
+  SddRoute r = {kNothing, plan_sdd(Tt, gt, d, nnz_cap, blocks, want), false, sdd_halves(Tt, gt, nnz_cap), 0, 0};
+  r.grid = r.plan.grid;
+  if (r.grid == 0) return r;
+  r.items = (long long)nnz_cap * gt < 1 << 20 ? nnz_cap * gt : 1 << 20;
+  if (quarters_pay(r.items, d, want)) {
+    r.by = kByQuarters;
+    r.grid = 4 * sdd_grid(kTileInfo[kT11], Tt, gt, nnz_cap);
+  } else if (r.plan.allowed) {
+    r.by = kBySet;
+    r.mix = sdd_may_mix(r.plan, Tt, gt, d, nnz_cap, want);
+    if (const int mixed = r.mix ? sdd_mix_grid(Tt, nnz_cap) : 0; mixed > r.grid) r.grid = mixed;
+  } else {
+    r.by = sdd_lean(r.plan.id, Tt, gt, nnz_cap) ? kByLean : kByTile;
+  }
+  return r;
+}
+struct DsdRoute {
+  Route by;
+  DsdPlan plan;
+  int grid, items;
+  int GM, GN;              // token groups and column chunks of the tile
+  DsdOrder order;          // lists per group of token tiles
+};
+// part_bytes: room for partial sums.
+inline DsdRoute dsd_route(int Tt, int gt, int d, long long ldw, int nnz_cap, size_t part_bytes, int want) {
+  DsdRoute r = {kByQuarters, {}, 0, Tt < 4096 ? Tt * (d / 64) : 1 << 20, Tt, d / 64, kUnranked};
+  if (quarters_pay(r.items, ldw, want)) {
+    r.grid = 32 * ceil_div(r.items, 8);
+    return r;
+  }
+  r.plan = choose_dsd(Tt, gt, d, nnz_cap, part_bytes, want);
+  if (dsd_may_mix(r.plan, Tt, gt, d, nnz_cap, want)) {
+    r.by = kByMix;
+    r.grid = sdd_mix_grid(Tt, d / 64);
+    return r;
+  }
+  const TileInfo& t = kTileInfo[r.plan.id];
+  r.GM = Tt / t.tm;
+  r.GN = ceil_div(d, 64 * t.tn);
+  const bool lean = dsd_lean(r.plan.id, Tt, gt, r.GM, r.GN, nnz_cap, ldw);
+  r.by = lean ? kByLean : kByTile;
+  r.order = dsd_order(r.GM, r.GN, t.tn, lean, ldw * d * 2);
+  r.grid = gt == Tt ? 8 * ceil_div(r.plan.full, 8) + 8 * ceil_div(r.plan.rest * r.plan.pieces, 8) : 8 * ceil_div(r.GM * r.GN, 8);
+  return r;
+}
+
 // Gradients of the LoRA matrices: whether a workgroup per quadrant of a product adds all its token tiles (lora_tn_quad), or
 // ranges of tiles are added apart, as parts in memory, and a second launch adds those.  By the shape only: the sums' order is
 // not to change with a list's capacity.  Quadrants read both operands twice, so there must not be much to add, and a

@@ -6,7 +6,7 @@ using namespace lx;
 extern "C" {
 
 int may_mix(int Tt, int d, int cap, int blocks, int want) {
-  return sdd_may_mix(plan_sdd(Tt, Tt, d, cap, blocks, want), Tt, Tt, d, cap, want);
+  return sdd_route(Tt, Tt, d, cap, blocks, want).mix;
 }
 int mix_grid(int Tt, int cap) { return sdd_mix_grid(Tt, cap); }
 // -2: a list of n entries does not run so, otherwise the tile of the rest (-1: none).
@@ -28,8 +28,7 @@ int mix_item(int Tt, int n, int w, int* out) {
 }
 // Second product: -2: by the plan's own tile, otherwise the tile of the rest.
 int down_tail(int Tt, int d, int cap, int want) {
-  if (!dsd_may_mix(choose_dsd(Tt, Tt, d, cap, ~(size_t)0, want), Tt, Tt, d, cap, want)) return -2;
-  return sdd_mix(Tt, d / 64).tail;
+  return dsd_route(Tt, Tt, d, 64ll * (cap + 3), cap, ~(size_t)0, want).by == kByMix ? sdd_mix(Tt, d / 64).tail : -2;
 }
 int keeps_own(int cap, int n) { return sdd_keeps_own(cap, n); }
 

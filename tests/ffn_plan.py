@@ -16,7 +16,25 @@ def load():
     L = C.CDLL(lib)
     L.sdd_us.restype = C.c_float
     L.dsd_tile.argtypes = [C.c_int] * 4 + [C.c_longlong, C.c_int, C.POINTER(C.c_int)]
+    L.dsd_by.argtypes = [C.c_int] * 5 + [C.c_longlong, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
     return L
+
+
+ROUTES = ("nothing", "quarters", "set", "mix", "lean", "tile")      # order of Route
+
+
+def sdd_by(L, Tt, gt, d, cap, blocks, want, n):
+    """(route, tile) of the first product of a list of n entries."""
+    t = C.c_int(0)
+    r = ROUTES[L.sdd_by(Tt, gt, d, cap, blocks, want, n, C.byref(t))]
+    return r, None if t.value < 0 else TILES[t.value]
+
+
+def dsd_by(L, Tt, gt, d, F, cap, part_bytes=0, want=0):
+    """(route, tile, pieces) of the second product."""
+    t, p = C.c_int(0), C.c_int(0)
+    r = ROUTES[L.dsd_by(Tt, gt, d, F, cap, part_bytes, want, C.byref(t), C.byref(p))]
+    return r, None if t.value < 0 else TILES[t.value], p.value
 
 
 def dsd(L, Tt, gt, d, cap, part_bytes=0, want=0):

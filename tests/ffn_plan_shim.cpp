@@ -31,6 +31,23 @@ int dsd_tile(int Tt, int gt, int d, int nnz_cap, long long part_bytes, int want,
   *pieces = p.pieces;
   return p.id;
 }
+// The kernel that the first product of a list with that capacity is launched by (Route), and the tile that it runs with for
+// a list of n entries (-1: quarters, or 4 x 4 tiles and narrower ones).
+int sdd_by(int Tt, int gt, int d, int nnz_cap, int blocks, int want, int n, int* tile) {
+  const SddRoute r = sdd_route(Tt, gt, d, nnz_cap, blocks, want);
+  const bool mixes = r.mix && sdd_keeps_own(nnz_cap, n) && sdd_mixes(sdd_mix(Tt, n));
+  *tile = r.by == kNothing || r.by == kByQuarters || mixes ? -1 : sdd_tile(Tt, gt, d, nnz_cap, blocks, want, n);
+  return r.by;
+}
+// Likewise the second; *pieces as in dsd_tile.
+int dsd_by(int Tt, int gt, int d, int F, int nnz_cap, long long part_bytes, int want, int* tile, int* pieces) {
+  const DsdRoute r = dsd_route(Tt, gt, d, F, nnz_cap, (size_t)part_bytes, want);
+  *tile = r.by == kByQuarters || r.by == kByMix ? -1 : r.plan.id;
+  *pieces = r.by == kByQuarters || r.by == kByMix ? 1 : r.plan.pieces;
+  return r.by;
+}
+// The predictor by quarters of its tiles (where d is no multiple of 128).
+int predict_quarters(int items, int d) { return quarters_pay(items, d, 0); }
 // 1: the gradients of the LoRA matrices by quadrants, 0: by parts.
 int grads_by_quads(int Tt, int d, int F) { return lora_grads_by_quads(Tt, d, F); }
 

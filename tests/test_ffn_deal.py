@@ -72,8 +72,8 @@ def test_deals_where_the_other_one_was_slower(L, Tt, d, share, lean, order):
 def test_first_products_of_thin_lists_take_whole_ones(L):
     """Lists of 6 - 10 entries in the mean, where halves were up to 1.13 times as slow; not the longer ones."""
     for Tt, mean in ((64, 6), (96, 7), (64, 10), (128, 10)):
-        assert not L.halves_of(Tt, 1, int(1.1 * mean * Tt) + 64), (Tt, mean)
+        assert not L.halves_of(Tt, 1, 2048, 128, int(1.1 * mean * Tt) + 64), (Tt, mean)
     for Tt, mean in ((64, 13), (96, 13), (128, 14), (64, 50)):
-        assert L.halves_of(Tt, 1, int(1.1 * mean * Tt) + 64), (Tt, mean)
-    assert {L.halves_of(c[1], c[2], c[5]) for c in CASES} == {0, 1}
-    assert not any(L.halves_of(c[1], c[2], c[5]) for c in THIN)
+        assert L.halves_of(Tt, 1, 2048, 128, int(1.1 * mean * Tt) + 64), (Tt, mean)
+    assert {L.halves_of(*c[1:6]) for c in CASES} == {0, 1}
+    assert not any(L.halves_of(*c[1:6]) for c in THIN)

@@ -50,7 +50,12 @@ def test_bits_of_the_mix(lx, dtype, Tt, d, Fb, cap, n, tail, lora):
     compare(lx, dtype, Tt, d, Fb, cap, n, lora)
 
 
-def compare(lx, dtype, Tt, d, Fb, cap, n, lora):
+@pytest.mark.parametrize("dtype,Tt,d,Fb,cap,n", [c[:6] for c in CASES[:2]] + [c[:3] + (c[3] + 3, c[3], c[3]) for c in DOWN[:3]])
+def test_bits_of_the_mix_with_a_bias(lx, dtype, Tt, d, Fb, cap, n):
+    compare(lx, dtype, Tt, d, Fb, cap, n, False, True)
+
+
+def compare(lx, dtype, Tt, d, Fb, cap, n, lora, bias=False):
     import torch
     T, F = 64 * Tt, 64 * Fb
     rng = np.random.default_rng(Tt + d)
@@ -67,6 +72,7 @@ def compare(lx, dtype, Tt, d, Fb, cap, n, lora):
     Wut, Wdt = lx.lx_ffn_pack_weights(Wu, Wd)
     mats = inputs.lora_matrices(d, F, 16, 3)
     A, B = (dev(mats[k], dtype) for k in ("A_pad", "B_pad"))
+    biases = dict(b_up=normal(F), b_down=normal(d)) if bias else {}
     lxt = {"bf16": lx.LX_BF16, "f16": lx.LX_F16}[dtype]
 
     def run(tiles):
@@ -85,7 +91,7 @@ def compare(lx, dtype, Tt, d, Fb, cap, n, lora):
             else:
                 wb = torch.empty(lx.lx_sparse_ffn_bwd_workspace_bytes(lxt, T, d, F, 64, 64, cap * Tt, 1), dtype=torch.uint8,
                                  device="cuda")
-                lx.lx_sparse_ffn_fwd(X, Wu, Wd, bl, 64, 64, Y, H)
+                lx.lx_sparse_ffn_fwd(X, Wu, Wd, bl, 64, 64, Y, H, **biases)
                 lx.lx_sparse_ffn_bwd_dx(dY, H, Wu, Wd, bl, 64, 64, dX, wb, W_up_t=Wut, W_down_t=Wdt)
                 more = []
             torch.cuda.synchronize()

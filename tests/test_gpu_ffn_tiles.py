@@ -81,9 +81,13 @@ def test_tile_edges(lx, oracle, dtype, Tt, d, Fb, nnz, bias):
             assert rel_err_max(g, r) <= TOL[dtype] and rel_err_fro(g, r) <= FRO[dtype]
 
 
-@pytest.mark.parametrize("Tt,d,nnz", [(65, 1024, 33), (65, 4352, 33)])
+CUT = [(65, 1024, 33), (65, 4352, 33)]
+
+
+@pytest.mark.parametrize("Tt,d,nnz", CUT)
 def test_cut_lists(lx, Tt, d, nnz):
-    """With room for partial sums the lists of the last round may be cut: equal to the uncut call to rounding."""
+    """With room for partial sums the lists of the last round may be cut (with four tiles per workgroup, or two and four, here):
+    equal to the uncut call to rounding."""
     import torch
     T, F = Tt * 64, 64 * 64
     g = torch.Generator(device="cuda").manual_seed(nnz)
@@ -139,6 +143,7 @@ CAPACITIES = [
     ("f16", 72, 64, 48, 33, 3, "4x4", "4x4"),
     ("bf16", 72, 64, 24, 17, 24, "1x4", "1x4"),
     ("bf16", 66, 1024, 12, 11, 66, "1x4 deep", "1x4 deep"),
+    ("bf16", 26, 1024, 8, 5, 1, "1x1", "1x1"),
 ]
 
 
@@ -177,7 +182,7 @@ def test_capacity_does_not_change_results(lx, dtype, Tt, d, Fb, nnz, rows, by_ca
 
 
 # token tiles, d, listed blocks; the second product's tile and the pieces its last lists are cut into
-CUT_BY_TILE = [(65, 256, 129, "2x2", 3), (130, 192, 129, "2x4", 3), (130, 2048, 33, "4x4", 4)]
+CUT_BY_TILE = [(65, 256, 129, "2x2", 3), (130, 192, 129, "2x4", 3), (16, 4352, 128, "4x4", 3)]
 
 
 @pytest.mark.parametrize("Tt,d,nnz,tile,pieces", CUT_BY_TILE)

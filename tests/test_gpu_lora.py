@@ -284,19 +284,21 @@ def test_lora_token_tile_counts(lx, oracle, Tt, d, F, rows, dtype):
 # test_ffn_plan.py)
 LORA_TILES = [
     (129, 64, 6, 1, "1x2", "1x1 many"),
-    (51, 64, 40, 1, "1x4", "1x1"),
-    (103, 64, 9, 1, "2x2", "1x1 many"),
+    (51, 64, 40, 1, "1x4", "quarters"),
+    (103, 64, 9, 1, "2x2", "quarters"),
     (57, 768, 9, 1, "2x2 deep", "1x1 many"),
     (103, 512, 9, 1, "2x4", "2x2 deep"),
-    (115, 64, 17, 1, "4x4", "1x1"),
+    (115, 64, 17, 1, "4x4", "quarters"),
     (42, 1024, 17, 2, "1x4 deep", "1x1 many"),
-    (103, 576, 1, 1, "1x1 many", "2x2"),
-    (85, 1536, 1, 1, "1x1", "1x4"),
+    (103, 576, 1, 1, "quarters", "2x2"),
+    (85, 1536, 1, 1, "quarters", "1x4"),
     (103, 576, 8, 1, "2x2 deep", "2x4"),
     (129, 1024, 1, 1, "1x1", "4x4"),
     (98, 512, 12, 2, "1x1 many", "1x4 deep"),
-    (97, 512, 1, 1, "1x1 many", "1x2"),
-    (6, 192, 3, 6, "1x1 many", "1x1 many"),
+    (97, 512, 1, 1, "quarters", "1x2"),
+    (6, 192, 3, 6, "quarters", "quarters"),
+    (21, 512, 17, 1, "1x2", "1x1"),
+    (24, 640, 9, 3, "1x1", "1x1"),
 ]
 
 

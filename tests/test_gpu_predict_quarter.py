@@ -13,21 +13,29 @@ def lx():
     return lx
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("Tt,d,nblk", [
+# token tiles, d, blocks
+CASES = [
     (1, 64, 64),          # one step
     (1, 192, 128),        # a pair and a half
     (3, 1088, 320),       # 15 tiles: the ring of eight pairs and one step more
     (64, 448, 64),        # the most of the long ring
     (13, 576, 320),       # 65: the first of the short one
     (128, 320, 64),       # the most
-])
+]
+
+
+def tiles_beyond(Tt, nblk):
+    """Token tiles of a call that does not run by quarters."""
+    return max(Tt, -(-129 * 64 // nblk))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("Tt,d,nblk", CASES)
 def test_mask_bytes_of_the_quarters(lx, Tt, d, nblk, dtype):
     import torch
     tdt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
     g = torch.Generator(device="cuda").manual_seed(d)
-    more = -(-129 * 64 // nblk)                      # tiles of a call beyond the line
-    X = torch.randn(64 * max(Tt, more), d, device="cuda", generator=g).to(tdt)
+    X = torch.randn(64 * tiles_beyond(Tt, nblk), d, device="cuda", generator=g).to(tdt)
     W = torch.randn(nblk, d, device="cuda", generator=g).to(tdt)
     thr = 2.5 * d ** 0.5                             # a third of the blocks of a tile
     few = torch.full((Tt, nblk), 7, dtype=torch.uint8, device="cuda")
