@@ -1148,8 +1148,9 @@ static hipError_t launch_fwd(const AttnArgs& a, int B, hipStream_t st) {
 constexpr int kBothOcc(int D) { return D == 64 ? 3 : 1; }
 static bool bwd_in_one(const AttnArgs& a, int D, int B) {
   const int nblk = a.S / 64;
-  if (!bwd_one_launch_pays(D, (long long)B * a.Hh * nblk, nblk)) return false;
   const long long rows = (long long)a.mask_batch * a.Hh * nblk, stats = (long long)B * a.Hh * a.S * 4;
+  const double mean = (double)(a.nnz_cap > a.cnnz_cap ? a.nnz_cap : a.cnnz_cap) / rows;
+  if (!bwd_one_launch_pays(D, (long long)B * a.Hh * nblk, nblk, a.causal != 0, mean)) return false;
   return bwd_sides_apart({{{B, a.Hh, a.S}, {2 * a.sb, 2 * a.sh, 2 * a.ss}, 2 * D},
                           {a.Q, a.K, a.V, a.O, a.dO},
                           {a.dQ, a.dK, a.dV},

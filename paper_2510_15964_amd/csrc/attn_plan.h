@@ -85,14 +85,20 @@ inline bool bwd_sides_apart(const BwdBuffers& b) {
 // Whether one launch pays.  The key side then makes Delta itself, for every block that it streams, from O tiles of which the
 // other two launches need none; and a CU has room for three workgroups (head size 64) or one (128: three tiles a stage
 // are 96 KB).  What it saves is the chain of loads that starts a launch, and a launch that lasts as long as its longest
-// row; so it pays while the rows of both sides are resident at about the same time, two each: up to 768 rows of all
-// heads and batch entries (1.3 - 1.6 times faster: 12 heads of 320 tokens 18 -> 12 us, 3 x 32 of 512 21 -> 14, 10 of 3136
-// 121 -> 75), with short rows up to 1728 (1.02 - 1.2; 16 heads of 4096, all blocks 0.97, 24 of 4096 0.88); head size 128
-// up to 256 (1.2 - 1.6; 384 rows 1.07, 512 0.96).  Not at the token strides of the kernels with 64-bit addresses (kWideStride),
-// where every row lies in pages of its own and reading O again costs more than a launch: head size 64, 2^26 elements, 128
-// heads of 512 tokens 114 us in one, 102 in two; 256 of 256 76 and 72; 32 of 1024 96 and 86 (2^25: 62 and 59, 42 and 43, 55 and 53).
-inline bool bwd_one_launch_pays(int D, long long rows, int nblk) {
-  return D == 128 ? rows <= 256 : rows <= 768 || (rows <= 1728 && rows * nblk <= 20000);
+// row.  While the rows of both sides are resident at once, it takes 0.56 - 0.85 of the time, whatever the lists: up to 384 rows
+// of all heads and batch entries at head size 64, 128 at 128.  Up to twice that it pays where rows are of different
+// lengths, as under a causal mask (one launch / two, us: 12 heads of 4096 tokens, all blocks 131 / 161, 10 % 25 / 37; D = 128, 4 of 4096
+// 138 / 176), or lists short.  Without causality long lists take longer: head size 64, 768 rows, 10 / 30 / 60 / 100 % of 64 blocks 35 /
+// 84 / 156 / 250 and 44 / 92 / 149 / 216, of 32 blocks 21 / 46 / 81 / 128 and 30 / 55 / 81 / 113, which is more won than lost while only the
+// lists' capacity is known; 128, 256 rows of 64 38 / 89 / 163 / 260 and 46 / 89 / 136 / 176, of 16 18 / 30 / 49 / 72 and 24 / 37 / 50 / 54,
+// so there the capacity has to say that they are short (`mean`: blocks per row).  With short rows up to 1728 (16 heads of 4096, all blocks 0.97, 24 of
+// 4096 0.88 of the speed; causal, 1152 rows of 16 blocks, all of them 70 and 65 us, 10 % 18 and 23).
+// Not at the token strides of the kernels with 64-bit addresses (kWideStride), where every row lies in pages of its own and
+// reading O again costs more than a launch: head size 64, 2^26 elements, 128 heads of 512 tokens 114 us in one, 102 in two; 256
+// of 256 76 and 72; 32 of 1024 96 and 86 (2^25: 62 and 59, 42 and 43, 55 and 53).
+inline bool bwd_one_launch_pays(int D, long long rows, int nblk, bool causal, double mean) {
+  if (D == 128) return rows <= 128 || (rows <= 256 && (causal || mean <= 2 || (mean <= 6 && 2 * mean <= nblk)));
+  return rows <= 768 || (rows <= 1728 && rows * nblk <= 20000);
 }
 
 }  // namespace lx

@@ -12,7 +12,7 @@ def load():
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-shared", "-fPIC", os.path.join(HERE, "attn_plan_shim.cpp"), "-o", lib],
                    check=True)
     L = C.CDLL(lib)
-    L.pays.argtypes = [C.c_int, C.c_longlong, C.c_int]
+    L.pays.argtypes = [C.c_int, C.c_longlong, C.c_int, C.c_int, C.c_double]
     return L
 
 

@@ -8,7 +8,7 @@ extern "C" {
 int meet(const long long* n, const long long* stride, long long row, long long delta) {
   return tensors_meet({{n[0], n[1], n[2]}, {stride[0], stride[1], stride[2]}, row}, delta);
 }
-int pays(int D, long long rows, int nblk) { return bwd_one_launch_pays(D, rows, nblk); }
+int pays(int D, long long rows, int nblk, int causal, double mean) { return bwd_one_launch_pays(D, rows, nblk, causal, mean); }
 // at: byte addresses of Q, K, V, O, dO; dQ, dK, dV; LSE, row_ptr, col_idx, Delta, the rescaled LSE
 int sides_apart(const long long* n, const long long* stride, long long row, const long long* at, long long stats, long long ptrs,
                 long long entries) {

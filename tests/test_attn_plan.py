@@ -78,7 +78,17 @@ def test_neighbours_are_not_overlaps(L):
 
 def test_the_cases_run_as_they_claim(L):
     """test_gpu_attn_one_launch.py compares one launch with two: all its calls are small enough for one."""
-    for _, B, Hh, S, D, *_ in CASES:
-        assert L.pays(D, B * Hh * (S // 64), S // 64), (B, Hh, S, D)
-    assert L.pays(64, 768, 64) and not L.pays(64, 769, 64) and L.pays(64, 1728, 11) and not L.pays(64, 1729, 1)
-    assert L.pays(128, 256, 64) and not L.pays(128, 257, 1)
+    for _, B, Hh, S, D, _, causal, *_ in CASES:
+        nb = S // 64
+        assert L.pays(D, B * Hh * nb, nb, causal, nb), (B, Hh, S, D)
+    assert L.pays(64, 768, 64, 1, 64) and not L.pays(64, 769, 64, 1, 64) and L.pays(64, 1728, 11, 1, 11) and not L.pays(64, 1729, 1, 1, 1)
+    assert L.pays(128, 256, 64, 1, 64) and not L.pays(128, 257, 1, 1, 1)
+
+
+@pytest.mark.parametrize("D,rows,nblk,mean,one", [
+    (64, 768, 64, 64, True), (64, 1728, 4, 4, True), (128, 128, 64, 64, True), (128, 192, 4, 4, False), (128, 256, 64, 64, False),
+    (128, 256, 64, 6, True), (128, 256, 16, 16, False), (128, 256, 2, 2, True),
+])
+def test_without_causality_long_lists_run_in_two(L, D, rows, nblk, mean, one):
+    """Head size 128, where one launch took up to 1.5 times as long as two."""
+    assert bool(L.pays(D, rows, nblk, 0, mean)) == one
