@@ -690,7 +690,7 @@ struct QuarterSddSrc {
 };
 
 template <int DT, bool LORA, int NST>
-__global__ __launch_bounds__(Quarter::kTileThreads, 2) void ffn_sdd_quarter(SddArgs a) {
+__global__ __launch_bounds__(Quarter::kTileThreads, NST == 8 ? 1 : 2) void ffn_sdd_quarter(SddArgs a) {
   __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * 2 * Quarter::kElems];
   const QuarterOf q;
   int m, e, rs;
@@ -763,7 +763,7 @@ struct QuarterDsdSrc {
 };
 
 template <int DT, bool LORA, int NST>
-__global__ __launch_bounds__(Quarter::kTileThreads, 2) void ffn_dsd_quarter(DsdArgs a) {
+__global__ __launch_bounds__(Quarter::kTileThreads, NST == 8 ? 1 : 2) void ffn_dsd_quarter(DsdArgs a) {
   __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * 2 * Quarter::kElems];
   const QuarterOf q;
   int chunk, i;

@@ -177,7 +177,7 @@ struct PredictSrc {
   __device__ __forceinline__ void issue(int s, uint32_t lds) const { t.issue(rows + (long long)s * kBK, lds + at); }
 };
 template <int DT, int NST>
-__global__ __launch_bounds__(Quarter::kTileThreads, 2) void predict_quarter_bf16(
+__global__ __launch_bounds__(Quarter::kTileThreads, NST == 8 ? 1 : 2) void predict_quarter_bf16(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wa_t, int tiles, int K, int nblk,
     int tiles_per_group, float thr, uint8_t* __restrict__ mask) {
   __shared__ __attribute__((aligned(1024))) uint16_t ring[NST * 2 * Quarter::kElems];
