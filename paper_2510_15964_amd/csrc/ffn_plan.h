@@ -23,8 +23,8 @@ enum TileId { kT44, kT24, kT22, kT22Deep, kT14, kT14Deep, kT12, kT11, kT11Many, 
 // ring, epilogue) and step[q - 1] per step with q workgroups on a CU.  Fitted to measured launches (64 - 8192 tokens,
 // d 576 - 5120, 6 - 320 listed blocks, lists shared and per tile).  Checked at 26 shapes, every tile of both products
 // (profiles/ffn_tile_sweep.txt): model to measured 0.99 in the geometric mean, rms 17 %, and the tile that is taken is
-// 1 % slower than the fastest one on average, 10 % at worst (4096 tokens, d = 2048, a list row per four tiles: 33 us by
-// 2 x 4 tiles, 30 by 2 x 2).
+// 2 % slower than the fastest one on average, 15 % at worst (second product, 4096 tokens, d = 2048, one list of 14
+// blocks: 25 us by 2 x 4 tiles, 22 by 2 x 2).
 struct TileInfo {
   int tm, tn, resident;
   float round, step[3];
