@@ -256,18 +256,6 @@ struct SlotOffset {
 // ---------------------------------------------------------------------------
 // products of a wavefront: its 16 own rows against the 64 rows of a streamed tile
 // ---------------------------------------------------------------------------
-// 16x16x32 MFMA on 16-bit operands.  Operand a: lane l holds row l%16, k = 8*(l/16)..+7; operand
-// b: column l%16, same k.  Accumulator register v of lane l is C[4*(l/16) + v][l%16].
-template <int DT>
-__device__ __forceinline__ f32x4 mfma16(uint4 a, uint4 b, f32x4 c) {
-  if constexpr (DT == kF16)
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
-                                                  __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
 // Per-lane offsets of the two access patterns into a streamed [64 x D] tile, for every XOR of the slot
 // bits that the patterns' rows and columns make.
 template <int D>

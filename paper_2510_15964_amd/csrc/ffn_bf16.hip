@@ -1,6 +1,6 @@
 // 16-bit sparse FFN kernels for gfx950 (Sec. VI-B: neuron-centric tiled matrix
 // products that take the list of active neuron blocks and load / compute only
-// those).  fp32 accumulation on the 32x32x16 MFMA for 16-bit operands.  The kernels are
+// those).  fp32 accumulation on the 16x16x32 MFMA for 16-bit operands.  The kernels are
 // templates over the element type DT (bfloat16 or IEEE half, same layouts and data movement).
 //
 // Both products of a pass are "NT" contractions whose operands are read along
@@ -22,17 +22,17 @@
 
 namespace lx {
 
-// The tiles of ffn_plan.h.  TM TN WM WN NST KS
-using Tile44 = Tile<4, 4, 2, 4, 2, 2>;
+// The tiles of ffn_plan.h.  TM TN WM WN NST PH
+using Tile44 = Tile<4, 4, 4, 2, 2, 2>;
 using Tile24 = Tile<2, 4, 2, 4, 3, 2>;
 using Tile22 = Tile<2, 2, 2, 2, 2, 2>;
-using Tile22Deep = Tile<2, 2, 2, 4, 4, 4>;
+using Tile22Deep = Tile<2, 2, 2, 4, 4, 1>;
 using Tile14 = Tile<1, 4, 1, 4, 2, 2>;
-using Tile14Lean = Tile<1, 4, 1, 4, 1, 1, 4>;      // four workgroups on a CU: see sdd_lean, dsd_lean
+using Tile14Lean = Tile<1, 4, 1, 4, 1, 4, 4, 32>;  // four workgroups on a CU: see sdd_lean, dsd_lean
 using Tile14Deep = Tile<1, 4, 2, 4, 4, 2>;
 using Tile12 = Tile<1, 2, 1, 4, 3, 2>;
-using Tile11 = Tile<1, 1, 2, 2, 4, 4>;
-using Tile11Many = Tile<1, 1, 2, 2, 3, 4, 3>;
+using Tile11 = Tile<1, 1, 2, 2, 4, 1, 2, 32>;
+using Tile11Many = Tile<1, 1, 2, 2, 3, 1, 3>;
 template <class Tl>
 constexpr int kRingElems = Tl::NST * Tl::kElems;
 
@@ -136,13 +136,13 @@ __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int r
 }
 
 template <class Tl>
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[Tl::NI][Tl::TI]) {
+__device__ __forceinline__ void zero_acc(typename Tl::Acc (&acc)[Tl::NI][Tl::TI]) {
 #pragma unroll
   for (int x = 0; x < Tl::NI; ++x)
 #pragma unroll
     for (int y = 0; y < Tl::TI; ++y)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
+      for (int v = 0; v < Tl::MF * Tl::MF / kWave; ++v) acc[x][y][v] = 0.f;
 }
 
 // Epilogue.  The accumulators hold four consecutive columns of a lane's token; stored as they are, the 8-byte
@@ -153,28 +153,35 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[Tl::NI][Tl::TI]) {
 __device__ __forceinline__ uint32_t out_slot(int block, int row, int slot) {
   return (uint32_t)(block * 8192 + row * 128 + ((slot ^ (row & 7)) << 4));
 }
-// One 32 x 32 accumulator (token rows th, columns nh .. of the block) -> LDS, rounded; bias: the 32 columns' (or
-// null), then ReLU.
+// Four consecutive columns of a token row -> LDS at `at`, rounded; bias: theirs (or null), then ReLU.
+template <int DT>
+__device__ __forceinline__ void cols_to_lds(f32x4 v, uint32_t at, const uint16_t* __restrict__ bias, bool relu) {
+  if (bias) {
+    const uint2 bb = *reinterpret_cast<const uint2*>(bias);
+    v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
+    v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
+  }
+  if (relu) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+  }
+  lds_write8(at, make_uint2(pack2<DT>(v[0], v[1]), pack2<DT>(v[2], v[3])));
+}
+// One accumulator (token rows th .., columns nh .. of the block) -> LDS; bias: its columns' (or null).
 template <int DT>
 __device__ __forceinline__ void acc_to_lds(const f32x16& acc, uint32_t lds, int block, int th, int nh,
                                            const uint16_t* __restrict__ bias, bool relu) {
   const int lane = threadIdx.x % kWave, tl = th + lane % 32, h2 = lane / 32;
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    float v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = acc[4 * g + e];
-    if (bias) {
-      const uint2 bb = *reinterpret_cast<const uint2*>(bias + 8 * g + 4 * h2);
-      v[0] += to_f32<DT>(bb.x & 0xFFFFu); v[1] += to_f32<DT>(bb.x >> 16);
-      v[2] += to_f32<DT>(bb.y & 0xFFFFu); v[3] += to_f32<DT>(bb.y >> 16);
-    }
-    if (relu) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-    }
-    lds_write8(lds + out_slot(block, tl, nh / 8 + g) + 8 * h2, make_uint2(pack2<DT>(v[0], v[1]), pack2<DT>(v[2], v[3])));
-  }
+  for (int g = 0; g < 4; ++g)
+    cols_to_lds<DT>(f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]},
+                    lds + out_slot(block, tl, nh / 8 + g) + 8 * h2, bias ? bias + 8 * g + 4 * h2 : nullptr, relu);
+}
+template <int DT>
+__device__ __forceinline__ void acc_to_lds(const f32x4& acc, uint32_t lds, int block, int th, int nh,
+                                           const uint16_t* __restrict__ bias, bool relu) {
+  const int lane = threadIdx.x % kWave, tl = th + lane % 16, q = lane / 16;
+  cols_to_lds<DT>(acc, lds + out_slot(block, tl, nh / 8 + q / 2) + 8 * (q % 2), bias ? bias + 4 * q : nullptr, relu);
 }
 // The elements of v whose gate is positive, 0 for the others (two packed 16-bit elements each).
 template <int DT>
@@ -218,11 +225,11 @@ __device__ __forceinline__ void lds_to_out(uint32_t lds, uint16_t* __restrict__ 
 
 // Offsets of the two products' transfer instructions: instruction u of wavefront w brings the stage
 // rows 8g .. 8g+7 with g = w + kWaves*u (token rows first); lane l brings the 16-byte slot l % 8 of row
-// l / 8, i.e. segment (l % 8) ^ (l / 8) ^ (g % 8) of that row's 128 bytes.
+// l / 8, i.e. the segment of that row's 128 bytes that tile_swz puts there.
 template <class Tl>
 __device__ __forceinline__ uint32_t lane_voff(long long ld, int g) {
   const int lane = threadIdx.x % kWave, lr = lane / 8;
-  return (uint32_t)(lr * ld * 2 + (((lane % 8) ^ lr ^ (g & 7)) << 4));
+  return (uint32_t)(lr * ld * 2 + (((lane % 8) ^ tile_swz<Tl>(8 * g + lr)) << 4));
 }
 
 struct SddArgs {
@@ -322,18 +329,18 @@ __device__ __forceinline__ void sdd_tile(const SddArgs& a, uint16_t* ring, GridI
     }
   }
   const int wm = wave / Tl::WN, wn = wave % Tl::WN;
-  f32x16 acc[Tl::NI][Tl::TI];
+  typename Tl::Acc acc[Tl::NI][Tl::TI];
   zero_acc<Tl>(acc);
   run_tile<Tl, DT>(src.ksteps + (LORA ? 1 : 0), lds_addr(ring), wm, wn, src, acc);
   lds_barrier();       // nobody reads the ring any more
 #pragma unroll
   for (int ni = 0; ni < Tl::NI; ++ni) {
-    const int e = (wn * Tl::NI + ni) / 2, nh = 32 * ((wn * Tl::NI + ni) % 2);
+    const int c = wn * Tl::NI + ni, e = c / Tl::kPer, nh = Tl::MF * (c % Tl::kPer);
     const uint16_t* bias = a.bias && e < nb ? a.bias + a.col_idx[p0 + e] * 64 + nh : nullptr;
 #pragma unroll
     for (int ti = 0; ti < Tl::TI; ++ti)
-      acc_to_lds<DT>(acc[ni][ti], lds_addr(ring), (wm * Tl::TI + ti) / 2 * Tl::TN + e, 32 * ((wm * Tl::TI + ti) % 2), nh,
-                     bias, !a.gate);
+      acc_to_lds<DT>(acc[ni][ti], lds_addr(ring), (wm * Tl::TI + ti) / Tl::kPer * Tl::TN + e,
+                     Tl::MF * ((wm * Tl::TI + ti) % Tl::kPer), nh, bias, !a.gate);
   }
   lds_barrier();
   lds_to_out<Tl, DT, false>(lds_addr(ring), a.out, 64, a.gate, [&](int t, int e) {
@@ -545,31 +552,26 @@ __device__ __forceinline__ void dsd_tile(const DsdArgs& a, uint16_t* ring, GridI
     }
   }
   const int wm = wave / Tl::WN, wn = wave % Tl::WN;
-  f32x16 acc[Tl::NI][Tl::TI];
+  typename Tl::Acc acc[Tl::NI][Tl::TI];
   zero_acc<Tl>(acc);
   run_tile<Tl, DT>(n_i + (LORA ? 1 : 0), lds_addr(ring), wm, wn, src, acc);
-  if (slot >= 0) {   // the piece's partial sums: [wave][accumulator][quarter][lane][4 registers]
-    f32x4* dst = reinterpret_cast<f32x4*>(a.part + ((size_t)slot * Tl::kWaves + wave) * (Tl::NI * Tl::TI * 16) * kWave) +
-                 threadIdx.x % kWave;
+  if constexpr (Tl::MF == 16)
+    if (slot >= 0) {   // the piece's partial sums: [wave][accumulator][lane][4 registers]
+      f32x4* dst = reinterpret_cast<f32x4*>(a.part) + ((size_t)slot * Tl::kWaves + wave) * (Tl::NI * Tl::TI) * kWave + threadIdx.x % kWave;
 #pragma unroll
-    for (int x = 0; x < Tl::NI; ++x)
+      for (int x = 0; x < Tl::NI; ++x)
 #pragma unroll
-      for (int y = 0; y < Tl::TI; ++y)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 v4 = {acc[x][y][4 * q], acc[x][y][4 * q + 1], acc[x][y][4 * q + 2], acc[x][y][4 * q + 3]};
-          dst[((x * Tl::TI + y) * 4 + q) * kWave] = v4;
-        }
-    return;
-  }
+        for (int y = 0; y < Tl::TI; ++y) dst[(x * Tl::TI + y) * kWave] = acc[x][y];
+      return;
+    }
   lds_barrier();       // nobody reads the ring any more
 #pragma unroll
   for (int ni = 0; ni < Tl::NI; ++ni) {
-    const int c = wn * Tl::NI + ni, n = n0 + 32 * c;
+    const int c = wn * Tl::NI + ni, n = n0 + Tl::MF * c;
 #pragma unroll
     for (int ti = 0; ti < Tl::TI; ++ti)
-      acc_to_lds<DT>(acc[ni][ti], lds_addr(ring), (wm * Tl::TI + ti) / 2 * Tl::TN + c / 2, 32 * ((wm * Tl::TI + ti) % 2),
-                     32 * (c % 2), a.bias && n < a.ncols ? a.bias + n : nullptr, false);
+      acc_to_lds<DT>(acc[ni][ti], lds_addr(ring), (wm * Tl::TI + ti) / Tl::kPer * Tl::TN + c / Tl::kPer,
+                     Tl::MF * ((wm * Tl::TI + ti) % Tl::kPer), Tl::MF * (c % Tl::kPer), a.bias && n < a.ncols ? a.bias + n : nullptr, false);
   }
   lds_barrier();
   lds_to_out<Tl, DT, true>(lds_addr(ring), a.out, a.ncols, nullptr, [&](int t, int e) {
@@ -600,33 +602,39 @@ __global__ __launch_bounds__(512, 2) void ffn_dsd_mix(DsdArgs a) {
 
 // Adds the pieces of each cut unit (piece 0 first, fixed order: reproducible) and stores like the kernel's own
 // epilogue: workgroup (b, y) is unit full + b and the y-th 64 x 64 block of its tile; wavefront w adds the
-// accumulator that holds quadrant (w % 2, w / 2) of the block.
+// four accumulators that hold quadrant (w % 2, w / 2) of the block.
 template <class Tl, int DT>
 __global__ __launch_bounds__(256) void ffn_dsd_reduce(DsdArgs a) {
   __shared__ __attribute__((aligned(1024))) uint16_t block[64 * 64];
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
   const int t = blockIdx.y / Tl::TN, e = blockIdx.y % Tl::TN, nh = w % 2, th = w / 2;
-  const int tg = 2 * t + th, ng = 2 * e + nh;        // 32-row groups of the tile
-  const int wave = tg / Tl::TI * Tl::WN + ng / Tl::NI, acc_i = ng % Tl::NI * Tl::TI + tg % Tl::TI;
   const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (a.ncols + 64 * Tl::TN - 1) / (64 * Tl::TN);
   const GridItem it = grid_item(a.full + blockIdx.x, GM, GN, a.band);
   const int i = it.m * Tl::TM + t, n = (it.n * Tl::TN + e) * 64;
   if (i >= a.Tt || n >= a.ncols) return;
-  f32x16 acc;
+  const f32x4* src[2][2];
+  f32x4 acc[2][2];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  for (int p = 0; p < a.pieces; ++p) {
-    const f32x4* src = reinterpret_cast<const f32x4*>(
-                           a.part + (((size_t)blockIdx.x * a.pieces + p) * Tl::kWaves + wave) * (Tl::NI * Tl::TI * 16) * kWave) +
-                       acc_i * (kWave * 4) + lane;
+  for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4 v4 = src[q * kWave];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[4 * q + r] += v4[r];
+    for (int y = 0; y < 2; ++y) {
+      const int ng = 4 * e + 2 * nh + x, tg = 4 * t + 2 * th + y;        // 16-row groups of the tile
+      const int wave = tg / Tl::TI * Tl::WN + ng / Tl::NI, acc_i = ng % Tl::NI * Tl::TI + tg % Tl::TI;
+      src[x][y] = reinterpret_cast<const f32x4*>(a.part) +
+                  (((size_t)blockIdx.x * a.pieces * Tl::kWaves + wave) * (Tl::NI * Tl::TI) + acc_i) * kWave + lane;
+      acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-  }
-  acc_to_lds<DT>(acc, lds_addr(block), 0, 32 * th, 32 * nh, a.bias ? a.bias + n + 32 * nh : nullptr, false);
+  for (int p = 0; p < a.pieces; ++p)
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y) acc[x][y] += src[x][y][(size_t)p * (Tl::kWaves * Tl::NI * Tl::TI * kWave)];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+      acc_to_lds<DT>(acc[x][y], lds_addr(block), 0, 32 * th + 16 * y, 32 * nh + 16 * x,
+                     a.bias ? a.bias + n + 32 * nh + 16 * x : nullptr, false);
   lds_barrier();
   lds_to_out<Tile<1, 1, 2, 2, 2, 2>, DT, true>(lds_addr(block), a.out, a.ncols, nullptr,
                                          [&](int, int) { return (long long)i * 64 * a.ncols + n; });

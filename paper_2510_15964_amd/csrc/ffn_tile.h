@@ -5,9 +5,17 @@
 // One barrier per step, and operands of the next phase on their way from LDS to registers while the
 // matrix instructions of the current one run (a plain "barrier, read, multiply" step leaves the matrix
 // cores idle for as long as all wavefronts of the CU read their operands at once: 256 x 256 x 64 steps
-// took 1800 ns that way).  A step is cut into 4 / KS phases of KS 16-deep slices; before the last phase
-// of step s a wavefront has all its operands of the step in registers, so past the barrier that also
-// tells it that step s + 1 has landed it may refill the stage of step s.
+// took 1800 ns that way).  A step is cut into PH phases; before the last phase of step s a wavefront has
+// all its operands of the step in registers, so past the barrier that also tells it that step s + 1 has
+// landed it may refill the stage of step s.
+//
+// The matrix instruction is the 16x16x32 one.  The 32x32x16 one reads half the operand bytes per product, but its
+// accumulators cross the register file once per 16 of the contraction index instead of 32, and power bounds the wide
+// tiles: on registers, with normally distributed operands, it reaches 1680 TFLOP/s and the 16x16x32 one 1930 (2300 and
+// 2340 with zeros).  Bits are the same.  4 x 4 tiles, first / second product, us: 4096 tokens, d = 5120, all 320 blocks 698 / 918
+// -> 638 / 857, 3840 tokens, 96 blocks 220 / 249 -> 206 / 233, 8192 tokens, d = 4096, 64 blocks 213 / 202 -> 194 / 186; over 250 drawn
+// launches 2 x 4 tiles 1.6 % less time, 1 x 4 ones 1.6, 2 x 2 ones 0.6, 1 x 2 ones 0.4.  The 1 x 1 tile keeps the larger one: it is a
+// chain of few instructions, and with them half as many it takes 1.3 % less.
 #pragma once
 #include <type_traits>
 
@@ -15,54 +23,74 @@
 
 namespace lx {
 
-// TM x TN groups of 64 token / weight rows, WM x WN wavefronts over them, NST ring stages, KS slices per
-// phase, MINW wavefronts per SIMD the registers have to leave room for.
-template <int TM_, int TN_, int WM_, int WN_, int NST_, int KS_, int MINW_ = 2>
+// TM x TN groups of 64 token / weight rows, WM x WN wavefronts over them, NST ring stages, PH phases per
+// step, MINW wavefronts per SIMD the registers have to leave room for, MF rows of the matrix instruction's tile (16; 32 for
+// the 1 x 1 tile, and for a ring of one stage, which has no registers for slices 32 deep).
+template <int MF>
+struct AccOf {
+  using T = f32x4;
+};
+template <>
+struct AccOf<32> {
+  using T = f32x16;
+};
+template <int TM_, int TN_, int WM_, int WN_, int NST_, int PH_, int MINW_ = 2, int MF_ = 16>
 struct Tile {
-  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, NST = NST_, KS = KS_, kMinWaves = MINW_;
+  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, NST = NST_, PH = PH_, kMinWaves = MINW_, MF = MF_;
   static constexpr int kWaves = WM * WN, kTileThreads = kWaves * kWave;
   static constexpr int kElems = 64 * (TM + TN) * kBK;        // one stage
   static constexpr int kIss = 8 * (TM + TN) / kWaves;        // transfer instructions per wavefront and stage
   static constexpr int kIssA = 8 * TM / kWaves;              // the first of them bring token rows
-  static constexpr int NI = 2 * TN / WN, TI = 2 * TM / WM;   // 32 x 32 accumulators of a wavefront
+  static constexpr int kPer = 64 / MF;                       // accumulators along 64 rows
+  static constexpr int NI = kPer * TN / WN, TI = kPer * TM / WM;      // MF x MF accumulators of a wavefront
+  static constexpr int kSlices = MF / 16 * 2, KS = kSlices / PH;      // slices of a step, 512 / MF deep; of a phase
+  using Acc = typename AccOf<MF>::T;
   static_assert(8 * TM % kWaves == 0 && 8 * TN % kWaves == 0 && (kWaves == 4 || kWaves == 8), "wavefronts");
-  static_assert(NI >= 1 && TI >= 1 && (KS == 2 || KS == 4 || (KS == 1 && NST == 1)), "wave tile");
+  static_assert(NI >= 1 && TI >= 1 && (NST == 1 ? PH == kSlices : PH == 1 || PH == 2), "wave tile");
 };
+template <int DT>
+__device__ __forceinline__ f32x16 mfma(uint4 a, uint4 b, f32x16 c) { return mfma32<DT>(a, b, c); }
+template <int DT>
+__device__ __forceinline__ f32x4 mfma(uint4 a, uint4 b, f32x4 c) { return mfma16<DT>(a, b, c); }
 
 template <class Tl>
 struct Frag {
   uint4 a[Tl::KS][Tl::NI], b[Tl::KS][Tl::TI];   // weight rows, token rows
 };
 
-// LDS byte offsets of this lane's operand rows inside a stage, per 16-deep slice.
+// What the 16-byte slots of a stage's row are XORed with, so that the lanes of an operand read that are served together
+// (0 .. 3, 12 .. 15 and 20 .. 27 of a half wavefront, and the others) meet in no bank: 16 rows of two slots, or 32 of one.
+template <class Tl>
+__device__ __forceinline__ int tile_swz(int row) {
+  return (Tl::MF == 16 ? row : row ^ row >> 3) & 7;
+}
+// LDS byte offsets of this lane's operand rows inside a stage, per slice.
 template <class Tl>
 struct LaneOff {
-  uint32_t a[4], b[4];
+  uint32_t a[Tl::kSlices], b[Tl::kSlices];
   __device__ __forceinline__ LaneOff(int wm, int wn) {
-    const int lane = threadIdx.x % kWave, r = lane % 32, h2 = lane / 32;
-    const int sw = (r & 7) ^ (r >> 3);
-    // 32-row groups with an odd index have bit 2 of the slot flipped (row >> 3 is 4 more): for even
-    // NI / TI that parity is a compile-time property of the accumulator, handled in read()
-    const int pa = Tl::NI == 1 ? 4 * (wn & 1) : 0, pb = Tl::TI == 1 ? 4 * (wm & 1) : 0;
+    const int lane = threadIdx.x % kWave, r = lane % Tl::MF;
+    const int ra = Tl::MF * Tl::NI * wn + r, rb = Tl::MF * Tl::TI * wm + r;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int seg = 2 * k + h2;
-      a[k] = (uint32_t)((64 * Tl::TM + 32 * Tl::NI * wn + r) * 128 + ((seg ^ sw ^ pa) << 4));
-      b[k] = (uint32_t)((32 * Tl::TI * wm + r) * 128 + ((seg ^ sw ^ pb) << 4));
+    for (int k = 0; k < Tl::kSlices; ++k) {
+      const int seg = k * (kWave / Tl::MF) + lane / Tl::MF;
+      a[k] = (uint32_t)((64 * Tl::TM + ra) * 128 + ((seg ^ tile_swz<Tl>(ra)) << 4));
+      b[k] = (uint32_t)(rb * 128 + ((seg ^ tile_swz<Tl>(rb)) << 4));
     }
   }
 };
 
-// Operand number x of phase ph of the stage at LDS address `stage`.
+// Operand number x of phase ph of the stage at LDS address `stage`.  (Every other group of 32 rows has bit 2 of
+// tile_swz flipped, which is a slice two further on.)
 template <class Tl>
 __device__ __forceinline__ void read_operand(Frag<Tl>& f, const LaneOff<Tl>& lo, uint32_t stage, int ph, int x) {
   constexpr int per = Tl::NI + Tl::TI;
-  const int e = x / per, y = x % per, k = ph * Tl::KS + e;
+  const int e = x / per, y = x % per, k = ph * Tl::KS + e, i = y < Tl::NI ? y : y - Tl::NI;
+  const int at = Tl::MF == 32 ? k ^ 2 * (i & 1) : k;
   if (y < Tl::NI)
-    f.a[e][y] = lds_read16(stage + lo.a[k ^ (Tl::NI > 1 ? 2 * (y & 1) : 0)] + y * 4096);
+    f.a[e][i] = lds_read16(stage + lo.a[at] + i * (Tl::MF * 128));
   else
-    f.b[e][y - Tl::NI] =
-        lds_read16(stage + lo.b[k ^ (Tl::TI > 1 ? 2 * ((y - Tl::NI) & 1) : 0)] + (y - Tl::NI) * 4096);
+    f.b[e][i] = lds_read16(stage + lo.b[at] + i * (Tl::MF * 128));
 }
 
 // One phase: the products of `cur`, meanwhile the operands of phase ph of the stage at `stage` go to
@@ -70,7 +98,7 @@ __device__ __forceinline__ void read_operand(Frag<Tl>& f, const LaneOff<Tl>& lo,
 template <class Tl, int DT, bool DMA, class Src>
 __device__ __forceinline__ void tile_phase(const Frag<Tl>& cur, Frag<Tl>& nxt, const LaneOff<Tl>& lo,
                                            uint32_t stage, int ph, Src& src, uint32_t dma_lds,
-                                           f32x16 (&acc)[Tl::NI][Tl::TI]) {
+                                           typename Tl::Acc (&acc)[Tl::NI][Tl::TI]) {
   constexpr int NM = Tl::KS * Tl::NI * Tl::TI, NR = Tl::KS * (Tl::NI + Tl::TI), ND = Tl::kIss;
   // operand reads over the first three quarters of the matrix instructions, transfers over all of them
   constexpr int RM = NM * 3 / 4 > 0 ? NM * 3 / 4 : 1;
@@ -93,7 +121,7 @@ __device__ __forceinline__ void tile_phase(const Frag<Tl>& cur, Frag<Tl>& nxt, c
             if (z >= xd && z < d_to) src.dma(z, dma_lds);
           xd = d_to;
         }
-        acc[ni][ti] = mfma32<DT>(cur.a[e][ni], cur.b[e][ti], acc[ni][ti]);
+        acc[ni][ti] = mfma<DT>(cur.a[e][ni], cur.b[e][ti], acc[ni][ti]);
         __builtin_amdgcn_sched_barrier(0);
         ++m;
       }
@@ -103,7 +131,7 @@ __device__ __forceinline__ void tile_phase(const Frag<Tl>& cur, Frag<Tl>& nxt, c
 // such a stage leaves room for on the CU compute meanwhile.
 template <class Tl, int DT, class Src>
 __device__ __forceinline__ void run_tile_one_stage(int nsteps, uint32_t ring, int wm, int wn, Src& src,
-                                                   f32x16 (&acc)[Tl::NI][Tl::TI]) {
+                                                   typename Tl::Acc (&acc)[Tl::NI][Tl::TI]) {
   if (nsteps <= 0) return;
   const LaneOff<Tl> lo(wm, wn);
   const uint32_t to = ring + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave) * 1024;
@@ -121,8 +149,8 @@ __device__ __forceinline__ void run_tile_one_stage(int nsteps, uint32_t ring, in
     read(0);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int ph = 0; ph < 4; ++ph) {
-      if (ph < 3) {
+    for (int ph = 0; ph < Tl::PH; ++ph) {
+      if (ph + 1 < Tl::PH) {
         read(ph + 1);
       } else {
         lds_barrier();     // every wavefront has the step's operands in registers
@@ -136,7 +164,7 @@ __device__ __forceinline__ void run_tile_one_stage(int nsteps, uint32_t ring, in
 #pragma unroll
       for (int ni = 0; ni < Tl::NI; ++ni)
 #pragma unroll
-        for (int ti = 0; ti < Tl::TI; ++ti) acc[ni][ti] = mfma32<DT>(f[ph % 2].a[0][ni], f[ph % 2].b[0][ti], acc[ni][ti]);
+        for (int ti = 0; ti < Tl::TI; ++ti) acc[ni][ti] = mfma<DT>(f[ph % 2].a[0][ni], f[ph % 2].b[0][ti], acc[ni][ti]);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -146,7 +174,7 @@ __device__ __forceinline__ void run_tile_one_stage(int nsteps, uint32_t ring, in
 // issues its transfer instruction u to the stage at that LDS address.
 template <class Tl, int DT, class Src>
 __device__ __forceinline__ void run_tile_ring(int nsteps, uint32_t ring, int wm, int wn, Src& src,
-                                         f32x16 (&acc)[Tl::NI][Tl::TI]) {
+                                         typename Tl::Acc (&acc)[Tl::NI][Tl::TI]) {
   constexpr int NST = Tl::NST, NISS = Tl::kIss;
   static_assert(NST >= 2 && NISS * (NST - 1) < 64, "ring depth");
   if (nsteps <= 0) return;
@@ -177,7 +205,7 @@ __device__ __forceinline__ void run_tile_ring(int nsteps, uint32_t ring, int wm,
     const uint32_t here = ring + stage * kStage;
     stage = stage + 1 == NST ? 0 : stage + 1;
     const uint32_t next = ring + stage * kStage;
-    if constexpr (Tl::KS == 2) tile_phase<Tl, DT, false>(fa, fb, lo, here, 1, src, 0u, acc);
+    if constexpr (Tl::PH == 2) tile_phase<Tl, DT, false>(fa, fb, lo, here, 1, src, 0u, acc);
     // step s + 1 has landed: at most the transfers of steps s + 2 .. s + NST - 1 are outstanding
     if constexpr (D) {
       wait_vmcnt<NISS * (NST - 2)>();
@@ -190,13 +218,13 @@ __device__ __forceinline__ void run_tile_ring(int nsteps, uint32_t ring, int wm,
     }
     lds_barrier();
     if constexpr (D) src.begin(s + NST);
-    if constexpr (Tl::KS == 2)
+    if constexpr (Tl::PH == 2)
       tile_phase<Tl, DT, D>(fb, fa, lo, next, 0, src, here + wave_lds, acc);
     else
       tile_phase<Tl, DT, D>(fa, fb, lo, next, 0, src, here + wave_lds, acc);
   };
   int s = 0;
-  if constexpr (Tl::KS == 2) {
+  if constexpr (Tl::PH == 2) {
     for (; s + NST < nsteps; ++s) step(s, std::true_type{}, f0, f1);
     for (; s < nsteps; ++s) step(s, std::false_type{}, f0, f1);
   } else {      // the two operand sets swap roles every step
@@ -222,7 +250,7 @@ __device__ __forceinline__ void run_tile_ring(int nsteps, uint32_t ring, int wm,
 
 template <class Tl, int DT, class Src>
 __device__ __forceinline__ void run_tile(int nsteps, uint32_t ring, int wm, int wn, Src& src,
-                                         f32x16 (&acc)[Tl::NI][Tl::TI]) {
+                                         typename Tl::Acc (&acc)[Tl::NI][Tl::TI]) {
   if constexpr (Tl::NST == 1)
     run_tile_one_stage<Tl, DT>(nsteps, ring, wm, wn, src, acc);
   else

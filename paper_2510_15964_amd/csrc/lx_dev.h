@@ -50,6 +50,18 @@ __device__ __forceinline__ f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// 16x16x32 MFMA on 16-bit operands.  Operand a: lane l holds row l%16, k = 8*(l/16)..+7; operand
+// b: column l%16, same k.  Accumulator register v of lane l is C[4*(l/16) + v][l%16].
+template <int DT>
+__device__ __forceinline__ f32x4 mfma16(uint4 a, uint4 b, f32x4 c) {
+  if constexpr (DT == kF16)
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
+                                                  __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
 // Asynchronous 16-byte-per-lane copy global -> LDS (global_load_lds_dwordx4): lane l of the
 // wave lands at lds_wave_base + 16*l; completion is counted by vmcnt.  Issued as assembly so
 // that the waits are entirely under the kernel's control: for DMA it knows about, the compiler
