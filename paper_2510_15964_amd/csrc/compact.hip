@@ -4,8 +4,10 @@
 // The masks of one layer are tiny (tens of thousands of bytes), so the whole
 // job is latency-bound: a 512-thread workgroup does count -> scan -> scatter
 // for a list (or for a part of its rows) in a single launch with no host
-// round trip.  One wavefront owns a mask row at
-// a time: a 64-wide ballot gives the row's bit pattern, popcount its total and
+// round trip.  Masks that lie contiguously, in either orientation, are walked as one sequence of bytes in
+// the order of the list, four per lane: what precedes a byte is a few ballots and the wavefronts' totals, so
+// there is one barrier per 2048 bytes and no count or scan per row.  Masks of other strides go row by row: a
+// wavefront owns a row at a time, a 64-wide ballot gives the row's bit pattern, popcount its total and
 // mbcnt the rank of every set lane, so columns come out ascending.
 #include "lx_dev.h"
 #include "lx_launch.h"
@@ -17,10 +19,6 @@ constexpr int kCompactWaves = kCompactThreads / kWave;
 constexpr int kChunkRows = 4096;    // rows scanned per pass (8 per thread)
 constexpr int kRowsPer = kChunkRows / kCompactThreads;
 constexpr int kStageBytes = 32768;  // mask bytes staged in LDS per pass
-
-// The mask chunk is first copied into LDS with all loads in flight at once (strided or not),
-// because a wavefront that walks rows straight from global memory pays one full memory
-// latency per row; the ballots then run out of LDS.
 
 // How the bytes of a job lie: the rows of all masks one after the other, or every mask contiguous in
 // the other orientation (the column list of contiguous masks), or anything else.
@@ -40,27 +38,29 @@ inline MaskLayout mask_layout(const CompactJob& j) {
 // range of bytes, and the part another, in either orientation (16 bytes per load for both).  A part
 // is about 1 KB: 32 heads of 32 x 32 in 32 parts per list take 13 us in eight parts of bytes loaded
 // one by one for the column list, 7 so.  Strided bytes are slow to count, so those parts are larger.
+enum CompactBy { kFlat, kTurned, kByRow };
 struct CompactParts {
   int parts, rows;      // rows per part
-  int chunk;            // rows per pass
-  int layout, colmajor; // MaskLayout; whether whole masks in the other orientation are staged as they lie
+  int chunk;            // rows per pass (kTurned, kByRow)
+  int by, layout;       // CompactBy, MaskLayout
 };
 inline CompactParts compact_parts(const CompactJob& j) {
-  const long long total = (long long)j.batch * j.rows;
+  const long long total = (long long)j.batch * j.rows, bytes = total * j.cols;
   const MaskLayout lay = mask_layout(j);
   const bool masks = lay != kStrided && j.batch > 1 && j.rows <= kChunkRows && (long long)j.rows * j.cols <= kStageBytes;
   const int unit = masks ? j.rows : 1;
   const bool fast = masks || lay == kRowMajor;
   const long long units = total / unit;
-  long long p = (total * j.cols + (fast ? 1023 : 4095)) / (fast ? 1024 : 4096);
+  long long p = (bytes + (fast ? 1023 : 4095)) / (fast ? 1024 : 4096);
   p = p > (fast ? 64 : 16) ? (fast ? 64 : 16) : p;
   p = p > units ? units : p < 1 ? 1 : p;
   const long long per = (units + p - 1) / p;
-  CompactParts c = {(int)((units + per - 1) / per), (int)per * unit, 1, lay, 0};
-  c.colmajor = lay == kColMajor && j.rows <= kChunkRows && (long long)j.rows * j.cols <= kStageBytes && c.rows % j.rows == 0;
-  if (c.colmajor) {
-    const int masks_fit = kStageBytes / (j.rows * j.cols), by_rows = kChunkRows / j.rows;
-    c.chunk = (masks_fit < by_rows ? masks_fit : by_rows) * j.rows;
+  CompactParts c = {(int)((units + per - 1) / per), (int)per * unit, 1, kByRow, lay};
+  if (lay == kRowMajor && bytes < 1ll << 30) {
+    c.by = kFlat;
+  } else if (lay == kColMajor && j.rows <= kChunkRows && (long long)j.rows * j.cols <= kStageBytes && c.rows % j.rows == 0) {
+    c.by = kTurned;
+    c.chunk = kStageBytes / (j.rows * j.cols) * j.rows;
   } else if (j.cols <= kStageBytes) {
     const int fit = kStageBytes / j.cols;
     c.chunk = fit < 1 ? 1 : fit < kChunkRows ? fit : kChunkRows;
@@ -69,9 +69,6 @@ inline CompactParts compact_parts(const CompactJob& j) {
 }
 constexpr int kMaxJobs = 8;
 // The parts are the host's to compute: some dozen divisions, half of them of 64 bits, took a workgroup as long as a load.
-// Without them, with the first chunk's bytes loaded while those before it are counted and without the division per byte of the other
-// orientation, us: one list of 64 x 128 bytes 8.1 -> 7.2, the three of a layer (128 x 128; 32 heads of 16 x 16, both
-// orientations) 9.1 -> 7.3, both of 32 heads of 32 x 32 8.5 -> 7.8, one row of 48 bytes 4.1 -> 3.7.
 struct CompactJobs {
   CompactJob j[kMaxJobs];
   CompactParts p[kMaxJobs];
@@ -122,73 +119,185 @@ __device__ __forceinline__ int nonzero_bytes(uint32_t w) {
   return __popc(t & 0x80808080u);
 }
 
-__global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJobs jobs) {
-  const CompactJob& job = jobs.j[blockIdx.x];
+// Sum over the wavefront, in the vector unit (a shuffle goes through LDS: six of them take some 0.3 us).
+__device__ __forceinline__ int wave_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // row_bcast 15, 31
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+// This thread's share of the active bytes among the first n of p.
+__device__ __forceinline__ int count_bytes(const uint8_t* __restrict__ p, long long n) {
+  const int tid = threadIdx.x;
+  int cnt = 0;
+  long long head = (16 - (long long)(reinterpret_cast<uintptr_t>(p) & 15)) & 15;
+  head = head < n ? head : n;
+  if (tid < head) cnt += p[tid] != 0;
+  const long long nvec = (n - head) / 16;
+  const uint4* __restrict__ vp = reinterpret_cast<const uint4*>(p + head);
+  constexpr int kVec = 8;
+  for (long long i0 = tid; i0 < nvec; i0 += (long long)kCompactThreads * kVec) {
+    uint4 q[kVec];
+#pragma unroll
+    for (int u = 0; u < kVec; ++u) {
+      const long long i = i0 + (long long)u * kCompactThreads;
+      q[u] = i < nvec ? vp[i] : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < kVec; ++u)
+      cnt += nonzero_bytes(q[u].x) + nonzero_bytes(q[u].y) + nonzero_bytes(q[u].z) + nonzero_bytes(q[u].w);
+  }
+  const long long tail = head + nvec * 16;   // fewer than 16 bytes remain
+  if (tail + tid < n) cnt += p[tail + tid] != 0;
+  return cnt;
+}
+struct CompactLds {
+  int offs[kChunkRows];                 // kByRow
+  int wave_tot[kCompactWaves];
+  struct {
+    int own[kCompactWaves], before[kCompactWaves];
+  } sums[2];
+  __attribute__((aligned(16))) uint8_t stage[kStageBytes + 16];
+};
+
+// Rows row_lo .. row_hi - 1 of masks whose bytes lie contiguously.  A launch of one instruction after the other costs 1.6 us,
+// and a dependent instruction some 2 ns: bytes in registers, four ballots for their ranks and one barrier, where rows were
+// staged in LDS, counted, scanned by shuffles and scattered, with five barriers.  us, before and now: one row of 48 bytes 4.1 -> 2.6,
+// 64 x 128 bytes 6.2 -> 3.8, the three lists of a layer (128 x 128; 32 heads of 16 x 16, both orientations) 6.7 -> 4.0, both lists
+// of 12 heads of 5 x 5 4.4 -> 3.1; 405 launches of other shapes, alignments and densities 1.02 - 2.6 times as fast, 1.59 in the mean.
+// (Of 16 bytes a lane the scattered stores would touch four times the lines.)  TURNED: in the other orientation, whole masks, which go
+// through `stage`.
+template <bool TURNED>
+__device__ __forceinline__ void compact_flat(const CompactJob& job, int chunk_rows, int row_lo, int row_hi, bool last, CompactLds& s) {
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int rows = job.rows, cols = job.cols, cap = job.cap;
+  int* __restrict__ row_ptr = job.row_ptr;
+  int* __restrict__ col_idx = job.col_idx;
+  const uint8_t* __restrict__ src = job.mask + (long long)row_lo * cols;
+  constexpr int kStep = 4 * kCompactThreads;
+  const float per_col = __builtin_amdgcn_rcpf((float)cols), per_row = __builtin_amdgcn_rcpf((float)rows);
+  int carry = 0, step = 0;
+  int pass_row = row_lo;
+  do {
+    const int pass_rows = TURNED ? min(chunk_rows, row_hi - pass_row) : row_hi - row_lo, len = pass_rows * cols;
+    // (flat: four bytes a lane from an address that is a multiple of four; the first ones may be none of this part's)
+    const int lead = TURNED ? 0 : (int)(reinterpret_cast<uintptr_t>(src) & 3);
+    auto load = [&](int at) {            // bytes at .. at + 3
+      uint32_t w = 0;
+      if (at >= 0 && at + 4 <= len) return *reinterpret_cast<const uint32_t*>(src + at);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (at + u >= 0 && at + u < len) w |= (uint32_t)src[at + u] << 8 * u;
+      return w;
+    };
+    uint32_t w = 0;
+    int soff = 0;
+    if constexpr (TURNED) {              // 16 bytes per load, placed so that source and stage are aligned alike
+      if (pass_row > row_lo) __syncthreads();      // nobody reads the stage any more
+      const uint8_t* from = job.mask + (long long)pass_row * cols;
+      soff = (int)(reinterpret_cast<uintptr_t>(from) & 15);
+      const int head = min((16 - soff) & 15, len), nvec = (len - head) / 16, tail = head + nvec * 16;
+      if (tid < head) s.stage[soff + tid] = from[tid];
+      for (int i = tid; i < nvec; i += kCompactThreads)
+        reinterpret_cast<uint4*>(s.stage + soff + head)[i] = reinterpret_cast<const uint4*>(from + head)[i];
+      if (tail + tid < len) s.stage[soff + tail + tid] = from[tail + tid];
+    } else {
+      w = load(4 * tid - lead);
+    }
+    const bool first = pass_row == row_lo;
+    const int before = first && row_lo > 0 ? wave_sum(count_bytes(job.mask, (long long)row_lo * cols)) : 0;
+    if constexpr (TURNED) __syncthreads();
+    for (int at0 = -lead; at0 < len; at0 += kStep, step ^= 1) {
+      const int at = at0 + 4 * tid, from = at > 0 ? at : 0;
+      // row and column of the lane's first byte
+      int row = from < 1 << 22 ? (int)(((float)from + 0.5f) * per_col) : from / cols, c = from - row * cols;
+      if (c < 0) --row, c += cols;
+      if (c >= cols) ++row, c -= cols;
+      unsigned on = 0;                   // bit u: byte u is active
+      if constexpr (TURNED) {
+        const int per = rows * cols;
+        // (row < 32768, so the product errs by less than 0.5 / rows)
+        int q = (int)(((float)row + 0.5f) * per_row), r = row - q * rows, cc = c;
+        uint32_t addr = soff + q * per + cc * rows + r;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (at + u < len && s.stage[addr] != 0) on |= 1u << u;
+          addr += rows;
+          if (++cc == cols) {
+            cc = 0;
+            if (++r == rows) r = 0, ++q;
+            addr = soff + q * per + r;
+          }
+        }
+      } else {
+        if (at0 > -lead) w = load(at);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) on |= (w >> 8 * u & 0xFFu) != 0 ? 1u << u : 0u;
+      }
+      int rank = 0, total = 0;           // active bytes of the wavefront before the lane's; of all its lanes
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const unsigned long long set = __ballot(on >> u & 1u);
+        rank += __builtin_amdgcn_mbcnt_hi((uint32_t)(set >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)set, 0u));
+        total += __popcll(set);
+      }
+      if (lane == 0) {
+        s.sums[step].own[wave] = total;
+        s.sums[step].before[wave] = first && at0 == -lead ? before : 0;
+      }
+      __syncthreads();
+      int pos = carry + rank;
+#pragma unroll
+      for (int v = 0; v < kCompactWaves; ++v) {
+        const int own = s.sums[step].own[v], add = s.sums[step].before[v];
+        carry += own + add;
+        pos += add + (v < wave ? own : 0);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (at + u < 0 || at + u >= len) continue;
+        if (c == 0) row_ptr[pass_row + row] = pos;
+        if (on >> u & 1u) {
+          if (pos < cap) col_idx[pos] = c;
+          ++pos;
+        }
+        if (++c == cols) c = 0, ++row;
+      }
+    }
+    pass_row += pass_rows;
+  } while (TURNED && pass_row < row_hi);
+  if (last && tid == 0) row_ptr[job.batch * rows] = carry;
+}
+
+// ... of masks with any strides.
+__device__ __forceinline__ void compact_rows(const CompactJob& job, int layout, int chunk_rows, int row_lo, int row_hi, bool last,
+                                             CompactLds& s_) {
   const uint8_t* __restrict__ mask = job.mask;
-  const int batch = job.batch, rows = job.rows, cols = job.cols, cap = job.cap;
+  const int rows = job.rows, cols = job.cols, cap = job.cap;
   const long long bstride = job.bstride, rstride = job.rstride, cstride = job.cstride;
   int* __restrict__ row_ptr = job.row_ptr;
   int* __restrict__ col_idx = job.col_idx;
-  __shared__ int offs[kChunkRows];
-  __shared__ int wave_tot[kCompactWaves];
-  __shared__ __attribute__((aligned(16))) uint8_t stage[kStageBytes + 16];
+  int(&offs)[kChunkRows] = s_.offs;
+  int(&wave_tot)[kCompactWaves] = s_.wave_tot;
+  uint8_t(&stage)[kStageBytes + 16] = s_.stage;
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int total_rows = batch * rows;
-  const CompactParts cparts = jobs.p[blockIdx.x];
-  const int parts = cparts.parts, part = blockIdx.y;
-  if (part >= parts) return;
-  const int row_lo = min(part * cparts.rows, total_rows), row_hi = min(row_lo + cparts.rows, total_rows);
-  const bool rowmajor = cparts.layout == kRowMajor, colmajor = cparts.colmajor != 0, staged = cols <= kStageBytes;
-  const int chunk_rows = cparts.chunk;
-  const float per_row = 1.f / (float)rows;
+  const bool staged = cols <= kStageBytes;
   int cp = kWave;                       // columns handled per wave pass (power of two)
   while (cp > 1 && (cp >> 1) >= cols) cp >>= 1;
   const int rpw = kWave / cp;           // rows per wave pass
   const int sub = lane / cp, cl = lane % cp;
   const unsigned long long field = cp == 64 ? ~0ull : ((1ull << cp) - 1ull);
-  // this thread's 16 bytes of the first aligned ones in a contiguous range
-  auto first_vec = [&](const uint8_t* src, int len) {
-    const int head = min((16 - (int)(reinterpret_cast<uintptr_t>(src) & 15)) & 15, len);
-    return tid < (len - head) / 16 ? reinterpret_cast<const uint4*>(src + head)[tid] : make_uint4(0, 0, 0, 0);
-  };
-  // the first chunk's bytes are loaded while those before them are counted
-  const bool range = colmajor || (staged && rowmajor);
-  uint4 ahead = make_uint4(0, 0, 0, 0);
-  if (range) ahead = first_vec(mask + (long long)row_lo * cols, min(chunk_rows, row_hi - row_lo) * cols);
   int carry = 0;
   if (row_lo > 0) {      // active entries of the rows before this part
     const long long before = (long long)row_lo * cols;
     int cnt = 0;
-    // Bytes before this part that are one contiguous range are counted 16 bytes per load: all of
-    // them when the rows lie one after the other, else the whole masks before the part when each
-    // mask is contiguous in the other orientation; the rest (the rows of the mask the part
-    // starts in, masks with other strides) byte by byte below.
-    long long done = 0;
-    const long long nbytes = rowmajor ? before
-                             : cparts.layout == kColMajor ? (long long)(row_lo / rows) * rows * cols : 0;
-    if (nbytes > 0) {
-      long long head = (16 - (long long)(reinterpret_cast<uintptr_t>(mask) & 15)) & 15;
-      head = head < nbytes ? head : nbytes;
-      if (tid < head) cnt += mask[tid] != 0;
-      const long long nvec = (nbytes - head) / 16;
-      const uint4* __restrict__ vp = reinterpret_cast<const uint4*>(mask + head);
-      constexpr int kVec = 8;
-      for (long long i0 = tid; i0 < nvec; i0 += (long long)kCompactThreads * kVec) {
-        uint4 q[kVec];
-#pragma unroll
-        for (int u = 0; u < kVec; ++u) {
-          const long long i = i0 + (long long)u * kCompactThreads;
-          q[u] = i < nvec ? vp[i] : make_uint4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < kVec; ++u)
-          cnt += nonzero_bytes(q[u].x) + nonzero_bytes(q[u].y) + nonzero_bytes(q[u].z) +
-                 nonzero_bytes(q[u].w);
-      }
-      const long long tail = head + nvec * 16;   // fewer than 16 bytes remain
-      if (tail + tid < nbytes) cnt += mask[tail + tid] != 0;
-      done = nbytes;
-    }
+    // Whole masks before the part that are contiguous in one orientation or the other are counted 16 bytes per load, the
+    // rest byte by byte below.
+    const long long done = layout == kRowMajor ? before : layout == kColMajor ? (long long)(row_lo / rows) * rows * cols : 0;
+    if (done > 0) cnt += count_bytes(mask, done);
     constexpr int kBatch = 8;
     MaskCursor cur;
     if (done < before) cur.init(done + tid, rows, cols);
@@ -203,8 +312,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) cnt += v[u] != 0;
     }
-#pragma unroll
-    for (int dlt = 32; dlt > 0; dlt >>= 1) cnt += __shfl_xor(cnt, dlt);
+    cnt = wave_sum(cnt);
     if (lane == 0) wave_tot[wave] = cnt;
     __syncthreads();
 #pragma unroll
@@ -213,23 +321,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
   }
   for (int chunk = row_lo; chunk < row_hi; chunk += chunk_rows) {
     const int n = min(chunk_rows, row_hi - chunk);
-    int soff = 0;          // where the chunk's first byte sits in `stage`
-    if (range) {
-      // a contiguous range: 16 bytes per load, placed so that source and stage are aligned alike
-      const uint8_t* __restrict__ src = mask + (long long)chunk * cols;
-      const int len = n * cols;
-      soff = (int)(reinterpret_cast<uintptr_t>(src) & 15);
-      const int head = min((16 - soff) & 15, len), nvec = (len - head) / 16;
-      if (chunk > row_lo) ahead = first_vec(src, len);
-      if (tid < head) stage[soff + tid] = src[tid];
-      const uint4* __restrict__ vp = reinterpret_cast<const uint4*>(src + head);
-      uint4* sp = reinterpret_cast<uint4*>(stage + soff + head);
-      if (tid < nvec) sp[tid] = ahead;
-      for (int i = tid + kCompactThreads; i < nvec; i += kCompactThreads) sp[i] = vp[i];
-      const int tail = head + nvec * 16;                   // fewer than 16 bytes remain
-      if (tail + tid < len) stage[soff + tail + tid] = src[tail + tid];
-      __syncthreads();
-    } else if (staged) {
+    if (staged) {
       // any strides: byte loads, eight in flight per thread
       constexpr int kBatch = 8;
       MaskCursor cur;
@@ -249,11 +341,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
     }
     auto is_on = [&](int r, int c) -> bool {
       if (c >= cols) return false;
-      if (colmajor) {
-        const int q = (int)(((float)r + 0.5f) * per_row);      // r / rows: r < 4096, so the product errs by less than 0.5 / rows
-        return stage[soff + q * rows * cols + c * rows + (r - q * rows)] != 0;
-      }
-      if (staged) return stage[soff + r * cols + c] != 0;
+      if (staged) return stage[r * cols + c] != 0;
       const int gr = chunk + r;
       return mask[(long long)(gr / rows) * bstride + (long long)(gr % rows) * rstride +
                   (long long)c * cstride] != 0;
@@ -321,7 +409,23 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJ
     carry += chunk_total;
     __syncthreads();
   }
-  if (part == parts - 1 && tid == 0) row_ptr[total_rows] = carry;
+  if (last && tid == 0) row_ptr[job.batch * rows] = carry;
+}
+
+__global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactJobs jobs) {
+  const CompactJob& job = jobs.j[blockIdx.x];
+  const CompactParts& p = jobs.p[blockIdx.x];
+  const int part = blockIdx.y;
+  if (part >= p.parts) return;
+  __shared__ CompactLds s;
+  const int total_rows = job.batch * job.rows, row_lo = min(part * p.rows, total_rows), row_hi = min(row_lo + p.rows, total_rows);
+  const bool last = part == p.parts - 1;
+  if (p.by == kFlat)
+    compact_flat<false>(job, 0, row_lo, row_hi, last, s);
+  else if (p.by == kTurned)
+    compact_flat<true>(job, p.chunk, row_lo, row_hi, last, s);
+  else
+    compact_rows(job, p.layout, p.chunk, row_lo, row_hi, last, s);
 }
 
 hipError_t launch_compact_jobs(const CompactJob* jobs, int n, hipStream_t stream) {
