@@ -1,14 +1,17 @@
-"""Thin ctypes binding of the C-ABI library declared in include/lx.h.
+"""Thin binding of the C-ABI library declared in include/lx.h.
 
 Only argument marshalling happens here: torch tensors supply device pointers
 and the current HIP stream; every step of the operators runs inside the
-library's kernels.  Importing this module fails loudly when the library has
-not been built (run `python paper_2510_15964_amd/build.py`); there is no CPU
-or PyTorch fallback.
+library's kernels.  The calls of a training step marshal in native code
+(csrc/lx_call.cpp), the others through ctypes.  Importing this module fails
+loudly when the library has not been built (run
+`python paper_2510_15964_amd/build.py`); there is no CPU or PyTorch fallback.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -16,10 +19,13 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblx_sparse.so")
 
-if not os.path.exists(LIB_PATH):
-    raise ImportError(
-        f"{LIB_PATH} is missing: build the HIP library first "
-        "(python paper_2510_15964_amd/build.py). There is no fallback path.")
+CALL_PATH = os.path.join(_HERE, "_lx_call.so")
+
+for _path in (LIB_PATH, CALL_PATH):
+    if not os.path.exists(_path):
+        raise ImportError(
+            f"{_path} is missing: build the HIP library first "
+            "(python paper_2510_15964_amd/build.py). There is no fallback path.")
 
 _lib = C.CDLL(LIB_PATH)
 
@@ -120,9 +126,7 @@ def _check(status: int, where: str):
         raise LxError(status, where)
 
 
-# Marshalling is on the critical path of the smallest calls (their kernels take a few microseconds
-# each), so it goes by plain integers: the argtypes above turn them into pointers, and the raw
-# stream handle is read without building a torch.cuda.Stream object (2.9 us -> 0.3 us per call).
+# The raw stream handle is read without building a torch.cuda.Stream object (2.9 us -> 0.3 us per call).
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -147,6 +151,19 @@ def _dt(t: torch.Tensor) -> int:
     return dt
 
 
+def _load_calls():
+    """csrc/lx_call.cpp, bound to this module's library.  By path: it is this tree's."""
+    loader = importlib.machinery.ExtensionFileLoader("_lx_call", CALL_PATH)
+    m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_lx_call", loader))
+    loader.exec_module(m)
+    m.bind({n: C.cast(getattr(_lib, n), _vp).value for n in EXPORTS}, _DTYPES, LxError, _stream,
+           torch.uint8, torch.float32, torch.int32)
+    return m
+
+
+_call = _load_calls()
+
+
 class BlockList:
     """Device-resident row-compressed active-block list plus its host header."""
 
@@ -162,38 +179,31 @@ def lx_mask_compact(mask: torch.Tensor, transpose: bool = False, nnz_cap: int | 
                     out: BlockList | None = None) -> BlockList:
     """mask: uint8 device tensor [..., R, C]; leading dims are flattened into
     the list's rows.  transpose=True builds the column-compressed list."""
-    assert mask.dtype == torch.uint8 and mask.is_cuda and mask.is_contiguous() and mask.dim() >= 2
-    R, Cc = mask.shape[-2], mask.shape[-1]
-    batch = mask.numel() // (R * Cc)
-    if transpose:
-        rows, cols, rs, cs = Cc, R, 1, Cc
-    else:
-        rows, cols, rs, cs = R, Cc, Cc, 1
-    cap = batch * rows * cols if nnz_cap is None else nnz_cap
     if out is None:
-        row_ptr = torch.empty(batch * rows + 1, dtype=torch.int32, device=mask.device)
+        assert mask.dtype == torch.uint8 and mask.is_cuda and mask.is_contiguous() and mask.dim() >= 2
+        rows, cols = (mask.shape[-1], mask.shape[-2]) if transpose else mask.shape[-2:]
+        total = mask.numel() // cols
+        cap = total * cols if nnz_cap is None else nnz_cap
+        row_ptr = torch.empty(total + 1, dtype=torch.int32, device=mask.device)
         col_idx = torch.empty(max(cap, 1), dtype=torch.int32, device=mask.device)
-        out = BlockList(batch * rows, cols, row_ptr, col_idx, cap)
-    _check(_lib.lx_mask_compact(_ptr(mask), batch, rows, cols, R * Cc, rs, cs, _ptr(out.row_ptr),
-                                _ptr(out.col_idx), max(cap, 1), _stream()), "lx_mask_compact")
+        out = BlockList(total, cols, row_ptr, col_idx, cap)
+    _call.mask_compact(mask, transpose, nnz_cap, out.row_ptr, out.col_idx)
     return out
 
 
 def lx_mask_compact_pair(mask: torch.Tensor, out=None):
     """Row list and column list of the same masks [..., R, C] in one launch."""
-    assert mask.dtype == torch.uint8 and mask.is_cuda and mask.is_contiguous() and mask.dim() >= 2
-    R, Cc = mask.shape[-2], mask.shape[-1]
-    batch = mask.numel() // (R * Cc)
-    cap = batch * R * Cc
     if out is None:
+        assert mask.dtype == torch.uint8 and mask.is_cuda and mask.is_contiguous() and mask.dim() >= 2
+        R, Cc = mask.shape[-2], mask.shape[-1]
+        batch = mask.numel() // (R * Cc)
+        cap = batch * R * Cc
         mk = lambda rows, cols: BlockList(
             batch * rows, cols, torch.empty(batch * rows + 1, dtype=torch.int32, device=mask.device),
             torch.empty(cap, dtype=torch.int32, device=mask.device), cap)
         out = (mk(R, Cc), mk(Cc, R))
     blr, blc = out
-    _check(_lib.lx_mask_compact_pair(_ptr(mask), batch, R, Cc, R * Cc, Cc, 1, _ptr(blr.row_ptr),
-                                     _ptr(blr.col_idx), _ptr(blc.row_ptr), _ptr(blc.col_idx), cap,
-                                     _stream()), "lx_mask_compact_pair")
+    _call.mask_compact_pair(mask, blr.row_ptr, blr.col_idx, blc.row_ptr, blc.col_idx)
     return blr, blc
 
 
@@ -228,21 +238,18 @@ def lx_attn_combine_patterns(pool_r: BlockList, pool_c: BlockList | None, nblk: 
                              head_pattern: torch.Tensor, nnz_cap: int | None = None, out=None):
     """Multi-head list(s) from the pool layouts and the pattern id of every head.  Returns
     (row list, column list or None)."""
-    assert head_pattern.dtype == torch.int32 and head_pattern.is_cuda and head_pattern.is_contiguous()
     Hm = head_pattern.numel()
-    P = pool_r.rows // nblk
     cap = Hm * nblk * nblk if nnz_cap is None else nnz_cap
     if out is None:
+        assert head_pattern.dtype == torch.int32 and head_pattern.is_cuda and head_pattern.is_contiguous()
         mk = lambda: BlockList(Hm * nblk, nblk,
                                torch.empty(Hm * nblk + 1, dtype=torch.int32, device=head_pattern.device),
                                torch.empty(max(cap, 1), dtype=torch.int32, device=head_pattern.device), cap)
         out = (mk(), mk() if pool_c is not None else None)
     blr, blc = out
-    _check(_lib.lx_attn_combine_patterns(
-        pool_r.ref, pool_c.ref if pool_c is not None else None, P, nblk,
-        _ptr(head_pattern), Hm, _ptr(blr.row_ptr), _ptr(blr.col_idx),
-        _ptr(blc.row_ptr) if blc is not None else None, _ptr(blc.col_idx) if blc is not None else None,
-        max(cap, 1), _stream()), "lx_attn_combine_patterns")
+    _call.combine(pool_r.c, pool_c.c if pool_c is not None else None, pool_r.rows // nblk, nblk, head_pattern, max(cap, 1),
+                  blr.row_ptr, blr.col_idx, blc.row_ptr if blc is not None else None,
+                  blc.col_idx if blc is not None else None)
     return blr, blc
 
 
@@ -305,42 +312,25 @@ def lx_sparse_ffn_lora_bwd_workspace_bytes(T, d, F, nnz_cap) -> int:
 
 def lx_sparse_ffn_lora_fwd(X, W_up, A_pad, B_pad, W_down, bl: BlockList, Y, H_act, U, workspace=None):
     """U = X A_pad^T, H = ReLU(X W_up^T + U B_pad^T) on the listed blocks, Y = H W_down^T."""
-    T, d = X.shape
-    F = W_up.shape[0]
-    assert A_pad.shape == (64, d) and B_pad.shape == (F, 64) and U.shape == (T, 64)
     if workspace is None:
+        T, d = X.shape
         workspace = torch.empty(_lib.lx_sparse_ffn_lora_fwd_workspace_bytes(T, d), dtype=torch.uint8,
                                 device=X.device)
-    _check(_lib.lx_sparse_ffn_lora_fwd(_dt(X), T, d, F, 64, 64, _ptr(X), _ptr(W_up), _ptr(A_pad),
-                                       _ptr(B_pad), _ptr(W_down), bl.ref, _ptr(Y), _ptr(H_act),
-                                       _ptr(U), _ptr(workspace), workspace.numel(), _stream()),
-           "lx_sparse_ffn_lora_fwd")
+    _call.lora_fwd(X, W_up, A_pad, B_pad, W_down, bl.c, Y, H_act, U, workspace)
 
 
 def lx_sparse_ffn_lora_bwd(X, dY, H_act, U, W_up_t, W_down_t, A_pad, B_pad, bl: BlockList, dX, dA, dB,
                            workspace):
     """dX, dA (fp32 [64,d]) and dB (fp32 [F,64]) of the LoRA-branch FFN."""
-    T, d = X.shape
-    F = W_down_t.shape[0]
-    assert dA.dtype == torch.float32 and dA.shape == (64, d) and dB.dtype == torch.float32
-    assert dB.shape == (F, 64) and W_up_t.shape == (d, F) and W_down_t.shape == (F, d)
-    _check(_lib.lx_sparse_ffn_lora_bwd(_dt(X), T, d, F, 64, 64, _ptr(X), _ptr(dY), _ptr(H_act), _ptr(U),
-                                       _ptr(W_up_t), _ptr(W_down_t), _ptr(A_pad), _ptr(B_pad),
-                                       bl.ref, _ptr(dX), _ptr(dA), _ptr(dB), _ptr(workspace),
-                                       workspace.numel(), _stream()), "lx_sparse_ffn_lora_bwd")
+    _call.lora_bwd(X, dY, H_act, U, W_up_t, W_down_t, A_pad, B_pad, bl.c, dX, dA, dB, workspace)
 
 
 def lx_mlp_predict_mask(X: torch.Tensor, Wa_t: torch.Tensor, thr: float, group_rows: int,
                         mask: torch.Tensor | None = None):
     """mask [T/group_rows, nblk] uint8 = OR over the tokens of a group of (X Wa_t^T > thr)."""
-    T, d = X.shape
-    nblk = Wa_t.shape[0]
-    assert Wa_t.shape == (nblk, d) and X.is_contiguous() and Wa_t.is_contiguous()
     if mask is None:
-        mask = torch.empty((T // group_rows, nblk), dtype=torch.uint8, device=X.device)
-    _check(_lib.lx_mlp_predict_mask(_dt(X), T, d, nblk, group_rows, _ptr(X), _ptr(Wa_t), thr,
-                                    _ptr(mask), _stream()),
-           "lx_mlp_predict_mask")
+        mask = torch.empty((X.shape[0] // group_rows, Wa_t.shape[0]), dtype=torch.uint8, device=X.device)
+    _call.predict(X, Wa_t, thr, group_rows, mask)
     return mask
 
 
@@ -350,24 +340,13 @@ def lx_sparse_attn_bwd_workspace_bytes(dt, B, Hh, S, D) -> int:
 
 def lx_sparse_ffn_fwd(X, W_up, W_down, bl: BlockList, tile_t: int, blk_n: int, Y, H_act,
                       b_up=None, b_down=None, workspace=None):
-    T, d = X.shape
-    F = W_up.shape[0]
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(_lib.lx_sparse_ffn_fwd(_dt(X), T, d, F, tile_t, blk_n, _ptr(X), _ptr(W_up), _ptr(b_up),
-                                  _ptr(W_down), _ptr(b_down), bl.ref, _ptr(Y), _ptr(H_act),
-                                  _ptr(workspace), ws_bytes, _stream()), "lx_sparse_ffn_fwd")
+    _call.ffn_fwd(X, W_up, W_down, bl.c, tile_t, blk_n, Y, H_act, b_up, b_down, workspace)
     return Y
 
 
 def lx_sparse_ffn_bwd_dx(dY, H_act, W_up, W_down, bl: BlockList, tile_t: int, blk_n: int, dX,
                          workspace, W_up_t=None, W_down_t=None):
-    T, d = dY.shape
-    F = W_up.shape[0] if W_up is not None else W_down_t.shape[0]
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(_lib.lx_sparse_ffn_bwd_dx(_dt(dY), T, d, F, tile_t, blk_n, _ptr(dY), _ptr(H_act),
-                                     _ptr(W_up), _ptr(W_down), _ptr(W_up_t), _ptr(W_down_t),
-                                     bl.ref, _ptr(dX), _ptr(workspace), ws_bytes, _stream()),
-           "lx_sparse_ffn_bwd_dx")
+    _call.ffn_bwd(dY, H_act, W_up, W_down, bl.c, tile_t, blk_n, dX, workspace, W_up_t, W_down_t)
     return dX
 
 
@@ -390,55 +369,24 @@ def lx_profile_end():
     return ms.value, n.value
 
 
-_Strides3 = _i64 * 3
-
-
-def _strides(Q: torch.Tensor, *others: torch.Tensor):
-    """The first three element strides of Q, which the other tensors share with its shape."""
-    shape, st = Q.shape, Q.stride()
-    for t in others:
-        assert t.stride() == st and t.shape == shape
-    assert len(st) == 4 and st[3] == 1
-    return _Strides3(st[0], st[1], st[2])
-
-
 def lx_sparse_attn_fwd(Q, K, V, bl: BlockList, scale: float, causal: bool, O, LSE,
                        mask_batch: int = 1, head_active=None):
-    B, Hh, S, D = Q.shape
-    strides = _strides(Q, K, V, O)
-    _check(_lib.lx_sparse_attn_fwd(_dt(Q), B, Hh, S, D, scale, int(causal), _ptr(Q), _ptr(K),
-                                   _ptr(V), strides, bl.ref, mask_batch,
-                                   _ptr(head_active), _ptr(O), _ptr(LSE), _stream()),
-           "lx_sparse_attn_fwd")
+    _call.attn_fwd(Q, K, V, bl.c, scale, int(causal), O, LSE, mask_batch, head_active)
     return O, LSE
 
 
 def lx_sparse_attn_bwd_dx(Q, K, V, O, LSE, dO, bl_rows: BlockList, bl_cols: BlockList,
                           scale: float, causal: bool, dQ, dK, dV, workspace, mask_batch: int = 1,
                           head_active=None):
-    B, Hh, S, D = Q.shape
-    strides = _strides(Q, K, V, O, dO, dQ, dK, dV)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(_lib.lx_sparse_attn_bwd_dx(_dt(Q), B, Hh, S, D, scale, int(causal), _ptr(Q), _ptr(K),
-                                      _ptr(V), _ptr(O), _ptr(LSE), _ptr(dO), strides,
-                                      bl_rows.ref, bl_cols.ref, mask_batch,
-                                      _ptr(head_active), _ptr(dQ), _ptr(dK), _ptr(dV),
-                                      _ptr(workspace), ws_bytes, _stream()),
-           "lx_sparse_attn_bwd_dx")
+    _call.attn_bwd(Q, K, V, O, LSE, dO, bl_rows.c, bl_cols.c, scale, int(causal), dQ, dK, dV, workspace, mask_batch,
+                   head_active)
     return dQ, dK, dV
 
 
 def lx_sparse_attn_bwd_dx_noalloc(Q, K, V, O, LSE, dO, bl_rows: BlockList, bl_cols: BlockList,
                                   scale: float, causal: bool, dQ, dK, dV, mask_batch: int = 1,
                                   head_active=None):
-    B, Hh, S, D = Q.shape
-    strides = _strides(Q, K, V, O, dO, dQ, dK, dV)
-    _check(_lib.lx_sparse_attn_bwd_dx_noalloc(_dt(Q), B, Hh, S, D, scale, int(causal), _ptr(Q),
-                                              _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(dO),
-                                              strides, bl_rows.ref, bl_cols.ref,
-                                              mask_batch, _ptr(head_active), _ptr(dQ), _ptr(dK),
-                                              _ptr(dV), _stream()),
-           "lx_sparse_attn_bwd_dx_noalloc")
+    _call.attn_bwd(Q, K, V, O, LSE, dO, bl_rows.c, bl_cols.c, scale, int(causal), dQ, dK, dV, mask_batch, head_active)
     return dQ, dK, dV
 
 
