@@ -336,6 +336,56 @@ __device__ __forceinline__ void mma_tr16(const TrOps16<D>& t, const f32x4 (&p)[4
   }
 }
 
+// The products of the two backward kernels issue a slot at a time: a matrix instruction, then the vector and LDS work of
+// other products that needs nothing of it, with the compiler's scheduler held off between slots.  kSlots: of a first product
+// (D / 32 slices, four row tiles), and of a second one (two slices, D / 16 column tiles).
+// The LDS operand reads bound these kernels, and the matrix and vector instructions that they hold up: with all blocks both
+// sides take 61 % of the time at D = 128 (71 % at 64) without the reads, 87 % (74 %) without the matrix instructions,
+// 93 % (88 %) without the exponentials.  Reads therefore go out a product ahead, into the registers that the operands
+// before them leave, as far as the kernel's wavefronts per SIMD leave registers; not further: a register in scratch memory
+// costs a drained ring (10 in dK/dV at D = 128: 1.2 times the time).  Both backward launches, us, product after product / in
+// slots: 4 x 32 heads of 2048 tokens, D = 128, all blocks 1007 / 987, causal 566 / 554, causal 25 % 207 / 205; 16 of 4096,
+// D = 128, causal 25 % 90.3 / 86.8; the same at D = 64 61.3 / 58.9; 2 x 40 of 2048, D = 64, causal 25 % 82.0 / 81.3.  (The
+// forward kernel by slots: no difference.)
+template <int D>
+constexpr int kSlots = D / 8;
+__device__ __forceinline__ void end_slot() { __builtin_amdgcn_sched_barrier(0); }
+// a first product's operand of slot i, from a row-major tile
+template <int D>
+__device__ __forceinline__ uint4 read_rows16(uint32_t tile, const LaneOff16<D>& lo, int i) {
+  return lds_read16(add_lds(lo.rows[i / 4], tile) + 16 * (i % 4) * 2 * D);
+}
+// a second product's, from a row-major tile
+template <int D>
+__device__ __forceinline__ uint4 read_tr16(uint32_t tile, const LaneOff16<D>& lo, int i) {
+  const int kk = i / (D / 16), ct = i % (D / 16);
+  const uint32_t a0 = add_lds(lo.tr[ct], tile);
+  const uint2 l = lds_read8_tr(a0 + (32 * kk) * 2 * D), h = lds_read8_tr(a0 + (32 * kk + 16) * 2 * D);
+  return make_uint4(l.x, l.y, h.x, h.y);
+}
+// slice kk of a second product's [64 x 16] factor, rounded to the element type
+template <int DT>
+__device__ __forceinline__ uint4 pack_slice(const f32x4 (&p)[4], int kk) {
+  return make_uint4(pack2<DT>(p[2 * kk][0], p[2 * kk][1]), pack2<DT>(p[2 * kk][2], p[2 * kk][3]),
+                    pack2<DT>(p[2 * kk + 1][0], p[2 * kk + 1][1]), pack2<DT>(p[2 * kk + 1][2], p[2 * kk + 1][3]));
+}
+// acc = R F^T as in mma_rows16; meanwhile the operands of a first product with the tile `next` are read
+template <int D, int DT>
+__device__ __forceinline__ void mma_rows16_ahead(uint32_t tile, uint32_t next, const LaneOff16<D>& lo, const uint4 (&frag)[D / 32],
+                                                 f32x4 (&acc)[4], uint4 (&ahead)[kSlots<D>]) {
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  uint4 a[kSlots<D>];
+#pragma unroll
+  for (int i = 0; i < kSlots<D>; ++i) a[i] = read_rows16<D>(tile, lo, i);
+  end_slot();
+#pragma unroll
+  for (int i = 0; i < kSlots<D>; ++i) {
+    acc[i % 4] = mfma16<DT>(a[i], frag[i / 4], i < 4 ? zero : acc[i % 4]);
+    ahead[i] = read_rows16<D>(next, lo, i);
+    end_slot();
+  }
+}
+
 // Scores in the layout of mma_rows16 with the streamed rows (16t + 4*(lane/16) + v) being KEYS
 // and the lane (own row `ql` of the block) the QUERY: keys after the query get -inf; `above`: the
 // whole block lies on the excluded side of the diagonal.  mask_diag16_t: the roles exchanged
@@ -877,21 +927,48 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   auto comp = [&](int stage, int e) {
     const int col = entry_blk(e);
     const uint32_t stg = st_addr + stage * kStage;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    constexpr int N = kSlots<D>, E = 16 / N, NC = D / 16;     // slots; score elements of a slot; column tiles
     f32x4 s[4], dp[4];
-    mma_rows16<D, DT>(stg, lo, qf, s);                   // S^T[key][q]
-    mma_rows16<D, DT>(stg + kTile, lo, dof, dp);         // dP^T[key][q]
+    uint4 vt[N], kt[N];
+    // S^T[key][q]; with room for them (at D = 64 four wavefronts share a SIMD) meanwhile V's operands
+    if constexpr (D == 64) {
+      mma_rows16<D, DT>(stg, lo, qf, s);
+#pragma unroll
+      for (int i = 0; i < N; ++i) vt[i] = read_rows16<D>(stg + kTile, lo, i);
+    } else {
+      mma_rows16_ahead<D, DT>(stg, stg + kTile, lo, qf, s, vt);
+    }
     if (a.causal && col >= qb) mask_diag16(s, ql, col > qb);   // excluded keys: P = exp2(-inf) = 0
+    // dP^T[key][q]; meanwhile P, and with room for them K's operands
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int i = 0; i < N; ++i) {
+      dp[i % 4] = mfma16<DT>(vt[i], dof[i / 4], i < 4 ? zero : dp[i % 4]);
+      if (D == 128) kt[i] = read_tr16<D>(stg, lo, i);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(s[t][v], sc, -lse2));
-        s[t][v] = p * (dp[t][v] - delta);       // dS^T
-      }
-    __builtin_amdgcn_sched_barrier(0);
-    TrOps16<D> kt;
-    load_tr16<D>(stg, lo, kt);
-    mma_tr16<D, DT>(kt, s, dq_acc);             // dQ^T += K^T dS^T
+      for (int x = E * i; x < E * (i + 1); ++x) s[x / 4][x % 4] = __builtin_amdgcn_exp2f(fmaf(s[x / 4][x % 4], sc, -lse2));
+      end_slot();
+    }
+    auto ds = [&](int x) { s[x / 4][x % 4] *= dp[x / 4][x % 4] - delta; };      // dS^T
+#pragma unroll
+    for (int x = 0; x < 8; ++x) ds(x);
+    uint4 f = pack_slice<DT>(s, 0);
+    if (D == 64) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) kt[i] = read_tr16<D>(stg, lo, i);
+    }
+    end_slot();
+    // dQ^T += K^T dS^T
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      dq_acc[i] = mfma16<DT>(kt[i], f, dq_acc[i]);
+#pragma unroll
+      for (int x = 8 + 8 / NC * i; x < 8 + 8 / NC * (i + 1); ++x) ds(x);
+      end_slot();
+    }
+    f = pack_slice<DT>(s, 1);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) dq_acc[i] = mfma16<DT>(kt[NC + i], f, dq_acc[i]);
   };
   auto row_end = [&](int) { store_acc16_asm<D, DT>(dq_acc, a.scale, a.dQ + qoff); };
   walk_table<NS, 2 * TileDma<D, WIDE>::kPerWave, TileDma<D, WIDE>::kPerWave + 1, 2 * TileDma<D, WIDE>::kPerWave, 2, D / 32>(
@@ -1007,34 +1084,51 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
       }
       lds_barrier();
     }
-    f32x4 s[4], dp[4];
-    mma_rows16<D, DT>(stg, lo, kf, s);                   // S[q][key]
-    mma_rows16<D, DT>(stg + kTile, lo, vf, dp);          // dP[q][key]
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    constexpr int N = kSlots<D>, E = 16 / N, NC = D / 16;     // slots; score elements of a slot; column tiles
+    f32x4 s[4], dp[4], stat[2];        // stat: -LSE or Delta of the row tile's queries, a tile ahead
+    uint4 ops[N], tr[N];
+    mma_rows16_ahead<D, DT>(stg, stg + kTile, lo, kf, s, ops);      // S[q][key]
     // diagonal block: here the rows of the score tile are queries and the lane is the key
     if (a.causal && col <= kb) mask_diag16_t(s, kl, col < kb);
+    auto read_stat = [&](int t, int which) { stat[t % 2] = *reinterpret_cast<const f32x4*>(&sstat[stage][t][16 * which + 4 * g]); };
+    read_stat(0, 0);
+    end_slot();
+    // dP[q][key]; meanwhile P
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      dp[i % 4] = mfma16<DT>(ops[i], vf[i / 4], i < 4 ? zero : dp[i % 4]);
+      if (E * i % 4 == 0 && i + 4 / E < N) read_stat(E * i / 4 + 1, 0);
+#pragma unroll
+      for (int x = E * i; x < E * (i + 1); ++x)
+        s[x / 4][x % 4] = __builtin_amdgcn_exp2f(fmaf(s[x / 4][x % 4], sc, stat[x / 4 % 2][x % 4]));
+      end_slot();
+    }
+    uint4 p16[2], ds16[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) p16[kk] = pack_slice<DT>(s, kk);
+    read_stat(0, 1);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const float4 nl = *reinterpret_cast<const float4*>(&sstat[stage][t][4 * g]);
-      const float4 dl = *reinterpret_cast<const float4*>(&sstat[stage][t][16 + 4 * g]);
-      const float nls[4] = {nl.x, nl.y, nl.z, nl.w}, dls[4] = {dl.x, dl.y, dl.z, dl.w};
+      if (t < 3) read_stat(t + 1, 1);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(s[t][v], sc, nls[v]));
-        s[t][v] = p;                                  // P
-        dp[t][v] = p * (dp[t][v] - dls[v]);           // dS
-      }
+      for (int v = 0; v < 4; ++v) dp[t][v] = s[t][v] * (dp[t][v] - stat[t % 2][v]);
     }
-    __builtin_amdgcn_sched_barrier(0);
-    {
-      TrOps16<D> dot;
-      load_tr16<D>(stg + kTile, lo, dot);
-      mma_tr16<D, DT>(dot, s, dv_acc);                // dV^T += dO^T P
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) ds16[kk] = pack_slice<DT>(dp, kk);
+#pragma unroll
+    for (int i = 0; i < N; ++i) tr[i] = read_tr16<D>(stg + kTile, lo, i);
+    end_slot();
+    // dV^T += dO^T P; meanwhile Q's operands
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      dv_acc[i % NC] = mfma16<DT>(tr[i], p16[i / NC], dv_acc[i % NC]);
+      ops[i] = read_tr16<D>(stg, lo, i);
+      end_slot();
     }
-    {
-      TrOps16<D> qt;
-      load_tr16<D>(stg, lo, qt);
-      mma_tr16<D, DT>(qt, dp, dk_acc);                // dK^T += Q^T dS
-    }
+    // dK^T += Q^T dS
+#pragma unroll
+    for (int i = 0; i < N; ++i) dk_acc[i % NC] = mfma16<DT>(ops[i], ds16[i / NC], dk_acc[i % NC]);
   };
   auto row_end = [&](int) {
     store_acc16_asm<D, DT>(dv_acc, 1.f, a.dV + koff);
