@@ -140,6 +140,15 @@ struct Args {
     if (!bad && len < 1) PyErr_SetString(PyExc_IndexError, "tuple index out of range"), bad = true;
     return s;
   }
+  void last_two(int i, long long& x, long long& y) {    // of a shape of two and more dimensions
+    PyObject* t = bad ? nullptr : PyObject_GetAttr(a[i], n.shape);
+    if (!t) { bad = true; return; }
+    const Py_ssize_t len = PyTuple_Check(t) ? PyTuple_GET_SIZE(t) : 0;
+    require(len >= 2);
+    if (!bad) x = number(PyTuple_GET_ITEM(t, len - 2));
+    if (!bad) y = number(PyTuple_GET_ITEM(t, len - 1));
+    Py_DECREF(t);
+  }
   void require_dtype(int i, PyObject* want) {
     if (bad) return;
     PyObject* d = PyObject_GetAttr(a[i], n.dtype);
@@ -201,18 +210,12 @@ bool count(Py_ssize_t got, Py_ssize_t want) {
 
 // A mask tensor [..., R, C], uint8, contiguous, on the GPU: {masks, R, C}.
 void mask_shape(Args& a, int i, long long (&m)[3]) {
-  long long s[16];
   a.require_dtype(i, g.uint8);
   a.require(a.is_cuda(i));
   a.require(a.is_contiguous(i));
-  const int dims = a.shape(i, s, 16);
+  a.last_two(i, m[1], m[2]);
+  const long long all = a.bad ? 0 : a.method(i, n.numel);
   if (a.bad) return;
-  a.require(dims >= 2 && dims <= 16);
-  if (a.bad) return;
-  long long all = 1;
-  for (int k = 0; k < dims; ++k) all *= s[k];
-  m[1] = s[dims - 2];
-  m[2] = s[dims - 1];
   if (m[1] * m[2] == 0) {
     PyErr_SetString(PyExc_ZeroDivisionError, "integer division or modulo by zero");
     a.bad = true;

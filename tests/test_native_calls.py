@@ -183,3 +183,19 @@ def test_errors(calls):
     with pytest.raises(AttributeError):
         lx.lx_sparse_ffn_fwd(X, W, 5, bl, 64, 64, X, X)
     assert seen == []
+
+
+def test_masks_of_many_dimensions(calls):
+    lx, seen, _ = calls
+    out, other = header(lx, 4), header(lx, 4)
+    m = GpuMask(torch.zeros([2, 3] + [1] * 14 + [5, 7], dtype=torch.uint8))
+    lx.lx_mask_compact(m, out=out)
+    lx.lx_mask_compact_pair(m, out=(out, other))
+    assert [(n, a[:7]) for n, a in seen] == [("lx_mask_compact", [p(m), 6, 5, 7, 35, 7, 1]),
+                                             ("lx_mask_compact_pair", [p(m), 6, 5, 7, 35, 7, 1])]
+    del seen[:]
+    with pytest.raises(AssertionError):                    # no row and column
+        lx.lx_mask_compact(GpuMask(torch.zeros(7, dtype=torch.uint8)), out=out)
+    with pytest.raises(ZeroDivisionError):
+        lx.lx_mask_compact(GpuMask(torch.zeros(2, 0, 7, dtype=torch.uint8)), out=out)
+    assert seen == []
