@@ -8,7 +8,9 @@
 //
 // Every argument is read when the call is made, through the same attributes and methods of the tensor that Python code would
 // use (data_ptr, shape, stride, dtype, numel); nothing about a tensor is kept.  The library's functions are handed over by
-// address (bind), so this module belongs to the library that loaded it.
+// address (bind), so this module belongs to the library that loaded it.  Numbers are converted as the C prototypes in ctypes
+// convert them: integers modulo 2^32, ctypes' own objects and what `_as_parameter_` holds through `types`' converter, and
+// everything else is its ArgumentError; last of all, after what is refused for other reasons.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -35,6 +37,10 @@ struct Bound {
   decltype(&lx_sparse_attn_bwd_dx_noalloc) attn_bwd_noalloc;
   PyObject *dtypes, *error, *stream, *uint8, *float32, *int32;     // {torch dtype: lx_dtype}, LxError, () -> raw stream, torch dtypes
 } g;
+// Set once by types.
+struct Types {
+  PyObject *list, *i32, *f32, *convert, *wrong;    // list header, c_int32, c_float, (value, type) -> number, the error of wrong types
+} ty;
 struct Names {
   PyObject *data_ptr, *shape, *stride, *dtype, *numel, *element_size, *is_cuda, *is_contiguous;
 } n;
@@ -55,16 +61,39 @@ struct Args {
       if (!PyErr_Occurred()) PyErr_SetNone(PyExc_AssertionError);
     }
   }
+  void wrong(const char* what, PyObject* o) {
+    bad = true;
+    PyErr_Format(ty.wrong, "%s expected, got %s", what, Py_TYPE(o)->tp_name);
+  }
+  // Of an integer; of anything else what `convert` makes of it.
   long long number(PyObject* o) {
-    const long long v = bad ? 0 : PyLong_AsLongLong(o);
-    if (v == -1 && PyErr_Occurred()) bad = true;
+    if (bad) return 0;
+    if (PyLong_Check(o)) return (long long)PyLong_AsUnsignedLongLongMask(o);
+    PyObject* r = PyObject_CallFunctionObjArgs(ty.convert, o, ty.i32, nullptr);
+    const long long v = r ? PyLong_AsLongLong(r) : -1;
+    Py_XDECREF(r);
+    bad |= v == -1 && PyErr_Occurred();
     return v;
   }
-  long long number(int i) { return number(a[i]); }
-  double real(int i) {
-    const double v = bad ? 0 : PyFloat_AsDouble(a[i]);
-    if (v == -1.0 && PyErr_Occurred()) bad = true;
-    return v;
+  int32_t number(int i) { return (int32_t)number(a[i]); }
+  float real(int i) {
+    if (bad) return 0;
+    if (PyFloat_Check(a[i])) return (float)PyFloat_AS_DOUBLE(a[i]);
+    PyObject* r = PyObject_CallFunctionObjArgs(ty.convert, a[i], ty.f32, nullptr);
+    const double v = r ? PyFloat_AsDouble(r) : -1.0;
+    Py_XDECREF(r);
+    bad |= v == -1.0 && PyErr_Occurred();
+    return (float)v;
+  }
+  void* address(PyObject* r) {          // of a number or None; releases it
+    if (!r) return bad = true, nullptr;
+    void* p = nullptr;
+    if (PyLong_Check(r))
+      p = reinterpret_cast<void*>((uintptr_t)PyLong_AsUnsignedLongLongMask(r));
+    else if (r != Py_None)
+      wrong("address", r);
+    Py_DECREF(r);
+    return p;
   }
   bool truth(int i) {
     const int v = bad ? 0 : PyObject_IsTrue(a[i]);
@@ -90,23 +119,19 @@ struct Args {
   bool is_contiguous(int i) { return !bad && flag(PyObject_CallMethodNoArgs(a[i], n.is_contiguous)); }
   void* ptr(int i) {          // of a tensor, or null for None
     if (bad || a[i] == Py_None) return nullptr;
-    PyObject* r = PyObject_CallMethodNoArgs(a[i], n.data_ptr);
-    if (!r) return bad = true, nullptr;
-    void* p = PyLong_AsVoidPtr(r);
-    Py_DECREF(r);
-    bad |= !p && PyErr_Occurred();
-    return p;
+    return address(PyObject_CallMethodNoArgs(a[i], n.data_ptr));
   }
   size_t bytes(int i) { return bad || a[i] == Py_None ? 0 : (size_t)(method(i, n.numel) * method(i, n.element_size)); }
   const lx_blocklist* list(int i) {       // of a ctypes structure, or null for None
     if (bad || a[i] == Py_None) return nullptr;
-    if (PyObject_GetBuffer(a[i], &header[headers], PyBUF_SIMPLE) != 0) return bad = true, nullptr;
-    const Py_buffer& b = header[headers++];
-    if (b.len < (Py_ssize_t)sizeof(lx_blocklist)) {
-      PyErr_SetString(PyExc_TypeError, "list header expected");
-      return bad = true, nullptr;
+    const int is = PyObject_IsInstance(a[i], ty.list);
+    if (is <= 0) {
+      bad = true;
+      if (is == 0) wrong("list header", a[i]);
+      return nullptr;
     }
-    return static_cast<const lx_blocklist*>(b.buf);
+    if (PyObject_GetBuffer(a[i], &header[headers], PyBUF_SIMPLE) != 0) return bad = true, nullptr;
+    return static_cast<const lx_blocklist*>(header[headers++].buf);
   }
   // The numbers of a tuple, at most `most` of them; how many it has, or -1.
   int tuple(PyObject* t, long long* out, int most) {
@@ -174,12 +199,7 @@ struct Args {
     return v ? (lx_dtype)PyLong_AsLong(v) : LX_F32;
   }
   void* stream() {
-    PyObject* r = bad ? nullptr : PyObject_CallNoArgs(g.stream);
-    if (!r) return bad = true, nullptr;
-    void* p = PyLong_AsVoidPtr(r);
-    Py_DECREF(r);
-    bad |= !p && PyErr_Occurred();
-    return p;
+    return bad ? nullptr : address(PyObject_CallNoArgs(g.stream));
   }
   static void raise(int status, PyObject* where) {
     PyObject* e = PyObject_CallFunction(g.error, "iO", status, where);
@@ -231,13 +251,14 @@ PyObject* mask_compact(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   long long m[3] = {};
   mask_shape(a, 0, m);
   const bool turned = a.truth(1);
-  const long long R = m[1], C = m[2], cap = args[2] == Py_None ? m[0] * R * C : a.number(2);
+  const long long R = m[1], C = m[2];
   const uint8_t* mask = (const uint8_t*)a.ptr(0);
   int32_t *rp = (int32_t*)a.ptr(3), *ci = (int32_t*)a.ptr(4);
   void* st = a.stream();
+  const int32_t cap = args[2] != Py_None ? a.number(2) : m[0] > 0 ? (int32_t)(m[0] * R * C) : 1;
   return finish(a, "lx_mask_compact", [&] {
     return g.mask_compact(mask, (int32_t)m[0], (int32_t)(turned ? C : R), (int32_t)(turned ? R : C), R * C, turned ? 1 : C,
-                          turned ? C : 1, rp, ci, (int32_t)(cap > 1 ? cap : 1), st);
+                          turned ? C : 1, rp, ci, cap, st);
   });
 }
 // mask, row_ptr and col_idx of the row list, those of the column list
@@ -264,11 +285,12 @@ PyObject* combine(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   a.require(a.is_cuda(4));
   a.require(a.is_contiguous(4));
   const lx_blocklist *r = a.list(0), *c = a.list(1);
-  const int32_t P = (int32_t)a.number(2), nblk = (int32_t)a.number(3), heads = (int32_t)a.method(4, n.numel), cap = (int32_t)a.number(5);
+  const int32_t heads = (int32_t)a.method(4, n.numel);
   const int32_t* hp = (const int32_t*)a.ptr(4);
   int32_t* p[4];
   for (int k = 0; k < 4; ++k) p[k] = (int32_t*)a.ptr(6 + k);
   void* st = a.stream();
+  const int32_t P = a.number(2), nblk = a.number(3), cap = a.number(5);
   return finish(a, "lx_attn_combine_patterns", [&] { return g.combine(r, c, P, nblk, hp, heads, p[0], p[1], p[2], p[3], cap, st); });
 }
 // X, Wa_t, thr, group_rows, mask
@@ -282,11 +304,11 @@ PyObject* predict(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   a.require(a.is_contiguous(0));
   a.require(a.is_contiguous(1));
   const lx_dtype dt = a.dtype(0);
-  const float thr = (float)a.real(2);
-  const int32_t group = (int32_t)a.number(3);
   const void *X = a.ptr(0), *W = a.ptr(1);
   uint8_t* mask = (uint8_t*)a.ptr(4);
   void* st = a.stream();
+  const int32_t group = a.number(3);
+  const float thr = a.real(2);
   return finish(a, "lx_mlp_predict_mask", [&] { return g.predict(dt, (int32_t)x[0], (int32_t)x[1], (int32_t)nblk, group, X, W, thr, mask, st); });
 }
 // X, W_up, W_down, header, tile_t, blk_n, Y, H_act, b_up, b_down, workspace
@@ -295,12 +317,13 @@ PyObject* ffn_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   Args a(args);
   long long x[2] = {};
   a.unpack(0, x, 2);
-  const int32_t F = (int32_t)a.first(1), tt = (int32_t)a.number(4), bn = (int32_t)a.number(5);
+  const int32_t F = (int32_t)a.first(1);
   const size_t ws_bytes = a.bytes(10);
   const lx_dtype dt = a.dtype(0);
-  const lx_blocklist* bl = a.list(3);
   const void *X = a.ptr(0), *Wu = a.ptr(1), *bu = a.ptr(8), *Wd = a.ptr(2), *bd = a.ptr(9);
   void *Y = a.ptr(6), *H = a.ptr(7), *ws = a.ptr(10), *st = a.stream();
+  const int32_t tt = a.number(4), bn = a.number(5);
+  const lx_blocklist* bl = a.list(3);
   return finish(a, "lx_sparse_ffn_fwd", [&] {
     return g.ffn_fwd(dt, (int32_t)x[0], (int32_t)x[1], F, tt, bn, X, Wu, bu, Wd, bd, bl, Y, H, ws, ws_bytes, st);
   });
@@ -311,12 +334,13 @@ PyObject* ffn_bwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   Args a(args);
   long long x[2] = {};
   a.unpack(0, x, 2);
-  const int32_t F = (int32_t)a.first(args[2] != Py_None ? 2 : 10), tt = (int32_t)a.number(5), bn = (int32_t)a.number(6);
+  const int32_t F = (int32_t)a.first(args[2] != Py_None ? 2 : 10);
   const size_t ws_bytes = a.bytes(8);
   const lx_dtype dt = a.dtype(0);
-  const lx_blocklist* bl = a.list(4);
   const void *dY = a.ptr(0), *H = a.ptr(1), *Wu = a.ptr(2), *Wd = a.ptr(3), *Wut = a.ptr(9), *Wdt = a.ptr(10);
   void *dX = a.ptr(7), *ws = a.ptr(8), *st = a.stream();
+  const int32_t tt = a.number(5), bn = a.number(6);
+  const lx_blocklist* bl = a.list(4);
   return finish(a, "lx_sparse_ffn_bwd_dx", [&] {
     return g.ffn_bwd(dt, (int32_t)x[0], (int32_t)x[1], F, tt, bn, dY, H, Wu, Wd, Wut, Wdt, bl, dX, ws, ws_bytes, st);
   });
@@ -332,10 +356,10 @@ PyObject* lora_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   a.require_shape(3, F, 64);
   a.require_shape(8, x[0], 64);
   const lx_dtype dt = a.dtype(0);
-  const lx_blocklist* bl = a.list(5);
   const size_t ws_bytes = a.bad ? 0 : (size_t)a.method(9, n.numel);
   const void *X = a.ptr(0), *Wu = a.ptr(1), *A = a.ptr(2), *B = a.ptr(3), *Wd = a.ptr(4);
   void *Y = a.ptr(6), *H = a.ptr(7), *U = a.ptr(8), *ws = a.ptr(9), *st = a.stream();
+  const lx_blocklist* bl = a.list(5);
   return finish(a, "lx_sparse_ffn_lora_fwd", [&] {
     return g.lora_fwd(dt, (int32_t)x[0], (int32_t)x[1], (int32_t)F, 64, 64, X, Wu, A, B, Wd, bl, Y, H, U, ws, ws_bytes, st);
   });
@@ -354,12 +378,11 @@ PyObject* lora_bwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   a.require_shape(4, x[1], F);
   a.require_shape(5, F, x[1]);
   const lx_dtype dt = a.dtype(0);
-  const lx_blocklist* bl = a.list(8);
   const size_t ws_bytes = a.bad ? 0 : (size_t)a.method(12, n.numel);
   const void *X = a.ptr(0), *dY = a.ptr(1), *H = a.ptr(2), *U = a.ptr(3), *Wut = a.ptr(4), *Wdt = a.ptr(5), *A = a.ptr(6), *B = a.ptr(7);
-  void *dX = a.ptr(9), *ws = a.ptr(12), *st = nullptr;
   float *dA = (float*)a.ptr(10), *dB = (float*)a.ptr(11);
-  st = a.stream();
+  void *dX = a.ptr(9), *ws = a.ptr(12), *st = a.stream();
+  const lx_blocklist* bl = a.list(8);
   return finish(a, "lx_sparse_ffn_lora_bwd", [&] {
     return g.lora_bwd(dt, (int32_t)x[0], (int32_t)x[1], (int32_t)F, 64, 64, X, dY, H, U, Wut, Wdt, A, B, bl, dX, dA, dB, ws, ws_bytes, st);
   });
@@ -403,14 +426,14 @@ PyObject* attn_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   const int others[] = {1, 2, 6};
   attn_shape(a, others, 3, q, st3);
   const lx_dtype dt = a.dtype(0);
-  const float scale = (float)a.real(4);
-  const int32_t causal = (int32_t)a.number(5), mb = (int32_t)a.number(8);
-  const lx_blocklist* bl = a.list(3);
   const void *Q = a.ptr(0), *K = a.ptr(1), *V = a.ptr(2);
   const uint8_t* act = (const uint8_t*)a.ptr(9);
   void* O = a.ptr(6);
   float* LSE = (float*)a.ptr(7);
   void* st = a.stream();
+  const float scale = a.real(4);
+  const int32_t causal = a.number(5), mb = a.number(8);
+  const lx_blocklist* bl = a.list(3);
   return finish(a, "lx_sparse_attn_fwd", [&] {
     return g.attn_fwd(dt, (int32_t)q[0], (int32_t)q[1], (int32_t)q[2], (int32_t)q[3], scale, causal, Q, K, V, st3, bl, mb, act, O, LSE, st);
   });
@@ -428,13 +451,13 @@ PyObject* attn_bwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   attn_shape(a, others, 7, q, st3);
   const size_t ws_bytes = scratch ? a.bytes(13) : 0;
   const lx_dtype dt = a.dtype(0);
-  const float scale = (float)a.real(8);
-  const int32_t causal = (int32_t)a.number(9), mb = (int32_t)a.number(after);
-  const lx_blocklist *rows = a.list(6), *cols = a.list(7);
   const void *Q = a.ptr(0), *K = a.ptr(1), *V = a.ptr(2), *O = a.ptr(3), *dO = a.ptr(5);
   const float* LSE = (const float*)a.ptr(4);
   const uint8_t* act = (const uint8_t*)a.ptr(after + 1);
   void *dQ = a.ptr(10), *dK = a.ptr(11), *dV = a.ptr(12), *ws = scratch ? a.ptr(13) : nullptr, *st = a.stream();
+  const float scale = a.real(8);
+  const int32_t causal = a.number(9), mb = a.number(after);
+  const lx_blocklist *rows = a.list(6), *cols = a.list(7);
   const int32_t B = (int32_t)q[0], H = (int32_t)q[1], S = (int32_t)q[2], D = (int32_t)q[3];
   return finish(a, scratch ? "lx_sparse_attn_bwd_dx" : "lx_sparse_attn_bwd_dx_noalloc", [&] {
     return scratch ? g.attn_bwd(dt, B, H, S, D, scale, causal, Q, K, V, O, LSE, dO, st3, rows, cols, mb, act, dQ, dK, dV, ws, ws_bytes, st)
@@ -476,8 +499,20 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   Py_RETURN_NONE;
 }
 
+// lx_blocklist, c_int32, c_float, converter, error of wrong types
+PyObject* types(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+  if (!count(nargs, 5)) return nullptr;
+  PyObject** to[] = {&ty.list, &ty.i32, &ty.f32, &ty.convert, &ty.wrong};
+  for (int k = 0; k < 5; ++k) {
+    Py_INCREF(args[k]);
+    Py_XDECREF(*to[k]);
+    *to[k] = args[k];
+  }
+  Py_RETURN_NONE;
+}
+
 #define LX_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {LX_METHOD(bind), LX_METHOD(mask_compact), LX_METHOD(mask_compact_pair), LX_METHOD(combine), LX_METHOD(predict),
+PyMethodDef methods[] = {LX_METHOD(bind), LX_METHOD(types), LX_METHOD(mask_compact), LX_METHOD(mask_compact_pair), LX_METHOD(combine), LX_METHOD(predict),
                          LX_METHOD(ffn_fwd), LX_METHOD(ffn_bwd), LX_METHOD(lora_fwd), LX_METHOD(lora_bwd), LX_METHOD(attn_fwd),
                          LX_METHOD(attn_bwd), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_lx_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -151,6 +151,22 @@ def _dt(t: torch.Tensor) -> int:
     return dt
 
 
+class _ArgumentError(C.ArgumentError, TypeError):
+    """An argument of a type that the C prototype does not take."""
+
+
+def _convert(value, kind):
+    """What a prototype with an argument of `kind` makes of a value that is no plain number."""
+    if isinstance(value, kind):
+        return value.value
+    try:
+        return kind(value).value
+    except Exception:
+        if hasattr(value, "_as_parameter_"):
+            return _convert(value._as_parameter_, kind)
+        raise _ArgumentError(f"{kind.__name__} expected, got {type(value).__name__}") from None
+
+
 def _load_calls():
     """csrc/lx_call.cpp, bound to this module's library.  By path: it is this tree's."""
     loader = importlib.machinery.ExtensionFileLoader("_lx_call", CALL_PATH)
@@ -158,6 +174,7 @@ def _load_calls():
     loader.exec_module(m)
     m.bind({n: C.cast(getattr(_lib, n), _vp).value for n in EXPORTS}, _DTYPES, LxError, _stream,
            torch.uint8, torch.float32, torch.int32)
+    m.types(lx_blocklist, _i32, _f, _convert, _ArgumentError)
     return m
 
 
@@ -187,7 +204,7 @@ def lx_mask_compact(mask: torch.Tensor, transpose: bool = False, nnz_cap: int | 
         row_ptr = torch.empty(total + 1, dtype=torch.int32, device=mask.device)
         col_idx = torch.empty(max(cap, 1), dtype=torch.int32, device=mask.device)
         out = BlockList(total, cols, row_ptr, col_idx, cap)
-    _call.mask_compact(mask, transpose, nnz_cap, out.row_ptr, out.col_idx)
+    _call.mask_compact(mask, transpose, None if nnz_cap is None else max(nnz_cap, 1), out.row_ptr, out.col_idx)
     return out
 
 

@@ -199,3 +199,48 @@ def test_masks_of_many_dimensions(calls):
     with pytest.raises(ZeroDivisionError):
         lx.lx_mask_compact(GpuMask(torch.zeros(2, 0, 7, dtype=torch.uint8)), out=out)
     assert seen == []
+
+
+class Held:
+    def __init__(self, v):
+        self._as_parameter_ = v
+
+
+@pytest.mark.parametrize("sixteen", [16, 2 ** 70 + 16, C.c_int32(16), Held(16), Held(C.c_int32(16)), torch.tensor(16)])
+def test_numbers_convert_as_in_the_prototype(calls, sixteen):
+    lx, seen, _ = calls
+    X, bl = bf(64, 64), header(lx, 1)
+    Q, LSE = torch.zeros(1, 2, 64, 64), torch.zeros(1, 2, 64)
+    lx.lx_sparse_ffn_fwd(X, X, X, bl, sixteen, 64, X, X)
+    lx.lx_sparse_attn_fwd(Q, Q, Q, bl, 0.25, False, Q, LSE, mask_batch=sixteen)
+    assert seen[0][1][4] == 16 and seen[1][1][12] == 16
+    assert C.CFUNCTYPE(C.c_int, C.c_int32)(lambda v: v)(sixteen) == 16      # (ctypes itself)
+
+
+@pytest.mark.parametrize("quarter,value", [(0.25, 0.25), (C.c_float(0.25), 0.25), (Held(0.25), 0.25), (1, 1.0), (torch.tensor(0.25), 0.25),
+                                           (1e300, float("inf"))])
+def test_reals_convert_as_in_the_prototype(calls, quarter, value):
+    lx, seen, _ = calls
+    Q, LSE, bl = torch.zeros(1, 2, 64, 64), torch.zeros(1, 2, 64), header(lx, 1)
+    lx.lx_sparse_attn_fwd(Q, Q, Q, bl, quarter, False, Q, LSE)
+    lx.lx_mlp_predict_mask(bf(64, 64), bf(64, 64), quarter, 64, mask=LSE)
+    assert seen[0][1][5] == value and seen[1][1][7] == value
+
+
+def test_wrong_types_are_ctypes_errors(calls):
+    lx, seen, _ = calls
+    X, bl = bf(64, 64), header(lx, 1)
+    Q, LSE = torch.zeros(1, 2, 64, 64), torch.zeros(1, 2, 64)
+    for wrong in (64.0, None, "64", C.c_int64(64), Held(64.0)):
+        with pytest.raises(C.ArgumentError):
+            lx.lx_sparse_ffn_fwd(X, X, X, bl, wrong, 64, X, X)
+    for wrong in (None, "1", C.c_double(1.0), 10 ** 400):
+        with pytest.raises(C.ArgumentError):
+            lx.lx_sparse_attn_fwd(Q, Q, Q, bl, wrong, False, Q, LSE)
+    other = header(lx, 1)
+    other.c = lx.lx_compact_job()                          # a structure, of another type
+    with pytest.raises(C.ArgumentError):
+        lx.lx_sparse_ffn_fwd(X, X, X, other, 64, 64, X, X)
+    with pytest.raises(lx.LxError):                        # an unsupported dtype comes first
+        lx.lx_sparse_ffn_fwd(X.double(), X, X, bl, 64.0, 64, X, X)
+    assert seen == []
