@@ -1,6 +1,7 @@
-"""Build in-tree: the HIP library liblx_sparse.so (gfx950) and the native part of its Python binding, _lx_call.so."""
+"""Build in-tree: the HIP library liblx_sparse.so (gfx950) and the native part of its Python binding, _lx_call.<ABI tag>.so."""
 from __future__ import annotations
 
+import importlib.machinery
 import os
 import subprocess
 import sys
@@ -9,7 +10,8 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblx_sparse.so")
-CALL = os.path.join(HERE, "_lx_call.so")
+# The tag of this interpreter is part of the name: another one, whose objects are laid out otherwise, finds no file.
+CALL = os.path.join(HERE, "_lx_call" + importlib.machinery.EXTENSION_SUFFIXES[0])
 SOURCES = ["lx_api.hip", "compact.hip", "ffn_f32.hip", "ffn_bf16.hip", "predict_bf16.hip", "lora_bf16.hip",
            "attn_bf16.hip", "attn_f32.hip", "probe.hip"]
 # -Wno-inline-asm: the DMA helpers name m0 (a register the compiler reserves) as clobbered, which

@@ -19,7 +19,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblx_sparse.so")
 
-CALL_PATH = os.path.join(_HERE, "_lx_call.so")
+CALL_PATH = os.path.join(_HERE, "_lx_call" + importlib.machinery.EXTENSION_SUFFIXES[0])      # built for this interpreter
 
 for _path in (LIB_PATH, CALL_PATH):
     if not os.path.exists(_path):

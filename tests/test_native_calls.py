@@ -1,6 +1,8 @@
 """The native part of the binding (csrc/lx_call.cpp), without a GPU: what reaches the C functions, recorded by functions bound in
 their place, and what is refused before them.  CPU tensors serve: only their attributes are read."""
 import ctypes as C
+import os
+import sysconfig
 
 import pytest
 import torch
@@ -244,3 +246,10 @@ def test_wrong_types_are_ctypes_errors(calls):
     with pytest.raises(lx.LxError):                        # an unsupported dtype comes first
         lx.lx_sparse_ffn_fwd(X.double(), X, X, bl, 64.0, 64, X, X)
     assert seen == []
+
+
+def test_the_module_is_of_this_interpreter():
+    from paper_2510_15964_amd import build, lx
+    assert build.CALL == lx.CALL_PATH == lx._call.__file__
+    assert os.path.basename(build.CALL) == "_lx_call" + sysconfig.get_config_var("EXT_SUFFIX")
+    assert sysconfig.get_config_var("SOABI") in build.CALL
