@@ -715,9 +715,8 @@ def main():
         raise SystemExit("bench.py: this build is single-GPU; run with --gpus 1 "
                          "(token tiles and (batch, head) pairs are independent: the path "
                          "shards without communication)")
-    if not os.path.exists(os.path.join(ROOT, "paper_2510_15964_amd", "liblx_sparse.so")):
-        import __graft_entry__
-        __graft_entry__.build()
+    from paper_2510_15964_amd import build as lib_build
+    lib_build.ensure()
     from oracle import build as oracle_build
     oracle_build.build(force=False)
     peaks = None

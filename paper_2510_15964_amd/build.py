@@ -43,5 +43,11 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def ensure() -> None:
+    """Builds if any of what the package loads is not there."""
+    if not (os.path.exists(LIB) and os.path.exists(CALL)):
+        build()
+
+
 if __name__ == "__main__":
     print(build(verbose="-v" in sys.argv))

@@ -8,6 +8,8 @@ sys.path.insert(0, ROOT)
 
 def test_backward_in_one_launch_is_counted_once():
     import bench
+    from paper_2510_15964_amd import build
+    build.ensure()
     from paper_2510_15964_amd import lx
     dq, dkv, fwd = lx.LX_K_ATTN_BWD_DQ, lx.LX_K_ATTN_BWD_DKV, lx.LX_K_ATTN_FWD
     model = {fwd: (1, 2.0, 4.0), dq: (1, 3.0, 62.0), dkv: (1, 4.0, 62.0)}

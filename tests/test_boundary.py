@@ -12,10 +12,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 @pytest.fixture(scope="module")
 def lxmod():
-    lib = os.path.join(ROOT, "paper_2510_15964_amd", "liblx_sparse.so")
-    if not os.path.exists(lib):
-        from paper_2510_15964_amd import build
-        build.build()
+    from paper_2510_15964_amd import build
+    build.ensure()
     from paper_2510_15964_amd import lx
     return lx
 

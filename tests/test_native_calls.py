@@ -16,6 +16,8 @@ STREAM = 0x7A0
 @pytest.fixture
 def calls():
     """(module, list of (name, arguments) of the calls made, status to return)."""
+    from paper_2510_15964_amd import build
+    build.ensure()
     from paper_2510_15964_amd import lx
     seen, status, keep, addr = [], [0], [], {}
     for n in NAMES:
@@ -249,7 +251,22 @@ def test_wrong_types_are_ctypes_errors(calls):
 
 
 def test_the_module_is_of_this_interpreter():
-    from paper_2510_15964_amd import build, lx
+    from paper_2510_15964_amd import build
+    build.ensure()
+    from paper_2510_15964_amd import lx
     assert build.CALL == lx.CALL_PATH == lx._call.__file__
     assert os.path.basename(build.CALL) == "_lx_call" + sysconfig.get_config_var("EXT_SUFFIX")
     assert sysconfig.get_config_var("SOABI") in build.CALL
+
+
+@pytest.mark.parametrize("there", [(), ("LIB",), ("CALL",), ("LIB", "CALL")])
+def test_built_unless_both_files_are_there(monkeypatch, tmp_path, there):
+    from paper_2510_15964_amd import build
+    built = []
+    monkeypatch.setattr(build, "build", lambda: built.append(1))
+    for f in ("LIB", "CALL"):
+        monkeypatch.setattr(build, f, str(tmp_path / f))
+        if f in there:
+            (tmp_path / f).touch()
+    build.ensure()
+    assert len(built) == (0 if len(there) == 2 else 1)

@@ -11,6 +11,8 @@ from paper_2510_15964_amd import inputs
 
 
 def _lx():
+    from paper_2510_15964_amd import build
+    build.ensure()
     from paper_2510_15964_amd import lx
     return lx
 
