@@ -555,6 +555,7 @@ __device__ __forceinline__ void dsd_tile(const DsdArgs& a, uint16_t* ring, GridI
   typename Tl::Acc acc[Tl::NI][Tl::TI];
   zero_acc<Tl>(acc);
   run_tile<Tl, DT>(n_i + (LORA ? 1 : 0), lds_addr(ring), wm, wn, src, acc);
+  // (the lists of tiles of 32-row accumulators are never cut, which launch_dsd sees to)
   if constexpr (Tl::MF == 16)
     if (slot >= 0) {   // the piece's partial sums: [wave][accumulator][lane][4 registers]
       f32x4* dst = reinterpret_cast<f32x4*>(a.part) + ((size_t)slot * Tl::kWaves + wave) * (Tl::NI * Tl::TI) * kWave + threadIdx.x % kWave;
@@ -605,6 +606,7 @@ __global__ __launch_bounds__(512, 2) void ffn_dsd_mix(DsdArgs a) {
 // four accumulators that hold quadrant (w % 2, w / 2) of the block.
 template <class Tl, int DT>
 __global__ __launch_bounds__(256) void ffn_dsd_reduce(DsdArgs a) {
+  static_assert(Tl::MF == 16, "partial sums are stored per 16 x 16 accumulator");
   __shared__ __attribute__((aligned(1024))) uint16_t block[64 * 64];
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
   const int t = blockIdx.y / Tl::TN, e = blockIdx.y % Tl::TN, nh = w % 2, th = w / 2;
@@ -902,6 +904,7 @@ static void launch_dsd(DsdArgs a, size_t part_bytes, hipStream_t st) {
 #undef LX_CALL
 #define LX_CALL(TL) \
   hipLaunchKernelGGL((ffn_dsd_reduce<TL, DT>), dim3(p.rest, TL::TM * TL::TN), dim3(256), 0, st, a)
+  static_assert(kLastCut == kT22, "the tiles whose lists may be cut are those that are reduced here");
   if (p.rest > 0) {
     if (p.id == kT44)
       LX_CALL(Tile44);

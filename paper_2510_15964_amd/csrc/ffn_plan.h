@@ -226,6 +226,7 @@ inline int sdd_mix_grid(int Tt, int n) { return 8 * (sdd_mix(Tt, n).whole + kCUs
 // Its steps are the list entries.  With one list row and room for partial sums
 // the units that do not fill a round may have their list cut into 2 - 4 pieces, each at least 8 entries
 // long, which costs a second launch and the pieces' way through memory.
+constexpr int kLastCut = kT22;     // the tiles whose lists may be cut: the wide ones up to this (a cut launch of narrow tiles never paid)
 struct DsdPlan {
   int id, full, rest, pieces;
   size_t part_bytes() const {
@@ -250,7 +251,7 @@ inline DsdPlan choose_dsd(int Tt, int gt, int d, int nnz_cap, size_t part_bytes,
     }
     const float c = tile_cost(t, t.resident, items, (float)nnz_cap);
     if (best.id < 0 || c < least) best = {id, items, 0, 1}, least = c;
-    if (id > kT22) continue;              // (a cut launch of narrow tiles never paid)
+    if (id > kLastCut) continue;
     for (int p = 2; p <= 4 && nnz_cap >= 8 * p; ++p) {
       const int full = items / (kCUs * t.resident) * (kCUs * t.resident);
       const DsdPlan plan = {id, full, items - full, p};
