@@ -9,6 +9,7 @@
 // there is one barrier per 2048 bytes and no count or scan per row.  Masks of other strides go row by row: a
 // wavefront owns a row at a time, a 64-wide ballot gives the row's bit pattern, popcount its total and
 // mbcnt the rank of every set lane, so columns come out ascending.
+#include "compact_plan.h"
 #include "lx_dev.h"
 #include "lx_launch.h"
 
@@ -16,57 +17,8 @@ namespace lx {
 
 constexpr int kCompactThreads = 512;
 constexpr int kCompactWaves = kCompactThreads / kWave;
-constexpr int kChunkRows = 4096;    // rows scanned per pass (8 per thread)
 constexpr int kRowsPer = kChunkRows / kCompactThreads;
-constexpr int kStageBytes = 32768;  // mask bytes staged in LDS per pass
 
-// How the bytes of a job lie: the rows of all masks one after the other, or every mask contiguous in
-// the other orientation (the column list of contiguous masks), or anything else.
-enum MaskLayout { kRowMajor, kColMajor, kStrided };
-inline MaskLayout mask_layout(const CompactJob& j) {
-  const bool whole = j.batch == 1 || j.bstride == (long long)j.rows * j.cols;
-  if (whole && j.cstride == 1 && j.rstride == j.cols) return kRowMajor;
-  if (whole && j.rstride == 1 && j.cstride == j.rows) return kColMajor;
-  return kStrided;
-}
-// Workgroups (blockIdx.x = job, blockIdx.y = part of the job's rows): a launch builds one list,
-// the row list and the column list of the same masks, or the lists of several independent masks
-// side by side.  A large mask is divided by rows; a workgroup that does not start at row 0 first
-// counts the active entries of all rows before its own (a plain count over bytes it would otherwise
-// wait for another workgroup to scan), so the parts need no communication.  Where several masks that
-// fit the stage lie one after the other, the parts are whole masks: what precedes a part is then one
-// range of bytes, and the part another, in either orientation (16 bytes per load for both).  A part
-// is about 1 KB: 32 heads of 32 x 32 in 32 parts per list take 13 us in eight parts of bytes loaded
-// one by one for the column list, 7 so.  Strided bytes are slow to count, so those parts are larger.
-enum CompactBy { kFlat, kTurned, kByRow };
-struct CompactParts {
-  int parts, rows;      // rows per part
-  int chunk;            // rows per pass (kTurned, kByRow)
-  int by, layout;       // CompactBy, MaskLayout
-};
-inline CompactParts compact_parts(const CompactJob& j) {
-  const long long total = (long long)j.batch * j.rows, bytes = total * j.cols;
-  const MaskLayout lay = mask_layout(j);
-  const bool masks = lay != kStrided && j.batch > 1 && j.rows <= kChunkRows && (long long)j.rows * j.cols <= kStageBytes;
-  const int unit = masks ? j.rows : 1;
-  const bool fast = masks || lay == kRowMajor;
-  const long long units = total / unit;
-  long long p = (bytes + (fast ? 1023 : 4095)) / (fast ? 1024 : 4096);
-  p = p > (fast ? 64 : 16) ? (fast ? 64 : 16) : p;
-  p = p > units ? units : p < 1 ? 1 : p;
-  const long long per = (units + p - 1) / p;
-  CompactParts c = {(int)((units + per - 1) / per), (int)per * unit, 1, kByRow, lay};
-  if (lay == kRowMajor && bytes < 1ll << 30) {
-    c.by = kFlat;
-  } else if (lay == kColMajor && j.rows <= kChunkRows && (long long)j.rows * j.cols <= kStageBytes && c.rows % j.rows == 0) {
-    c.by = kTurned;
-    c.chunk = kStageBytes / (j.rows * j.cols) * j.rows;
-  } else if (j.cols <= kStageBytes) {
-    const int fit = kStageBytes / j.cols;
-    c.chunk = fit < 1 ? 1 : fit < kChunkRows ? fit : kChunkRows;
-  }
-  return c;
-}
 constexpr int kMaxJobs = 8;
 // The parts are the host's to compute: some dozen divisions, half of them of 64 bits, took a workgroup as long as a load.
 struct CompactJobs {
@@ -294,8 +246,8 @@ __device__ __forceinline__ void compact_rows(const CompactJob& job, int layout, 
   if (row_lo > 0) {      // active entries of the rows before this part
     const long long before = (long long)row_lo * cols;
     int cnt = 0;
-    // Whole masks before the part that are contiguous in one orientation or the other are counted 16 bytes per load, the
-    // rest byte by byte below.
+    // Whole masks before the part that are contiguous in one orientation or the other (kRowMajor: rows of 2^30 bytes and more) are
+    // counted 16 bytes per load, the rest byte by byte below.
     const long long done = layout == kRowMajor ? before : layout == kColMajor ? (long long)(row_lo / rows) * rows * cols : 0;
     if (done > 0) cnt += count_bytes(mask, done);
     constexpr int kBatch = 8;

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "compact_plan.h"
 #include "lx_chip.h"
 
 namespace lx {
@@ -46,15 +47,6 @@ struct AttnArgs {
 
 hipError_t launch_compact(const uint8_t*, int, int, int, long long, long long, long long, int*, int*,
                           int, hipStream_t);
-// One compaction job: `batch` masks of rows x cols bytes -> one list (see lx_mask_compact).
-struct CompactJob {
-  const uint8_t* mask;
-  int batch, rows, cols;
-  long long bstride, rstride, cstride;
-  int* row_ptr;
-  int* col_idx;
-  int cap;
-};
 hipError_t launch_compact_jobs(const CompactJob* jobs, int n, hipStream_t stream);
 // One list built by the pattern combination: pool layout in, per-head layout out.
 struct CombineList {

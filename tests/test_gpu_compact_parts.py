@@ -40,3 +40,31 @@ def test_contiguous_bytes_four_a_lane(lx, oracle, shape, offset, transpose):  # 
     mask = (rng.random(shape) < 0.6).astype(np.uint8)
     mask[mask > 0] = rng.integers(1, 256, size=int(mask.sum()), dtype=np.uint8)
     _check(lx, oracle, mask, transpose, offset)
+
+
+def test_the_longest_row_of_a_part(lx):  # noqa: F811
+    """2^30 - 1 bytes from an odd address, a few of them active: the first ones, the last ones, and where a byte's number in the
+    part passes 2^22 (rows by division) and the last step begins."""
+    import torch
+    n = 2 ** 30 - 1
+    buf = torch.zeros(n + 1, dtype=torch.uint8, device="cuda")
+    at = sorted({0, 1, 2, 3, 2 ** 22 - 1, 2 ** 22, n - 2049, n - 2048} | set(range(n - 5, n)))
+    buf[1:][torch.tensor(at, device="cuda")] = 7
+    bl = lx.lx_mask_compact(buf[1:].view(1, n), nnz_cap=64)
+    assert bl.row_ptr.tolist() == [0, len(at)]
+    assert bl.col_idx[:len(at)].tolist() == at
+
+
+@pytest.mark.parametrize("shape", [((1 << 18) + 3, 4097), (70000, 127, 127)])
+def test_masks_beyond_2_to_30_bytes(lx, shape):  # noqa: F811
+    import torch
+    rng = np.random.default_rng(shape[0])
+    n = int(np.prod(shape))
+    flat = np.unique(np.concatenate([rng.integers(0, n, 5000), [0, n - 1]]))
+    mask = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    mask[torch.from_numpy(flat).cuda()] = 1
+    bl = lx.lx_mask_compact(mask.view(shape), nnz_cap=6000)
+    rows = n // shape[-1]
+    rp = np.searchsorted(flat, np.arange(rows + 1, dtype=np.int64) * shape[-1])
+    assert np.array_equal(bl.row_ptr.cpu().numpy(), rp)
+    assert np.array_equal(bl.col_idx[:len(flat)].cpu().numpy(), flat % shape[-1])
