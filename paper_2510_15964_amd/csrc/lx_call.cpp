@@ -165,14 +165,16 @@ struct Args {
     if (!bad && len < 1) PyErr_SetString(PyExc_IndexError, "tuple index out of range"), bad = true;
     return s;
   }
-  void last_two(int i, long long& x, long long& y) {    // of a shape of two and more dimensions
+  // The last two sizes of a shape of two and more dimensions, and the product of all.
+  long long sizes(int i, long long& x, long long& y) {
     PyObject* t = bad ? nullptr : PyObject_GetAttr(a[i], n.shape);
-    if (!t) { bad = true; return; }
+    if (!t) return bad = true, 0;
     const Py_ssize_t len = PyTuple_Check(t) ? PyTuple_GET_SIZE(t) : 0;
     require(len >= 2);
-    if (!bad) x = number(PyTuple_GET_ITEM(t, len - 2));
-    if (!bad) y = number(PyTuple_GET_ITEM(t, len - 1));
+    long long all = 1;
+    for (Py_ssize_t k = 0; k < len && !bad; ++k) x = y, y = number(PyTuple_GET_ITEM(t, k)), all *= y;
     Py_DECREF(t);
+    return all;
   }
   void require_dtype(int i, PyObject* want) {
     if (bad) return;
@@ -233,8 +235,7 @@ void mask_shape(Args& a, int i, long long (&m)[3]) {
   a.require_dtype(i, g.uint8);
   a.require(a.is_cuda(i));
   a.require(a.is_contiguous(i));
-  a.last_two(i, m[1], m[2]);
-  const long long all = a.bad ? 0 : a.method(i, n.numel);
+  const long long all = a.sizes(i, m[1], m[2]);
   if (a.bad) return;
   if (m[1] * m[2] == 0) {
     PyErr_SetString(PyExc_ZeroDivisionError, "integer division or modulo by zero");
