@@ -337,7 +337,7 @@ __device__ __forceinline__ void mma_tr16(const TrOps16<D>& t, const f32x4 (&p)[4
 }
 
 // The products of the two backward kernels issue a slot at a time: a matrix instruction, then the vector and LDS work of
-// other products that needs nothing of it, with the compiler's scheduler held off between slots.  kSlots: of a first product
+// other products that needs nothing of it, with the compiler's scheduler held off between slots.  kMmaSlots: of a first product
 // (D / 32 slices, four row tiles), and of a second one (two slices, D / 16 column tiles).
 // The LDS operand reads bound these kernels, and the matrix and vector instructions that they hold up: with all blocks both
 // sides take 61 % of the time at D = 128 (71 % at 64) without the reads, 87 % (74 %) without the matrix instructions,
@@ -348,7 +348,7 @@ __device__ __forceinline__ void mma_tr16(const TrOps16<D>& t, const f32x4 (&p)[4
 // D = 128, causal 25 % 90.3 / 86.8; the same at D = 64 61.3 / 58.9; 2 x 40 of 2048, D = 64, causal 25 % 82.0 / 81.3.  (The
 // forward kernel by slots: no difference.)
 template <int D>
-constexpr int kSlots = D / 8;
+constexpr int kMmaSlots = D / 8;
 __device__ __forceinline__ void end_slot() { __builtin_amdgcn_sched_barrier(0); }
 // a first product's operand of slot i, from a row-major tile
 template <int D>
@@ -372,14 +372,14 @@ __device__ __forceinline__ uint4 pack_slice(const f32x4 (&p)[4], int kk) {
 // acc = R F^T as in mma_rows16; meanwhile the operands of a first product with the tile `next` are read
 template <int D, int DT>
 __device__ __forceinline__ void mma_rows16_ahead(uint32_t tile, uint32_t next, const LaneOff16<D>& lo, const uint4 (&frag)[D / 32],
-                                                 f32x4 (&acc)[4], uint4 (&ahead)[kSlots<D>]) {
+                                                 f32x4 (&acc)[4], uint4 (&ahead)[kMmaSlots<D>]) {
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  uint4 a[kSlots<D>];
+  uint4 a[kMmaSlots<D>];
 #pragma unroll
-  for (int i = 0; i < kSlots<D>; ++i) a[i] = read_rows16<D>(tile, lo, i);
+  for (int i = 0; i < kMmaSlots<D>; ++i) a[i] = read_rows16<D>(tile, lo, i);
   end_slot();
 #pragma unroll
-  for (int i = 0; i < kSlots<D>; ++i) {
+  for (int i = 0; i < kMmaSlots<D>; ++i) {
     acc[i % 4] = mfma16<DT>(a[i], frag[i / 4], i < 4 ? zero : acc[i % 4]);
     ahead[i] = read_rows16<D>(next, lo, i);
     end_slot();
@@ -928,7 +928,7 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
     const int col = entry_blk(e);
     const uint32_t stg = st_addr + stage * kStage;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    constexpr int N = kSlots<D>, E = 16 / N, NC = D / 16;     // slots; score elements of a slot; column tiles
+    constexpr int N = kMmaSlots<D>, E = 16 / N, NC = D / 16;     // slots; score elements of a slot; column tiles
     f32x4 s[4], dp[4];
     uint4 vt[N], kt[N];
     // S^T[key][q]; with room for them (at D = 64 four wavefronts share a SIMD) meanwhile V's operands
@@ -1085,7 +1085,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
       lds_barrier();
     }
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    constexpr int N = kSlots<D>, E = 16 / N, NC = D / 16;     // slots; score elements of a slot; column tiles
+    constexpr int N = kMmaSlots<D>, E = 16 / N, NC = D / 16;     // slots; score elements of a slot; column tiles
     f32x4 s[4], dp[4], stat[2];        // stat: -LSE or Delta of the row tile's queries, a tile ahead
     uint4 ops[N], tr[N];
     mma_rows16_ahead<D, DT>(stg, stg + kTile, lo, kf, s, ops);      // S[q][key]

@@ -119,7 +119,8 @@ struct CompactLds {
 // and a dependent instruction some 2 ns: bytes in registers, four ballots for their ranks and one barrier, where rows were
 // staged in LDS, counted, scanned by shuffles and scattered, with five barriers.  us, before and now: one row of 48 bytes 4.1 -> 2.6,
 // 64 x 128 bytes 6.2 -> 3.8, the three lists of a layer (128 x 128; 32 heads of 16 x 16, both orientations) 6.7 -> 4.0, both lists
-// of 12 heads of 5 x 5 4.4 -> 3.1; 405 launches of other shapes, alignments and densities 1.02 - 2.6 times as fast, 1.59 in the mean.
+// of 12 heads of 5 x 5 4.4 -> 3.1, 4096 x 8000 1212 -> 697; 114 launches of 48 bytes to 1.2 GB, both orientations, 1.01 - 17.6 times as fast,
+// 1.55 in the mean (profiles/compact_sweep.txt: launches back to back, which take 4.3 us at least).
 // (Of 16 bytes a lane the scattered stores would touch four times the lines.)  TURNED: in the other orientation, whole masks, which go
 // through `stage`.
 template <bool TURNED>

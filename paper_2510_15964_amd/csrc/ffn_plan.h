@@ -21,10 +21,11 @@ namespace lx {
 enum TileId { kT44, kT24, kT22, kT22Deep, kT14, kT14Deep, kT12, kT11, kT11Many, kTiles };
 // What a launch of a tile costs, in us: `round` per round of workgroups (finding the item, filling the
 // ring, epilogue) and step[q - 1] per step with q workgroups on a CU.  Fitted to measured launches (64 - 8192 tokens,
-// d 576 - 5120, 6 - 320 listed blocks, lists shared and per tile).  Checked at 26 shapes, every tile of both products
-// (profiles/ffn_tile_sweep.txt): model to measured 0.99 in the geometric mean, rms 17 %, and the tile that is taken is
-// 2 % slower than the fastest one on average, 15 % at worst (second product, 4096 tokens, d = 2048, one list of 14
-// blocks: 25 us by 2 x 4 tiles, 22 by 2 x 2).
+// d 576 - 5120, 6 - 320 listed blocks, lists shared and per tile) of the kernels on the 32x32x16 matrix instruction, before
+// the 16x16x32 one.  Checked with the present ones at 26 shapes, every tile of both products (profiles/ffn_tile_sweep.txt):
+// model to measured 1.01 in the geometric mean, rms 19 %, and the tile that is taken is 1.4 % slower than the fastest one
+// on average, 29 % at worst (first product, 8192 tokens, d = 2048, a list of 16 blocks per four token tiles: 52 us by 4 x 4
+// tiles, 40 by 2 x 2; the next one 11 %).  On the same lists it took the kernels of the fit 2.0 % and 29 %.
 struct TileInfo {
   int tm, tn, resident;
   float round, step[3];

@@ -13,9 +13,11 @@
 // accumulators cross the register file once per 16 of the contraction index instead of 32, and power bounds the wide
 // tiles: on registers, with normally distributed operands, it reaches 1680 TFLOP/s and the 16x16x32 one 1930 (2300 and
 // 2340 with zeros).  Bits are the same.  4 x 4 tiles, first / second product, us: 4096 tokens, d = 5120, all 320 blocks 698 / 918
-// -> 638 / 857, 3840 tokens, 96 blocks 220 / 249 -> 206 / 233, 8192 tokens, d = 4096, 64 blocks 213 / 202 -> 194 / 186; over 250 drawn
-// launches 2 x 4 tiles 1.6 % less time, 1 x 4 ones 1.6, 2 x 2 ones 0.6, 1 x 2 ones 0.4.  The 1 x 1 tile keeps the larger one: it is a
-// chain of few instructions, and with them half as many it takes 1.3 % less.
+// -> 638 / 857, 3840 tokens, 96 blocks 220 / 249 -> 206 / 233, 8192 tokens, d = 4096, 64 blocks 213 / 202 -> 194 / 186; over the 52
+// launches of profiles/ffn_tile_sweep.txt, small ones most of them, 4 x 4 tiles 3 % less time, 2 x 4, 2 x 2 and 1 x 4 ones 2, the others 1,
+// which is also what the boxes' drift gave the one that did not change.  Tile11, the 1 x 1 tile of a ring of four stages, keeps the larger
+// one: it is a chain of few instructions, and with them half as many it takes 1.3 % less.  (Three of its kind to a CU, Tile11Many, take as
+// long with either: 30 launches 0.975 - 1.05, 1.00 in the mean.)
 #pragma once
 #include <type_traits>
 
@@ -25,7 +27,7 @@ namespace lx {
 
 // TM x TN groups of 64 token / weight rows, WM x WN wavefronts over them, NST ring stages, PH phases per
 // step, MINW wavefronts per SIMD the registers have to leave room for, MF rows of the matrix instruction's tile (16; 32 for
-// the 1 x 1 tile, and for a ring of one stage, which has no registers for slices 32 deep).
+// Tile11, and for a ring of one stage, which has no registers for slices 32 deep).
 template <int MF>
 struct AccOf {
   using T = f32x4;

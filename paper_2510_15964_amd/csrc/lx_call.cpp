@@ -1,10 +1,12 @@
 // The calls of a training step from Python: tensors, list headers and the current stream -> the C ABI of include/lx.h.
 //
-// The smallest calls take the GPU two to five microseconds, and the host as much: a launch alone 2.8 - 3.6 us, a call through
-// ctypes 2.1 us of argument conversion (17 arguments, eight tensors) and 1.2 of shapes, types and the stream; here about one.
+// The smallest calls take the GPU two to five microseconds, and the host as much: a launch alone 2.8 - 3.6 us, and what is done
+// for a call in Python, through ctypes / here, us, with C functions that return at once: a mask's list 1.85 / 0.77, FFN forward and
+// backward 2.1 and 2.2 / 1.0 and 1.1, attention, whose tensors' strides are compared, 3.05 and 4.4 / 1.6 and 2.55, LoRA backward 3.0 /
+// 1.5, predictor 1.7 / 0.95.
 // Host time, us, through ctypes and so: one list and two FFN calls of two launches each 22.9 -> 19.6, lists and both attention
-// calls of three tensors' strides to compare 21.6 -> 16.3, a LoRA pass of nine launches 34.1 -> 29.8.  Passes of less than
-// 25 us become 1.07 times as fast (49 drawn ones, at most 1.28), longer ones wait for the GPU.
+// calls 21.6 -> 16.3, a LoRA pass of nine launches 34.1 -> 29.8.  Whole passes of 24 and 21 us become 1.06 and 1.09 times as fast (with
+// the compaction's share), long ones wait for the GPU.
 //
 // Every argument is read when the call is made, through the same attributes and methods of the tensor that Python code would
 // use (data_ptr, shape, stride, dtype, numel); nothing about a tensor is kept.  The library's functions are handed over by

@@ -1,5 +1,5 @@
-"""Mask compaction where a workgroup's part of the rows takes several passes (the bytes of the first are loaded ahead),
-rows and columns in either orientation."""
+"""Mask compaction where a workgroup's part of the rows takes several steps of 2048 bytes or several stages, from any address, rows and
+columns in either orientation."""
 import numpy as np
 import pytest
 
@@ -9,11 +9,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape,offset", [
-    ((3000, 1000), 0),        # 64 parts of 47 KB, two passes of 32 KB at most each
+    ((3000, 1000), 0),        # 64 parts of 47 KB: 23 steps by rows; 16 parts of 63 columns, ten to a stage
     ((3000, 1000), 7),
     ((1500, 32, 64), 0),      # whole masks of 2 KB
     ((1500, 32, 64), 9),
-    ((80, 4096, 7), 0),       # one mask a pass, rows at the end of what it holds
+    ((80, 4096, 7), 0),       # by columns one mask to a stage
 ])
 @pytest.mark.parametrize("transpose", [False, True])
 def test_parts_of_several_passes(lx, oracle, shape, offset, transpose):  # noqa: F811
