@@ -1163,11 +1163,11 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_both_bf16(const AttnArgs a,
 // r rows plus its start, which weighs more where lists are short; a last round that is not full is faster,
 // workgroups being alone on their CUs, and the more so when earlier rounds have spread the starts; a single round
 // lasts 1.5 % longer per row, having nothing to even it out.  Over 173 launches of both head sizes
-// (profiles/attn_rows_sweep.txt) the chosen count is 1.2 % slower than the best one on average, 12 % at worst (12 heads of
-// 2048 tokens, D = 128, all blocks, dK and dV: 63 us with one row, 57 with two); against one round always, forward / dQ /
-// dK and dV take 0.993 / 0.994 / 0.997 of the time with head size 128 and 0.996 / 0.987 / 1.001 with 64, at worst 1.07 /
-// 1.09 / 1.04, the first two at 2 x 40 heads of 2048 tokens, 25 % of the blocks, D = 128 (2 rows for 6; with all blocks
-// the same choice takes 0.97 - 1.00).  What it is for: 4 x 32 heads of 2048 tokens, 25 %, D = 128, forward 85 -> 68 us
+// (profiles/attn_rows_sweep.txt) the chosen count is 1.2 % slower than the best one on average, 14 % at worst (12 heads of
+// 2048 tokens, D = 128, all blocks, dK and dV: 61 us with one row, 54 with two); against one round always, forward / dQ /
+// dK and dV take 0.990 / 0.996 / 0.995 of the time with head size 128 and 0.994 / 0.990 / 0.994 with 64, at worst 1.03 /
+// 1.05 / 1.06, the last at 2 x 40 heads of 2048 tokens, 25 % of the blocks, D = 128 (2 rows for 6; with all blocks
+// the same choice takes 0.95 - 1.00).  What it is for: 4 x 32 heads of 2048 tokens, 25 %, D = 128, forward 82 -> 66 us
 // (8 rows -> 4).
 static thread_local int g_rows_per_wg = 0;   // one value per host thread
 hipError_t set_attn_rows_per_wg(int r) {
