@@ -42,9 +42,9 @@ def _check(lx, oracle, mask, transpose=False, offset=0):
     ((16, 96), 0.3), ((64, 128), 0.11), ((128, 256), 0.08), ((64, 320), 0.05), ((64, 320), 1.0),
     ((1, 1), 1.0), ((1, 1), 0.0), ((3, 65), 0.5), ((7, 63), 0.5), ((5, 200), 0.0),
     ((32, 16, 16), 0.3), ((2, 32, 32, 32), 0.25), ((40, 32, 32), 0.5),
-    ((9000, 5), 0.4),       # more rows than one scan pass holds
+    ((9000, 5), 0.4),       # many short rows, and few long ones (the columns)
     ((4, 1100, 3), 0.7),
-    ((3, 40000), 0.01),     # a row longer than the LDS staging buffer
+    ((3, 40000), 0.01),     # a row longer than the LDS staging buffer, and many short ones (the columns)
 ])
 @pytest.mark.parametrize("transpose", [False, True])
 def test_compact_bit_exact(lx, oracle, shape, density, transpose):

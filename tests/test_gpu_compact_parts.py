@@ -68,3 +68,42 @@ def test_masks_beyond_2_to_30_bytes(lx, shape):  # noqa: F811
     rp = np.searchsorted(flat, np.arange(rows + 1, dtype=np.int64) * shape[-1])
     assert np.array_equal(bl.row_ptr.cpu().numpy(), rp)
     assert np.array_equal(bl.col_idx[:len(flat)].cpu().numpy(), flat % shape[-1])
+
+
+@pytest.mark.parametrize("shape", [
+    (2, 70000),               # 16 parts of 4375 rows, more than a scan holds
+    (40000, 3),               # rows longer than the stage
+    (3, 5, 4100),             # parts that start inside a mask
+    (7, 190, 200),
+])
+def test_columns_of_masks_that_no_stage_holds(lx, oracle, shape):  # noqa: F811
+    """Masks that are contiguous in the other orientation and go row by row."""
+    rng = np.random.default_rng(shape[0])
+    mask = (rng.random(shape) < 0.3).astype(np.uint8)
+    mask[mask > 0] = rng.integers(1, 256, size=int(mask.sum()), dtype=np.uint8)
+    _check(lx, oracle, mask, transpose=True, offset=3)
+
+
+@pytest.mark.parametrize("shape,strides", [
+    ((1, 9, 11), (0, 16, 1)),                 # rows with a gap
+    ((5, 61, 67), (61 * 67 + 13, 67, 1)),     # masks with a gap, several parts
+    ((5, 61, 67), (61 * 67 * 3, 67 * 3, 3)),  # every third byte
+    ((2, 5000, 3), (3, 6, 1)),                # masks interleaved row by row, several parts
+    ((1, 2, 33000), (0, 1, 2)),               # rows longer than the stage, interleaved
+    ((3, 40, 50), (0, 50, 1)),                # one mask thrice
+])
+def test_masks_of_any_strides(lx, oracle, shape, strides):  # noqa: F811
+    """Through the C interface: the Python one takes contiguous masks."""
+    import torch
+    rng = np.random.default_rng(shape[1])
+    buf = (rng.random(sum((n - 1) * s for n, s in zip(shape, strides)) + 1) < 0.4).astype(np.uint8) * 5
+    mask = np.lib.stride_tricks.as_strided(buf, shape, strides)
+    dev = torch.from_numpy(buf).cuda()
+    rows = shape[0] * shape[1]
+    row_ptr = torch.empty(rows + 1, dtype=torch.int32, device="cuda")
+    col_idx = torch.empty(mask.size, dtype=torch.int32, device="cuda")
+    lx._check(lx._lib.lx_mask_compact(dev.data_ptr(), *shape, *strides, row_ptr.data_ptr(), col_idx.data_ptr(), mask.size,
+                                      lx._stream()), "lx_mask_compact")
+    rp, ci = oracle.mask_compact(np.ascontiguousarray(mask.reshape(rows, shape[2])))
+    assert np.array_equal(row_ptr.cpu().numpy(), rp)
+    assert np.array_equal(col_idx.cpu().numpy()[:rp[-1]], ci)
