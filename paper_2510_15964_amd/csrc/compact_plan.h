@@ -35,7 +35,7 @@ inline MaskLayout mask_layout(const CompactJob& j) {
 // fit the stage lie one after the other, the parts are whole masks: what precedes a part is then one
 // range of bytes, and the part another, in either orientation (16 bytes per load for both).  A part
 // is about 1 KB: both lists of 32 heads of 32 x 32, staged and scanned row by row, took 13 us in eight parts of
-// bytes loaded one by one for the column list, 7 in 32 parts (4.5 by the present kernel).  Strided bytes are slow to count, so
+// bytes loaded one by one for the column list, 7 in 32 parts (one list 4.5 by the present kernel).  Strided bytes are slow to count, so
 // those parts are larger.
 // kFlat numbers the bytes of a part in 32 bits: rows one after the other go row by row only where one alone has 2^30 bytes and
 // more.  (2^18 rows of 4096 bytes, 1 GiB, flat 25.5 ms, row by row 34.8.)

@@ -15,7 +15,7 @@
 // 2340 with zeros).  Bits are the same.  4 x 4 tiles, first / second product, us: 4096 tokens, d = 5120, all 320 blocks 698 / 918
 // -> 638 / 857, 3840 tokens, 96 blocks 220 / 249 -> 206 / 233, 8192 tokens, d = 4096, 64 blocks 213 / 202 -> 194 / 186; over the 52
 // launches of profiles/ffn_tile_sweep.txt, small ones most of them, 4 x 4 tiles 3 % less time, 2 x 4, 2 x 2 and 1 x 4 ones 2, the others 1,
-// which is also what the boxes' drift gave the one that did not change.  Tile11, the 1 x 1 tile of a ring of four stages, keeps the larger
+// which is also what two runs of the tile that did not change are apart.  Tile11, the 1 x 1 tile of a ring of four stages, keeps the larger
 // one: it is a chain of few instructions, and with them half as many it takes 1.3 % less.  (Three of its kind to a CU, Tile11Many, take as
 // long with either: 30 launches 0.975 - 1.05, 1.00 in the mean.)
 #pragma once
