@@ -24,8 +24,8 @@
 
 namespace {
 
-// Set once by bind.
-struct Bound {
+// Of one module object: every copy of the binding has its own.  Set by bind and types.
+struct State {
   decltype(&lx_mask_compact) mask_compact;
   decltype(&lx_mask_compact_pair) mask_compact_pair;
   decltype(&lx_attn_combine_patterns) combine;
@@ -38,22 +38,23 @@ struct Bound {
   decltype(&lx_sparse_attn_bwd_dx) attn_bwd;
   decltype(&lx_sparse_attn_bwd_dx_noalloc) attn_bwd_noalloc;
   PyObject *dtypes, *error, *stream, *uint8, *float32, *int32;     // {torch dtype: lx_dtype}, LxError, () -> raw stream, torch dtypes
-} g;
-// Set once by types.
-struct Types {
   PyObject *list, *i32, *f32, *convert, *wrong;    // list header, c_int32, c_float, (value, type) -> number, the error of wrong types
-} ty;
+};
+constexpr PyObject* State::*kHeld[] = {&State::dtypes, &State::error, &State::stream, &State::uint8, &State::float32, &State::int32,
+                                       &State::list, &State::i32, &State::f32, &State::convert, &State::wrong};
+State& state(PyObject* module) { return *static_cast<State*>(PyModule_GetState(module)); }
 struct Names {
   PyObject *data_ptr, *shape, *stride, *dtype, *numel, *element_size, *is_cuda, *is_contiguous;
 } n;
 
 // An error is pending once `bad` is set; what follows is then skipped by the callers' single test before the call.
 struct Args {
+  const State& g;
   PyObject* const* a;
   bool bad = false;
   Py_buffer header[4];
   int headers = 0;
-  explicit Args(PyObject* const* args) : a(args) {}
+  Args(const State& state, PyObject* const* args) : g(state), a(args) {}
   ~Args() {
     for (int i = 0; i < headers; ++i) PyBuffer_Release(&header[i]);
   }
@@ -65,13 +66,13 @@ struct Args {
   }
   void wrong(const char* what, PyObject* o) {
     bad = true;
-    PyErr_Format(ty.wrong, "%s expected, got %s", what, Py_TYPE(o)->tp_name);
+    PyErr_Format(g.wrong, "%s expected, got %s", what, Py_TYPE(o)->tp_name);
   }
   // Of an integer; of anything else what `convert` makes of it.
   long long number(PyObject* o) {
     if (bad) return 0;
     if (PyLong_Check(o)) return (long long)PyLong_AsUnsignedLongLongMask(o);
-    PyObject* r = PyObject_CallFunctionObjArgs(ty.convert, o, ty.i32, nullptr);
+    PyObject* r = PyObject_CallFunctionObjArgs(g.convert, o, g.i32, nullptr);
     const long long v = r ? PyLong_AsLongLong(r) : -1;
     Py_XDECREF(r);
     bad |= v == -1 && PyErr_Occurred();
@@ -81,7 +82,7 @@ struct Args {
   float real(int i) {
     if (bad) return 0;
     if (PyFloat_Check(a[i])) return (float)PyFloat_AS_DOUBLE(a[i]);
-    PyObject* r = PyObject_CallFunctionObjArgs(ty.convert, a[i], ty.f32, nullptr);
+    PyObject* r = PyObject_CallFunctionObjArgs(g.convert, a[i], g.f32, nullptr);
     const double v = r ? PyFloat_AsDouble(r) : -1.0;
     Py_XDECREF(r);
     bad |= v == -1.0 && PyErr_Occurred();
@@ -126,7 +127,7 @@ struct Args {
   size_t bytes(int i) { return bad || a[i] == Py_None ? 0 : (size_t)(method(i, n.numel) * method(i, n.element_size)); }
   const lx_blocklist* list(int i) {       // of a ctypes structure, or null for None
     if (bad || a[i] == Py_None) return nullptr;
-    const int is = PyObject_IsInstance(a[i], ty.list);
+    const int is = PyObject_IsInstance(a[i], g.list);
     if (is <= 0) {
       bad = true;
       if (is == 0) wrong("list header", a[i]);
@@ -205,7 +206,7 @@ struct Args {
   void* stream() {
     return bad ? nullptr : address(PyObject_CallNoArgs(g.stream));
   }
-  static void raise(int status, PyObject* where) {
+  void raise(int status, PyObject* where) const {
     PyObject* e = PyObject_CallFunction(g.error, "iO", status, where);
     if (e) PyErr_SetObject(g.error, e);
     Py_XDECREF(e);
@@ -221,7 +222,7 @@ PyObject* finish(const Args& a, const char* where, Call call) {
   Py_END_ALLOW_THREADS
   if (s == LX_OK) Py_RETURN_NONE;
   if (PyObject* w = PyUnicode_FromString(where)) {
-    Args::raise(s, w);
+    a.raise(s, w);
     Py_DECREF(w);
   }
   return nullptr;
@@ -234,7 +235,7 @@ bool count(Py_ssize_t got, Py_ssize_t want) {
 
 // A mask tensor [..., R, C], uint8, contiguous, on the GPU: {masks, R, C}.
 void mask_shape(Args& a, int i, long long (&m)[3]) {
-  a.require_dtype(i, g.uint8);
+  a.require_dtype(i, a.g.uint8);
   a.require(a.is_cuda(i));
   a.require(a.is_contiguous(i));
   const long long all = a.sizes(i, m[1], m[2]);
@@ -248,9 +249,10 @@ void mask_shape(Args& a, int i, long long (&m)[3]) {
 }
 
 // mask, transpose, nnz_cap or None, row_ptr, col_idx
-PyObject* mask_compact(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* mask_compact(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 5)) return nullptr;
-  Args a(args);
+  const State& g = state(self);
+  Args a(g, args);
   long long m[3] = {};
   mask_shape(a, 0, m);
   const bool turned = a.truth(1);
@@ -265,9 +267,10 @@ PyObject* mask_compact(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   });
 }
 // mask, row_ptr and col_idx of the row list, those of the column list
-PyObject* mask_compact_pair(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* mask_compact_pair(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 5)) return nullptr;
-  Args a(args);
+  const State& g = state(self);
+  Args a(g, args);
   long long m[3] = {};
   mask_shape(a, 0, m);
   const long long R = m[1], C = m[2];
@@ -281,9 +284,10 @@ PyObject* mask_compact_pair(PyObject*, PyObject* const* args, Py_ssize_t nargs) 
 }
 // headers of the pool's row list and of its column list or None, patterns, nblk, head_pattern, nnz_cap, row_ptr, col_idx of the
 // row list, those of the column list or None
-PyObject* combine(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* combine(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 10)) return nullptr;
-  Args a(args);
+  const State& g = state(self);
+  Args a(g, args);
   a.require_dtype(4, g.int32);
   a.require(a.is_cuda(4));
   a.require(a.is_contiguous(4));
@@ -297,9 +301,10 @@ PyObject* combine(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   return finish(a, "lx_attn_combine_patterns", [&] { return g.combine(r, c, P, nblk, hp, heads, p[0], p[1], p[2], p[3], cap, st); });
 }
 // X, Wa_t, thr, group_rows, mask
-PyObject* predict(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* predict(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 5)) return nullptr;
-  Args a(args);
+  const State& g = state(self);
+  Args a(g, args);
   long long x[2] = {};
   a.unpack(0, x, 2);
   const long long nblk = a.first(1);
@@ -315,9 +320,10 @@ PyObject* predict(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   return finish(a, "lx_mlp_predict_mask", [&] { return g.predict(dt, (int32_t)x[0], (int32_t)x[1], (int32_t)nblk, group, X, W, thr, mask, st); });
 }
 // X, W_up, W_down, header, tile_t, blk_n, Y, H_act, b_up, b_down, workspace
-PyObject* ffn_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* ffn_fwd(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 11)) return nullptr;
-  Args a(args);
+  const State& g = state(self);
+  Args a(g, args);
   long long x[2] = {};
   a.unpack(0, x, 2);
   const int32_t F = (int32_t)a.first(1);
@@ -332,9 +338,10 @@ PyObject* ffn_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   });
 }
 // dY, H_act, W_up, W_down, header, tile_t, blk_n, dX, workspace, W_up_t, W_down_t
-PyObject* ffn_bwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* ffn_bwd(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 11)) return nullptr;
-  Args a(args);
+  const State& g = state(self);
+  Args a(g, args);
   long long x[2] = {};
   a.unpack(0, x, 2);
   const int32_t F = (int32_t)a.first(args[2] != Py_None ? 2 : 10);
@@ -349,9 +356,10 @@ PyObject* ffn_bwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   });
 }
 // X, W_up, A_pad, B_pad, W_down, header, Y, H_act, U, workspace
-PyObject* lora_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* lora_fwd(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 10)) return nullptr;
-  Args a(args);
+  const State& g = state(self);
+  Args a(g, args);
   long long x[2] = {};
   a.unpack(0, x, 2);
   const long long F = a.first(1);
@@ -368,9 +376,10 @@ PyObject* lora_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   });
 }
 // X, dY, H_act, U, W_up_t, W_down_t, A_pad, B_pad, header, dX, dA, dB, workspace
-PyObject* lora_bwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* lora_bwd(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 13)) return nullptr;
-  Args a(args);
+  const State& g = state(self);
+  Args a(g, args);
   long long x[2] = {};
   a.unpack(0, x, 2);
   const long long F = a.first(5);
@@ -421,9 +430,10 @@ void attn_shape(Args& a, const int* others, int count, long long (&q)[4], int64_
   Py_XDECREF(stride);
 }
 // Q, K, V, header, scale, causal, O, LSE, mask_batch, head_active
-PyObject* attn_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* attn_fwd(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 10)) return nullptr;
-  Args a(args);
+  const State& g = state(self);
+  Args a(g, args);
   long long q[4] = {};
   int64_t st3[3] = {};
   const int others[] = {1, 2, 6};
@@ -443,10 +453,11 @@ PyObject* attn_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
 }
 // Q, K, V, O, LSE, dO, header of the row list, of the column list, scale, causal, dQ, dK, dV, workspace, mask_batch, head_active;
 // without the workspace: the noalloc call
-PyObject* attn_bwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* attn_bwd(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   const bool scratch = nargs == 16;
   if (!scratch && !count(nargs, 15)) return nullptr;
-  Args a(args);
+  const State& g = state(self);
+  Args a(g, args);
   const int after = scratch ? 14 : 13;
   long long q[4] = {};
   int64_t st3[3] = {};
@@ -468,9 +479,19 @@ PyObject* attn_bwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   });
 }
 
+// The objects of kHeld from `first` on.
+void hold(State& g, PyObject* const* from, int first, int n) {
+  for (int k = 0; k < n; ++k) {
+    PyObject* old = g.*kHeld[first + k];
+    Py_INCREF(from[k]);
+    g.*kHeld[first + k] = from[k];
+    Py_XDECREF(old);
+  }
+}
 // {function name: address}, dtypes, LxError, stream, torch.uint8, torch.float32, torch.int32
-PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* bind(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 7)) return nullptr;
+  State& g = state(self);
   bool ok = true;
   auto take = [&](const char* name, auto& fn) {
     PyObject* v = PyDict_GetItemString(args[0], name);
@@ -493,24 +514,13 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   take("lx_sparse_attn_bwd_dx", g.attn_bwd);
   take("lx_sparse_attn_bwd_dx_noalloc", g.attn_bwd_noalloc);
   if (!ok) return nullptr;
-  PyObject** to[] = {&g.dtypes, &g.error, &g.stream, &g.uint8, &g.float32, &g.int32};
-  for (int k = 0; k < 6; ++k) {
-    Py_INCREF(args[1 + k]);
-    Py_XDECREF(*to[k]);
-    *to[k] = args[1 + k];
-  }
+  hold(g, args + 1, 0, 6);
   Py_RETURN_NONE;
 }
-
 // lx_blocklist, c_int32, c_float, converter, error of wrong types
-PyObject* types(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* types(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   if (!count(nargs, 5)) return nullptr;
-  PyObject** to[] = {&ty.list, &ty.i32, &ty.f32, &ty.convert, &ty.wrong};
-  for (int k = 0; k < 5; ++k) {
-    Py_INCREF(args[k]);
-    Py_XDECREF(*to[k]);
-    *to[k] = args[k];
-  }
+  hold(state(self), args, 6, 5);
   Py_RETURN_NONE;
 }
 
@@ -518,17 +528,27 @@ PyObject* types(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
 PyMethodDef methods[] = {LX_METHOD(bind), LX_METHOD(types), LX_METHOD(mask_compact), LX_METHOD(mask_compact_pair), LX_METHOD(combine), LX_METHOD(predict),
                          LX_METHOD(ffn_fwd), LX_METHOD(ffn_bwd), LX_METHOD(lora_fwd), LX_METHOD(lora_bwd), LX_METHOD(attn_fwd),
                          LX_METHOD(attn_bwd), {nullptr, nullptr, 0, nullptr}};
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_lx_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
-
-}  // namespace
-
-PyMODINIT_FUNC PyInit__lx_call() {
+int visit_held(PyObject* m, visitproc visit, void* arg) {
+  for (auto p : kHeld) Py_VISIT(state(m).*p);
+  return 0;
+}
+int clear_held(PyObject* m) {
+  for (auto p : kHeld) Py_CLEAR(state(m).*p);
+  return 0;
+}
+int intern_names(PyObject*) {
   struct {
     PyObject** to;
     const char* name;
   } const names[] = {{&n.data_ptr, "data_ptr"}, {&n.shape, "shape"}, {&n.stride, "stride"}, {&n.dtype, "dtype"}, {&n.numel, "numel"},
                      {&n.element_size, "element_size"}, {&n.is_cuda, "is_cuda"}, {&n.is_contiguous, "is_contiguous"}};
   for (const auto& x : names)
-    if (!(*x.to = PyUnicode_InternFromString(x.name))) return nullptr;
-  return PyModule_Create(&module);
+    if (!*x.to && !(*x.to = PyUnicode_InternFromString(x.name))) return -1;
+  return 0;
 }
+PyModuleDef_Slot slots[] = {{Py_mod_exec, reinterpret_cast<void*>(intern_names)}, {0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_lx_call", nullptr, sizeof(State), methods, slots, visit_held, clear_held, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__lx_call() { return PyModuleDef_Init(&module); }

@@ -270,3 +270,17 @@ def test_built_unless_both_files_are_there(monkeypatch, tmp_path, there):
             (tmp_path / f).touch()
     build.ensure()
     assert len(built) == (0 if len(there) == 2 else 1)
+
+
+def test_a_second_copy_of_the_binding_leaves_the_first_alone():
+    import importlib.util
+    from paper_2510_15964_amd import build
+    build.ensure()
+    from paper_2510_15964_amd import lx
+    spec = importlib.util.spec_from_file_location("lx_again", lx.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    X = bf(64, 64)
+    for m in (lx, again, lx):
+        with pytest.raises(m.LxError):
+            m.lx_sparse_ffn_fwd(X.double(), X, X, m.BlockList(1, 4, X, X, 1), 64, 64, X, X)
