@@ -29,6 +29,7 @@ using Tile22 = Tile<2, 2, 2, 2, 2, 2>;
 using Tile22Deep = Tile<2, 2, 2, 4, 4, 1>;
 using Tile14 = Tile<1, 4, 1, 4, 2, 2>;
 using Tile14Lean = Tile<1, 4, 1, 4, 1, 4, 4, 32>;  // four workgroups on a CU: see sdd_lean, dsd_lean
+using Tile18Lean = Tile<1, 8, 1, 8, 1, 4, 4, 32>;  // two workgroups on a CU: see sdd_even
 using Tile14Deep = Tile<1, 4, 2, 4, 4, 2>;
 using Tile12 = Tile<1, 2, 1, 4, 3, 2>;
 using Tile11 = Tile<1, 1, 2, 2, 4, 1, 2, 32>;
@@ -133,6 +134,64 @@ __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int r
     work -= seg;
   }
   return false;
+}
+
+// Items of the sdd kernel as pieces of lists of about equal length (sdd_even): with `per`, the fewest entries for which
+// pieces of at most so many (kEvenLeast .. kEvenMost) fill no more rounds than the longest ones do, a tile's list of n entries
+// falls into k = ceil(n / per) pieces of n / k entries, rounded up or down.  Numbered by halves of the lists as in find_work;
+// an XCD takes its eighth in order.  A list per token tile, up to kEvenTiles of them and 2^16 entries.  Returns false past
+// the end.
+__device__ __forceinline__ bool find_piece(const int* __restrict__ row_ptr, int Tt, int w, int nnz_cap, int& tile, int& first,
+                                           int& count, int& per) {
+  if (w >= sdd_even_grid(Tt, min(row_ptr[Tt], nnz_cap))) return false;      // before the scans
+  const int lane = threadIdx.x % kWave;
+  auto entries = [&](int i) { return i < Tt ? min(row_ptr[i + 1], nnz_cap) - min(row_ptr[i], nnz_cap) : 0; };
+  const bool two = Tt > kWave;
+  const int n0 = entries(two ? 2 * lane : lane), n1 = two ? entries(2 * lane + 1) : 0;
+  constexpr int kPers = kEvenMost - kEvenLeast + 1;
+  int k0[kPers], k1[kPers], sum[(kPers + 1) / 2];     // pieces of this lane's tiles; of all tiles, 16 bits each
+#pragma unroll
+  for (int i = 0; i < kPers; ++i) {
+    k0[i] = (unsigned)(n0 + kEvenLeast + i - 1) / (unsigned)(kEvenLeast + i);
+    k1[i] = (unsigned)(n1 + kEvenLeast + i - 1) / (unsigned)(kEvenLeast + i);
+    sum[i / 2] = i % 2 ? sum[i / 2] | (k0[i] + k1[i]) << 16 : k0[i] + k1[i];
+  }
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1)
+#pragma unroll
+    for (int i = 0; i < (kPers + 1) / 2; ++i) sum[i] += __shfl_xor(sum[i], d);
+  auto pieces = [&](int i) { return (int)((unsigned)sum[i / 2] >> (i % 2 ? 16 : 0) & 0xFFFFu); };
+  const int room = (pieces(kPers - 1) + kEvenRound - 1) / kEvenRound * kEvenRound;
+  int total = pieces(kPers - 1), k_a = k0[kPers - 1], k_b = k1[kPers - 1];
+  per = kEvenMost;
+#pragma unroll
+  for (int i = kPers - 2; i >= 0; --i)
+    if (pieces(i) <= room) total = pieces(i), k_a = k0[i], k_b = k1[i], per = kEvenLeast + i;
+  const int L = (total + 7) / 8, slot = w / 8;
+  int work = w % 8 * L + slot;
+  if (slot >= L || work >= total) return false;
+  const int h_a = (k_a + 1) / 2, h_b = (k_b + 1) / 2, h = h_a + h_b, k = k_a + k_b;      // first halves
+  int both = h | (k - h) << 16;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int up = __shfl_up(both, d);
+    if (lane >= d) both += up;
+  }
+  const int firsts = __shfl(both, kWave - 1) & 0xFFFF;
+  const bool second = work >= firsts;
+  if (second) work -= firsts;
+  const int incl = second ? (int)((unsigned)both >> 16) : both & 0xFFFF;
+  const int l = __ffsll((long long)__ballot(incl > work)) - 1;
+  work -= __shfl(incl - (second ? k - h : h), l);
+  const int ka = __shfl(k_a, l), ha = __shfl(h_a, l), held = second ? ka - ha : ha;
+  const bool b = work >= held;
+  const int kk = b ? __shfl(k_b, l) : ka, n = b ? __shfl(n1, l) : __shfl(n0, l);
+  int chunk = b ? work - held : work;
+  if (second) chunk += (kk + 1) / 2;
+  tile = __builtin_amdgcn_readfirstlane((two ? 2 * l : l) + (b ? 1 : 0));
+  first = __builtin_amdgcn_readfirstlane(quick_div(chunk * n, kk));
+  count = __builtin_amdgcn_readfirstlane(quick_div((chunk + 1) * n, kk)) - first;
+  return true;
 }
 
 template <class Tl>
@@ -254,7 +313,9 @@ struct SddSrc {
   const uint16_t* base2[LORA ? Tl::kIss : 1];
   uint32_t voff[2], voff2[2];
   long long off;
-  int ksteps;
+  int ksteps, entries, lines;     // of the item: entries; entries whose transfers are issued (rings of one stage)
+  __device__ __forceinline__ int live() const { return Tl::kIssA + lines * 8 / Tl::kWaves; }
+  __device__ __forceinline__ bool busy(int wn) const { return wn * Tl::TN < entries * Tl::WN; }
   __device__ __forceinline__ void begin(int s) {
     off = (long long)s * kBK;
     if (LORA && s == ksteps) {
@@ -277,37 +338,46 @@ struct SddSrc {
 // z = W x + B (A x) of Sec. II-C with A2 = X A^T computed beforehand and W2 = B, both padded to
 // rank 64.
 // placed: the item's number along the tokens and along the list where the caller has chosen it (one list row), -1: this
-// workgroup's of a launch of such tiles.
-template <class Tl, int DT, bool LORA>
+// workgroup's of a launch of such tiles.  EVEN: the items are those of find_piece.
+template <class Tl, int DT, bool LORA, bool EVEN = false>
 __device__ __forceinline__ void sdd_tile(const SddArgs& a, uint16_t* ring, GridItem placed = {-1, -1}) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (wave >= Tl::kWaves) return;      // (barriers wait for the wavefronts that are left)
-  int m, chunk, n_i, rs;
-  if (a.gt == a.Tt) {
-    rs = min(a.row_ptr[0], a.nnz_cap);
-    n_i = min(a.row_ptr[1], a.nnz_cap) - rs;
-    if (placed.m < 0) {
-      const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (n_i + Tl::TN - 1) / Tl::TN;
-      const int total = GM * GN, L = (total + 7) / 8, slot = blockIdx.x / 8, idx = (blockIdx.x % 8) * L + slot;
-      if (slot >= L || idx >= total) return;
-      placed = grid_item(idx, GM, GN, Tl::TM == 4 ? 4 : 8);
-    }
-    m = placed.m;
-    chunk = placed.n;
+  int m, first, nb, rs, lines;
+  if constexpr (EVEN) {
+    if (!find_piece(a.row_ptr, a.Tt, blockIdx.x, a.nnz_cap, m, first, nb, lines)) return;
+    rs = a.row_ptr[m];
   } else {
-    if (!find_work(a.row_ptr, a.Tt / Tl::TM, a.gt / Tl::TM, blockIdx.x, Tl::TN, a.nnz_cap, a.halves, m, chunk)) return;
-    m = __builtin_amdgcn_readfirstlane(m);
-    chunk = __builtin_amdgcn_readfirstlane(chunk);
-    const int lr = m * Tl::TM / a.gt;
-    rs = a.row_ptr[lr];
-    n_i = min(a.row_ptr[lr + 1], a.nnz_cap) - rs;   // entries beyond the capacity of the list buffers are ignored
+    int chunk, n_i;
+    if (a.gt == a.Tt) {
+      rs = min(a.row_ptr[0], a.nnz_cap);
+      n_i = min(a.row_ptr[1], a.nnz_cap) - rs;
+      if (placed.m < 0) {
+        const int GM = (a.Tt + Tl::TM - 1) / Tl::TM, GN = (n_i + Tl::TN - 1) / Tl::TN;
+        const int total = GM * GN, L = (total + 7) / 8, slot = blockIdx.x / 8, idx = (blockIdx.x % 8) * L + slot;
+        if (slot >= L || idx >= total) return;
+        placed = grid_item(idx, GM, GN, Tl::TM == 4 ? 4 : 8);
+      }
+      m = placed.m;
+      chunk = placed.n;
+    } else {
+      if (!find_work(a.row_ptr, a.Tt / Tl::TM, a.gt / Tl::TM, blockIdx.x, Tl::TN, a.nnz_cap, a.halves, m, chunk)) return;
+      m = __builtin_amdgcn_readfirstlane(m);
+      chunk = __builtin_amdgcn_readfirstlane(chunk);
+      const int lr = m * Tl::TM / a.gt;
+      rs = a.row_ptr[lr];
+      n_i = min(a.row_ptr[lr + 1], a.nnz_cap) - rs;   // entries beyond the capacity of the list buffers are ignored
+    }
+    first = chunk * Tl::TN;
+    nb = lines = min(Tl::TN, n_i - first);
   }
-  const int i0 = m * Tl::TM, first = chunk * Tl::TN, p0 = rs + first;
-  const int nb = min(Tl::TN, n_i - first);
+  const int i0 = m * Tl::TM, p0 = rs + first;
   if (nb <= 0) return;
 
   SddSrc<Tl, LORA> src;
   src.ksteps = a.K / kBK;
+  src.entries = nb;
+  src.lines = lines;
   src.voff[0] = lane_voff<Tl>(a.K, wave);
   src.voff[1] = lane_voff<Tl>(a.K, wave + 4);
   if (LORA) {
@@ -353,6 +423,11 @@ template <class Tl, int DT, bool LORA>
 __global__ __launch_bounds__(Tl::kTileThreads, Tl::kMinWaves) void ffn_sdd(SddArgs a) {
   __shared__ __attribute__((aligned(1024))) uint16_t ring[kRingElems<Tl>];
   sdd_tile<Tl, DT, LORA>(a, ring);
+}
+template <int DT, bool LORA>
+__global__ __launch_bounds__(Tile18Lean::kTileThreads, Tile18Lean::kMinWaves) void ffn_sdd_even(SddArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[kRingElems<Tile18Lean>];
+  sdd_tile<Tile18Lean, DT, LORA, true>(a, ring);
 }
 // The tile that suits the list as it is, of the set with RESIDENT workgroups per CU: see SddSet.  First product with
 // the list's length / four times that / every block as capacity: 4096 tokens, d = 2048, 14 blocks 24.2 / 24.1 / 24.2 us
@@ -444,6 +519,8 @@ struct DsdSrc {
   long long off_a, off_w, step_a;
   const int* list;             // col_idx of the range
   int lsteps, next;            // list entries of 64 steps, one per lane
+  __device__ __forceinline__ int live() const { return Tl::kIss; }
+  __device__ __forceinline__ bool busy(int) const { return true; }
   // Loads the entries of steps s .. s + 63.  In assembly, with its own wait: a load that the compiler
   // tracks would make it wait for vmcnt(0), and so for the whole ring, at every step's use of `next`
   // (twice the time with three stages).  The drain that is left costs about 1 us per 64 steps.
@@ -867,6 +944,8 @@ static void launch_sdd(SddArgs a, hipStream_t st) {
     hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 1>), grid, dim3(512), 0, st, a);
   else if (r.by == kBySet)
     hipLaunchKernelGGL((ffn_sdd_any<DT, LORA, 2>), grid, dim3(256), 0, st, a);
+  else if (r.by == kByPieces)
+    hipLaunchKernelGGL((ffn_sdd_even<DT, LORA>), grid, dim3(Tile18Lean::kTileThreads), 0, st, a);
   else if (r.by == kByLean)
     LX_CALL(Tile14Lean);
   else if (r.by == kByTile)

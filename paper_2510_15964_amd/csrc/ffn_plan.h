@@ -396,10 +396,41 @@ inline bool dsd_lean(int id, int Tt, int gt, int GM, int GN, int nnz_cap, long l
   return 4.f * mean <= (float)GM || (256 * 2 * ldw <= 4 << 20 && GM * GN % (2 * kCUs) != 0);
 }
 
+// First product, a list per token tile: whether it runs by pieces of lists of about equal length, 4 to 8 entries each
+// (find_piece), on a 1 x 8 tile of one stage, two workgroups to a CU.  These launches are bound by what misses the L2s, some
+// 6.3 TB/s (8192 tokens, d = 4096, 8 % of the blocks by 1 x 4 tiles: 154 us, 156 without the matrix instructions, 72 without
+// the transfers), and what one workgroup fetches its XCD's others find there only while they keep step along the contraction.
+// They do if a round's workgroups have the same to do: 704 items of up to four entries are two or three to a CU, 1.4 rounds;
+// 489 pieces of up to six, all resident, run the same lists in 110 us.  So the pieces are as short as lets them fill whole
+// rounds of kEvenRound, and all of a launch transfer the same number of lines per step, the missing entries' from the first one
+// (without: 1.02 times the time over 120 launches).  Against the items before, which took their kernel by the model (1 x 4 tiles
+// of one, two or four stages): 154 launches of 768 - 8192 tokens, d = 640 - 5120, 3 - 100 % of the blocks, plain and with the
+// low-rank step, capacities a tenth over the list 0.90 of the time on average, twice the list 0.93, 0.69 at best.  The lines:
+// - at least 2.5 entries per workgroup of a round where d is large and tiles are many (48 tiles on, d >= 3200, 3 entries 0.84 - 0.92), else
+//   more items than one round of 1 x 4 tiles holds (d = 2048, 3 entries 1.0 - 1.1, 16 tiles, d = 5120 0.96 - 1.05; 4 entries and
+//   more 0.77 - 0.95);
+// - below d = 3200 not where the longest pieces just need a second round, which short ones then fill (7.5 entries:
+//   0.95 - 1.15);
+// - lists, or a loose capacity, of more than half of the blocks only from 97 tiles and d = 3200 on: with so many in common the 1 x 4
+//   tiles keep step as they are (16 - 32 tiles, 60 - 80 %, 1.0 - 1.25), and a short list in a long capacity pays for the workgroups
+//   that find nothing (7000 tokens, 4 %, d = 1792 30 -> 35 us).
+constexpr int kEvenLeast = 4, kEvenMost = 8, kEvenRound = 2 * kCUs;
+constexpr int kEvenTiles = 128;    // most token tiles: two per lane of the scan
+// Workgroups that hold the pieces of any list of at most nnz_cap entries.
+LX_HD int sdd_even_grid(int Tt, int nnz_cap) { return ceil_div(ceil_div(nnz_cap, kEvenMost) + Tt, kEvenRound) * kEvenRound; }
+inline bool sdd_even(int Tt, int gt, int d, int nnz_cap, int blocks, int want) {
+  if (want != 0 || gt != 1 || Tt < 2 || Tt > kEvenTiles || nnz_cap >= 1 << 16) return false;
+  const float n = 6.f / 7.f * (float)nnz_cap;
+  if (n > 0.5f * (float)blocks && (Tt <= 96 || d < 3200)) return false;
+  if (d >= 3200 && Tt >= 48) return n >= 2.5f * kEvenRound;
+  if (d < 3200 && n / kEvenMost + 0.44f * (float)Tt > 0.9f * kEvenRound && n < 4.3f * 2 * kEvenRound) return false;
+  return n >= 3.5f * kEvenRound && sdd_items_about(kTileInfo[kT14], Tt, gt, (int)n) > kEvenRound;
+}
+
 // ---- which kernel a launch runs by -----------------------------------------------------------
-// kBySet: a kernel that holds several tiles and takes the one that suits the list (SddSet, with `mix` its SddMix), kByMix: 4 x 4
+// kByPieces: pieces of lists (find_piece); kBySet: a kernel that holds several tiles and takes the one that suits the list (SddSet, with `mix` its SddMix), kByMix: 4 x 4
 // tiles and narrower ones for a rest, kByLean: the 1 x 4 tile of one stage, kByTile: the plan's own tile.
-enum Route { kNothing, kByQuarters, kBySet, kByMix, kByLean, kByTile };
+enum Route { kNothing, kByQuarters, kBySet, kByMix, kByLean, kByTile, kByPieces };
 struct SddRoute {
   Route by;
   SddPlan plan;
@@ -414,6 +445,9 @@ inline SddRoute sdd_route(int Tt, int gt, int d, int nnz_cap, int blocks, int wa
   if (quarters_pay(r.items, d, want)) {
     r.by = kByQuarters;
     r.grid = 4 * sdd_grid(kTileInfo[kT11], Tt, gt, nnz_cap);
+  } else if (sdd_even(Tt, gt, d, nnz_cap, blocks, want)) {
+    r.by = kByPieces;
+    r.grid = sdd_even_grid(Tt, nnz_cap);
   } else if (r.plan.allowed) {
     r.by = kBySet;
     r.mix = sdd_may_mix(r.plan, Tt, gt, d, nnz_cap, want);

@@ -129,8 +129,9 @@ __device__ __forceinline__ void tile_phase(const Frag<Tl>& cur, Frag<Tl>& nxt, c
       }
 }
 
-// run_tile with a ring of one stage: a workgroup waits for the transfers of its next step, and the three others that
-// such a stage leaves room for on the CU compute meanwhile.
+// run_tile with a ring of one stage: a workgroup waits for the transfers of its next step, and the others that such a stage
+// leaves room for on the CU compute meanwhile.  A wavefront issues the first src.live() transfer instructions of a step, and
+// multiplies if src.busy(wn): an item may have fewer weight groups than the tile.
 template <class Tl, int DT, class Src>
 __device__ __forceinline__ void run_tile_one_stage(int nsteps, uint32_t ring, int wm, int wn, Src& src,
                                                    typename Tl::Acc (&acc)[Tl::NI][Tl::TI]) {
@@ -142,9 +143,23 @@ __device__ __forceinline__ void run_tile_one_stage(int nsteps, uint32_t ring, in
 #pragma unroll
     for (int x = 0; x < Tl::NI + Tl::TI; ++x) read_operand<Tl>(f[ph % 2], lo, ring, ph, x);
   };
-  src.begin(0);
+  const int live = src.live();
+  auto issue = [&](int s) {
+    src.begin(s);
 #pragma unroll
-  for (int u = 0; u < Tl::kIss; ++u) src.dma(u, to);
+    for (int u = 0; u < Tl::kIss; ++u)
+      if (u < live) src.dma(u, to);
+  };
+  issue(0);
+  if (!src.busy(wn)) {       // the two barriers of a step and its transfers
+    for (int s = 0; s < nsteps; ++s) {
+      wait_vmcnt<0>();
+      lds_barrier();
+      lds_barrier();
+      if (s + 1 < nsteps) issue(s + 1);
+    }
+    return;
+  }
   for (int s = 0; s < nsteps; ++s) {
     wait_vmcnt<0>();
     lds_barrier();
@@ -156,11 +171,7 @@ __device__ __forceinline__ void run_tile_one_stage(int nsteps, uint32_t ring, in
         read(ph + 1);
       } else {
         lds_barrier();     // every wavefront has the step's operands in registers
-        if (s + 1 < nsteps) {
-          src.begin(s + 1);
-#pragma unroll
-          for (int u = 0; u < Tl::kIss; ++u) src.dma(u, to);
-        }
+        if (s + 1 < nsteps) issue(s + 1);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

@@ -20,7 +20,7 @@ def load():
     return L
 
 
-ROUTES = ("nothing", "quarters", "set", "mix", "lean", "tile")      # order of Route
+ROUTES = ("nothing", "quarters", "set", "mix", "lean", "tile", "pieces")      # order of Route
 
 
 def sdd_by(L, Tt, gt, d, cap, blocks, want, n):
