@@ -146,18 +146,82 @@ constexpr int kRMax = 8;   // rows of the mask per workgroup, at most
 // that with the group index as the slowest grid dimension the longest rows of a causal mask are
 // dispatched first).  The row pointers of all slots are fetched once and kept in a small LDS table.
 struct RowSet {
-  const int* tab;   // LDS: blk[kRMax] (-1 = slot not used), rs[kRMax], n[kRMax], head[kRMax]
+  const int* tab;   // LDS: blk[kRMax] (-1 = slot not used), rs[kRMax], n[kRMax], head[kRMax], batch entry[kRMax]
   int reg;          // the same table, entry i in lane i of every wavefront (one LDS read for all accessors)
+  // How many of 64 lists are longer than this lane's, of n entries (-1: none, shorter than any), or as long and of a lower
+  // lane: by a radix walk over the bits of the length with one ballot per bit.  `gt` collects the lanes known to be
+  // longer, `eq` those equal in the bits seen so far.
+  static __device__ __forceinline__ int rank_of(int n) {
+    const unsigned key = (unsigned)(n + 1);
+    unsigned long long gt = 0, eq = ~0ull;
+#pragma unroll
+    for (int bit = 6; bit >= 0; --bit) {     // a list has at most 64 entries here
+      const unsigned long long set = __ballot((key >> bit) & 1u);
+      if ((key >> bit) & 1u) {
+        eq &= set;
+      } else {
+        gt |= eq & set;
+        eq &= ~set;
+      }
+    }
+    return __popcll(gt) + __popcll(eq & ((1ull << threadIdx.x % kWave) - 1ull));
+  }
+  // By turns (see attn_turns): slot k is a row of the k-th cohort that this workgroup's place takes part in.  Like init.
+  __device__ __forceinline__ void init_turns(int* tab_lds, const int* __restrict__ row_ptr, int cap, const AttnArgs& a, int nblk, int w) {
+    tab = tab_lds;
+    const int lane = threadIdx.x % kWave, V = a.vheads, G = V * nblk, Z = a.places;
+    const int x = w % 8, s = w / 8, place = s / G, r = s - place * G;
+    const int mine = lane / nblk, k0 = threadIdx.x / kWave;
+    constexpr int kMine = kRMax / kAW;          // slots k0, k0 + kAW, .. are this wavefront's; the loads of all before any is ranked
+    bool valid[kMine], head_on[kMine];
+    int hh[kMine], b[kMine], rs[kMine], end[kMine];
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+      const int k = k0 + kAW * i;
+      // (every XCD begins elsewhere, so that what they read at a time lies in all parts of the tensors)
+      const int number = k * Z + place, from = number + a.cohorts * x / 8, cohort = from < a.cohorts ? from : from - a.cohorts;
+      const int pair = x + 8 * (cohort * V + mine);
+      valid[i] = k < a.turns && number < a.cohorts && lane < G && pair < a.B * a.Hh;
+      hh[i] = valid[i] ? pair / a.B : 0;
+      b[i] = valid[i] ? pair - hh[i] * a.B : 0;
+      rs[i] = end[i] = 0;
+      head_on[i] = true;
+      if (valid[i]) {
+        const long long at = (long long)((a.mask_batch == 1 ? 0 : b[i]) * a.Hh + hh[i]) * nblk + lane - mine * nblk;
+        if (a.head_active) head_on[i] = a.head_active[hh[i]] != 0;
+        rs[i] = row_ptr[at];
+        end[i] = row_ptr[at + 1];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+      const int k = k0 + kAW * i;
+      // entries beyond the capacity of the index buffer are ignored
+      const int n = !valid[i] ? -1 : head_on[i] ? max(min(end[i], cap) - rs[i], 0) : 0;
+      const int rank = rank_of(n), want = turn_rank(r, k, G, a.turns);
+      if (valid[i] && rank == want) {
+        tab_lds[k] = lane - mine * nblk;
+        tab_lds[kRMax + k] = rs[i];
+        tab_lds[2 * kRMax + k] = n;
+        tab_lds[3 * kRMax + k] = hh[i];
+        tab_lds[4 * kRMax + k] = b[i];
+      }
+      if (want >= __popcll(__ballot(valid[i])) && lane < 5) tab_lds[lane * kRMax + k] = lane == 0 ? -1 : 0;
+    }
+    __syncthreads();
+    reg = tab_lds[min(lane, 5 * kRMax - 1)];
+  }
   // The rows are those of `heads` consecutive heads, h0 .. (nb1 blocks each, their list rows one
   // after the other from head_row0), ranked and dealt together: heads whose lists differ in
   // length then share their workgroups instead of each keeping G of its own.
-  // tab_lds: 4 * kRMax ints of LDS; contains a barrier: call from uniform control flow
+  // tab_lds: 5 * kRMax ints of LDS; contains a barrier: call from uniform control flow
   __device__ __forceinline__ void init(int* tab_lds, const int* __restrict__ row_ptr,
                                        int cap, int head_row0, int nb1, int heads, int h0,
                                        const uint8_t* __restrict__ head_active, int g, int G, int R,
-                                       bool mirror) {
+                                       bool mirror, int batch) {
     tab = tab_lds;
     const int tid = threadIdx.x;
+    if (tid < kRMax) tab_lds[4 * kRMax + tid] = batch;
     const int nblk = nb1 * heads;
     if (nblk <= kWave) {
       // Groups balanced by the actual lengths of the lists: the rows of the head are ranked by
@@ -174,23 +238,7 @@ struct RowSet {
           // entries beyond the capacity of the index buffer are ignored
           n = head_on ? max(min(row_ptr[head_row0 + tid + 1], cap) - rs, 0) : 0;
         }
-        // rank = rows with a longer list + rows before this one with an equally long list, by a
-        // radix walk over the bits of the length with one ballot per bit: `gt` collects the lanes
-        // known to be longer, `eq` those equal in the bits seen so far (lanes past the last row
-        // carry key 0, below every row's)
-        const unsigned key = (unsigned)(n + 1);
-        unsigned long long gt = 0, eq = ~0ull;
-#pragma unroll
-        for (int bit = 6; bit >= 0; --bit) {     // a list has at most 64 entries here
-          const unsigned long long set = __ballot((key >> bit) & 1u);
-          if ((key >> bit) & 1u) {
-            eq &= set;
-          } else {
-            gt |= eq & set;
-            eq &= ~set;
-          }
-        }
-        const int rank = __popcll(gt) + __popcll(eq & ((1ull << tid) - 1ull));
+        const int rank = rank_of(n);     // (lanes past the last row are behind every row)
         const int j = rank / G, pos = rank - j * G;
         if (valid && ((j & 1) ? G - 1 - pos : pos) == g) {
           tab_lds[j] = tid - hh * nb1;
@@ -227,13 +275,14 @@ struct RowSet {
       tab_lds[3 * kRMax + j] = h0;
     }
     __syncthreads();
-    reg = tab_lds[threadIdx.x % (4 * kRMax)];
+    reg = tab_lds[min((int)threadIdx.x % kWave, 5 * kRMax - 1)];
   }
   // k is wave-uniform; the results are scalars taken from the register copy of the table
   __device__ __forceinline__ int blk(int k) const { return __builtin_amdgcn_readlane(reg, k); }
   __device__ __forceinline__ int rs(int k) const { return __builtin_amdgcn_readlane(reg, kRMax + k); }
   __device__ __forceinline__ int n(int k) const { return __builtin_amdgcn_readlane(reg, 2 * kRMax + k); }
   __device__ __forceinline__ int head(int k) const { return __builtin_amdgcn_readlane(reg, 3 * kRMax + k); }
+  __device__ __forceinline__ int batch(int k) const { return __builtin_amdgcn_readlane(reg, 4 * kRMax + k); }
 };
 
 // One 64-bit byte offset per row slot (its head's in a tensor), in the lanes of a register pair; with an entry's block added.
@@ -241,7 +290,7 @@ struct SlotOffset {
   uint32_t lo, hi;
   template <class OfHead>
   __device__ __forceinline__ void init(const RowSet& rows, OfHead of_head) {
-    const long long v = of_head(rows.tab[3 * kRMax + threadIdx.x % kRMax]);
+    const long long v = of_head(rows.tab[4 * kRMax + threadIdx.x % kRMax], rows.tab[3 * kRMax + threadIdx.x % kRMax]);
     lo = (uint32_t)v;
     hi = (uint32_t)((unsigned long long)v >> 32);
   }
@@ -683,38 +732,40 @@ __device__ __forceinline__ bool pair_work(const AttnArgs& a, int w, PairWork& p)
 template <int D, int DT, int NS, int OCC, bool WIDE>
 __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   __shared__ __attribute__((aligned(2 * 64 * D))) uint16_t st[NS][2 * 64 * D];   // stage: K tile, V tile
-  __shared__ int rowtab[4 * kRMax];
+  __shared__ int rowtab[5 * kRMax];
   __shared__ int btab[kTabInts];
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;   // bytes
   const int nqb = a.S / 64;
   PairWork pw;
-  if (!pair_work(a, blockIdx.x, pw)) return;
-  const int b = pw.b, h0 = pw.group * a.vheads;
+  if (a.turns == 0 && !pair_work(a, blockIdx.x, pw)) return;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, ql = 16 * wave + lane % 16;    // this lane's query inside the block
-  auto base_of = [&](int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
-  auto stat_of = [&](int hh) { return ((long long)b * a.Hh + hh) * a.S; };
+  auto base_of = [&](int b, int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
+  auto stat_of = [&](int b, int hh) { return ((long long)b * a.Hh + hh) * a.S; };
   const uint32_t st_addr = lds_addr(&st[0][0]);
   const uint32_t own_off = tile_off<D>(ql, 8 * g);       // this lane's fragments inside an own tile
 
   RowSet rows;
-  rows.init(rowtab, a.row_ptr, a.nnz_cap, ((a.mask_batch == 1 ? 0 : b) * a.Hh + h0) * nqb, nqb,
-            a.vheads, h0, a.head_active, pw.z, a.gz, a.rows_per_wg, true);
+  if (a.turns > 0)
+    rows.init_turns(rowtab, a.row_ptr, a.nnz_cap, a, nqb, blockIdx.x);
+  else
+    rows.init(rowtab, a.row_ptr, a.nnz_cap, ((a.mask_batch == 1 ? 0 : pw.b) * a.Hh + pw.group * a.vheads) * nqb, nqb,
+              a.vheads, pw.group * a.vheads, a.head_active, pw.z, a.gz, a.rows_per_wg, true, pw.b);
   // rows without a listed block (or of an inactive head): O = 0, LSE = -inf, nothing to read
   for (int j = 0; j < kRMax; ++j)
     if (rows.blk(j) >= 0 && rows.n(j) == 0) {
       f32x4 z[D / 16];
       zero4(z);
-      const int hh = rows.head(j);
-      store_acc16<D, DT>(z, 0.f, a.Out + base_of(hh) + (long long)(rows.blk(j) * 64 + ql) * a.ss);
-      if (g == 0) a.LSE[stat_of(hh) + rows.blk(j) * 64 + ql] = -INFINITY;
+      const int hh = rows.head(j), b = rows.batch(j);
+      store_acc16<D, DT>(z, 0.f, a.Out + base_of(b, hh) + (long long)(rows.blk(j) * 64 + ql) * a.ss);
+      if (g == 0) a.LSE[stat_of(b, hh) + rows.blk(j) * 64 + ql] = -INFINITY;
     }
 
   TileDma<D, WIDE> dma;
   dma.init(a.ss);
   using Step = std::conditional_t<WIDE, unsigned long long, uint32_t>;
   SlotOffset heads;
-  heads.init(rows, [&](int hh) { return 2 * base_of(hh); });
+  heads.init(rows, [&](int b, int hh) { return 2 * base_of(b, hh); });
   // tensor p's tile of an entry
   auto tile_of = [&](const uint16_t* p, int e) {
     return reinterpret_cast<const char*>(p) + heads.at(entry_slot(e), entry_blk(e), (Step)(128 * a.ss));
@@ -738,9 +789,9 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   };
   auto row_begin = [&](int stage, int e) {
     qb = entry_blk(e);
-    const int hh = rows.head(entry_slot(e));
-    qoff = base_of(hh) + (long long)(qb * 64 + ql) * a.ss;
-    soff = stat_of(hh) + qb * 64 + ql;
+    const int hh = rows.head(entry_slot(e)), b = rows.batch(entry_slot(e));
+    qoff = base_of(b, hh) + (long long)(qb * 64 + ql) * a.ss;
+    soff = stat_of(b, hh) + qb * 64 + ql;
     const uint32_t q0 = (st_addr + stage * kStage) | own_off;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) qf[kk] = lds_read16(q0 ^ tile_off<D>(0, 32 * kk));
@@ -823,7 +874,7 @@ template <int D, int NS>
 struct DqLds {                       // (aligned to a tile where it is declared)
   uint16_t st[NS][2 * 64 * D];       // stage: K, V (or Q, dO; or O) tile
   float slse[NS][4][16];             // stage, wavefront: LSE of its 16 own rows
-  int rowtab[4 * kRMax];
+  int rowtab[5 * kRMax];
   int btab[kTabInts];
 };
 template <int D, int DT, int NS, bool WIDE>
@@ -833,28 +884,30 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;
   const int nqb = a.S / 64;
   PairWork pw;
-  if (!pair_work(a, w, pw)) return;
-  const int b = pw.b, h0 = pw.group * a.vheads;
+  if (a.turns == 0 && !pair_work(a, w, pw)) return;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, ql = 16 * wave + lane % 16;
-  auto base_of = [&](int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
-  auto stat_of = [&](int hh) { return ((long long)b * a.Hh + hh) * a.S; };
+  auto base_of = [&](int b, int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
+  auto stat_of = [&](int b, int hh) { return ((long long)b * a.Hh + hh) * a.S; };
   const uint32_t st_addr = lds_addr(&st[0][0]), slse_addr = lds_addr(&slse[0][0][0]);
   const uint32_t own_off = tile_off<D>(ql, 8 * g);
 
   RowSet rows;
-  rows.init(sh.rowtab, a.row_ptr, a.nnz_cap, ((a.mask_batch == 1 ? 0 : b) * a.Hh + h0) * nqb, nqb,
-            a.vheads, h0, a.head_active, pw.z, a.gz, a.rows_per_wg, true);
+  if (a.turns > 0)
+    rows.init_turns(sh.rowtab, a.row_ptr, a.nnz_cap, a, nqb, w);
+  else
+    rows.init(sh.rowtab, a.row_ptr, a.nnz_cap, ((a.mask_batch == 1 ? 0 : pw.b) * a.Hh + pw.group * a.vheads) * nqb, nqb,
+              a.vheads, pw.group * a.vheads, a.head_active, pw.z, a.gz, a.rows_per_wg, true, pw.b);
   // rows without a listed block (or of an inactive head): dQ = 0, Delta = 0, nothing to read
   for (int j = 0; j < kRMax; ++j)
     if (rows.blk(j) >= 0 && rows.n(j) == 0) {
       f32x4 z[D / 16];
       zero4(z);
-      const int hh = rows.head(j);
-      store_acc16<D, DT>(z, 0.f, a.dQ + base_of(hh) + (long long)(rows.blk(j) * 64 + ql) * a.ss);
+      const int hh = rows.head(j), b = rows.batch(j);
+      store_acc16<D, DT>(z, 0.f, a.dQ + base_of(b, hh) + (long long)(rows.blk(j) * 64 + ql) * a.ss);
       if (g == 0) {
-        a.Delta[stat_of(hh) + rows.blk(j) * 64 + ql] = 0.f;
-        a.NegLse2[stat_of(hh) + rows.blk(j) * 64 + ql] = -INFINITY;      // no probability, if a column list names the row
+        a.Delta[stat_of(b, hh) + rows.blk(j) * 64 + ql] = 0.f;
+        a.NegLse2[stat_of(b, hh) + rows.blk(j) * 64 + ql] = -INFINITY;      // no probability, if a column list names the row
       }
     }
 
@@ -862,7 +915,7 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   dma.init(a.ss);
   using Step = std::conditional_t<WIDE, unsigned long long, uint32_t>;
   SlotOffset heads;
-  heads.init(rows, [&](int hh) { return 2 * base_of(hh); });
+  heads.init(rows, [&](int b, int hh) { return 2 * base_of(b, hh); });
   // tensor p's tile of an entry
   auto tile_of = [&](const uint16_t* p, int e) {
     return reinterpret_cast<const char*>(p) + heads.at(entry_slot(e), entry_blk(e), (Step)(128 * a.ss));
@@ -885,9 +938,9 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   // the row's O tile, needed once for Delta = rowsum(dO . O), and the LSE of its 64 queries
   // (lanes 0-15 of wavefront w bring those of its own rows 16w .. 16w+15)
   auto issue_aux = [&](int stage, int e) {
-    const int hh = rows.head(entry_slot(e)), blk = entry_blk(e);
+    const int hh = rows.head(entry_slot(e)), b = rows.batch(entry_slot(e)), blk = entry_blk(e);
     dma.issue(st_addr + stage * kStage, tile_of(a.O, e));
-    if (lane < 16) dma4(a.LSEin + stat_of(hh) + blk * 64 + ql, slse_addr + stage * 256 + wave * 64);
+    if (lane < 16) dma4(a.LSEin + stat_of(b, hh) + blk * 64 + ql, slse_addr + stage * 256 + wave * 64);
   };
   auto issue_blk = [&](int stage, int e) {
     const uint32_t dst = st_addr + stage * kStage;
@@ -897,8 +950,8 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   auto row_begin = [&](int stage, int e) {
     qb = entry_blk(e);
     const int slot = entry_slot(e);
-    qoff = base_of(rows.head(slot)) + (long long)(qb * 64 + ql) * a.ss;
-    soff = stat_of(rows.head(slot)) + qb * 64 + ql;
+    qoff = base_of(rows.batch(slot), rows.head(slot)) + (long long)(qb * 64 + ql) * a.ss;
+    soff = stat_of(rows.batch(slot), rows.head(slot)) + qb * 64 + ql;
     const uint32_t q0 = (st_addr + stage * kStage) | own_off;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) {
@@ -989,7 +1042,7 @@ template <int D, int NS, bool ALONE>
 struct DkvLds {                      // (aligned to a tile where it is declared)
   uint16_t st[NS][(ALONE ? 3 : 2) * 64 * D];      // stage: Q, dO (or K, V), O tile
   float sstat[NS][4][32];            // stage, query tile: -LSE*log2e [16], Delta [16]
-  int rowtab[4 * kRMax];
+  int rowtab[5 * kRMax];
   int btab[kTabInts];
 };
 template <int D, int DT, int NS, bool WIDE, bool ALONE>
@@ -999,24 +1052,26 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
   constexpr uint32_t kTile = 2 * 64 * D, kStage = (ALONE ? 3 : 2) * kTile;
   const int nkb = a.S / 64;
   PairWork pw;
-  if (!pair_work(a, w, pw)) return;
-  const int b = pw.b, h0 = pw.group * a.vheads;
+  if (a.turns == 0 && !pair_work(a, w, pw)) return;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, kl = 16 * wave + lane % 16;    // this lane's key inside the block
-  auto base_of = [&](int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
-  auto stat_of = [&](int hh) { return ((long long)b * a.Hh + hh) * a.S; };
+  auto base_of = [&](int b, int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
+  auto stat_of = [&](int b, int hh) { return ((long long)b * a.Hh + hh) * a.S; };
   const uint32_t st_addr = lds_addr(&st[0][0]), sstat_addr = lds_addr(&sstat[0][0][0]);
   const uint32_t own_off = tile_off<D>(kl, 8 * g);
 
   RowSet rows;
-  rows.init(sh.rowtab, a.crow_ptr, a.cnnz_cap, ((a.mask_batch == 1 ? 0 : b) * a.Hh + h0) * nkb, nkb,
-            a.vheads, h0, a.head_active, pw.z, a.gz, a.rows_per_wg, false);
+  if (a.turns > 0)
+    rows.init_turns(sh.rowtab, a.crow_ptr, a.cnnz_cap, a, nkb, w);
+  else
+    rows.init(sh.rowtab, a.crow_ptr, a.cnnz_cap, ((a.mask_batch == 1 ? 0 : pw.b) * a.Hh + pw.group * a.vheads) * nkb, nkb,
+              a.vheads, pw.group * a.vheads, a.head_active, pw.z, a.gz, a.rows_per_wg, false, pw.b);
   // key blocks used by no query block: zero gradients, nothing to read
   for (int j = 0; j < kRMax; ++j)
     if (rows.blk(j) >= 0 && rows.n(j) == 0) {
       f32x4 z[D / 16];
       zero4(z);
-      const long long koff = base_of(rows.head(j)) + (long long)(rows.blk(j) * 64 + kl) * a.ss;
+      const long long koff = base_of(rows.batch(j), rows.head(j)) + (long long)(rows.blk(j) * 64 + kl) * a.ss;
       store_acc16<D, DT>(z, 0.f, a.dV + koff);
       store_acc16<D, DT>(z, 0.f, a.dK + koff);
     }
@@ -1025,7 +1080,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
   dma.init(a.ss);
   using Step = std::conditional_t<WIDE, unsigned long long, uint32_t>;
   SlotOffset heads;
-  heads.init(rows, [&](int hh) { return 2 * base_of(hh); });
+  heads.init(rows, [&](int b, int hh) { return 2 * base_of(b, hh); });
   // tensor p's tile of an entry
   auto tile_of = [&](const uint16_t* p, int e) {
     return reinterpret_cast<const char*>(p) + heads.at(entry_slot(e), entry_blk(e), (Step)(128 * a.ss));
@@ -1036,7 +1091,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
   // lanes 0-15 of wave w bring -LSE*log2(e), lanes 16-31 Delta of queries 16w .. 16w+15 of a block; ALONE: lanes 0-15 LSE
   const char* stat_src = reinterpret_cast<const char*>((ALONE ? a.LSEin : lane < 16 ? a.NegLse2 : a.Delta) + 16 * wave + lane % 16);
   SlotOffset stats;
-  stats.init(rows, [&](int hh) { return 4 * stat_of(hh); });
+  stats.init(rows, [&](int b, int hh) { return 4 * stat_of(b, hh); });
   int kb = 0;
   long long koff = 0;
   uint4 kf[D / 32], vf[D / 32];
@@ -1056,7 +1111,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
   };
   auto row_begin = [&](int stage, int e) {
     kb = entry_blk(e);
-    koff = base_of(rows.head(entry_slot(e))) + (long long)(kb * 64 + kl) * a.ss;
+    koff = base_of(rows.batch(entry_slot(e)), rows.head(entry_slot(e))) + (long long)(kb * 64 + kl) * a.ss;
     const uint32_t k0 = (st_addr + stage * kStage) | own_off;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) {
@@ -1159,7 +1214,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_both_bf16(const AttnArgs a,
 // launch are resident at once on the chip's `slots` workgroup slots (a causal mask keeps the groups balanced for
 // every count, because slots are filled in pairs k, 2G-1-k), or a smaller one with more workgroups than slots.
 // Those pay a start per round, but the dispatcher hands them out as slots become free, which evens out pairs with
-// long and short lists, and fewer pairs share an L2 at a time.  The estimate, in units of one row: a round costs
+// long and short lists, and fewer pairs share an L2 at a time.  The estimate (attn_rows_cost), in units of one row: a round costs
 // r rows plus its start, which weighs more where lists are short; a last round that is not full is faster,
 // workgroups being alone on their CUs, and the more so when earlier rounds have spread the starts; a single round
 // lasts 1.5 % longer per row, having nothing to even it out.  Over 173 launches of both head sizes
@@ -1187,26 +1242,29 @@ static int rows_per_wg(int nblk, int heads, int B, int slots) {
   auto groups = [&](int r) { return (long long)((nblk + r - 1) / r) * heads * B; };
   int r = 1;
   while (r < kRMax && groups(r) > slots) ++r;
-  const double start = 0.38 * (1 + 16.0 / nblk);
-  auto cost = [&](int q) {
-    const long long n = groups(q), full = n / slots, left = n % slots;
-    if (n <= slots) return (q + start) * (1 + 0.015 * q);
-    const double f = (double)left / slots;
-    const double last = left == 0 ? 0.0 : full > 1 && f <= 0.5 ? 0.5 + 0.35 * f : fmin(1.0, 0.5 + 1.1 * f);
-    return q * (full + last) + start * (full + (left > 0));
-  };
   for (int q = r - 1; q >= 1; --q)
-    if (cost(q) < cost(r)) r = q;
+    if (attn_rows_cost(q, groups(q), slots, nblk) < attn_rows_cost(r, groups(r), slots, nblk)) r = q;
   if (g_rows_per_wg > 0) r = g_rows_per_wg;
   return r > nblk ? nblk : r;
 }
 
-// Completes the arguments for workgroups of which `slots` fit the chip; returns the grid (see pair_work).
-static int attn_grid(AttnArgs& a, int B, int slots) {
+// Completes the arguments for workgroups of which `slots` fit the chip; returns the grid (see pair_work, attn_turns).
+static int attn_grid(AttnArgs& a, int B, int slots, bool may_turn) {
   const int nblk = a.S / 64;
   a.B = B;
   a.vheads = heads_per_group(nblk, a.Hh);
   a.rows_per_wg = rows_per_wg(nblk, a.Hh, B, slots);
+  a.turns = 0;
+  if (may_turn && g_rows_per_wg == 0 && (long long)B * a.Hh < 1 << 20) {
+    const AttnTurns t = attn_turns(B * a.Hh, nblk, slots, a.rows_per_wg);
+    if (t.turns > 0) {
+      a.turns = t.turns;
+      a.places = t.places;
+      a.cohorts = t.cohorts;
+      a.vheads = t.pairs;
+      return t.grid;
+    }
+  }
   a.gz = (nblk + a.rows_per_wg - 1) / a.rows_per_wg * a.vheads;
   const int P = B * (a.Hh / a.vheads);
   const long long n = (long long)P * a.gz;
@@ -1218,7 +1276,7 @@ template <int D, int DT, bool WIDE>
 static hipError_t launch_fwd_t(AttnArgs a, int B, hipStream_t st) {
   ProfScope ps(kKAttnFwd, st);
   constexpr int kNs = D == 64 ? kFwdNs64 : 2, kOcc = D == 64 ? kFwdOcc64 : 2;
-  const int grid = attn_grid(a, B, kCUs * kOcc);
+  const int grid = attn_grid(a, B, kCUs * kOcc, true);
   hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
   return hipGetLastError();
 }
@@ -1247,14 +1305,14 @@ static hipError_t launch_bwd_t(AttnArgs a, int B, hipStream_t st) {
     if (bwd_in_one(a, D, B)) {
       ProfScope ps(kKAttnDkv, st);
       constexpr int kOcc = kBothOcc(D);
-      const int half = attn_grid(a, B, kCUs * kOcc / 2);
+      const int half = attn_grid(a, B, kCUs * kOcc / 2, false);
       hipLaunchKernelGGL((attn_bwd_both_bf16<D, DT, 2, kOcc>), dim3(2 * half), dim3(kAT), 0, st, a, half);
       return hipGetLastError();
     }
   {
     ProfScope ps(kKAttnDq, st);
     constexpr int kNs = D == 64 ? kDqNs64 : 2, kOcc = D == 64 ? kDqOcc64 : 2;
-    const int grid = attn_grid(a, B, kCUs * kOcc);
+    const int grid = attn_grid(a, B, kCUs * kOcc, true);
     hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
   }
   hipError_t e = hipGetLastError();
@@ -1262,7 +1320,7 @@ static hipError_t launch_bwd_t(AttnArgs a, int B, hipStream_t st) {
   {
     ProfScope ps(kKAttnDkv, st);
     constexpr int kNs = D == 64 ? kDkvNs64 : 2, kOcc = D == 64 ? kDkvOcc64 : 2;
-    const int grid = attn_grid(a, B, kCUs * kOcc);
+    const int grid = attn_grid(a, B, kCUs * kOcc, true);
     hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
   }
   return hipGetLastError();

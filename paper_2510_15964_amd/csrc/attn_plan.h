@@ -1,5 +1,7 @@
-// Which attention backward calls run their two sides in one launch.  Plain C++, without the device's headers.
+// Which attention backward calls run their two sides in one launch, and which rows of the mask a workgroup of any
+// attention kernel takes.  Plain C++, without the device's headers.
 #pragma once
+#include "lx_chip.h"
 
 namespace lx {
 
@@ -99,6 +101,60 @@ inline bool bwd_sides_apart(const BwdBuffers& b) {
 inline bool bwd_one_launch_pays(int D, long long rows, int nblk, bool causal, double mean) {
   if (D == 128) return rows <= 128 || (rows <= 256 && (causal || mean <= 2 || (mean <= 6 && 2 * mean <= nblk)));
   return rows <= 768 || (rows <= 1728 && rows * nblk <= 20000);
+}
+
+// ---- which rows of the mask a workgroup takes ----------------------------------------------------
+// Estimate of a launch of `groups` workgroups with r rows each, `slots` of them at a time, in units of one row (see
+// rows_per_wg in attn_bf16.hip).
+inline double attn_rows_cost(int r, long long groups, int slots, int nblk) {
+  const double start = 0.38 * (1 + 16.0 / nblk);
+  const long long full = groups / slots, left = groups % slots;
+  if (groups <= slots) return (r + start) * (1 + 0.015 * r);
+  const double f = (double)left / slots;
+  const double part = 0.5 + (full > 1 && f <= 0.5 ? 0.35 : 1.1) * f, last = left == 0 ? 0.0 : part < 1.0 ? part : 1.0;
+  return r * (full + last) + start * (full + (left > 0));
+}
+// By turns: an XCD's (batch entry, head) pairs are x, x + 8, ..; as many consecutive ones of those as have up to 64 rows together
+// are a cohort, and a workgroup has one row of each of several cohorts, the same number of rows as every other one and about
+// the same number of blocks, all workgroups being resident at once.  The rows of one pair (or four) that a workgroup has
+// otherwise divide evenly only by chance: 2 x 40 heads of 2048 tokens at head size 128 are 5 rows for each of 512 workgroups, but 32
+// rows of a pair do not divide by 5, and by two rows a workgroup they are 2.5 rounds.  Taken where the estimate says a tenth
+// less.  Forward / backward, us, that way / by turns: 2 x 40 of 2048, D = 128, all blocks 130.6 / 357.8 -> 124.3 / 351.0, 25 %
+// 50.8 / 135.6 -> 46.2 / 128.2; 8 x 12 of 1024, no causality, 30 % 36.0 / 97.5 -> 30.3 / 87.0; 8 x 40 of 512, 40 % 32.6 / 88.9 ->
+// 30.3 / 84.7.  34 calls of 320 - 4096 tokens and 10 - 100 % of the blocks for which it is taken, both head sizes: 0.81 - 1.05 of the
+// time, 0.93 on average, backward 0.80 - 1.07 and 0.95; the slower ones are all but one of 10 - 15 %, where a workgroup's
+// lists are too short to even each other out.  Where the estimates are alike, 0.81 - 1.17 either way.
+constexpr double kTurnsLine = 0.92;
+struct AttnTurns {
+  int turns, places, cohorts, pairs, grid;      // rows per workgroup (0: not by turns), cohorts at a time, of an XCD; pairs of a cohort
+};
+inline AttnTurns attn_turns(int pairs, int nblk, int slots, int rows_per_wg) {
+  AttnTurns best = {0, 0, 0, 0, 0};
+  if (nblk > 64 || pairs < 8) return best;
+  const int room = slots / 8, per = (pairs + 7) / 8;
+  const int groups = (nblk + rows_per_wg - 1) / rows_per_wg;
+  double least = kTurnsLine * attn_rows_cost(rows_per_wg, (long long)groups * pairs, slots, nblk);
+  for (int V = 64 / nblk; V >= 1; --V) {
+    const int G = V * nblk, Z = room / G;
+    if (Z < 1) continue;
+    const int cohorts = (per + V - 1) / V, turns = (cohorts + Z - 1) / Z;
+    if (turns < 2 || turns > 8) continue;
+    const double cost = attn_rows_cost(turns, 8 * Z * G, slots, nblk);
+    if (cost < least) least = cost, best = {turns, Z, cohorts, V, 8 * Z * G};
+  }
+  return best;
+}
+// The rank by length, among the n rows of a cohort, of the row that a place's workgroup r takes in turn k of `turns`, so that
+// the ranks of all turns add up to about the same for every r: up and down by turns, of an odd number the first three by
+// r, n - 1 - 2 r and r + n / 2 modulo n.
+LX_HD int turn_rank(int r, int k, int n, int turns) {
+  if (turns % 2 == 1 && turns >= 3) {
+    const int low = (n + 1) / 2;         // r below: the first half
+    if (k == 1) return r < low ? n - 1 - 2 * r : 2 * n - 1 - (n % 2 == 0 ? 1 : 0) - 2 * r;
+    if (k == 2) return r < low ? r + n / 2 : r - low;
+    if (k > 2) k -= 3;
+  }
+  return k % 2 == 0 ? r : n - 1 - r;
 }
 
 }  // namespace lx

@@ -5,12 +5,6 @@
 
 #include "lx_chip.h"
 
-#if defined(__HIPCC__)
-#define LX_HD __host__ __device__ inline
-#else
-#define LX_HD inline
-#endif
-
 namespace lx {
 
 // The tiles, widest first.  A wide tile moves fewer bytes and LDS reads per product (a workgroup step

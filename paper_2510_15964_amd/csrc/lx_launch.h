@@ -42,6 +42,7 @@ struct AttnArgs {
   int rows_per_wg;   // rows of the mask per workgroup, set by the launcher
   int vheads;        // consecutive heads whose rows one group of workgroups shares, set by the launcher
   int B, gz;         // batch entries, workgroups of a group, set by the launcher
+  int turns, places, cohorts; // rows per workgroup, of another cohort each, and cohorts at a time on an XCD (attn_turns; 0: none)
   int spread;        // 1: the workgroups of an XCD by their length (pair_work), set by the launcher
 };
 

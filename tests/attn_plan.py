@@ -1,4 +1,4 @@
-"""The library's rules for the launches of the attention backward call (csrc/attn_plan.h) for the tests."""
+"""The library's rules for the launches of the attention calls (csrc/attn_plan.h) for the tests."""
 import ctypes as C
 import os
 import subprocess
@@ -26,3 +26,10 @@ def meet(L, n, stride, row, delta):
 
 def sides_apart(L, n, stride, row, at, stats, ptrs, entries):
     return bool(L.sides_apart(arr(n), arr(stride), C.c_longlong(row), arr(at), *map(C.c_longlong, (stats, ptrs, entries))))
+
+
+def turns(L, pairs, nblk, slots, rows_per_wg):
+    """turns, places, cohorts, pairs of a cohort, grid; None: not by turns."""
+    out = (C.c_int * 5)()
+    L.turns(pairs, nblk, slots, rows_per_wg, out)
+    return tuple(out) if out[0] else None

@@ -1,4 +1,4 @@
-// Which attention backward calls run in one launch (csrc/attn_plan.h), as C functions.
+// Which attention backward calls run in one launch and which rows a workgroup takes (csrc/attn_plan.h), as C functions.
 #include "../paper_2510_15964_amd/csrc/attn_plan.h"
 
 using namespace lx;
@@ -20,5 +20,13 @@ int sides_apart(const long long* n, const long long* stride, long long row, cons
                           {{p(9), ptrs}, {p(10), entries}},
                           {{p(11), stats}, {p(12), stats}}});
 }
+
+// turns, places, cohorts, pairs, grid
+void turns(int pairs, int nblk, int slots, int rows_per_wg, int* out) {
+  const AttnTurns t = attn_turns(pairs, nblk, slots, rows_per_wg);
+  const int v[5] = {t.turns, t.places, t.cohorts, t.pairs, t.grid};
+  for (int i = 0; i < 5; ++i) out[i] = v[i];
+}
+int rank_in_turn(int r, int k, int n, int turns) { return turn_rank(r, k, n, turns); }
 
 }  // extern "C"
