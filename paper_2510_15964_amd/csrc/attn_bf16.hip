@@ -145,9 +145,12 @@ constexpr int kRMax = 8;   // rows of the mask per workgroup, at most
 // j*G + g for even j and (j+1)*G - 1 - g for odd j, counted from the last block if `mirror`, so
 // that with the group index as the slowest grid dimension the longest rows of a causal mask are
 // dispatched first).  The row pointers of all slots are fetched once and kept in a small LDS table.
+// TURNS: the rows' batch entries differ (attn_turns); kernels of calls that do not run so are compiled without.
+template <bool TURNS>
 struct RowSet {
   const int* tab;   // LDS: blk[kRMax] (-1 = slot not used), rs[kRMax], n[kRMax], head[kRMax], batch entry[kRMax]
   int reg;          // the same table, entry i in lane i of every wavefront (one LDS read for all accessors)
+  int b0, Hh;       // the batch entry of all rows, without TURNS; heads
   // How many of 64 lists are longer than this lane's, of n entries (-1: none, shorter than any), or as long and of a lower
   // lane: by a radix walk over the bits of the length with one ballot per bit.  `gt` collects the lanes known to be
   // longer, `eq` those equal in the bits seen so far.
@@ -169,7 +172,7 @@ struct RowSet {
   // By turns (see attn_turns): slot k is a row of the k-th cohort that this workgroup's place takes part in.  Like init.
   __device__ __forceinline__ void init_turns(int* tab_lds, const int* __restrict__ row_ptr, int cap, const AttnArgs& a, int nblk, int w) {
     tab = tab_lds;
-    const int lane = threadIdx.x % kWave, V = a.vheads, G = V * nblk, Z = a.places;
+    const int lane = threadIdx.x % kWave, turns = a.rows_per_wg, V = a.vheads, G = V * nblk, Z = a.gz, cohorts = a.spread;
     const int x = w % 8, s = w / 8, place = s / G, r = s - place * G;
     const int mine = lane / nblk, k0 = threadIdx.x / kWave;
     constexpr int kMine = kRMax / kAW;          // slots k0, k0 + kAW, .. are this wavefront's; the loads of all before any is ranked
@@ -179,9 +182,9 @@ struct RowSet {
     for (int i = 0; i < kMine; ++i) {
       const int k = k0 + kAW * i;
       // (every XCD begins elsewhere, so that what they read at a time lies in all parts of the tensors)
-      const int number = k * Z + place, from = number + a.cohorts * x / 8, cohort = from < a.cohorts ? from : from - a.cohorts;
+      const int number = k * Z + place, from = number + cohorts * x / 8, cohort = from < cohorts ? from : from - cohorts;
       const int pair = x + 8 * (cohort * V + mine);
-      valid[i] = k < a.turns && number < a.cohorts && lane < G && pair < a.B * a.Hh;
+      valid[i] = k < turns && number < cohorts && lane < G && pair < a.B * a.Hh;
       hh[i] = valid[i] ? pair / a.B : 0;
       b[i] = valid[i] ? pair - hh[i] * a.B : 0;
       rs[i] = end[i] = 0;
@@ -198,7 +201,7 @@ struct RowSet {
       const int k = k0 + kAW * i;
       // entries beyond the capacity of the index buffer are ignored
       const int n = !valid[i] ? -1 : head_on[i] ? max(min(end[i], cap) - rs[i], 0) : 0;
-      const int rank = rank_of(n), want = turn_rank(r, k, G, a.turns);
+      const int rank = rank_of(n), want = turn_rank(r, k, G, turns);
       if (valid[i] && rank == want) {
         tab_lds[k] = lane - mine * nblk;
         tab_lds[kRMax + k] = rs[i];
@@ -209,7 +212,9 @@ struct RowSet {
       if (want >= __popcll(__ballot(valid[i])) && lane < 5) tab_lds[lane * kRMax + k] = lane == 0 ? -1 : 0;
     }
     __syncthreads();
-    reg = tab_lds[min(lane, 5 * kRMax - 1)];
+    // behind the table's copy the slots' numbers of their (batch entry, head) pair
+    const int k = lane % kRMax, own = tab_lds[min(lane, 5 * kRMax - 1)];
+    reg = lane < 5 * kRMax ? own : tab_lds[4 * kRMax + k] * a.Hh + tab_lds[3 * kRMax + k];
   }
   // The rows are those of `heads` consecutive heads, h0 .. (nb1 blocks each, their list rows one
   // after the other from head_row0), ranked and dealt together: heads whose lists differ in
@@ -218,10 +223,10 @@ struct RowSet {
   __device__ __forceinline__ void init(int* tab_lds, const int* __restrict__ row_ptr,
                                        int cap, int head_row0, int nb1, int heads, int h0,
                                        const uint8_t* __restrict__ head_active, int g, int G, int R,
-                                       bool mirror, int batch) {
+                                       bool mirror, int batch, int n_heads) {
     tab = tab_lds;
     const int tid = threadIdx.x;
-    if (tid < kRMax) tab_lds[4 * kRMax + tid] = batch;
+    b0 = batch;
     const int nblk = nb1 * heads;
     if (nblk <= kWave) {
       // Groups balanced by the actual lengths of the lists: the rows of the head are ranked by
@@ -275,22 +280,24 @@ struct RowSet {
       tab_lds[3 * kRMax + j] = h0;
     }
     __syncthreads();
-    reg = tab_lds[min((int)threadIdx.x % kWave, 5 * kRMax - 1)];
+    Hh = n_heads;
+    reg = tab_lds[threadIdx.x % (4 * kRMax)];
   }
   // k is wave-uniform; the results are scalars taken from the register copy of the table
   __device__ __forceinline__ int blk(int k) const { return __builtin_amdgcn_readlane(reg, k); }
   __device__ __forceinline__ int rs(int k) const { return __builtin_amdgcn_readlane(reg, kRMax + k); }
   __device__ __forceinline__ int n(int k) const { return __builtin_amdgcn_readlane(reg, 2 * kRMax + k); }
   __device__ __forceinline__ int head(int k) const { return __builtin_amdgcn_readlane(reg, 3 * kRMax + k); }
-  __device__ __forceinline__ int batch(int k) const { return __builtin_amdgcn_readlane(reg, 4 * kRMax + k); }
+  __device__ __forceinline__ int batch(int k) const { return TURNS ? __builtin_amdgcn_readlane(reg, 4 * kRMax + k) : b0; }
+  __device__ __forceinline__ int pair(int k) const { return TURNS ? __builtin_amdgcn_readlane(reg, 5 * kRMax + k) : b0 * Hh + head(k); }
 };
 
 // One 64-bit byte offset per row slot (its head's in a tensor), in the lanes of a register pair; with an entry's block added.
 struct SlotOffset {
   uint32_t lo, hi;
-  template <class OfHead>
-  __device__ __forceinline__ void init(const RowSet& rows, OfHead of_head) {
-    const long long v = of_head(rows.tab[4 * kRMax + threadIdx.x % kRMax], rows.tab[3 * kRMax + threadIdx.x % kRMax]);
+  template <bool TURNS, class OfHead>
+  __device__ __forceinline__ void init(const RowSet<TURNS>& rows, OfHead of_head) {
+    const long long v = of_head(TURNS ? rows.tab[4 * kRMax + threadIdx.x % kRMax] : rows.b0, rows.tab[3 * kRMax + threadIdx.x % kRMax]);
     lo = (uint32_t)v;
     hi = (uint32_t)((unsigned long long)v >> 32);
   }
@@ -527,7 +534,8 @@ __device__ __forceinline__ int entry_slot(int e) { return (e >> 24) & 7; }
 // Entries first .. first+cnt-1 of the sequence -> tab[0 .. cnt).  Uniform control flow; ends
 // with a barrier.  offs[i]: first entry of slot i (offs[kRMax] = length of the sequence); pre:
 // entries of a row before its first block (1: OWN; 2: OWN, AUX).
-__device__ __forceinline__ void fill_table(int* tab, const RowSet& rows, const int* __restrict__ col_idx,
+template <class Rows>
+__device__ __forceinline__ void fill_table(int* tab, const Rows& rows, const int* __restrict__ col_idx,
                                            const int (&offs)[kRMax + 1], int first, int cnt, int pre) {
   for (int e = first + (int)threadIdx.x; e < first + cnt; e += kAT) {
     int j = 0, o = 0;
@@ -606,8 +614,8 @@ struct NoAux {
   __device__ __forceinline__ void operator()(int, int) const {}
 };
 template <int NS, int XOWN, int XAUX, int XBLK, int YAUX, int YST, class IssueOwn, class IssueAux, class IssueBlk,
-          class RowBegin, class Aux, class Comp, class RowEnd>
-__device__ __forceinline__ void walk_table(int* tab, const RowSet& rows, const int* __restrict__ col_idx,
+          class RowBegin, class Aux, class Comp, class RowEnd, class Rows>
+__device__ __forceinline__ void walk_table(int* tab, const Rows& rows, const int* __restrict__ col_idx,
                                            IssueOwn issue_own, IssueAux issue_aux, IssueBlk issue_blk,
                                            RowBegin row_begin, Aux aux, Comp comp, RowEnd row_end) {
   static_assert(NS >= 2 && NS <= 4, "ring depth");
@@ -729,7 +737,7 @@ __device__ __forceinline__ bool pair_work(const AttnArgs& a, int w, PairWork& p)
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-template <int D, int DT, int NS, int OCC, bool WIDE>
+template <int D, int DT, int NS, int OCC, bool WIDE, bool TURNS>
 __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   __shared__ __attribute__((aligned(2 * 64 * D))) uint16_t st[NS][2 * 64 * D];   // stage: K tile, V tile
   __shared__ int rowtab[5 * kRMax];
@@ -737,7 +745,7 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;   // bytes
   const int nqb = a.S / 64;
   PairWork pw;
-  if (a.turns == 0 && !pair_work(a, blockIdx.x, pw)) return;
+  if (!TURNS && !pair_work(a, blockIdx.x, pw)) return;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, ql = 16 * wave + lane % 16;    // this lane's query inside the block
   auto base_of = [&](int b, int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
@@ -745,12 +753,12 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   const uint32_t st_addr = lds_addr(&st[0][0]);
   const uint32_t own_off = tile_off<D>(ql, 8 * g);       // this lane's fragments inside an own tile
 
-  RowSet rows;
-  if (a.turns > 0)
+  RowSet<TURNS> rows;
+  if constexpr (TURNS)
     rows.init_turns(rowtab, a.row_ptr, a.nnz_cap, a, nqb, blockIdx.x);
   else
     rows.init(rowtab, a.row_ptr, a.nnz_cap, ((a.mask_batch == 1 ? 0 : pw.b) * a.Hh + pw.group * a.vheads) * nqb, nqb,
-              a.vheads, pw.group * a.vheads, a.head_active, pw.z, a.gz, a.rows_per_wg, true, pw.b);
+              a.vheads, pw.group * a.vheads, a.head_active, pw.z, a.gz, a.rows_per_wg, true, pw.b, a.Hh);
   // rows without a listed block (or of an inactive head): O = 0, LSE = -inf, nothing to read
   for (int j = 0; j < kRMax; ++j)
     if (rows.blk(j) >= 0 && rows.n(j) == 0) {
@@ -789,9 +797,9 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   };
   auto row_begin = [&](int stage, int e) {
     qb = entry_blk(e);
-    const int hh = rows.head(entry_slot(e)), b = rows.batch(entry_slot(e));
-    qoff = base_of(b, hh) + (long long)(qb * 64 + ql) * a.ss;
-    soff = stat_of(b, hh) + qb * 64 + ql;
+    const int slot = entry_slot(e);
+    qoff = heads.at(slot, qb, (Step)(128 * a.ss)) / 2 + ql * a.ss;
+    soff = (long long)rows.pair(slot) * a.S + qb * 64 + ql;
     const uint32_t q0 = (st_addr + stage * kStage) | own_off;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) qf[kk] = lds_read16(q0 ^ tile_off<D>(0, 32 * kk));
@@ -877,14 +885,14 @@ struct DqLds {                       // (aligned to a tile where it is declared)
   int rowtab[5 * kRMax];
   int btab[kTabInts];
 };
-template <int D, int DT, int NS, bool WIDE>
+template <int D, int DT, int NS, bool WIDE, bool TURNS>
 __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, NS>& sh) {
   auto& st = sh.st;
   auto& slse = sh.slse;
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;
   const int nqb = a.S / 64;
   PairWork pw;
-  if (a.turns == 0 && !pair_work(a, w, pw)) return;
+  if (!TURNS && !pair_work(a, w, pw)) return;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, ql = 16 * wave + lane % 16;
   auto base_of = [&](int b, int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
@@ -892,12 +900,12 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   const uint32_t st_addr = lds_addr(&st[0][0]), slse_addr = lds_addr(&slse[0][0][0]);
   const uint32_t own_off = tile_off<D>(ql, 8 * g);
 
-  RowSet rows;
-  if (a.turns > 0)
+  RowSet<TURNS> rows;
+  if constexpr (TURNS)
     rows.init_turns(sh.rowtab, a.row_ptr, a.nnz_cap, a, nqb, w);
   else
     rows.init(sh.rowtab, a.row_ptr, a.nnz_cap, ((a.mask_batch == 1 ? 0 : pw.b) * a.Hh + pw.group * a.vheads) * nqb, nqb,
-              a.vheads, pw.group * a.vheads, a.head_active, pw.z, a.gz, a.rows_per_wg, true, pw.b);
+              a.vheads, pw.group * a.vheads, a.head_active, pw.z, a.gz, a.rows_per_wg, true, pw.b, a.Hh);
   // rows without a listed block (or of an inactive head): dQ = 0, Delta = 0, nothing to read
   for (int j = 0; j < kRMax; ++j)
     if (rows.blk(j) >= 0 && rows.n(j) == 0) {
@@ -938,9 +946,9 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   // the row's O tile, needed once for Delta = rowsum(dO . O), and the LSE of its 64 queries
   // (lanes 0-15 of wavefront w bring those of its own rows 16w .. 16w+15)
   auto issue_aux = [&](int stage, int e) {
-    const int hh = rows.head(entry_slot(e)), b = rows.batch(entry_slot(e)), blk = entry_blk(e);
+    const int blk = entry_blk(e);
     dma.issue(st_addr + stage * kStage, tile_of(a.O, e));
-    if (lane < 16) dma4(a.LSEin + stat_of(b, hh) + blk * 64 + ql, slse_addr + stage * 256 + wave * 64);
+    if (lane < 16) dma4(a.LSEin + (long long)rows.pair(entry_slot(e)) * a.S + blk * 64 + ql, slse_addr + stage * 256 + wave * 64);
   };
   auto issue_blk = [&](int stage, int e) {
     const uint32_t dst = st_addr + stage * kStage;
@@ -950,8 +958,8 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   auto row_begin = [&](int stage, int e) {
     qb = entry_blk(e);
     const int slot = entry_slot(e);
-    qoff = base_of(rows.batch(slot), rows.head(slot)) + (long long)(qb * 64 + ql) * a.ss;
-    soff = stat_of(rows.batch(slot), rows.head(slot)) + qb * 64 + ql;
+    qoff = heads.at(slot, qb, (Step)(128 * a.ss)) / 2 + ql * a.ss;
+    soff = (long long)rows.pair(slot) * a.S + qb * 64 + ql;
     const uint32_t q0 = (st_addr + stage * kStage) | own_off;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) {
@@ -1027,10 +1035,10 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   walk_table<NS, 2 * TileDma<D, WIDE>::kPerWave, TileDma<D, WIDE>::kPerWave + 1, 2 * TileDma<D, WIDE>::kPerWave, 2, D / 32>(
       sh.btab, rows, a.col_idx, issue_own, issue_aux, issue_blk, row_begin, aux, comp, row_end);
 }
-template <int D, int DT, int NS, int OCC, bool WIDE>
+template <int D, int DT, int NS, int OCC, bool WIDE, bool TURNS>
 __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
   __shared__ __attribute__((aligned(2 * 64 * D))) DqLds<D, NS> sh;
-  attn_bwd_dq<D, DT, NS, WIDE>(a, blockIdx.x, sh);
+  attn_bwd_dq<D, DT, NS, WIDE, TURNS>(a, blockIdx.x, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -1045,14 +1053,14 @@ struct DkvLds {                      // (aligned to a tile where it is declared)
   int rowtab[5 * kRMax];
   int btab[kTabInts];
 };
-template <int D, int DT, int NS, bool WIDE, bool ALONE>
+template <int D, int DT, int NS, bool WIDE, bool ALONE, bool TURNS>
 __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D, NS, ALONE>& sh) {
   auto& st = sh.st;
   auto& sstat = sh.sstat;
   constexpr uint32_t kTile = 2 * 64 * D, kStage = (ALONE ? 3 : 2) * kTile;
   const int nkb = a.S / 64;
   PairWork pw;
-  if (a.turns == 0 && !pair_work(a, w, pw)) return;
+  if (!TURNS && !pair_work(a, w, pw)) return;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int g = lane / 16, kl = 16 * wave + lane % 16;    // this lane's key inside the block
   auto base_of = [&](int b, int hh) { return (long long)b * a.sb + (long long)hh * a.sh; };
@@ -1060,12 +1068,12 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
   const uint32_t st_addr = lds_addr(&st[0][0]), sstat_addr = lds_addr(&sstat[0][0][0]);
   const uint32_t own_off = tile_off<D>(kl, 8 * g);
 
-  RowSet rows;
-  if (a.turns > 0)
+  RowSet<TURNS> rows;
+  if constexpr (TURNS)
     rows.init_turns(sh.rowtab, a.crow_ptr, a.cnnz_cap, a, nkb, w);
   else
     rows.init(sh.rowtab, a.crow_ptr, a.cnnz_cap, ((a.mask_batch == 1 ? 0 : pw.b) * a.Hh + pw.group * a.vheads) * nkb, nkb,
-              a.vheads, pw.group * a.vheads, a.head_active, pw.z, a.gz, a.rows_per_wg, false, pw.b);
+              a.vheads, pw.group * a.vheads, a.head_active, pw.z, a.gz, a.rows_per_wg, false, pw.b, a.Hh);
   // key blocks used by no query block: zero gradients, nothing to read
   for (int j = 0; j < kRMax; ++j)
     if (rows.blk(j) >= 0 && rows.n(j) == 0) {
@@ -1111,7 +1119,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
   };
   auto row_begin = [&](int stage, int e) {
     kb = entry_blk(e);
-    koff = base_of(rows.batch(entry_slot(e)), rows.head(entry_slot(e))) + (long long)(kb * 64 + kl) * a.ss;
+    koff = heads.at(entry_slot(e), kb, (Step)(128 * a.ss)) / 2 + kl * a.ss;
     const uint32_t k0 = (st_addr + stage * kStage) | own_off;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) {
@@ -1192,10 +1200,10 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
   walk_table<NS, 2 * TileDma<D, WIDE>::kPerWave, -1, (ALONE ? 3 : 2) * TileDma<D, WIDE>::kPerWave + 1, 0, 2 * (D / 32)>(
       sh.btab, rows, a.ccol_idx, issue_own, NoAux(), issue_blk, row_begin, NoAux(), comp, row_end);
 }
-template <int D, int DT, int NS, int OCC, bool WIDE>
+template <int D, int DT, int NS, int OCC, bool WIDE, bool TURNS>
 __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) {
   __shared__ __attribute__((aligned(2 * 64 * D))) DkvLds<D, NS, false> sh;
-  attn_bwd_dkv<D, DT, NS, WIDE, false>(a, blockIdx.x, sh);
+  attn_bwd_dkv<D, DT, NS, WIDE, false, TURNS>(a, blockIdx.x, sh);
 }
 
 // Both sides in one launch (bwd_in_one): the first `half` workgroups take the key side, which is the longer one.
@@ -1204,9 +1212,9 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_both_bf16(const AttnArgs a,
   __shared__ __attribute__((aligned(2 * 64 * D))) DkvLds<D, NS, true> sh;
   static_assert(sizeof(DqLds<D, NS>) <= sizeof(sh), "shared memory");
   if ((int)blockIdx.x < half)
-    attn_bwd_dkv<D, DT, NS, false, true>(a, blockIdx.x, sh);
+    attn_bwd_dkv<D, DT, NS, false, true, false>(a, blockIdx.x, sh);
   else
-    attn_bwd_dq<D, DT, NS, false>(a, blockIdx.x - half, reinterpret_cast<DqLds<D, NS>&>(sh));
+    attn_bwd_dq<D, DT, NS, false, false>(a, blockIdx.x - half, reinterpret_cast<DqLds<D, NS>&>(sh));
 }
 
 
@@ -1248,36 +1256,43 @@ static int rows_per_wg(int nblk, int heads, int B, int slots) {
   return r > nblk ? nblk : r;
 }
 
-// Completes the arguments for workgroups of which `slots` fit the chip; returns the grid (see pair_work, attn_turns).
-static int attn_grid(AttnArgs& a, int B, int slots, bool may_turn) {
+// Completes the arguments for workgroups of which `slots` fit the chip; the grid (see pair_work) and whether its workgroups
+// take their rows by turns, which `may_turn` allows (attn_turns).
+struct AttnGrid {
+  int n;
+  bool turns;
+};
+static AttnGrid attn_grid(AttnArgs& a, int B, int slots, bool may_turn) {
   const int nblk = a.S / 64;
   a.B = B;
   a.vheads = heads_per_group(nblk, a.Hh);
   a.rows_per_wg = rows_per_wg(nblk, a.Hh, B, slots);
-  a.turns = 0;
   if (may_turn && g_rows_per_wg == 0 && (long long)B * a.Hh < 1 << 20) {
     const AttnTurns t = attn_turns(B * a.Hh, nblk, slots, a.rows_per_wg);
     if (t.turns > 0) {
-      a.turns = t.turns;
-      a.places = t.places;
-      a.cohorts = t.cohorts;
+      a.rows_per_wg = t.turns;
+      a.gz = t.places;
+      a.spread = t.cohorts;
       a.vheads = t.pairs;
-      return t.grid;
+      return {t.grid, true};
     }
   }
   a.gz = (nblk + a.rows_per_wg - 1) / a.rows_per_wg * a.vheads;
   const int P = B * (a.Hh / a.vheads);
   const long long n = (long long)P * a.gz;
   a.spread = a.rows_per_wg <= 3 && n > kCUs && n <= slots;
-  return 8 * (P / 8 * a.gz + (P % 8 * a.gz + 7) / 8);
+  return {8 * (P / 8 * a.gz + (P % 8 * a.gz + 7) / 8), false};
 }
 
 template <int D, int DT, bool WIDE>
 static hipError_t launch_fwd_t(AttnArgs a, int B, hipStream_t st) {
   ProfScope ps(kKAttnFwd, st);
   constexpr int kNs = D == 64 ? kFwdNs64 : 2, kOcc = D == 64 ? kFwdOcc64 : 2;
-  const int grid = attn_grid(a, B, kCUs * kOcc, true);
-  hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
+  const AttnGrid grid = attn_grid(a, B, kCUs * kOcc, true);
+  if (grid.turns)
+    hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc, WIDE, true>), dim3(grid.n), dim3(kAT), 0, st, a);
+  else
+    hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc, WIDE, false>), dim3(grid.n), dim3(kAT), 0, st, a);
   return hipGetLastError();
 }
 template <int D, int DT>
@@ -1305,23 +1320,29 @@ static hipError_t launch_bwd_t(AttnArgs a, int B, hipStream_t st) {
     if (bwd_in_one(a, D, B)) {
       ProfScope ps(kKAttnDkv, st);
       constexpr int kOcc = kBothOcc(D);
-      const int half = attn_grid(a, B, kCUs * kOcc / 2, false);
+      const int half = attn_grid(a, B, kCUs * kOcc / 2, false).n;
       hipLaunchKernelGGL((attn_bwd_both_bf16<D, DT, 2, kOcc>), dim3(2 * half), dim3(kAT), 0, st, a, half);
       return hipGetLastError();
     }
   {
     ProfScope ps(kKAttnDq, st);
     constexpr int kNs = D == 64 ? kDqNs64 : 2, kOcc = D == 64 ? kDqOcc64 : 2;
-    const int grid = attn_grid(a, B, kCUs * kOcc, true);
-    hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
+    const AttnGrid grid = attn_grid(a, B, kCUs * kOcc, true);
+    if (grid.turns)
+      hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc, WIDE, true>), dim3(grid.n), dim3(kAT), 0, st, a);
+    else
+      hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc, WIDE, false>), dim3(grid.n), dim3(kAT), 0, st, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKAttnDkv, st);
     constexpr int kNs = D == 64 ? kDkvNs64 : 2, kOcc = D == 64 ? kDkvOcc64 : 2;
-    const int grid = attn_grid(a, B, kCUs * kOcc, true);
-    hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc, WIDE>), dim3(grid), dim3(kAT), 0, st, a);
+    const AttnGrid grid = attn_grid(a, B, kCUs * kOcc, true);
+    if (grid.turns)
+      hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc, WIDE, true>), dim3(grid.n), dim3(kAT), 0, st, a);
+    else
+      hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc, WIDE, false>), dim3(grid.n), dim3(kAT), 0, st, a);
   }
   return hipGetLastError();
 }

@@ -130,14 +130,13 @@ struct AttnTurns {
 };
 inline AttnTurns attn_turns(int pairs, int nblk, int slots, int rows_per_wg) {
   AttnTurns best = {0, 0, 0, 0, 0};
-  if (nblk > 64 || pairs < 8) return best;
+  if (nblk > 64 || pairs < 8 || (long long)pairs * nblk <= slots) return best;      // (a row per workgroup is the least that there is)
   const int room = slots / 8, per = (pairs + 7) / 8;
   const int groups = (nblk + rows_per_wg - 1) / rows_per_wg;
   double least = kTurnsLine * attn_rows_cost(rows_per_wg, (long long)groups * pairs, slots, nblk);
   for (int V = 64 / nblk; V >= 1; --V) {
     const int G = V * nblk, Z = room / G;
-    if (Z < 1) continue;
-    const int cohorts = (per + V - 1) / V, turns = (cohorts + Z - 1) / Z;
+    const int cohorts = (per + V - 1) / V, turns = Z > 0 ? (cohorts + Z - 1) / Z : 0;
     if (turns < 2 || turns > 8) continue;
     const double cost = attn_rows_cost(turns, 8 * Z * G, slots, nblk);
     if (cost < least) least = cost, best = {turns, Z, cohorts, V, 8 * Z * G};

@@ -40,10 +40,9 @@ struct AttnArgs {
   int Hh, S, mask_batch, causal;
   float scale;
   int rows_per_wg;   // rows of the mask per workgroup, set by the launcher
-  int vheads;        // consecutive heads whose rows one group of workgroups shares, set by the launcher
-  int B, gz;         // batch entries, workgroups of a group, set by the launcher
-  int turns, places, cohorts; // rows per workgroup, of another cohort each, and cohorts at a time on an XCD (attn_turns; 0: none)
-  int spread;        // 1: the workgroups of an XCD by their length (pair_work), set by the launcher
+  int vheads;        // consecutive heads whose rows one group of workgroups shares; by turns: pairs of a cohort; set by the launcher
+  int B, gz;         // batch entries; workgroups of a group, by turns: cohorts at a time on an XCD; set by the launcher
+  int spread;        // 1: the workgroups of an XCD by their length (pair_work); by turns: cohorts of an XCD; set by the launcher
 };
 
 hipError_t launch_compact(const uint8_t*, int, int, int, long long, long long, long long, int*, int*,
