@@ -307,15 +307,16 @@ struct SddArgs {
 // Sources of the sdd kernel's transfers; step K/64, if there is one, is the low-rank step.  It is the last
 // one, so its sources replace the others; a choice at each transfer instruction instead was a branch between
 // the matrix instructions and cost a 64 x 64 tile 90 ns per step (704 tokens, 4928 -> 19712: 26.6 -> 19.9 us).
-template <class Tl, bool LORA>
+// EVEN: an item's transfers and products are those of the entries that it has; else of as many as the tile holds.
+template <class Tl, bool LORA, bool EVEN>
 struct SddSrc {
   const uint16_t* base[Tl::kIss];
   const uint16_t* base2[LORA ? Tl::kIss : 1];
   uint32_t voff[2], voff2[2];
   long long off;
-  int ksteps, entries, lines;     // of the item: entries; entries whose transfers are issued (rings of one stage)
-  __device__ __forceinline__ int live() const { return Tl::kIssA + lines * 8 / Tl::kWaves; }
-  __device__ __forceinline__ bool busy(int wn) const { return wn * Tl::TN < entries * Tl::WN; }
+  int ksteps, entries, lines;     // EVEN, of the item: entries; entries whose transfers are issued
+  __device__ __forceinline__ int live() const { return EVEN ? Tl::kIssA + lines * 8 / Tl::kWaves : Tl::kIss; }
+  __device__ __forceinline__ bool busy(int wn) const { return !EVEN || wn * Tl::TN < entries * Tl::WN; }
   __device__ __forceinline__ void begin(int s) {
     off = (long long)s * kBK;
     if (LORA && s == ksteps) {
@@ -374,7 +375,7 @@ __device__ __forceinline__ void sdd_tile(const SddArgs& a, uint16_t* ring, GridI
   const int i0 = m * Tl::TM, p0 = rs + first;
   if (nb <= 0) return;
 
-  SddSrc<Tl, LORA> src;
+  SddSrc<Tl, LORA, EVEN> src;
   src.ksteps = a.K / kBK;
   src.entries = nb;
   src.lines = lines;
