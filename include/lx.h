@@ -451,11 +451,12 @@ lx_status lx_probe_stream_copy(const void* src, void* dst, size_t bytes, void* s
 /*
  * Tuning knob of the attention kernels (Sec. VI-A leaves the launch shape open).
  * A workgroup walks the block lists of `rows` rows of the mask (query blocks in
- * the forward and dQ kernels, key blocks in the dK/dV kernel) of one (batch,
- * head) as one stream of blocks.  rows = 0 (the default) lets the library
- * choose from the problem size; 1..8 fixes it for all later calls of the
- * calling host thread (the setting is per thread: concurrent callers on other
- * threads keep theirs).  Results do not depend on it: it changes neither the
+ * the forward and dQ kernels, key blocks in the dK/dV kernel) of up to four
+ * consecutive heads of a batch entry as one stream of blocks.  rows = 0 (the
+ * default) lets the library choose from the problem size, and then the rows may
+ * also be of several batch entries and heads that are further apart; 1..8 fixes
+ * the number for all later calls of the calling host thread (the setting is per
+ * thread: concurrent callers on other threads keep theirs).  Results do not depend on it: it changes neither the
  * arithmetic of a row nor its order.  Returns LX_ERR_INVALID_ARG outside 0..8.
  */
 lx_status lx_attn_set_rows_per_workgroup(int32_t rows);

@@ -17,17 +17,19 @@
 // At the block densities of the paper a row of the mask lists only a few
 // blocks, so a workgroup that handled one row would spend most of its life in
 // the chain of dependent loads that starts it (row pointer -> list -> tiles).
-// A workgroup therefore owns up to eight rows of one batch entry and walks
+// A workgroup therefore owns up to eight rows and walks
 // their lists as ONE sequence of ring entries, written once into an LDS table:
 // per row an entry that brings the row's own tiles, then its listed blocks.
 // The transfers of the entries ahead -- of the same row or of the next -- are
 // in flight while the current one is computed, and nothing in the walk reads
-// global memory directly.  The rows of a group of up to four consecutive heads
-// are ranked by the length of their lists and dealt to the group's workgroups
-// in a snake over the ranks, which evens out the number of blocks per
-// workgroup for any mask and between heads with long and short lists (where all
-// workgroups of a launch are resident at once, it lasts as long as its longest
-// workgroup).
+// global memory directly.  Which rows: those of a group of up to four
+// consecutive heads of a batch entry are ranked by the length of their lists and
+// dealt to the group's workgroups in a snake over the ranks, which evens out the
+// number of blocks per workgroup for any mask and between heads with long and
+// short lists (where all workgroups of a launch are resident at once, it lasts as
+// long as its longest workgroup); or, where a launch's rows do not divide evenly
+// that way, one row of each of several cohorts of (batch entry, head) pairs, again
+// by the rank of its list (by turns: attn_turns).
 //
 // Data movement: tiles go from global memory straight into LDS
 // (global_load_lds, 16 bytes per lane) through a ring of two or three stages.
@@ -138,13 +140,11 @@ __device__ __forceinline__ constexpr uint32_t tile_off(int row, int col) {
 // ---------------------------------------------------------------------------
 // rows of a workgroup and the walk over their blocks
 // ---------------------------------------------------------------------------
-constexpr int kRMax = 8;   // rows of the mask per workgroup, at most
-
-// The rows (query blocks, or key blocks for dK/dV) of one (batch, head) that workgroup g of G
-// owns (see init for how they are chosen; with more than 64 blocks per head: slot j holds block
+// The rows (query blocks, or key blocks for dK/dV) that a workgroup owns: of one batch entry's group of heads, as number g of
+// the group's G workgroups (see init for how they are chosen; with more than 64 blocks per head: slot j holds block
 // j*G + g for even j and (j+1)*G - 1 - g for odd j, counted from the last block if `mirror`, so
 // that with the group index as the slowest grid dimension the longest rows of a causal mask are
-// dispatched first).  The row pointers of all slots are fetched once and kept in a small LDS table.
+// dispatched first), or by turns (init_turns).  The row pointers of all slots are fetched once and kept in a small LDS table.
 // TURNS: the rows' batch entries differ (attn_turns); kernels of calls that do not run so are compiled without.
 template <bool TURNS>
 struct RowSet {
@@ -172,7 +172,8 @@ struct RowSet {
   // By turns (see attn_turns): slot k is a row of the k-th cohort that this workgroup's place takes part in.  Like init.
   __device__ __forceinline__ void init_turns(int* tab_lds, const int* __restrict__ row_ptr, int cap, const AttnArgs& a, int nblk, int w) {
     tab = tab_lds;
-    const int lane = threadIdx.x % kWave, turns = a.rows_per_wg, V = a.vheads, G = V * nblk, Z = a.gz, cohorts = a.spread;
+    const int lane = threadIdx.x % kWave, turns = a.by_turns.turns, V = a.by_turns.pairs, G = V * nblk, Z = a.by_turns.places,
+              cohorts = a.by_turns.cohorts;
     const int x = w % 8, s = w / 8, place = s / G, r = s - place * G;
     const int mine = lane / nblk, k0 = threadIdx.x / kWave;
     constexpr int kMine = kRMax / kAW;          // slots k0, k0 + kAW, .. are this wavefront's; the loads of all before any is ranked
@@ -1218,81 +1219,35 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_both_bf16(const AttnArgs a,
 }
 
 
-// Rows per workgroup, unless the caller fixed the number: the smallest count with which all workgroups of the
-// launch are resident at once on the chip's `slots` workgroup slots (a causal mask keeps the groups balanced for
-// every count, because slots are filled in pairs k, 2G-1-k), or a smaller one with more workgroups than slots.
-// Those pay a start per round, but the dispatcher hands them out as slots become free, which evens out pairs with
-// long and short lists, and fewer pairs share an L2 at a time.  The estimate (attn_rows_cost), in units of one row: a round costs
-// r rows plus its start, which weighs more where lists are short; a last round that is not full is faster,
-// workgroups being alone on their CUs, and the more so when earlier rounds have spread the starts; a single round
-// lasts 1.5 % longer per row, having nothing to even it out.  Over 173 launches of both head sizes
-// (profiles/attn_rows_sweep.txt) the chosen count is 1.2 % slower than the best one on average, 14 % at worst (12 heads of
-// 2048 tokens, D = 128, all blocks, dK and dV: 61 us with one row, 54 with two); against one round always, forward / dQ /
-// dK and dV take 0.990 / 0.996 / 0.995 of the time with head size 128 and 0.994 / 0.990 / 0.994 with 64, at worst 1.03 /
-// 1.05 / 1.06, the last at 2 x 40 heads of 2048 tokens, 25 % of the blocks, D = 128 (2 rows for 6; with all blocks
-// the same choice takes 0.95 - 1.00).  What it is for: 4 x 32 heads of 2048 tokens, 25 %, D = 128, forward 82 -> 66 us
-// (8 rows -> 4).
 static thread_local int g_rows_per_wg = 0;   // one value per host thread
 hipError_t set_attn_rows_per_wg(int r) {
   if (r < 0 || r > kRMax) return hipErrorInvalidValue;
   g_rows_per_wg = r;
   return hipSuccess;
 }
-// Heads per group of workgroups: as many consecutive heads (4, 2 or 1) as divide the head count
-// and whose rows one wavefront can rank (64 lanes).  The rows of the group are dealt to its
-// workgroups together, so heads with long and with short lists even each other out.
-static int heads_per_group(int nblk, int heads) {
-  for (int v = 4; v > 1; v /= 2)
-    if (heads % v == 0 && v * nblk <= kWave) return v;
-  return 1;
-}
-static int rows_per_wg(int nblk, int heads, int B, int slots) {
-  auto groups = [&](int r) { return (long long)((nblk + r - 1) / r) * heads * B; };
-  int r = 1;
-  while (r < kRMax && groups(r) > slots) ++r;
-  for (int q = r - 1; q >= 1; --q)
-    if (attn_rows_cost(q, groups(q), slots, nblk) < attn_rows_cost(r, groups(r), slots, nblk)) r = q;
-  if (g_rows_per_wg > 0) r = g_rows_per_wg;
-  return r > nblk ? nblk : r;
-}
 
-// Completes the arguments for workgroups of which `slots` fit the chip; the grid (see pair_work) and whether its workgroups
-// take their rows by turns, which `may_turn` allows (attn_turns).
-struct AttnGrid {
-  int n;
-  bool turns;
-};
-static AttnGrid attn_grid(AttnArgs& a, int B, int slots, bool may_turn) {
-  const int nblk = a.S / 64;
+// Completes the arguments for workgroups of which `slots` fit the chip; returns the grid (see pair_work and
+// RowSet::init_turns: a.by_turns.turns > 0).
+static int attn_grid(AttnArgs& a, int B, int slots, bool may_turn) {
+  const AttnShape s = attn_shape(B, a.Hh, a.S / 64, slots, may_turn, g_rows_per_wg);
   a.B = B;
-  a.vheads = heads_per_group(nblk, a.Hh);
-  a.rows_per_wg = rows_per_wg(nblk, a.Hh, B, slots);
-  if (may_turn && g_rows_per_wg == 0 && (long long)B * a.Hh < 1 << 20) {
-    const AttnTurns t = attn_turns(B * a.Hh, nblk, slots, a.rows_per_wg);
-    if (t.turns > 0) {
-      a.rows_per_wg = t.turns;
-      a.gz = t.places;
-      a.spread = t.cohorts;
-      a.vheads = t.pairs;
-      return {t.grid, true};
-    }
-  }
-  a.gz = (nblk + a.rows_per_wg - 1) / a.rows_per_wg * a.vheads;
-  const int P = B * (a.Hh / a.vheads);
-  const long long n = (long long)P * a.gz;
-  a.spread = a.rows_per_wg <= 3 && n > kCUs && n <= slots;
-  return {8 * (P / 8 * a.gz + (P % 8 * a.gz + 7) / 8), false};
+  a.vheads = s.vheads;
+  a.rows_per_wg = s.rows_per_wg;
+  a.gz = s.gz;
+  a.spread = s.spread;
+  a.by_turns = s.by_turns;
+  return s.grid;
 }
 
 template <int D, int DT, bool WIDE>
 static hipError_t launch_fwd_t(AttnArgs a, int B, hipStream_t st) {
   ProfScope ps(kKAttnFwd, st);
   constexpr int kNs = D == 64 ? kFwdNs64 : 2, kOcc = D == 64 ? kFwdOcc64 : 2;
-  const AttnGrid grid = attn_grid(a, B, kCUs * kOcc, true);
-  if (grid.turns)
-    hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc, WIDE, true>), dim3(grid.n), dim3(kAT), 0, st, a);
+  const int grid = attn_grid(a, B, kCUs * kOcc, true);
+  if (a.by_turns.turns > 0)
+    hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc, WIDE, true>), dim3(grid), dim3(kAT), 0, st, a);
   else
-    hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc, WIDE, false>), dim3(grid.n), dim3(kAT), 0, st, a);
+    hipLaunchKernelGGL((attn_fwd_bf16<D, DT, kNs, kOcc, WIDE, false>), dim3(grid), dim3(kAT), 0, st, a);
   return hipGetLastError();
 }
 template <int D, int DT>
@@ -1320,29 +1275,29 @@ static hipError_t launch_bwd_t(AttnArgs a, int B, hipStream_t st) {
     if (bwd_in_one(a, D, B)) {
       ProfScope ps(kKAttnDkv, st);
       constexpr int kOcc = kBothOcc(D);
-      const int half = attn_grid(a, B, kCUs * kOcc / 2, false).n;
+      const int half = attn_grid(a, B, kCUs * kOcc / 2, false);
       hipLaunchKernelGGL((attn_bwd_both_bf16<D, DT, 2, kOcc>), dim3(2 * half), dim3(kAT), 0, st, a, half);
       return hipGetLastError();
     }
   {
     ProfScope ps(kKAttnDq, st);
     constexpr int kNs = D == 64 ? kDqNs64 : 2, kOcc = D == 64 ? kDqOcc64 : 2;
-    const AttnGrid grid = attn_grid(a, B, kCUs * kOcc, true);
-    if (grid.turns)
-      hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc, WIDE, true>), dim3(grid.n), dim3(kAT), 0, st, a);
+    const int grid = attn_grid(a, B, kCUs * kOcc, true);
+    if (a.by_turns.turns > 0)
+      hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc, WIDE, true>), dim3(grid), dim3(kAT), 0, st, a);
     else
-      hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc, WIDE, false>), dim3(grid.n), dim3(kAT), 0, st, a);
+      hipLaunchKernelGGL((attn_bwd_dq_bf16<D, DT, kNs, kOcc, WIDE, false>), dim3(grid), dim3(kAT), 0, st, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   {
     ProfScope ps(kKAttnDkv, st);
     constexpr int kNs = D == 64 ? kDkvNs64 : 2, kOcc = D == 64 ? kDkvOcc64 : 2;
-    const AttnGrid grid = attn_grid(a, B, kCUs * kOcc, true);
-    if (grid.turns)
-      hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc, WIDE, true>), dim3(grid.n), dim3(kAT), 0, st, a);
+    const int grid = attn_grid(a, B, kCUs * kOcc, true);
+    if (a.by_turns.turns > 0)
+      hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc, WIDE, true>), dim3(grid), dim3(kAT), 0, st, a);
     else
-      hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc, WIDE, false>), dim3(grid.n), dim3(kAT), 0, st, a);
+      hipLaunchKernelGGL((attn_bwd_dkv_bf16<D, DT, kNs, kOcc, WIDE, false>), dim3(grid), dim3(kAT), 0, st, a);
   }
   return hipGetLastError();
 }

@@ -104,15 +104,39 @@ inline bool bwd_one_launch_pays(int D, long long rows, int nblk, bool causal, do
 }
 
 // ---- which rows of the mask a workgroup takes ----------------------------------------------------
-// Estimate of a launch of `groups` workgroups with r rows each, `slots` of them at a time, in units of one row (see
-// rows_per_wg in attn_bf16.hip).
-inline double attn_rows_cost(int r, long long groups, int slots, int nblk) {
+// Estimate of a launch of `groups` workgroups with r rows each on average, `slots` of them at a time, in units of one row (see
+// attn_rows_per_wg).
+inline double attn_rows_cost(double r, long long groups, int slots, int nblk) {
   const double start = 0.38 * (1 + 16.0 / nblk);
   const long long full = groups / slots, left = groups % slots;
   if (groups <= slots) return (r + start) * (1 + 0.015 * r);
   const double f = (double)left / slots;
   const double part = 0.5 + (full > 1 && f <= 0.5 ? 0.35 : 1.1) * f, last = left == 0 ? 0.0 : part < 1.0 ? part : 1.0;
   return r * (full + last) + start * (full + (left > 0));
+}
+constexpr int kRMax = 8;   // rows of the mask per workgroup, at most
+// Rows per workgroup, unless the caller fixed the number (`forced`): the smallest count with which all workgroups of the
+// launch are resident at once on the chip's `slots` workgroup slots (a causal mask keeps the groups balanced for
+// every count, because slots are filled in pairs k, 2G-1-k), or a smaller one with more workgroups than slots.
+// Those pay a start per round, but the dispatcher hands them out as slots become free, which evens out pairs with
+// long and short lists, and fewer pairs share an L2 at a time.  The estimate (attn_rows_cost), in units of one row: a round costs
+// r rows plus its start, which weighs more where lists are short; a last round that is not full is faster,
+// workgroups being alone on their CUs, and the more so when earlier rounds have spread the starts; a single round
+// lasts 1.5 % longer per row, having nothing to even it out.  Over 173 launches of both head sizes
+// (profiles/attn_rows_sweep.txt) the chosen count is 1.2 % slower than the best one on average, 14 % at worst (12 heads of
+// 2048 tokens, D = 128, all blocks, dK and dV: 61 us with one row, 54 with two); against one round always, forward / dQ /
+// dK and dV take 0.990 / 0.996 / 0.995 of the time with head size 128 and 0.994 / 0.990 / 0.994 with 64, at worst 1.03 /
+// 1.05 / 1.06, the last at 2 x 40 heads of 2048 tokens, 25 % of the blocks, D = 128 (2 rows for 6; with all blocks
+// the same choice takes 0.95 - 1.00).  What it is for: 4 x 32 heads of 2048 tokens, 25 %, D = 128, forward 82 -> 66 us
+// (8 rows -> 4).
+inline int attn_rows_per_wg(int nblk, long long pairs, int slots, int forced) {
+  auto groups = [&](int r) { return (long long)((nblk + r - 1) / r) * pairs; };
+  int r = 1;
+  while (r < kRMax && groups(r) > slots) ++r;
+  for (int q = r - 1; q >= 1; --q)
+    if (attn_rows_cost(q, groups(q), slots, nblk) < attn_rows_cost(r, groups(r), slots, nblk)) r = q;
+  if (forced > 0) r = forced;
+  return r > nblk ? nblk : r;
 }
 // By turns: an XCD's (batch entry, head) pairs are x, x + 8, ..; as many consecutive ones of those as have up to 64 rows together
 // are a cohort, and a workgroup has one row of each of several cohorts, the same number of rows as every other one and about
@@ -129,23 +153,22 @@ struct AttnTurns {
   int turns, places, cohorts, pairs, grid;      // rows per workgroup (0: not by turns), cohorts at a time, of an XCD; pairs of a cohort
 };
 inline AttnTurns attn_turns(int pairs, int nblk, int slots, int rows_per_wg) {
-  AttnTurns best = {0, 0, 0, 0, 0};
-  if (nblk > 64 || pairs < 8 || (long long)pairs * nblk <= slots) return best;      // (a row per workgroup is the least that there is)
-  const int room = slots / 8, per = (pairs + 7) / 8;
-  const int groups = (nblk + rows_per_wg - 1) / rows_per_wg;
-  double least = kTurnsLine * attn_rows_cost(rows_per_wg, (long long)groups * pairs, slots, nblk);
-  for (int V = 64 / nblk; V >= 1; --V) {
-    const int G = V * nblk, Z = room / G;
-    const int cohorts = (per + V - 1) / V, turns = Z > 0 ? (cohorts + Z - 1) / Z : 0;
-    if (turns < 2 || turns > 8) continue;
-    const double cost = attn_rows_cost(turns, 8 * Z * G, slots, nblk);
-    if (cost < least) least = cost, best = {turns, Z, cohorts, V, 8 * Z * G};
+  const AttnTurns none = {0, 0, 0, 0, 0};
+  if (nblk > 64 || pairs < 8 || (long long)pairs * nblk <= slots) return none;      // (a row per workgroup is the least that there is)
+  const int room = slots / 8, per = (pairs + 7) / 8, most = room / nblk;    // places of an XCD, its pairs, those at a time
+  const int turns = (per + most - 1) / most;
+  if (turns > kRMax) return none;
+  const int groups = (nblk + rows_per_wg - 1) / rows_per_wg, grid = 8 * most * nblk;
+  if (attn_rows_cost(turns, grid, slots, nblk) >= kTurnsLine * attn_rows_cost(rows_per_wg, (long long)groups * pairs, slots, nblk)) return none;
+  // the largest cohorts that take no more turns (those of one pair take that many)
+  for (int V = 64 / nblk;; --V) {
+    const int G = V * nblk, Z = room / G, cohorts = (per + V - 1) / V;
+    if (V == 1 || (cohorts + Z - 1) / Z == turns) return {turns, Z, cohorts, V, 8 * Z * G};
   }
-  return best;
 }
 // The rank by length, among the n rows of a cohort, of the row that a place's workgroup r takes in turn k of `turns`, so that
 // the ranks of all turns add up to about the same for every r: up and down by turns, of an odd number the first three by
-// r, n - 1 - 2 r and r + n / 2 modulo n.
+// r; n - 1 - 2 r in the first half, and 2 n - 1 - 2 r, for an even n 2 n - 2 - 2 r, in the second; r + n / 2 and r - (n + 1) / 2.
 LX_HD int turn_rank(int r, int k, int n, int turns) {
   if (turns % 2 == 1 && turns >= 3) {
     const int low = (n + 1) / 2;         // r below: the first half
@@ -154,6 +177,34 @@ LX_HD int turn_rank(int r, int k, int n, int turns) {
     if (k > 2) k -= 3;
   }
   return k % 2 == 0 ? r : n - 1 - r;
+}
+
+// How an attention launch of B * Hh pairs with nblk rows each is laid out, `slots` workgroups at a time.
+struct AttnShape {
+  int rows_per_wg, vheads, gz, spread, grid;      // (see AttnArgs)
+  AttnTurns by_turns;
+};
+// Heads per group of workgroups: as many consecutive heads (4, 2 or 1) as divide the head count
+// and whose rows one wavefront can rank (64 lanes).  The rows of the group are dealt to its
+// workgroups together, so heads with long and with short lists even each other out.
+inline int heads_per_group(int nblk, int heads) {
+  for (int v = 4; v > 1; v /= 2)
+    if (heads % v == 0 && v * nblk <= 64) return v;
+  return 1;
+}
+// may_turn: the kernel can take its rows by turns; forced: rows per workgroup that the caller fixed, 0 otherwise.
+inline AttnShape attn_shape(int B, int Hh, int nblk, int slots, bool may_turn, int forced) {
+  AttnShape a = {};
+  const long long pairs = (long long)B * Hh;
+  a.rows_per_wg = attn_rows_per_wg(nblk, pairs, slots, forced);
+  if (may_turn && forced == 0 && pairs < 1 << 20) a.by_turns = attn_turns((int)pairs, nblk, slots, a.rows_per_wg);
+  a.vheads = heads_per_group(nblk, Hh);
+  a.gz = (nblk + a.rows_per_wg - 1) / a.rows_per_wg * a.vheads;
+  const int P = B * (Hh / a.vheads);
+  const long long n = (long long)P * a.gz;
+  a.spread = a.rows_per_wg <= 3 && n > kCUs && n <= slots;
+  a.grid = a.by_turns.turns > 0 ? a.by_turns.grid : 8 * (P / 8 * a.gz + (P % 8 * a.gz + 7) / 8);
+  return a;
 }
 
 }  // namespace lx

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_plan.h"
 #include "compact_plan.h"
 #include "lx_chip.h"
 
@@ -40,9 +41,10 @@ struct AttnArgs {
   int Hh, S, mask_batch, causal;
   float scale;
   int rows_per_wg;   // rows of the mask per workgroup, set by the launcher
-  int vheads;        // consecutive heads whose rows one group of workgroups shares; by turns: pairs of a cohort; set by the launcher
-  int B, gz;         // batch entries; workgroups of a group, by turns: cohorts at a time on an XCD; set by the launcher
-  int spread;        // 1: the workgroups of an XCD by their length (pair_work); by turns: cohorts of an XCD; set by the launcher
+  int vheads;        // consecutive heads whose rows one group of workgroups shares, set by the launcher
+  int B, gz;         // batch entries, workgroups of a group, set by the launcher
+  int spread;        // 1: the workgroups of an XCD by their length (pair_work), set by the launcher
+  AttnTurns by_turns;      // where its turns are not 0, in the place of rows_per_wg, vheads, gz and spread; set by the launcher
 };
 
 hipError_t launch_compact(const uint8_t*, int, int, int, long long, long long, long long, int*, int*,

@@ -78,6 +78,14 @@ def test_cases_take_that_route(L):
         assert plans(L, B, Hh, S, D), (B, Hh, S, D)
 
 
+def test_choice_takes_little_of_the_host(L):
+    """Short sequences of many heads, whose calls wait for the host: the choice is no search over the cohorts (200 - 400 ns a
+    launch, six times the count of rows per workgroup)."""
+    for pairs, nblk, slots, rows in [(320, 2, 512, 2), (700, 1, 512, 1), (320, 3, 512, 2), (330, 4, 1024, 2)]:
+        turns, count = (min(f(pairs, nblk, slots, rows) for _ in range(50)) for f in (L.turns_ns, L.rows_ns))
+        assert turns <= 2 * count + 10, (pairs, nblk, slots, turns, count)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,Hh,S,D,causal,per_batch,density", CASES)
 def test_same_bits(lx, B, Hh, S, D, causal, per_batch, density):  # noqa: F811
