@@ -138,17 +138,25 @@ inline int attn_rows_per_wg(int nblk, long long pairs, int slots, int forced) {
   if (forced > 0) r = forced;
   return r > nblk ? nblk : r;
 }
-// By turns: an XCD's (batch entry, head) pairs are x, x + 8, ..; as many consecutive ones of those as have up to 64 rows together
-// are a cohort, and a workgroup has one row of each of several cohorts, the same number of rows as every other one and about
+// By turns: an XCD's (batch entry, head) pairs are x, x + 8, ..; the rows, at most 64, of several consecutive ones of those are
+// a cohort, and a workgroup has one row of each of several cohorts, the same number of rows as every other one and about
 // the same number of blocks, all workgroups being resident at once.  The rows of one pair (or four) that a workgroup has
-// otherwise divide evenly only by chance: 2 x 40 heads of 2048 tokens at head size 128 are 5 rows for each of 512 workgroups, but 32
-// rows of a pair do not divide by 5, and by two rows a workgroup they are 2.5 rounds.  Taken where the estimate says a tenth
-// less.  Forward / backward, us, that way / by turns: 2 x 40 of 2048, D = 128, all blocks 130.6 / 357.8 -> 124.3 / 351.0, 25 %
-// 50.8 / 135.6 -> 46.2 / 128.2; 8 x 12 of 1024, no causality, 30 % 36.0 / 97.5 -> 30.3 / 87.0; 8 x 40 of 512, 40 % 32.6 / 88.9 ->
-// 30.3 / 84.7.  34 calls of 320 - 4096 tokens and 10 - 100 % of the blocks for which it is taken, both head sizes: 0.81 - 1.05 of the
-// time, 0.93 on average, backward 0.80 - 1.07 and 0.95; the slower ones are all but one of 10 - 15 %, where a workgroup's
-// lists are too short to even each other out.  Where the estimates are alike, 0.81 - 1.17 either way.
-constexpr double kTurnsLine = 0.92;
+// otherwise divide evenly only by chance: 8 x 33 heads of 256 tokens at head size 128 are two rows for each of 512 workgroups, otherwise
+// 264 workgroups of four rows, CUs with two of them next to CUs with one.
+// The rank of a list says less of its length where most lists have no more than a block, and a launch of several rounds evens
+// out by itself, so it has to promise more than that:
+// - where all workgroups are resident the other way too, a workgroup has fewer rows and the busiest CU a fifth fewer;
+// - where they are several rounds, the estimate (with the rows that a workgroup has on average) says 12 % less, and there are
+//   two workgroups to a CU: four or three (head size 64) even each other out unless they have a row each;
+// - at most five rows: with six and seven the launches took 0.97 of the time, 24 of 152 more than 1.02, up to 1.12.
+// 863 launches of 128 - 4096 tokens, 8 - 40 heads and 1 - 8 batch entries, 10 - 100 % of the blocks, for which it is taken: forward 0.89, dQ
+// 0.90, dK and dV 0.89 of the time on average, 0.72 - 1.09, 23 of them above 1.02, with a block or so per row (profiles/attn_turns_sweep.txt).
+// Of 1450 launches that were estimated 8 % faster, with workgroups of as many rows as the fullest one, 139 took more than 1.02 of
+// the time, up to 1.14.  Where a workgroup has as many rows either way and the busiest CU a fifth fewer: 810 launches 0.97, 190 above
+// 1.02, up to 1.17.  Forward / backward, us, that way / by turns: 2 x 40 of 2048, D = 128, all blocks 130.6 / 357.8 -> 124.3 / 351.0, 25 %
+// 50.8 / 135.6 -> 46.2 / 128.2; 8 x 40 of 512, 40 % 32.6 / 88.9 -> 30.3 / 84.7.
+constexpr int kTurnsMost = 5;
+constexpr double kTurnsBusiest = 0.8, kTurnsRounds = 0.88;
 struct AttnTurns {
   int turns, places, cohorts, pairs, grid;      // rows per workgroup (0: not by turns), cohorts at a time, of an XCD; pairs of a cohort
 };
@@ -157,9 +165,17 @@ inline AttnTurns attn_turns(int pairs, int nblk, int slots, int rows_per_wg) {
   if (nblk > 64 || pairs < 8 || (long long)pairs * nblk <= slots) return none;      // (a row per workgroup is the least that there is)
   const int room = slots / 8, per = (pairs + 7) / 8, most = room / nblk;    // places of an XCD, its pairs, those at a time
   const int turns = (per + most - 1) / most;
-  if (turns > kRMax) return none;
+  if (turns > kTurnsMost) return none;
   const int groups = (nblk + rows_per_wg - 1) / rows_per_wg, grid = 8 * most * nblk;
-  if (attn_rows_cost(turns, grid, slots, nblk) >= kTurnsLine * attn_rows_cost(rows_per_wg, (long long)groups * pairs, slots, nblk)) return none;
+  const long long wgs = (long long)groups * pairs;
+  const double rows = (double)nblk / groups;
+  if (wgs <= slots) {
+    const double busiest = (double)((wgs + kCUs - 1) / kCUs) * rows;
+    if (turns >= rows_per_wg || (double)((grid + kCUs - 1) / kCUs) * pairs * nblk / grid > kTurnsBusiest * busiest) return none;
+  } else if ((rows_per_wg > 1 && slots > 2 * kCUs) ||
+             attn_rows_cost(turns, grid, slots, nblk) > kTurnsRounds * attn_rows_cost(rows, wgs, slots, nblk)) {
+    return none;
+  }
   // the largest cohorts that take no more turns (those of one pair take that many)
   for (int V = 64 / nblk;; --V) {
     const int G = V * nblk, Z = room / G, cohorts = (per + V - 1) / V;
