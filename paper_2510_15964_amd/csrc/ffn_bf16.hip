@@ -136,61 +136,55 @@ __device__ __forceinline__ bool find_work(const int* __restrict__ row_ptr, int r
   return false;
 }
 
-// Items of the sdd kernel as pieces of lists of about equal length (sdd_even): with `per`, the fewest entries for which
-// pieces of at most so many (kEvenLeast .. kEvenMost) fill no more rounds than the longest ones do, a tile's list of n entries
-// falls into k = ceil(n / per) pieces of n / k entries, rounded up or down.  Numbered by halves of the lists as in find_work;
-// an XCD takes its eighth in order.  A list per token tile, up to kEvenTiles of them and 2^16 entries.  Returns false past
-// the end.
+// Items of the sdd kernel as pieces of lists of about equal length (sdd_even, whose arithmetic these scans serve): with `per`,
+// their most entries, a tile's list of n entries falls into k = ceil(n / per) pieces of n / k entries, rounded up or down.
+// Numbered by halves of the lists as in find_work; an XCD takes its eighth in order.  A list per token tile, up to kEvenTiles
+// of them and 2^16 entries.  Returns false past the end.
 __device__ __forceinline__ bool find_piece(const int* __restrict__ row_ptr, int Tt, int w, int nnz_cap, int& tile, int& first,
                                            int& count, int& per) {
   if (w >= sdd_even_grid(Tt, min(row_ptr[Tt], nnz_cap))) return false;      // before the scans
   const int lane = threadIdx.x % kWave;
   auto entries = [&](int i) { return i < Tt ? min(row_ptr[i + 1], nnz_cap) - min(row_ptr[i], nnz_cap) : 0; };
   const bool two = Tt > kWave;
-  const int n0 = entries(two ? 2 * lane : lane), n1 = two ? entries(2 * lane + 1) : 0;
+  EvenLane own = {two ? entries(2 * lane) : entries(lane), two ? entries(2 * lane + 1) : 0};
   constexpr int kPers = kEvenMost - kEvenLeast + 1;
-  int k0[kPers], k1[kPers], sum[(kPers + 1) / 2];     // pieces of this lane's tiles; of all tiles, 16 bits each
+  int sum[(kPers + 1) / 2];     // pieces of all tiles by at most kEvenLeast + i entries, 16 bits each
 #pragma unroll
   for (int i = 0; i < kPers; ++i) {
-    k0[i] = (unsigned)(n0 + kEvenLeast + i - 1) / (unsigned)(kEvenLeast + i);
-    k1[i] = (unsigned)(n1 + kEvenLeast + i - 1) / (unsigned)(kEvenLeast + i);
-    sum[i / 2] = i % 2 ? sum[i / 2] | (k0[i] + k1[i]) << 16 : k0[i] + k1[i];
+    const int k = own.pieces(kEvenLeast + i);
+    sum[i / 2] = i % 2 ? sum[i / 2] | k << 16 : k;
   }
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1)
 #pragma unroll
     for (int i = 0; i < (kPers + 1) / 2; ++i) sum[i] += __shfl_xor(sum[i], d);
-  auto pieces = [&](int i) { return (int)((unsigned)sum[i / 2] >> (i % 2 ? 16 : 0) & 0xFFFFu); };
-  const int room = (pieces(kPers - 1) + kEvenRound - 1) / kEvenRound * kEvenRound;
-  int total = pieces(kPers - 1), k_a = k0[kPers - 1], k_b = k1[kPers - 1];
-  per = kEvenMost;
-#pragma unroll
-  for (int i = kPers - 2; i >= 0; --i)
-    if (pieces(i) <= room) total = pieces(i), k_a = k0[i], k_b = k1[i], per = kEvenLeast + i;
-  const int L = (total + 7) / 8, slot = w / 8;
-  int work = w % 8 * L + slot;
-  if (slot >= L || work >= total) return false;
-  const int h_a = (k_a + 1) / 2, h_b = (k_b + 1) / 2, h = h_a + h_b, k = k_a + k_b;      // first halves
-  int both = h | (k - h) << 16;
+  per = even_per([&](int p) { return (int)((unsigned)sum[(p - kEvenLeast) / 2] >> ((p - kEvenLeast) % 2 ? 16 : 0) & 0xFFFFu); },
+                 [&] {
+                   int k = own.pieces(kEvenShort);
+                   for (int d = 1; d < kWave; d <<= 1) k += __shfl_xor(k, d);
+                   return k;
+                 });
+  own.cut(per);
+  int both = own.firsts() | (own.k0 + own.k1 - own.firsts()) << 16;
+  const int mine = both;
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) {
     const int up = __shfl_up(both, d);
     if (lane >= d) both += up;
   }
-  const int firsts = __shfl(both, kWave - 1) & 0xFFFF;
+  const int all = __shfl(both, kWave - 1), firsts = all & 0xFFFF, total = firsts + (int)((unsigned)all >> 16);
+  int work = even_place(w, total);
+  if (work < 0) return false;
   const bool second = work >= firsts;
   if (second) work -= firsts;
   const int incl = second ? (int)((unsigned)both >> 16) : both & 0xFFFF;
   const int l = __ffsll((long long)__ballot(incl > work)) - 1;
-  work -= __shfl(incl - (second ? k - h : h), l);
-  const int ka = __shfl(k_a, l), ha = __shfl(h_a, l), held = second ? ka - ha : ha;
-  const bool b = work >= held;
-  const int kk = b ? __shfl(k_b, l) : ka, n = b ? __shfl(n1, l) : __shfl(n0, l);
-  int chunk = b ? work - held : work;
-  if (second) chunk += (kk + 1) / 2;
-  tile = __builtin_amdgcn_readfirstlane((two ? 2 * l : l) + (b ? 1 : 0));
-  first = __builtin_amdgcn_readfirstlane(quick_div(chunk * n, kk));
-  count = __builtin_amdgcn_readfirstlane(quick_div((chunk + 1) * n, kk)) - first;
+  work -= __shfl(incl - (second ? (int)((unsigned)mine >> 16) : mine & 0xFFFF), l);
+  const EvenLane at = {__shfl(own.n0, l), __shfl(own.n1, l), __shfl(own.k0, l), __shfl(own.k1, l)};
+  const EvenPiece p = at.piece(second, work);
+  tile = __builtin_amdgcn_readfirstlane((two ? 2 * l : l) + p.odd);
+  first = __builtin_amdgcn_readfirstlane(p.first);
+  count = __builtin_amdgcn_readfirstlane(p.count);
   return true;
 }
 

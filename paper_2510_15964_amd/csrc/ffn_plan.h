@@ -370,8 +370,8 @@ inline bool sdd_halves(int Tt, int gt, int nnz_cap) { return 6.f / 7.f * (float)
 // Lists per group of token tiles, 1 x 4 tiles: whether four workgroups per CU with one stage each (Tile14Lean) run the
 // launch instead of two with two stages.  A workgroup is slower with the one, so it has to pay otherwise:
 // - first product: up to one and a half rounds of two, where the second round is short (four: 0.8 - 1.0 of the time at
-//   525 - 720 items: 8192 tokens, d = 768, 40 % of the blocks 41 -> 33 us, 4096 tokens, d = 1024, 55 % 45 -> 37, 8192
-//   tokens, d = 4096, 8 % 172 -> 162; at 850 and more 1.0 - 1.15);
+//   525 - 720 items: 8192 tokens, d = 768, 40 % of the blocks 41 -> 33 us, 4096 tokens, d = 1024, 55 % 45 -> 37; at 850
+//   and more 1.0 - 1.15; asked after sdd_even);
 // - second product: where an XCD's eighth is whole column chunks of more than 64 token groups, which two per CU would
 //   walk through in more than one round, fetching the chunk's weight rows in each (8192 tokens, d = 2048, 10 / 30 % 50 / 101
 //   -> 43 / 94 us; with parts of chunks or 64 groups 0.98 - 1.11 of the time).  A chunk's rows have to fit an L2 for that, and
@@ -390,14 +390,15 @@ inline bool dsd_lean(int id, int Tt, int gt, int GM, int GN, int nnz_cap, long l
   return 4.f * mean <= (float)GM || (256 * 2 * ldw <= 4 << 20 && GM * GN % (2 * kCUs) != 0);
 }
 
-// First product, a list per token tile: whether it runs by pieces of lists of about equal length, 4 to 8 entries each
+// First product, a list per token tile: whether it runs by pieces of lists of about equal length, 2 to 8 entries each
 // (find_piece), on a 1 x 8 tile of one stage, two workgroups to a CU.  These launches are bound by what misses the L2s, some
 // 6.3 TB/s (8192 tokens, d = 4096, 8 % of the blocks by 1 x 4 tiles: 154 us, 156 without the matrix instructions, 72 without
 // the transfers), and what one workgroup fetches its XCD's others find there only while they keep step along the contraction.
 // They do if a round's workgroups have the same to do: 704 items of up to four entries are two or three to a CU, 1.4 rounds;
 // 489 pieces of up to six, all resident, run the same lists in 110 us.  So the pieces are as short as lets them fill whole
 // rounds of kEvenRound, and all of a launch transfer the same number of lines per step, the missing entries' from the first one
-// (without: 1.02 times the time over 120 launches).  Against the items before, which took their kernel by the model (1 x 4 tiles
+// (without: 1.02 times the time over 120 launches).  At least three entries (with four: 59 launches of 2 - 2.7 entries per workgroup of a
+// round 0.95 of the time of the items before, now 0.88), two where those fit a round (of 15 launches 1.03 with four, now 0.90).  Against the items before, which took their kernel by the model (1 x 4 tiles
 // of one, two or four stages): 154 launches of 768 - 8192 tokens, d = 640 - 5120, 3 - 100 % of the blocks, plain and with the
 // low-rank step, capacities a tenth over the list 0.90 of the time on average, twice the list 0.93, 0.69 at best.  The lines:
 // - at least 2.5 entries per workgroup of a round where d is large and tiles are many (48 tiles on, d >= 3200, 3 entries 0.84 - 0.92), else
@@ -408,10 +409,50 @@ inline bool dsd_lean(int id, int Tt, int gt, int GM, int GN, int nnz_cap, long l
 // - lists, or a loose capacity, of more than half of the blocks only from 97 tiles and d = 3200 on: with so many in common the 1 x 4
 //   tiles keep step as they are (16 - 32 tiles, 60 - 80 %, 1.0 - 1.25), and a short list in a long capacity pays for the workgroups
 //   that find nothing (7000 tokens, 4 %, d = 1792 30 -> 35 us).
-constexpr int kEvenLeast = 4, kEvenMost = 8, kEvenRound = 2 * kCUs;
+constexpr int kEvenLeast = 3, kEvenMost = 8, kEvenRound = 2 * kCUs;
+constexpr int kEvenShort = 2;      // of short lists
 constexpr int kEvenTiles = 128;    // most token tiles: two per lane of the scan
 // Workgroups that hold the pieces of any list of at most nnz_cap entries.
 LX_HD int sdd_even_grid(int Tt, int nnz_cap) { return ceil_div(ceil_div(nnz_cap, kEvenMost) + Tt, kEvenRound) * kEvenRound; }
+// The most entries of a piece: the fewest for which there are no more rounds than with the longest pieces.  pieces(p): pieces of
+// all lists by at most p entries; short_pieces(): by kEvenShort, asked for only if the shortest others fit.
+template <class Pieces, class Short>
+LX_HD int even_per(Pieces pieces, Short short_pieces) {
+  const int room = ceil_div(pieces(kEvenMost), kEvenRound) * kEvenRound;
+  int per = kEvenMost;
+#pragma unroll
+  for (int p = kEvenMost - 1; p >= kEvenLeast; --p)
+    if (pieces(p) <= room) per = p;
+  // (n / 2 pieces or more are 3/2 of n / 3 less one per list, or more)
+  if (per == kEvenLeast && 3 * pieces(kEvenLeast) <= 2 * (room + kEvenTiles) && short_pieces() <= room) per = kEvenShort;
+  return per;
+}
+// The piece of workgroup w out of `total`, -1 past the end: XCD w % 8 takes the w % 8th eighth.
+LX_HD int even_place(int w, int total) {
+  const int L = ceil_div(total, 8), slot = w / 8, work = w % 8 * L + slot;
+  return slot < L && work < total ? work : -1;
+}
+LX_HD int quick_div(int a, int b);
+struct EvenPiece {
+  int odd, first, count;      // 1: of the second of two tiles; entries of that tile's list
+};
+// The lists of one or two tiles, n0 and n1 entries, and the pieces that they fall into.  The pieces are numbered first halves
+// before second ones; a first half is the larger one.
+struct EvenLane {
+  int n0, n1, k0, k1;
+  static LX_HD int of(int n, int per) { return (int)((unsigned)(n + per - 1) / (unsigned)per); }
+  LX_HD int pieces(int per) const { return of(n0, per) + of(n1, per); }
+  LX_HD void cut(int per) { k0 = quick_div(n0 + per - 1, per), k1 = quick_div(n1 + per - 1, per); }
+  LX_HD int firsts() const { return (k0 + 1) / 2 + (k1 + 1) / 2; }
+  // number `work` of the lane's first halves, or of its second ones
+  LX_HD EvenPiece piece(bool second, int work) const {
+    const int held = second ? k0 / 2 : (k0 + 1) / 2;
+    const bool b = work >= held;
+    const int k = b ? k1 : k0, n = b ? n1 : n0, chunk = (b ? work - held : work) + (second ? (k + 1) / 2 : 0);
+    const int first = quick_div(chunk * n, k);
+    return {b ? 1 : 0, first, quick_div((chunk + 1) * n, k) - first};
+  }
+};
 inline bool sdd_even(int Tt, int gt, int d, int nnz_cap, int blocks, int want) {
   if (want != 0 || gt != 1 || Tt < 2 || Tt > kEvenTiles || nnz_cap >= 1 << 16) return false;
   const float n = 6.f / 7.f * (float)nnz_cap;

@@ -41,3 +41,15 @@ def dsd(L, Tt, gt, d, cap, part_bytes=0, want=0):
     """(tile, pieces) of the second product."""
     p = C.c_int(0)
     return TILES[L.dsd_tile(Tt, gt, d, cap, part_bytes, want, C.byref(p))], p.value
+
+
+def even_items(L, lens, cap):
+    """The pieces of lists of these lengths, capacity cap, as their workgroups find them: ([(tile, first, entries)], most entries)."""
+    ptr = [0]
+    for n in lens:
+        ptr.append(ptr[-1] + int(n))
+    room = cap // 8 + len(lens) + 512
+    out, per = (C.c_int * (3 * room))(), C.c_int(0)
+    grid = L.even_items((C.c_int * len(ptr))(*ptr), len(lens), cap, room, out, C.byref(per))
+    assert grid <= room
+    return [tuple(out[3 * w:3 * w + 3]) for w in range(grid) if out[3 * w] >= 0], per.value

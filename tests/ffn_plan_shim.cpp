@@ -46,6 +46,43 @@ int dsd_by(int Tt, int gt, int d, int F, int nnz_cap, long long part_bytes, int 
   *pieces = r.by == kByQuarters || r.by == kByMix ? 1 : r.plan.pieces;
   return r.by;
 }
+// The first product by pieces, as ffn_sdd_even's workgroups find theirs: workgroups launched for a list with that capacity, and per
+// workgroup tile, first entry, entries in out (room for cap of them; tile -1: none); *per: the most entries of a piece.
+int even_items(const int* row_ptr, int Tt, int cap, int room, int* out, int* per) {
+  auto clip = [&](int v) { return v < cap ? v : cap; };
+  auto entries = [&](int i) { return i < Tt ? clip(row_ptr[i + 1]) - clip(row_ptr[i]) : 0; };
+  const bool two = Tt > 64;
+  EvenLane lane[64];
+  for (int l = 0; l < 64; ++l) lane[l] = {two ? entries(2 * l) : entries(l), two ? entries(2 * l + 1) : 0, 0, 0};
+  auto pieces = [&](int p) {
+    int k = 0;
+    for (const EvenLane& l : lane) k += l.pieces(p);
+    return k;
+  };
+  *per = even_per(pieces, [&] { return pieces(kEvenShort); });
+  int firsts = 0, total = 0;
+  for (EvenLane& l : lane) l.cut(*per), firsts += l.firsts(), total += l.k0 + l.k1;
+  const int grid = sdd_even_grid(Tt, cap), found = sdd_even_grid(Tt, clip(row_ptr[Tt]));
+  for (int w = 0; w < grid && w < room; ++w) {
+    int* o = out + 3 * w;
+    o[0] = -1;
+    int work = w < found ? even_place(w, total) : -1;
+    if (work < 0) continue;
+    const bool second = work >= firsts;
+    if (second) work -= firsts;
+    for (int l = 0; l < 64; ++l) {
+      const int mine = second ? lane[l].k0 + lane[l].k1 - lane[l].firsts() : lane[l].firsts();
+      if (work >= mine) {
+        work -= mine;
+        continue;
+      }
+      const EvenPiece p = lane[l].piece(second, work);
+      o[0] = (two ? 2 * l : l) + p.odd, o[1] = p.first, o[2] = p.count;
+      break;
+    }
+  }
+  return grid;
+}
 // The predictor by quarters of its tiles (where d is no multiple of 128).
 int predict_quarters(int items, int d) { return quarters_pay(items, d, 0); }
 // 1: the gradients of the LoRA matrices by quadrants, 0: by parts.
