@@ -391,19 +391,26 @@ inline bool dsd_lean(int id, int Tt, int gt, int GM, int GN, int nnz_cap, long l
 }
 
 // First product, a list per token tile: whether it runs by pieces of lists of about equal length, 2 to 8 entries each
-// (find_piece), on a 1 x 8 tile of one stage, two workgroups to a CU.  These launches are bound by what misses the L2s, some
-// 6.3 TB/s (8192 tokens, d = 4096, 8 % of the blocks by 1 x 4 tiles: 154 us, 156 without the matrix instructions, 72 without
+// (find_piece), on a 1 x 8 tile of one stage, two workgroups to a CU.  By 1 x 4 tiles these launches are bound by what misses the L2s,
+// some 6.3 TB/s (8192 tokens, d = 4096, 8 % of the blocks: 154 us, 156 without the matrix instructions, 72 without
 // the transfers), and what one workgroup fetches its XCD's others find there only while they keep step along the contraction.
 // They do if a round's workgroups have the same to do: 704 items of up to four entries are two or three to a CU, 1.4 rounds;
-// 489 pieces of up to six, all resident, run the same lists in 110 us.  So the pieces are as short as lets them fill whole
+// 489 pieces of up to six, all resident, run the same lists in 110 us, where they fetch 56 KB a step for at most 64 x 384 outputs, 16 TB/s of
+// what L2-resident loops reach 15 - 19 of.  So the pieces are as short as lets them fill whole
 // rounds of kEvenRound, and all of a launch transfer the same number of lines per step, the missing entries' from the first one
 // (without: 1.02 times the time over 120 launches).  At least three entries (with four: 59 launches of 2 - 2.7 entries per workgroup of a
-// round 0.95 of the time of the items before, now 0.88), two where those fit a round (of 15 launches 1.03 with four, now 0.90).  Against the items before, which took their kernel by the model (1 x 4 tiles
-// of one, two or four stages): 154 launches of 768 - 8192 tokens, d = 640 - 5120, 3 - 100 % of the blocks, plain and with the
-// low-rank step, capacities a tenth over the list 0.90 of the time on average, twice the list 0.93, 0.69 at best.  The lines:
-// - at least 2.5 entries per workgroup of a round where d is large and tiles are many (48 tiles on, d >= 3200, 3 entries 0.84 - 0.92), else
-//   more items than one round of 1 x 4 tiles holds (d = 2048, 3 entries 1.0 - 1.1, 16 tiles, d = 5120 0.96 - 1.05; 4 entries and
-//   more 0.77 - 0.95);
+// round 0.95 of the time of the items before, now 0.88), two where those fit a round (of 15 launches 1.03 with four, now 0.90).
+// Against the items before, which took their kernel by the model (1 x 4 tiles
+// of one, two or four stages), for what the lines below take of calls drawn from 2 - 128 tiles, d = 512 - 5120, 3 - 100 % of the blocks,
+// plain and with the low-rank step, up and gate product (profiles/ffn_pieces_sweep.txt): 860 launches, of capacities a
+// tenth over the list 0.85 of the time on average, 0.64 - 1.08, 20 of 660 above 1.02; 1.5 and 2 times the list 0.89, up to 1.06; every block 0.81, up to 0.95.
+// The lines:
+// - more items than one round of 1 x 4 tiles holds (d = 2048, 3 entries per workgroup of a round 1.0 - 1.1, 16 tiles, d = 5120 0.96 - 1.05;
+//   4 entries and more 0.77 - 0.95), which is also where the pieces have five entries;
+// - where d is large and tiles are many (48 on, d >= 3200) also what pieces of three hold in one round (0.81 - 0.97 from 2.5
+//   entries on).  Not what takes pieces of four: 98 launches 0.98, those with columns that most tiles list 1.00, up to 1.14;
+// - there from 90 tiles on not the longest pieces in one round: the waiting for nine lines outweighs what is saved where tiles have many
+//   columns in common anyway (19 launches with planted support 1.02, up to 1.19; with independent columns 0.90 - 0.97);
 // - below d = 3200 not where the longest pieces just need a second round, which short ones then fill (7.5 entries:
 //   0.95 - 1.15);
 // - lists, or a loose capacity, of more than half of the blocks only from 97 tiles and d = 3200 on: with so many in common the 1 x 4
@@ -455,11 +462,15 @@ struct EvenLane {
 };
 inline bool sdd_even(int Tt, int gt, int d, int nnz_cap, int blocks, int want) {
   if (want != 0 || gt != 1 || Tt < 2 || Tt > kEvenTiles || nnz_cap >= 1 << 16) return false;
-  const float n = 6.f / 7.f * (float)nnz_cap;
+  const float n = 6.f / 7.f * (float)nnz_cap;      // (a list that fills a capacity of a tenth over the mean has 1.06 n)
+  auto pieces = [&](int per) { return n / (float)per + (float)Tt * (float)(per - 1) / (float)(2 * per); };
   if (n > 0.5f * (float)blocks && (Tt <= 96 || d < 3200)) return false;
-  if (d >= 3200 && Tt >= 48) return n >= 2.5f * kEvenRound;
+  if (d >= 3200 && Tt >= 48) {
+    if (n < 2.5f * kEvenRound || (pieces(3) > kEvenRound && pieces(4) <= 0.97f * kEvenRound)) return false;
+    return Tt < 90 || pieces(kEvenMost - 1) <= 0.95f * kEvenRound || pieces(kEvenMost) > 0.99f * kEvenRound;
+  }
   if (d < 3200 && n / kEvenMost + 0.44f * (float)Tt > 0.9f * kEvenRound && n < 4.3f * 2 * kEvenRound) return false;
-  return n >= 3.5f * kEvenRound && sdd_items_about(kTileInfo[kT14], Tt, gt, (int)n) > kEvenRound;
+  return sdd_items_about(kTileInfo[kT14], Tt, gt, (int)n) > kEvenRound;
 }
 
 // ---- which kernel a launch runs by -----------------------------------------------------------

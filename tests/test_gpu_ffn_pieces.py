@@ -95,6 +95,26 @@ def test_cases_take_that_route(L):
         assert ffn_plan.sdd_by(L, Tt, 1, d, cap, Tt * Fb, 1, cap)[0] != "pieces"
 
 
+# token tiles, d, share of the blocks, room for a tenth more: by pieces or not, for what the rule says of them
+RULES = [
+    (128, 4096, 0.077, True),
+    (74, 3712, 0.077, True),        # pieces of three fill one round: 0.91 - 0.95 of the time
+    (63, 3904, 0.111, False),       # of four: 1.05 - 1.10 with lists that have much in common, 0.96 with others
+    (58, 3776, 0.111, False),
+    (89, 3712, 0.077, False),
+    (64, 4096, 0.13, True),
+    (116, 4160, 0.111, False),      # the longest pieces in one round: 1.19
+    (112, 4992, 0.13, True),        # two rounds
+]
+
+
+@pytest.mark.parametrize("Tt,d,share,by", RULES)
+def test_rule(L, Tt, d, share, by):
+    Fb = d // 16
+    cap = int(1.1 * share * Tt * Fb) + 64
+    assert (ffn_plan.sdd_by(L, Tt, 1, d, cap, Tt * Fb, 0, cap)[0] == "pieces") == by
+
+
 CUT = (None, 100, 640, 60, 2600, 0.8)      # the lists have some 3500 entries
 
 
