@@ -220,7 +220,7 @@ struct RowSet {
   // The rows are those of `heads` consecutive heads, h0 .. (nb1 blocks each, their list rows one
   // after the other from head_row0), ranked and dealt together: heads whose lists differ in
   // length then share their workgroups instead of each keeping G of its own.
-  // tab_lds: 5 * kRMax ints of LDS; contains a barrier: call from uniform control flow
+  // tab_lds: 4 * kRMax ints of LDS (init_turns: 5); contains a barrier: call from uniform control flow
   __device__ __forceinline__ void init(int* tab_lds, const int* __restrict__ row_ptr,
                                        int cap, int head_row0, int nb1, int heads, int h0,
                                        const uint8_t* __restrict__ head_active, int g, int G, int R,
@@ -741,7 +741,7 @@ __device__ __forceinline__ bool pair_work(const AttnArgs& a, int w, PairWork& p)
 template <int D, int DT, int NS, int OCC, bool WIDE, bool TURNS>
 __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   __shared__ __attribute__((aligned(2 * 64 * D))) uint16_t st[NS][2 * 64 * D];   // stage: K tile, V tile
-  __shared__ int rowtab[5 * kRMax];
+  __shared__ int rowtab[TURNS ? 5 * kRMax : 4 * kRMax];
   __shared__ int btab[kTabInts];
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;   // bytes
   const int nqb = a.S / 64;
@@ -775,6 +775,20 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   using Step = std::conditional_t<WIDE, unsigned long long, uint32_t>;
   SlotOffset heads;
   heads.init(rows, [&](int b, int hh) { return 2 * base_of(b, hh); });
+  // the element offset of this lane's own row in block blk of a slot, and of its head's statistics.  (Without TURNS from the head's number: from the
+  // table's registers the machine code is another one and layer-sized launches of head size 64 were no faster, 0.99 - 1.02.)
+  auto row_of = [&](int slot, int blk) -> long long {
+    if constexpr (TURNS)
+      return heads.at(slot, blk, (Step)(128 * a.ss)) / 2 + ql * a.ss;
+    else
+      return base_of(rows.b0, rows.head(slot)) + (long long)(blk * 64 + ql) * a.ss;
+  };
+  auto stats_of = [&](int slot) -> long long {
+    if constexpr (TURNS)
+      return (long long)rows.pair(slot) * a.S;
+    else
+      return stat_of(rows.b0, rows.head(slot));
+  };
   // tensor p's tile of an entry
   auto tile_of = [&](const uint16_t* p, int e) {
     return reinterpret_cast<const char*>(p) + heads.at(entry_slot(e), entry_blk(e), (Step)(128 * a.ss));
@@ -799,8 +813,8 @@ __global__ __launch_bounds__(kAT, OCC) void attn_fwd_bf16(const AttnArgs a) {
   auto row_begin = [&](int stage, int e) {
     qb = entry_blk(e);
     const int slot = entry_slot(e);
-    qoff = heads.at(slot, qb, (Step)(128 * a.ss)) / 2 + ql * a.ss;
-    soff = (long long)rows.pair(slot) * a.S + qb * 64 + ql;
+    qoff = row_of(slot, qb);
+    soff = stats_of(slot) + qb * 64 + ql;
     const uint32_t q0 = (st_addr + stage * kStage) | own_off;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) qf[kk] = lds_read16(q0 ^ tile_off<D>(0, 32 * kk));
@@ -879,15 +893,15 @@ __device__ __forceinline__ float dot8(uint4 a, uint4 b, float sum) {
     sum += to_f32<DT>(x[q] & 0xFFFFu) * to_f32<DT>(y[q] & 0xFFFFu) + to_f32<DT>(x[q] >> 16) * to_f32<DT>(y[q] >> 16);
   return sum;
 }
-template <int D, int NS>
+template <int D, int NS, bool TURNS>
 struct DqLds {                       // (aligned to a tile where it is declared)
   uint16_t st[NS][2 * 64 * D];       // stage: K, V (or Q, dO; or O) tile
   float slse[NS][4][16];             // stage, wavefront: LSE of its 16 own rows
-  int rowtab[5 * kRMax];
+  int rowtab[TURNS ? 5 * kRMax : 4 * kRMax];
   int btab[kTabInts];
 };
 template <int D, int DT, int NS, bool WIDE, bool TURNS>
-__device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, NS>& sh) {
+__device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, NS, TURNS>& sh) {
   auto& st = sh.st;
   auto& slse = sh.slse;
   constexpr uint32_t kStage = 4 * 64 * D, kTile = 2 * 64 * D;
@@ -925,6 +939,19 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   using Step = std::conditional_t<WIDE, unsigned long long, uint32_t>;
   SlotOffset heads;
   heads.init(rows, [&](int b, int hh) { return 2 * base_of(b, hh); });
+  // the element offset of this lane's own row in block blk of a slot, and of its head's statistics
+  auto row_of = [&](int slot, int blk) -> long long {
+    if constexpr (TURNS)
+      return heads.at(slot, blk, (Step)(128 * a.ss)) / 2 + ql * a.ss;
+    else
+      return base_of(rows.b0, rows.head(slot)) + (long long)(blk * 64 + ql) * a.ss;
+  };
+  auto stats_of = [&](int slot) -> long long {
+    if constexpr (TURNS)
+      return (long long)rows.pair(slot) * a.S;
+    else
+      return stat_of(rows.b0, rows.head(slot));
+  };
   // tensor p's tile of an entry
   auto tile_of = [&](const uint16_t* p, int e) {
     return reinterpret_cast<const char*>(p) + heads.at(entry_slot(e), entry_blk(e), (Step)(128 * a.ss));
@@ -947,9 +974,10 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   // the row's O tile, needed once for Delta = rowsum(dO . O), and the LSE of its 64 queries
   // (lanes 0-15 of wavefront w bring those of its own rows 16w .. 16w+15)
   auto issue_aux = [&](int stage, int e) {
+    const long long stats = stats_of(entry_slot(e));
     const int blk = entry_blk(e);
     dma.issue(st_addr + stage * kStage, tile_of(a.O, e));
-    if (lane < 16) dma4(a.LSEin + (long long)rows.pair(entry_slot(e)) * a.S + blk * 64 + ql, slse_addr + stage * 256 + wave * 64);
+    if (lane < 16) dma4(a.LSEin + stats + blk * 64 + ql, slse_addr + stage * 256 + wave * 64);
   };
   auto issue_blk = [&](int stage, int e) {
     const uint32_t dst = st_addr + stage * kStage;
@@ -959,8 +987,8 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
   auto row_begin = [&](int stage, int e) {
     qb = entry_blk(e);
     const int slot = entry_slot(e);
-    qoff = heads.at(slot, qb, (Step)(128 * a.ss)) / 2 + ql * a.ss;
-    soff = (long long)rows.pair(slot) * a.S + qb * 64 + ql;
+    qoff = row_of(slot, qb);
+    soff = stats_of(slot) + qb * 64 + ql;
     const uint32_t q0 = (st_addr + stage * kStage) | own_off;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) {
@@ -1038,7 +1066,7 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnArgs& a, int w, DqLds<D, N
 }
 template <int D, int DT, int NS, int OCC, bool WIDE, bool TURNS>
 __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
-  __shared__ __attribute__((aligned(2 * 64 * D))) DqLds<D, NS> sh;
+  __shared__ __attribute__((aligned(2 * 64 * D))) DqLds<D, NS, TURNS> sh;
   attn_bwd_dq<D, DT, NS, WIDE, TURNS>(a, blockIdx.x, sh);
 }
 
@@ -1047,15 +1075,15 @@ __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dq_bf16(const AttnArgs a) {
 // query blocks, with the queries' -LSE*log2(e) and Delta beside them.  ALONE: O is streamed too and they are made here,
 // as the query side makes them, so that the two sides need not follow each other
 // ---------------------------------------------------------------------------
-template <int D, int NS, bool ALONE>
+template <int D, int NS, bool ALONE, bool TURNS>
 struct DkvLds {                      // (aligned to a tile where it is declared)
   uint16_t st[NS][(ALONE ? 3 : 2) * 64 * D];      // stage: Q, dO (or K, V), O tile
   float sstat[NS][4][32];            // stage, query tile: -LSE*log2e [16], Delta [16]
-  int rowtab[5 * kRMax];
+  int rowtab[TURNS ? 5 * kRMax : 4 * kRMax];
   int btab[kTabInts];
 };
 template <int D, int DT, int NS, bool WIDE, bool ALONE, bool TURNS>
-__device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D, NS, ALONE>& sh) {
+__device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D, NS, ALONE, TURNS>& sh) {
   auto& st = sh.st;
   auto& sstat = sh.sstat;
   constexpr uint32_t kTile = 2 * 64 * D, kStage = (ALONE ? 3 : 2) * kTile;
@@ -1090,6 +1118,13 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
   using Step = std::conditional_t<WIDE, unsigned long long, uint32_t>;
   SlotOffset heads;
   heads.init(rows, [&](int b, int hh) { return 2 * base_of(b, hh); });
+  // the element offset of this lane's own row in block blk of a slot
+  auto row_of = [&](int slot, int blk) -> long long {
+    if constexpr (TURNS)
+      return heads.at(slot, blk, (Step)(128 * a.ss)) / 2 + kl * a.ss;
+    else
+      return base_of(rows.b0, rows.head(slot)) + (long long)(blk * 64 + kl) * a.ss;
+  };
   // tensor p's tile of an entry
   auto tile_of = [&](const uint16_t* p, int e) {
     return reinterpret_cast<const char*>(p) + heads.at(entry_slot(e), entry_blk(e), (Step)(128 * a.ss));
@@ -1120,7 +1155,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
   };
   auto row_begin = [&](int stage, int e) {
     kb = entry_blk(e);
-    koff = heads.at(entry_slot(e), kb, (Step)(128 * a.ss)) / 2 + kl * a.ss;
+    koff = row_of(entry_slot(e), kb);
     const uint32_t k0 = (st_addr + stage * kStage) | own_off;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) {
@@ -1203,19 +1238,19 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnArgs& a, int w, DkvLds<D,
 }
 template <int D, int DT, int NS, int OCC, bool WIDE, bool TURNS>
 __global__ __launch_bounds__(kAT, OCC) void attn_bwd_dkv_bf16(const AttnArgs a) {
-  __shared__ __attribute__((aligned(2 * 64 * D))) DkvLds<D, NS, false> sh;
+  __shared__ __attribute__((aligned(2 * 64 * D))) DkvLds<D, NS, false, TURNS> sh;
   attn_bwd_dkv<D, DT, NS, WIDE, false, TURNS>(a, blockIdx.x, sh);
 }
 
 // Both sides in one launch (bwd_in_one): the first `half` workgroups take the key side, which is the longer one.
 template <int D, int DT, int NS, int OCC>
 __global__ __launch_bounds__(kAT, OCC) void attn_bwd_both_bf16(const AttnArgs a, int half) {
-  __shared__ __attribute__((aligned(2 * 64 * D))) DkvLds<D, NS, true> sh;
-  static_assert(sizeof(DqLds<D, NS>) <= sizeof(sh), "shared memory");
+  __shared__ __attribute__((aligned(2 * 64 * D))) DkvLds<D, NS, true, false> sh;
+  static_assert(sizeof(DqLds<D, NS, false>) <= sizeof(sh), "shared memory");
   if ((int)blockIdx.x < half)
     attn_bwd_dkv<D, DT, NS, false, true, false>(a, blockIdx.x, sh);
   else
-    attn_bwd_dq<D, DT, NS, false, false>(a, blockIdx.x - half, reinterpret_cast<DqLds<D, NS>&>(sh));
+    attn_bwd_dq<D, DT, NS, false, false>(a, blockIdx.x - half, reinterpret_cast<DqLds<D, NS, false>&>(sh));
 }
 
 
