@@ -148,13 +148,13 @@ inline int attn_rows_per_wg(int nblk, long long pairs, int slots, int forced) {
 // - where all workgroups are resident the other way too, a workgroup has fewer rows and the busiest CU a fifth fewer;
 // - where they are several rounds, the estimate (with the rows that a workgroup has on average) says 12 % less, and there are
 //   two workgroups to a CU: four or three (head size 64) even each other out unless they have a row each;
-// - at most five rows: with six and seven the launches took 0.97 of the time, 24 of 152 more than 1.02, up to 1.12.
-// 863 launches of 128 - 4096 tokens, 8 - 40 heads and 1 - 8 batch entries, 10 - 100 % of the blocks, for which it is taken: forward 0.89, dQ
-// 0.90, dK and dV 0.89 of the time on average, 0.72 - 1.09, 23 of them above 1.02, with a block or so per row (profiles/attn_turns_sweep.txt).
-// Of 1450 launches that were estimated 8 % faster, with workgroups of as many rows as the fullest one, 139 took more than 1.02 of
-// the time, up to 1.14.  Where a workgroup has as many rows either way and the busiest CU a fifth fewer: 810 launches 0.97, 190 above
-// 1.02, up to 1.17.  Forward / backward, us, that way / by turns: 2 x 40 of 2048, D = 128, all blocks 130.6 / 357.8 -> 124.3 / 351.0, 25 %
-// 50.8 / 135.6 -> 46.2 / 128.2; 8 x 40 of 512, 40 % 32.6 / 88.9 -> 30.3 / 84.7.
+// - at most five rows: with six and seven the launches took 0.97 of the time, 26 of 152 more than 1.02, up to 1.12.
+// 755 launches of 64 - 4096 tokens, 8 - 40 heads and 1 - 8 batch entries, 10 - 100 % of the blocks, for which it is taken, on the same
+// buffers: forward 0.89, dQ 0.90, dK and dV 0.90 of the time on average, 0.72 - 1.11, 29 of them above 1.02, with a block or so per row
+// (profiles/attn_turns_sweep.txt).  Of 695 more that were estimated 8 % faster, with workgroups of as many rows as the fullest one, 132 took more
+// than 1.02 of the time, up to 1.16, 0.965 on average; of 810 with as many rows in a workgroup either way and a fifth fewer on the busiest CU
+// 190, up to 1.17, 0.97 on average.  Forward / backward, us, that way / by turns: 2 x 40 of 2048, D = 128, all blocks 130.6 / 357.8 -> 124.3 /
+// 351.0, 25 % 50.8 / 135.6 -> 46.2 / 128.2; 8 x 40 of 512, 40 % 32.6 / 88.9 -> 30.3 / 84.7.
 constexpr int kTurnsMost = 5;
 constexpr double kTurnsBusiest = 0.8, kTurnsRounds = 0.88;
 struct AttnTurns {

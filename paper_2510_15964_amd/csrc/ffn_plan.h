@@ -402,15 +402,17 @@ inline bool dsd_lean(int id, int Tt, int gt, int GM, int GN, int nnz_cap, long l
 // round 0.95 of the time of the items before, now 0.88), two where those fit a round (of 15 launches 1.03 with four, now 0.90).
 // Against the items before, which took their kernel by the model (1 x 4 tiles
 // of one, two or four stages), for what the lines below take of calls drawn from 2 - 128 tiles, d = 512 - 5120, 3 - 100 % of the blocks,
-// plain and with the low-rank step, up and gate product (profiles/ffn_pieces_sweep.txt): 860 launches, of capacities a
-// tenth over the list 0.85 of the time on average, 0.64 - 1.08, 20 of 660 above 1.02; 1.5 and 2 times the list 0.89, up to 1.06; every block 0.81, up to 0.95.
+// plain and with the low-rank step, up and gate product, on the same buffers (profiles/ffn_pieces_sweep.txt): with a capacity a tenth over
+// the list 0.83 of the time where all columns are as likely (1116 launches, 10 of them above 1.02, 1.06 at most) and 0.89 where they
+// differ as the support of trained layers does (548, 23 above 1.02, up to 1.13); 1.5 and 2 times the list 0.88 (756, 66, 1.09), beyond 0.84 (276, 4, 1.14).
 // The lines:
 // - more items than one round of 1 x 4 tiles holds (d = 2048, 3 entries per workgroup of a round 1.0 - 1.1, 16 tiles, d = 5120 0.96 - 1.05;
 //   4 entries and more 0.77 - 0.95), which is also where the pieces have five entries;
 // - where d is large and tiles are many (48 on, d >= 3200) also what pieces of three hold in one round (0.81 - 0.97 from 2.5
-//   entries on).  Not what takes pieces of four: 98 launches 0.98, those with columns that most tiles list 1.00, up to 1.14;
-// - there from 90 tiles on not the longest pieces in one round: the waiting for nine lines outweighs what is saved where tiles have many
-//   columns in common anyway (19 launches with planted support 1.02, up to 1.19; with independent columns 0.90 - 0.97);
+//   entries on).  Not what takes pieces of four: 1.02 and up to 1.14 where most tiles list the same columns, 0.96 elsewhere;
+// - there from 90 tiles on not the longest pieces in one round: the waiting for nine lines a step outweighs what is saved where tiles have many
+//   columns in common anyway (1.02 of the time, up to 1.19; with independent columns 0.85 - 0.97).  The two lines leave out 256 launches with
+//   a tenth of room, 1.00 of the time where columns differ, 80 of 186 above 1.02, and 0.90 where they do not;
 // - below d = 3200 not where the longest pieces just need a second round, which short ones then fill (7.5 entries:
 //   0.95 - 1.15);
 // - lists, or a loose capacity, of more than half of the blocks only from 97 tiles and d = 3200 on: with so many in common the 1 x 4
@@ -474,8 +476,9 @@ inline bool sdd_even(int Tt, int gt, int d, int nnz_cap, int blocks, int want) {
 }
 
 // ---- which kernel a launch runs by -----------------------------------------------------------
-// kByPieces: pieces of lists (find_piece); kBySet: a kernel that holds several tiles and takes the one that suits the list (SddSet, with `mix` its SddMix), kByMix: 4 x 4
-// tiles and narrower ones for a rest, kByLean: the 1 x 4 tile of one stage, kByTile: the plan's own tile.
+// kByPieces: pieces of lists (find_piece); kBySet: a kernel that holds several tiles and takes the one that suits the list (SddSet,
+// with `mix` its SddMix), kByMix: 4 x 4 tiles and narrower ones for a rest, kByLean: the 1 x 4 tile of one stage, kByTile: the plan's
+// own tile.
 enum Route { kNothing, kByQuarters, kBySet, kByMix, kByLean, kByTile, kByPieces };
 struct SddRoute {
   Route by;
