@@ -395,8 +395,8 @@ inline bool dsd_lean(int id, int Tt, int gt, int GM, int GN, int nnz_cap, long l
 // some 6.3 TB/s (8192 tokens, d = 4096, 8 % of the blocks: 154 us, 156 without the matrix instructions, 72 without
 // the transfers), and what one workgroup fetches its XCD's others find there only while they keep step along the contraction.
 // They do if a round's workgroups have the same to do: 704 items of up to four entries are two or three to a CU, 1.4 rounds;
-// 489 pieces of up to six, all resident, run the same lists in 110 us, where they fetch 56 KB a step for at most 64 x 384 outputs, 16 TB/s of
-// what L2-resident loops reach 15 - 19 of.  So the pieces are as short as lets them fill whole
+// 467 pieces of up to six, all resident, fetch 56 KB a step for at most 64 x 384 outputs each, 0.63 GB of misses in all where the items had 0.95, and
+// take 134 us for 164 on one box, three fifths of their wavefronts' time in waits (12.5 TB/s from the L2s).  So the pieces are as short as lets them fill whole
 // rounds of kEvenRound, and all of a launch transfer the same number of lines per step, the missing entries' from the first one
 // (without: 1.02 times the time over 120 launches).  At least three entries (with four: 59 launches of 2 - 2.7 entries per workgroup of a
 // round 0.95 of the time of the items before, now 0.88), two where those fit a round (of 15 launches 1.03 with four, now 0.90).
